@@ -112,7 +112,7 @@ hipError_t launch_quantize_alternating(const float* W, int64_t V, int64_t n, int
 // Scales are alpha[q][N][K / g] (g = group size along K, a multiple of 32 that divides K; g = K is the row-wise
 // case alpha[q][N]); the scale gradient has the same shape.
 
-// ---- any-shape kernels (plain vector ALU; need no workspace) --------------------------------
+// ---- any-shape kernels (fp64 matrix cores; need no workspace) --------------------------------
 hipError_t launch_fwd_generic(const uint32_t* packed, const float* alpha, const void* x, int dtype, int64_t T,
                               int64_t N, int64_t K, int64_t g, int q, void* y, hipStream_t st);
 hipError_t launch_bwd_input_generic(const uint32_t* packed, const float* alpha, const void* dy, int dtype,

@@ -1,0 +1,48 @@
+"""The any-shape kernels (fp64 matrix cores; fp32 activations, or bf16 without a workspace) at the edges of their tiles.
+
+All sums are fp64, so a result differs from the oracle's fp64 value by its own rounding: half a unit in
+the last place, 2^-24 of the value for fp32 outputs (24 significant bits) and 2^-8 for bf16 ones (8 significant bits;
+they are rounded to fp32 first, hence the 1 %); the normalised error divides by the largest value, which
+can only make it smaller."""
+import pytest
+
+from _util import make_case, nmax_err, packed_to_dev, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f32": 1.05 * 2.0 ** -24, "bf16": 1.01 * 2.0 ** -8}
+
+# T, N, K, g, q, q_train
+EDGES = [
+    (1, 1, 32, 32, 1, 1),          # smallest of everything: seven of eight waves without work
+    (15, 17, 96, 32, 8, 5),        # one row beyond a tile, three groups
+    (16, 16, 256, 256, 2, 2),      # whole tiles, one word per wave
+    (17, 31, 288, 96, 3, 3),       # nine words over eight waves, groups of three words
+    (32, 1001, 512, 32, 4, 4),     # more groups (16) than waves, odd row count
+    (33, 33, 1056, 352, 3, 1),     # groups over two waves each
+    (100, 1100, 64, 64, 3, 3),     # two token tiles per workgroup in the forward
+    (130, 4100, 32, 32, 2, 1),     # four token tiles per workgroup in the forward
+    (70, 40, 3072, 3072, 1, 1),    # two token tiles x a whole word in the input gradient
+    (8, 72, 2560, 64, 4, 2),       # forty groups, one wave each
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T,N,K,g,q,q_train", EDGES)
+def test_generic_kernels_are_correctly_rounded(oracle, dtype, T, N, K, g, q, q_train):
+    import torch
+    import paper_2210_03858_amd as bcq
+    _, alpha, planes, packed, x, dy = make_case(1, "out", T, N, K, q, dtype, oracle, extra=T + N, g=g)
+    d_packed, d_alpha = packed_to_dev(packed), to_dev(alpha.reshape(q, N, K // g))
+    d_x, d_dy = to_dev(x, dtype), to_dev(dy, dtype)
+    rowwise_small = dtype == "bf16" and g == K and T < 32  # kernels of their own without a workspace
+    a_or = alpha.reshape(q, N) if g == K else alpha
+    dx = bcq.bcq_linear_bwd_input_grouped(d_packed, d_alpha, d_dy, g)
+    assert nmax_err(to_host(dx), oracle.bwd_input(a_or, planes, dy)) <= TOL[dtype]
+    if not rowwise_small:
+        y = bcq.bcq_linear_fwd_grouped(d_packed, d_alpha, d_x, g)
+        da = bcq.bcq_linear_bwd_alpha_grouped(d_packed, d_x, d_dy, g, q_train=q_train)
+        assert nmax_err(to_host(y), oracle.fwd(a_or, planes, x)) <= TOL[dtype]
+        ref = oracle.bwd_alpha(planes, x, dy, q_train=q_train, grad_scale=1.0, g=g)
+        assert nmax_err(to_host(da).reshape(ref.shape), ref) <= TOL["f32"]
+    torch.cuda.synchronize()
