@@ -2,9 +2,8 @@
 // then `iters` rounds of
 //   (1) alpha <- (B^T B)^{-1} B^T w      least-squares refit of the q scales of one vector (Eq. ap4),
 //   (2) every element takes the sign pattern whose level sum_i +-alpha_i is nearest to its weight.
-// One 256-thread workgroup per vector (a row, or one length-g group of a row).  The vector (fp32) and one byte of
-// sign pattern per element stay in LDS for all rounds, so W is read from HBM once.  This is one-time PTQ work:
-// the kernel is written for reproducibility, not speed.
+// One workgroup of one to four waves per vector (a row, or one length-g group of a row), specialised by q.  The vector
+// (fp32) and one byte of sign pattern per element stay in LDS for all rounds, so W is read from HBM once.
 //
 // Arithmetic: every sum, the Cholesky solve and the level comparison are fp64; alpha is rounded to fp32 once at
 // the end.  The loop stops early at a fixed point (round (2) changed nothing) and stops BEFORE a refit whose
@@ -12,174 +11,300 @@
 // keeping the current pair.  Ties between two levels go to the larger level, ties between equal levels to the
 // larger pattern index (bit i of the pattern = plane i is +1).  Only the ORDER of the fp64 sums over the
 // elements is free.
+//
+// What bounds it: a round is a chain of two barriers, a cross-lane fp64 sum, the solve (about a dozen dependent fp64
+// divisions and roots at q = 3) and 2^q distances per element.  Therefore a round makes ONE pass over the elements (the
+// re-assignment and the next round's sums together), the Gram matrix is counted in integers from the pattern bytes
+// (its entries are n - 2 * disagreements, exact), only wave 0 solves, and the levels are sorted so that a distance
+// costs one subtraction, one strict comparison and its selects.  Four elements per lane, so that vectors of at most
+// 256 elements (groups) take one wave and no cross-wave step.  Measured: 1024 x 1024, q = 3, 15 rounds 735 -> 86 us
+// (a kernel for every q reduced 36 fp64 sums per round over four waves and solved in all of them).
 #include "bcq_internal.h"
 
 namespace bcq {
 
-constexpr int ALT_THREADS = 256;
-constexpr int ALT_NRED = 8 + 28;  // right-hand side (q) + strict lower triangle of the Gram matrix (q (q - 1) / 2)
+constexpr int ALT_MAX_WAVES = 4;
 
-// Sum of `cnt` doubles per thread over the workgroup; every thread returns with all totals (same order in all).
-__device__ __forceinline__ void block_sum(double* vals, int cnt, double* scratch /* [4][ALT_NRED] */) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int i = 0; i < cnt; ++i) {
-        double s = vals[i];
+// fp64 / integer sum over the wave; every lane returns with it
+__device__ __forceinline__ double wave_sum(double s) {
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-        vals[i] = s;
-    }
-    __syncthreads();  // scratch of the previous call has been read by everyone
-    if (lane == 0)
-        for (int i = 0; i < cnt; ++i) scratch[wave * ALT_NRED + i] = vals[i];
-    __syncthreads();
-    for (int i = 0; i < cnt; ++i)
-        vals[i] = (scratch[i] + scratch[ALT_NRED + i]) + (scratch[2 * ALT_NRED + i] + scratch[3 * ALT_NRED + i]);
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+    return s;
+}
+__device__ __forceinline__ uint32_t wave_sum(uint32_t s) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += (uint32_t)__shfl_xor((int)s, off);
+    return s;
 }
 
-__global__ __launch_bounds__(ALT_THREADS) void alternating_kernel(const float* __restrict__ W, int64_t V, int n, int q,
-                                                                  int iters, float* __restrict__ alpha,
-                                                                  uint32_t* __restrict__ packed,
-                                                                  int8_t* __restrict__ planes,
-                                                                  int* __restrict__ status_word) {
+template <int Q>
+struct AltShared {
+    static constexpr int PAIRS = Q * (Q - 1) / 2, LEVELS = 1 << Q;
+    double rhs[ALT_MAX_WAVES][Q];                             // partial B^T w (greedy start: [0] = partial |residual|)
+    double alpha[Q];
+    double raw[LEVELS], level[LEVELS];                        // by pattern; in descending order
+    uint32_t disagree[ALT_MAX_WAVES][(PAIRS + 1) / 2 + 1];    // two 16-bit counts per word
+    uint32_t changed[ALT_MAX_WAVES];
+    uint32_t stop;
+    uint8_t pattern[LEVELS];                                  // of the sorted levels
+};
+
+template <int Q>
+__global__ __launch_bounds__(64 * ALT_MAX_WAVES) void alternating_kernel(const float* __restrict__ W, int64_t V, int n,
+                                                                         int iters, float* __restrict__ alpha,
+                                                                         uint32_t* __restrict__ packed,
+                                                                         int8_t* __restrict__ planes,
+                                                                         int* __restrict__ status_word) {
+    using Shared = AltShared<Q>;
+    constexpr int PAIRS = Shared::PAIRS, LEVELS = Shared::LEVELS, PW = (PAIRS + 1) / 2;
     extern __shared__ __attribute__((aligned(16))) unsigned char alt_smem[];
-    double* scratch = reinterpret_cast<double*>(alt_smem);                 // [4][ALT_NRED]
-    double* lv = scratch + 4 * ALT_NRED;                                    // [256] levels of the current alpha
-    float* w = reinterpret_cast<float*>(lv + 256);                          // [n]
-    uint8_t* code = reinterpret_cast<uint8_t*>(w + n);                      // [n]
-    const int tid = threadIdx.x;
+    Shared& sh = *reinterpret_cast<Shared*>(alt_smem);
+    float4* w4 = reinterpret_cast<float4*>(alt_smem + (sizeof(Shared) + 15) / 16 * 16);  // [n / 4]
+    uint32_t* code4 = reinterpret_cast<uint32_t*>(w4 + n / 4);                           // [n / 4], a pattern per byte
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6;
+    const int quads = n / 4;
     const int64_t v = blockIdx.x;
-    const float* wrow = W + v * (int64_t)n;
-    for (int k = tid; k < n; k += ALT_THREADS) w[k] = wrow[k];
-    __syncthreads();
+    const float4* wrow = reinterpret_cast<const float4*>(W + v * (int64_t)n);
+
+    // waves' partial sums, in wave order
+    auto total_rhs = [&](int i) {
+        double s = sh.rhs[0][i];
+        for (int u = 1; u < waves; ++u) s += sh.rhs[u][i];
+        return s;
+    };
 
     // ---- greedy start: plane i takes the sign of the residual w - sum_{j<i} alpha_j b_j (each element's residual
-    // is rebuilt from its pattern so far, by the same chain of fp64 subtractions), alpha_i = fp32(mean |residual|)
-    double a[8];
+    // is rebuilt from its pattern so far, by the same chain of fp64 subtractions), alpha_i = fp32(mean |residual|).
+    // A lane only touches its own quads until the packed words are formed.
+    double a[Q];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) a[i] = 0.0;
-    for (int i = 0; i < q; ++i) {
+    for (int i = 0; i < Q; ++i) a[i] = 0.0;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
         double s = 0.0;
-        for (int k = tid; k < n; k += ALT_THREADS) {
-            const uint8_t c = (i == 0) ? (uint8_t)0 : code[k];
-            double r = (double)w[k];
-            for (int j = 0; j < i; ++j) r = ((c >> j) & 1) ? r - a[j] : r + a[j];
-            s += fabs(r);
-            code[k] = (uint8_t)(c | ((r >= 0.0 ? 1u : 0u) << i));
+        for (int k = tid; k < quads; k += blockDim.x) {
+            float4 x;
+            if (i == 0) {
+                x = wrow[k];
+                w4[k] = x;
+            } else {
+                x = w4[k];
+            }
+            const float xs[4] = {x.x, x.y, x.z, x.w};
+            uint32_t c = (i == 0) ? 0u : code4[k];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                double r = (double)xs[e];
+#pragma unroll
+                for (int j = 0; j < i; ++j) r = ((c >> (8 * e + j)) & 1u) ? r - a[j] : r + a[j];
+                s += fabs(r);
+                c |= (r >= 0.0 ? 1u : 0u) << (8 * e + i);
+            }
+            code4[k] = c;
         }
-        block_sum(&s, 1, scratch);
+        s = wave_sum(s);
+        if (i) __syncthreads();  // the previous plane's partial sums have been read
+        if (lane == 0) sh.rhs[wave][0] = s;
+        __syncthreads();
+        s = total_rhs(0);
         if (i == 0 && tid == 0 && status_word && !(fabs(s) <= 1.79769313486231570e308)) atomicAdd(status_word, 1);
         a[i] = (double)(float)(s / (double)n);
     }
     __syncthreads();
 
-    const int levels = 1 << q;
-    for (int it = 0; it < iters; ++it) {
-        // ---- (1) Eq. ap4: right-hand side B^T w and Gram matrix B^T B (diagonal = n), summed over the workgroup
-        double red[ALT_NRED];
+    // right-hand side B^T w of this wave and its counts of disagreeing signs, from the patterns c of four elements
+    double rhs[Q];
+    uint32_t dis[PAIRS + 1];
+    auto clear_sums = [&]() {
 #pragma unroll
-        for (int i = 0; i < ALT_NRED; ++i) red[i] = 0.0;
-        for (int k = tid; k < n; k += ALT_THREADS) {
-            const uint8_t c = code[k];
-            const double x = (double)w[k];
-            int p = 8;
+        for (int i = 0; i < Q; ++i) rhs[i] = 0.0;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                if (i < q) {
-                    red[i] += ((c >> i) & 1) ? x : -x;
+        for (int p = 0; p < PAIRS; ++p) dis[p] = 0u;
+    };
+    auto add_sums = [&](const double (&x)[4], uint32_t c) {
+        int p = 0;
 #pragma unroll
-                    for (int j = 0; j < i; ++j) red[p + j] += (((c >> i) ^ (c >> j)) & 1) ? -1.0 : 1.0;
-                }
-                p += i;
-            }
+        for (int i = 0; i < Q; ++i) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) rhs[i] += ((c >> (8 * e + i)) & 1u) ? x[e] : -x[e];
+#pragma unroll
+            for (int j = 0; j < i; ++j) dis[p++] += __popc(((c >> i) ^ (c >> j)) & 0x01010101u);
         }
-        block_sum(red, ALT_NRED, scratch);
-        // Cholesky of the Gram matrix, every thread on its own copy (identical values in all threads)
-        double L[8][8], y[8];
-        bool singular = false;
+    };
+    auto publish_sums = [&]() {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if (j < q && !singular) {
-                double d = (double)n;
-                for (int p = 0; p < j; ++p) d -= L[j][p] * L[j][p];
-                if (!(d > 1e-9 * (double)n)) {
-                    singular = true;
-                } else {
-                    L[j][j] = sqrt(d);
+        for (int i = 0; i < Q; ++i) {
+            const double s = wave_sum(rhs[i]);
+            if (lane == 0) sh.rhs[wave][i] = s;
+        }
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        if (i > j && i < q) {
-                            double s = red[8 + i * (i - 1) / 2 + j];
+        for (int p = 0; p < PW; ++p) {  // a count is at most n <= 16384: two fit one word
+            const uint32_t s = wave_sum(dis[2 * p] + ((2 * p + 1 < PAIRS ? dis[2 * p + 1] : 0u) << 16));
+            if (lane == 0) sh.disagree[wave][p] = s;
+        }
+    };
+    if (iters > 0) {
+        clear_sums();
+        for (int k = tid; k < quads; k += blockDim.x) {
+            const float4 xf = w4[k];
+            const double x[4] = {(double)xf.x, (double)xf.y, (double)xf.z, (double)xf.w};
+            add_sums(x, code4[k]);
+        }
+        publish_sums();
+        __syncthreads();
+    }
+
+    for (int it = 0; it < iters; ++it) {
+        // ---- (1) Eq. ap4, by wave 0: Cholesky of the Gram matrix B^T B (diagonal = n), all lanes on the same numbers
+        if (wave == 0) {
+            double red[Q], L[Q][Q], y[Q];
+#pragma unroll
+            for (int i = 0; i < Q; ++i) red[i] = total_rhs(i);
+            bool singular = false;
+#pragma unroll
+            for (int j = 0; j < Q; ++j) {
+                if (!singular) {
+                    double d = (double)n;
+#pragma unroll
+                    for (int p = 0; p < j; ++p) d -= L[j][p] * L[j][p];
+                    if (!(d > 1e-9 * (double)n)) {
+                        singular = true;
+                    } else {
+                        L[j][j] = sqrt(d);
+#pragma unroll
+                        for (int i = j + 1; i < Q; ++i) {
+                            const int pr = i * (i - 1) / 2 + j;
+                            uint32_t cnt = 0u;
+                            for (int u = 0; u < waves; ++u) cnt += (sh.disagree[u][pr >> 1] >> (16 * (pr & 1))) & 0xFFFFu;
+                            double s = (double)(n - 2 * (int)cnt);
+#pragma unroll
                             for (int p = 0; p < j; ++p) s -= L[i][p] * L[j][p];
                             L[i][j] = s / L[j][j];
                         }
                     }
                 }
             }
-        }
-        if (singular) break;  // uniform: all threads hold the same numbers
+            if (!singular) {  // uniform: all lanes hold the same numbers
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if (i < q) {
-                double s = red[i];
-                for (int p = 0; p < i; ++p) s -= L[i][p] * y[p];
-                y[i] = s / L[i][i];
-            }
-        }
+                for (int i = 0; i < Q; ++i) {
+                    double s = red[i];
 #pragma unroll
-        for (int i = 7; i >= 0; --i) {
-            if (i < q) {
-                double s = y[i];
-                for (int p = i + 1; p < q; ++p) s -= L[p][i] * a[p];
-                a[i] = s / L[i][i];
-            }
-        }
-        // ---- (2) levels of the new alpha, then the nearest level for every element
-        __syncthreads();  // lv of the previous round has been read by everyone
-        for (int c = tid; c < levels; c += ALT_THREADS) {
-            double s = 0.0;
-            for (int i = 0; i < q; ++i) s += ((c >> i) & 1) ? a[i] : -a[i];
-            lv[c] = s;
-        }
-        __syncthreads();
-        int changed = 0;
-        for (int k = tid; k < n; k += ALT_THREADS) {
-            const double x = (double)w[k];
-            int best = levels - 1;
-            double bl = lv[best], bd = fabs(x - bl);
-            for (int c = levels - 2; c >= 0; --c) {
-                const double l = lv[c], d = fabs(x - l);
-                if (d < bd || (d == bd && l > bl)) {
-                    best = c;
-                    bd = d;
-                    bl = l;
+                    for (int p = 0; p < i; ++p) s -= L[i][p] * y[p];
+                    y[i] = s / L[i][i];
+                }
+#pragma unroll
+                for (int i = Q - 1; i >= 0; --i) {
+                    double s = y[i];
+#pragma unroll
+                    for (int p = i + 1; p < Q; ++p) s -= L[p][i] * a[p];
+                    a[i] = s / L[i][i];
+                }
+                // levels of the new alpha, sorted by (level, pattern) downwards.  The slots are filled in pattern order
+                // first: with non-finite levels the ranks need not be a permutation.
+                for (int c = lane; c < LEVELS; c += 64) {
+                    double s = 0.0;
+#pragma unroll
+                    for (int i = 0; i < Q; ++i) s += ((c >> i) & 1) ? a[i] : -a[i];
+                    sh.raw[c] = s;
+                    sh.level[LEVELS - 1 - c] = s;
+                    sh.pattern[LEVELS - 1 - c] = (uint8_t)c;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // one wave's LDS instructions execute in order
+                for (int c = lane; c < LEVELS; c += 64) {
+                    const double own = sh.raw[c];
+                    int rank = 0;
+#pragma unroll 8
+                    for (int o = 0; o < LEVELS; ++o) {
+                        const double l = sh.raw[o];
+                        rank += (l > own || (!(l < own) && o > c)) ? 1 : 0;
+                    }
+                    sh.level[rank] = own;
+                    sh.pattern[rank] = (uint8_t)c;
                 }
             }
-            if ((uint8_t)best != code[k]) {
-                code[k] = (uint8_t)best;
-                changed = 1;
-            }
+            if (lane == 0) sh.stop = singular ? 1u : 0u;
         }
-        if (!__syncthreads_or(changed)) break;
+        __syncthreads();
+        if (sh.stop) break;
+        // ---- (2) the nearest level for every element: in descending order the first of the smallest distances is the
+        // one the tie rules ask for.  The next round's sums are formed from the new pattern in the same pass.
+        clear_sums();
+        uint32_t diff = 0u;
+        for (int k = tid; k < quads; k += blockDim.x) {
+            const float4 xf = w4[k];
+            const double x[4] = {(double)xf.x, (double)xf.y, (double)xf.z, (double)xf.w};
+            double bd[4];
+            int best[4];
+            const double l0 = sh.level[0];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                bd[e] = fabs(x[e] - l0);
+                best[e] = 0;
+            }
+#pragma unroll 8
+            for (int c = 1; c < LEVELS; ++c) {
+                const double l = sh.level[c];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double d = fabs(x[e] - l);
+                    const bool nearer = d < bd[e];
+                    bd[e] = nearer ? d : bd[e];
+                    best[e] = nearer ? c : best[e];
+                }
+            }
+            uint32_t c4 = 0u;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) c4 |= (uint32_t)sh.pattern[best[e]] << (8 * e);
+            diff |= c4 ^ code4[k];
+            code4[k] = c4;
+            add_sums(x, c4);
+        }
+        const bool wave_changed = __any(diff != 0u);
+        if (lane == 0) sh.changed[wave] = wave_changed ? 1u : 0u;
+        publish_sums();
+        __syncthreads();
+        uint32_t changed = 0u;
+        for (int u = 0; u < waves; ++u) changed |= sh.changed[u];
+        if (!changed) break;
     }
     __syncthreads();
 
     // ---- outputs: alpha[i][v], packed[i][v][n / 32], planes[i][v][n]
     const int nw = n / 32;
-    if (tid < q) alpha[(int64_t)tid * V + v] = (float)a[tid];
-    for (int i = 0; i < q; ++i) {
-        for (int wq = tid; wq < nw; wq += ALT_THREADS) {
-            uint32_t word = 0u;
-#pragma unroll 8
-            for (int j = 0; j < 32; ++j) word |= (uint32_t)((code[32 * wq + j] >> i) & 1) << j;
-            packed[((int64_t)i * V + v) * nw + wq] = word;
-        }
-        if (planes)
-            for (int k = tid; k < n; k += ALT_THREADS)
-                planes[((int64_t)i * V + v) * n + k] = ((code[k] >> i) & 1) ? (int8_t)1 : (int8_t)-1;
+    if (tid == 0) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) alpha[(int64_t)i * V + v] = (float)a[i];
+    }
+    for (int idx = tid; idx < Q * nw; idx += blockDim.x) {
+        const int i = idx / nw, wq = idx % nw;
+        uint32_t word = 0u;
+#pragma unroll
+        for (int b = 0; b < 8; ++b)  // bits 0, 8, 16, 24 of a pattern quad -> a nibble
+            word |= (((((code4[8 * wq + b] >> i) & 0x01010101u) * 0x01020408u) >> 24) & 0xFu) << (4 * b);
+        packed[((int64_t)i * V + v) * nw + wq] = word;
+    }
+    if (planes) {
+        uint32_t* out = reinterpret_cast<uint32_t*>(planes);
+        for (int i = 0; i < Q; ++i)
+            for (int k = tid; k < quads; k += blockDim.x)  // a byte per element: 1 -> 0x01, 0 -> 0xFF
+                out[((int64_t)i * V + v) * quads + k] = ~(((code4[k] >> i) & 0x01010101u) * 0xFEu);
     }
 }
 
 __global__ void alt_zero_word_kernel(int* p) { *p = 0; }
+
+template <int Q>
+static hipError_t launch_q(const float* W, int64_t V, int n, int iters, float* alpha, uint32_t* packed, int8_t* planes,
+                           int* status_word, hipStream_t st) {
+    const size_t lds = (sizeof(AltShared<Q>) + 15) / 16 * 16 + (size_t)n * 5;
+    static LdsLimit limit;
+    hipError_t e = limit.ensure((const void*)alternating_kernel<Q>, lds);
+    if (e != hipSuccess) return e;
+    const int waves = n <= 256 ? 1 : n <= 512 ? 2 : ALT_MAX_WAVES;  // four elements per lane and pass
+    BCQ_LAUNCH((alternating_kernel<Q>), dim3((unsigned)V), dim3(64 * waves), lds, st, W, V, n, iters, alpha, packed,
+                       planes, status_word);
+    return hipGetLastError();
+}
 
 hipError_t launch_quantize_alternating(const float* W, int64_t V, int64_t n, int q, int iters, float* alpha,
                                        uint32_t* packed, int8_t* planes, int* status_word, hipStream_t st) {
@@ -188,13 +313,16 @@ hipError_t launch_quantize_alternating(const float* W, int64_t V, int64_t n, int
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const size_t lds = (size_t)(4 * ALT_NRED + 256) * sizeof(double) + (size_t)n * 5;
-    static LdsLimit limit;
-    hipError_t ea = limit.ensure((const void*)alternating_kernel, lds);
-    if (ea != hipSuccess) return ea;
-    BCQ_LAUNCH(alternating_kernel, dim3((unsigned)V), dim3(ALT_THREADS), lds, st, W, V, (int)n, q, iters, alpha,
-                       packed, planes, status_word);
-    return hipGetLastError();
+    switch (q) {
+        case 1: return launch_q<1>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
+        case 2: return launch_q<2>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
+        case 3: return launch_q<3>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
+        case 4: return launch_q<4>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
+        case 5: return launch_q<5>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
+        case 6: return launch_q<6>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
+        case 7: return launch_q<7>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
+        default: return launch_q<8>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
+    }
 }
 
 }  // namespace bcq

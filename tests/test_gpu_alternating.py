@@ -93,3 +93,10 @@ def test_alternating_gpt2_medium_layer(bcq, oracle):
     """One full (h, h) layer of the GPT-2-medium block, q = 3, 15 rounds."""
     W = synth.weights(2, "out", 1024, 1024)
     _check(bcq, oracle, W, 3)
+
+
+@pytest.mark.parametrize("q,N,K,g", [(3, 9, 288, None), (2, 7, 512, None), (6, 5, 544, None), (7, 4, 1056, None),
+                                     (1, 3, 32, None), (4, 3, 2080, None), (3, 2, 8192, 256)])
+def test_alternating_wave_counts_and_plane_counts(bcq, oracle, q, N, K, g):
+    """One, two and four waves per vector with partly idle waves, every specialisation by q, same bar as above."""
+    _check(bcq, oracle, synth.weights(1, "out", N, K, extra=11 * K + q), q, g=g)
