@@ -1,0 +1,329 @@
+// Forward of the BCQ linear layer for a few hundred tokens at most, in one kernel (bf16 in, fp32 accumulate, q <= 4).
+//
+// AlphaTuning Eq. 2 as one contraction with What = sum_i alpha_i B_i rounded once to bf16 (Eq. 1), like the two-kernel
+// path of bcq_mfma.hip, but What never reaches memory: every wave expands the sign planes of its 32 rows straight into
+// the registers of v_mfma_f32_32x32x16_bf16 and multiplies them with all the tokens of its tile.  At these token counts
+// the two-kernel path is bound by writing and re-reading 16 bits per weight, here a weight costs q bits.
+//
+// Expansion by table: within a scale group a row has only 2^q different weights, in pairs of opposite sign, so the
+// 2^(q - 1) <= 8 positive-last-plane values fit the eight bytes that v_perm_b32 selects from (low bytes and high bytes
+// apart).  Selectors for four columns at a time are bits s, s + 8, s + 16, s + 24 of the planes, XNORed with the last plane, whose
+// complement is the sign.  2.6 (q = 3) to 3.2 (q = 4) vector operations per weight instead of about 3 q + 0.5 for signed sums,
+// so that from 64 tokens on the matrix instructions take longer than the expansion.  The table is the same chain of
+// fp32 sums and one rounding as the other paths use, negation commutes with both: the same weights bit for bit.
+//
+// Split: a workgroup owns 32 rows x 32 TT tokens; its W waves take runs of 128 columns in turn and add their tiles
+// through LDS in wave order (deterministic).  Up to 32 tokens are read from their rows; more are first rewritten in
+// operand order, because a wave's 16-byte pieces of 32 rows would touch 32 cache lines per load (256 tokens of
+// 10240 x 2560: 80 us from the rows, 41 us in order).  What bounds it: up to 32 tokens the planes' scattered rows and launch
+// latency (6144 x 2048, groups of 128, 4 tokens: 26 -> 9 us against two kernels), above that the activation fragments,
+// which every 32 rows read again from L2 through the vector memory path.
+#include "bcq_internal.h"
+
+namespace bcq {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 fu_bf16x8;
+typedef __attribute__((ext_vector_type(16))) float fu_f32x16;
+typedef __attribute__((ext_vector_type(4))) uint32_t fu_u32x4;
+typedef __attribute__((ext_vector_type(4))) float fu_f32x4;
+typedef __attribute__((ext_vector_type(2))) __bf16 fu_bf16x2;
+typedef __attribute__((ext_vector_type(2))) float fu_f32x2;
+
+__device__ __forceinline__ uint32_t fu_pack(float lo, float hi) {
+    const fu_f32x2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, fu_bf16x2));
+}
+
+// The positive-last-plane weights of one row and scale group: bit i of the index = plane i is +1, i < Q - 1.
+template <int Q>
+struct LevelTable {
+    uint32_t lo[2], hi[2];  // low and high bytes of the bf16 values, four to a word
+    __device__ __forceinline__ void build(const float (&a)[Q]) {
+        constexpr int E = 1 << (Q - 1);
+        float v[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int cc = c < E ? c : 0;
+            float s = 0.f;
+#pragma unroll
+            for (int i = 0; i < Q; ++i) s += (i == Q - 1 || ((cc >> i) & 1)) ? a[i] : -a[i];
+            v[c] = s;
+        }
+        uint32_t p[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) p[c] = fu_pack(v[2 * c], v[2 * c + 1]);
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            lo[w] = __builtin_amdgcn_perm(p[2 * w + 1], p[2 * w], 0x06040200u);
+            hi[w] = __builtin_amdgcn_perm(p[2 * w + 1], p[2 * w], 0x07050301u);
+        }
+    }
+};
+
+// 32 signs of each plane -> 32 bf16 weights: frag[2 j + sub] = columns 16 j + 8 sub .. + 7 of the 32
+template <int Q>
+__device__ __forceinline__ void expand32(const uint32_t (&w)[Q], const LevelTable<Q>& t, fu_u32x4 (&frag)[4]) {
+    const uint32_t neg = ~w[Q - 1];
+    uint32_t c[Q > 1 ? Q - 1 : 1];
+#pragma unroll
+    for (int i = 0; i + 1 < Q; ++i) c[i] = w[i] ^ neg;
+    uint32_t even = 0u, odd = 0u;  // two-bit codes of the even and the odd columns
+    if constexpr (Q >= 3) {
+        even = (c[0] & 0x55555555u) | ((c[1] & 0x55555555u) << 1);
+        odd = ((c[0] >> 1) & 0x55555555u) | (c[1] & 0xAAAAAAAAu);
+    }
+    uint32_t ab[8], cd[8];  // columns (s, s + 8) and (s + 16, s + 24)
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        uint32_t sel = 0u;
+        if constexpr (Q == 2) sel = (c[0] >> s) & 0x01010101u;
+        if constexpr (Q >= 3) sel = (((s & 1) ? odd : even) >> (s & 6)) & 0x03030303u;
+        if constexpr (Q == 4) sel |= (s >= 2 ? c[2] >> (s - 2) : c[2] << (2 - s)) & 0x04040404u;
+        const uint32_t l = __builtin_amdgcn_perm(t.lo[1], t.lo[0], sel);
+        const uint32_t h = __builtin_amdgcn_perm(t.hi[1], t.hi[0], sel) ^ ((neg << (7 - s)) & 0x80808080u);
+        ab[s] = __builtin_amdgcn_perm(h, l, 0x05010400u);
+        cd[s] = __builtin_amdgcn_perm(h, l, 0x07030602u);
+    }
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        frag[0][p] = __builtin_amdgcn_perm(ab[2 * p + 1], ab[2 * p], 0x05040100u);
+        frag[1][p] = __builtin_amdgcn_perm(ab[2 * p + 1], ab[2 * p], 0x07060302u);
+        frag[2][p] = __builtin_amdgcn_perm(cd[2 * p + 1], cd[2 * p], 0x05040100u);
+        frag[3][p] = __builtin_amdgcn_perm(cd[2 * p + 1], cd[2 * p], 0x07060302u);
+    }
+}
+
+// Activations -> the order the matrix instruction reads them in: for every 32-token tile, 32-column word and half slice
+// one contiguous KiB, lane (t, h) holding columns 16 h + 8 sub .. + 7 of the word.  Tokens beyond T become zeros.
+// A wave takes 8 tokens x 128 bytes: whole lines in, 128-byte runs out.
+__global__ __launch_bounds__(256) void order_act_kernel(const bf16_t* __restrict__ x, int64_t T, int64_t K,
+                                                        fu_u32x4* __restrict__ xfrag) {
+    const int lane = threadIdx.x & 63;
+    const int64_t Kw = K / 32, pairs = (Kw + 1) / 2;
+    const int64_t job = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // (eight tokens, two words)
+    const int64_t t = (job / pairs) * 8 + (lane & 7), w = (job % pairs) * 2 + (lane >> 5);
+    const int chunk = (lane >> 3) & 3;
+    if (w >= Kw || t >= (T + 31) / 32 * 32) return;
+    fu_u32x4 v = {0u, 0u, 0u, 0u};
+    if (t < T) v = *reinterpret_cast<const fu_u32x4*>(x + t * K + 32 * w + 8 * chunk);
+    xfrag[(((t / 32) * Kw + w) * 2 + (chunk & 1)) * 64 + (t % 32) + 32 * (chunk >> 1)] = v;
+}
+
+// GROUPED: group-wise scales (the table follows the group); else one table per row.
+// ORDERED: x is the output of order_act_kernel; else row-major.
+template <int Q, int TT, int W, bool GROUPED, bool ORDERED>
+__global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __restrict__ packed,
+                                                           const float* __restrict__ alpha, const bf16_t* __restrict__ x,
+                                                           bf16_t* __restrict__ y, int64_t T, int64_t N, int64_t K,
+                                                           int64_t g) {
+    __shared__ fu_f32x4 part[2][W][4][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 31, h = lane >> 5;
+    const int64_t n0 = (int64_t)blockIdx.x * 32, t0 = (int64_t)blockIdx.y * (32 * TT);
+    const int64_t n = n0 + col < N ? n0 + col : N - 1;  // rows and tokens beyond the edge are computed, never stored
+    const int Kw = (int)(K / 32), G = (int)(K / g), gw = (int)(g / 32);
+    const int units = (Kw + 3) / 4;
+
+    const uint32_t* prow[Q];
+    const float* arow[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        prow[i] = packed + ((int64_t)i * N + n) * Kw;
+        arow[i] = alpha + ((int64_t)i * N + n) * G;
+    }
+    // of a 32-column word, lane half h contracts over columns 16 h .. 16 h + 15
+    const bf16_t* xrow[TT];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+        if (ORDERED) {
+            const int64_t tile = t0 / 32 + tt, tiles = (T + 31) / 32;
+            xrow[tt] = x + (tile < tiles ? tile : tiles - 1) * K * 32 + lane * 8;
+        } else {
+            const int64_t t = t0 + tt * 32 + col;
+            xrow[tt] = x + (t < T ? t : T - 1) * K + 16 * h;
+        }
+    }
+    fu_f32x16 acc[TT];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[tt][v] = 0.f;
+
+    // In flight per wave: the planes (and scales of group-wise calls) D units ahead, the activations XW words ahead.
+    // One token tile: one unit, so that four waves fit a SIMD (two units ahead: 8.7 -> 12 us for 6144 x 2048 at 4 tokens).
+    constexpr int D = TT == 1 ? 1 : 2, XW = TT == 2 ? 4 : 2;
+    uint32_t bits[D][Q][4];
+    float a[D][2][Q];  // [unit][pair of words]
+    auto load_bits = [&](int u, int buf) {
+        if (4 * u + 4 <= Kw) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) __builtin_memcpy(bits[buf][i], prow[i] + 4 * u, 16);
+        } else {
+#pragma unroll
+            for (int i = 0; i < Q; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) bits[buf][i][j] = 4 * u + j < Kw ? prow[i][4 * u + j] : 0u;
+        }
+    };
+    auto load_alpha = [&](int w, float (&dst)[Q]) {
+        const int grp = GROUPED ? (w < Kw ? w : Kw - 1) / gw : 0;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) dst[i] = arow[i][grp];
+    };
+    auto load_unit = [&](int u, int buf) {
+        load_bits(u, buf);
+        if (GROUPED) {
+            load_alpha(4 * u, a[buf][0]);
+            load_alpha(4 * u + 2, a[buf][1]);
+        }
+    };
+    fu_u32x4 xf[XW][2][TT];  // [word][slice][token tile]
+    const fu_u32x4 zero = {0u, 0u, 0u, 0u};
+    auto load_x = [&](int w, int slot) {  // words beyond K contribute nothing
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt)
+                xf[slot][sub][tt] = w < Kw ? *reinterpret_cast<const fu_u32x4*>(
+                                                 xrow[tt] + (ORDERED ? (2 * w + sub) * 512 : 32 * w + 8 * sub)) : zero;
+    };
+    LevelTable<Q> table;
+    // the two words of a pair may lie in two groups (g = 32): then the table is rebuilt between them
+    const bool split = GROUPED && (gw & 1);
+    const uint32_t half_sel = h ? 0x07060302u : 0x05040100u;
+
+    auto clamp_unit = [&](int u) { return u < units ? u : units - 1; };
+    load_unit(clamp_unit(wave), 0);
+    if (!GROUPED) load_alpha(0, a[0][0]);
+#pragma unroll
+    for (int j = 0; j < XW; ++j) load_x(4 * clamp_unit(wave) + j, j);
+    if (D == 2) load_unit(clamp_unit(wave + W), D - 1);
+    if (!GROUPED) table.build(a[0][0]);
+
+    auto unit = [&](int u, int buf) {
+        uint32_t own[2][Q];  // this lane half's 2 x 16 signs of each pair of words
+        LevelTable<Q> tables[2];
+#pragma unroll
+        for (int pr = 0; pr < 2; ++pr) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i)
+                own[pr][i] = __builtin_amdgcn_perm(bits[buf][i][2 * pr + 1], bits[buf][i][2 * pr], half_sel);
+            if (GROUPED) tables[pr].build(a[buf][pr]);
+        }
+        load_unit(clamp_unit(u + D * W), buf);
+#pragma unroll
+        for (int pr = 0; pr < 2; ++pr) {
+            if (4 * u + 2 * pr < Kw) {
+                fu_u32x4 frag[4];
+                expand32<Q>(own[pr], GROUPED ? tables[pr] : table, frag);
+                if (split) {
+                    fu_u32x4 second[4];
+                    float as[Q];
+                    load_alpha(4 * u + 2 * pr + 1, as);
+                    table.build(as);
+                    expand32<Q>(own[pr], table, second);
+                    frag[2] = second[2];
+                    frag[3] = second[3];
+                }
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    constexpr int MASK = XW - 1;
+                    const int slot = (2 * pr + j) & MASK;
+#pragma unroll
+                    for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+                        for (int tt = 0; tt < TT; ++tt)
+                            acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                __builtin_bit_cast(fu_bf16x8, frag[2 * j + sub]),
+                                __builtin_bit_cast(fu_bf16x8, xf[slot][sub][tt]), acc[tt], 0, 0, 0);
+                    if (XW == 2 && pr == 0)
+                        load_x(4 * u + 2 + j, slot);
+                    else
+                        load_x(4 * clamp_unit(u + W) + 2 * pr + j - (XW == 2 ? 2 : 0), slot);
+                }
+            }
+        }
+    };
+    for (int u = wave; u < units; u += D * W) {
+        unit(u, 0);
+        if (D == 2 && u + W < units) unit(u + W, D - 1);
+    }
+
+    // accumulator register 4 gg + e of lane l: row n0 + 8 gg + 4 (l / 32) + e, token l % 32
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+#pragma unroll
+        for (int gg = 0; gg < 4; ++gg)
+            part[tt & 1][wave][gg][lane] = fu_f32x4{acc[tt][4 * gg], acc[tt][4 * gg + 1], acc[tt][4 * gg + 2], acc[tt][4 * gg + 3]};
+        __syncthreads();  // two buffers: the sums of tile tt are read while tile tt + 1 is written
+        if (threadIdx.x < 256) {
+            const int gg = threadIdx.x >> 6;
+            fu_f32x4 s = part[tt & 1][0][gg][lane];
+#pragma unroll
+            for (int w = 1; w < W; ++w) s += part[tt & 1][w][gg][lane];
+            const int64_t t = t0 + tt * 32 + col, nn = n0 + 8 * gg + 4 * h;
+            if (t < T) {
+                bf16_t* dst = y + t * N + nn;
+                if (nn + 3 < N && (N & 3) == 0) {
+                    *reinterpret_cast<uint2*>(dst) = make_uint2(fu_pack(s[0], s[1]), fu_pack(s[2], s[3]));
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (nn + e < N) dst[e] = f32_to_bf16(s[e]);
+                }
+            }
+        }
+    }
+}
+
+template <int Q, bool GROUPED>
+static hipError_t launch_q(const uint32_t* packed, const float* alpha, const bf16_t* x, int64_t T, int64_t N, int64_t K,
+                           int64_t g, bf16_t* y, void* workspace, hipStream_t st) {
+    const unsigned cols = (unsigned)((N + 31) / 32);
+    if (T <= 32) {
+        BCQ_LAUNCH((fused_fwd_kernel<Q, 1, 8, GROUPED, false>), dim3(cols), dim3(512), 0, st, packed, alpha, x, y, T, N, K,
+                           g);
+        return hipGetLastError();
+    }
+    const int64_t jobs = (T + 31) / 32 * 4 * ((K / 32 + 1) / 2);
+    BCQ_LAUNCH(order_act_kernel, dim3((unsigned)((jobs + 3) / 4)), dim3(256), 0, st, x, T, K, (fu_u32x4*)workspace);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const bf16_t* xo = (const bf16_t*)workspace;
+    // 128 tokens per workgroup read and expand every plane half as often, 64 make twice as many workgroups: measured
+    // (256 tokens, q = 4) 7680 x 2560 27 against 31 us, 10240 x 2560 35 / 38, 2560 x 2560 17 / 17, 1024 x 1024 10 / 8
+    if ((int64_t)cols * ((T + 127) / 128) >= 256)
+        BCQ_LAUNCH((fused_fwd_kernel<Q, 4, 4, GROUPED, true>), dim3(cols, (unsigned)((T + 127) / 128)), dim3(256), 0, st,
+                           packed, alpha, xo, y, T, N, K, g);
+    else
+        BCQ_LAUNCH((fused_fwd_kernel<Q, 2, 4, GROUPED, true>), dim3(cols, (unsigned)((T + 63) / 64)), dim3(256), 0, st,
+                           packed, alpha, xo, y, T, N, K, g);
+    return hipGetLastError();
+}
+
+// Up to 384 tokens (q = 4, 10240 x 2560: 96 tokens 29 -> 17 us against two kernels, 256 tokens 46 -> 35, 400 tokens 54 -> 53;
+// from there on re-expanding the planes for every 128 tokens costs more than writing What once).  The re-ordered
+// activations of more than 32 tokens take the place of the expanded weights in the workspace.
+bool fused_fwd_ok(int64_t T, int64_t N, int64_t K, int q) {
+    if (q > 4 || T > 384) return false;
+    return T <= 32 || (size_t)((T + 31) / 32 * 32 * K * 2) <= mfma_fwd_workspace(N, K);
+}
+
+hipError_t launch_fwd_fused(const uint32_t* packed, const float* alpha, const void* x, int64_t T, int64_t N, int64_t K,
+                            int64_t g, int q, void* y, void* workspace, hipStream_t st) {
+    const bf16_t* xb = (const bf16_t*)x;
+    bf16_t* yb = (bf16_t*)y;
+#define BCQ_FUSED_GO(QQ)                                                                                 \
+    if (g != K) return launch_q<QQ, true>(packed, alpha, xb, T, N, K, g, yb, workspace, st);             \
+    return launch_q<QQ, false>(packed, alpha, xb, T, N, K, g, yb, workspace, st);
+    switch (q) {
+        case 1: BCQ_FUSED_GO(1)
+        case 2: BCQ_FUSED_GO(2)
+        case 3: BCQ_FUSED_GO(3)
+        default: BCQ_FUSED_GO(4)
+    }
+#undef BCQ_FUSED_GO
+}
+
+}  // namespace bcq
