@@ -2,7 +2,8 @@
 scales are trained; Section 4.2: normally alpha_1 alone).
 
 `BCQLinearFunction` routes forward (Eq. 2), input gradient (Eq. 3) and scale gradient (Eq. 4) to the C-ABI entry
-points; `BCQLinear` is the module around it.  Nothing is computed here: every product runs in the HIP kernels.
+points; `BCQLinear` is the module around it, which takes the same node in native code (csrc/bcq_torch.cpp) for plain
+tensors outside of transforms and traces.  Nothing is computed here: every product runs in the HIP kernels.
 """
 import torch
 
@@ -93,5 +94,10 @@ class BCQLinear(torch.nn.Module):
         return cls(packed, alpha, g=g, bias=bias, q_train=q_train, grad_scale=grad_scale)
 
     def forward(self, x):
-        y = BCQLinearFunction.apply(x, self.alpha_train, self.alpha_frozen, self._layer)
+        y, layer = None, self._layer
+        if not torch.compiler.is_compiling():
+            y = B._try_native("linear", x, self.alpha_train, self.alpha_frozen, layer.packed, layer.twin, layer.g,
+                              layer.q_train, layer.grad_scale)
+        if y is None:
+            y = BCQLinearFunction.apply(x, self.alpha_train, self.alpha_frozen, layer)
         return y if self.bias is None else y + self.bias.to(y.dtype)

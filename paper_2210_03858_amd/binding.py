@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libbcq_hip.so (include/bcq.h): argument marshalling only.
+"""Thin ctypes binding of libbcq_hip.so (include/bcq.h): argument marshalling only.  The entry points that are called
+once per layer and pass try csrc/bcq_torch.cpp first, the same checks and the same call in native code.
 
 Every function takes torch tensors that live on the GPU (PyTorch is used for device memory and streams
 only), checks dtype/shape/contiguity on the host, passes raw device pointers and the current HIP stream to
@@ -26,6 +27,7 @@ EXPORTS = ("bcq_status_string", "bcq_abi_version", "bcq_workspace_bytes", "bcq_q
            "bcq_prepare", "bcq_batch_prepare")
 
 _lib = None
+_native = None
 
 
 class AdamW(ctypes.Structure):
@@ -93,6 +95,30 @@ def load():
         getattr(lib, name).restype = i32
     _lib = lib
     return lib
+
+
+def native():
+    """The in-tree torch extension with the host path of the hot entry points; raises if it has not been built.
+
+    Its functions return None for everything but the plain case; the callers then go on in Python, which checks and
+    raises."""
+    global _native
+    if _native is None:
+        load()
+        try:
+            from . import _bcq_torch
+        except ImportError as e:
+            raise RuntimeError("_bcq_torch.so is missing or does not load: run `python -m paper_2210_03858_amd.build` "
+                               "(or __graft_entry__.build()) first") from e
+        _native = _bcq_torch
+    return _native
+
+
+def _try_native(name, *args):
+    try:
+        return getattr(_native or native(), name)(*args)
+    except TypeError:  # an argument that is no tensor: the Python path says which
+        return None
 
 
 def status_string(status):
@@ -223,6 +249,9 @@ def bcq_pack_decode(packed, tiled=None):
 
 def bcq_linear_fwd_decode(tiled, alpha, x, g=None, y=None, workspace=None):
     """Forward from the decode layout; alpha[q,N] or [q,N,K/g]; at most 80 tokens of bf16; workspace required."""
+    out = _try_native("fwd_decode", tiled, alpha, x, x.shape[-1] if g is None else int(g), y, workspace)
+    if out is not None:
+        return out
     T, K = x.shape
     q, N = alpha.shape[0], alpha.shape[1]
     g = K if g is None else int(g)
@@ -354,6 +383,9 @@ def bcq_quantize_grouped(W, q, g, alpha=None, packed=None, planes_i8=None, want_
 
 
 def bcq_linear_fwd_grouped(packed, alpha, x, g, y=None, workspace=None):
+    out = _try_native("fwd_grouped", packed, alpha, x, int(g), y, workspace)
+    if out is not None:
+        return out
     q, N, Kw = packed.shape
     K = Kw * 32
     T = x.shape[0]
@@ -371,6 +403,9 @@ def bcq_linear_fwd_grouped(packed, alpha, x, g, y=None, workspace=None):
 
 
 def bcq_linear_bwd_input_grouped(packed, alpha, dy, g, packed_t=None, dx=None, workspace=None):
+    out = _try_native("bwd_input_grouped", packed, alpha, dy, int(g), packed_t, dx, workspace)
+    if out is not None:
+        return out
     q, N, Kw = packed.shape
     K = Kw * 32
     T = dy.shape[0]
@@ -390,6 +425,10 @@ def bcq_linear_bwd_input_grouped(packed, alpha, dy, g, packed_t=None, dx=None, w
 
 
 def bcq_linear_bwd_alpha_grouped(packed, x, dy, g, q_train=None, grad_scale=1.0, dalpha=None, workspace=None):
+    out = _try_native("bwd_alpha_grouped", packed, x, dy, int(g), packed.shape[0] if q_train is None else int(q_train),
+                      float(grad_scale), dalpha, workspace)
+    if out is not None:
+        return out
     q, N, Kw = packed.shape
     K = Kw * 32
     T = x.shape[0]

@@ -1,0 +1,93 @@
+"""The native host path against the Python one: the same kernels on the same buffers, so results are bit-equal, and the
+calls that only the Python node handles or refuses still reach it."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def layer():
+    import torch
+    from paper_2210_03858_amd.autograd import BCQLinear
+    torch.manual_seed(3)
+    W = torch.randn((96, 256), device="cuda") * 0.02
+    return BCQLinear.from_weight(W, 3, g=64, q_train=2, grad_scale=0.5)
+
+
+def _apply(layer, x):
+    from paper_2210_03858_amd.autograd import BCQLinearFunction
+    return BCQLinearFunction.apply(x, layer.alpha_train, layer.alpha_frozen, layer._layer)
+
+
+
+@pytest.mark.parametrize("shape,dtype", [((40, 256), "bfloat16"), ((2, 3, 256), "float32"), ((256,), "bfloat16"),
+                                         ((300, 256), "bfloat16")])
+def test_module_equals_python_node(layer, shape, dtype):
+    import torch
+    x = torch.randn(shape, device="cuda").to(getattr(torch, dtype)).requires_grad_(True)
+    y, ref = layer(x), _apply(layer, x)
+    assert y.shape == ref.shape and torch.equal(y, ref)
+    dy = torch.randn_like(y)
+    for wanted in ((x, layer.alpha_train), (layer.alpha_train,), (x,)):
+        got = torch.autograd.grad(y, wanted, dy, retain_graph=True)
+        for a, b in zip(got, torch.autograd.grad(ref, wanted, dy, retain_graph=True)):
+            assert a.shape == b.shape and torch.equal(a, b)
+    strided = torch.randn(shape + (2,), device="cuda").to(x.dtype)[..., 0]  # not contiguous
+    assert torch.equal(layer(strided), _apply(layer, strided.contiguous()))
+    with torch.no_grad():
+        assert layer(x).grad_fn is None
+
+
+def test_hooks_versions_and_refusals(layer):
+    import torch
+    import paper_2210_03858_amd as bcq
+    x = torch.randn((8, 256), device="cuda").bfloat16().requires_grad_(True)
+    seen = []
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: seen.append(t.shape) or t.clone(), lambda t: t):
+        y = layer(x)
+    assert sorted(map(len, seen)) == [2, 3]  # activations and scales
+    torch.autograd.grad(y, (x, layer.alpha_train), torch.ones_like(y))
+    y = layer(x)
+    with torch.no_grad():
+        x.add_(1.0)  # the saved activations have changed
+    with pytest.raises(RuntimeError, match="inplace"):
+        torch.autograd.grad(y, x, torch.ones_like(y))
+    y = layer(x)
+    torch.autograd.grad(y, x, torch.ones_like(y))
+    with pytest.raises(RuntimeError, match="second time"):
+        torch.autograd.grad(y, x, torch.ones_like(y))
+    odd = torch.randn(8 * 96 + 1, device="cuda").bfloat16()[1:].view(8, 96)  # two bytes off
+    with pytest.raises(bcq.BcqError):
+        torch.autograd.grad(layer(x), x, odd)
+    with pytest.raises(bcq.BcqError):
+        layer(x.detach()[:0])
+    for bad in (x.detach().cpu(), x.detach().half()):
+        with pytest.raises(ValueError):
+            layer(bad)
+    with pytest.raises(RuntimeError):
+        torch.func.vmap(layer)(torch.randn((2, 4, 256), device="cuda"))
+    with pytest.raises(RuntimeError):
+        torch.func.grad(lambda t: layer(t).sum())(torch.randn((4, 256), device="cuda"))
+    import torch.autograd.forward_ad as fwd
+    with fwd.dual_level(), pytest.raises(RuntimeError):
+        layer(fwd.make_dual(torch.randn((4, 256), device="cuda"), torch.ones((4, 256), device="cuda")))
+
+
+def test_bindings_keep_their_checks(layer):
+    import torch
+    import paper_2210_03858_amd as bcq
+    L = layer._layer
+    alpha = torch.cat((layer.alpha_train, layer.alpha_frozen)).detach()
+    x = torch.randn((4, 256), device="cuda")
+    y = torch.empty((4, 96), device="cuda")
+    assert bcq.bcq_linear_fwd_grouped(L.packed, alpha, x, 64, y=y) is y
+    for args in ((L.packed, alpha, x[:, :128], 64), (L.packed, alpha, x.t(), 64), (L.packed, alpha.double(), x, 64),
+                 (L.packed.float(), alpha, x, 64), (L.packed, alpha, x.double(), 64), (L.packed, alpha, x.cpu(), 64)):
+        with pytest.raises(ValueError):
+            bcq.bcq_linear_fwd_grouped(*args)
+    with pytest.raises(ValueError):
+        bcq.bcq_linear_fwd_grouped(L.packed, alpha, x, 64, y=y[:3])
+    with pytest.raises((bcq.BcqError, ValueError)):
+        bcq.bcq_linear_fwd_grouped(L.packed, alpha, x, 48)
+    with pytest.raises(bcq.BcqError):
+        bcq.bcq_linear_bwd_alpha_grouped(L.packed, x, y, 64, q_train=4)
