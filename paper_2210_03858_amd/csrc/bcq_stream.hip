@@ -164,8 +164,14 @@ static hipError_t launch_lds(const uint32_t* planes, const unsigned char* xq, co
 // 5120 x 1280 gain 2.3 - 2.7 us per call, 7680 x 2560 loses 1.7 us, 10240 x 2560 loses 8 us)
 constexpr int FUSED_MAX_SEGS = 1;
 constexpr int64_t FUSED_MAX_WAVES = 1024;
+// From the decode layout the two-kernel form is faster than from the canonical planes, so the single kernel pays only
+// while no compute unit re-codes for two row tiles or more than four segments: at 1 / 8 tokens 3072 x 1024 6.2 -> 5.5 /
+// 6.3 -> 5.8 us, 4096 x 2048 6.7 -> 6.0 / 6.7 -> 6.3, but 5120 x 1280 (320 workgroups) 6.7 -> 6.6 / 6.7 -> 7.4 and
+// 2560 x 2560 (five waves) 6.8 -> 6.7 / 6.9 -> 7.4; more than 8 tokens re-code twice as much (3072 x 1024, 16: 6.6 -> 7.6).
+constexpr unsigned FUSED_TILED_MAX_WGS = 256;
+constexpr int FUSED_TILED_MAX_WAVES = 4;
 
-template <int MODE, int QP, bool TWO>
+template <int MODE, int QP, bool TWO, bool TILED>
 static hipError_t launch_fused_cfg(const uint32_t* planes, const bf16_t* act, const float* alpha, const bf16_t* dy,
                                    void* out, int64_t T, int64_t rows, int64_t cw, int q_used, float scale,
                                    const StreamPlan& p, int gsegs, int G, hipStream_t st) {
@@ -174,21 +180,21 @@ static hipError_t launch_fused_cfg(const uint32_t* planes, const bf16_t* act, co
     const size_t stage = (size_t)p.W * (4 * H * QBLK + H * QSCL), red = (size_t)p.W * nout * 1024;
     const size_t lds = stage > red ? stage : red;
     static LdsLimit limit;
-    hipError_t e = limit.ensure((const void*)stream_fused_kernel<MODE, QP, TWO>, lds);
+    hipError_t e = limit.ensure((const void*)stream_fused_kernel<MODE, QP, TWO, TILED>, lds);
     if (e != hipSuccess) return e;
-    BCQ_LAUNCH((stream_fused_kernel<MODE, QP, TWO>), dim3(p.grid_x, (unsigned)p.tiles), dim3((unsigned)(64 * p.W)),
+    BCQ_LAUNCH((stream_fused_kernel<MODE, QP, TWO, TILED>), dim3(p.grid_x, (unsigned)p.tiles), dim3((unsigned)(64 * p.W)),
                        lds, st, planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p.segs_per_wave, p.segs, gsegs, G);
     return hipGetLastError();
 }
 
-template <int MODE>
+template <int MODE, bool TILED>
 static hipError_t launch_fused(const uint32_t* planes, const bf16_t* act, const float* alpha, const bf16_t* dy, void* out,
                                int64_t T, int64_t rows, int64_t cw, int q_used, float scale, const StreamPlan& p,
                                int gsegs, int G, hipStream_t st) {
 #define BCQ_FUSED_Q(QQ)                                                                                                \
     if (p.halves == 2)                                                                                                 \
-        return launch_fused_cfg<MODE, QQ, true>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st); \
-    return launch_fused_cfg<MODE, QQ, false>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st);
+        return launch_fused_cfg<MODE, QQ, true, TILED>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st); \
+    return launch_fused_cfg<MODE, QQ, false, TILED>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st);
     switch (q_used <= 4 ? q_used : 8) {
         case 1: BCQ_FUSED_Q(1)
         case 2: BCQ_FUSED_Q(2)
@@ -208,10 +214,11 @@ static hipError_t launch_stream(const uint32_t* planes, const bf16_t* act, const
     const int gsegs = (grouped && MODE != STREAM_DX) ? (int)(g / 512) : 0;  // needs g % 512 == 0 (checked by the caller)
     const StreamPlan p = stream_plan(T, rows, cw, gsegs);
     if (p.W < 1 || p.W > 8 || p.R != 1) return hipErrorInvalidConfiguration;  // compiled for at most 512 threads, R = 1
-    if constexpr (MODE != STREAM_DX && !TILED) {
-        int fused_max = FUSED_MAX_SEGS;
-        if (p.segs_per_wave <= fused_max && p.R == 1 && (int64_t)p.grid_x * p.tiles * p.W <= FUSED_MAX_WAVES)
-            return launch_fused<MODE>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st);
+    if constexpr (MODE != STREAM_DX) {
+        const bool fits = TILED ? p.halves == 1 && p.grid_x <= FUSED_TILED_MAX_WGS && p.W <= FUSED_TILED_MAX_WAVES
+                                : (int64_t)p.grid_x * p.tiles * p.W <= FUSED_MAX_WAVES;
+        if (p.segs_per_wave <= FUSED_MAX_SEGS && fits)
+            return launch_fused<MODE, TILED>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st);
     }
     const int sets = (MODE == STREAM_DX) ? q * G : 1;
     unsigned char* xq = reinterpret_cast<unsigned char*>(workspace);

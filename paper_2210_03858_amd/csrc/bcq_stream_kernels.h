@@ -1018,8 +1018,8 @@ __global__ __launch_bounds__(512) void stream_lds_kernel(const uint32_t* __restr
 // segment (it is repeated by every row tile), which is why larger layers keep the separate pre-kernel.
 // One workgroup = one row tile; its W waves split the segments.  LDS: W wave-private staging areas
 // ([4 instructions][halves][2 KiB] + [halves][256 B] scales), reused for the cross-wave sum at the end.
-// gsegs == 0: row-wise scales; else groups of gsegs segments (every wave owns whole groups).
-template <int MODE, int QP, bool TWO>
+// gsegs == 0: row-wise scales; else groups of gsegs segments (every wave owns whole groups).  TILED: decode layout.
+template <int MODE, int QP, bool TWO, bool TILED>
 __global__ __launch_bounds__(512) void stream_fused_kernel(const uint32_t* __restrict__ planes,
                                                             const bf16_t* __restrict__ act,
                                                             const float* __restrict__ alpha,
@@ -1087,7 +1087,15 @@ __global__ __launch_bounds__(512) void stream_fused_kernel(const uint32_t* __res
             for (int b = 0; b < 4; ++b) raw[u][b] = src[b];  // a dead unit reads the first 64 bytes of act (in bounds)
         }
         uint32_t bits[QP][4];
-        {
+        if (TILED) {  // the KiB that a wave reads per plane is one contiguous run
+            const uint32_t* tb = planes + ((row0 >> 4) * segs + seg) * (int64_t)(q_used * 256) + lane * 4;
+#pragma unroll
+            for (int i = 0; i < QP; ++i) {
+                const q_u32x4 v4 = *reinterpret_cast<const q_u32x4*>(tb + (i < q_used ? i : q_used - 1) * 256);
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) bits[i][jj] = v4[jj];
+            }
+        } else {
             uint32_t w0 = (uint32_t)seg * 16u + 4u * (uint32_t)g;
 #pragma unroll
             for (int i = 0; i < QP; ++i) {
