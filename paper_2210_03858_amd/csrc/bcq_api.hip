@@ -96,7 +96,35 @@ bool mfma_bwd_alpha_ok(int64_t T, int64_t N, int64_t K, bool rowwise, int dtype)
     return dtype == BCQ_BF16 && (T > 16 || !rowwise) && N % 8 == 0 && N >= 8 && K >= 8;  // rows of dy 16-byte aligned
 }
 
+// Calls that neither the streaming nor the aligned matrix-core kernels take (row counts that are no multiple of 8 or, with
+// few tokens, of 32) have single kernels on the fp64 matrix cores; the padded bf16 forms take two or three launches more
+// and go from where both were measured equal.  Scale gradient (fp64: 16 rows per compute unit against all tokens and
+// columns): 1500 x 1056 at 130 tokens 27 / 27 us, at 333 70 -> 29.  Input gradient: 1500 x 1056 at 200 tokens 32 -> 39,
+// at 333 52 -> 40, 2999 x 3008 at 1000 tokens 115.
+bool unaligned_bwd_alpha_ok(int64_t T, int64_t N, int64_t K, bool rowwise, int dtype) {
+    return dtype == BCQ_BF16 && (T > 16 || !rowwise) && N % 8 != 0 && T * K * (N > 4096 ? N : 4096) >= ((int64_t)1 << 29);
+}
+bool split_bwd_input_ok(int64_t T, int64_t N, int64_t K, bool rowwise, int dtype) {
+    return dtype == BCQ_BF16 && N % 32 != 0 && !mfma_bwd_input_ok(T, N, rowwise, dtype) &&
+           T * N * K >= ((int64_t)3 << 27);
+}
+
+// What the caller must bring when it brings a workspace at all.  The unaligned forms do not count: with less than they
+// need the call runs on the kernels that need none.
+size_t workspace_least(int op, int64_t T, int64_t N, int64_t K, int64_t g, int q, int dtype);
+
 size_t workspace_need(int op, int64_t T, int64_t N, int64_t K, int64_t g, int q, int dtype) {
+    const size_t least = workspace_least(op, T, N, K, g, q, dtype);
+    const bool rowwise = (g == K);
+    size_t more = 0;
+    if (op == BCQ_OP_BWD_INPUT && split_bwd_input_ok(T, N, K, rowwise, dtype))
+        more = bcq::mfma_bwd_input_split_workspace(T, N, K);
+    if (op == BCQ_OP_BWD_ALPHA && unaligned_bwd_alpha_ok(T, N, K, rowwise, dtype))
+        more = bcq::mfma_bwd_alpha_workspace(T, N, K, g, q);
+    return least > more ? least : more;
+}
+
+size_t workspace_least(int op, int64_t T, int64_t N, int64_t K, int64_t g, int q, int dtype) {
     const bool rowwise = (g == K);
     switch (op) {
         case BCQ_OP_QUANTIZE: return 16;  // status word
@@ -243,7 +271,7 @@ bcq_status bcq_linear_fwd_grouped(const uint32_t* packed, const float* alpha, co
     if (s != BCQ_OK) return s;
     if (dtype != BCQ_F32 && dtype != BCQ_BF16) return BCQ_ERR_DTYPE;
     if (misaligned(packed) || misaligned(alpha) || misaligned(x) || misaligned(y)) return BCQ_ERR_ALIGN;
-    s = check_workspace(workspace, workspace_bytes, workspace_need(BCQ_OP_FWD, T, N, K, g, q, dtype));
+    s = check_workspace(workspace, workspace_bytes, workspace_least(BCQ_OP_FWD, T, N, K, g, q, dtype));
     if (s != BCQ_OK) return s;
     s = check_device();
     if (s != BCQ_OK) return s;
@@ -313,7 +341,7 @@ bcq_status bcq_linear_bwd_input_grouped(const uint32_t* packed, const uint32_t* 
     if (dtype != BCQ_F32 && dtype != BCQ_BF16) return BCQ_ERR_DTYPE;
     if (misaligned(packed) || misaligned(packed_t) || misaligned(alpha) || misaligned(dy) || misaligned(dx))
         return BCQ_ERR_ALIGN;
-    s = check_workspace(workspace, workspace_bytes, workspace_need(BCQ_OP_BWD_INPUT, T, N, K, g, q, dtype));
+    s = check_workspace(workspace, workspace_bytes, workspace_least(BCQ_OP_BWD_INPUT, T, N, K, g, q, dtype));
     if (s != BCQ_OK) return s;
     s = check_device();
     if (s != BCQ_OK) return s;
@@ -323,6 +351,9 @@ bcq_status bcq_linear_bwd_input_grouped(const uint32_t* packed, const uint32_t* 
         return done(bcq::launch_bwd_input_stream(packed_t, alpha, dy, T, N, K, g, q, dx, workspace, st));
     if (workspace && mfma_bwd_input_ok(T, N, rowwise, dtype))
         return done(bcq::launch_bwd_input_mfma(packed, packed_t, alpha, dy, T, N, K, g, q, dx, workspace, st));
+    if (workspace && split_bwd_input_ok(T, N, K, rowwise, dtype) &&
+        workspace_bytes >= bcq::mfma_bwd_input_split_workspace(T, N, K))
+        return done(bcq::launch_bwd_input_mfma_split(packed, packed_t, alpha, dy, T, N, K, g, q, dx, workspace, st));
     return done(bcq::launch_bwd_input_generic(packed, alpha, dy, dtype, T, N, K, g, q, dx, st));
 }
 
@@ -412,7 +443,7 @@ bcq_status bwd_alpha_impl(const uint32_t* packed, const void* x, const void* dy,
         s = make_adamw(opt, alpha, m, v, &oargs);
         if (s != BCQ_OK) return s;
     }
-    s = check_workspace(workspace, workspace_bytes, workspace_need(BCQ_OP_BWD_ALPHA, T, N, K, g, q, dtype));
+    s = check_workspace(workspace, workspace_bytes, workspace_least(BCQ_OP_BWD_ALPHA, T, N, K, g, q, dtype));
     if (s != BCQ_OK) return s;
     s = check_device();
     if (s != BCQ_OK) return s;
@@ -423,7 +454,9 @@ bcq_status bwd_alpha_impl(const uint32_t* packed, const void* x, const void* dy,
         if (e == hipSuccess && with_opt) e = bcq::launch_adamw(dalpha, (int64_t)q_train * N * (K / g), oargs, st);
         return done(e);
     }
-    if (workspace && !stream_bwd_alpha_ok(T, K, g, dtype) && mfma_bwd_alpha_ok(T, N, K, rowwise, dtype))
+    const bool unaligned = unaligned_bwd_alpha_ok(T, N, K, rowwise, dtype) &&
+                           workspace_bytes >= bcq::mfma_bwd_alpha_workspace(T, N, K, g, q);
+    if (workspace && !stream_bwd_alpha_ok(T, K, g, dtype) && (mfma_bwd_alpha_ok(T, N, K, rowwise, dtype) || unaligned))
         return done(bcq::launch_bwd_alpha_mfma(packed, x, dy, T, N, K, g, q, q_train, grad_scale, dalpha, workspace,
                                                with_opt ? &oargs : nullptr, st));
     hipError_t e;

@@ -136,7 +136,9 @@ __global__ __launch_bounds__(256) void expand_fwd_kernel(const uint32_t* __restr
 // twin when the caller has one (one word = 32 consecutive n of this thread's column), else the canonical words
 // (the 32 lanes of a column tile share a word and each takes its own bit).  The scales of the block's 256 rows
 // pass through LDS.
-template <bool TWIN>
+// SPLIT: What is written as three bf16 terms hi + mid + lo (24 significant bits, all of the fp32 sum), one after the
+// other along the contraction, smallest first; a value that has no finite bf16 form is its first term alone.
+template <bool TWIN, bool SPLIT>
 __global__ __launch_bounds__(256) void expand_bwd_kernel(const uint32_t* __restrict__ planes,
                                                          const float* __restrict__ alpha, int64_t N, int64_t K,
                                                          int64_t g, int q, int64_t R16 /* padded N / 16 */,
@@ -176,7 +178,46 @@ __global__ __launch_bounds__(256) void expand_bwd_kernel(const uint32_t* __restr
             s[e] += ((bits >> e) & 1u) ? a : -a;
         }
     }
-    store_word_frags(s, frag, ct * R16 + 2 * v, c);
+    if (!SPLIT) {
+        store_word_frags(s, frag, ct * R16 + 2 * v, c);
+        return;
+    }
+    store_word_frags(s, frag, (ct * 3 + 2) * R16 + 2 * v, c);
+#pragma unroll
+    for (int term = 1; term >= 0; --term) {
+#pragma unroll
+        for (int e = 0; e < 32; ++e) {
+            const float t = bf16_to_f32(f32_to_bf16(s[e]));
+            s[e] = fabsf(t) <= 3.4028234e38f ? s[e] - t : 0.f;  // exact
+        }
+        store_word_frags(s, frag, (ct * 3 + term) * R16 + 2 * v, c);
+    }
+}
+
+// act[T][C] (any C) -> out[T][REP][P] with rows padded by zeros to P >= C (a multiple of 8): what the kernels below need
+// of an operand whose rows are not 16-byte aligned.  REP = 3 goes with the three weight terms: non-finite values stand
+// in the last copy only, the one that meets the leading term, so that an Inf meets every weight once.
+template <int REP>
+__global__ __launch_bounds__(256) void pad_act_kernel(const bf16_t* __restrict__ act, int64_t T, int64_t C, int64_t P,
+                                                      u32x4* __restrict__ out) {
+    const int64_t chunks = P / 8, idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= T * chunks) return;
+    const int64_t t = idx / chunks, c = idx % chunks;
+    const bf16_t* row = act + t * C;
+    uint32_t h[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) h[e] = 8 * c + e < C ? row[8 * c + e] : 0u;
+    u32x4 v;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) v[p] = h[2 * p] | (h[2 * p + 1] << 16);
+    out[(t * REP + REP - 1) * chunks + c] = v;
+    if (REP == 1) return;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) h[e] = (h[e] & 0x7F80u) == 0x7F80u ? 0u : h[e];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) v[p] = h[2 * p] | (h[2 * p + 1] << 16);
+#pragma unroll
+    for (int r = 0; r < REP - 1; ++r) out[(t * REP + r) * chunks + c] = v;
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -519,20 +560,46 @@ hipError_t launch_fwd_mfma(const uint32_t* packed, const float* alpha, const voi
     return launch_gemm((const bf16_t*)x, K, (const u32x4*)workspace, (bf16_t*)y, N, T, N, K, R16, st);
 }
 
+template <bool SPLIT>
+static hipError_t launch_expand_bwd(const uint32_t* packed, const uint32_t* packed_t, const float* alpha, int64_t N,
+                                    int64_t K, int64_t g, int q, int64_t R16, u32x4* frag, hipStream_t st) {
+    dim3 grid((unsigned)(K / 32), (unsigned)((R16 / 2 + 7) / 8));
+    if (packed_t && N % 32 == 0)
+        BCQ_LAUNCH((expand_bwd_kernel<true, SPLIT>), grid, dim3(256), 0, st, packed_t, alpha, N, K, g, q, R16, frag);
+    else
+        BCQ_LAUNCH((expand_bwd_kernel<false, SPLIT>), grid, dim3(256), 0, st, packed, alpha, N, K, g, q, R16, frag);
+    return hipGetLastError();
+}
+
 hipError_t launch_bwd_input_mfma(const uint32_t* packed, const uint32_t* packed_t, const float* alpha, const void* dy,
                                  int64_t T, int64_t N, int64_t K, int64_t g, int q, void* dx, void* workspace,
                                  hipStream_t st) {
     const int64_t R16 = round_up(N, RPAD) / 16;
-    dim3 grid((unsigned)(K / 32), (unsigned)((R16 / 2 + 7) / 8));
-    if (packed_t && N % 32 == 0)
-        BCQ_LAUNCH(expand_bwd_kernel<true>, grid, dim3(256), 0, st, packed_t, alpha, N, K, g, q, R16,
-                           (u32x4*)workspace);
-    else
-        BCQ_LAUNCH(expand_bwd_kernel<false>, grid, dim3(256), 0, st, packed, alpha, N, K, g, q, R16,
-                           (u32x4*)workspace);
+    u32x4* frag = (u32x4*)workspace;
+    hipError_t e = launch_expand_bwd<false>(packed, packed_t, alpha, N, K, g, q, R16, frag, st);
+    if (e != hipSuccess) return e;
+    return launch_gemm((const bf16_t*)dy, N, frag, (bf16_t*)dx, K, T, K, N, R16, st);
+}
+
+// Input gradient with fp32 weights for row counts (or token counts) that launch_bwd_input_mfma does not take: dX = [dY dY
+// dY] [lo; mid; hi], the same contraction three times as long, on the same kernel.
+size_t mfma_bwd_input_split_workspace(int64_t T, int64_t N, int64_t K) {
+    return (size_t)(3 * round_up(N, RPAD) * 2 * (T + round_up(K, 32)));
+}
+
+hipError_t launch_bwd_input_mfma_split(const uint32_t* packed, const uint32_t* packed_t, const float* alpha,
+                                       const void* dy, int64_t T, int64_t N, int64_t K, int64_t g, int q, void* dx,
+                                       void* workspace, hipStream_t st) {
+    const int64_t P = round_up(N, RPAD), R16 = P / 16;
+    u32x4* frag = (u32x4*)workspace;
+    u32x4* rows = frag + round_up(K, 32) * 3 * P / 8;
+    BCQ_LAUNCH((pad_act_kernel<3>), dim3((unsigned)((T * (P / 8) + 255) / 256)), dim3(256), 0, st, (const bf16_t*)dy, T, N,
+                       P, rows);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_gemm((const bf16_t*)dy, N, (const u32x4*)workspace, (bf16_t*)dx, K, T, K, N, R16, st);
+    e = launch_expand_bwd<true>(packed, packed_t, alpha, N, K, g, q, R16, frag, st);
+    if (e != hipSuccess) return e;
+    return launch_gemm((const bf16_t*)rows, 3 * P, frag, (bf16_t*)dx, K, T, K, 3 * P, 3 * R16, st);
 }
 
 
@@ -925,7 +992,7 @@ struct DalphaPlan {
     int tiles_k, tiles_n, splits;
     int64_t per_split, T16;
     bool xg, fine;
-    size_t frag_bytes, part_bytes;
+    size_t frag_bytes, part_bytes, pad_bytes;
 };
 
 static DalphaPlan dalpha_plan(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
@@ -945,12 +1012,14 @@ static DalphaPlan dalpha_plan(int64_t T, int64_t N, int64_t K, int64_t g, int q)
     pl.frag_bytes = (size_t)(((gcols + 31) / 32) * pl.T16 * 1024);
     pl.fine = (g != K) && (g % DA_TILE != 0);  // groups that are not whole k tiles need per-32-column partials
     pl.part_bytes = (size_t)pl.splits * pl.tiles_k * q * N * sizeof(float) * (pl.fine ? 8 : 1);
+    // rows of dy that are not 16-byte aligned are copied into padded ones first
+    pl.pad_bytes = N % 8 ? (size_t)(T * round_up(N, 8) * 2) : 0;
     return pl;
 }
 
 size_t mfma_bwd_alpha_workspace(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
     const DalphaPlan pl = dalpha_plan(T, N, K, g, q);
-    return pl.frag_bytes + pl.part_bytes;
+    return pl.frag_bytes + (pl.part_bytes + 15) / 16 * 16 + pl.pad_bytes;
 }
 
 hipError_t launch_bwd_alpha_mfma(const uint32_t* packed, const void* x, const void* dy, int64_t T, int64_t N,
@@ -960,9 +1029,19 @@ hipError_t launch_bwd_alpha_mfma(const uint32_t* packed, const void* x, const vo
     const DalphaPlan pl = dalpha_plan(T, N, K, g, q);
     u32x4* frag = reinterpret_cast<u32x4*>(workspace);
     float* part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(workspace) + pl.frag_bytes);
+    int64_t dcols = N;
+    if (pl.pad_bytes) {
+        dcols = round_up(N, 8);
+        u32x4* rows = reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(part) + (pl.part_bytes + 15) / 16 * 16);
+        BCQ_LAUNCH((pad_act_kernel<1>), dim3((unsigned)((T * (dcols / 8) + 255) / 256)), dim3(256), 0, st, (const bf16_t*)dy,
+                           T, N, dcols, rows);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        dy = rows;
+    }
     const bf16_t* gact = (const bf16_t*)(pl.xg ? x : dy);
     const bf16_t* lact = (const bf16_t*)(pl.xg ? dy : x);
-    const int64_t gcols = pl.xg ? K : N, lcols = pl.xg ? N : K;
+    const int64_t gcols = pl.xg ? K : dcols, lcols = pl.xg ? dcols : K;
     {
         dim3 grid((unsigned)((gcols + 127) / 128), (unsigned)((pl.T16 * 2 + 15) / 16));
         BCQ_LAUNCH(transpose_frag_kernel, grid, dim3(256), 0, st, gact, T, gcols, pl.T16, frag);
