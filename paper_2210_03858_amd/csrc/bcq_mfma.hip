@@ -123,11 +123,22 @@ __global__ __launch_bounds__(256) void expand_fwd_kernel(const uint32_t* __restr
     float s[32];
 #pragma unroll
     for (int e = 0; e < 32; ++e) s[e] = 0.f;
-    for (int i = 0; i < q; ++i) {
-        const float a = live ? alpha[((int64_t)i * N + n) * G + grp] : 0.f;
-        const uint32_t bits = live ? packed[((int64_t)i * N + n) * Kw + w] : 0u;
+    // every plane's word and scale is requested before the first is used: one memory latency instead of one per plane
+    float a[8];
+    uint32_t bits[8];
 #pragma unroll
-        for (int e = 0; e < 32; ++e) s[e] += ((bits >> e) & 1u) ? a : -a;
+    for (int i = 0; i < 8; ++i) {
+        if (i < q) {
+            a[i] = live ? alpha[((int64_t)i * N + n) * G + grp] : 0.f;
+            bits[i] = live ? packed[((int64_t)i * N + n) * Kw + w] : 0u;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        if (i < q) {
+#pragma unroll
+            for (int e = 0; e < 32; ++e) s[e] += ((bits[i] >> e) & 1u) ? a[i] : -a[i];
+        }
     }
     store_word_frags(s, frag, ct * R16 + 2 * w, c);
 }
@@ -149,33 +160,48 @@ __global__ __launch_bounds__(256) void expand_bwd_kernel(const uint32_t* __restr
     const int64_t Kw = K / 32, Nw = N / 32;
     const int64_t n_blk = (int64_t)blockIdx.y * 256;
     const int64_t G = K / g, grp = (ct * 32) / g;  // the 32 columns of this block share one scale group
-    for (int i = 0; i < q; ++i) {
-        const int64_t n = n_blk + threadIdx.x;
-        sa[i][threadIdx.x] = (n < N) ? alpha[((int64_t)i * N + n) * G + grp] : 0.f;  // rows beyond N expand to zero
-    }
-    __syncthreads();
     const int64_t v = (int64_t)blockIdx.y * 8 + vl;  // word index along n
-    if (v * 2 >= R16) return;
     const int64_t k = ct * 32 + c;
+    // all planes' scales and, with a twin, all words of this thread are requested before the first is used
+    uint32_t twin[8];
+    float mine[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        if (i < q) {
+            const int64_t n = n_blk + threadIdx.x;
+            mine[i] = (n < N) ? alpha[((int64_t)i * N + n) * G + grp] : 0.f;  // rows beyond N expand to zero
+            if (TWIN) twin[i] = (v < Nw) ? planes[((int64_t)i * K + k) * Nw + v] : 0u;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        if (i < q) sa[i][threadIdx.x] = mine[i];
+    __syncthreads();
+    if (v * 2 >= R16) return;
     float s[32];
 #pragma unroll
     for (int e = 0; e < 32; ++e) s[e] = 0.f;
-    for (int i = 0; i < q; ++i) {
-        uint32_t bits = 0u;
-        if (TWIN) {
-            bits = (v < Nw) ? planes[((int64_t)i * K + k) * Nw + v] : 0u;
-        } else {
+    auto add_plane = [&](int i, uint32_t bits) {
+#pragma unroll
+        for (int e = 0; e < 32; ++e) {
+            const float a = sa[i][vl * 32 + e];
+            s[e] += ((bits >> e) & 1u) ? a : -a;
+        }
+    };
+    if (TWIN) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (i < q) add_plane(i, twin[i]);
+    } else {
+        for (int i = 0; i < q; ++i) {
+            uint32_t bits = 0u;
 #pragma unroll
             for (int e = 0; e < 32; ++e) {
                 const int64_t n = v * 32 + e;
                 const uint32_t wv = (n < N) ? planes[((int64_t)i * N + n) * Kw + ct] : 0u;
                 bits |= ((wv >> c) & 1u) << e;
             }
-        }
-#pragma unroll
-        for (int e = 0; e < 32; ++e) {
-            const float a = sa[i][vl * 32 + e];
-            s[e] += ((bits >> e) & 1u) ? a : -a;
+            add_plane(i, bits);
         }
     }
     if (!SPLIT) {
