@@ -115,7 +115,7 @@ template <int Q, int TT, int W, bool GROUPED, bool ORDERED>
 __global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __restrict__ packed,
                                                            const float* __restrict__ alpha, const bf16_t* __restrict__ x,
                                                            bf16_t* __restrict__ y, int64_t T, int64_t N, int64_t K,
-                                                           int64_t g) {
+                                                           int64_t g, int per, float* __restrict__ sums) {
     __shared__ fu_f32x4 part[2][W][4][64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -123,7 +123,9 @@ __global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __res
     const int64_t n0 = (int64_t)blockIdx.x * 32, t0 = (int64_t)blockIdx.y * (32 * TT);
     const int64_t n = n0 + col < N ? n0 + col : N - 1;  // rows and tokens beyond the edge are computed, never stored
     const int Kw = (int)(K / 32), G = (int)(K / g), gw = (int)(g / 32);
-    const int units = (Kw + 3) / 4;
+    // this workgroup's units of 128 columns: part blockIdx.z of `per` each (all of them when the contraction is not split)
+    const int first = (int)blockIdx.z * per + wave;
+    const int units = min((Kw + 3) / 4, (int)(blockIdx.z + 1) * per);
 
     const uint32_t* prow[Q];
     const float* arow[Q];
@@ -194,11 +196,11 @@ __global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __res
     const uint32_t half_sel = h ? 0x07060302u : 0x05040100u;
 
     auto clamp_unit = [&](int u) { return u < units ? u : units - 1; };
-    load_unit(clamp_unit(wave), 0);
+    load_unit(clamp_unit(first), 0);
     if (!GROUPED) load_alpha(0, a[0][0]);
 #pragma unroll
-    for (int j = 0; j < XW; ++j) load_x(4 * clamp_unit(wave) + j, j);
-    if (D == 2) load_unit(clamp_unit(wave + W), D - 1);
+    for (int j = 0; j < XW; ++j) load_x(4 * clamp_unit(first) + j, j);
+    if (D == 2) load_unit(clamp_unit(first + W), D - 1);
     if (!GROUPED) table.build(a[0][0]);
 
     auto unit = [&](int u, int buf) {
@@ -245,7 +247,7 @@ __global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __res
             }
         }
     };
-    for (int u = wave; u < units; u += D * W) {
+    for (int u = first; u < units; u += D * W) {
         unit(u, 0);
         if (D == 2 && u + W < units) unit(u + W, D - 1);
     }
@@ -263,7 +265,10 @@ __global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __res
 #pragma unroll
             for (int w = 1; w < W; ++w) s += part[tt & 1][w][gg][lane];
             const int64_t t = t0 + tt * 32 + col, nn = n0 + 8 * gg + 4 * h;
-            if (t < T) {
+            if (sums) {  // split contraction: sum_parts_kernel adds the parts
+                if (t < T && nn < N)
+                    *reinterpret_cast<fu_f32x4*>(sums + ((int64_t)blockIdx.z * T + t) * ((N + 3) / 4 * 4) + nn) = s;
+            } else if (t < T) {
                 bf16_t* dst = y + t * N + nn;
                 if (nn + 3 < N && (N & 3) == 0) {
                     *reinterpret_cast<uint2*>(dst) = make_uint2(fu_pack(s[0], s[1]), fu_pack(s[2], s[3]));
@@ -277,28 +282,71 @@ __global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __res
     }
 }
 
+// y[t][n] = sum of the parts, in order; a thread adds four rows n of one token
+__global__ __launch_bounds__(256) void sum_parts_kernel(const float* __restrict__ sums, int parts, int64_t T, int64_t N,
+                                                        bf16_t* __restrict__ y) {
+    const int64_t quads = (N + 3) / 4, idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= T * quads) return;
+    const fu_f32x4* p = reinterpret_cast<const fu_f32x4*>(sums) + idx;
+    fu_f32x4 s = p[0];
+    for (int i = 1; i < parts; ++i) s += p[i * T * quads];
+    const int64_t t = idx / quads, n = idx % quads * 4;
+    bf16_t* dst = y + t * N + n;
+    if ((N & 3) == 0) {
+        *reinterpret_cast<uint2*>(dst) = make_uint2(fu_pack(s[0], s[1]), fu_pack(s[2], s[3]));
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (n + e < N) dst[e] = f32_to_bf16(s[e]);
+    }
+}
+
+static size_t order_bytes(int64_t T, int64_t K) { return T <= 32 ? 0 : (size_t)((T + 31) / 32 * 32 * K * 2); }
+static size_t sums_bytes(int64_t T, int64_t N, int parts) { return (size_t)parts * T * ((N + 3) / 4 * 4) * 4; }
+
 template <int Q, bool GROUPED>
 static hipError_t launch_q(const uint32_t* packed, const float* alpha, const bf16_t* x, int64_t T, int64_t N, int64_t K,
                            int64_t g, bf16_t* y, void* workspace, hipStream_t st) {
     const unsigned cols = (unsigned)((N + 31) / 32);
-    if (T <= 32) {
-        BCQ_LAUNCH((fused_fwd_kernel<Q, 1, 8, GROUPED, false>), dim3(cols), dim3(512), 0, st, packed, alpha, x, y, T, N, K,
-                           g);
-        return hipGetLastError();
+    const int units = (int)((K + 127) / 128);
+    const bf16_t* xo = x;
+    if (T > 32) {
+        const int64_t jobs = (T + 31) / 32 * 4 * ((K / 32 + 1) / 2);
+        BCQ_LAUNCH(order_act_kernel, dim3((unsigned)((jobs + 3) / 4)), dim3(256), 0, st, x, T, K, (fu_u32x4*)workspace);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        xo = (const bf16_t*)workspace;
     }
-    const int64_t jobs = (T + 31) / 32 * 4 * ((K / 32 + 1) / 2);
-    BCQ_LAUNCH(order_act_kernel, dim3((unsigned)((jobs + 3) / 4)), dim3(256), 0, st, x, T, K, (fu_u32x4*)workspace);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const bf16_t* xo = (const bf16_t*)workspace;
     // 128 tokens per workgroup read and expand every plane half as often, 64 make twice as many workgroups: measured
-    // (256 tokens, q = 4) 7680 x 2560 27 against 31 us, 10240 x 2560 35 / 38, 2560 x 2560 17 / 17, 1024 x 1024 10 / 8
-    if ((int64_t)cols * ((T + 127) / 128) >= 256)
-        BCQ_LAUNCH((fused_fwd_kernel<Q, 4, 4, GROUPED, true>), dim3(cols, (unsigned)((T + 127) / 128)), dim3(256), 0, st,
-                           packed, alpha, xo, y, T, N, K, g);
+    // (256 tokens, q = 4) 7680 x 2560 27 against 31 us, 10240 x 2560 35 / 38, 2560 x 2560 17 / 17, 1024 x 1024 10 / 8, and
+    // with the contraction split 2560 x 10240 48 / 53.
+    const int64_t wide_tiles = (int64_t)cols * ((T + 127) / 128);
+    const bool wide = T > 64 && (wide_tiles >= 256 || (wide_tiles >= 64 && units >= 64));
+    const int W = T <= 32 ? 8 : 4, tile = T <= 32 ? 32 : wide ? 128 : 64;
+    const unsigned tiles = (unsigned)((T + tile - 1) / tile);
+    // Few rows and a long contraction: parts of it go to workgroups of their own while they still find an idle compute
+    // unit and every wave keeps a unit (2048 x 8192, groups of 128, 4 tokens: 25.2 -> 12.5 us, 1024 x 4096 at 32 tokens
+    // 16.5 -> 9.7; below 2048 columns the extra launch costs more, 1024 x 1024 at 96 tokens 8 -> 9).
+    int parts = 1;
+    while (units >= 16 && cols * tiles * parts * 2 <= (wide ? 512u : 256u) && units >= 2 * W * parts &&
+           order_bytes(T, K) + sums_bytes(T, N, 2 * parts) <= mfma_fwd_workspace(N, K))
+        parts *= 2;
+    const int per = (units + parts - 1) / parts;
+    parts = (units + per - 1) / per;
+    float* sums = parts > 1 ? reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + order_bytes(T, K)) : nullptr;
+    const dim3 grid(cols, tiles, (unsigned)parts), block(64 * W);
+    if (T <= 32)
+        BCQ_LAUNCH((fused_fwd_kernel<Q, 1, 8, GROUPED, false>), grid, block, 0, st, packed, alpha, xo, y, T, N, K, g, per,
+                           sums);
+    else if (wide)
+        BCQ_LAUNCH((fused_fwd_kernel<Q, 4, 4, GROUPED, true>), grid, block, 0, st, packed, alpha, xo, y, T, N, K, g, per,
+                           sums);
     else
-        BCQ_LAUNCH((fused_fwd_kernel<Q, 2, 4, GROUPED, true>), dim3(cols, (unsigned)((T + 63) / 64)), dim3(256), 0, st,
-                           packed, alpha, xo, y, T, N, K, g);
+        BCQ_LAUNCH((fused_fwd_kernel<Q, 2, 4, GROUPED, true>), grid, block, 0, st, packed, alpha, xo, y, T, N, K, g, per,
+                           sums);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || parts == 1) return e;
+    BCQ_LAUNCH(sum_parts_kernel, dim3((unsigned)((T * ((N + 3) / 4) + 255) / 256)), dim3(256), 0, st, sums, parts, T, N, y);
     return hipGetLastError();
 }
 
@@ -307,7 +355,7 @@ static hipError_t launch_q(const uint32_t* packed, const float* alpha, const bf1
 // activations of more than 32 tokens take the place of the expanded weights in the workspace.
 bool fused_fwd_ok(int64_t T, int64_t N, int64_t K, int q) {
     if (q > 4 || T > 384) return false;
-    return T <= 32 || (size_t)((T + 31) / 32 * 32 * K * 2) <= mfma_fwd_workspace(N, K);
+    return order_bytes(T, K) <= mfma_fwd_workspace(N, K);
 }
 
 hipError_t launch_fwd_fused(const uint32_t* packed, const float* alpha, const void* x, int64_t T, int64_t N, int64_t K,

@@ -39,7 +39,9 @@ def test_expanded_weights_bit_exact(oracle, N, K, g, q):
 @pytest.mark.parametrize("T,N,K,g,q", [(1, 64, 64, 32, 3), (31, 35, 96, 96 // 3, 4), (32, 1056, 1024, 64, 2),
                                        (33, 96, 4128, 32, 4), (64, 33, 2048, 128, 3), (65, 130, 1056, 96, 1),
                                        (81, 70, 1056, 1056, 3), (128, 64, 320, 320, 4), (129, 257, 640, 640, 2),
-                                       (512, 40, 1024, 1024, 4), (300, 1500, 32, 32, 1)])
+                                       (512, 40, 1024, 1024, 4), (300, 1500, 32, 32, 1),
+                                       (4, 33, 2080, 32, 3), (40, 70, 8224, 8224, 2), (200, 1030, 8192, 8192, 1),
+                                       (1, 5, 16384, 64, 4), (100, 161, 3072, 96, 2)])
 def test_fused_forward(oracle, T, N, K, g, q):
     import paper_2210_03858_amd as bcq
     _, alpha, planes, packed, x, _ = make_case(1, "out", T, N, K, q, "bf16", oracle, extra=T + N, g=g)
