@@ -5,37 +5,26 @@
 // One workgroup of one to four waves per vector (a row, or one length-g group of a row), specialised by q.  The vector
 // (fp32) and one byte of sign pattern per element stay in LDS for all rounds, so W is read from HBM once.
 //
-// Arithmetic: every sum, the Cholesky solve and the level comparison are fp64; alpha is rounded to fp32 once at
+// Arithmetic: every sum, the solve (L D L^T) and the level comparison are fp64; alpha is rounded to fp32 once at
 // the end.  The loop stops early at a fixed point (round (2) changed nothing) and stops BEFORE a refit whose
-// Gram matrix is singular (a Cholesky pivot <= 1e-9 n: two planes equal or opposite, e.g. an all-zero vector),
+// Gram matrix is singular (a pivot <= 1e-9 n: two planes equal or opposite, e.g. an all-zero vector),
 // keeping the current pair.  Ties between two levels go to the larger level, ties between equal levels to the
 // larger pattern index (bit i of the pattern = plane i is +1).  Only the ORDER of the fp64 sums over the
 // elements is free.
 //
-// What bounds it: a round is a chain of two barriers, a cross-lane fp64 sum, the solve (about a dozen dependent fp64
-// divisions and roots at q = 3) and 2^q distances per element.  Therefore a round makes ONE pass over the elements (the
-// re-assignment and the next round's sums together), the Gram matrix is counted in integers from the pattern bytes
-// (its entries are n - 2 * disagreements, exact), only wave 0 solves, and the levels are sorted so that a distance
-// costs one subtraction, one strict comparison and its selects.  Four elements per lane, so that vectors of at most
-// 256 elements (groups) take one wave and no cross-wave step.  Measured: 1024 x 1024, q = 3, 15 rounds 735 -> 86 us
-// (a kernel for every q reduced 36 fp64 sums per round over four waves and solved in all of them).
+// What bounds it: a round is a chain of two barriers, a cross-lane fp64 sum, the solve (q dependent fp64 divisions; with
+// square roots and a division per entry a dozen at q = 3) and 2^q distances per element.  Therefore a round makes ONE
+// pass over the elements (the re-assignment and the next round's sums together), the Gram matrix is counted in integers
+// from the pattern bytes (its entries are n - 2 * disagreements, exact), only wave 0 solves, and the levels are sorted
+// so that a distance costs one subtraction, one strict comparison and its selects.  Four elements per lane, so that
+// vectors of at most 256 elements (groups) take one wave and no cross-wave step.  Measured: 1024 x 1024, q = 3, 15
+// rounds 735 -> 68 us (86 us with the sums through LDS shuffles and a Cholesky solve; before, a kernel for every q
+// reduced 36 fp64 sums per round over four waves and solved in all of them).
 #include "bcq_internal.h"
 
 namespace bcq {
 
 constexpr int ALT_MAX_WAVES = 4;
-
-// fp64 / integer sum over the wave; every lane returns with it
-__device__ __forceinline__ double wave_sum(double s) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-    return s;
-}
-__device__ __forceinline__ uint32_t wave_sum(uint32_t s) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += (uint32_t)__shfl_xor((int)s, off);
-    return s;
-}
 
 template <int Q>
 struct AltShared {
@@ -155,22 +144,20 @@ __global__ __launch_bounds__(64 * ALT_MAX_WAVES) void alternating_kernel(const f
     }
 
     for (int it = 0; it < iters; ++it) {
-        // ---- (1) Eq. ap4, by wave 0: Cholesky of the Gram matrix B^T B (diagonal = n), all lanes on the same numbers
+        // ---- (1) Eq. ap4, by wave 0: L D L^T of the Gram matrix B^T B (diagonal = n), all lanes on the same numbers
         if (wave == 0) {
-            double red[Q], L[Q][Q], y[Q];
-#pragma unroll
-            for (int i = 0; i < Q; ++i) red[i] = total_rhs(i);
+            double L[Q][Q], M[Q][Q], inv[Q], z[Q];  // G = L D L^T with unit diagonal in L, M = L D, inv = 1 / D
             bool singular = false;
 #pragma unroll
             for (int j = 0; j < Q; ++j) {
                 if (!singular) {
                     double d = (double)n;
 #pragma unroll
-                    for (int p = 0; p < j; ++p) d -= L[j][p] * L[j][p];
+                    for (int p = 0; p < j; ++p) d -= M[j][p] * L[j][p];
                     if (!(d > 1e-9 * (double)n)) {
                         singular = true;
                     } else {
-                        L[j][j] = sqrt(d);
+                        inv[j] = 1.0 / d;
 #pragma unroll
                         for (int i = j + 1; i < Q; ++i) {
                             const int pr = i * (i - 1) / 2 + j;
@@ -178,8 +165,9 @@ __global__ __launch_bounds__(64 * ALT_MAX_WAVES) void alternating_kernel(const f
                             for (int u = 0; u < waves; ++u) cnt += (sh.disagree[u][pr >> 1] >> (16 * (pr & 1))) & 0xFFFFu;
                             double s = (double)(n - 2 * (int)cnt);
 #pragma unroll
-                            for (int p = 0; p < j; ++p) s -= L[i][p] * L[j][p];
-                            L[i][j] = s / L[j][j];
+                            for (int p = 0; p < j; ++p) s -= M[i][p] * L[j][p];
+                            M[i][j] = s;
+                            L[i][j] = s * inv[j];
                         }
                     }
                 }
@@ -187,17 +175,16 @@ __global__ __launch_bounds__(64 * ALT_MAX_WAVES) void alternating_kernel(const f
             if (!singular) {  // uniform: all lanes hold the same numbers
 #pragma unroll
                 for (int i = 0; i < Q; ++i) {
-                    double s = red[i];
+                    z[i] = total_rhs(i);
 #pragma unroll
-                    for (int p = 0; p < i; ++p) s -= L[i][p] * y[p];
-                    y[i] = s / L[i][i];
+                    for (int p = 0; p < i; ++p) z[i] -= L[i][p] * z[p];
                 }
 #pragma unroll
                 for (int i = Q - 1; i >= 0; --i) {
-                    double s = y[i];
+                    double s = z[i] * inv[i];
 #pragma unroll
                     for (int p = i + 1; p < Q; ++p) s -= L[p][i] * a[p];
-                    a[i] = s / L[i][i];
+                    a[i] = s;
                 }
                 // levels of the new alpha, sorted by (level, pattern) downwards.  The slots are filled in pattern order
                 // first: with non-finite levels the ranks need not be a permutation.

@@ -31,6 +31,44 @@ template <> struct Elem<bf16_t> {
     __device__ static __forceinline__ void store(bf16_t* p, float v) { *p = f32_to_bf16(v); }
 };
 
+// ---- Cross-lane moves inside a row of 16 lanes (data-parallel primitives of the vector ALU: a few cycles, where a trip
+// through the LDS crossbar costs a hundred).  Every pattern used here is a permutation, so all lanes receive a value.
+constexpr int DPP_XOR1 = 0xB1;         // quad_perm [1, 0, 3, 2]
+constexpr int DPP_XOR2 = 0x4E;         // quad_perm [2, 3, 0, 1]
+constexpr int DPP_QUAD_REVERSE = 0x1B; // quad_perm [3, 2, 1, 0]
+constexpr int DPP_HALF_MIRROR = 0x141; // lane i of each 8 takes lane 7 - i
+constexpr int DPP_MIRROR = 0x140;      // lane i of each 16 takes lane 15 - i
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+    return __hiloint2double((int)dpp_move<CTRL>((uint32_t)__double2hiint(v)), (int)dpp_move<CTRL>((uint32_t)__double2loint(v)));
+}
+
+// sum over the 64 lanes of a wave, the same value in every lane: four exchange steps inside each row of 16, then
+// the four row sums through scalar registers
+__device__ __forceinline__ double wave_sum(double s) {
+    s += dpp_move<DPP_XOR1>(s);
+    s += dpp_move<DPP_XOR2>(s);
+    s += dpp_move<DPP_HALF_MIRROR>(s);
+    s += dpp_move<DPP_MIRROR>(s);
+    auto row = [&](int l) {
+        return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(s), l), __builtin_amdgcn_readlane(__double2loint(s), l));
+    };
+    return (row(0) + row(16)) + (row(32) + row(48));
+}
+__device__ __forceinline__ uint32_t wave_sum(uint32_t s) {
+    s += dpp_move<DPP_XOR1>(s);
+    s += dpp_move<DPP_XOR2>(s);
+    s += dpp_move<DPP_HALF_MIRROR>(s);
+    s += dpp_move<DPP_MIRROR>(s);
+    auto row = [&](int l) { return (uint32_t)__builtin_amdgcn_readlane((int)s, l); };
+    return (row(0) + row(16)) + (row(32) + row(48));
+}
+
 // ---- AdamW on the trained scales (Appendix A; decoupled weight decay) ---------------------------
 // Device pointers to the scales and their two moment buffers (fp32, same shape as the scale gradient) plus the
 // step's constants; alpha == nullptr means "no update".  inv_bc = 1 / (1 - beta^t), formed in fp64 on the host.

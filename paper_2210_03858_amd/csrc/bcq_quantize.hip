@@ -188,36 +188,6 @@ __global__ void zero_word_kernel(int* p) { *p = 0; }
 // collected after 8 chunks holds one nibble per chunk; the 32-column words of the canonical layout need one nibble
 // from each of 8 neighbouring lanes instead, which is an 8 x 8 nibble transpose inside every group of 8 lanes:
 // three exchange steps per 2048 columns and plane.
-// Cross-lane moves inside a row of 16 lanes (data-parallel primitives of the vector ALU: a few cycles, where a trip
-// through the LDS crossbar costs a hundred).  Every pattern used here is a permutation, so all lanes receive a value.
-constexpr int DPP_XOR1 = 0xB1;         // quad_perm [1, 0, 3, 2]
-constexpr int DPP_XOR2 = 0x4E;         // quad_perm [2, 3, 0, 1]
-constexpr int DPP_QUAD_REVERSE = 0x1B; // quad_perm [3, 2, 1, 0]
-constexpr int DPP_HALF_MIRROR = 0x141; // lane i of each 8 takes lane 7 - i
-constexpr int DPP_MIRROR = 0x140;      // lane i of each 16 takes lane 15 - i
-
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_move(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double v) {
-    return __hiloint2double((int)dpp_move<CTRL>((uint32_t)__double2hiint(v)), (int)dpp_move<CTRL>((uint32_t)__double2loint(v)));
-}
-
-// sum over the 64 lanes of a wave, the same value in every lane: four exchange steps inside each row of 16, then
-// the four row sums through scalar registers
-__device__ __forceinline__ double wave_sum_f64(double s) {
-    s += dpp_move<DPP_XOR1>(s);
-    s += dpp_move<DPP_XOR2>(s);
-    s += dpp_move<DPP_HALF_MIRROR>(s);
-    s += dpp_move<DPP_MIRROR>(s);
-    auto row = [&](int l) {
-        return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(s), l), __builtin_amdgcn_readlane(__double2loint(s), l));
-    };
-    return (row(0) + row(16)) + (row(32) + row(48));
-}
-
 template <int D>
 __device__ __forceinline__ uint32_t nibble_exchange(uint32_t x, bool upper) {
     constexpr uint32_t LOW = D == 4 ? 0x0000FFFFu : D == 2 ? 0x00FF00FFu : 0x0F0F0F0Fu;
@@ -290,7 +260,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const float* __restr
                 x = nibble_exchange<2>(x, (j & 2) != 0);
                 X[g] = ~nibble_exchange<1>(x, (j & 1) != 0);  // 1 <=> +1 <=> sign bit clear
             }
-            const double s = wave_sum_f64(s0 + s1);
+            const double s = bcq::wave_sum(s0 + s1);
             double S = s;
             if constexpr (NW > 1) {
                 double* ws = wave_sum[par];  // two sets in turn: one barrier per plane is enough
