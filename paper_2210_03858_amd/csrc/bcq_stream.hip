@@ -314,25 +314,28 @@ hipError_t launch_fwd_stream_decode(const uint32_t* tiled, const float* alpha, c
 
 // canonical packed[q][N][K/32] -> decode layout [N/16 up][K/512 up][q][64 lanes][4 words]; lane = (n % 16) + 16 g holds
 // words 16 seg + 4 g .. + 3 of row n; rows and columns beyond the matrix read as 0 bits
-__global__ __launch_bounds__(256) void pack_decode_kernel(const uint32_t* __restrict__ packed, int64_t N, int64_t cw,
-                                                          int q, int64_t segs, int64_t units,
+// A wave writes one KiB (row tile, segment, plane); the grid is (four segments, row tile, plane), so that no lane divides (10240 x 2560,
+// q = 4: 9.6 -> 6.5 us; 26 MB in and out take 5.2 us at the rate of a large copy).
+// QUAD: rows of whole 16-byte units (cw % 4 == 0), one load per lane.
+template <bool QUAD>
+__global__ __launch_bounds__(256) void pack_decode_kernel(const uint32_t* __restrict__ packed, int64_t N, int cw, int segs,
                                                           q_u32x4* __restrict__ tiled) {
-    const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;  // one 16-byte unit of the output
-    if (u >= units) return;
-    const int lane = (int)(u & 63);
-    const int i = (int)((u >> 6) % q);
-    const int64_t ts = (u >> 6) / q;
-    const int64_t seg = ts % segs, rt = ts / segs;
-    const int64_t n = rt * 16 + (lane & 15);
-    const int64_t w0 = seg * 16 + 4 * (lane >> 4);
+    const int lane = threadIdx.x & 63, seg = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+    if (seg >= segs) return;
+    const int64_t rt = blockIdx.y, n = rt * 16 + (lane & 15);
+    const int w0 = 16 * seg + 4 * (lane >> 4);
     q_u32x4 v = {0u, 0u, 0u, 0u};
     if (n < N) {
-        const uint32_t* src = packed + ((int64_t)i * N + n) * cw;
+        const uint32_t* src = packed + ((int64_t)blockIdx.z * N + n) * cw + w0;
+        if (QUAD) {
+            if (w0 < cw) v = *reinterpret_cast<const q_u32x4*>(src);
+        } else {
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj)
-            if (w0 + jj < cw) v[jj] = src[w0 + jj];
+            for (int jj = 0; jj < 4; ++jj)
+                if (w0 + jj < cw) v[jj] = src[jj];
+        }
     }
-    tiled[u] = v;
+    tiled[((rt * segs + seg) * gridDim.z + blockIdx.z) * 64 + lane] = v;
 }
 
 size_t decode_layout_bytes(int64_t N, int64_t K, int q) {
@@ -340,10 +343,12 @@ size_t decode_layout_bytes(int64_t N, int64_t K, int q) {
 }
 
 hipError_t launch_pack_decode(const uint32_t* packed, int64_t N, int64_t K, int q, uint32_t* tiled, hipStream_t st) {
-    const int64_t segs = (K + 511) / 512;
-    const int64_t units = (int64_t)(decode_layout_bytes(N, K, q) / 16);
-    BCQ_LAUNCH(pack_decode_kernel, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, st, packed, N, K / 32, q, segs,
-                       units, reinterpret_cast<q_u32x4*>(tiled));
+    const int segs = (int)((K + 511) / 512), cw = (int)(K / 32);
+    const dim3 grid((unsigned)((segs + 3) / 4), (unsigned)((N + 15) / 16), (unsigned)q);
+    if (cw % 4 == 0)
+        BCQ_LAUNCH(pack_decode_kernel<true>, grid, dim3(256), 0, st, packed, N, cw, segs, reinterpret_cast<q_u32x4*>(tiled));
+    else
+        BCQ_LAUNCH(pack_decode_kernel<false>, grid, dim3(256), 0, st, packed, N, cw, segs, reinterpret_cast<q_u32x4*>(tiled));
     return hipGetLastError();
 }
 
