@@ -30,7 +30,9 @@
  *     contents before the call are ignored and after the call are unspecified (except where an
  *     entry point documents a status word).  Pass NULL / 0 to make the library choose a path that
  *     needs none (always available, possibly slower).  bcq_workspace_bytes() gives the size that
- *     enables the fastest path; a non-NULL workspace smaller than that is BCQ_ERR_WORKSPACE.
+ *     enables the fastest path; a non-NULL workspace smaller than that is BCQ_ERR_WORKSPACE, except
+ *     for the backward products of bf16 calls whose N is no multiple of 8 (input gradient: of 32),
+ *     which then run on the path without one.
  *   - Return value: BCQ_OK or the first problem found; nothing is enqueued unless BCQ_OK.
  *     Order of checks: NULL pointers, shapes, dtype, alignment, workspace, device.
  *   - Limits: 1 <= q <= 8; K % 32 == 0; 1 <= N, K <= 2^17; 1 <= T <= 2^24; N*K and T*max(N,K) at most 2^40.
@@ -42,7 +44,8 @@
  *     stays fp32.  The streaming paths (few tokens) multiply exact signs with activations split into two FP8 terms:
  *     exact for bf16 activations within 2^-13 of the largest of their 32-element block (forward, scale gradient); the
  *     input gradient re-codes the fp32 product dy * alpha_i and keeps 8 significant bits of it (relative 2^-9 per
- *     term).  Without a workspace, and for fp32 activations, no such rounding happens.
+ *     term).  Without a workspace, for fp32 activations and for row counts that are no multiple of 8 (input
+ *     gradient) no such rounding happens: those sums are fp64, or multiply 24-bit What.
  *   - Non-finite activations: a token row of x or dy that holds an Inf or NaN makes the outputs of that token
  *     non-finite and leaves every other token's outputs untouched (the scale gradient sums over tokens and becomes
  *     non-finite as a whole); the streaming paths return NaN for every output of such a token.
