@@ -608,9 +608,11 @@ hipError_t launch_bwd_input_mfma(const uint32_t* packed, const uint32_t* packed_
 }
 
 // Input gradient with fp32 weights for row counts (or token counts) that launch_bwd_input_mfma does not take: dX = [dY dY
-// dY] [lo; mid; hi], the same contraction three times as long, on the same kernel.
+// dY] [lo; mid; hi], the same contraction three times as long, on the same kernel.  Tokens are taken SPLIT_TOKENS at a
+// time, which bounds the copies (50257 rows: 1.2 GB) and still fills the chip.
+constexpr int64_t SPLIT_TOKENS = 4096;
 size_t mfma_bwd_input_split_workspace(int64_t T, int64_t N, int64_t K) {
-    return (size_t)(3 * round_up(N, RPAD) * 2 * (T + round_up(K, 32)));
+    return (size_t)(3 * round_up(N, RPAD) * 2 * ((T < SPLIT_TOKENS ? T : SPLIT_TOKENS) + round_up(K, 32)));
 }
 
 hipError_t launch_bwd_input_mfma_split(const uint32_t* packed, const uint32_t* packed_t, const float* alpha,
@@ -619,13 +621,16 @@ hipError_t launch_bwd_input_mfma_split(const uint32_t* packed, const uint32_t* p
     const int64_t P = round_up(N, RPAD), R16 = P / 16;
     u32x4* frag = (u32x4*)workspace;
     u32x4* rows = frag + round_up(K, 32) * 3 * P / 8;
-    BCQ_LAUNCH((pad_act_kernel<3>), dim3((unsigned)((T * (P / 8) + 255) / 256)), dim3(256), 0, st, (const bf16_t*)dy, T, N,
-                       P, rows);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = launch_expand_bwd<true>(packed, packed_t, alpha, N, K, g, q, R16, frag, st);
-    if (e != hipSuccess) return e;
-    return launch_gemm((const bf16_t*)rows, 3 * P, frag, (bf16_t*)dx, K, T, K, 3 * P, 3 * R16, st);
+    hipError_t e = launch_expand_bwd<true>(packed, packed_t, alpha, N, K, g, q, R16, frag, st);
+    for (int64_t t0 = 0; t0 < T && e == hipSuccess; t0 += SPLIT_TOKENS) {
+        const int64_t M = T - t0 < SPLIT_TOKENS ? T - t0 : SPLIT_TOKENS;
+        BCQ_LAUNCH((pad_act_kernel<3>), dim3((unsigned)((M * (P / 8) + 255) / 256)), dim3(256), 0, st,
+                           (const bf16_t*)dy + t0 * N, M, N, P, rows);
+        e = hipGetLastError();
+        if (e == hipSuccess)
+            e = launch_gemm((const bf16_t*)rows, 3 * P, frag, (bf16_t*)dx + t0 * K, K, M, K, 3 * P, 3 * R16, st);
+    }
+    return e;
 }
 
 
