@@ -11,8 +11,9 @@
 // chosen to put every compute unit to work: one workgroup per 16 output columns, its eight waves share the
 // contraction and add their tiles in wave order through LDS (bit-reproducible).
 // Measured against one wave per row / one thread per column on the vector ALU (which read every activation once per
-// plane and ran the contraction over N serially): forward, input and scale gradient of 1024 x 1024 at 32 fp32 tokens
-// 755 -> 150 us, of 1500 x 1056 at 333 bf16 tokens 1941 -> 157 us, both now with the host as the slower side.
+// plane and ran the contraction over N serially), kernel times: 1024 x 1024 at 32 fp32 tokens forward 26 -> 9, input
+// gradient 685 -> 10, scale gradient 42 -> 14 us; 1500 x 1056 at 333 bf16 tokens input gradient 1347 -> 52, scale
+// gradient 527 -> 70 us (with a workspace the padded forms of bcq_mfma.hip take these from there on).
 //
 // Lane layout (checked by measurement): lane l holds A[row l % 16][k l / 16], B[k l / 16][col l % 16] and, in
 // accumulator register r, D[row 4 r + l / 16][col l % 16].  The contraction index of a lane group may be any
