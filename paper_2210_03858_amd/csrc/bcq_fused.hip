@@ -223,10 +223,18 @@ __global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __res
                     fu_u32x4 second[4];
                     float as[Q];
                     load_alpha(4 * u + 2 * pr + 1, as);
+                    if (4 * u + 2 * pr + 1 >= Kw) {  // no such columns: zero weights, as Inf times a zero activation is NaN
+#pragma unroll
+                        for (int i = 0; i < Q; ++i) as[i] = 0.f;
+                    }
                     table.build(as);
                     expand32<Q>(own[pr], table, second);
                     frag[2] = second[2];
                     frag[3] = second[3];
+                }
+                if (!GROUPED && 4 * u + 2 * pr + 1 >= Kw) {  // the same for row-wise scales
+                    frag[2] = zero;
+                    frag[3] = zero;
                 }
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {

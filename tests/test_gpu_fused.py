@@ -49,3 +49,17 @@ def test_fused_forward(oracle, T, N, K, g, q):
                                    workspace=_workspace(bcq, T, N, K, g, q))
     ref = oracle.fwd(alpha.reshape(q, N) if g == K else alpha, planes, x)
     assert nmax_err(to_host(y), ref) <= 1e-2
+
+
+@pytest.mark.parametrize("T,N,K,g,q", [(8, 40, 96, 32, 2), (40, 40, 96, 32, 4), (100, 200, 160, 160, 1), (300, 8200, 160, 160, 3)])
+def test_infinite_scale_stays_in_its_row(oracle, T, N, K, g, q):
+    """Columns beyond an odd number of words are zero activations: an infinite scale must not meet them."""
+    import paper_2210_03858_amd as bcq
+    import torch
+    _, alpha, _, packed, _, _ = make_case(1, "out", T, N, K, q, "bf16", oracle, g=g)
+    packed, alpha = packed.copy(), alpha.reshape(q, N, K // g).copy()
+    packed[:, 3], alpha[0, 3] = 0xFFFFFFFF, np.inf
+    x = torch.rand((T, K), device="cuda").add_(0.5).bfloat16()
+    y = bcq.bcq_linear_fwd_grouped(packed_to_dev(packed), to_dev(alpha), x, g, workspace=_workspace(bcq, T, N, K, g, q))
+    assert (y[:, 3] == float("inf")).all()
+    assert torch.cat((y[:, :3], y[:, 4:]), dim=1).isfinite().all()
