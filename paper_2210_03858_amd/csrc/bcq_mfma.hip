@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256) void expand_fwd_kernel(const uint32_t* __restr
 // (the 32 lanes of a column tile share a word and each takes its own bit).  The scales of the block's 256 rows
 // pass through LDS.
 // SPLIT: What is written as three bf16 terms hi + mid + lo (24 significant bits, all of the fp32 sum), one after the
-// other along the contraction, smallest first; a value that has no finite bf16 form is its first term alone.
+// other along the contraction, smallest first; an Inf or NaN is its first term alone.
 template <bool TWIN, bool SPLIT>
 __global__ __launch_bounds__(256) void expand_bwd_kernel(const uint32_t* __restrict__ planes,
                                                          const float* __restrict__ alpha, int64_t N, int64_t K,
@@ -208,15 +208,40 @@ __global__ __launch_bounds__(256) void expand_bwd_kernel(const uint32_t* __restr
         store_word_frags(s, frag, ct * R16 + 2 * v, c);
         return;
     }
-    store_word_frags(s, frag, (ct * 3 + 2) * R16 + 2 * v, c);
+    // A finite sum that would round beyond the largest bf16 value stops there and leaves the rest to the next terms.  Lanes
+    // without any (their largest magnitude says so) take two operations per value and term.
+    constexpr uint32_t BF16_LARGEST = 0x7F7F0000u;
+    uint32_t top = 0u;
 #pragma unroll
-    for (int term = 1; term >= 0; --term) {
+    for (int e = 0; e < 32; ++e) {
+        const uint32_t m = __float_as_uint(s[e]) & 0x7FFFFFFFu;
+        top = m > top ? m : top;
+    }
+    const bool ordinary = top <= BF16_LARGEST;
 #pragma unroll
-        for (int e = 0; e < 32; ++e) {
-            const float t = bf16_to_f32(f32_to_bf16(s[e]));
-            s[e] = fabsf(t) <= 3.4028234e38f ? s[e] - t : 0.f;  // exact
+    for (int term = 2; term >= 0; --term) {
+        float t[32];
+#pragma unroll
+        for (int p = 0; p < 16; ++p) {
+            const uint32_t r = pack_bf16x2(s[2 * p], s[2 * p + 1]);
+            t[2 * p] = __uint_as_float(r << 16);
+            t[2 * p + 1] = __uint_as_float(r & 0xFFFF0000u);
         }
-        store_word_frags(s, frag, (ct * 3 + term) * R16 + 2 * v, c);
+        if (!ordinary) {
+            const float largest = __uint_as_float(BF16_LARGEST);
+#pragma unroll
+            for (int e = 0; e < 32; ++e) {
+                const bool finite = (__float_as_uint(s[e]) & 0x7FFFFFFFu) < 0x7F800000u;
+                t[e] = finite ? fminf(fmaxf(t[e], -largest), largest) : s[e];
+            }
+        }
+        store_word_frags(t, frag, (ct * 3 + term) * R16 + 2 * v, c);
+#pragma unroll
+        for (int e = 0; e < 32; ++e) s[e] -= t[e];  // exact
+        if (!ordinary) {
+#pragma unroll
+            for (int e = 0; e < 32; ++e) s[e] = (__float_as_uint(t[e]) & 0x7FFFFFFFu) < 0x7F800000u ? s[e] : 0.f;
+        }
     }
 }
 

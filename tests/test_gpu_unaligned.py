@@ -39,7 +39,7 @@ def test_unaligned_input_gradient_keeps_infinities_and_nan(oracle):
     T, N, K, q = 260, 1500, 1056, 2
     _, alpha, planes, packed, _, dy = make_case(1, "out", T, N, K, q, "bf16", oracle)
     dy[3, 70], dy[9, 5], dy[20, 1499] = np.inf, np.nan, -np.inf
-    alpha = alpha.reshape(q, N, 1)  # ordinary scales: a weight above 3.39e38 has no finite first term (bf16's range)
+    alpha = alpha.reshape(q, N, 1)
     args = packed_to_dev(packed), to_dev(alpha), to_dev(dy, "bf16"), K
     ref = bcq.bcq_linear_bwd_input_grouped(*args).float()  # without a workspace: one fp64 sum
     got = bcq.bcq_linear_bwd_input_grouped(*args, workspace=_ws(bcq, 2, T, N, K, K, q, False)).float()
@@ -47,3 +47,20 @@ def test_unaligned_input_gradient_keeps_infinities_and_nan(oracle):
         finite = ref[t].isfinite()
         assert torch.equal(finite, got[t].isfinite()) and torch.equal(ref[t].isnan(), got[t].isnan())
         assert torch.equal(ref[t][~finite & ~ref[t].isnan()], got[t][~finite & ~ref[t].isnan()])
+
+
+@pytest.mark.parametrize("scale", [3.4e38, -3.3961776e38, 1e-37])
+def test_unaligned_input_gradient_at_the_ends_of_the_weights_range(oracle, scale):
+    """Weights beyond bf16's largest value, and ones whose lower terms are subnormal bf16 values (and may be flushed, which
+    leaves 16 significant bits): one rounding of the result, as for all others."""
+    import paper_2210_03858_amd as bcq
+    T, N, K = 260, 1500, 1056
+    _, alpha, _, packed, _, dy = make_case(1, "out", T, N, K, 1, "bf16", oracle)
+    alpha, dy = alpha.reshape(1, N, 1).copy(), dy.copy()
+    alpha[0, 7], dy[:, 7], dy[5] = scale, 0.0, 0.0
+    dy[5, 7] = 2.0 ** -20 if abs(scale) > 1.0 else 2.0 ** 20
+    args = packed_to_dev(packed), to_dev(alpha), to_dev(dy, "bf16"), K
+    ref = bcq.bcq_linear_bwd_input_grouped(*args).double()  # without a workspace: one fp64 sum
+    got = bcq.bcq_linear_bwd_input_grouped(*args, workspace=_ws(bcq, 2, T, N, K, K, 1, False)).double()
+    assert ref.isfinite().all() and got.isfinite().all()
+    assert ((got - ref).abs().amax(1) <= 1.05 * 2.0 ** -7 * ref.abs().amax(1)).all()  # each rounds once
