@@ -1048,7 +1048,7 @@ struct DalphaPlan {
     int tiles_k, tiles_n, splits;
     int64_t per_split, T16;
     bool xg, fine;
-    size_t frag_bytes, part_bytes, pad_bytes;
+    size_t frag_bytes, part_bytes;
 };
 
 static DalphaPlan dalpha_plan(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
@@ -1068,35 +1068,50 @@ static DalphaPlan dalpha_plan(int64_t T, int64_t N, int64_t K, int64_t g, int q)
     pl.frag_bytes = (size_t)(((gcols + 31) / 32) * pl.T16 * 1024);
     pl.fine = (g != K) && (g % DA_TILE != 0);  // groups that are not whole k tiles need per-32-column partials
     pl.part_bytes = (size_t)pl.splits * pl.tiles_k * q * N * sizeof(float) * (pl.fine ? 8 : 1);
-    // rows of dy that are not 16-byte aligned are copied into padded ones first
-    pl.pad_bytes = N % 8 ? (size_t)(T * round_up(N, 8) * 2) : 0;
     return pl;
 }
 
-size_t mfma_bwd_alpha_workspace(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
-    const DalphaPlan pl = dalpha_plan(T, N, K, g, q);
-    return pl.frag_bytes + (pl.part_bytes + 15) / 16 * 16 + pl.pad_bytes;
+// Rows of dy that are not 16-byte aligned are copied into padded ones, this many tokens at a time (a multiple of 64): the
+// copy stays below 512 MiB (50257 rows: 5312 tokens), and the partial sums of all pieces are added at the end.
+static int64_t dalpha_piece(int64_t T, int64_t N) {
+    if (N % 8 == 0) return T;
+    int64_t piece = ((int64_t)1 << 29) / (2 * round_up(N, 8)) / 64 * 64;
+    if (piece > ((int64_t)1 << 20)) piece = (int64_t)1 << 20;
+    return T < piece ? T : piece;
 }
 
-hipError_t launch_bwd_alpha_mfma(const uint32_t* packed, const void* x, const void* dy, int64_t T, int64_t N,
-                                 int64_t K, int64_t g, int q, int q_train, float grad_scale, float* dalpha,
-                                 void* workspace, const AdamWArgs* opt, hipStream_t st) {
-    const int lds = 3 * DA_STAGE;
-    const DalphaPlan pl = dalpha_plan(T, N, K, g, q);
-    u32x4* frag = reinterpret_cast<u32x4*>(workspace);
-    float* part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(workspace) + pl.frag_bytes);
-    int64_t dcols = N;
-    if (pl.pad_bytes) {
-        dcols = round_up(N, 8);
-        u32x4* rows = reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(part) + (pl.part_bytes + 15) / 16 * 16);
-        BCQ_LAUNCH((pad_act_kernel<1>), dim3((unsigned)((T * (dcols / 8) + 255) / 256)), dim3(256), 0, st, (const bf16_t*)dy,
-                           T, N, dcols, rows);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        dy = rows;
+struct DalphaScratch {
+    size_t frag, part, pad;  // bytes: fragments of a piece, partial sums of all pieces, padded copy of a piece
+    int splits;              // token slices of all pieces
+};
+static DalphaScratch dalpha_scratch(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
+    const int64_t piece = dalpha_piece(T, N), whole = T / piece, rest = T % piece;
+    const DalphaPlan a = dalpha_plan(piece, N, K, g, q);
+    DalphaScratch s = {a.frag_bytes, (size_t)whole * a.part_bytes, 0, (int)whole * a.splits};
+    if (rest) {
+        const DalphaPlan b = dalpha_plan(rest, N, K, g, q);
+        s.part += b.part_bytes;
+        s.splits += b.splits;
     }
-    const bf16_t* gact = (const bf16_t*)(pl.xg ? x : dy);
-    const bf16_t* lact = (const bf16_t*)(pl.xg ? dy : x);
+    if (N % 8) {
+        s.part = (s.part + 15) / 16 * 16;
+        s.pad = (size_t)(piece * round_up(N, 8) * 2);
+    }
+    return s;
+}
+
+size_t mfma_bwd_alpha_workspace(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
+    const DalphaScratch s = dalpha_scratch(T, N, K, g, q);
+    return s.frag + s.part + s.pad;
+}
+
+// Partial sums of T tokens into `part`: transposition of one activation, then the product
+static hipError_t launch_dalpha_piece(const uint32_t* packed, const bf16_t* x, const bf16_t* dy, int64_t dcols, int64_t T,
+                                      int64_t N, int64_t K, int q_train, const DalphaPlan& pl, u32x4* frag, float* part,
+                                      hipStream_t st) {
+    const int lds = 3 * DA_STAGE;
+    const bf16_t* gact = pl.xg ? x : dy;
+    const bf16_t* lact = pl.xg ? dy : x;
     const int64_t gcols = pl.xg ? K : dcols, lcols = pl.xg ? dcols : K;
     {
         dim3 grid((unsigned)((gcols + 127) / 128), (unsigned)((pl.T16 * 2 + 15) / 16));
@@ -1139,18 +1154,45 @@ hipError_t launch_bwd_alpha_mfma(const uint32_t* packed, const void* x, const vo
     }
 #undef BCQ_DA_Q
 #undef BCQ_DA_LAUNCH
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    return hipGetLastError();
+}
+
+hipError_t launch_bwd_alpha_mfma(const uint32_t* packed, const void* x, const void* dy, int64_t T, int64_t N,
+                                 int64_t K, int64_t g, int q, int q_train, float grad_scale, float* dalpha,
+                                 void* workspace, const AdamWArgs* opt, hipStream_t st) {
+    const DalphaScratch sc = dalpha_scratch(T, N, K, g, q);
+    const int64_t piece = dalpha_piece(T, N), dcols = sc.pad ? round_up(N, 8) : N;
+    unsigned char* ws = static_cast<unsigned char*>(workspace);
+    u32x4* frag = reinterpret_cast<u32x4*>(ws);
+    float* part = reinterpret_cast<float*>(ws + sc.frag);
+    float* next = part;
+    DalphaPlan pl;
+    for (int64_t t0 = 0; t0 < T; t0 += piece) {
+        const int64_t M = T - t0 < piece ? T - t0 : piece;
+        pl = dalpha_plan(M, N, K, g, q);
+        const bf16_t* rows = (const bf16_t*)dy + t0 * N;
+        if (sc.pad) {
+            u32x4* padded = reinterpret_cast<u32x4*>(ws + sc.frag + sc.part);
+            BCQ_LAUNCH((pad_act_kernel<1>), dim3((unsigned)((M * (dcols / 8) + 255) / 256)), dim3(256), 0, st, rows, M, N,
+                               dcols, padded);
+            hipError_t ep = hipGetLastError();
+            if (ep != hipSuccess) return ep;
+            rows = reinterpret_cast<const bf16_t*>(padded);
+        }
+        hipError_t ep = launch_dalpha_piece(packed, (const bf16_t*)x + t0 * K, rows, dcols, M, N, K, q_train, pl, frag, next, st);
+        if (ep != hipSuccess) return ep;
+        next += (int64_t)pl.splits * pl.tiles_k * q_train * N * (pl.fine ? 8 : 1);
+    }
     const int64_t rows = (int64_t)q_train * N, G = K / g;
     const dim3 rgrid((unsigned)((rows * G + 63) / 64));
     AdamWArgs oa = {};
     if (opt) oa = *opt;
     if (pl.fine)
         BCQ_LAUNCH(dalpha_reduce_fine_kernel, rgrid, dim3(256), 0, st, (const float*)part, dalpha, rows, G,
-                           pl.splits, (int64_t)pl.tiles_k * 8, (int)(g / 32), grad_scale, oa);
+                           sc.splits, (int64_t)pl.tiles_k * 8, (int)(g / 32), grad_scale, oa);
     else
         BCQ_LAUNCH(dalpha_reduce_kernel, rgrid, dim3(256), 0, st, (const float*)part, dalpha, rows, G,
-                           pl.splits, pl.tiles_k, (int)(g == K ? pl.tiles_k : g / DA_TILE), grad_scale, oa);
+                           sc.splits, pl.tiles_k, (int)(g == K ? pl.tiles_k : g / DA_TILE), grad_scale, oa);
     return hipGetLastError();
 }
 
