@@ -11,7 +11,7 @@ from . import binding as B
 
 
 class _Layer:
-    """Frozen state of one quantized layer: packed planes, optional transposed twin, workspaces by token count."""
+    """Frozen state of one quantized layer: packed planes and the optional transposed twin."""
 
     def __init__(self, packed, g, q_train, grad_scale, twin=True):
         self.packed = packed
@@ -21,14 +21,11 @@ class _Layer:
         self.q_train = self.q if q_train is None else int(q_train)
         self.grad_scale = float(grad_scale)
         self.twin = B.bcq_pack_transposed(packed) if (twin and self.N % 32 == 0) else None
-        self._ws = {}
 
     def workspace(self, op, T, dtype_code):
-        key = (op, T, dtype_code)
-        if key not in self._ws:
-            n = B.workspace_bytes_grouped(op, T, self.N, self.K, self.g, self.q, dtype_code)
-            self._ws[key] = torch.empty((max(n, 16),), dtype=torch.uint8, device=self.packed.device)
-        return self._ws[key]
+        """Scratch of one call, from torch's caching allocator: kept by nobody and never shared between streams."""
+        n = B.workspace_bytes_grouped(op, T, self.N, self.K, self.g, self.q, dtype_code)
+        return torch.empty((max(n, 16),), dtype=torch.uint8, device=self.packed.device)
 
 
 class BCQLinearFunction(torch.autograd.Function):

@@ -91,3 +91,11 @@ def test_bindings_keep_their_checks(layer):
         bcq.bcq_linear_fwd_grouped(L.packed, alpha, x, 48)
     with pytest.raises(bcq.BcqError):
         bcq.bcq_linear_bwd_alpha_grouped(L.packed, x, y, 64, q_train=4)
+
+
+def test_python_node_keeps_no_scratch(layer):
+    import torch
+    before = torch.cuda.memory_allocated()
+    for T in (100, 200, 300):
+        _apply(layer, torch.randn((T, 256), device="cuda").bfloat16())
+    assert torch.cuda.memory_allocated() == before
