@@ -8,6 +8,7 @@ if the shared library is missing, load() raises.
 """
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -27,7 +28,7 @@ EXPORTS = ("bcq_status_string", "bcq_abi_version", "bcq_workspace_bytes", "bcq_q
            "bcq_prepare", "bcq_batch_prepare")
 
 _lib = None
-_native = None
+_native = None  # False: not there
 
 
 class AdamW(ctypes.Structure):
@@ -103,20 +104,28 @@ def native():
     Its functions return None for everything but the plain case; the callers then go on in Python, which checks and
     raises."""
     global _native
-    if _native is None:
+    if not _native:
         load()
         try:
             from . import _bcq_torch
         except ImportError as e:
-            raise RuntimeError("_bcq_torch.so is missing or does not load: run `python -m paper_2210_03858_amd.build` "
-                               "(or __graft_entry__.build()) first") from e
+            raise RuntimeError("_bcq_torch.so is missing or does not load (%s): run `python -m paper_2210_03858_amd.build` "
+                               "(or __graft_entry__.build())" % e) from e
         _native = _bcq_torch
     return _native
 
 
 def _try_native(name, *args):
+    global _native
+    if _native is None:
+        load()  # without the kernels nothing runs
+        try:
+            native()
+        except RuntimeError as e:  # built for another torch, say: the same kernels are called through ctypes
+            _native = False
+            warnings.warn("%s; until then calls take the slower host path" % e, RuntimeWarning, stacklevel=3)
     try:
-        return getattr(_native or native(), name)(*args)
+        return getattr(_native, name)(*args) if _native else None
     except TypeError:  # an argument that is no tensor: the Python path says which
         return None
 
