@@ -124,10 +124,7 @@ def _try_native(name, *args):
         except RuntimeError as e:  # built for another torch, say: the same kernels are called through ctypes
             _native = False
             warnings.warn("%s; until then calls take the slower host path" % e, RuntimeWarning, stacklevel=3)
-    try:
-        return getattr(_native, name)(*args) if _native else None
-    except TypeError:  # an argument that is no tensor: the Python path says which
-        return None
+    return getattr(_native, name)(*args) if _native else None
 
 
 def status_string(status):

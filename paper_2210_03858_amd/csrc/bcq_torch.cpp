@@ -266,12 +266,20 @@ py::object linear(const Tensor& x, const Tensor& alpha_train, const OptTensor& a
     }
 }
 
+// Arguments of other types reach the second form, so that the caller need not catch the TypeError of a failed conversion
+// and take one that user code raised inside the call (a saved-tensor hook) for it.
+template <typename F>
+void define(py::module_& m, const char* name, F f) {
+    m.def(name, f);
+    m.def(name, [](const py::args&) -> py::object { return py::none(); });
+}
+
 }  // namespace
 
 PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
-    m.def("fwd_grouped", &fwd_grouped);
-    m.def("fwd_decode", &fwd_decode);
-    m.def("bwd_input_grouped", &bwd_input_grouped);
-    m.def("bwd_alpha_grouped", &bwd_alpha_grouped);
-    m.def("linear", &linear);
+    define(m, "fwd_grouped", &fwd_grouped);
+    define(m, "fwd_decode", &fwd_decode);
+    define(m, "bwd_input_grouped", &bwd_input_grouped);
+    define(m, "bwd_alpha_grouped", &bwd_alpha_grouped);
+    define(m, "linear", &linear);
 }

@@ -99,3 +99,31 @@ def test_python_node_keeps_no_scratch(layer):
     for T in (100, 200, 300):
         _apply(layer, torch.randn((T, 256), device="cuda").bfloat16())
     assert torch.cuda.memory_allocated() == before
+
+
+def test_type_error_of_a_hook_is_the_callers(layer):
+    """It is no sign of arguments that the native path does not take: the hook runs once."""
+    import torch
+    x = torch.randn((8, 256), device="cuda").bfloat16().requires_grad_(True)
+    calls = []
+
+    def pack(t):
+        calls.append(t)
+        raise TypeError("not this tensor")
+
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda t: t), pytest.raises(TypeError, match="not this tensor"):
+        layer(x)
+    assert len(calls) == 1
+
+
+def test_arguments_of_other_types(layer):
+    import torch
+    import paper_2210_03858_amd as bcq
+    L = layer._layer
+    alpha = torch.cat((layer.alpha_train, layer.alpha_frozen)).detach()
+    x = torch.randn((4, 256), device="cuda")
+    for args in ((L.packed, alpha.tolist(), x), (L.packed, alpha, x.cpu().numpy())):
+        with pytest.raises((ValueError, AttributeError)):
+            bcq.bcq_linear_fwd_grouped(*args, 64)
+    with pytest.raises((ValueError, AttributeError)):
+        bcq.bcq_linear_bwd_alpha_grouped(L.packed, x, None, 64)
