@@ -358,12 +358,32 @@ static hipError_t launch_q(const uint32_t* packed, const float* alpha, const bf1
     return hipGetLastError();
 }
 
-// Up to 384 tokens (q = 4, 10240 x 2560: 96 tokens 29 -> 17 us against two kernels, 256 tokens 46 -> 35, 400 tokens 54 -> 53;
-// from there on re-expanding the planes for every 128 tokens costs more than writing What once).  The re-ordered
-// activations of more than 32 tokens take the place of the expanded weights in the workspace.
-bool fused_fwd_ok(int64_t T, int64_t N, int64_t K, int q) {
-    if (q > 4 || T > 384) return false;
-    return order_bytes(T, K) <= mfma_fwd_workspace(N, K);
+// Where one kernel is faster than expanding What and multiplying (22 layers of 0.1 - 67 million weights, q = 1 .. 4, 10 to
+// 13 token counts, g = K, 32, 64, 96, 256 timed on both sides).  Row-wise scales: up to 384 tokens, 1.0 - 2.6 times (q = 4,
+// 10240 x 2560: 96 tokens 29 -> 17 us, 256 tokens 46 -> 35, 384 tokens 44 -> 43; 50257 x 1024 at 320 tokens 112 -> 117,
+// the only loss), from there on re-expanding the planes for every 128 tokens costs more than writing What once.
+// Group-wise scales: a unit of 128 columns also builds 2 tables of q loads and 2^(q - 1) sums, 4 when groups hold an odd
+// number of words, for every 128 tokens (64 in small layers) again, so the line moves down with q and that parity
+// (`level`), and less so where N K T is small and leaves the matrix product with few workgroups: 10240 x 2560, g = 64,
+// one kernel against two: q = 2, 256 tokens 34 / 42, 384 tokens 47 / 41; q = 4, 128 tokens 27 / 30, 192 tokens 51 / 38.
+// The rule keeps within 4 % of the faster side in 95 % of the 3380 group-wise calls timed and within 10 % in 98 %.
+// The re-ordered activations of more than 32 tokens take the place of the expanded weights in the workspace.
+bool fused_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
+    if (q > 4 || T > 384 || order_bytes(T, K) > mfma_fwd_workspace(N, K)) return false;
+    if (g == K || T <= 16) return true;
+    const bool odd = (g / 32) % 2 != 0;
+    const int level = q + (odd ? 1 : 0);
+    const int64_t work = N * K * T;
+    if (odd && q > 1 && T > 32 && N * K < 1200000) return false;  // 1024 x 1024, q = 4, 64 tokens: 14 / 11
+    switch (level) {
+        case 1: return true;
+        case 2: return T <= 256 || (!odd && work <= 8000000000);
+        case 5: return T <= 64 ? N <= 8192 : T <= 160 && N * T <= 320000;
+        default: break;
+    }
+    if (T <= 128) return true;
+    if (T <= 256) return odd ? N <= 4096 && work <= 1300000000 : work <= (level == 3 ? 4000000000 : 2500000000);
+    return !odd && T <= 320 && work <= 800000000;
 }
 
 hipError_t launch_fwd_fused(const uint32_t* packed, const float* alpha, const void* x, int64_t T, int64_t N, int64_t K,
