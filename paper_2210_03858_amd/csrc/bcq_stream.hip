@@ -169,7 +169,13 @@ constexpr int64_t FUSED_MAX_WAVES = 1024;
 // 6.3 -> 5.8 us, 4096 x 2048 6.7 -> 6.0 / 6.7 -> 6.3, but 5120 x 1280 (320 workgroups) 6.7 -> 6.6 / 6.7 -> 7.4 and
 // 2560 x 2560 (five waves) 6.8 -> 6.7 / 6.9 -> 7.4; more than 8 tokens re-code twice as much (3072 x 1024, 16: 6.6 -> 7.6).
 constexpr unsigned FUSED_TILED_MAX_WGS = 256;
-constexpr int FUSED_TILED_MAX_WAVES = 4;
+// More than four planes run the kernel of eight, whose sums leave room for few waves: 512 x 512, q = 8 7.2 -> 6.6 us, but
+// 4096 x 2048 8.2 -> 9.3.  Group-wise scales cost the single kernel more from three planes and four tokens on (4096 x 2048,
+// groups of 512, q = 4: one token 7.0 -> 6.9, eight 7.0 -> 7.3).
+static int fused_tiled_max_waves(int q, bool grouped, int64_t T) {
+    if (q > 4) return grouped ? 0 : 1;
+    return grouped && q > 2 && T > 4 ? 3 : 4;
+}
 
 template <int MODE, int QP, bool TWO, bool TILED>
 static hipError_t launch_fused_cfg(const uint32_t* planes, const bf16_t* act, const float* alpha, const bf16_t* dy,
@@ -215,7 +221,7 @@ static hipError_t launch_stream(const uint32_t* planes, const bf16_t* act, const
     const StreamPlan p = stream_plan(T, rows, cw, gsegs);
     if (p.W < 1 || p.W > 8 || p.R != 1) return hipErrorInvalidConfiguration;  // compiled for at most 512 threads, R = 1
     if constexpr (MODE != STREAM_DX) {
-        const bool fits = TILED ? p.halves == 1 && p.grid_x <= FUSED_TILED_MAX_WGS && p.W <= FUSED_TILED_MAX_WAVES
+        const bool fits = TILED ? p.halves == 1 && p.grid_x <= FUSED_TILED_MAX_WGS && p.W <= fused_tiled_max_waves(q_used, grouped, T)
                                 : (int64_t)p.grid_x * p.tiles * p.W <= FUSED_MAX_WAVES;
         if (p.segs_per_wave <= FUSED_MAX_SEGS && fits)
             return launch_fused<MODE, TILED>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st);
