@@ -320,15 +320,18 @@ hipError_t launch_fwd_stream_decode(const uint32_t* tiled, const float* alpha, c
 
 // canonical packed[q][N][K/32] -> decode layout [N/16 up][K/512 up][q][64 lanes][4 words]; lane = (n % 16) + 16 g holds
 // words 16 seg + 4 g .. + 3 of row n; rows and columns beyond the matrix read as 0 bits
-// A wave writes one KiB (row tile, segment, plane); the grid is (four segments, row tile, plane), so that no lane divides (10240 x 2560,
-// q = 4: 9.6 -> 6.5 us; 26 MB in and out take 5.2 us at the rate of a large copy).
+// A wave writes one KiB (row tile, segment, plane); the grid is (four segments, row tile, plane), so that no lane divides
+// (10240 x 2560, q = 4: 9.6 -> 6.5 us; 26 MB in and out take 5.2 us at the rate of a large copy).  Rows of one or two segments
+// put 1 << tiles_log2 row tiles into a workgroup instead: it is the workgroups' launch rate that bounds them (131072 x 64,
+// q = 8: 14 us with a division per lane, 31 us with one busy wave to a workgroup, of 64 or of 256 threads, 13 us so).
 // QUAD: rows of whole 16-byte units (cw % 4 == 0), one load per lane.
 template <bool QUAD>
-__global__ __launch_bounds__(256) void pack_decode_kernel(const uint32_t* __restrict__ packed, int64_t N, int cw, int segs,
+__global__ __launch_bounds__(256) void pack_decode_kernel(const uint32_t* __restrict__ packed, int64_t N, int cw, int segs, int tiles_log2,
                                                           q_u32x4* __restrict__ tiled) {
-    const int lane = threadIdx.x & 63, seg = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
-    if (seg >= segs) return;
-    const int64_t rt = blockIdx.y, n = rt * 16 + (lane & 15);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, segs_log2 = 2 - tiles_log2;
+    const int seg = (int)(blockIdx.x << segs_log2) + (wave & ((1 << segs_log2) - 1));
+    const int64_t rt = ((int64_t)blockIdx.y << tiles_log2) + (wave >> segs_log2), n = rt * 16 + (lane & 15);
+    if (seg >= segs || rt * 16 >= N) return;
     const int w0 = 16 * seg + 4 * (lane >> 4);
     q_u32x4 v = {0u, 0u, 0u, 0u};
     if (n < N) {
@@ -350,11 +353,12 @@ size_t decode_layout_bytes(int64_t N, int64_t K, int q) {
 
 hipError_t launch_pack_decode(const uint32_t* packed, int64_t N, int64_t K, int q, uint32_t* tiled, hipStream_t st) {
     const int segs = (int)((K + 511) / 512), cw = (int)(K / 32);
-    const dim3 grid((unsigned)((segs + 3) / 4), (unsigned)((N + 15) / 16), (unsigned)q);
+    const int tl = segs == 1 ? 2 : segs == 2 ? 1 : 0, rows = 16 << tl;
+    const dim3 grid((unsigned)((segs + 3) / 4), (unsigned)((N + rows - 1) / rows), (unsigned)q);
     if (cw % 4 == 0)
-        BCQ_LAUNCH(pack_decode_kernel<true>, grid, dim3(256), 0, st, packed, N, cw, segs, reinterpret_cast<q_u32x4*>(tiled));
+        BCQ_LAUNCH(pack_decode_kernel<true>, grid, dim3(256), 0, st, packed, N, cw, segs, tl, reinterpret_cast<q_u32x4*>(tiled));
     else
-        BCQ_LAUNCH(pack_decode_kernel<false>, grid, dim3(256), 0, st, packed, N, cw, segs, reinterpret_cast<q_u32x4*>(tiled));
+        BCQ_LAUNCH(pack_decode_kernel<false>, grid, dim3(256), 0, st, packed, N, cw, segs, tl, reinterpret_cast<q_u32x4*>(tiled));
     return hipGetLastError();
 }
 

@@ -8,7 +8,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("q,N,K", [(1, 32, 32), (3, 288, 256), (2, 256, 288), (1, 4096, 8224), (4, 2080, 4096),
-                                   (8, 33 * 32, 1056), (1, 17, 2080), (2, 5, 16384)])
+                                   (8, 33 * 32, 1056), (1, 17, 2080), (2, 5, 16384), (2, 64, 512), (3, 65, 32),
+                                   (1, 33, 544), (2, 47, 1024), (8, 31, 96)])
 def test_twin_and_decode_layout(q, N, K):
     import paper_2210_03858_amd as bcq
     rng = np.random.default_rng(N + K)
