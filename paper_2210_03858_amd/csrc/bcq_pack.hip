@@ -110,10 +110,11 @@ hipError_t launch_unpack(const uint32_t* packed, int64_t total_words, int8_t* pl
 hipError_t launch_pack_transposed(const uint32_t* packed, int64_t N, int64_t K, int q, uint32_t* packed_t,
                                   hipStream_t st) {
     const int64_t Kw = K / 32, Nw = N / 32;
-    // Tiles of 16 x 16 words move 64-byte pieces both ways; while they leave compute units without one, tiles of 8 x 8 are
-    // faster (10240 x 2560, q = 4: 12.2 against 14.2 us; 2560 x 2560 7.3 / 6.5, 1024 x 1024 at q = 3 6.8 / 5.2).
+    // Tiles of 16 x 16 words move 64-byte pieces both ways; tiles of 8 x 8 are faster while they leave many compute units
+    // without one (2560 x 2560 at q = 4 7.3 / 6.5 us, 1024 x 1024 at q = 3 6.8 / 5.2), up to about 190 tiles: 180 (3072 x
+    // 3072, q = 5) 7.7 / 8.1, 192 (8192 x 1536, q = 4; 4096 x 4096, q = 3) 7.6 / 9.3 and 7.6 / 6.8, 240 7.9 / 11.1.
     const auto blocks = [&](int t) { return dim3((unsigned)((Kw + t - 1) / t), (unsigned)((Nw + t - 1) / t), (unsigned)q); };
-    if ((Kw + 15) / 16 * ((Nw + 15) / 16) * q >= 256)
+    if ((Kw + 15) / 16 * ((Nw + 15) / 16) * q >= 192)
         BCQ_LAUNCH((transpose_kernel<16, 16>), blocks(16), dim3(256), 0, st, packed, N, K, packed_t);
     else
         BCQ_LAUNCH((transpose_kernel<8, 8>), blocks(8), dim3(64), 0, st, packed, N, K, packed_t);
