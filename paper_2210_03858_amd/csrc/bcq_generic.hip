@@ -1,15 +1,16 @@
-// Any-shape kernels for the BCQ linear layer on the fp64 matrix cores (v_mfma_f64_16x16x4_f64; fp32 or bf16 I/O).
+// Any-shape kernels for the BCQ linear layer in fp64: on the matrix cores (v_mfma_f64_16x16x4_f64) and, for few tokens or
+// few rows, on the vector ALU; fp32 or bf16 I/O.
 // They evaluate AlphaTuning Eq. 2 (forward), Eq. 3 (input gradient) and Eq. 4 (scale gradient, read as the
 // gradient of Eq. 2) directly on the packed sign planes, never forming W in memory, and need no workspace.
 // The library uses them for fp32 activations, for shapes the tiled bf16 matrix-core kernels do not take, and
 // whenever the caller passes no workspace.
 //
-// Why fp64: activations, scales and What = sum_i +-alpha_i are exact in it, so the only roundings that matter are
-// the one of the result and, with bf16 or fp32 outputs, nothing else; the order in which waves share the contraction
-// is then free.  One 16 x 16 x 4 instruction is 2048 flops, ~45 TFLOP/s measured over the chip: the 1024 x 1024
-// layer at 32 tokens needs 1.5 us per product, so the calls are bound by launch and load latency, and the split is
-// chosen to put every compute unit to work: one workgroup per 16 output columns, its eight waves share the
-// contraction and add their tiles in wave order through LDS (bit-reproducible).
+// Why fp64: its roundings, 2^-53 relative for every step of What = sum_i +-alpha_i and of the contraction, stay far below
+// the one rounding of a bf16 or fp32 result, so that the order in which waves share the contraction is free.  One
+// 16 x 16 x 4 instruction is 2048 flops, ~45 TFLOP/s measured over the chip: the 1024 x 1024 layer at 32 tokens needs 1.5 us
+// per product, so the calls are bound by launch and load latency, and the split is chosen to put every compute unit to work:
+// one workgroup per 16 output columns, its eight waves share the contraction and add their tiles in wave order through LDS
+// (bit-reproducible).
 // Measured against one wave per row / one thread per column on the vector ALU (which read every activation once per
 // plane and ran the contraction over N serially), kernel times: 1024 x 1024 at 32 fp32 tokens forward 26 -> 9, input
 // gradient 685 -> 10, scale gradient 42 -> 14 us; 1500 x 1056 at 333 bf16 tokens input gradient 1347 -> 52, scale
@@ -329,6 +330,199 @@ __global__ __launch_bounds__(GEN_WAVES * 64) void bwd_alpha_generic_kernel(const
     }
 }
 
+// ---- few tokens or few rows: the vector ALU, also in fp64 ---------------------------------------------------------
+// A 16 x 16 tile of the matrix instruction wastes most of its work on one or two tokens, or on a few rows; what remains
+// are the planes, which these kernels read with whole waves, and What, which costs three operations per weight and plane.
+
+// the value with the sign of an inverted plane bit, kept in fp64 from the start: shift, and-xor
+__device__ __forceinline__ double signed_value(double a, uint32_t inverted, int s) {
+    return __hiloint2double(__double2hiint(a) ^ (int)((inverted << (31 - s)) & 0x80000000u), __double2loint(a));
+}
+
+// Sums of the `share` (1 or 4) waves that work on one row, in wave order; all lanes of the first of them get the result.
+template <int COUNT>
+__device__ __forceinline__ void share_sums(double (&part)[4][COUNT], double (&s)[COUNT], int share) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i) s[i] = wave_sum(s[i]);
+    if (share == 1) return;
+    if (lane == 0)
+#pragma unroll
+        for (int i = 0; i < COUNT; ++i) part[wave][i] = s[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i) s[i] = (part[0][i] + part[1][i]) + (part[2][i] + part[3][i]);
+}
+
+// Forward: `share` waves per row n and ROW_TOKENS tokens, their lanes take the words of the row in turn.
+constexpr int ROW_TOKENS = 4;
+template <typename XT>
+__global__ __launch_bounds__(256) void fwd_rows_kernel(const uint32_t* __restrict__ packed,
+                                                       const float* __restrict__ alpha, const XT* __restrict__ x,
+                                                       XT* __restrict__ y, int64_t T, int64_t N, int64_t K, int64_t g,
+                                                       int q, int share) {
+    __shared__ double part[4][ROW_TOKENS];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = share == 1 ? 0 : wave;
+    const int64_t row = share == 1 ? (int64_t)blockIdx.y * 4 + wave : blockIdx.y, n = row < N ? row : N - 1;
+    const int64_t t0 = (int64_t)blockIdx.x * ROW_TOKENS;
+    const int Kw = (int)(K / 32), G = (int)(K / g), gw = (int)(g / 32);
+    double acc[ROW_TOKENS];
+#pragma unroll
+    for (int t = 0; t < ROW_TOKENS; ++t) acc[t] = 0.0;
+    uint32_t bits[8];
+    float a[8];
+    auto load = [&](int w) {
+        const int grp = w / gw;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (i < q) {
+                bits[i] = packed[((int64_t)i * N + n) * Kw + w];
+                a[i] = alpha[((int64_t)i * N + n) * G + grp];
+            }
+        }
+    };
+    const int first = sub * 64 + lane, step = 64 * share;
+    if (first < Kw) load(first);
+    for (int w = first; w < Kw; w += step) {
+        Eight<XT> v[4];
+        auto load_x = [&](int t) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) v[b].load(x + (t0 + t) * K + 32 * w + 8 * b);
+        };
+        load_x(0);  // in flight during the expansion
+        double what[32];
+#pragma unroll
+        for (int j = 0; j < 32; ++j) what[j] = 0.0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (i < q) {
+                const double ad = (double)a[i];
+                const uint32_t inv = ~bits[i];
+#pragma unroll
+                for (int j = 0; j < 32; ++j) what[j] += signed_value(ad, inv, j);
+            }
+        }
+        if (w + step < Kw) load(w + step);  // in flight during the products
+#pragma unroll
+        for (int t = 0; t < ROW_TOKENS; ++t) {
+            if (t0 + t < T) {
+                if (t) load_x(t);
+#pragma unroll
+                for (int j = 0; j < 32; ++j) acc[t] = __builtin_fma((double)v[j >> 3].at(j & 7), what[j], acc[t]);
+            }
+        }
+    }
+    share_sums(part, acc, share);
+    if (lane == 0 && sub == 0 && row < N)
+#pragma unroll
+        for (int t = 0; t < ROW_TOKENS; ++t)
+            if (t0 + t < T) Elem<XT>::store(y + (t0 + t) * N + n, (float)acc[t]);
+}
+
+// Scale gradient: `share` waves per row n; a lane forms G[n][k] of its words over all tokens and adds it with the signs
+// of every trained plane, one scale group after the other.
+template <typename XT>
+__global__ __launch_bounds__(256) void bwd_alpha_rows_kernel(const uint32_t* __restrict__ packed,
+                                                             const XT* __restrict__ x, const XT* __restrict__ dy,
+                                                             float* __restrict__ dalpha, int64_t T, int64_t N,
+                                                             int64_t K, int64_t g, int q_train, float grad_scale,
+                                                             int share) {
+    __shared__ double part[4][8];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = share == 1 ? 0 : wave;
+    const int64_t row = share == 1 ? (int64_t)blockIdx.x * 4 + wave : blockIdx.x, n = row < N ? row : N - 1;
+    const int Kw = (int)(K / 32), G = (int)(K / g), gw = (int)(g / 32);
+    for (int grp = 0; grp < G; ++grp) {
+        double s[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s[i] = 0.0;
+        for (int w = grp * gw + sub * 64 + lane; w < (grp + 1) * gw; w += 64 * share) {
+            uint32_t inv[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (i < q_train) inv[i] = ~packed[((int64_t)i * N + n) * Kw + w];
+            double gk[32];
+#pragma unroll
+            for (int j = 0; j < 32; ++j) gk[j] = 0.0;
+            for (int64_t t = 0; t < T; ++t) {
+                const double d = (double)Elem<XT>::load(dy + t * N + n);
+                Eight<XT> v[4];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) v[b].load(x + t * K + 32 * w + 8 * b);
+#pragma unroll
+                for (int j = 0; j < 32; ++j) gk[j] = __builtin_fma(d, (double)v[j >> 3].at(j & 7), gk[j]);
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (i < q_train) {
+#pragma unroll
+                    for (int j = 0; j < 32; ++j) s[i] += signed_value(gk[j], inv[i], j);
+                }
+            }
+        }
+        if (grp && share > 1) __syncthreads();  // the previous group's sums have been read
+        share_sums(part, s, share);
+        if (lane == 0 && sub == 0 && row < N)
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (i < q_train) dalpha[((int64_t)i * N + n) * G + grp] = (float)((double)grad_scale * s[i]);
+    }
+}
+
+// Input gradient for few rows n: a thread per column k and COL_TOKENS tokens, the rows in turn.
+constexpr int COL_TOKENS = 8;
+template <typename XT>
+__global__ __launch_bounds__(256) void bwd_input_cols_kernel(const uint32_t* __restrict__ packed,
+                                                             const float* __restrict__ alpha,
+                                                             const XT* __restrict__ dy, XT* __restrict__ dx, int64_t T,
+                                                             int64_t N, int64_t K, int64_t g, int q) {
+    const int64_t k = (int64_t)blockIdx.y * 256 + threadIdx.x, t0 = (int64_t)blockIdx.x * COL_TOKENS;
+    if (k >= K) return;
+    const int64_t Kw = K / 32, G = K / g;
+    const uint32_t* word = packed + (k >> 5);
+    const float* scale = alpha + k / g;
+    const int bit = (int)(k & 31);
+    double acc[COL_TOKENS];
+#pragma unroll
+    for (int t = 0; t < COL_TOKENS; ++t) acc[t] = 0.0;
+    for (int64_t n = 0; n < N; ++n) {
+        double what = 0.0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (i < q) what += signed_scale(scale[((int64_t)i * N + n) * G], ~word[((int64_t)i * N + n) * Kw], bit);
+#pragma unroll
+        for (int t = 0; t < COL_TOKENS; ++t)
+            if (t0 + t < T) acc[t] = __builtin_fma((double)Elem<XT>::load(dy + (t0 + t) * N + n), what, acc[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < COL_TOKENS; ++t)
+        if (t0 + t < T) Elem<XT>::store(dx + (t0 + t) * K + k, (float)acc[t]);
+}
+
+// The lines, from 24 layers at 1 .. 6000 tokens with both sides timed (matrix instruction / vector ALU, us, fp32).
+// Forward: 256 x 16384, q = 2, 1 token 74 / 6, 4 tokens 48 / 8; 10000 x 4096, q = 3, 1 token 57 / 28, 4 tokens 58 / 77;
+// q = 8, 4 tokens 180 / 108; 1500 x 4096 at 4 tokens 18 / 15, at 8 19 / 23; 3 x 4096 at 2048 tokens 19 / 18.  bf16, whose
+// activations are half the reads: 1500 x 4096, q = 1, 8 tokens 1.7 times as fast, 10000 x 4096, 8 tokens 0.85 times.
+static bool fwd_rows_ok(int64_t T, int64_t N, int64_t K, int q, bool fp32) {
+    const int64_t jobs = N * T;
+    if (T == 1 || jobs <= 6000) return true;
+    if (K < 2048) return false;
+    if (T <= (fp32 && q <= 4 ? 2 : 4)) return true;
+    return fp32 ? K >= 8192 && jobs <= 8200 : K >= 4096 && jobs <= 20000;
+}
+// Scale gradient, row-wise or long groups: 256 x 16384 at 8 tokens 65 / 18; 10000 x 4096, all of 8 planes, 2 tokens 133 / 78,
+// one plane 4 tokens 41 / 72; 1500 x 4096, one plane, 3 tokens 16 / 15, 8 tokens 17 / 27.
+static bool bwd_alpha_rows_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q_train) {
+    return (g == K || g >= 2048) && (T == 1 || (T <= 8 && N * T <= 5000) || T <= (q_train > 4 ? 4 : q_train > 2 && K >= 2048 ? 2 : 1));
+}
+// Input gradient: the threads of few rows must fill the chip.  7 x 16384, q = 1, 4 tokens 3.8 / 4.5, 17 tokens 8.2 / 5.9,
+// 6000 tokens 1237 / 198; 16 x 4096 at 64 tokens 5.6 / 11, at 333 22 / 12; 24 x 1024 at 333 tokens 6 / 10, at 2048 29 / 18;
+// 33 x 4096, q = 3, 333 tokens 0.8 times as fast, 2048 tokens 1.1 times.
+static bool bwd_input_cols_ok(int64_t T, int64_t N, int64_t K) {
+    return N == 1 || (N <= 40 && T * K >= 30000 * N + 80 * N * N * N);
+}
+// waves per row: all four of a workgroup while the rows alone leave compute units idle
+static int row_share(int64_t jobs, int64_t words) { return jobs < 1024 && words >= 128 ? 4 : 1; }
+
 // Token tiles per workgroup: one more halves the reads of the planes and the work of summing them, but also the
 // number of workgroups; more than one only when at least one workgroup per compute unit is left.
 static int token_tiles(int64_t T, int64_t column_tiles) {
@@ -340,6 +534,13 @@ static int token_tiles(int64_t T, int64_t column_tiles) {
 template <typename XT>
 static hipError_t fwd_typed(const uint32_t* packed, const float* alpha, const XT* x, int64_t T, int64_t N, int64_t K,
                             int64_t g, int q, XT* y, hipStream_t st) {
+    if (fwd_rows_ok(T, N, K, q, sizeof(XT) == 4)) {
+        const int64_t tiles = (T + ROW_TOKENS - 1) / ROW_TOKENS;
+        const int share = row_share(N * tiles, K / 32);
+        BCQ_LAUNCH(fwd_rows_kernel<XT>, dim3((unsigned)tiles, (unsigned)((N * share + 3) / 4)), dim3(256), 0, st, packed,
+                           alpha, x, y, T, N, K, g, q, share);
+        return hipGetLastError();
+    }
     const int64_t nb = (N + 15) / 16;
     const int tt = token_tiles(T, nb);
     dim3 grid((unsigned)((T + 16 * tt - 1) / (16 * tt)), (unsigned)nb), block(GEN_WAVES * 64);
@@ -355,6 +556,11 @@ static hipError_t fwd_typed(const uint32_t* packed, const float* alpha, const XT
 template <typename XT>
 static hipError_t bwd_input_typed(const uint32_t* packed, const float* alpha, const XT* dy, int64_t T, int64_t N,
                                   int64_t K, int64_t g, int q, XT* dx, hipStream_t st) {
+    if (bwd_input_cols_ok(T, N, K)) {
+        dim3 cols((unsigned)((T + COL_TOKENS - 1) / COL_TOKENS), (unsigned)((K + 255) / 256));
+        BCQ_LAUNCH(bwd_input_cols_kernel<XT>, cols, dim3(256), 0, st, packed, alpha, dy, dx, T, N, K, g, q);
+        return hipGetLastError();
+    }
     const int64_t kb = K / 32;
     const int tt = token_tiles(T, kb);
     const int64_t tiles = (T + 16 * tt - 1) / (16 * tt);
@@ -373,6 +579,12 @@ static hipError_t bwd_input_typed(const uint32_t* packed, const float* alpha, co
 template <typename XT>
 static hipError_t bwd_alpha_typed(const uint32_t* packed, const XT* x, const XT* dy, int64_t T, int64_t N, int64_t K,
                                   int64_t g, int q_train, float grad_scale, float* dalpha, hipStream_t st) {
+    if (bwd_alpha_rows_ok(T, N, K, g, q_train)) {
+        const int share = row_share(N, g / 32);
+        BCQ_LAUNCH(bwd_alpha_rows_kernel<XT>, dim3((unsigned)((N * share + 3) / 4)), dim3(256), 0, st, packed, x, dy,
+                           dalpha, T, N, K, g, q_train, grad_scale, share);
+        return hipGetLastError();
+    }
     int per = GEN_WAVES;  // waves per scale group
     while (per > 1 && per * (K / g) > GEN_WAVES) per /= 2;
     BCQ_LAUNCH(bwd_alpha_generic_kernel<XT>, dim3((unsigned)((N + 15) / 16)), dim3(GEN_WAVES * 64), 0, st, packed, x,

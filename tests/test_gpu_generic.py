@@ -25,10 +25,24 @@ EDGES = [
     (70, 40, 3072, 3072, 1, 1),    # two token tiles x a whole word in the input gradient
     (8, 72, 2560, 64, 4, 2),       # forty groups, one wave each
 ]
+# Few tokens or rows: the vector ALU forms
+FEW = [
+    (1, 5, 32, 32, 8, 8),          # one word; four waves of which rows stay without one
+    (4, 1501, 2080, 2080, 2, 2),   # a wave per row, 65 words; scale gradient on the matrix cores
+    (2, 6, 16384, 2048, 3, 3),     # four waves per row, eight groups
+    (5, 1000, 4128, 96, 5, 3),     # a second, ragged token tile
+    (8, 600, 1056, 1056, 4, 1),    # scale gradient of eight tokens
+    (3, 10000, 2048, 512, 8, 8),   # all of eight planes, groups too short for the row form of the scale gradient
+    (1, 9999, 64, 32, 3, 2),
+    (700, 7, 1056, 352, 4, 4),     # input gradient by columns, ragged last tile of tokens and of columns
+    (2100, 33, 4096, 4096, 1, 1),
+    (70, 1, 544, 32, 2, 2),
+    (333, 16, 4096, 128, 8, 1),
+]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("T,N,K,g,q,q_train", EDGES)
+@pytest.mark.parametrize("T,N,K,g,q,q_train", EDGES + FEW)
 def test_generic_kernels_are_correctly_rounded(oracle, dtype, T, N, K, g, q, q_train):
     import torch
     import paper_2210_03858_amd as bcq
