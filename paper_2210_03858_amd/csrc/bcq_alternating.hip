@@ -38,6 +38,28 @@ struct AltShared {
     uint8_t pattern[LEVELS];                                  // of the sorted levels
 };
 
+// The first of the smallest distances |x - level[c]| over descending levels, by bisection: the level above x and the one
+// below, then upwards over equal distances (equal levels, or ones that the rounding of the distance makes equal).  Any
+// index in range when x or a level is not finite.
+template <int LEVELS>
+__device__ __forceinline__ int nearest_level(const double* level, double x) {
+    int pos = 0;  // levels above x
+#pragma unroll
+    for (int step = LEVELS / 2; step >= 1; step >>= 1) pos += level[pos + step - 1] > x ? step : 0;
+    pos += level[pos] > x ? 1 : 0;
+    const int below = pos < LEVELS ? pos : LEVELS - 1;
+    if (pos == 0) return 0;
+    const double above = fabs(x - level[pos - 1]);
+    if (pos < LEVELS && !(above <= fabs(x - level[below]))) return below;
+    int best = pos - 1;
+    while (best > 0 && fabs(x - level[best - 1]) <= above) --best;
+    return best;
+}
+// 2^q distances per element, or q steps and two distances: at four planes the distances, which need no per-lane addresses,
+// hold (1024 x 1024 115 us); from five on bisection is faster at every size timed (15 rounds, us): 1024 x 1024 q = 5 259 ->
+// 140, q = 8 1898 -> 1242; 8 vectors of 256, q = 8, one wave each 743 -> 519 (565 with four waves and distances).
+constexpr int ALT_BISECT_FROM = 5;
+
 template <int Q>
 __global__ __launch_bounds__(64 * ALT_MAX_WAVES) void alternating_kernel(const float* __restrict__ W, int64_t V, int n,
                                                                          int iters, float* __restrict__ alpha,
@@ -220,23 +242,28 @@ __global__ __launch_bounds__(64 * ALT_MAX_WAVES) void alternating_kernel(const f
         for (int k = tid; k < quads; k += blockDim.x) {
             const float4 xf = w4[k];
             const double x[4] = {(double)xf.x, (double)xf.y, (double)xf.z, (double)xf.w};
-            double bd[4];
             int best[4];
-            const double l0 = sh.level[0];
+            if constexpr (Q >= ALT_BISECT_FROM) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                bd[e] = fabs(x[e] - l0);
-                best[e] = 0;
-            }
-#pragma unroll 8
-            for (int c = 1; c < LEVELS; ++c) {
-                const double l = sh.level[c];
+                for (int e = 0; e < 4; ++e) best[e] = nearest_level<LEVELS>(sh.level, x[e]);
+            } else {
+                double bd[4];
+                const double l0 = sh.level[0];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const double d = fabs(x[e] - l);
-                    const bool nearer = d < bd[e];
-                    bd[e] = nearer ? d : bd[e];
-                    best[e] = nearer ? c : best[e];
+                    bd[e] = fabs(x[e] - l0);
+                    best[e] = 0;
+                }
+#pragma unroll 8
+                for (int c = 1; c < LEVELS; ++c) {
+                    const double l = sh.level[c];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const double d = fabs(x[e] - l);
+                        const bool nearer = d < bd[e];
+                        bd[e] = nearer ? d : bd[e];
+                        best[e] = nearer ? c : best[e];
+                    }
                 }
             }
             uint32_t c4 = 0u;

@@ -100,3 +100,11 @@ def test_alternating_gpt2_medium_layer(bcq, oracle):
 def test_alternating_wave_counts_and_plane_counts(bcq, oracle, q, N, K, g):
     """One, two and four waves per vector with partly idle waves, every specialisation by q, same bar as above."""
     _check(bcq, oracle, synth.weights(1, "out", N, K, extra=11 * K + q), q, g=g)
+
+
+@pytest.mark.parametrize("q,N,K,g", [(5, 6, 256, 32), (6, 4, 768, None), (7, 3, 512, 256), (8, 5, 1056, None)])
+def test_alternating_bisection(bcq, oracle, q, N, K, g):
+    """Five planes and more find the nearest level by bisection: same bar, with a zero and a constant row."""
+    W = synth.weights(1, "out", N, K, extra=q)
+    W[0], W[1] = 0.0, 0.25
+    _check(bcq, oracle, W, q, g=g)
