@@ -353,7 +353,7 @@ bcq_status bcq_linear_bwd_input_grouped(const uint32_t* packed, const uint32_t* 
         return done(bcq::launch_bwd_input_mfma(packed, packed_t, alpha, dy, T, N, K, g, q, dx, workspace, st));
     if (workspace && split_bwd_input_ok(T, N, K, rowwise, dtype) &&
         workspace_bytes >= bcq::mfma_bwd_input_split_workspace(T, N, K))
-        return done(bcq::launch_bwd_input_mfma_split(packed, packed_t, alpha, dy, T, N, K, g, q, dx, workspace, st));
+        return done(bcq::launch_bwd_input_mfma_split(packed, alpha, dy, T, N, K, g, q, dx, workspace, st));
     return done(bcq::launch_bwd_input_generic(packed, alpha, dy, dtype, T, N, K, g, q, dx, st));
 }
 

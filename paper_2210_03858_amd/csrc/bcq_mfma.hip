@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void expand_fwd_kernel(const uint32_t* __restr
 // twin when the caller has one (one word = 32 consecutive n of this thread's column), else the canonical words
 // (the 32 lanes of a column tile share a word and each takes its own bit).  The scales of the block's 256 rows
 // pass through LDS.
-// SPLIT: What is written as three bf16 terms hi + mid + lo (24 significant bits, all of the fp32 sum), one after the
+// SPLIT (never with a twin): What is written as three bf16 terms hi + mid + lo (24 significant bits, all of the fp32 sum), one after the
 // other along the contraction, smallest first; an Inf or NaN is its first term alone.
 template <bool TWIN, bool SPLIT>
 __global__ __launch_bounds__(256) void expand_bwd_kernel(const uint32_t* __restrict__ planes,
@@ -611,42 +611,39 @@ hipError_t launch_fwd_mfma(const uint32_t* packed, const float* alpha, const voi
     return launch_gemm((const bf16_t*)x, K, (const u32x4*)workspace, (bf16_t*)y, N, T, N, K, R16, st);
 }
 
-template <bool SPLIT>
-static hipError_t launch_expand_bwd(const uint32_t* packed, const uint32_t* packed_t, const float* alpha, int64_t N,
-                                    int64_t K, int64_t g, int q, int64_t R16, u32x4* frag, hipStream_t st) {
-    dim3 grid((unsigned)(K / 32), (unsigned)((R16 / 2 + 7) / 8));
-    if (packed_t && N % 32 == 0)
-        BCQ_LAUNCH((expand_bwd_kernel<true, SPLIT>), grid, dim3(256), 0, st, packed_t, alpha, N, K, g, q, R16, frag);
-    else
-        BCQ_LAUNCH((expand_bwd_kernel<false, SPLIT>), grid, dim3(256), 0, st, packed, alpha, N, K, g, q, R16, frag);
-    return hipGetLastError();
-}
+static dim3 expand_bwd_grid(int64_t K, int64_t R16) { return dim3((unsigned)(K / 32), (unsigned)((R16 / 2 + 7) / 8)); }
 
 hipError_t launch_bwd_input_mfma(const uint32_t* packed, const uint32_t* packed_t, const float* alpha, const void* dy,
                                  int64_t T, int64_t N, int64_t K, int64_t g, int q, void* dx, void* workspace,
                                  hipStream_t st) {
     const int64_t R16 = round_up(N, RPAD) / 16;
     u32x4* frag = (u32x4*)workspace;
-    hipError_t e = launch_expand_bwd<false>(packed, packed_t, alpha, N, K, g, q, R16, frag, st);
+    if (packed_t && N % 32 == 0)
+        BCQ_LAUNCH((expand_bwd_kernel<true, false>), expand_bwd_grid(K, R16), dim3(256), 0, st, packed_t, alpha, N, K, g, q,
+                           R16, frag);
+    else
+        BCQ_LAUNCH((expand_bwd_kernel<false, false>), expand_bwd_grid(K, R16), dim3(256), 0, st, packed, alpha, N, K, g, q,
+                           R16, frag);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_gemm((const bf16_t*)dy, N, frag, (bf16_t*)dx, K, T, K, N, R16, st);
 }
 
-// Input gradient with fp32 weights for row counts (or token counts) that launch_bwd_input_mfma does not take: dX = [dY dY
-// dY] [lo; mid; hi], the same contraction three times as long, on the same kernel.  Tokens are taken SPLIT_TOKENS at a
-// time, which bounds the copies (50257 rows: 1.2 GB) and still fills the chip.
+// Input gradient with fp32 weights for row counts that launch_bwd_input_mfma does not take and that have no twin (N % 32 != 0):
+// dX = [dY dY dY] [lo; mid; hi], the same contraction three times as long, on the same kernel.  Tokens are taken SPLIT_TOKENS
+// at a time, which bounds the copies (50257 rows: 1.2 GB) and still fills the chip.
 constexpr int64_t SPLIT_TOKENS = 4096;
 size_t mfma_bwd_input_split_workspace(int64_t T, int64_t N, int64_t K) {
     return (size_t)(3 * round_up(N, RPAD) * 2 * ((T < SPLIT_TOKENS ? T : SPLIT_TOKENS) + round_up(K, 32)));
 }
 
-hipError_t launch_bwd_input_mfma_split(const uint32_t* packed, const uint32_t* packed_t, const float* alpha,
-                                       const void* dy, int64_t T, int64_t N, int64_t K, int64_t g, int q, void* dx,
+hipError_t launch_bwd_input_mfma_split(const uint32_t* packed, const float* alpha, const void* dy, int64_t T, int64_t N, int64_t K, int64_t g, int q, void* dx,
                                        void* workspace, hipStream_t st) {
     const int64_t P = round_up(N, RPAD), R16 = P / 16;
     u32x4* frag = (u32x4*)workspace;
     u32x4* rows = frag + round_up(K, 32) * 3 * P / 8;
-    hipError_t e = launch_expand_bwd<true>(packed, packed_t, alpha, N, K, g, q, R16, frag, st);
+    BCQ_LAUNCH((expand_bwd_kernel<false, true>), expand_bwd_grid(K, R16), dim3(256), 0, st, packed, alpha, N, K, g, q, R16, frag);
+    hipError_t e = hipGetLastError();
     for (int64_t t0 = 0; t0 < T && e == hipSuccess; t0 += SPLIT_TOKENS) {
         const int64_t M = T - t0 < SPLIT_TOKENS ? T - t0 : SPLIT_TOKENS;
         BCQ_LAUNCH((pad_act_kernel<3>), dim3((unsigned)((M * (P / 8) + 255) / 256)), dim3(256), 0, st,
