@@ -36,7 +36,7 @@ if ROOT not in sys.path:
 
 PEAK_BF16_MFMA_TFLOPS = 2500.0   # MI355X dense bf16 matrix-core peak
 PEAK_HBM_GBS = 8000.0            # MI355X HBM3E peak
-PEAK_FP32_VECTOR_TFLOPS = 157.3  # 256 compute units x 4 SIMDs x 16 lanes x 2 flops x 2.4 GHz
+PEAK_FP64_MFMA_TFLOPS = 78.6     # MI355X fp64 matrix-core peak
 TRAFFIC_TABLE = os.path.join(ROOT, "profiles", "hbm_traffic.md")
 
 
@@ -285,9 +285,9 @@ def run_large(args, env, config, T, q, steps, warmup, custom=None, context=True,
                  "dalpha": "dalpha_kernel (+ transpose_frag_kernel, dalpha_reduce_kernel)"}
         bound, peak = "mfma", PEAK_BF16_MFMA_TFLOPS
         if dtype != "bf16":
-            # fp32 activations take the any-shape vector-ALU kernels, which execute q plane products (2 q T N K lane
-            # operations for 2 T N K effective flops): priced against the fp32 vector peak of the chip
-            bound, peak = "alu", PEAK_FP32_VECTOR_TFLOPS
+            # fp32 activations take the any-shape fp64 kernels, one product of 2 T N K flops per call: priced against the
+            # fp64 matrix-core peak of the chip (few tokens or rows run on the vector ALU, of the same fp64 peak)
+            bound, peak = "mfma_f64", PEAK_FP64_MFMA_TFLOPS
             names = {"gemm": "fwd_generic_kernel, bwd_input_generic_kernel", "dalpha": "bwd_alpha_generic_kernel"}
         calls = len(kern[domk]) * len(layers)
         achieved = len(kern[domk]) * fam_flops / (kern_ms[domk] * 1e-3) / 1e12

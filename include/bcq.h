@@ -31,8 +31,13 @@
  *     entry point documents a status word).  Pass NULL / 0 to make the library choose a path that
  *     needs none (always available, possibly slower).  bcq_workspace_bytes() gives the size that
  *     enables the fastest path; a non-NULL workspace smaller than that is BCQ_ERR_WORKSPACE, except
- *     for the backward products of bf16 calls whose N is no multiple of 8 (input gradient: of 32),
- *     which then run on the path without one.
+ *     for three kinds of bf16 backward products, which then run on the path without one: the input
+ *     gradient when N % 8 != 0, or when N % 32 != 0 with row-wise scales and fewer than 32 tokens;
+ *     the scale gradient when N % 8 != 0 and the call has more than 16 tokens or groups that are no
+ *     multiple of 512.  Those ask for much where N and T are large: the input gradient for
+ *     6 (N up to 128) (min(T, 4096) + K) bytes, the scale gradient for up to 512 MiB, the fragments
+ *     of a like part of x or dy, and partial sums (50257 x 1024, q = 3, any T: 1.55 GB and 0.55 GB
+ *     plus 1 % of dy's size).
  *   - Return value: BCQ_OK or the first problem found; nothing is enqueued unless BCQ_OK.
  *     Order of checks: NULL pointers, shapes, dtype, alignment, workspace, device.
  *   - Limits: 1 <= q <= 8; K % 32 == 0; 1 <= N, K <= 2^17; 1 <= T <= 2^24; N*K and T*max(N,K) at most 2^40.
@@ -44,8 +49,10 @@
  *     stays fp32.  The streaming paths (few tokens) multiply exact signs with activations split into two FP8 terms:
  *     exact for bf16 activations within 2^-13 of the largest of their 32-element block (forward, scale gradient); the
  *     input gradient re-codes the fp32 product dy * alpha_i and keeps 8 significant bits of it (relative 2^-9 per
- *     term).  Without a workspace, for fp32 activations and for row counts that are no multiple of 8 (input
- *     gradient) no such rounding happens: those sums are fp64, or multiply 24-bit What.
+ *     term).  No such rounding happens for fp32 activations and without a workspace: those sums are fp64, except that
+ *     the row-wise bf16 forward of fewer than 32 and scale gradient of at most 16 tokens add exact products in fp32, plane
+ *     by plane.  The input gradient of row counts that are no multiple of 8 multiplies What as three bf16 terms (24 bits,
+ *     any finite value; terms below 2^-126 may count as zero) and adds in fp32.
  *   - Non-finite activations: a token row of x or dy that holds an Inf or NaN makes the outputs of that token
  *     non-finite and leaves every other token's outputs untouched (the scale gradient sums over tokens and becomes
  *     non-finite as a whole); the streaming paths return NaN for every output of such a token.

@@ -314,7 +314,10 @@ static hipError_t launch_q(const float* W, int64_t V, int n, int iters, float* a
     static LdsLimit limit;
     hipError_t e = limit.ensure((const void*)alternating_kernel<Q>, lds);
     if (e != hipSuccess) return e;
-    const int waves = n <= 256 ? 1 : n <= 512 ? 2 : ALT_MAX_WAVES;  // four elements per lane and pass
+    // Four elements per lane and pass.  One / two / four waves, 15 rounds, q = 3, us: 8 vectors of 128 31 / 35 / 42, 8192 of
+    // them 99 / 141 / 259; 4096 of 256 65 / 100 / 170; 8 and 256 of 512 41 / 38 / 46; 256 of 1024 60 / 48 / 47, 1024 of them
+    // 63 / 62 / 70; 1024 of 2560 117 / 106 / 109.
+    const int waves = n <= 256 ? 1 : n <= 512 ? 2 : ALT_MAX_WAVES;
     BCQ_LAUNCH((alternating_kernel<Q>), dim3((unsigned)V), dim3(64 * waves), lds, st, W, V, n, iters, alpha, packed,
                        planes, status_word);
     return hipGetLastError();

@@ -119,7 +119,7 @@ SHAPES = [
     (33, 304, 416, 32, 4),     # per-32-column partial sums, ragged tiles in every extent
     (300, 544, 1024, 512, 3),  # groups of two whole 256-column tiles
     (300, 544, 1056, 96, 3),   # group size that is no power of two
-    (17, 35, 64, 32, 8),       # N % 8 != 0: vector-ALU kernels
+    (17, 35, 64, 32, 8),       # N % 8 != 0: any-shape fp64 kernels
     (260, 256, 1024, 256, 4),  # one group per 256-column tile
     (65, 128, 768, 768, 2),    # g = K through the group-wise entry points
     (70, 264, 2048, 1024, 4),  # g = K / 2, the setting of the OPT experiments (Table 7)

@@ -24,7 +24,7 @@ HP = dict(beta1=0.9, beta2=0.98, eps=1e-7, weight_decay=0.05)
     (256, 256, 1024, 1024, 3, 1, "bf16", True),    # matrix-core path: update inside the final reduction
     (300, 264, 1056, 96, 4, 2, "bf16", True),      # per-32-column partial sums
     (8, 128, 512, 512, 3, 1, "bf16", True),        # streaming kernel + separate update kernel
-    (40, 96, 256, 64, 2, 2, "f32", False),         # vector-ALU kernel + separate update kernel
+    (40, 96, 256, 64, 2, 2, "f32", False),         # any-shape fp64 kernel + separate update kernel
 ])
 def test_bwd_alpha_adamw_steps(bcq, oracle, T, N, K, g, q, q_train, dtype, workspace):
     """Three optimizer steps with a decaying learning rate.  The gradient the call returns is checked against the
