@@ -1,4 +1,4 @@
-"""The any-shape kernels (fp64 matrix cores; fp32 activations, or bf16 without a workspace) at the edges of their tiles.
+"""The any-shape kernels (fp64; fp32 activations, or bf16 without a workspace) at the edges of their tiles.
 
 All sums are fp64, so a result differs from the oracle's fp64 value by its own rounding: half a unit in
 the last place, 2^-24 of the value for fp32 outputs (24 significant bits) and 2^-8 for bf16 ones (8 significant bits;
