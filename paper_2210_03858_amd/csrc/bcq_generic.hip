@@ -502,23 +502,30 @@ __global__ __launch_bounds__(256) void bwd_input_cols_kernel(const uint32_t* __r
 // Forward: 256 x 16384, q = 2, 1 token 74 / 6, 4 tokens 48 / 8; 10000 x 4096, q = 3, 1 token 57 / 28, 4 tokens 58 / 77;
 // q = 8, 4 tokens 180 / 108; 1500 x 4096 at 4 tokens 18 / 15, at 8 19 / 23; 3 x 4096 at 2048 tokens 19 / 18.  bf16, whose
 // activations are half the reads: 1500 x 4096, q = 1, 8 tokens 1.7 times as fast, 10000 x 4096, 8 tokens 0.85 times.
+// Lanes hold whole words: below 24 of them most of a wave idles (400 x 256, 4 tokens, q = 4 4.2 / 8.5; 384 columns, 1 token
+// 4.7 / 4.4, 4 tokens 4.8 / 5.7; 768 columns, 4 tokens 7.5 / 5.9; one plane, 8 tokens of 700 x 768 5.6 / 6.6).
 static bool fwd_rows_ok(int64_t T, int64_t N, int64_t K, int q, bool fp32) {
     const int64_t jobs = N * T;
-    if (T == 1 || jobs <= 6000) return true;
-    if (K < 2048) return false;
+    if (K < 768) return K >= 384 && T <= (K >= 512 ? 2 : 1) && jobs <= 1500;
+    if (T == 1 || jobs <= (K < 1408 ? 4096 : 6000)) return true;
+    if (K < 1408) return false;
     if (T <= (fp32 && q <= 4 ? 2 : 4)) return true;
     return fp32 ? K >= 8192 && jobs <= 8200 : K >= 4096 && jobs <= 20000;
 }
 // Scale gradient, row-wise or long groups: 256 x 16384 at 8 tokens 65 / 18; 10000 x 4096, all of 8 planes, 2 tokens 133 / 78,
 // one plane 4 tokens 41 / 72; 1500 x 4096, one plane, 3 tokens 16 / 15, 8 tokens 17 / 27.
+// 400 x 256, one plane, 8 tokens 5.3 / 7.5; 384 columns, 4 tokens 5.3 / 5.1.
 static bool bwd_alpha_rows_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q_train) {
-    return (g == K || g >= 2048) && (T == 1 || (T <= 8 && N * T <= 5000) || T <= (q_train > 4 ? 4 : q_train > 2 && K >= 2048 ? 2 : 1));
+    if (K < 384 || (g != K && g < 2048)) return false;
+    return T == 1 || (T <= (K >= 768 ? 8 : 4) && N * T <= 5000) || T <= (q_train > 4 ? 4 : q_train > 2 && K >= 1408 ? 2 : 1);
 }
 // Input gradient: the threads of few rows must fill the chip.  7 x 16384, q = 1, 4 tokens 3.8 / 4.5, 17 tokens 8.2 / 5.9,
 // 6000 tokens 1237 / 198; 16 x 4096 at 64 tokens 5.6 / 11, at 333 22 / 12; 24 x 1024 at 333 tokens 6 / 10, at 2048 29 / 18;
-// 33 x 4096, q = 3, 333 tokens 0.8 times as fast, 2048 tokens 1.1 times.
-static bool bwd_input_cols_ok(int64_t T, int64_t N, int64_t K) {
-    return N == 1 || (N <= 40 && T * K >= 30000 * N + 80 * N * N * N);
+// 33 x 4096, q = 3, 333 tokens 0.8 times as fast, 2048 tokens 1.1 times.  More planes move the line up (12 x 512, 1024 tokens,
+// q = 1 1.05 times as fast, q = 8 0.76 times; 32 x 1024, 4096 tokens, q = 8 73 / 83), a second run of 32 rows for the
+// matrix form moves it down (36 x 1024, 4096 tokens, q = 1 56 / 43).
+static bool bwd_input_cols_ok(int64_t T, int64_t N, int64_t K, int q) {
+    return N == 1 || (N <= (q > 4 ? 27 : 40) && T * K >= (3750 * (7 + q) * N + 50 * N * N * N) / (N > 32 ? 2 : 1));
 }
 // waves per row: all four of a workgroup while the rows alone leave compute units idle
 static int row_share(int64_t jobs, int64_t words) { return jobs < 1024 && words >= 128 ? 4 : 1; }
@@ -556,7 +563,7 @@ static hipError_t fwd_typed(const uint32_t* packed, const float* alpha, const XT
 template <typename XT>
 static hipError_t bwd_input_typed(const uint32_t* packed, const float* alpha, const XT* dy, int64_t T, int64_t N,
                                   int64_t K, int64_t g, int q, XT* dx, hipStream_t st) {
-    if (bwd_input_cols_ok(T, N, K)) {
+    if (bwd_input_cols_ok(T, N, K, q)) {
         dim3 cols((unsigned)((T + COL_TOKENS - 1) / COL_TOKENS), (unsigned)((K + 255) / 256));
         BCQ_LAUNCH(bwd_input_cols_kernel<XT>, cols, dim3(256), 0, st, packed, alpha, dy, dx, T, N, K, g, q);
         return hipGetLastError();

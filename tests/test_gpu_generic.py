@@ -27,13 +27,16 @@ EDGES = [
 ]
 # Few tokens or rows: the vector ALU forms
 FEW = [
-    (1, 5, 32, 32, 8, 8),          # one word; four waves of which rows stay without one
-    (4, 1501, 2080, 2080, 2, 2),   # a wave per row, 65 words; scale gradient on the matrix cores
+    (1, 5, 384, 384, 8, 8),        # twelve words; the last workgroup's waves without a row
+    (4, 1499, 2080, 2080, 2, 2),   # a wave per row, 65 words; scale gradient on the matrix cores
     (2, 6, 16384, 2048, 3, 3),     # four waves per row, eight groups
     (5, 1000, 4128, 96, 5, 3),     # a second, ragged token tile
     (8, 600, 1056, 1056, 4, 1),    # scale gradient of eight tokens
     (3, 10000, 2048, 512, 8, 8),   # all of eight planes, groups too short for the row form of the scale gradient
-    (1, 9999, 64, 32, 3, 2),
+    (1, 9999, 800, 32, 3, 2),
+    (2, 700, 512, 512, 3, 3),      # the longest calls that rows of 16 words take
+    (8, 500, 1056, 1056, 2, 2),    # two whole token tiles
+    (1, 5, 352, 352, 3, 3),        # too short for the row forms
     (700, 7, 1056, 352, 4, 4),     # input gradient by columns, ragged last tile of tokens and of columns
     (2100, 33, 4096, 4096, 1, 1),
     (70, 1, 544, 32, 2, 2),
