@@ -10,12 +10,12 @@
 //      workspace, already in the register order of the MFMA B operand ("fragment order"): for every tile of
 //      32 output columns and every 16-long slice of the contraction, 64 lanes x 8 bf16 = 1 KiB contiguous.
 //      This scratch is transient per call; persistent storage stays q bits per weight.
-//   2. gemm_kernel: 256 x 256 output tile per workgroup, 4 waves in a 2 x 2 grid, each wave 128 x 128 =
-//      4 x 4 MFMA tiles of v_mfma_f32_32x32x16_bf16.  The activation tile goes global -> LDS directly
-//      (buffer_load ... lds, three stages in flight, 16-byte chunks XOR-swizzled by row so that the fragment
-//      reads are bank-conflict free); the weight fragments are loaded straight from the workspace into
-//      registers (1 KiB coalesced per wave load), so LDS carries only the activations.
+//   2. gemm_kernel: 64 x 64 to 256 x 256 output tile per workgroup, 4 or 8 waves, v_mfma_f32_16x16x32_bf16.  Both operand
+//      tiles go global -> LDS directly (buffer_load ... lds), several K-steps in flight; the activations' 16-byte chunks are
+//      XOR-swizzled by row so that the fragment reads are bank-conflict free, the weights lie in LDS as in the workspace.
 #include "bcq_internal.h"
+#include <math.h>
+
 #include <type_traits>
 
 namespace bcq {
@@ -25,6 +25,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 
@@ -36,62 +37,47 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
 // ---------------------------------------------------------------------------------------------------------
-// Workgroup -> tile mapping.  Consecutive workgroup ids go round-robin over the 8 XCDs, each with its own L2.
-// The tile grid is cut into super-blocks of a x b tiles; all workgroups that run on one XCD at the same time
-// belong to one super-block, so that XCD's L2 fetches only a/tiles_m of the first operand and b/tiles_n of the
-// second instead of a whole operand.
+// Workgroup -> tile mapping.  Consecutive workgroup ids go round-robin over the 8 XCDs, each with its own L2.  The tiles
+// (of all copies of the tile grid: token slices, parts of a contraction) are numbered in bands of `a` tile rows, down the
+// rows first, and every XCD takes an eighth of that sequence: what it runs at one time is a block of a x (32 / a) tiles,
+// so that its L2 fetches only those rows of the first operand and columns of the second, and the XCDs' shares differ
+// by one tile at most (super-blocks of whole rectangles left 252 tiles in two rounds: 7000 tokens of 1696 x 1696 62 -> 34 us).
 struct TileMap {
-    int tiles_m, tiles_n, a, b, sbm, sbn;
+    int tiles_m, tiles_n, a, total;
 };
 
-__device__ __forceinline__ bool map_tile(const TileMap& tm, int copies, int bid, int& copy, int& tile_m, int& tile_n) {
+__device__ __forceinline__ bool map_tile(const TileMap& tm, int bid, int& copy, int& tile_m, int& tile_n) {
     const int xcd = bid & 7, slot = bid >> 3;
-    const int per = tm.a * tm.b;
-    const int sbg = (slot / per) * 8 + xcd;  // super-block index over all copies of the tile grid
-    const int within = slot % per;
-    const int nsb = tm.sbm * tm.sbn;
-    if (sbg >= nsb * copies) return false;
-    copy = sbg / nsb;
-    const int sb = sbg % nsb;
-    tile_m = (sb % tm.sbm) * tm.a + within % tm.a;
-    tile_n = (sb / tm.sbm) * tm.b + within / tm.a;
-    return tile_m < tm.tiles_m && tile_n < tm.tiles_n;
+    const int first = (int)((int64_t)tm.total * xcd >> 3), end = (int)((int64_t)tm.total * (xcd + 1) >> 3);
+    if (first + slot >= end) return false;
+    const int tiles = tm.tiles_m * tm.tiles_n;
+    copy = (first + slot) / tiles;
+    const int idx = (first + slot) % tiles;
+    const int band = idx / (tm.a * tm.tiles_n), within = idx % (tm.a * tm.tiles_n);
+    const int height = min(tm.a, tm.tiles_m - band * tm.a);
+    tile_m = band * tm.a + within % height;
+    tile_n = within / height;
+    return true;
 }
 
-// Super-block shape: about `cap` tiles (what one XCD runs concurrently), minimising the bytes both operands bring
-// in, a * cost_m + b * cost_n.  Returns the number of workgroups to launch.
-static inline unsigned make_tile_map(int tiles_m, int tiles_n, int copies, int cap, double cost_m, double cost_n,
-                                     TileMap* out) {
-    // never make a super-block larger than one XCD's share of all tiles (copies = independent tile grids, e.g.
-    // token slices), or some XCDs would get no work
-    const long share = ((long)tiles_m * tiles_n * copies + 7) / 8;
-    if (cap > share) cap = (int)(share < 1 ? 1 : share);
-    int best_a = 1, best_b = 1;
-    double best = 1e300;
+// The band height that brings in the fewest operand bytes for the tiles that an XCD runs at one time; cost_m and cost_n:
+// bytes of a tile row and a tile column.  Returns the number of workgroups to launch.
+static inline unsigned make_tile_map(int tiles_m, int tiles_n, int copies, double cost_m, double cost_n, TileMap* out) {
+    const int64_t total = (int64_t)tiles_m * tiles_n * copies, share = (total + 7) / 8;
+    const int cap = (int)(share < 32 ? share : 32);
+    int best = 1;
+    double least = 1e300;
     for (int a = 1; a <= tiles_m && a <= cap; ++a) {
-        for (int b = 1; b <= tiles_n && a * b <= cap; ++b) {
-            const int sbm = (tiles_m + a - 1) / a, sbn = (tiles_n + b - 1) / b;
-            const long nsb = (long)sbm * sbn * copies;
-            // work really done per XCD round, including empty slots of ragged super-blocks and idle XCDs
-            const double slots = (double)((nsb + 7) / 8) * 8 * a * b;
-            const double waste = slots / ((double)tiles_m * tiles_n * copies);
-            const double per_tile = (a * cost_m + b * cost_n) / ((double)a * b);
-            const double score = per_tile * waste * waste * waste;  // balance first, then operand traffic
-            if (score < best) {
-                best = score;
-                best_a = a;
-                best_b = b;
-            }
+        int b = (cap + a - 1) / a;
+        if (b > tiles_n) b = tiles_n;
+        const double cost = a * cost_m + b * cost_n;
+        if (a * b * 8 >= cap * 7 && cost < least) {  // (a block that is too small to be a share says nothing)
+            least = cost;
+            best = a;
         }
     }
-    out->tiles_m = tiles_m;
-    out->tiles_n = tiles_n;
-    out->a = best_a;
-    out->b = best_b;
-    out->sbm = (tiles_m + best_a - 1) / best_a;
-    out->sbn = (tiles_n + best_b - 1) / best_b;
-    const int nsb = out->sbm * out->sbn * copies;
-    return (unsigned)(((nsb + 7) / 8) * 8 * best_a * best_b);
+    *out = TileMap{tiles_m, tiles_n, best, (int)total};
+    return (unsigned)(8 * share);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -274,287 +260,290 @@ __global__ __launch_bounds__(256) void pad_act_kernel(const bf16_t* __restrict__
 // ---------------------------------------------------------------------------------------------------------
 // C[M][NC] = A[M][R] * Bfrag, A row-major bf16 with leading dimension lda, Bfrag in fragment order with R16
 // slices per column tile (R16 * 16 >= R, a multiple of 128), C row-major bf16 with leading dimension ldc.
-// Workgroup tile (64 TM) x (64 TN), 4 waves in a 2 x 2 grid, each wave TM x TN MFMA tiles.
-// The weight fragment is the first MFMA operand, so one lane ends up with 4 consecutive output columns of
-// one token.  Nothing branches on the ragged edges: activation rows beyond M and bytes beyond the end of A come
-// back as zeros from the buffer range check, contraction indices beyond R meet zero weights, and column tiles
-// beyond NC are clamped to the last valid tile (their products are never stored).
-template <int TM, int TN>
-struct GemmCfg {
-    static constexpr int BMT = 64 * TM, BNT = 64 * TN;
-    static constexpr int BKC = (TM * TN <= 2) ? 128 : 64;      // contraction per K-step: 64-token tiles take longer steps
-    static constexpr int KS = BKC / 16;                        // 16-slices per K-step
-    static constexpr int ROWB = BKC * 2;                       // LDS row of the activation tile (8 or 16 swizzled chunks of 16 B)
-    static constexpr int STAGE_B = BMT * ROWB;                 // one activation stage
-    static constexpr int NST = 3;                              // stages in flight
-    static constexpr int EPI_ROWB = 64 * TN + 8;               // epilogue row: 32 TN columns of bf16 + pad
-    static constexpr int EPI_B = 4 * 64 * EPI_ROWB;            // 4 waves x 64 tokens
-    static constexpr int LDS_B = (NST * STAGE_B > EPI_B) ? NST * STAGE_B : EPI_B;
-    static constexpr int OCC = (TM * TN >= 16) ? 1 : 2;
+//
+// Both operand tiles go global -> LDS directly (buffer_load ... lds, 16 B per lane, no register round trip), several
+// K-steps ahead, and come back as v_mfma_f32_16x16x32_bf16 operands, one 32-column slice ahead of their use.  Against weight
+// fragments loaded straight into registers (one K-step ahead, twice per workgroup) this takes a third of the vector-memory
+// traffic away and covers the latency of HBM; against v_mfma_f32_32x32x16_bf16 the 16 x 16 x 32 form reads and writes half
+// the accumulator bits per product.  With all compute units busy the chip is at its power limit (1.7 GHz instead of 2.4),
+// so that what a product costs in energy is what bounds the kernel: 6144 x 2048 at 16384 tokens 393 -> 312 us, 2048 x 8192
+// 432 -> 372 us (1.32 and 1.48 PFLOP/s; weights expanded beforehand).
+//
+// Eight or four waves in a WM x WN grid, each TM x TN tiles of 16 x 16: two waves per vector unit hide each other's waits,
+// and a wave keeps within 256 registers (accumulators in the other half of the file would be moved back and forth).  Per
+// K-step one barrier: behind it every wave has the step's last fragments in registers, so the step's LDS is requested
+// anew at once, and the first fragments of the next step are read under the MFMAs of the last slice.
+// Nothing branches on the ragged edges: activation rows beyond M and column tiles beyond NC come back as zeros from the
+// buffer range check, contraction indices beyond R meet zero weights.
+//
+// Tile shapes: 256 x 256 has the fewest operand bytes per product; the smaller ones fill the chip where it would leave
+// compute units idle (launch_gemm).  NA, NB: stages of A and B, as many as 160 KiB hold.  KC: 64-column chunks per K-step, two
+// for the smallest tiles, whose steps would otherwise be mostly barrier (about 360 cycles a step, beside BM BN / 32 of MFMA).
+template <int BM, int BN> struct GemmShape;
+template <> struct GemmShape<256, 256> { static constexpr int WM = 2, WN = 4, NA = 3, NB = 2, KC = 1; };
+template <> struct GemmShape<256, 192> { static constexpr int WM = 2, WN = 4, NA = 3, NB = 2, KC = 1; };
+template <> struct GemmShape<256, 160> { static constexpr int WM = 4, WN = 2, NA = 3, NB = 3, KC = 1; };
+template <> struct GemmShape<256, 128> { static constexpr int WM = 4, WN = 2, NA = 3, NB = 3, KC = 1; };
+template <> struct GemmShape<128, 160> { static constexpr int WM = 2, WN = 2, NA = 4, NB = 4, KC = 1; };
+template <> struct GemmShape<128, 128> { static constexpr int WM = 2, WN = 2, NA = 5, NB = 5, KC = 1; };
+template <> struct GemmShape<64, 128> { static constexpr int WM = 2, WN = 2, NA = 3, NB = 3, KC = 2; };
+template <> struct GemmShape<64, 64> { static constexpr int WM = 2, WN = 2, NA = 5, NB = 5, KC = 2; };
+
+template <int BM, int BN>
+struct GemmCfg : GemmShape<BM, BN> {
+    using S = GemmShape<BM, BN>;
+    static constexpr int NW = S::WM * S::WN;
+    static constexpr int TM = BM / S::WM / 16, TN = BN / S::WN / 16;
+    static constexpr int CA = BM * 128, CB = BN * 128;             // bytes of a 64-column chunk of either operand
+    static constexpr int A_B = CA * S::KC, B_B = CB * S::KC;       // bytes of a stage
+    static constexpr int LDS_B = S::NA * A_B + S::NB * B_B;
+    static constexpr int JA = BM / 8 / NW, JB = (BN / 8 + NW - 1) / NW;  // 1 KiB requests per wave and chunk
+    static constexpr int DA = JA * S::KC, DB = JB * S::KC;               // and stage
+    static_assert(BM % (16 * S::WM) == 0 && BN % (16 * S::WN) == 0 && BN % 32 == 0, "whole tiles");
+    static_assert(BM % (8 * NW) == 0 && JA % 2 == 0, "the swizzle term of a row group depends on the request's index only");
+    static_assert(S::NA >= S::NB && S::NA - S::NB <= 1, "the waits count on this order of requests");
+    static_assert((S::NA - 1) * DA + (S::NB - 1) * DB < 64, "vmcnt");
+    static_assert(LDS_B <= 160 * 1024, "LDS of a compute unit");
 };
 
-template <int TM, int TN>
-__global__ __launch_bounds__(256, (TM * TN >= 16 ? 1 : 2)) void gemm_kernel(
+// gfx9 s_waitcnt immediate: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] at [15:14]; vmcnt alone
+constexpr int wait_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
+
+// sums != nullptr: the contraction is cut into parts of `per` K-steps (the tile map's copies), each workgroup stores its
+// fp32 tile to sums[part][M][NC rounded up to 4].
+template <int BM, int BN>
+__global__ __launch_bounds__((64 * GemmCfg<BM, BN>::NW), 2) void gemm_kernel(
     const bf16_t* __restrict__ A, int64_t lda, const u32x4* __restrict__ Bfrag, bf16_t* __restrict__ C, int64_t ldc,
-    int64_t M, int64_t NC, int64_t R, int64_t R16, TileMap tmap) {
+    int64_t M, int64_t NC, int64_t R, int64_t R16, TileMap tmap, int per, float* __restrict__ sums) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the buffer-resource builtins exist in the device pass only
-    using Cfg = GemmCfg<TM, TN>;
-    constexpr int STAGE_B = Cfg::STAGE_B, ROWB = Cfg::ROWB, KS = Cfg::KS, BKC = Cfg::BKC, NST = Cfg::NST;
+    using Cfg = GemmCfg<BM, BN>;
+    constexpr int WN = Cfg::WN, TM = Cfg::TM, TN = Cfg::TN, NA = Cfg::NA, NB = Cfg::NB, KC = Cfg::KC, SL = 2 * KC;
+    constexpr int A_B = Cfg::A_B, B_B = Cfg::B_B, JA = Cfg::JA, JB = Cfg::JB, DA = Cfg::DA, DB = Cfg::DB;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: keeps descriptors and LDS bases scalar
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = wave / WN, wn = wave % WN;
 
-    int tile_m, tile_n, copy_unused;
-    if (!map_tile(tmap, 1, blockIdx.x, copy_unused, tile_m, tile_n)) return;  // padding workgroup of the last round
-    const int64_t m0 = (int64_t)tile_m * Cfg::BMT, n0 = (int64_t)tile_n * Cfg::BNT;
-    const int64_t ct_count = (NC + 31) / 32;
+    int tile_m, tile_n, part;
+    if (!map_tile(tmap, blockIdx.x, part, tile_m, tile_n)) return;  // the eighths differ by one tile
+    const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
+    const int total = (int)((R + 64 * KC - 1) / (64 * KC));  // K-steps of the whole contraction
+    const int first = part * per, last = min(total, first + per) - 1;
 
-    f32x16 acc[TN][TM];  // [weight tile][token tile]
+    f32x4 acc[TN][TM];  // [weight tile][token tile]
 #pragma unroll
-    for (int i = 0; i < TN; ++i)
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int j = 0; j < TM; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int i = 0; i < TM; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // Activation tile: global -> LDS without passing registers (buffer_load ... lds, 16 B per lane).  One wave
-    // instruction fills 1 KiB of LDS = RPB tile rows of CPR chunks; lane l lands in row l / CPR, slot l % CPR and
-    // fetches the chunk that the swizzle assigns to that slot, so the fragment reads (16 lanes: one chunk index of
-    // 16 consecutive rows) are bank-conflict free without padding:
-    //   128-byte rows: slot = chunk ^ (r & 7) ^ ((r >> 3) & 1)   (rows r and r + 8 lie four passes over the 64
-    //                                                              banks apart and would meet in the same banks)
-    //   256-byte rows: slot = chunk ^ (r & 15)                    (every row starts at bank 0)
-    // Each wave has one buffer descriptor, based at the first of its 16 TM rows and ending at the end of A, so
-    // rows beyond M read zeros; the per-lane offset is loop invariant up to the swizzle term of the row group
-    // (NV variants), the row group and the K-step advance through the scalar offset (below 2^31 because
-    // lda < 2^24, checked by the host).
-    constexpr int CPR = ROWB / 16;             // chunks per row
-    constexpr int RPB = 64 / CPR;              // rows per wave instruction
-    constexpr int NDMA = Cfg::BMT / RPB / 4;   // wave instructions per wave and stage
-    constexpr int NV = (CPR == 8) ? 2 : 4;     // distinct swizzle terms of a row group: (j & 1) or (j & 3) << 2
-    static_assert(CPR == 8 || CPR == 16, "128- or 256-byte rows");
-    static_assert(NDMA % NV == 0, "the row-group term depends on the instruction index only");
-    const int64_t steps = R16 * 16 / BKC;
-    const int64_t last = steps - 1;
-    const int64_t wrow0 = m0 + wave * NDMA * RPB;
+    // A: one wave instruction fills 1 KiB of LDS = 8 tile rows of 128 bytes; lane l lands in row l / 8, 16-byte slot l % 8
+    // and fetches the chunk that the swizzle assigns to that slot, slot = chunk ^ (r & 7) ^ ((r >> 3) & 1), so that the
+    // fragment reads (one chunk index of 16 consecutive rows) are bank-conflict free without padding.  Each wave has one
+    // buffer descriptor, based at the first of its rows and ending at the end of A; rows advance through the lane offset
+    // (below 2^31: lda < 2^24 and at most 64 rows), K-steps through the scalar offset.
+    const int64_t wrow0 = m0 + wave * JA * 8;
     const int64_t left = (M - wrow0) * lda * 2;  // bytes from this wave's first row to the end of A (lda >= R)
-    __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+    __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(A + (left > 0 ? wrow0 * lda : 0)), 0, (int)(left > 0 ? (left < 0x7fffffffll ? left : 0x7fffffffll) : 0),
         0x00020000);
-    const int drow = lane / CPR, dslot = lane % CPR;
-    uint32_t voff[NV], voff_tail[NV];
+    const int drow = lane >> 3, dslot = lane & 7;
+    const bool ragged = (int64_t)total * 64 * KC > R;
+    uint32_t avoff[JA], atail[KC][2];  // lane offsets; what the last step, which may reach beyond R, adds to them
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        const int achunk = dslot ^ drow ^ ((CPR == 8) ? v : (v << 2));
-        voff[v] = (uint32_t)(drow * lda * 2 + achunk * 16);
-        // the last K-step may reach beyond R: its chunks are clamped into the row (they meet zero weights)
-        int64_t k_tail = last * BKC + achunk * 8;
-        k_tail = k_tail < R - 8 ? k_tail : R - 8;
-        voff_tail[v] = (uint32_t)(drow * lda * 2 + k_tail * 2);
-    }
-    const int group_b = (int)(RPB * lda * 2);   // bytes between two row groups
-    auto dma_a = [&](int64_t step, int stage) {
-        const bool tail = step >= last;
-        uint32_t vo[NV];
+    for (int j = 0; j < JA; ++j) avoff[j] = (uint32_t)((j * 8 + drow) * lda * 2 + (dslot ^ drow ^ (j & 1)) * 16);
 #pragma unroll
-        for (int v = 0; v < NV; ++v) vo[v] = tail ? voff_tail[v] : voff[v];
-        const int so = tail ? 0 : (int)(step * BKC * 2);
+    for (int c = 0; c < KC; ++c)
 #pragma unroll
-        for (int j = 0; j < NDMA; ++j)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                rsrc, (void __attribute__((address_space(3)))*)(smem + stage * STAGE_B + (wave * NDMA + j) * 1024), 16,
-                vo[j % NV], so + j * group_b, 0, 0);
+        for (int v = 0; v < 2; ++v) {  // chunks beyond R are clamped into the row (they meet zero weights)
+            const int64_t k = (int64_t)(total - 1) * 64 * KC + c * 64 + (dslot ^ drow ^ v) * 8;
+            atail[c][v] = k < R - 8 ? 0u : (uint32_t)((R - 8 - k) * 2);
+        }
+    auto dma_a = [&](int step, int slot, int d) {  // request d of a stage; steps beyond the last repeat it
+        step = step < last ? step : last;
+        const uint32_t tail = ragged && step == total - 1 ? ~0u : 0u;
+        const int c = d / JA, j = d % JA;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            ra, (void __attribute__((address_space(3)))*)(smem + slot * A_B + c * Cfg::CA + (wave * JA + j) * 1024), 16,
+            avoff[j] + (atail[c][j & 1] & tail), (step * KC + c) * 128, 0, 0);
     };
-
-    // weight fragments of this wave: column tiles ct0 .. ct0+TN-1, straight from global memory into registers
-    const int64_t ct0 = (n0 + wn * 32 * TN) / 32;
-    const u32x4* bptr[TN];
+    // B: per column tile of 32 the four 16-slices of a chunk are 4 KiB in a row, and LDS holds them as they come.  Where a
+    // wave's share is no whole number of requests the last ones are repeated.
+    const int64_t ct0 = n0 / 32, ct_count = (NC + 31) / 32;
+    const int64_t bleft = (ct_count - ct0) * R16 * 1024;
+    __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(Bfrag + ct0 * R16 * 64), 0, (int)(bleft < 0x7fffffffll ? bleft : 0x7fffffffll), 0x00020000);
+    uint32_t bvoff[JB];
+    int bblk[JB];
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        int64_t ct = ct0 + j;
-        ct = ct < ct_count ? ct : ct_count - 1;
-        bptr[j] = Bfrag + ct * R16 * 64 + lane;
+    for (int j = 0; j < JB; ++j) {
+        const int blk = wave * JB + j;
+        bblk[j] = (BN / 8) % Cfg::NW == 0 ? blk : min(blk, BN / 8 - 1);
+        bvoff[j] = (uint32_t)((bblk[j] >> 2) * (int)(R16 * 1024) + (bblk[j] & 3) * 1024 + lane * 16);
     }
-    u32x4 b[KS][TN];  // [kk][j]; slot kk is refilled for the next K-step right after its MFMAs are issued
-    auto load_b = [&](int kk, int64_t step) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j) b[kk][j] = bptr[j][(step * KS + kk) * 64];
+    auto dma_b = [&](int step, int slot, int d) {
+        step = step < last ? step : last;
+        const int c = d / JB, j = d % JB;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            rb, (void __attribute__((address_space(3)))*)(smem + NA * A_B + slot * B_B + c * Cfg::CB + bblk[j] * 1024), 16,
+            bvoff[j], (step * KC + c) * 4096, 0, 0);
     };
 
     // Fragment reads are inline assembly: the compiler guards every LDS read it sees that may alias a direct-to-LDS
-    // load with a wait for ALL outstanding loads.  wait_x / wait_stage tie the fragment registers to an explicit
-    // s_waitcnt, so no consumer can be scheduled above the wait.
-    u32x4 xf[2][TM];  // activation fragments of two consecutive 16-slices
-    // lane (r = lane % 32, h = lane / 32) takes chunk 2 kk + h of row wm * 32 TM + 32 i + r
-    const int xrow = wm * 32 * TM + (lane & 31);
-    const int xswz = (CPR == 8) ? ((xrow & 7) ^ ((xrow >> 3) & 1)) : (xrow & 15);  // the same for rows 32 i further on
-    uint32_t xoff[KS];
+    // load with a wait for ALL outstanding loads.  `arrived` ties the fragment registers to an explicit s_waitcnt, so no
+    // consumer can be scheduled above the wait.  Lane (r = lane % 16, h = lane / 16) takes columns 8 h .. + 7 of the slice.
+    u32x4 xf[2][TM], wf[2][TN];  // fragments of two consecutive slices
+    const int xrow = wm * 16 * TM + (lane & 15);
+    const int xswz = (xrow & 7) ^ ((xrow >> 3) & 1);  // the same for rows 16 i further on
+    uint32_t xoff[2];
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk)
-        xoff[kk] = (uint32_t)(xrow * ROWB + (((2 * kk + (lane >> 5)) ^ xswz) * 16));
-    auto read_x = [&](int stage, int kk) {
-        const uint32_t addr = xoff[kk] + (uint32_t)(stage * STAGE_B);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(xf[kk & 1][i]) : "v"(addr), "n"(i * 32 * ROWB));
+    for (int kk = 0; kk < 2; ++kk) xoff[kk] = (uint32_t)(xrow * 128 + (((4 * kk + (lane >> 4)) ^ xswz) * 16));
+    // column tile of 16 number c16 = half c16 & 1 of column tile c16 >> 1; with an odd TN every other wave starts at an odd one
+    const int c16 = wn * TN;
+    const uint32_t wlane = (uint32_t)(NA * A_B + (c16 >> 1) * 4096 + (lane >> 5) * 1024 + ((lane >> 4) & 1) * 512 + (lane & 15) * 16);
+    const bool odd = (TN & 1) && (c16 & 1);
+    const uint32_t woff[2] = {wlane + (odd ? 256u : 0u), wlane + (odd ? 4096u : 256u)};  // even and odd tiles of the wave
+    auto read_x = [&](uint32_t stage, int kk, int i) {
+        const uint32_t addr = xoff[kk & 1] + stage;
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(xf[kk & 1][i]) : "v"(addr), "n"((kk >> 1) * Cfg::CA + i * 2048));
     };
-    // gfx9 s_waitcnt immediate: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] at [15:14]
-    auto wait_regs = [&](int kk, auto imm) {
-        constexpr int IMM = decltype(imm)::value;
-        u32x4* f = xf[kk & 1];
-        if constexpr (TM == 4)
-            asm volatile("s_waitcnt %4" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]) : "n"(IMM) : "memory");
-        else if constexpr (TM == 2)
-            asm volatile("s_waitcnt %2" : "+v"(f[0]), "+v"(f[1]) : "n"(IMM) : "memory");
-        else
-            asm volatile("s_waitcnt %1" : "+v"(f[0]) : "n"(IMM) : "memory");
+    auto read_w = [&](uint32_t stage, int kk, int j) {
+        const uint32_t addr = woff[j & 1] + stage;
+        asm volatile("ds_read_b128 %0, %1 offset:%2"
+                     : "=v"(wf[kk & 1][j]) : "v"(addr), "n"((kk >> 1) * Cfg::CB + (j >> 1) * 4096 + (kk & 1) * 2048));
     };
-    // the fragments of slice kk are usable once only the TM reads of the following slice are outstanding
-    auto wait_x = [&](int kk) { wait_regs(kk, std::integral_constant<int, 63 | (3 << 14) | (7 << 4) | (TM << 8)>()); };
-    // Before the barrier of a K-step: every LDS read of this wave has returned (the stage may be refilled after
-    // the barrier) and this wave's part of the next stage has landed.  That stage was requested a whole K-step
-    // ago and loads complete in order, so it is enough that at most the loads issued during this K-step (the
-    // fill and KS - 1 slices of weights) remain in flight - which the coming MFMAs need anyway.
-    auto wait_stage = [&](int kk) {
-        constexpr int MAXV = NDMA + (KS - 1) * TN;
-        wait_regs(kk, std::integral_constant<int, (MAXV & 15) | ((MAXV >> 4) << 14) | (7 << 4) | (0 << 8)>());
-    };
-    auto mfma_slice = [&](int kk) {
+    auto arrived = [&](int p) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(xf[p][i]));
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
-                acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(b[kk][j]), as_bf16x8(xf[kk & 1][i]),
-                                                                    acc[j][i], 0, 0, 0);
-    };
-
-    // Prologue: stages 0 .. NST-2 requested, then the weights of step 0.  These first weight loads are inline
-    // assembly as well, so that they are issued HERE, in flight together with the activation stages (the
-    // compiler would sink them below the barrier); tie_b makes them usable.
-#pragma unroll
-    for (int p = 0; p < NST - 1; ++p) dma_a(p, p);
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-            asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(b[kk][j]) : "v"(bptr[j] + kk * 64));
-    {
-        constexpr int MAXV = (NST - 2) * NDMA + KS * TN;  // stage 0 has landed (this wave's part)
-        asm volatile("s_waitcnt %0" ::"n"((MAXV & 15) | ((MAXV >> 4) << 14) | (7 << 4) | (15 << 8)) : "memory");
-    }
-    __builtin_amdgcn_s_barrier();
-    read_x(0, 0);
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {  // all prologue loads have returned
-        u32x4* f = b[kk];
-        if constexpr (TN == 4)
-            asm volatile("s_waitcnt vmcnt(0)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3])::"memory");
-        else if constexpr (TN == 2)
-            asm volatile("s_waitcnt vmcnt(0)" : "+v"(f[0]), "+v"(f[1])::"memory");
-        else
-            asm volatile("s_waitcnt vmcnt(0)" : "+v"(f[0])::"memory");
-    }
-
-    // One K-step = KS 16-slices.  At its start the stage NST - 1 steps ahead is requested into the buffer that was
-    // read during the previous step.  Per slice: issue the LDS reads of the next slice, the MFMAs of this one,
-    // then refill this slice's weight registers for the next K-step (a full step of latency cover).  The
-    // hand-over to the next stage (wait, barrier, first fragment read) sits BEFORE the MFMAs of the last slice,
-    // whose operands are already in registers, so the matrix pipe stays busy across the barrier.
-    int st = 0;  // stage of step s
-    for (int64_t s = 0; s < steps; ++s) {
-        const int64_t nx = s < last ? s + 1 : last;
-        const int st_next = (st + 1 == NST) ? 0 : st + 1;
-        const int st_fill = (st == 0) ? NST - 1 : st - 1;
-        dma_a(s + NST - 1, st_fill);
+        for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(wf[p][j]));
         __builtin_amdgcn_sched_barrier(0);
+    };
+    // The MFMAs of slice kk in boustrophedon order (neighbours share an operand), with the reads of the next slice and
+    // `also` (the requests) spread between them.
+    auto slice = [&](auto KK, uint32_t astage, uint32_t bstage, auto&& also) {
+        constexpr int kk = decltype(KK)::value, next = (kk + 1) % SL, NM = TM * TN, NR = TM + TN;
+        constexpr int GAP = NM * 3 / 4 / NR > 0 ? NM * 3 / 4 / NR : 1, PER = (NR + NM - 1) / NM;
 #pragma unroll
-        for (int kk = 0; kk < KS - 1; ++kk) {
-            read_x(st, kk + 1);
-            wait_x(kk);
-            mfma_slice(kk);
-            load_b(kk, nx);
+        for (int m = 0; m < NM; ++m) {
+            const int j = m / TM, i = (j & 1) ? TM - 1 - m % TM : m % TM;
+            acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wf[kk & 1][j]), as_bf16x8(xf[kk & 1][i]), acc[j][i], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (m % GAP == 0) {
+#pragma unroll
+                for (int r = m / GAP * PER; r < m / GAP * PER + PER; ++r) {
+                    if (r < TN) read_w(bstage, next, r);
+                    else if (r < NR) read_x(astage, next, r - TN);
+                }
+            }
+            also(m);
             __builtin_amdgcn_sched_barrier(0);
         }
-        wait_stage(KS - 1);
-        __builtin_amdgcn_s_barrier();
-        read_x(st_next, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_slice(KS - 1);
-        load_b(KS - 1, nx);
-        __builtin_amdgcn_sched_barrier(0);
-        st = st_next;
-    }
-    // the clamped requests of the last steps are still writing LDS, and the last fragment read is in flight
-    wait_regs(0, std::integral_constant<int, 0 | (7 << 4)>());
+    };
 
-    // epilogue: acc register 4g+e of lane l is weight column 8g + 4*(l/32) + e, token l%32 of its 32 x 32 tile.
-    // Pass the tile through LDS (64 tokens per wave at a time) so that global stores are 16 B per lane and
-    // whole rows of 64 TN bytes are contiguous.
-    constexpr int EROW = Cfg::EPI_ROWB;
-    const bool vec_ok = (ldc % 8 == 0);
-    if (vec_ok) {
-        unsigned char* ew = smem + wave * 64 * EROW;
-        constexpr int CH = 4 * TN;        // 16-byte chunks per row
-        constexpr int RPI = 64 / CH;      // rows per store instruction
-        __syncthreads();  // every wave is done with the activation stages; from here on a wave touches only its own region
+    // Prologue: all stages requested in the order in which they are needed; the first one waited for.
 #pragma unroll
-        for (int pass = 0; pass < (TM + 1) / 2; ++pass) {
-            // LDS executes one wave's instructions in order: between its own writes and reads of its region only the
-            // compiler has to keep the order
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    for (int p = 0; p < NA; ++p) {
 #pragma unroll
-            for (int il = 0; il < 2; ++il) {
-                const int it = pass * 2 + il;
-                if (it < TM) {
+        for (int d = 0; d < DA; ++d) dma_a(first + p, p, d);
+        if (p < NB) {
 #pragma unroll
-                    for (int jw = 0; jw < TN; ++jw)
+            for (int d = 0; d < DB; ++d) dma_b(first + p, p, d);
+        }
+    }
+    asm volatile("s_waitcnt %0" ::"n"(wait_vm((NA - 1) * DA + (NB - 1) * DB)) : "memory");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int g = 0; g < 4; ++g) {
-                            uint2 o;
-                            o.x = pack_bf16x2(acc[jw][it][4 * g], acc[jw][it][4 * g + 1]);
-                            o.y = pack_bf16x2(acc[jw][it][4 * g + 2], acc[jw][it][4 * g + 3]);
-                            *reinterpret_cast<uint2*>(ew + (il * 32 + (lane & 31)) * EROW +
-                                                      (jw * 32 + 8 * g + 4 * (lane >> 5)) * 2) = o;
-                        }
-                }
+    for (int j = 0; j < TN; ++j) read_w(0, 0, j);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) read_x(0, 0, i);
+    __builtin_amdgcn_sched_barrier(0);
+
+    int sa = 0, sb = 0;  // stages of step s
+    for (int s = first; s <= last; ++s) {
+        const int sa_next = sa + 1 == NA ? 0 : sa + 1, sb_next = sb + 1 == NB ? 0 : sb + 1;
+        const uint32_t ab = (uint32_t)(sa * A_B), bb = (uint32_t)(sb * B_B);
+        auto nothing = [](int) {};
+        arrived(0);
+        slice(std::integral_constant<int, 0>{}, ab, bb, nothing);
+        if constexpr (KC == 2) {
+            arrived(1);
+            slice(std::integral_constant<int, 1>{}, ab, bb, nothing);
+            arrived(0);
+            slice(std::integral_constant<int, 2>{}, ab, bb, nothing);
+        }
+        arrived(1);
+        // Hand-over: this wave's part of the next stage has landed (loads complete in order, only those of later stages
+        // may remain), and behind the barrier everybody's has, and nobody reads this step's stage any more.
+        asm volatile("s_waitcnt %0" ::"n"(wait_vm((NA - 2) * DA + (NB - 2) * DB)) : "memory");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        slice(std::integral_constant<int, SL - 1>{}, (uint32_t)(sa_next * A_B), (uint32_t)(sb_next * B_B), [&](int m) {
+            constexpr int NM = TM * TN, ND = DA + DB, GAP = NM / ND > 0 ? NM / ND : 1, PER = (ND + NM - 1) / NM;
+            if (m % GAP != GAP - 1) return;
+#pragma unroll
+            for (int d = m / GAP * PER; d < m / GAP * PER + PER; ++d) {
+                if (d < DB) dma_b(s + NB, sb, d);
+                else if (d < ND) dma_a(s + NA, sa, d - DB);
             }
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            const int rows_here = (TM - pass * 2 >= 2) ? 64 : 32;
-            const int ch = lane % CH, r0 = lane / CH;
+        });
+        sa = sa_next;
+        sb = sb_next;
+    }
+    // the repeated requests of the last steps are still writing LDS, and the last fragment reads are in flight
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    arrived(0);
+
+    // Epilogue: lane (t = lane % 16, h = lane / 16) holds columns 4 h .. + 3 of token t in every 16 x 16 tile.  Exchanging
+    // odd against even rows of lanes between two neighbouring tiles leaves 8 consecutive columns in a lane, and 64
+    // consecutive bytes of a token in the four lanes that share it: 16-byte stores without a trip through LDS (which
+    // took 3.6 us instead of 1.9 per 256 x 256 tile).
+    const int h = lane >> 4;
+    if (sums) {
+        const int64_t lds_ = (NC + 3) / 4 * 4;
 #pragma unroll
-            for (int rr = 0; rr < 64 / RPI; ++rr) {
-                const int r = rr * RPI + r0;
-                if (r < rows_here) {
-                    const int64_t t = m0 + wm * 32 * TM + pass * 64 + r;
-                    const int64_t n = n0 + wn * 32 * TN + ch * 8;
-                    if (t < M) {
-                        const u32x4 vv = *reinterpret_cast<const u32x4*>(ew + r * EROW + ch * 16);
-                        if (n + 7 < NC) {
-                            *reinterpret_cast<u32x4*>(C + t * ldc + n) = vv;
-                        } else {
+        for (int i = 0; i < TM; ++i) {
+            const int64_t t = m0 + (wm * TM + i) * 16 + (lane & 15);
+            float* row = sums + ((int64_t)part * M + t) * lds_;
 #pragma unroll
-                            for (int e = 0; e < 8; ++e)
-                                if (n + e < NC) C[t * ldc + n + e] = (bf16_t)((vv[e >> 1] >> (16 * (e & 1))) & 0xFFFFu);
-                        }
-                    }
-                }
+            for (int j = 0; j < TN; ++j) {
+                const int64_t n = n0 + (wn * TN + j) * 16 + 4 * h;
+                if (t < M && n < NC) *reinterpret_cast<f32x4*>(row + n) = acc[j][i];
             }
         }
-    } else {
+        return;
+    }
+    const bool vec_ok = (ldc % 8 == 0);
 #pragma unroll
-        for (int it = 0; it < TM; ++it) {
-            const int64_t t = m0 + wm * 32 * TM + it * 32 + (lane & 31);
-            if (t >= M) continue;
-            bf16_t* crow = C + t * ldc;
+    for (int i = 0; i < TM; ++i) {
+        const int64_t t = m0 + (wm * TM + i) * 16 + (lane & 15);
+        bf16_t* crow = C + t * ldc;
+        const int64_t nw = n0 + wn * TN * 16;
+        if (vec_ok) {
 #pragma unroll
-            for (int jw = 0; jw < TN; ++jw)
+            for (int j = 0; j + 1 < TN; j += 2) {
+                const uint32_t a0 = pack_bf16x2(acc[j][i][0], acc[j][i][1]), a1 = pack_bf16x2(acc[j][i][2], acc[j][i][3]);
+                const uint32_t b0 = pack_bf16x2(acc[j + 1][i][0], acc[j + 1][i][1]);
+                const uint32_t b1 = pack_bf16x2(acc[j + 1][i][2], acc[j + 1][i][3]);
+                const auto s0 = __builtin_amdgcn_permlane16_swap(a0, b0, false, false);
+                const auto s1 = __builtin_amdgcn_permlane16_swap(a1, b1, false, false);
+                const u32x4 v = {s0[0], s1[0], s0[1], s1[1]};
+                const int64_t n = nw + (j + (h & 1)) * 16 + (h >> 1) * 8;
+                if (t < M && n < NC) *reinterpret_cast<u32x4*>(crow + n) = v;  // NC % 8 == 0 where ldc is (ldc = NC)
+            }
+            if (TN & 1) {
+                const int64_t n = nw + (TN - 1) * 16 + 4 * h;
+                const f32x4 a = acc[TN - 1][i];
+                if (t < M && n < NC) *reinterpret_cast<uint2*>(crow + n) = make_uint2(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]));
+            }
+        } else if (t < M) {
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int64_t n = n0 + wn * 32 * TN + jw * 32 + 8 * g + 4 * (lane >> 5);
+            for (int j = 0; j < TN; ++j)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (n + e < NC) crow[n + e] = f32_to_bf16(acc[jw][it][4 * g + e]);
+                for (int e = 0; e < 4; ++e) {
+                    const int64_t n = nw + j * 16 + 4 * h + e;
+                    if (n < NC) crow[n] = f32_to_bf16(acc[j][i][e]);
                 }
         }
     }
@@ -567,37 +556,63 @@ constexpr int RPAD = 128;  // contraction padding of the expanded operand: the l
 size_t mfma_fwd_workspace(int64_t N, int64_t K) { return (size_t)(round_up(N, 32) * round_up(K, RPAD) * 2); }
 size_t mfma_bwd_input_workspace(int64_t N, int64_t K) { return (size_t)(round_up(K, 32) * round_up(N, RPAD) * 2); }
 
-template <int TM, int TN>
+template <int BM, int BN>
 static hipError_t launch_gemm_cfg(const bf16_t* A, int64_t lda, const u32x4* frag, bf16_t* C, int64_t ldc, int64_t M,
                                   int64_t NC, int64_t R, int64_t R16, hipStream_t st) {
-    using Cfg = GemmCfg<TM, TN>;
+    using Cfg = GemmCfg<BM, BN>;
     static LdsLimit limit;
-    hipError_t e = limit.ensure((const void*)gemm_kernel<TM, TN>, Cfg::LDS_B);
+    hipError_t e = limit.ensure((const void*)gemm_kernel<BM, BN>, Cfg::LDS_B);
     if (e != hipSuccess) return e;
-    const int tiles_m = (int)((M + Cfg::BMT - 1) / Cfg::BMT), tiles_n = (int)((NC + Cfg::BNT - 1) / Cfg::BNT);
     TileMap tmap;
-    const unsigned wgs = make_tile_map(tiles_m, tiles_n, 1, 32 * Cfg::OCC, (double)Cfg::BMT, (double)Cfg::BNT, &tmap);
-    BCQ_LAUNCH((gemm_kernel<TM, TN>), dim3(wgs), dim3(256), Cfg::LDS_B, st, A, lda, frag, C, ldc, M, NC, R, R16,
-                       tmap);
+    const unsigned wgs = make_tile_map((int)((M + BM - 1) / BM), (int)((NC + BN - 1) / BN), 1, (double)BM, (double)BN, &tmap);
+    const int steps = (int)((R + 64 * Cfg::KC - 1) / (64 * Cfg::KC));
+    BCQ_LAUNCH((gemm_kernel<BM, BN>), dim3(wgs), dim3(64 * Cfg::NW), Cfg::LDS_B, st, A, lda, frag, C, ldc, M, NC, R, R16,
+                       tmap, steps, (float*)nullptr);
     return hipGetLastError();
 }
 
-// Tile choice from measurements on the workloads' shapes: 256 x 256 tiles (one workgroup per compute unit, the best
-// MFMA rate) when they fill at least 80 % of their last round on the 256 compute units, else 128 x 128 tiles
-// (two or three resident per compute unit, so ragged tile counts level out).  256 x 128 never won by more than 6 %.
+// Tile choice: the least estimated time over the rounds of workgroups on 256 compute units (one resident on each).  A K-step
+// of 64 takes 0.0115 ns per product and 1.11 ns per row and column of the tile (a little less when fewer compute units
+// share power and caches: the share of them that works to the power 0.22), at least the 362 ns of its barrier and waits; a
+// round costs another 2.6 us to start and 5 us per 256 x 256 outputs to store.  Fitted to 333 products of 64 to 16384 tokens
+// with 768 to 10240 rows and columns, every shape timed: the pick is the fastest or within 3 % of it for 328 of them,
+// within 7 % for all (256 x 256 tiles against the pick: 1280 x 5120 at 4096 tokens 87 / 47 us, 3072 x 1024 29 / 27).
+static double gemm_estimate(int bm, int bn, int kc, int64_t M, int64_t NC, int64_t R) {
+    const double tiles = (double)((M + bm - 1) / bm) * (double)((NC + bn - 1) / bn), steps = (double)((R + 63) / 64);
+    const double full = 0.01153 * bm * bn + 1.112 * (bm + bn), least = 362.0 / kc;
+    const double fixed = 2600.0 + 4955.0 * bm * bn / 65536.0;
+    const double rounds = (double)(int64_t)(tiles / 256), busy = (tiles - 256 * rounds) / 256;
+    double t = rounds * (steps * (full > least ? full : least) + fixed);
+    if (busy > 0) {
+        const double part = full * pow(busy, 0.22);
+        t += steps * (part > least ? part : least) + fixed;
+    }
+    return t;
+}
+
 static hipError_t launch_gemm(const bf16_t* A, int64_t lda, const u32x4* frag, bf16_t* C, int64_t ldc, int64_t M,
                               int64_t NC, int64_t R, int64_t R16, hipStream_t st) {
-    const int64_t tiles = ((M + 255) / 256) * ((NC + 255) / 256);
-    const int64_t rounds = (tiles + 255) / 256;
-    if (tiles * 10 >= rounds * 256 * 8) return launch_gemm_cfg<4, 4>(A, lda, frag, C, ldc, M, NC, R, R16, st);
-    // few tokens (a few hundred): 128 x 128 tiles would leave compute units without work; 64-token tiles fill them
-    const int64_t tiles128 = ((M + 127) / 128) * ((NC + 127) / 128);
-    if (tiles128 < 192) {
-        const int64_t tiles_64x128 = ((M + 63) / 64) * ((NC + 127) / 128);
-        if (tiles_64x128 >= 192) return launch_gemm_cfg<1, 2>(A, lda, frag, C, ldc, M, NC, R, R16, st);
-        return launch_gemm_cfg<1, 1>(A, lda, frag, C, ldc, M, NC, R, R16, st);
+    static constexpr int shapes[][3] = {{256, 256, 1}, {256, 192, 1}, {256, 160, 1}, {256, 128, 1},
+                                        {128, 160, 1}, {128, 128, 1}, {64, 128, 2}, {64, 64, 2}};
+    int best = 0;
+    double least = 1e300;
+    for (int i = 0; i < 8; ++i) {
+        const double t = gemm_estimate(shapes[i][0], shapes[i][1], shapes[i][2], M, NC, R);
+        if (t < least) {
+            least = t;
+            best = i;
+        }
     }
-    return launch_gemm_cfg<2, 2>(A, lda, frag, C, ldc, M, NC, R, R16, st);
+    switch (best) {
+        case 0: return launch_gemm_cfg<256, 256>(A, lda, frag, C, ldc, M, NC, R, R16, st);
+        case 1: return launch_gemm_cfg<256, 192>(A, lda, frag, C, ldc, M, NC, R, R16, st);
+        case 2: return launch_gemm_cfg<256, 160>(A, lda, frag, C, ldc, M, NC, R, R16, st);
+        case 3: return launch_gemm_cfg<256, 128>(A, lda, frag, C, ldc, M, NC, R, R16, st);
+        case 4: return launch_gemm_cfg<128, 160>(A, lda, frag, C, ldc, M, NC, R, R16, st);
+        case 5: return launch_gemm_cfg<128, 128>(A, lda, frag, C, ldc, M, NC, R, R16, st);
+        case 6: return launch_gemm_cfg<64, 128>(A, lda, frag, C, ldc, M, NC, R, R16, st);
+        default: return launch_gemm_cfg<64, 64>(A, lda, frag, C, ldc, M, NC, R, R16, st);
+    }
 }
 
 hipError_t launch_fwd_mfma(const uint32_t* packed, const float* alpha, const void* x, int64_t T, int64_t N,
@@ -730,7 +745,7 @@ __global__ __launch_bounds__(256, 1) void dalpha_kernel(const bf16_t* __restrict
     const int wm = wave >> 1, wn = wave & 1;  // wm: k half, wn: n half
     const int tiles_k = tmap.tiles_m;
     int split, tile_k, tile_n;
-    if (!map_tile(tmap, splits, blockIdx.x, split, tile_k, tile_n)) return;
+    if (!map_tile(tmap, blockIdx.x, split, tile_k, tile_n)) return;
     const int64_t k0 = (int64_t)tile_k * DA_TILE, n0 = (int64_t)tile_n * DA_TILE;
     const int64_t t_begin = (int64_t)split * tokens_per_split;  // a multiple of 64
     const int64_t t_end = (t_begin + tokens_per_split < T) ? t_begin + tokens_per_split : T;
@@ -1117,7 +1132,7 @@ static hipError_t launch_dalpha_piece(const uint32_t* packed, const bf16_t* x, c
         if (e != hipSuccess) return e;
     }
     TileMap tmap;
-    const unsigned wgs = make_tile_map(pl.tiles_k, pl.tiles_n, pl.splits, 32, 1.0, 1.0, &tmap);
+    const unsigned wgs = make_tile_map(pl.tiles_k, pl.tiles_n, pl.splits, 1.0, 1.0, &tmap);
     dim3 grid(wgs);
     const int qt = q_train <= 4 ? q_train : 8;
 #define BCQ_DA_LAUNCH(XGV, QTV, FV)                                                                                   \
