@@ -21,11 +21,9 @@
 namespace bcq {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-
-
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 
@@ -577,17 +575,24 @@ static hipError_t launch_gemm_cfg(const bf16_t* A, int64_t lda, const u32x4* fra
 // round costs another 2.6 us to start and 5 us per 256 x 256 outputs to store.  Fitted to 333 products of 64 to 16384 tokens
 // with 768 to 10240 rows and columns, every shape timed: the pick is the fastest or within 3 % of it for 328 of them,
 // within 7 % for all (256 x 256 tiles against the pick: 1280 x 5120 at 4096 tokens 87 / 47 us, 3072 x 1024 29 / 27).
-static double gemm_estimate(int bm, int bn, int kc, int64_t M, int64_t NC, int64_t R) {
-    const double tiles = (double)((M + bm - 1) / bm) * (double)((NC + bn - 1) / bn), steps = (double)((R + 63) / 64);
-    const double full = 0.01153 * bm * bn + 1.112 * (bm + bn), least = 362.0 / kc;
-    const double fixed = 2600.0 + 4955.0 * bm * bn / 65536.0;
-    const double rounds = (double)(int64_t)(tiles / 256), busy = (tiles - 256 * rounds) / 256;
-    double t = rounds * (steps * (full > least ? full : least) + fixed);
-    if (busy > 0) {
-        const double part = full * pow(busy, 0.22);
-        t += steps * (part > least ? part : least) + fixed;
+struct ShareTable {  // (k / 256) ^ e
+    double v[256];
+    explicit ShareTable(double e) {
+        for (int k = 0; k < 256; ++k) v[k] = pow(k / 256.0, e);
+    }
+};
+static double round_estimate(double full, double least, const ShareTable& share, int64_t tiles, int64_t steps, double fixed) {
+    double t = (double)(tiles / 256) * ((double)steps * (full > least ? full : least) + fixed);
+    if (tiles % 256) {
+        const double part = full * share.v[tiles % 256];
+        t += (double)steps * (part > least ? part : least) + fixed;
     }
     return t;
+}
+static double gemm_estimate(int bm, int bn, int kc, int64_t M, int64_t NC, int64_t R) {
+    static const ShareTable share(0.22);
+    return round_estimate(0.01153 * bm * bn + 1.112 * (bm + bn), 362.0 / kc, share, ((M + bm - 1) / bm) * ((NC + bn - 1) / bn),
+                          (R + 63) / 64, 2600.0 + 4955.0 * bm * bn / 65536.0);
 }
 
 static hipError_t launch_gemm(const bf16_t* A, int64_t lda, const u32x4* frag, bf16_t* C, int64_t ldc, int64_t M,
@@ -677,326 +682,258 @@ hipError_t launch_bwd_input_mfma_split(const uint32_t* packed, const float* alph
 // G is one dense contraction over the tokens (2 T N K matrix-core flops for ALL planes together, instead of
 // 2 q T N K for q plane products); the sign planes only enter a signed row sum of the accumulators.
 //
-// Both MFMA operands need the token index innermost, which neither activation has in memory.  LDS fragment
-// reads are the scarce resource of a compute unit (a 16-byte-per-lane read instruction takes ~16 clocks), so
-// only ONE operand may pass through LDS:
-//   1. transpose_frag_kernel rewrites the smaller activation (x if K <= N, else dy) into MFMA fragment order
-//      with the token index innermost (8 x 8 register transposes); its fragments are then loaded straight
-//      from global memory, 1 KiB coalesced per wave load, exactly like the expanded weights of the forward.
-//   2. dalpha_kernel: 256 (k) x 256 (n) tile of G^T for one slice of the tokens; 4 waves in a 2 x 2 grid, each
-//      128 x 128 = 4 x 4 tiles of v_mfma_f32_32x32x16_bf16 with X^T as first and dY^T as second operand, so a
-//      lane holds one n and 16 k of every tile.  The other activation goes global -> registers -> 8 x 8
-//      transpose (32 v_perm) -> XOR-swizzled LDS tile [column][64 tokens]; writes and fragment reads are
-//      bank-conflict free.  The epilogue forms the signed sums over k for every trained plane.
-//   3. dalpha_reduce_kernel adds the partial sums of all (token slice, k tile) pairs in a fixed order (no
+// Both MFMA operands need the token index innermost, which neither activation has in memory:
+//   1. dalpha_kernel: a tile of G^T (k x n) for one slice of the tokens.  Both activations go global -> LDS directly as
+//      they lie in memory (rows of tokens) and are transposed on the way out by ds_read_b64_tr_b16: no transposed copy
+//      (34 us and 64 MB each way for 2048 columns at 16384 tokens), no transposition in registers.  Loop, waits and barrier are
+//      those of gemm_kernel, and so is what bounds it: power with all compute units busy (8192 x 2048 at 16384 tokens,
+//      q = 3, the whole call 490 -> 404 us, 6144 x 2048 463 -> 322, 3072 x 1024 at 4096 tokens 41 -> 33).  The epilogue forms the signed sums
+//      over k for every trained plane.
+//   2. dalpha_reduce_kernel adds the partial sums of all (token slice, k tile) pairs in a fixed order (no
 //      floating-point atomics, bit-reproducible).
-constexpr int DA_TILE = 256;               // k and n extent of a workgroup tile
-constexpr int DA_STAGE = DA_TILE * 128;    // bytes per LDS stage: 256 columns x 64 tokens x 2 B
 
-__device__ __forceinline__ int da_swz(int col, int chunk) { return col * 128 + ((chunk ^ (col & 7) ^ ((col >> 3) & 7)) << 4); }
+// Rows of 64 tokens, BK or BN columns wide, in 32-byte pieces (16 columns) with piece c of token t at c ^ da_swizzle(t): the
+// transposing read takes 4 tokens x 32 bytes per 16 lanes, and the eight tokens that 32 lanes touch then lie in different banks.
+__device__ __forceinline__ int da_swizzle(int t) { return (t & 3) | (((t >> 3) & 1) << 2); }
 
-// 8 x 8 transpose of 16-bit elements: in[r] holds row r (8 elements), out[c] holds column c.
-__device__ __forceinline__ void transpose8x8(const u32x4 (&in)[8], u32x4 (&out)[8]) {
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-            out[c][w] = __builtin_amdgcn_perm(in[2 * w + 1][c >> 1], in[2 * w][c >> 1], (c & 1) ? 0x07060302u : 0x05040100u);
-}
+template <int TILE> struct DalphaShape;  // TILE x TILE outputs; WK x WN waves; NX, NY: stages of x and dy
+template <> struct DalphaShape<256> { static constexpr int WK = 2, WN = 4, NX = 3, NY = 2; };
+template <> struct DalphaShape<128> { static constexpr int WK = 2, WN = 2, NX = 5, NY = 5; };
+template <int TILE>
+struct DalphaCfg : DalphaShape<TILE> {
+    using S = DalphaShape<TILE>;
+    static constexpr int NW = S::WK * S::WN;
+    static constexpr int TK = TILE / S::WK / 16, TN = TILE / S::WN / 16;
+    static constexpr int ROWB = TILE * 2, STAGE_B = 64 * ROWB;     // a stage: 64 tokens
+    static constexpr int RPI = 1024 / ROWB;                        // tokens per 1 KiB request
+    static constexpr int J = 64 / RPI / NW;                        // requests per wave and stage
+    static constexpr int LDS_B = (S::NX + S::NY) * STAGE_B;
+    static_assert(J * RPI * NW == 64 && LDS_B <= 160 * 1024 && S::NX >= S::NY && S::NX - S::NY <= 1, "as in gemm_kernel");
+};
 
-// act[T][C] (row-major bf16) -> fragments with the token index innermost: for column tile ct (32 columns) and
-// token slice ks (16 tokens) one 1 KiB block; lane (c % 32) + 32 g holds tokens 16 ks + 8 g .. + 7 of column c.
-// Tokens >= T (up to T16 * 16) and columns >= C are written as zeros.
-__global__ __launch_bounds__(256) void transpose_frag_kernel(const bf16_t* __restrict__ act, int64_t T, int64_t C,
-                                                             int64_t T16, u32x4* __restrict__ frag) {
-    const int cb = threadIdx.x & 15, tbl = threadIdx.x >> 4;       // 16 column blocks x 16 token blocks per group
-    const int64_t c0 = ((int64_t)blockIdx.x * 16 + cb) * 8;       // first of 8 columns
-    const int64_t tb = (int64_t)blockIdx.y * 16 + tbl;            // block of 8 tokens
-    if (tb * 8 >= T16 * 16) return;
-    u32x4 in[8], out[8];
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const int64_t t = tb * 8 + r;
-        in[r] = (t < T && c0 < C) ? *reinterpret_cast<const u32x4*>(act + t * C + c0) : zero;
-    }
-    transpose8x8(in, out);
-    const int64_t ct = c0 / 32, ks = tb >> 1;
-    const int g = (int)(tb & 1);
-    if (ct * 32 >= ((C + 31) / 32) * 32) return;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) frag[(ct * T16 + ks) * 64 + (c0 % 32) + c + 32 * g] = out[c];
-}
-
-// XG: x comes as fragments from global memory and dy through LDS; otherwise the reverse.
 // QT: planes summed in the epilogue (q_train rounded up to 1, 2, 3, 4 or 8; extra planes are computed, not stored).
-// FINE: partial sums are kept per 32 columns k (for scale groups that are not whole 256-column tiles) instead of
-//       per tile; they go to part[split][plane][n][8 tiles_k] and dalpha_reduce_fine_kernel adds each group's run.
-template <bool XG, int QT, bool FINE>
-__global__ __launch_bounds__(256, 1) void dalpha_kernel(const bf16_t* __restrict__ L /* activation through LDS */,
-                                                        int64_t ldl, int64_t lcols,
-                                                        const u32x4* __restrict__ Gfrag, int64_t T16,
-                                                        const uint32_t* __restrict__ packed,
-                                                        float* __restrict__ part, int64_t T, int64_t N, int64_t K,
-                                                        int q_train, TileMap tmap, int splits,
-                                                        int64_t tokens_per_split) {
+// FINE: partial sums are kept per 32 columns k (for scale groups that are not whole tiles) instead of per tile; they
+//       go to part[split][plane][n][TILE / 32 tiles_k] and dalpha_reduce_fine_kernel adds each group's run.
+template <int TILE, int QT, bool FINE>
+__global__ __launch_bounds__((64 * DalphaCfg<TILE>::NW), 2) void dalpha_kernel(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy, int64_t ldy, const uint32_t* __restrict__ packed,
+    float* __restrict__ part, int64_t T, int64_t N, int64_t K, int q_train, TileMap tmap, int64_t tokens_per_split) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    using Cfg = DalphaCfg<TILE>;
+    constexpr int WN = Cfg::WN, TK = Cfg::TK, TN = Cfg::TN, NX = Cfg::NX, NY = Cfg::NY, J = Cfg::J, RPI = Cfg::RPI;
+    constexpr int ROWB = Cfg::ROWB, STAGE_B = Cfg::STAGE_B;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;  // wm: k half, wn: n half
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = wave / WN, wn = wave % WN;
     const int tiles_k = tmap.tiles_m;
     int split, tile_k, tile_n;
     if (!map_tile(tmap, blockIdx.x, split, tile_k, tile_n)) return;
-    const int64_t k0 = (int64_t)tile_k * DA_TILE, n0 = (int64_t)tile_n * DA_TILE;
+    const int64_t k0 = (int64_t)tile_k * TILE, n0 = (int64_t)tile_n * TILE;
     const int64_t t_begin = (int64_t)split * tokens_per_split;  // a multiple of 64
     const int64_t t_end = (t_begin + tokens_per_split < T) ? t_begin + tokens_per_split : T;
-    const int64_t steps = (t_end - t_begin + 63) / 64;
-    const int64_t step0 = t_begin / 64;
+    const int last = (int)((t_end - t_begin + 63) / 64) - 1;
 
-    f32x16 acc[4][4];  // [k tile][n tile]
+    f32x4 acc[TN][TK];  // [n tile][k tile]
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int i = 0; i < TK; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // LDS-side activation: thread = (cb = column block of 8, tb = token block of 8)
-    const int cb = tid & 31, tb = tid >> 5;
-    int64_t lcol = (XG ? n0 : k0) + cb * 8;
-    lcol = lcol < lcols - 8 ? lcol : lcols - 8;  // clamped columns only feed outputs that are never stored
-    u32x4 lr[8];
-    // rows of one step: uniform base (advances by 64 rows per step) + 32-bit lane offset + r rows
-    const uint32_t row_b = (uint32_t)(ldl * 2);
-    const uint32_t voff0 = (uint32_t)(tb * 8) * row_b + (uint32_t)(lcol * 2);
-    auto load_blocks = [&](int64_t step) {
-        const int64_t t0 = (step0 + step) * 64;
-        const unsigned char* base = reinterpret_cast<const unsigned char*>(L + t0 * ldl);
-        if (t0 + 64 <= T) {
+    // Requests: a lane's 16 bytes land at its place of the row and come from where the swizzle puts them.  The descriptor of a
+    // step starts at its first token and ends with the activation, so tokens beyond T come back as zeros; columns beyond
+    // K or N (of the next row) only feed outputs that are never stored.
+    uint32_t xoff[J], yoff[J];
 #pragma unroll
-            for (int r = 0; r < 8; ++r) lr[r] = *reinterpret_cast<const u32x4*>(base + (voff0 + (uint32_t)r * row_b));
-        } else {  // last, ragged step: rows beyond T are clamped (they meet zero fragments of the other operand)
+    for (int j = 0; j < J; ++j) {
+        const int t = (wave * J + j) * RPI + lane / (64 / RPI);
+        const int col = ((lane % (64 / RPI)) ^ (da_swizzle(t) << 1)) * 16;
+        xoff[j] = (uint32_t)(t * K * 2 + col);
+        yoff[j] = (uint32_t)(t * ldy * 2 + col);
+    }
+    auto rows_from = [&](const bf16_t* act, int64_t ld, int64_t col, int step) {
+        const int64_t t = t_begin + (int64_t)(step < last ? step : last) * 64;
+        const int64_t left = ((T - t) * ld - col) * 2;
+        return __builtin_amdgcn_make_buffer_rsrc((void*)(act + t * ld + col), 0, (int)(left < 0x7fffffffll ? left : 0x7fffffffll),
+                                                 0x00020000);
+    };
+    auto dma = [&](__amdgpu_buffer_rsrc_t rows, int stage_byte, uint32_t off, int j) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            rows, (void __attribute__((address_space(3)))*)(smem + stage_byte + (wave * J + j) * 1024), 16, off, 0, 0, 0);
+    };
+
+    // Fragments (16 columns x 32 tokens): two transposing reads, lanes 16 h .. + 15 give the addresses of tokens 8 h + 0 .. 3
+    // and + 4 .. 7 (four lanes to a token's 32 bytes) and receive one column each.  As in gemm_kernel the reads are inline
+    // assembly, tied to an explicit wait.
+    u32x2 xf[2][TK][2], yf[2][TN][2];
+    const int h = lane >> 4, tok = 8 * h + ((lane >> 2) & 3);
+    const uint32_t lanebase = (uint32_t)(tok * ROWB + (lane & 3) * 8);
+    uint32_t xaddr[TK], yaddr[TN];
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                int64_t t = t0 + tb * 8 + r;
-                t = t < T ? t : T - 1;
-                lr[r] = *reinterpret_cast<const u32x4*>(L + t * ldl + lcol);
+    for (int i = 0; i < TK; ++i) xaddr[i] = lanebase + (uint32_t)(((wk * TK + i) ^ da_swizzle(tok)) * 32);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) yaddr[j] = lanebase + (uint32_t)(((wn * TN + j) ^ da_swizzle(tok)) * 32 + NX * STAGE_B);
+    auto read_t = [&](u32x2 (&f)[2], uint32_t addr, auto KK) {
+        constexpr int kk = decltype(KK)::value;
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f[0]) : "v"(addr), "n"(kk * 32 * ROWB));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f[1]) : "v"(addr), "n"(kk * 32 * ROWB + 4 * ROWB));
+    };
+    auto arrived = [&](int p) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < TK; ++i) asm volatile("" : "+v"(xf[p][i][0]), "+v"(xf[p][i][1]));
+#pragma unroll
+        for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(yf[p][j][0]), "+v"(yf[p][j][1]));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto whole = [](const u32x2 (&f)[2]) { return as_bf16x8(u32x4{f[0][0], f[0][1], f[1][0], f[1][1]}); };
+    auto slice = [&](auto KK, uint32_t xstage, uint32_t ystage, auto&& also) {
+        constexpr int kk = decltype(KK)::value, NM = TK * TN, NR = TK + TN;
+        constexpr int GAP = NM * 3 / 4 / NR > 0 ? NM * 3 / 4 / NR : 1;
+        static_assert(NR <= NM, "one fragment per MFMA");
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+            const int j = m / TK, i = (j & 1) ? TK - 1 - m % TK : m % TK;
+            acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(whole(xf[kk][i]), whole(yf[kk][j]), acc[j][i], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (m % GAP == 0) {
+                const int r = m / GAP;
+                if (r < TN) read_t(yf[1 - kk][r], yaddr[r] + ystage, std::integral_constant<int, 1 - kk>{});
+                else if (r < NR) read_t(xf[1 - kk][r - TN], xaddr[r - TN] + xstage, std::integral_constant<int, 1 - kk>{});
             }
-        }
-    };
-    // column c of this thread's 8 x 8 block: 8 tokens of one column = one 16-byte LDS chunk (4 v_perm + 1 write)
-    auto store_col = [&](int buf, int c) {
-        u32x4 o;
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-            o[w] = __builtin_amdgcn_perm(lr[2 * w + 1][c >> 1], lr[2 * w][c >> 1], (c & 1) ? 0x07060302u : 0x05040100u);
-        *reinterpret_cast<u32x4*>(smem + buf * DA_STAGE + da_swz(cb * 8 + c, tb)) = o;
-    };
-    auto store_blocks = [&](int buf) {
-#pragma unroll
-        for (int c = 0; c < 8; ++c) store_col(buf, c);
-    };
-    bf16x8 lf[2][4];
-    const int lbase = (XG ? wn : wm) * 128 + (lane & 31);
-    auto read_frags = [&](int buf, int kk) {
-        const unsigned char* sl = smem + buf * DA_STAGE;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            lf[kk & 1][i] = *reinterpret_cast<const bf16x8*>(sl + da_swz(lbase + i * 32, kk * 2 + (lane >> 5)));
-    };
-    // global-side fragments of this wave: 4 column tiles
-    const int64_t gct_count = ((XG ? K : N) + 31) / 32;
-    const int64_t gct0 = ((XG ? k0 + wm * 128 : n0 + wn * 128)) / 32;
-    const u32x4* gptr[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        int64_t ct = gct0 + j;
-        ct = ct < gct_count ? ct : gct_count - 1;
-        gptr[j] = Gfrag + (ct * T16 + step0 * 4) * 64 + lane;
-    }
-    u32x4 g[4][4];  // [kk][tile]
-    auto load_g = [&](int kk, int64_t step) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) g[kk][j] = gptr[j][(step * 4 + kk) * 64];
-    };
-    auto mfma_one = [&](int kk, int i, int j) {
-        if (XG)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(g[kk][i]), lf[kk & 1][j], acc[i][j], 0, 0, 0);
-        else
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lf[kk & 1][i], as_bf16x8(g[kk][j]), acc[i][j], 0, 0, 0);
-    };
-    auto mfma_slice = [&](int kk) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) mfma_one(kk, i, j);
-    };
-
-    // Three LDS stages.  The blocks of step s + 1 are requested during step s - 1, transposed and written into
-    // their stage during the FIRST slice of step s, interleaved with its MFMAs (a stage is free from the barrier
-    // that ends the step after its last read), and read from the barrier that ends step s: the global latency
-    // has a whole step of cover and neither the transposes nor the LDS writes wait in front of a barrier.
-    const int64_t last = steps - 1;
-    load_blocks(0);
-    load_g(0, 0);
-    store_blocks(0);
-    load_blocks(last < 1 ? last : 1);  // followed by three slices of fragment loads, as in every step of the loop
-#pragma unroll
-    for (int kk = 1; kk < 4; ++kk) load_g(kk, 0);
-    __syncthreads();
-    read_frags(0, 0);
-    int stg = 0;  // stage of step s
-    for (int64_t s = 0; s < steps; ++s) {
-        const int64_t nx = s < last ? s + 1 : last;
-        const int64_t nx2 = s + 2 < steps ? s + 2 : last;
-        const int stg_next = (stg == 2) ? 0 : stg + 1;
-        read_frags(stg, 1);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {  // two MFMAs (64 clocks of the matrix pipe) cover one column's perms and write
-            mfma_one(0, c >> 1, 2 * (c & 1));
-            mfma_one(0, c >> 1, 2 * (c & 1) + 1);
-            store_col(stg_next, c);
+            also(m);
             __builtin_amdgcn_sched_barrier(0);
         }
-        load_g(0, nx);
-        load_blocks(nx2);
-        __builtin_amdgcn_sched_barrier(0);
+    };
+
 #pragma unroll
-        for (int kk = 1; kk < 3; ++kk) {
-            read_frags(stg, kk + 1);
-            mfma_slice(kk);
-            load_g(kk, nx);
-            __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 16, 0);
-            __builtin_amdgcn_sched_group_barrier(0x020, 4, 0);
-            __builtin_amdgcn_sched_barrier(0);
+    for (int p = 0; p < NX; ++p) {
+        const auto xr = rows_from(x, K, k0, p), yr = rows_from(dy, ldy, n0, p);
+#pragma unroll
+        for (int j = 0; j < J; ++j) dma(xr, p * STAGE_B, xoff[j], j);
+        if (p < NY) {
+#pragma unroll
+            for (int j = 0; j < J; ++j) dma(yr, (NX + p) * STAGE_B, yoff[j], j);
         }
-        __syncthreads();
-        read_frags(stg_next, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_slice(3);
-        load_g(3, nx);
-        __builtin_amdgcn_sched_group_barrier(0x008, 16, 0);
-        __builtin_amdgcn_sched_group_barrier(0x020, 4, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        stg = stg_next;
     }
+    asm volatile("s_waitcnt %0" ::"n"(wait_vm((NX + NY - 2) * J)) : "memory");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) read_t(yf[0][j], yaddr[j], std::integral_constant<int, 0>{});
+#pragma unroll
+    for (int i = 0; i < TK; ++i) read_t(xf[0][i], xaddr[i], std::integral_constant<int, 0>{});
+    __builtin_amdgcn_sched_barrier(0);
+
+    int sx = 0, sy = 0;  // stages of step s
+    for (int s = 0; s <= last; ++s) {
+        const int sx_next = sx + 1 == NX ? 0 : sx + 1, sy_next = sy + 1 == NY ? 0 : sy + 1;
+        arrived(0);
+        slice(std::integral_constant<int, 0>{}, (uint32_t)(sx * STAGE_B), (uint32_t)(sy * STAGE_B), [](int) {});
+        arrived(1);
+        asm volatile("s_waitcnt %0" ::"n"(wait_vm((NX + NY - 4) * J)) : "memory");  // the hand-over, as in gemm_kernel
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        const auto xr = rows_from(x, K, k0, s + NX), yr = rows_from(dy, ldy, n0, s + NY);
+        slice(std::integral_constant<int, 1>{}, (uint32_t)(sx_next * STAGE_B), (uint32_t)(sy_next * STAGE_B), [&](int m) {
+            constexpr int GAP = TK * TN / (2 * J);
+            static_assert(GAP > 0, "at most one request per MFMA");
+            if (m % GAP != GAP - 1) return;
+            const int d = m / GAP;
+            if (d < J) dma(yr, (NX + sy) * STAGE_B, yoff[d], d);
+            else if (d < 2 * J) dma(xr, sx * STAGE_B, xoff[d - J], d - J);
+        });
+        sx = sx_next;
+        sy = sy_next;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    arrived(0);
     __syncthreads();
 
-    // epilogue: signed sums over this wave's 128 k for each plane; lane owns n = n_base + j*32 + lane%32.
-    // All packed words of all trained planes are requested first (one memory latency instead of one per plane);
+    // epilogue: signed sums over this wave's k for each plane; lane (c = lane % 16, h) owns n = 16 j + c and k = 16 i + 4 h + e.
+    // The packed words of (up to four) planes are requested first (one memory latency instead of one per plane);
     // a sign is applied as a factor +-1.0 built from the (inverted) plane bit: shift, and-or, fused multiply-add
     // per value (the product with +-1.0 is exact, so this equals adding the signed value).
-    float* red = reinterpret_cast<float*>(smem);  // [plane][wm][256 n]
-    const int64_t Kw = K / 32;
-    uint32_t words[QT][4][4];  // [plane][k tile][n tile], already inverted and shifted to this lane's rows
-    const int64_t kt0 = (k0 + wm * 128) / 32;                      // first of this wave's four k tiles
-    const bool quad = (kt0 + 3 < Kw) && ((Kw & 3) == 0);           // one aligned 16-byte load per row and plane
+    constexpr int WORDS = TK / 2;  // packed words (32 columns) of this wave
+    constexpr int SLOTS = FINE ? TILE / 32 : Cfg::WK;  // sums per (plane, n): per 32 columns, or per wave row
+    constexpr int PB = QT > 4 ? 4 : QT;                // planes at a time
+    float* red = reinterpret_cast<float*>(smem);       // [plane][slot][n]
+    const int64_t Kw = K / 32, kt0 = (k0 + wk * 16 * TK) / 32;
+    const bool quad = WORDS == 4 && (kt0 + 3 < Kw) && ((Kw & 3) == 0);  // one aligned 16-byte load per row and plane
 #pragma unroll
-    for (int p = 0; p < QT; ++p) {
-        const int pc = p < q_train ? p : q_train - 1;
+    for (int pb = 0; pb < QT; pb += PB) {
+        uint32_t words[PB][TN][WORDS];  // already inverted and shifted to this lane's columns
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t n = n0 + wn * 128 + j * 32 + (lane & 31);
-            const int64_t nc = n < N ? n : N - 1;
-            const uint32_t* prow = packed + ((int64_t)pc * N + nc) * Kw;
-            u32x4 w4;
-            if (quad) {
-                w4 = *reinterpret_cast<const u32x4*>(prow + kt0);
-            } else {
+        for (int p = 0; p < PB; ++p) {
+            const int pc = pb + p < q_train ? pb + p : q_train - 1;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int64_t kt = kt0 + i < Kw ? kt0 + i : Kw - 1;  // tiles beyond K hold zero accumulators
-                    w4[i] = prow[kt];
+            for (int j = 0; j < TN; ++j) {
+                const int64_t n = n0 + (wn * TN + j) * 16 + (lane & 15);
+                const int64_t nc = n < N ? n : N - 1;
+                const uint32_t* prow = packed + ((int64_t)pc * N + nc) * Kw;
+                if (quad) {
+                    const u32x4 w4 = *reinterpret_cast<const u32x4*>(prow + kt0);
+#pragma unroll
+                    for (int w = 0; w < WORDS; ++w) words[p][j][w] = ~(w4[w & 3] >> (4 * h));
+                } else {
+#pragma unroll
+                    for (int w = 0; w < WORDS; ++w) words[p][j][w] = ~(prow[kt0 + w < Kw ? kt0 + w : Kw - 1] >> (4 * h));
                 }
             }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) words[p][i][j] = ~(w4[i] >> (4 * (lane >> 5)));
         }
-    }
-    if (FINE) {
-        // one signed sum per (plane, 32-column k tile, n): red[plane][chunk = 4 wm + i][256 n]
+        // the four lanes that share an n, in a fixed order
+        auto put = [&](const float (&sum)[PB][TN], int slot) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float fs[QT][4];
+            for (int p = 0; p < PB; ++p)
 #pragma unroll
-            for (int p = 0; p < QT; ++p)
+                for (int j = 0; j < TN; ++j) {
+                    float s = sum[p][j];
+                    s += __shfl_xor(s, 16);
+                    s += __shfl_xor(s, 32);
+                    if (lane < 16) red[((pb + p) * SLOTS + slot) * TILE + (wn * TN + j) * 16 + lane] = s;
+                }
+        };
+        float sum[PB][TN] = {};  // every accumulator is read once and added, with its sign, into the sums of the planes
 #pragma unroll
-                for (int j = 0; j < 4; ++j) fs[p][j] = 0.f;
-            if ((k0 + wm * 128 + i * 32) < K) {
+        for (int w = 0; w < WORDS; ++w) {
+            if (kt0 + w < Kw) {  // uniform: words beyond K hold nothing that counts
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < TN; ++j)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int bit = 8 * (v >> 2) + (v & 3);
-                        const float a = acc[i][j][v];
+                    for (int v = 0; v < 8; ++v) {
+                        const int bit = 16 * (v >> 2) + (v & 3);
+                        const float a = acc[j][2 * w + (v >> 2)][v & 3];
 #pragma unroll
-                        for (int p = 0; p < QT; ++p)
-                            fs[p][j] = __builtin_fmaf(a, __uint_as_float(((words[p][i][j] << (31 - bit)) & 0x80000000u) | 0x3f800000u), fs[p][j]);
+                        for (int p = 0; p < PB; ++p)  // sign bit set where the plane bit is 0 (-1): words are inverted
+                            sum[p][j] = __builtin_fmaf(a, __uint_as_float(((words[p][j][w] << (31 - bit)) & 0x80000000u) | 0x3f800000u), sum[p][j]);
                     }
             }
+            if (FINE) {
+                put(sum, wk * WORDS + w);
 #pragma unroll
-            for (int p = 0; p < QT; ++p)
+                for (int p = 0; p < PB; ++p)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    float s = fs[p][j];
-                    s += __shfl_xor(s, 32);
-                    if (lane < 32) red[(p * 8 + wm * 4 + i) * 256 + wn * 128 + j * 32 + lane] = s;
-                }
-        }
-        __syncthreads();
-        const int64_t n = n0 + tid;
-        const int64_t Kc = (int64_t)tiles_k * 8;
-        if (n < N) {
-            for (int p = 0; p < q_train; ++p) {
-                float* dst = part + (((int64_t)split * q_train + p) * N + n) * Kc + (int64_t)tile_k * 8;
-                u32x4 lo, hi;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    lo[c] = __float_as_uint(red[(p * 8 + c) * 256 + tid]);
-                    hi[c] = __float_as_uint(red[(p * 8 + 4 + c) * 256 + tid]);
-                }
-                *reinterpret_cast<u32x4*>(dst) = lo;
-                *reinterpret_cast<u32x4*>(dst + 4) = hi;
+                    for (int j = 0; j < TN; ++j) sum[p][j] = 0.f;
             }
         }
-        return;
+        if (!FINE) put(sum, wk);
     }
-    // every accumulator is read once and added, with its sign, into the sums of all planes
-    float sums[QT][4];  // [plane][n tile]
-#pragma unroll
-    for (int p = 0; p < QT; ++p)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) sums[p][j] = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if ((k0 + wm * 128 + i * 32) < K) {  // uniform: tiles beyond K hold nothing
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int bit = 8 * (v >> 2) + (v & 3);
-                    const float a = acc[i][j][v];
-#pragma unroll
-                    for (int p = 0; p < QT; ++p)  // sign bit set where the plane bit is 0 (-1): words are inverted
-                        sums[p][j] = __builtin_fmaf(a, __uint_as_float(((words[p][i][j] << (31 - bit)) & 0x80000000u) | 0x3f800000u), sums[p][j]);
-                }
-        }
-    }
-#pragma unroll
-    for (int p = 0; p < QT; ++p)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float s = sums[p][j];
-            s += __shfl_xor(s, 32);
-            if (lane < 32) red[(p * 2 + wm) * 256 + wn * 128 + j * 32 + lane] = s;
-        }
     __syncthreads();
-    const int64_t part_id = (int64_t)split * tiles_k + tile_k;
+    const int64_t n = n0 + tid;
+    if (tid >= TILE || n >= N) return;
     for (int p = 0; p < q_train; ++p) {
-        const int64_t n = n0 + tid;
-        if (n < N) part[(part_id * q_train + p) * N + n] = red[(p * 2 + 0) * 256 + tid] + red[(p * 2 + 1) * 256 + tid];
+        const float* sums = red + p * SLOTS * TILE + tid;
+        if (FINE) {
+            float* dst = part + (((int64_t)split * q_train + p) * N + n) * ((int64_t)tiles_k * SLOTS) + (int64_t)tile_k * SLOTS;
+#pragma unroll
+            for (int c = 0; c < SLOTS; c += 4)
+                *reinterpret_cast<f32x4*>(dst + c) = f32x4{sums[c * TILE], sums[(c + 1) * TILE], sums[(c + 2) * TILE], sums[(c + 3) * TILE]};
+        } else {
+            static_assert(FINE || SLOTS == 2, "two rows of waves");
+            part[(((int64_t)split * tiles_k + tile_k) * q_train + p) * N + n] = sums[0] + sums[TILE];
+        }
     }
+#endif
 }
 
 // dalpha[pn][grp] = scale * sum over token slices and over the k tiles of group grp of part[slice][tile][pn],
@@ -1056,31 +993,68 @@ __global__ __launch_bounds__(256) void dalpha_reduce_fine_kernel(const float* __
     if (opt.alpha) adamw_apply(opt, idx, total);
 }
 
-struct DalphaPlan {
-    int tiles_k, tiles_n, splits;
-    int64_t per_split, T16;
-    bool xg, fine;
-    size_t frag_bytes, part_bytes;
+// Bytes of scratch that a call may use for its partial sums: what callers have been told since the kernel also kept a
+// transposed copy of the smaller activation there (which bounds the token slices only where T or both dimensions are small).
+struct DalphaBudget {
+    size_t copy, part;
 };
-
-static DalphaPlan dalpha_plan(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
-    DalphaPlan pl;
-    pl.tiles_k = (int)((K + DA_TILE - 1) / DA_TILE);
-    pl.tiles_n = (int)((N + DA_TILE - 1) / DA_TILE);
-    const int64_t tiles = (int64_t)pl.tiles_k * pl.tiles_n;
-    int64_t s = tiles >= 256 ? 1 : 256 / tiles;       // one round of workgroups on the 256 compute units
-    const int64_t max_s = (T + 255) / 256;            // at least 256 tokens (4 steps) per slice
+static DalphaBudget dalpha_budget(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
+    const int64_t tiles_k = (K + 255) / 256, tiles = tiles_k * ((N + 255) / 256);
+    int64_t s = tiles >= 256 ? 1 : 256 / tiles;
+    const int64_t max_s = (T + 255) / 256;
     if (s > max_s) s = max_s;
     if (s < 1) s = 1;
-    pl.per_split = ((T + s - 1) / s + 63) / 64 * 64;
-    pl.splits = (int)((T + pl.per_split - 1) / pl.per_split);
-    pl.T16 = (T + 63) / 64 * 4;
-    pl.xg = (K <= N);
-    const int64_t gcols = pl.xg ? K : N;
-    pl.frag_bytes = (size_t)(((gcols + 31) / 32) * pl.T16 * 1024);
-    pl.fine = (g != K) && (g % DA_TILE != 0);  // groups that are not whole k tiles need per-32-column partials
-    pl.part_bytes = (size_t)pl.splits * pl.tiles_k * q * N * sizeof(float) * (pl.fine ? 8 : 1);
-    return pl;
+    const int64_t per_split = ((T + s - 1) / s + 63) / 64 * 64, splits = (T + per_split - 1) / per_split;
+    DalphaBudget b;
+    b.copy = (size_t)((((K <= N ? K : N) + 31) / 32) * ((T + 63) / 64 * 4) * 1024);
+    b.part = (size_t)splits * tiles_k * q * N * sizeof(float) * (g != K && g % 256 != 0 ? 8 : 1);
+    return b;
+}
+
+struct DalphaPlan {
+    int tile, tiles_k, tiles_n, splits;
+    int64_t per_split;
+    bool fine;  // groups that are not whole k tiles need per-32-column partials
+    size_t part_bytes;
+};
+
+// Tile and token slices by an estimate like that of launch_gemm: a step of 64 tokens 0.0117 ns per product and 1.25 ns per
+// row and column, at least 490 ns; a round 6.4 us and 0.5 us per plane and 256 x 256 outputs; the partial sums, written and
+// read by the reduction, 2 ns a KB.  `budget` bounds those.  Fitted to 237 products of 64 to 16384 tokens, up to 14 slice
+// counts of both tiles timed: within 3 % of the fastest for 218, within 14 % for all (6144 x 2048 at 16384 tokens: 192 tiles
+// in one slice leave a quarter of the chip idle, 430 us; four slices 322).
+static DalphaPlan dalpha_plan(int64_t T, int64_t N, int64_t K, int64_t g, int q, int smallest, size_t budget) {
+    static const ShareTable share(0.112);
+    DalphaPlan best = {};
+    double least = 1e300;
+    const int64_t steps = (T + 63) / 64;
+    for (int tile = 256; tile >= smallest; tile -= 128) {
+        DalphaPlan pl;
+        pl.tile = tile;
+        pl.tiles_k = (int)((K + tile - 1) / tile);
+        pl.tiles_n = (int)((N + tile - 1) / tile);
+        pl.fine = (g != K) && (g % tile != 0);
+        const int64_t tiles = (int64_t)pl.tiles_k * pl.tiles_n;
+        const size_t slice_bytes = (size_t)pl.tiles_k * q * N * sizeof(float) * (pl.fine ? tile / 32 : 1);
+        int64_t before = 0;
+        for (int64_t s = 1; s <= steps && s <= 64 && (s == 1 || s * tiles <= 2048); ++s) {
+            const int64_t per = (steps + s - 1) / s, splits = (steps + per - 1) / per;
+            if (splits == before) continue;
+            before = splits;
+            const size_t bytes = (size_t)splits * slice_bytes;
+            if (bytes > budget) break;  // (256 x 256 tiles in one slice always fit)
+            const double t = round_estimate(0.0117 * tile * tile + 2.5 * tile, 490.0, share, tiles * splits, per,
+                                            6400.0 + 500.0 * q * tile * tile / 65536.0) + (double)bytes / 484.0;
+            if (t < least) {
+                least = t;
+                best = pl;
+                best.splits = (int)splits;
+                best.per_split = per * 64;
+                best.part_bytes = bytes;
+            }
+        }
+    }
+    return best;
 }
 
 // Rows of dy that are not 16-byte aligned are copied into padded ones, this many tokens at a time (a multiple of 64): the
@@ -1092,77 +1066,59 @@ static int64_t dalpha_piece(int64_t T, int64_t N) {
     return T < piece ? T : piece;
 }
 
+// Workspace: [partial sums][padded copy of a piece]
 struct DalphaScratch {
-    size_t frag, part, pad;  // bytes: fragments of a piece, partial sums of all pieces, padded copy of a piece
-    int splits;              // token slices of all pieces
+    size_t part, pad;
 };
 static DalphaScratch dalpha_scratch(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
     const int64_t piece = dalpha_piece(T, N), whole = T / piece, rest = T % piece;
-    const DalphaPlan a = dalpha_plan(piece, N, K, g, q);
-    DalphaScratch s = {a.frag_bytes, (size_t)whole * a.part_bytes, 0, (int)whole * a.splits};
-    if (rest) {
-        const DalphaPlan b = dalpha_plan(rest, N, K, g, q);
-        s.part += b.part_bytes;
-        s.splits += b.splits;
-    }
+    const DalphaBudget a = dalpha_budget(piece, N, K, g, q);
+    DalphaScratch s = {a.copy + (size_t)whole * a.part, 0};
+    if (rest) s.part += dalpha_budget(rest, N, K, g, q).part;
     if (N % 8) {
         s.part = (s.part + 15) / 16 * 16;
         s.pad = (size_t)(piece * round_up(N, 8) * 2);
     }
     return s;
 }
+// One piece: any plan within the budget.  Several: 256 x 256 tiles for all, so that one reduction takes their partial sums.
+static DalphaPlan dalpha_piece_plan(int64_t M, int64_t T, int64_t N, int64_t K, int64_t g, int q) {
+    const DalphaBudget b = dalpha_budget(M, N, K, g, q);
+    return M == T ? dalpha_plan(M, N, K, g, q, 128, b.copy + b.part) : dalpha_plan(M, N, K, g, q, 256, b.part);
+}
 
 size_t mfma_bwd_alpha_workspace(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
     const DalphaScratch s = dalpha_scratch(T, N, K, g, q);
-    return s.frag + s.part + s.pad;
+    return s.part + s.pad;
 }
 
-// Partial sums of T tokens into `part`: transposition of one activation, then the product
-static hipError_t launch_dalpha_piece(const uint32_t* packed, const bf16_t* x, const bf16_t* dy, int64_t dcols, int64_t T,
-                                      int64_t N, int64_t K, int q_train, const DalphaPlan& pl, u32x4* frag, float* part,
-                                      hipStream_t st) {
-    const int lds = 3 * DA_STAGE;
-    const bf16_t* gact = pl.xg ? x : dy;
-    const bf16_t* lact = pl.xg ? dy : x;
-    const int64_t gcols = pl.xg ? K : dcols, lcols = pl.xg ? dcols : K;
-    {
-        dim3 grid((unsigned)((gcols + 127) / 128), (unsigned)((pl.T16 * 2 + 15) / 16));
-        BCQ_LAUNCH(transpose_frag_kernel, grid, dim3(256), 0, st, gact, T, gcols, pl.T16, frag);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
+// Partial sums of T tokens into `part`
+template <int TILE>
+static hipError_t launch_dalpha_tile(const uint32_t* packed, const bf16_t* x, const bf16_t* dy, int64_t dcols, int64_t T,
+                                     int64_t N, int64_t K, int q_train, const DalphaPlan& pl, float* part, hipStream_t st) {
     TileMap tmap;
     const unsigned wgs = make_tile_map(pl.tiles_k, pl.tiles_n, pl.splits, 1.0, 1.0, &tmap);
-    dim3 grid(wgs);
-    const int qt = q_train <= 4 ? q_train : 8;
-#define BCQ_DA_LAUNCH(XGV, QTV, FV)                                                                                   \
+    using Cfg = DalphaCfg<TILE>;
+#define BCQ_DA_LAUNCH(QTV, FV)                                                                                        \
     {                                                                                                                 \
         static LdsLimit limit;                                                                                        \
-        hipError_t ea = limit.ensure((const void*)dalpha_kernel<XGV, QTV, FV>, (size_t)lds);                           \
+        hipError_t ea = limit.ensure((const void*)dalpha_kernel<TILE, QTV, FV>, (size_t)Cfg::LDS_B);                   \
         if (ea != hipSuccess) return ea;                                                                              \
-        BCQ_LAUNCH((dalpha_kernel<XGV, QTV, FV>), grid, dim3(256), lds, st, lact, lcols, lcols, frag, pl.T16,  \
-                           packed, part, T, N, K, q_train, tmap, pl.splits, pl.per_split);                            \
+        BCQ_LAUNCH((dalpha_kernel<TILE, QTV, FV>), dim3(wgs), dim3(64 * Cfg::NW), Cfg::LDS_B, st, x, dy, dcols, packed, \
+                   part, T, N, K, q_train, tmap, pl.per_split);                                                       \
     }
-#define BCQ_DA_Q(XGV, FV)                                  \
-    switch (qt) {                                          \
-        case 1: BCQ_DA_LAUNCH(XGV, 1, FV) break;           \
-        case 2: BCQ_DA_LAUNCH(XGV, 2, FV) break;           \
-        case 3: BCQ_DA_LAUNCH(XGV, 3, FV) break;           \
-        case 4: BCQ_DA_LAUNCH(XGV, 4, FV) break;           \
-        default: BCQ_DA_LAUNCH(XGV, 8, FV) break;          \
+#define BCQ_DA_Q(FV)                                \
+    switch (q_train) {                              \
+        case 1: BCQ_DA_LAUNCH(1, FV) break;         \
+        case 2: BCQ_DA_LAUNCH(2, FV) break;         \
+        case 3: BCQ_DA_LAUNCH(3, FV) break;         \
+        case 4: BCQ_DA_LAUNCH(4, FV) break;         \
+        default: BCQ_DA_LAUNCH(8, FV) break;        \
     }
     if (pl.fine) {
-        if (pl.xg) {
-            BCQ_DA_Q(true, true)
-        } else {
-            BCQ_DA_Q(false, true)
-        }
+        BCQ_DA_Q(true)
     } else {
-        if (pl.xg) {
-            BCQ_DA_Q(true, false)
-        } else {
-            BCQ_DA_Q(false, false)
-        }
+        BCQ_DA_Q(false)
     }
 #undef BCQ_DA_Q
 #undef BCQ_DA_LAUNCH
@@ -1175,25 +1131,28 @@ hipError_t launch_bwd_alpha_mfma(const uint32_t* packed, const void* x, const vo
     const DalphaScratch sc = dalpha_scratch(T, N, K, g, q);
     const int64_t piece = dalpha_piece(T, N), dcols = sc.pad ? round_up(N, 8) : N;
     unsigned char* ws = static_cast<unsigned char*>(workspace);
-    u32x4* frag = reinterpret_cast<u32x4*>(ws);
-    float* part = reinterpret_cast<float*>(ws + sc.frag);
+    float* part = reinterpret_cast<float*>(ws);
     float* next = part;
-    DalphaPlan pl;
+    DalphaPlan pl = {};
+    int splits = 0;
     for (int64_t t0 = 0; t0 < T; t0 += piece) {
         const int64_t M = T - t0 < piece ? T - t0 : piece;
-        pl = dalpha_plan(M, N, K, g, q);
+        pl = dalpha_piece_plan(M, T, N, K, g, q);
         const bf16_t* rows = (const bf16_t*)dy + t0 * N;
         if (sc.pad) {
-            u32x4* padded = reinterpret_cast<u32x4*>(ws + sc.frag + sc.part);
+            u32x4* padded = reinterpret_cast<u32x4*>(ws + sc.part);
             BCQ_LAUNCH((pad_act_kernel<1>), dim3((unsigned)((M * (dcols / 8) + 255) / 256)), dim3(256), 0, st, rows, M, N,
                                dcols, padded);
             hipError_t ep = hipGetLastError();
             if (ep != hipSuccess) return ep;
             rows = reinterpret_cast<const bf16_t*>(padded);
         }
-        hipError_t ep = launch_dalpha_piece(packed, (const bf16_t*)x + t0 * K, rows, dcols, M, N, K, q_train, pl, frag, next, st);
+        const bf16_t* xrows = (const bf16_t*)x + t0 * K;
+        hipError_t ep = pl.tile == 256 ? launch_dalpha_tile<256>(packed, xrows, rows, dcols, M, N, K, q_train, pl, next, st)
+                                       : launch_dalpha_tile<128>(packed, xrows, rows, dcols, M, N, K, q_train, pl, next, st);
         if (ep != hipSuccess) return ep;
-        next += (int64_t)pl.splits * pl.tiles_k * q_train * N * (pl.fine ? 8 : 1);
+        next += (int64_t)pl.splits * pl.tiles_k * q_train * N * (pl.fine ? pl.tile / 32 : 1);
+        splits += pl.splits;
     }
     const int64_t rows = (int64_t)q_train * N, G = K / g;
     const dim3 rgrid((unsigned)((rows * G + 63) / 64));
@@ -1201,10 +1160,10 @@ hipError_t launch_bwd_alpha_mfma(const uint32_t* packed, const void* x, const vo
     if (opt) oa = *opt;
     if (pl.fine)
         BCQ_LAUNCH(dalpha_reduce_fine_kernel, rgrid, dim3(256), 0, st, (const float*)part, dalpha, rows, G,
-                           sc.splits, (int64_t)pl.tiles_k * 8, (int)(g / 32), grad_scale, oa);
+                           splits, (int64_t)pl.tiles_k * (pl.tile / 32), (int)(g / 32), grad_scale, oa);
     else
         BCQ_LAUNCH(dalpha_reduce_kernel, rgrid, dim3(256), 0, st, (const float*)part, dalpha, rows, G,
-                           sc.splits, pl.tiles_k, (int)(g == K ? pl.tiles_k : g / DA_TILE), grad_scale, oa);
+                           splits, pl.tiles_k, (int)(g == K ? pl.tiles_k : g / pl.tile), grad_scale, oa);
     return hipGetLastError();
 }
 
