@@ -2,8 +2,8 @@
 // then `iters` rounds of
 //   (1) alpha <- (B^T B)^{-1} B^T w      least-squares refit of the q scales of one vector (Eq. ap4),
 //   (2) every element takes the sign pattern whose level sum_i +-alpha_i is nearest to its weight.
-// One workgroup of one to four waves per vector (a row, or one length-g group of a row), specialised by q.  The vector
-// (fp32) and one byte of sign pattern per element stay in LDS for all rounds, so W is read from HBM once.
+// One workgroup of one or more waves per vector (a row, or one length-g group of a row), specialised by q; W is read from HBM
+// once.
 //
 // Arithmetic: every sum, the solve (L D L^T) and the level comparison are fp64; alpha is rounded to fp32 once at
 // the end.  The loop stops early at a fixed point (round (2) changed nothing) and stops BEFORE a refit whose
@@ -12,14 +12,23 @@
 // larger pattern index (bit i of the pattern = plane i is +1).  Only the ORDER of the fp64 sums over the
 // elements is free.
 //
-// What bounds it: a round is a chain of two barriers, a cross-lane fp64 sum, the solve (q dependent fp64 divisions; with
-// square roots and a division per entry a dozen at q = 3) and 2^q distances per element.  Therefore a round makes ONE
-// pass over the elements (the re-assignment and the next round's sums together), the Gram matrix is counted in integers
-// from the pattern bytes (its entries are n - 2 * disagreements, exact), only wave 0 solves, and the levels are sorted
-// so that a distance costs one subtraction, one strict comparison and its selects.  Four elements per lane, so that
-// vectors of at most 256 elements (groups) take one wave and no cross-wave step.  Measured: 1024 x 1024, q = 3, 15
-// rounds 735 -> 68 us (86 us with the sums through LDS shuffles and a Cholesky solve; before, a kernel for every q
-// reduced 36 fp64 sums per round over four waves and solved in all of them).
+// From five planes on (alternating_kernel) the vector (fp32) and one byte of sign pattern per element stay in LDS.  A round is
+// a chain of two barriers, a cross-lane fp64 sum, the solve (q dependent fp64 divisions) and q steps of bisection per
+// element; it makes ONE pass over the elements (the re-assignment and the next round's sums together), counts the
+// Gram matrix in integers from the pattern bytes (its entries are n - 2 * disagreements, exact) and only wave 0 solves.
+//
+// Up to four planes (alternating_reg_kernel) the elements stay in registers, up to 16 per lane, and a round compares no
+// distances: the weights are fp32, so the place where the nearest level changes is one fp32 number per pair of
+// neighbouring levels, found by the distances themselves at the three floats around their middle.  The levels lie
+// symmetrically about zero, so |w| is compared with the 2^(q-1) - 1 thresholds of the positive half and the sign of w
+// mirrors the pattern.  Where that might not decide as the distances do (equal or nearly equal levels, a tie at a float, elements
+// far smaller or larger than the levels, non-finite ones) the round takes the fp64 distances.  What bounds it: the
+// chain of a round, about 20 vector operations per element, one joint cross-lane sum of all totals, the solve and the sorting,
+// which every wave does for itself, so that a vector of one wave meets no barrier and any other one per round.  Measured:
+// 15 rounds of 1024 x 1024: q = 3 72 -> 27 us, q = 4 119 -> 38 (against four waves, the vector in LDS and 2^q fp64
+// distances per element).
+#include <type_traits>
+
 #include "bcq_internal.h"
 
 namespace bcq {
@@ -55,11 +64,6 @@ __device__ __forceinline__ int nearest_level(const double* level, double x) {
     while (best > 0 && fabs(x - level[best - 1]) <= above) --best;
     return best;
 }
-// 2^q distances per element, or q steps and two distances: at four planes the distances, which need no per-lane addresses,
-// hold (1024 x 1024 115 us); from five on bisection is faster at every size timed (15 rounds, us): 1024 x 1024 q = 5 259 ->
-// 140, q = 8 1898 -> 1242; 8 vectors of 256, q = 8, one wave each 743 -> 519 (565 with four waves and distances).
-constexpr int ALT_BISECT_FROM = 5;
-
 template <int Q>
 __global__ __launch_bounds__(64 * ALT_MAX_WAVES) void alternating_kernel(const float* __restrict__ W, int64_t V, int n,
                                                                          int iters, float* __restrict__ alpha,
@@ -243,29 +247,8 @@ __global__ __launch_bounds__(64 * ALT_MAX_WAVES) void alternating_kernel(const f
             const float4 xf = w4[k];
             const double x[4] = {(double)xf.x, (double)xf.y, (double)xf.z, (double)xf.w};
             int best[4];
-            if constexpr (Q >= ALT_BISECT_FROM) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) best[e] = nearest_level<LEVELS>(sh.level, x[e]);
-            } else {
-                double bd[4];
-                const double l0 = sh.level[0];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    bd[e] = fabs(x[e] - l0);
-                    best[e] = 0;
-                }
-#pragma unroll 8
-                for (int c = 1; c < LEVELS; ++c) {
-                    const double l = sh.level[c];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const double d = fabs(x[e] - l);
-                        const bool nearer = d < bd[e];
-                        bd[e] = nearer ? d : bd[e];
-                        best[e] = nearer ? c : best[e];
-                    }
-                }
-            }
+            for (int e = 0; e < 4; ++e) best[e] = nearest_level<LEVELS>(sh.level, x[e]);
             uint32_t c4 = 0u;
 #pragma unroll
             for (int e = 0; e < 4; ++e) c4 |= (uint32_t)sh.pattern[best[e]] << (8 * e);
@@ -305,6 +288,406 @@ __global__ __launch_bounds__(64 * ALT_MAX_WAVES) void alternating_kernel(const f
     }
 }
 
+// ---- up to four planes -----------------------------------------------------------------------------------------
+
+// Sums over the 64 lanes of NV values (NV a power of two), the same in every lane.  The first log2(NV) exchange steps halve
+// the number of values a lane carries (a lane passes on what its partner keeps), so that the others move one value.
+template <int NV>
+__device__ __forceinline__ void wave_sums(double (&v)[NV]) {
+    static_assert(NV == 1 || NV == 2 || NV == 4 || NV == 8, "a power of two");
+    const int lane = threadIdx.x & 63;
+    auto step = [&](auto COUNT, auto CTRL, bool upper) {  // COUNT values -> COUNT / 2
+        constexpr int half = decltype(COUNT)::value / 2;
+#pragma unroll
+        for (int i = 0; i < half; ++i) {
+            const double keep = upper ? v[i + half] : v[i], pass = upper ? v[i] : v[i + half];
+            v[i] = keep + dpp_move<decltype(CTRL)::value>(pass);
+        }
+    };
+    using std::integral_constant;
+    constexpr int ROR4 = 0x124, ROR8 = 0x128, ROR1 = 0x121, ROR2 = 0x122;  // rotations inside a row of 16 lanes
+    if constexpr (NV == 8) step(integral_constant<int, 8>{}, integral_constant<int, DPP_HALF_MIRROR>{}, (lane & 4) != 0);
+    // (the mirror turns the places of 1 and 2 over as well: the next steps count them from there)
+    if constexpr (NV >= 4) step(integral_constant<int, 4>{}, integral_constant<int, DPP_XOR1>{}, (lane & 1) != 0);
+    if constexpr (NV >= 2) step(integral_constant<int, 2>{}, integral_constant<int, NV == 2 ? DPP_XOR1 : DPP_XOR2>{}, (lane & (NV == 2 ? 1 : 2)) != 0);
+    double r = v[0];
+    r += dpp_move<ROR8>(r);
+    if constexpr (NV <= 4) r += dpp_move<ROR4>(r);
+    if constexpr (NV <= 2) r += dpp_move<ROR2>(r);
+    if constexpr (NV == 1) r += dpp_move<ROR1>(r);
+    auto rows = [&](auto swap) {  // both operands the same value: the sums of pairs of rows
+        const auto lo = swap((uint32_t)__double2loint(r)), hi = swap((uint32_t)__double2hiint(r));
+        r = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    };
+    rows([](uint32_t x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
+    rows([](uint32_t x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {  // the lane that holds value i
+        const int l = NV == 1 ? 0 : NV == 2 ? i : NV == 4 ? (i >> 1) + 2 * (i & 1) : ((i >> 2) << 2) + ((i >> 1) & 1) + 2 * (i & 1);
+        v[i] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(r), l), __builtin_amdgcn_readlane(__double2loint(r), l));
+    }
+}
+
+template <int Q, int MW>
+struct AltRegShared {
+    static constexpr int LEVELS = 1 << Q, PAIRS = Q * (Q - 1) / 2, SUMS = Q + (PAIRS + 2) / 3;
+    double part[2][MW][SUMS];                 // waves' totals of a round, rounds in turn
+    double level[MW][LEVELS], raw[MW][LEVELS];  // every wave sorts for itself
+    uint32_t changed[2][MW];
+    float extreme[MW][2];                     // smallest non-zero and largest |w|
+    uint8_t pattern[MW][LEVELS];
+};
+
+// QL: quads of elements per lane; MW: waves at most.
+template <int Q, int QL, int MW>
+__global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* __restrict__ W, int64_t V, int n, int iters,
+                                                                  float* __restrict__ alpha, uint32_t* __restrict__ packed,
+                                                                  int8_t* __restrict__ planes, int* __restrict__ status_word) {
+    using Shared = AltRegShared<Q, MW>;
+    constexpr int PAIRS = Shared::PAIRS, LEVELS = Shared::LEVELS, HALF = LEVELS / 2, SUMS = Shared::SUMS;
+    constexpr int NV = SUMS <= 1 ? 1 : SUMS <= 2 ? 2 : SUMS <= 4 ? 4 : 8;
+    extern __shared__ __attribute__((aligned(16))) unsigned char alt_smem[];
+    Shared& sh = *reinterpret_cast<Shared*>(alt_smem);
+    uint32_t* code4 = reinterpret_cast<uint32_t*>(alt_smem + (sizeof(Shared) + 15) / 16 * 16);  // [n / 4], for the output
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int waves = MW == 1 ? 1 : blockDim.x >> 6;
+    const int quads = n / 4;
+    const int64_t v = blockIdx.x;
+    const float4* wrow = reinterpret_cast<const float4*>(W + v * (int64_t)n);
+
+    // this lane's elements: quad tid + u * blockDim.x; beyond the vector zeros with all signs equal, which add nothing
+    float x[QL][4];
+    uint32_t code[QL], mask[QL];
+#pragma unroll
+    for (int u = 0; u < QL; ++u) {
+        const int k = tid + u * 64 * waves;
+        const float4 f = k < quads ? wrow[k] : float4{0.f, 0.f, 0.f, 0.f};
+        mask[u] = k < quads ? ~0u : 0u;
+        code[u] = 0u;
+        x[u][0] = f.x + 0.f;  // -0 becomes +0
+        x[u][1] = f.y + 0.f;
+        x[u][2] = f.z + 0.f;
+        x[u][3] = f.w + 0.f;
+    }
+
+    // ---- greedy start: plane i takes the sign of the residual w - sum_{j<i} alpha_j b_j (each element's residual
+    // is rebuilt from its pattern so far, by the same chain of fp64 subtractions), alpha_i = fp32(mean |residual|).
+    double a[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) a[i] = 0.0;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        double s = 0.0;
+#pragma unroll
+        for (int u = 0; u < QL; ++u) {
+            uint32_t c = code[u];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                double r = (double)x[u][e];
+#pragma unroll
+                for (int j = 0; j < i; ++j) r = ((c >> (8 * e + j)) & 1u) ? r - a[j] : r + a[j];
+                s += mask[u] ? fabs(r) : 0.0;
+                c |= (r >= 0.0 ? 1u : 0u) << (8 * e + i);
+            }
+            code[u] = c & mask[u];
+        }
+        s = wave_sum(s);
+        if (MW > 1) {
+            if (lane == 0) sh.part[i & 1][wave][0] = s;
+            __syncthreads();
+            s = 0.0;
+            for (int u = 0; u < waves; ++u) s += sh.part[i & 1][u][0];
+        }
+        if (i == 0 && tid == 0 && status_word && !(fabs(s) <= 1.79769313486231570e308)) atomicAdd(status_word, 1);
+        a[i] = (double)(float)(s / (double)n);
+    }
+    float smallest = 3.402823466e38f, largest = 0.f;
+#pragma unroll
+    for (int u = 0; u < QL; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float m = fabsf(x[u][e]);
+            smallest = m > 0.f ? fminf(smallest, m) : smallest;
+            largest = fmaxf(largest, m);
+        }
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        smallest = fminf(smallest, __shfl_xor(smallest, d));
+        largest = fmaxf(largest, __shfl_xor(largest, d));
+    }
+    if (MW > 1) {
+        if (lane == 0) {
+            sh.extreme[wave][0] = smallest;
+            sh.extreme[wave][1] = largest;
+        }
+        __syncthreads();
+        for (int u = 0; u < waves; ++u) {
+            smallest = fminf(smallest, sh.extreme[u][0]);
+            largest = fmaxf(largest, sh.extreme[u][1]);
+        }
+    }
+
+    // B^T w and, three counts of at most 16384 to a double, the disagreeing signs of pairs of planes
+    double sum[NV];
+    auto form_sums = [&]() {
+        double rhs[Q];
+        uint32_t dis[PAIRS + 1];
+#pragma unroll
+        for (int i = 0; i < Q; ++i) rhs[i] = 0.0;
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p) dis[p] = 0u;
+#pragma unroll
+        for (int u = 0; u < QL; ++u) {
+            const uint32_t c = code[u], inv = ~c;
+            int p = 0;
+#pragma unroll
+            for (int i = 0; i < Q; ++i) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {  // the sign bit flipped where the plane bit is 0
+                    const double xd = (double)x[u][e];
+                    const uint32_t flip = (inv << (31 - 8 * e - i)) & 0x80000000u;
+                    rhs[i] += __hiloint2double(__double2hiint(xd) ^ (int)flip, __double2loint(xd));
+                }
+#pragma unroll
+                for (int j = 0; j < i; ++j) dis[p++] += __popc(((c >> i) ^ (c >> j)) & 0x01010101u);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) sum[i] = 0.0;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) sum[i] = rhs[i];
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p) sum[Q + p / 3] += (double)dis[p] * (double)(1ll << (16 * (p % 3)));
+        wave_sums(sum);
+    };
+    if (iters > 0) form_sums();
+
+    for (int it = 0; it < iters; ++it) {
+        bool changed_elsewhere = false;
+        if (MW > 1) {  // totals over the waves, in wave order; every wave leaves the loop with the others
+            const int turn = it & 1;
+            if (lane == 0) {
+#pragma unroll
+                for (int i = 0; i < SUMS; ++i) sh.part[turn][wave][i] = sum[i];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < SUMS; ++i) sum[i] = 0.0;
+            for (int u = 0; u < waves; ++u) {
+#pragma unroll
+                for (int i = 0; i < SUMS; ++i) sum[i] += sh.part[turn][u][i];
+                if (it > 0) changed_elsewhere = changed_elsewhere || sh.changed[turn ^ 1][u] != 0u;
+            }
+            if (it > 0 && !changed_elsewhere) break;
+        }
+        // ---- (1) Eq. ap4: L D L^T of the Gram matrix B^T B (diagonal = n), all lanes on the same numbers
+        double L[Q][Q], M[Q][Q], inv[Q], z[Q];  // G = L D L^T with unit diagonal in L, M = L D, inv = 1 / D
+        bool singular = false;
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            if (!singular) {
+                double d = (double)n;
+#pragma unroll
+                for (int p = 0; p < j; ++p) d -= M[j][p] * L[j][p];
+                if (!(d > 1e-9 * (double)n)) {
+                    singular = true;
+                } else {
+                    inv[j] = 1.0 / d;
+#pragma unroll
+                    for (int i = j + 1; i < Q; ++i) {
+                        const int pr = i * (i - 1) / 2 + j;
+                        const uint64_t counts = (uint64_t)__double_as_longlong(sum[Q + pr / 3] + 4503599627370496.0);  // 2^52: an integer in the mantissa
+                        double s = (double)(n - 2 * (int)((counts >> (16 * (pr % 3))) & 0xFFFFu));
+#pragma unroll
+                        for (int p = 0; p < j; ++p) s -= M[i][p] * L[j][p];
+                        M[i][j] = s;
+                        L[i][j] = s * inv[j];
+                    }
+                }
+            }
+        }
+        if (singular) break;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            z[i] = sum[i];
+#pragma unroll
+            for (int p = 0; p < i; ++p) z[i] -= L[i][p] * z[p];
+        }
+#pragma unroll
+        for (int i = Q - 1; i >= 0; --i) {
+            double s = z[i] * inv[i];
+#pragma unroll
+            for (int p = i + 1; p < Q; ++p) s -= L[p][i] * a[p];
+            a[i] = s;
+        }
+        // ---- the positive half of the levels: lane c < HALF holds pattern c (last plane +1) or its mirror, whichever is positive
+        double size = 0.0;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) size += fabs(a[i]);
+        double own = 0.0;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) own += (i == Q - 1 || ((lane >> i) & 1)) ? a[i] : -a[i];
+        const uint32_t own_pattern = ((uint32_t)(lane & (HALF - 1)) | (uint32_t)HALF) ^ (own < 0.0 ? (uint32_t)(LEVELS - 1) : 0u);
+        own = fabs(own);
+        int rank = 0;
+        double lv[HALF];
+#pragma unroll
+        for (int c = 0; c < HALF; ++c) {
+            lv[c] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(own), c), __builtin_amdgcn_readlane(__double2loint(own), c));
+            rank += lv[c] > own ? 1 : 0;
+        }
+        // sorted downwards: level k is the one of rank k (all different, or `clear` fails below)
+        double up = 0.0, down = 0.0;  // of lane k: level k and level k + 1, the one below the last being its mirror
+        uint64_t lut = 0u;            // patterns of the positive levels, outermost first
+        float thr[HALF];
+        bool clear = size < 1e30 && size > 1e-25 && (double)largest <= 1048576.0 * size && (double)smallest >= 9.3e-10 * size;
+        uint32_t found = 0u;
+#pragma unroll
+        for (int c = 0; c < HALF; ++c) {
+            const int r = __builtin_amdgcn_readlane(rank, c);
+            const uint32_t pat = (uint32_t)__builtin_amdgcn_readlane((int)own_pattern, c);
+            lut |= (uint64_t)pat << (8 * r);
+            found |= 1u << r;
+            up = lane == r ? lv[c] : up;
+            down = lane + 1 == r ? lv[c] : down;
+        }
+        clear = clear && found == (1u << HALF) - 1u;
+        if (lane == HALF - 1) down = -up;
+        if (lane < HALF) clear = clear && up - down >= 1e-9 * size;
+        float mine = 0.f;
+        if (HALF > 1) {  // lane k < HALF - 1: the first float that is nearer to level k than to level k + 1
+            const double mid = 0.5 * (up + down);
+            const float f = (float)mid;
+            const float t[3] = {__uint_as_float(__float_as_uint(f) - 1u), f, __uint_as_float(__float_as_uint(f) + 1u)};
+            bool outer[3], tie = false;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const double du = fabs((double)t[c] - up), dd = fabs((double)t[c] - down);
+                outer[c] = du < dd;
+                tie = tie || du == dd;  // there the two signs of w part
+            }
+            if (lane + 1 < HALF) clear = clear && mid >= 9.6e-7 * size && !tie && !outer[0] && outer[2];
+            mine = outer[1] ? t[1] : t[2];
+        }
+        // ---- (2) the nearest level for every element
+        uint32_t diff = 0u;
+        if (__all(clear)) {
+#pragma unroll
+            for (int k = 0; k + 1 < HALF; ++k) thr[k] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(mine), k));
+            const uint32_t lo = (uint32_t)lut, hi = (uint32_t)(lut >> 32);
+#pragma unroll
+            for (int u = 0; u < QL; ++u) {
+                uint32_t sel = 0u, neg = 0u;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float m = fabsf(x[u][e]);
+                    uint32_t idx = 0u;  // thresholds above |w|
+                    if constexpr (HALF == 8) {
+                        const bool far = m < thr[3];
+                        const float second = far ? thr[5] : thr[1];
+                        const bool b = m < second;
+                        const float third = far ? (b ? thr[6] : thr[4]) : (b ? thr[2] : thr[0]);
+                        idx = (far ? 4u : 0u) + (b ? 2u : 0u) + (m < third ? 1u : 0u);
+                    } else {
+#pragma unroll
+                        for (int k = 0; k + 1 < HALF; ++k) idx += m < thr[k] ? 1u : 0u;
+                    }
+                    sel |= idx << (8 * e);
+                    neg |= (uint32_t)((int)__float_as_uint(x[u][e]) >> 31) & ((uint32_t)(LEVELS - 1) << (8 * e));
+                }
+                const uint32_t c4 = (__builtin_amdgcn_perm(hi, lo, sel) ^ neg) & mask[u];
+                diff |= c4 ^ code[u];
+                code[u] = c4;
+            }
+        } else {
+            // distances to all levels, sorted by (level, pattern) downwards: the first of the smallest ones is the one the tie
+            // rules ask for.  The slots are filled in pattern order first: with non-finite levels the ranks need not be a
+            // permutation.  (One wave's LDS instructions execute in order.)
+            double* level = sh.level[wave];
+            double* raw = sh.raw[wave];
+            uint8_t* pattern = sh.pattern[wave];
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            if (lane < LEVELS) {
+                double s = 0.0;
+#pragma unroll
+                for (int i = 0; i < Q; ++i) s += ((lane >> i) & 1) ? a[i] : -a[i];
+                raw[lane] = s;
+                level[LEVELS - 1 - lane] = s;
+                pattern[LEVELS - 1 - lane] = (uint8_t)lane;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            if (lane < LEVELS) {
+                const double mine_l = raw[lane];
+                int place = 0;
+                for (int o = 0; o < LEVELS; ++o) {
+                    const double l = raw[o];
+                    place += (l > mine_l || (!(l < mine_l) && o > lane)) ? 1 : 0;
+                }
+                level[place] = mine_l;
+                pattern[place] = (uint8_t)lane;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+#pragma unroll
+            for (int u = 0; u < QL; ++u) {
+                double bd[4];
+                int best[4];
+                const double l0 = level[0];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    bd[e] = fabs((double)x[u][e] - l0);
+                    best[e] = 0;
+                }
+#pragma unroll 1
+                for (int c = 1; c < LEVELS; ++c) {
+                    const double l = level[c];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const double d = fabs((double)x[u][e] - l);
+                        const bool nearer = d < bd[e];
+                        bd[e] = nearer ? d : bd[e];
+                        best[e] = nearer ? c : best[e];
+                    }
+                }
+                uint32_t c4 = 0u;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) c4 |= (uint32_t)pattern[best[e]] << (8 * e);
+                c4 &= mask[u];
+                diff |= c4 ^ code[u];
+                code[u] = c4;
+            }
+        }
+        const bool changed = __any(diff != 0u);
+        if (MW == 1 && !changed) break;
+        if (MW > 1 && lane == 0) sh.changed[it & 1][wave] = changed ? 1u : 0u;
+        form_sums();
+    }
+#pragma unroll
+    for (int u = 0; u < QL; ++u)
+        if (mask[u]) code4[tid + u * 64 * waves] = code[u];
+    __syncthreads();
+
+    // ---- outputs: alpha[i][v], packed[i][v][n / 32], planes[i][v][n]
+    const int nw = n / 32;
+    if (tid == 0) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) alpha[(int64_t)i * V + v] = (float)a[i];
+    }
+    for (int idx = tid; idx < Q * nw; idx += 64 * waves) {
+        const int i = idx / nw, wq = idx % nw;
+        uint32_t word = 0u;
+#pragma unroll
+        for (int b = 0; b < 8; ++b)  // bits 0, 8, 16, 24 of a pattern quad -> a nibble
+            word |= (((((code4[8 * wq + b] >> i) & 0x01010101u) * 0x01020408u) >> 24) & 0xFu) << (4 * b);
+        packed[((int64_t)i * V + v) * nw + wq] = word;
+    }
+    if (planes) {
+        uint32_t* out = reinterpret_cast<uint32_t*>(planes);
+        for (int i = 0; i < Q; ++i)
+            for (int k = tid; k < quads; k += 64 * waves)  // a byte per element: 1 -> 0x01, 0 -> 0xFF
+                out[((int64_t)i * V + v) * quads + k] = ~(((code4[k] >> i) & 0x01010101u) * 0xFEu);
+    }
+}
+
 __global__ void alt_zero_word_kernel(int* p) { *p = 0; }
 
 template <int Q>
@@ -314,13 +697,37 @@ static hipError_t launch_q(const float* W, int64_t V, int n, int iters, float* a
     static LdsLimit limit;
     hipError_t e = limit.ensure((const void*)alternating_kernel<Q>, lds);
     if (e != hipSuccess) return e;
-    // Four elements per lane and pass.  One / two / four waves, 15 rounds, q = 3, us: 8 vectors of 128 31 / 35 / 42, 8192 of
-    // them 99 / 141 / 259; 4096 of 256 65 / 100 / 170; 8 and 256 of 512 41 / 38 / 46; 256 of 1024 60 / 48 / 47, 1024 of them
-    // 63 / 62 / 70; 1024 of 2560 117 / 106 / 109.
+    // four elements per lane and pass (8 vectors of 256, q = 8, 15 rounds: one wave 519 us, four 565)
     const int waves = n <= 256 ? 1 : n <= 512 ? 2 : ALT_MAX_WAVES;
     BCQ_LAUNCH((alternating_kernel<Q>), dim3((unsigned)V), dim3(64 * waves), lds, st, W, V, n, iters, alpha, packed,
                        planes, status_word);
     return hipGetLastError();
+}
+
+template <int Q, int QL, int MW>
+static hipError_t launch_reg(const float* W, int64_t V, int n, int iters, float* alpha, uint32_t* packed, int8_t* planes,
+                             int* status_word, hipStream_t st) {
+    const size_t lds = (sizeof(AltRegShared<Q, MW>) + 15) / 16 * 16 + (size_t)n;
+    static LdsLimit limit;
+    hipError_t e = limit.ensure((const void*)alternating_reg_kernel<Q, QL, MW>, lds);
+    if (e != hipSuccess) return e;
+    const int waves = (n / 4 + 64 * QL - 1) / (64 * QL);
+    BCQ_LAUNCH((alternating_reg_kernel<Q, QL, MW>), dim3((unsigned)V), dim3(64 * waves), lds, st, W, V, n, iters, alpha, packed,
+                       planes, status_word);
+    return hipGetLastError();
+}
+
+// As many elements per lane as one wave's registers hold, then more waves.  q = 3, 15 rounds, us, one wave against one to four
+// with 4 / 8 / 16 elements per lane: 1024 vectors of 1024 27 against 52 / 38 / 31, 256 of them 26 against 27 / 28 / 30, 1024 of
+// 512 22 against 33 / 26 / 31, 4096 of 256 41 (with 8 and 16: 51, 73); 1024 of 2560 73 with 16 (112 through LDS).
+template <int Q>
+static hipError_t launch_reg_q(const float* W, int64_t V, int n, int iters, float* alpha, uint32_t* packed, int8_t* planes,
+                               int* status_word, hipStream_t st) {
+    if (n <= 256) return launch_reg<Q, 1, 1>(W, V, n, iters, alpha, packed, planes, status_word, st);
+    if (n <= 512) return launch_reg<Q, 2, 1>(W, V, n, iters, alpha, packed, planes, status_word, st);
+    if (n <= 1024) return launch_reg<Q, 4, 1>(W, V, n, iters, alpha, packed, planes, status_word, st);
+    if (n <= 4096) return launch_reg<Q, 4, 4>(W, V, n, iters, alpha, packed, planes, status_word, st);
+    return launch_reg<Q, 4, 16>(W, V, n, iters, alpha, packed, planes, status_word, st);
 }
 
 hipError_t launch_quantize_alternating(const float* W, int64_t V, int64_t n, int q, int iters, float* alpha,
@@ -331,10 +738,10 @@ hipError_t launch_quantize_alternating(const float* W, int64_t V, int64_t n, int
         if (e != hipSuccess) return e;
     }
     switch (q) {
-        case 1: return launch_q<1>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
-        case 2: return launch_q<2>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
-        case 3: return launch_q<3>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
-        case 4: return launch_q<4>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
+        case 1: return launch_reg_q<1>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
+        case 2: return launch_reg_q<2>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
+        case 3: return launch_reg_q<3>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
+        case 4: return launch_reg_q<4>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
         case 5: return launch_q<5>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
         case 6: return launch_q<6>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);
         case 7: return launch_q<7>(W, V, (int)n, iters, alpha, packed, planes, status_word, st);

@@ -108,3 +108,30 @@ def test_alternating_bisection(bcq, oracle, q, N, K, g):
     W = synth.weights(1, "out", N, K, extra=q)
     W[0], W[1] = 0.0, 0.25
     _check(bcq, oracle, W, q, g=g)
+
+
+@pytest.mark.parametrize("kind", ["normal", "small", "large"])
+@pytest.mark.parametrize("N,K", [(40, 32), (12, 256), (12, 288), (8, 512), (8, 544), (6, 1024), (6, 1056), (3, 4096), (2, 4128)])
+def test_registers_and_thresholds(bcq, oracle, N, K, kind):
+    """One to sixteen waves with 4, 8 or 16 elements per lane, at and behind each limit.  Scaling by a power of two changes no
+    decision; above 1e30 every round compares distances (all levels) instead of thresholds.  (Elements far above or below
+    the levels get there too, but are no input for this check: from 2^-30 of sum |alpha| down, an element's two nearest
+    levels +l and -l differ in distance by less than the 1e-9 of it that make a vector robust.)"""
+    for q in (1, 2, 3, 4):
+        W = synth.weights(1, "out", N, K, extra=11 * K + q)
+        W *= np.float32({"normal": 1.0, "small": 2.0 ** -60, "large": 2.0 ** 106}[kind])
+        _check(bcq, oracle, W, q, iters=6)
+
+
+def test_ties_at_floats(bcq, oracle):
+    """Weights on a coarse grid put levels' middles on floats; the distances decide there, so that the error is no worse."""
+    rng = np.random.default_rng(5)
+    W = (rng.integers(-6, 7, size=(64, 256)) / 64.0).astype(np.float32)
+    for q in (2, 3, 4):
+        alpha, packed, _ = bcq.bcq_quantize_alternating(to_dev(W), q, iters=15)
+        a = alpha.cpu().numpy().reshape(q, 64, 1).astype(np.float64)
+        b = oracle.unpack(packed_to_host(packed), 256).reshape(q, 64, 256)
+        a_ref, b_ref = oracle.quantize_alternating(W, q, iters=15)[:2]
+        e_gpu = ((W - (a * b).sum(0)) ** 2).sum()
+        e_ref = ((W - (a_ref.reshape(q, 64, 1).astype(np.float64) * b_ref.reshape(q, 64, 256)).sum(0)) ** 2).sum()
+        assert e_gpu <= 1.02 * e_ref + 1e-12
