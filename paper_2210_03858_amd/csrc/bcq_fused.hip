@@ -5,12 +5,7 @@
 // the registers of v_mfma_f32_32x32x16_bf16 and multiplies them with all the tokens of its tile.  At these token counts
 // the two-kernel path is bound by writing and re-reading 16 bits per weight, here a weight costs q bits.
 //
-// Expansion by table: within a scale group a row has only 2^q different weights, in pairs of opposite sign, so the
-// 2^(q - 1) <= 8 positive-last-plane values fit the eight bytes that v_perm_b32 selects from (low bytes and high bytes
-// apart).  Selectors for four columns at a time are bits s, s + 8, s + 16, s + 24 of the planes, XNORed with the last plane, whose
-// complement is the sign.  2.6 (q = 3) to 3.2 (q = 4) vector operations per weight instead of about 3 q + 0.5 for signed sums,
-// so that from 64 tokens on the matrix instructions take longer than the expansion.  The table is the same chain of
-// fp32 sums and one rounding as the other paths use, negation commutes with both: the same weights bit for bit.
+// Expansion by table (bcq_expand.h): from 64 tokens on the matrix instructions take longer than it.
 //
 // Split: a workgroup owns 32 rows x 32 TT tokens; its W waves take runs of 128 columns in turn and add their tiles
 // through LDS in wave order (deterministic).  Up to 32 tokens are read from their rows; more are first rewritten in
@@ -18,94 +13,25 @@
 // 10240 x 2560: 80 us from the rows, 41 us in order).  What bounds it: up to 32 tokens the planes' scattered rows and launch
 // latency (6144 x 2048, groups of 128, 4 tokens: 26 -> 9 us against two kernels), above that the activation fragments,
 // which every 32 rows read again from L2 through the vector memory path.
-#include "bcq_internal.h"
+#include "bcq_expand.h"
 
 namespace bcq {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 fu_bf16x8;
 typedef __attribute__((ext_vector_type(16))) float fu_f32x16;
-typedef __attribute__((ext_vector_type(4))) uint32_t fu_u32x4;
-typedef __attribute__((ext_vector_type(4))) float fu_f32x4;
-typedef __attribute__((ext_vector_type(2))) __bf16 fu_bf16x2;
-typedef __attribute__((ext_vector_type(2))) float fu_f32x2;
-
-__device__ __forceinline__ uint32_t fu_pack(float lo, float hi) {
-    const fu_f32x2 v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, fu_bf16x2));
-}
-
-// The positive-last-plane weights of one row and scale group: bit i of the index = plane i is +1, i < Q - 1.
-template <int Q>
-struct LevelTable {
-    uint32_t lo[2], hi[2];  // low and high bytes of the bf16 values, four to a word
-    __device__ __forceinline__ void build(const float (&a)[Q]) {
-        constexpr int E = 1 << (Q - 1);
-        float v[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int cc = c < E ? c : 0;
-            float s = 0.f;
-#pragma unroll
-            for (int i = 0; i < Q; ++i) s += (i == Q - 1 || ((cc >> i) & 1)) ? a[i] : -a[i];
-            v[c] = s;
-        }
-        uint32_t p[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) p[c] = fu_pack(v[2 * c], v[2 * c + 1]);
-#pragma unroll
-        for (int w = 0; w < 2; ++w) {
-            lo[w] = __builtin_amdgcn_perm(p[2 * w + 1], p[2 * w], 0x06040200u);
-            hi[w] = __builtin_amdgcn_perm(p[2 * w + 1], p[2 * w], 0x07050301u);
-        }
-    }
-};
-
-// 32 signs of each plane -> 32 bf16 weights: frag[2 j + sub] = columns 16 j + 8 sub .. + 7 of the 32
-template <int Q>
-__device__ __forceinline__ void expand32(const uint32_t (&w)[Q], const LevelTable<Q>& t, fu_u32x4 (&frag)[4]) {
-    const uint32_t neg = ~w[Q - 1];
-    uint32_t c[Q > 1 ? Q - 1 : 1];
-#pragma unroll
-    for (int i = 0; i + 1 < Q; ++i) c[i] = w[i] ^ neg;
-    uint32_t even = 0u, odd = 0u;  // two-bit codes of the even and the odd columns
-    if constexpr (Q >= 3) {
-        even = (c[0] & 0x55555555u) | ((c[1] & 0x55555555u) << 1);
-        odd = ((c[0] >> 1) & 0x55555555u) | (c[1] & 0xAAAAAAAAu);
-    }
-    uint32_t ab[8], cd[8];  // columns (s, s + 8) and (s + 16, s + 24)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        uint32_t sel = 0u;
-        if constexpr (Q == 2) sel = (c[0] >> s) & 0x01010101u;
-        if constexpr (Q >= 3) sel = (((s & 1) ? odd : even) >> (s & 6)) & 0x03030303u;
-        if constexpr (Q == 4) sel |= (s >= 2 ? c[2] >> (s - 2) : c[2] << (2 - s)) & 0x04040404u;
-        const uint32_t l = __builtin_amdgcn_perm(t.lo[1], t.lo[0], sel);
-        const uint32_t h = __builtin_amdgcn_perm(t.hi[1], t.hi[0], sel) ^ ((neg << (7 - s)) & 0x80808080u);
-        ab[s] = __builtin_amdgcn_perm(h, l, 0x05010400u);
-        cd[s] = __builtin_amdgcn_perm(h, l, 0x07030602u);
-    }
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        frag[0][p] = __builtin_amdgcn_perm(ab[2 * p + 1], ab[2 * p], 0x05040100u);
-        frag[1][p] = __builtin_amdgcn_perm(ab[2 * p + 1], ab[2 * p], 0x07060302u);
-        frag[2][p] = __builtin_amdgcn_perm(cd[2 * p + 1], cd[2 * p], 0x05040100u);
-        frag[3][p] = __builtin_amdgcn_perm(cd[2 * p + 1], cd[2 * p], 0x07060302u);
-    }
-}
 
 // Activations -> the order the matrix instruction reads them in: for every 32-token tile, 32-column word and half slice
 // one contiguous KiB, lane (t, h) holding columns 16 h + 8 sub .. + 7 of the word.  Tokens beyond T become zeros.
 // A wave takes 8 tokens x 128 bytes: whole lines in, 128-byte runs out.
 __global__ __launch_bounds__(256) void order_act_kernel(const bf16_t* __restrict__ x, int64_t T, int64_t K,
-                                                        fu_u32x4* __restrict__ xfrag) {
+                                                        u32x4* __restrict__ xfrag) {
     const int lane = threadIdx.x & 63;
     const int64_t Kw = K / 32, pairs = (Kw + 1) / 2;
     const int64_t job = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // (eight tokens, two words)
     const int64_t t = (job / pairs) * 8 + (lane & 7), w = (job % pairs) * 2 + (lane >> 5);
     const int chunk = (lane >> 3) & 3;
     if (w >= Kw || t >= (T + 31) / 32 * 32) return;
-    fu_u32x4 v = {0u, 0u, 0u, 0u};
-    if (t < T) v = *reinterpret_cast<const fu_u32x4*>(x + t * K + 32 * w + 8 * chunk);
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (t < T) v = *reinterpret_cast<const u32x4*>(x + t * K + 32 * w + 8 * chunk);
     xfrag[(((t / 32) * Kw + w) * 2 + (chunk & 1)) * 64 + (t % 32) + 32 * (chunk >> 1)] = v;
 }
 
@@ -116,7 +42,7 @@ __global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __res
                                                            const float* __restrict__ alpha, const bf16_t* __restrict__ x,
                                                            bf16_t* __restrict__ y, int64_t T, int64_t N, int64_t K,
                                                            int64_t g, int per, float* __restrict__ sums) {
-    __shared__ fu_f32x4 part[2][W][4][64];
+    __shared__ f32x4 part[2][W][4][64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 31, h = lane >> 5;
@@ -180,14 +106,14 @@ __global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __res
             load_alpha(4 * u + 2, a[buf][1]);
         }
     };
-    fu_u32x4 xf[XW][2][TT];  // [word][slice][token tile]
-    const fu_u32x4 zero = {0u, 0u, 0u, 0u};
+    u32x4 xf[XW][2][TT];  // [word][slice][token tile]
+    const u32x4 zero = {0u, 0u, 0u, 0u};
     auto load_x = [&](int w, int slot) {  // words beyond K contribute nothing
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt)
-                xf[slot][sub][tt] = w < Kw ? *reinterpret_cast<const fu_u32x4*>(
+                xf[slot][sub][tt] = w < Kw ? *reinterpret_cast<const u32x4*>(
                                                  xrow[tt] + (ORDERED ? (2 * w + sub) * 512 : 32 * w + 8 * sub)) : zero;
     };
     LevelTable<Q> table;
@@ -217,10 +143,10 @@ __global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __res
 #pragma unroll
         for (int pr = 0; pr < 2; ++pr) {
             if (4 * u + 2 * pr < Kw) {
-                fu_u32x4 frag[4];
+                u32x4 frag[4];
                 expand32<Q>(own[pr], GROUPED ? tables[pr] : table, frag);
                 if (split) {
-                    fu_u32x4 second[4];
+                    u32x4 second[4];
                     float as[Q];
                     load_alpha(4 * u + 2 * pr + 1, as);
                     if (4 * u + 2 * pr + 1 >= Kw) {  // no such columns: zero weights, as Inf times a zero activation is NaN
@@ -245,8 +171,8 @@ __global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __res
 #pragma unroll
                         for (int tt = 0; tt < TT; ++tt)
                             acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                __builtin_bit_cast(fu_bf16x8, frag[2 * j + sub]),
-                                __builtin_bit_cast(fu_bf16x8, xf[slot][sub][tt]), acc[tt], 0, 0, 0);
+                                __builtin_bit_cast(bf16x8, frag[2 * j + sub]),
+                                __builtin_bit_cast(bf16x8, xf[slot][sub][tt]), acc[tt], 0, 0, 0);
                     if (XW == 2 && pr == 0)
                         load_x(4 * u + 2 + j, slot);
                     else
@@ -265,21 +191,21 @@ __global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __res
     for (int tt = 0; tt < TT; ++tt) {
 #pragma unroll
         for (int gg = 0; gg < 4; ++gg)
-            part[tt & 1][wave][gg][lane] = fu_f32x4{acc[tt][4 * gg], acc[tt][4 * gg + 1], acc[tt][4 * gg + 2], acc[tt][4 * gg + 3]};
+            part[tt & 1][wave][gg][lane] = f32x4{acc[tt][4 * gg], acc[tt][4 * gg + 1], acc[tt][4 * gg + 2], acc[tt][4 * gg + 3]};
         __syncthreads();  // two buffers: the sums of tile tt are read while tile tt + 1 is written
         if (threadIdx.x < 256) {
             const int gg = threadIdx.x >> 6;
-            fu_f32x4 s = part[tt & 1][0][gg][lane];
+            f32x4 s = part[tt & 1][0][gg][lane];
 #pragma unroll
             for (int w = 1; w < W; ++w) s += part[tt & 1][w][gg][lane];
             const int64_t t = t0 + tt * 32 + col, nn = n0 + 8 * gg + 4 * h;
             if (sums) {  // split contraction: sum_parts_kernel adds the parts
                 if (t < T && nn < N)
-                    *reinterpret_cast<fu_f32x4*>(sums + ((int64_t)blockIdx.z * T + t) * ((N + 3) / 4 * 4) + nn) = s;
+                    *reinterpret_cast<f32x4*>(sums + ((int64_t)blockIdx.z * T + t) * ((N + 3) / 4 * 4) + nn) = s;
             } else if (t < T) {
                 bf16_t* dst = y + t * N + nn;
                 if (nn + 3 < N && (N & 3) == 0) {
-                    *reinterpret_cast<uint2*>(dst) = make_uint2(fu_pack(s[0], s[1]), fu_pack(s[2], s[3]));
+                    *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3]));
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
@@ -295,13 +221,13 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(const float* __restrict_
                                                         bf16_t* __restrict__ y) {
     const int64_t quads = (N + 3) / 4, idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= T * quads) return;
-    const fu_f32x4* p = reinterpret_cast<const fu_f32x4*>(sums) + idx;
-    fu_f32x4 s = p[0];
+    const f32x4* p = reinterpret_cast<const f32x4*>(sums) + idx;
+    f32x4 s = p[0];
     for (int i = 1; i < parts; ++i) s += p[i * T * quads];
     const int64_t t = idx / quads, n = idx % quads * 4;
     bf16_t* dst = y + t * N + n;
     if ((N & 3) == 0) {
-        *reinterpret_cast<uint2*>(dst) = make_uint2(fu_pack(s[0], s[1]), fu_pack(s[2], s[3]));
+        *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3]));
     } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -320,7 +246,7 @@ static hipError_t launch_q(const uint32_t* packed, const float* alpha, const bf1
     const bf16_t* xo = x;
     if (T > 32) {
         const int64_t jobs = (T + 31) / 32 * 4 * ((K / 32 + 1) / 2);
-        BCQ_LAUNCH(order_act_kernel, dim3((unsigned)((jobs + 3) / 4)), dim3(256), 0, st, x, T, K, (fu_u32x4*)workspace);
+        BCQ_LAUNCH(order_act_kernel, dim3((unsigned)((jobs + 3) / 4)), dim3(256), 0, st, x, T, K, (u32x4*)workspace);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         xo = (const bf16_t*)workspace;

@@ -13,26 +13,13 @@
 //   2. gemm_kernel: 64 x 64 to 256 x 256 output tile per workgroup, 4 or 8 waves, v_mfma_f32_16x16x32_bf16.  Both operand
 //      tiles go global -> LDS directly (buffer_load ... lds), several K-steps in flight; the activations' 16-byte chunks are
 //      XOR-swizzled by row so that the fragment reads are bank-conflict free, the weights lie in LDS as in the workspace.
-#include "bcq_internal.h"
 #include <math.h>
 
 #include <type_traits>
 
+#include "bcq_expand.h"
+
 namespace bcq {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-
-// two fp32 -> two bf16 (round to nearest even) in one v_cvt_pk_bf16_f32; `lo` lands in the low half
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-    f32x2 v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-__device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
 // ---------------------------------------------------------------------------------------------------------
 // Workgroup -> tile mapping.  Consecutive workgroup ids go round-robin over the 8 XCDs, each with its own L2.  The tiles
@@ -91,46 +78,109 @@ __device__ __forceinline__ void store_word_frags(const float (&s)[32], u32x4* __
 }
 
 // expand for the forward: columns of the GEMM = rows n of W, contraction = k.
-// thread = (c = n % 32, one packed word = 32 columns k) -> four 16-byte fragment slots.
+// thread = (one row n, one packed word = 32 columns k) -> four 16-byte fragment slots; block = 8 rows x 32 words, so that it
+// reads whole 128-byte lines and stores whole 128-byte pieces (32 rows x 8 words, the lines shared by four blocks: 13.4 us
+// instead of 12.1).  Q planes by table up to four, else (Q = 0) q of them as signed sums.  What bounds it is the 16 bits per
+// weight that it writes (5.4 TB/s with its reads); by signed sums four planes were bound by vector operations.  Measured:
+// 10240 x 2560, q = 4 17.7 -> 12.5 us, 2560 x 10240 17.5 -> 11.8, 8192 x 2048, q = 3 10.8 -> 8.4, 4096 x 1024 5.6 -> 5.2.
+template <int Q>
 __global__ __launch_bounds__(256) void expand_fwd_kernel(const uint32_t* __restrict__ packed,
                                                          const float* __restrict__ alpha, int64_t N, int64_t K,
                                                          int64_t g, int q, int64_t R16 /* padded K / 16 */,
                                                          u32x4* __restrict__ frag) {
-    const int c = threadIdx.x & 31;
-    const int64_t ct = blockIdx.x;
+    const int c = (threadIdx.x & 7) + 8 * (blockIdx.x & 3);
+    const int64_t ct = blockIdx.x >> 2;
     const int64_t n = ct * 32 + c;
     const int64_t Kw = K / 32;
-    const int64_t w = (int64_t)blockIdx.y * 8 + (threadIdx.x >> 5);
+    const int64_t w = (int64_t)blockIdx.y * 32 + (threadIdx.x >> 3);
     if (w * 2 >= R16) return;
     const bool live = (n < N) && (w < Kw);
     const int64_t G = K / g, grp = live ? (w * 32) / g : 0;  // a packed word lies in one scale group (g % 32 == 0)
-    float s[32];
-#pragma unroll
-    for (int e = 0; e < 32; ++e) s[e] = 0.f;
     // every plane's word and scale is requested before the first is used: one memory latency instead of one per plane
-    float a[8];
-    uint32_t bits[8];
+    constexpr int P = Q ? Q : 8;
+    float a[P];
+    uint32_t bits[P];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        if (i < q) {
+    for (int i = 0; i < P; ++i) {
+        if (Q || i < q) {
             a[i] = live ? alpha[((int64_t)i * N + n) * G + grp] : 0.f;
             bits[i] = live ? packed[((int64_t)i * N + n) * Kw + w] : 0u;
         }
     }
+    if constexpr (Q > 0) {
+        LevelTable<Q> table;
+        table.build(a);
+        u32x4 out[4];
+        expand32<Q>(bits, table, out);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        if (i < q) {
+        for (int gg = 0; gg < 4; ++gg) frag[(ct * R16 + 2 * w + (gg >> 1)) * 64 + c + 32 * (gg & 1)] = out[gg];
+    } else {
+        float s[32];
 #pragma unroll
-            for (int e = 0; e < 32; ++e) s[e] += ((bits[i] >> e) & 1u) ? a[i] : -a[i];
+        for (int e = 0; e < 32; ++e) s[e] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (i < q) {
+#pragma unroll
+                for (int e = 0; e < 32; ++e) s[e] += ((bits[i] >> e) & 1u) ? a[i] : -a[i];
+            }
         }
+        store_word_frags(s, frag, ct * R16 + 2 * w, c);
     }
-    store_word_frags(s, frag, ct * R16 + 2 * w, c);
 }
 
-// expand for the input gradient: columns of the GEMM = columns k of W, contraction = n.  Reads the transposed
-// twin when the caller has one (one word = 32 consecutive n of this thread's column), else the canonical words
-// (the 32 lanes of a column tile share a word and each takes its own bit).  The scales of the block's 256 rows
-// pass through LDS.
+// The same for the input gradient (columns of the GEMM = columns k, contraction = n), up to four planes: a thread expands 32
+// columns of one row n with that row's table, the tile of 32 rows x 256 columns goes through LDS, and ds_read_b64_tr_b16
+// returns it with the rows innermost.  (With the bits running along n, as in the twin, every weight of a word has scales of
+// its own: signed sums, 12.5 operations per weight.  10240 x 2560, q = 4: 18.1 -> 11.8 us, 8192 x 2048, q = 3 11.2 -> 8.0,
+// 4096 x 1024 6.8 -> 6.4.)
+template <int Q>
+__global__ __launch_bounds__(256) void expand_bwd_rows_kernel(const uint32_t* __restrict__ packed,
+                                                              const float* __restrict__ alpha, int64_t N, int64_t K,
+                                                              int64_t g, int64_t R16 /* padded N / 16 */,
+                                                              u32x4* __restrict__ frag) {
+    __shared__ __attribute__((aligned(16))) unsigned char tile[32 * 512];  // rows of 256 columns, in 32-byte pieces c ^ swz(row)
+    const int r = threadIdx.x >> 3, wl = threadIdx.x & 7;
+    const int64_t Kw = K / 32, G = K / g;
+    const uint32_t row_tiles = (uint32_t)(R16 / 2);
+    const int64_t rt = blockIdx.x % row_tiles, wg = blockIdx.x / row_tiles;  // one grid dimension: neither N nor K is limited by it
+    const int64_t n = rt * 32 + r, w = wg * 8 + wl;
+    const bool live = n < N && w < Kw;
+    float a[Q];
+    uint32_t bits[Q];
+    const int64_t grp = live ? (w * 32) / g : 0;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        a[i] = live ? alpha[((int64_t)i * N + n) * G + grp] : 0.f;  // rows beyond N expand to zero
+        bits[i] = live ? packed[((int64_t)i * N + n) * Kw + w] : 0u;
+    }
+    LevelTable<Q> table;
+    table.build(a);
+    u32x4 out[4];
+    expand32<Q>(bits, table, out);
+    auto swz = [](int row) { return (row & 3) | (((row >> 3) & 1) << 2); };
+#pragma unroll
+    for (int f = 0; f < 4; ++f)
+        *reinterpret_cast<u32x4*>(tile + r * 512 + (((2 * wl + (f >> 1)) ^ swz(r)) * 32) + (f & 1) * 16) = out[f];
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int piece = (lane >> 4) & 1, grow = 8 * (lane >> 5) + ((lane >> 2) & 3);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {  // column tile 2 wave + (j >> 1) of 32, slice j & 1 of 16 rows
+        const int ctl = 2 * wave + (j >> 1), row = 16 * (j & 1) + grow;
+        const uint32_t addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)tile +
+                              (uint32_t)(row * 512 + (((2 * ctl + piece) ^ swz(row)) * 32) + (lane & 3) * 8);
+        u32x2 lo, hi;
+        asm volatile("ds_read_b64_tr_b16 %0, %2\n\tds_read_b64_tr_b16 %1, %2 offset:2048\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(lo), "=&v"(hi) : "v"(addr) : "memory");
+        const int64_t ct = wg * 8 + ctl, ks = rt * 2 + (j & 1);
+        if (ct < Kw && ks < R16) frag[(ct * R16 + ks) * 64 + lane] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+    }
+}
+
+// expand for the input gradient by signed sums, from five planes on and for three terms.  Reads the transposed twin when the
+// caller has one (one word = 32 consecutive n of this thread's column), else the canonical words (the 32 lanes of a column
+// tile share a word and each takes its own bit).  The scales of the block's 256 rows pass through LDS.
 // SPLIT (never with a twin): What is written as three bf16 terms hi + mid + lo (24 significant bits, all of the fp32 sum), one after the
 // other along the contraction, smallest first; an Inf or NaN is its first term alone.
 template <bool TWIN, bool SPLIT>
@@ -624,8 +674,16 @@ hipError_t launch_fwd_mfma(const uint32_t* packed, const float* alpha, const voi
                            int64_t K, int64_t g, int q, void* y, void* workspace, hipStream_t st) {
     const int64_t R16 = round_up(K, RPAD) / 16;
     const int64_t ct = (N + 31) / 32;
-    dim3 grid((unsigned)ct, (unsigned)((R16 / 2 + 7) / 8));
-    BCQ_LAUNCH(expand_fwd_kernel, grid, dim3(256), 0, st, packed, alpha, N, K, g, q, R16, (u32x4*)workspace);
+    dim3 grid((unsigned)(4 * ct), (unsigned)((R16 / 2 + 31) / 32));
+#define BCQ_EXPAND(Q) BCQ_LAUNCH(expand_fwd_kernel<Q>, grid, dim3(256), 0, st, packed, alpha, N, K, g, q, R16, (u32x4*)workspace)
+    switch (q) {
+        case 1: BCQ_EXPAND(1); break;
+        case 2: BCQ_EXPAND(2); break;
+        case 3: BCQ_EXPAND(3); break;
+        case 4: BCQ_EXPAND(4); break;
+        default: BCQ_EXPAND(0); break;
+    }
+#undef BCQ_EXPAND
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_gemm((const bf16_t*)x, K, (const u32x4*)workspace, (bf16_t*)y, N, T, N, K, R16, st);
@@ -638,12 +696,22 @@ hipError_t launch_bwd_input_mfma(const uint32_t* packed, const uint32_t* packed_
                                  hipStream_t st) {
     const int64_t R16 = round_up(N, RPAD) / 16;
     u32x4* frag = (u32x4*)workspace;
-    if (packed_t && N % 32 == 0)
-        BCQ_LAUNCH((expand_bwd_kernel<true, false>), expand_bwd_grid(K, R16), dim3(256), 0, st, packed_t, alpha, N, K, g, q,
+    const dim3 rows_grid((unsigned)(R16 / 2 * ((K / 32 + 7) / 8)));
+#define BCQ_EXPAND(Q) BCQ_LAUNCH(expand_bwd_rows_kernel<Q>, rows_grid, dim3(256), 0, st, packed, alpha, N, K, g, R16, frag)
+    switch (q) {
+        case 1: BCQ_EXPAND(1); break;
+        case 2: BCQ_EXPAND(2); break;
+        case 3: BCQ_EXPAND(3); break;
+        case 4: BCQ_EXPAND(4); break;
+        default:
+            if (packed_t && N % 32 == 0)
+                BCQ_LAUNCH((expand_bwd_kernel<true, false>), expand_bwd_grid(K, R16), dim3(256), 0, st, packed_t, alpha, N, K, g, q,
                            R16, frag);
-    else
-        BCQ_LAUNCH((expand_bwd_kernel<false, false>), expand_bwd_grid(K, R16), dim3(256), 0, st, packed, alpha, N, K, g, q,
+            else
+                BCQ_LAUNCH((expand_bwd_kernel<false, false>), expand_bwd_grid(K, R16), dim3(256), 0, st, packed, alpha, N, K, g, q,
                            R16, frag);
+    }
+#undef BCQ_EXPAND
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_gemm((const bf16_t*)dy, N, frag, (bf16_t*)dx, K, T, K, N, R16, st);

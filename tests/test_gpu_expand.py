@@ -1,0 +1,44 @@
+"""Expanded weights of the large-token route, bit for bit.
+
+With one-hot rows of activations every element of Y = X W^T and dX = dY W is one weight, rounded once to bf16 when the sum of
+the planes is stored and exact from there on.  Sizes are edges of the expansion's blocks: fewer rows than a fragment, rows
+that are no multiple of 8 or 32, one word, word counts below and above a block's 8 or 32, scale groups of one word.
+"""
+import pytest
+import torch
+
+import paper_2210_03858_amd as bcq
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("q", [1, 2, 3, 4, 5, 8])
+@pytest.mark.parametrize("N,K,g", [(5, 32, 32), (32, 256, 32), (72, 288, 96), (264, 1056, 1056), (300, 2080, 32)])
+def test_expanded_weights_bit_exact(N, K, g, q):
+    gen = torch.Generator().manual_seed(N * K + q)
+    packed = torch.randint(-2**31, 2**31 - 1, (q, N, K // 32), dtype=torch.int32, generator=gen)
+    alpha = torch.rand((q, N, K // g), generator=gen) - 0.3
+    bits = (packed.unsqueeze(-1) >> torch.arange(32, dtype=torch.int32)) & 1
+    signs = (2 * bits.reshape(q, N, K) - 1).float()
+    w = torch.zeros(N, K)
+    for i in range(q):  # in plane order, in fp32
+        w += signs[i] * alpha[i].repeat_interleave(g, dim=1)
+    want = w.bfloat16()
+    packed, alpha = packed.cuda(), alpha.cuda()
+    twin = bcq.bcq_pack_transposed(packed) if N % 32 == 0 else None
+
+    def rows(n):  # a row of the identity per token, and enough zero rows for the large-token route
+        x = torch.zeros((max(n, 640), n), dtype=torch.bfloat16, device="cuda")
+        x[:n] = torch.eye(n, dtype=torch.bfloat16, device="cuda")
+        return x
+
+    x, dy = rows(K), rows(N)
+    ws = [torch.empty(bcq.workspace_bytes_grouped(op, t.shape[0], N, K, g, q, 1), dtype=torch.uint8, device="cuda")
+          for op, t in ((1, x), (2, dy))]
+    y = bcq.bcq_linear_fwd_grouped(packed, alpha, x, g, workspace=ws[0])
+    assert torch.equal(y[:K].t().cpu(), want)
+    if N % 8:  # dX takes other kernels there, whose sums over planes and rows are not one rounding of a weight
+        return
+    for t in {twin is not None, False}:
+        dx = bcq.bcq_linear_bwd_input_grouped(packed, alpha, dy, g, packed_t=twin if t else None, workspace=ws[1])
+        assert torch.equal(dx[:N].cpu(), want)
