@@ -284,11 +284,14 @@ static hipError_t launch_q(const uint32_t* packed, const float* alpha, const bf1
     return hipGetLastError();
 }
 
-// Where one kernel is faster than expanding What and multiplying (22 layers of 0.1 - 67 million weights, q = 1 .. 4, 10 to
-// 13 token counts, g = K, 32, 64, 96, 256 timed on both sides).  Row-wise scales: up to 384 tokens, 1.0 - 2.6 times (q = 4,
-// 10240 x 2560: 96 tokens 29 -> 17 us, 256 tokens 46 -> 35, 384 tokens 44 -> 43; 50257 x 1024 at 320 tokens 112 -> 117,
-// the only loss), from there on re-expanding the planes for every 128 tokens costs more than writing What once.
-// Group-wise scales: a unit of 128 columns also builds 2 tables of q loads and 2^(q - 1) sums, 4 when groups hold an odd
+// Where one kernel is faster than expanding What and multiplying.  Row-wise scales, 7528 calls of 22 and more layers of 0.05
+// to 100 million weights, q = 1 .. 4, 81 to 384 tokens timed on both sides (one kernel / two, us ratio): up to 128 tokens
+// everywhere (50257 x 1024, q = 4: 0.86); above that the planes are expanded again for every 128 tokens, which costs more
+// than writing What once where the product alone fills the chip: 50257 x 1024 at 144 to 256 tokens 1.01 (q = 1) to 1.24
+// (q = 4), at 384 1.10 to 1.30, and with four planes above 256 tokens from 8 million weights on (10240 x 2560 at 288 tokens
+// 1.17, 8192 x 2048 at 320 1.01; 4096 x 1024 0.89).  Above 384 tokens two kernels.  The rule is more than 4 % slower than the
+// faster side in 4.5 % of these calls; one kernel up to 384 tokens for all of them was in 8.7 %.
+// Group-wise scales (timed on both sides before): a unit of 128 columns also builds 2 tables of q loads and 2^(q - 1) sums, 4 when groups hold an odd
 // number of words, for every 128 tokens (64 in small layers) again, so the line moves down with q and that parity
 // (`level`), and less so where N K T is small and leaves the matrix product with few workgroups: 10240 x 2560, g = 64,
 // one kernel against two: q = 2, 256 tokens 34 / 42, 384 tokens 47 / 41; q = 4, 128 tokens 27 / 30, 192 tokens 51 / 38.
@@ -296,7 +299,8 @@ static hipError_t launch_q(const uint32_t* packed, const float* alpha, const bf1
 // The re-ordered activations of more than 32 tokens take the place of the expanded weights in the workspace.
 bool fused_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
     if (q > 4 || T > 384 || order_bytes(T, K) > mfma_fwd_workspace(N, K)) return false;
-    if (g == K || T <= 16) return true;
+    if (T <= 16) return true;
+    if (g == K) return !(T > 128 && N * K > 40000000) && !(T > 256 && q == 4 && N * K > 8000000);
     const bool odd = (g / 32) % 2 != 0;
     const int level = q + (odd ? 1 : 0);
     const int64_t work = N * K * T;

@@ -85,6 +85,20 @@ def test_beyond_the_rule_two_kernels_run(oracle, T, N, K, g, q):
     assert nmax_err(to_host(y), ref) <= 1e-2
 
 
+@pytest.mark.parametrize("T,N,K,q", [(257, 8200, 992, 4), (129, 40100, 1024, 1)])
+def test_rows_beyond_the_size_line(oracle, T, N, K, q):
+    """Row-wise scales: one token less takes one kernel, and both agree with the oracle (same bound as above)."""
+    import paper_2210_03858_amd as bcq
+    _, alpha, planes, packed, x, _ = make_case(1, "out", T, N, K, q, "bf16", oracle, extra=T + N)
+    ref = oracle.fwd(alpha.reshape(q, N), planes, x)
+    d_packed, d_alpha, dx = packed_to_dev(packed), to_dev(alpha.reshape(q, N, 1)), to_dev(x, "bf16")
+    for tokens in (T, T - 1):
+        ws = _workspace(bcq, tokens, N, K, K, q)
+        y = bcq.bcq_linear_fwd_grouped(d_packed, d_alpha, dx[:tokens].contiguous(), K, workspace=ws)
+        assert _one_kernel(ws) == (tokens < T)
+        assert nmax_err(to_host(y), ref[:tokens]) <= 1e-2
+
+
 @pytest.mark.parametrize("T,N,K,g,q", [(8, 40, 96, 32, 2), (40, 40, 96, 32, 1), (100, 200, 160, 160, 1), (300, 8200, 160, 160, 3)])
 def test_infinite_scale_stays_in_its_row(oracle, T, N, K, g, q):
     """Columns beyond an odd number of words are zero activations: an infinite scale must not meet them."""
