@@ -291,8 +291,8 @@ static hipError_t launch_q(const uint32_t* packed, const float* alpha, const bf1
 // (q = 4), at 384 1.10 to 1.30, and with four planes above 256 tokens from 8 million weights on (10240 x 2560 at 288 tokens
 // 1.17, 8192 x 2048 at 320 1.01; 4096 x 1024 0.89).  Above 384 tokens two kernels.  The rule is more than 4 % slower than the
 // faster side in 4.5 % of these calls; one kernel up to 384 tokens for all of them was in 8.7 %.
-// Group-wise scales (timed on both sides before): a unit of 128 columns also builds 2 tables of q loads and 2^(q - 1) sums, 4 when groups hold an odd
-// number of words, for every 128 tokens (64 in small layers) again, so the line moves down with q and that parity
+// Group-wise scales (timed against an earlier product kernel): a unit of 128 columns also builds 2 tables of q loads and
+// 2^(q - 1) sums, 4 when groups hold an odd number of words, for every 128 tokens (64 in small layers) again, so the line moves down with q and that parity
 // (`level`), and less so where N K T is small and leaves the matrix product with few workgroups: 10240 x 2560, g = 64,
 // one kernel against two: q = 2, 256 tokens 34 / 42, 384 tokens 47 / 41; q = 4, 128 tokens 27 / 30, 192 tokens 51 / 38.
 // The rule keeps within 4 % of the faster side in 95 % of the 3380 group-wise calls timed and within 10 % in 98 %.
