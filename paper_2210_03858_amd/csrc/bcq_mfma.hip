@@ -321,8 +321,8 @@ __global__ __launch_bounds__(256) void pad_act_kernel(const bf16_t* __restrict__
 // and a wave keeps within 256 registers (accumulators in the other half of the file would be moved back and forth).  Per
 // K-step one barrier: behind it every wave has the step's last fragments in registers, so the step's LDS is requested
 // anew at once, and the first fragments of the next step are read under the MFMAs of the last slice.
-// Nothing branches on the ragged edges: activation rows beyond M and column tiles beyond NC come back as zeros from the
-// buffer range check, contraction indices beyond R meet zero weights.
+// Nothing branches on the ragged edges: activation rows beyond M, their columns beyond R and column tiles beyond NC come back
+// as zeros from the buffer range check (zeros and no other finite or infinite value: an Inf times the zero weights there is NaN).
 //
 // Tile shapes: 256 x 256 has the fewest operand bytes per product; the smaller ones fill the chip where it would leave
 // compute units idle (launch_gemm).  NA, NB: stages of A and B, as many as 160 KiB hold.  KC: 64-column chunks per K-step, two
@@ -402,9 +402,9 @@ __global__ __launch_bounds__((64 * GemmCfg<BM, BN>::NW), 2) void gemm_kernel(
 #pragma unroll
     for (int c = 0; c < KC; ++c)
 #pragma unroll
-        for (int v = 0; v < 2; ++v) {  // chunks beyond R are clamped into the row (they meet zero weights)
+        for (int v = 0; v < 2; ++v) {  // chunks beyond R are sent beyond every descriptor: zeros, as the weights they meet
             const int64_t k = (int64_t)(total - 1) * 64 * KC + c * 64 + (dslot ^ drow ^ v) * 8;
-            atail[c][v] = k < R - 8 ? 0u : (uint32_t)((R - 8 - k) * 2);
+            atail[c][v] = k < R ? 0u : 0x80000000u;
         }
     auto dma_a = [&](int step, int slot, int d) {  // request d of a stage; steps beyond the last repeat it
         step = step < last ? step : last;

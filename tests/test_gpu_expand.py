@@ -42,3 +42,29 @@ def test_expanded_weights_bit_exact(N, K, g, q):
     for t in {twin is not None, False}:
         dx = bcq.bcq_linear_bwd_input_grouped(packed, alpha, dy, g, packed_t=twin if t else None, workspace=ws[1])
         assert torch.equal(dx[:N].cpu(), want)
+
+
+@pytest.mark.parametrize("contraction", [1056, 1088, 1000, 1032])
+def test_infinity_in_the_last_columns_stays_infinite(contraction):
+    """Contractions that end inside a K-step (of 64 or of 128 columns): what stands beyond them is zero on both sides, so one
+    infinite activation in the last eight columns makes its token's results infinite, not NaN, and no other's."""
+    q, T, other, bad = 3, 640, 72 if contraction % 32 else 96, 5
+    N, K = (other, contraction) if contraction % 32 == 0 else (contraction, 96)
+    gen = torch.Generator().manual_seed(contraction)
+    packed = torch.randint(-2**31, 2**31 - 1, (q, N, K // 32), dtype=torch.int32, generator=gen).cuda()
+    alpha = (torch.rand((q, N, 1), generator=gen) * torch.tensor([4.0, 2.0, 1.0]).view(q, 1, 1) + 0.01).cuda()
+    act = torch.randn((T, contraction), generator=gen).bfloat16().cuda()
+    clean = act.clone()
+    act[bad, contraction - 3] = float("inf")
+
+    def product(a):
+        op = 1 if contraction == K else 2
+        ws = torch.empty(bcq.workspace_bytes_grouped(op, T, N, K, K, q, 1), dtype=torch.uint8, device="cuda")
+        if op == 1:
+            return bcq.bcq_linear_fwd_grouped(packed, alpha, a, K, workspace=ws)
+        return bcq.bcq_linear_bwd_input_grouped(packed, alpha, a, K, workspace=ws)
+
+    out, ref = product(act), product(clean)
+    assert out[bad].isinf().all()
+    keep = torch.arange(T, device="cuda") != bad
+    assert torch.equal(out[keep], ref[keep])
