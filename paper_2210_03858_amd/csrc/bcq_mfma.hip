@@ -22,22 +22,29 @@
 namespace bcq {
 
 // ---------------------------------------------------------------------------------------------------------
-// Workgroup -> tile mapping.  Consecutive workgroup ids go round-robin over the 8 XCDs, each with its own L2.  The tiles
-// (of all copies of the tile grid: token slices, parts of a contraction) are numbered in bands of `a` tile rows, down the
-// rows first, and every XCD takes an eighth of that sequence: what it runs at one time is a block of a x (32 / a) tiles,
-// so that its L2 fetches only those rows of the first operand and columns of the second, and the XCDs' shares differ
-// by one tile at most (super-blocks of whole rectangles left 252 tiles in two rounds: 7000 tokens of 1696 x 1696 62 -> 34 us).
+// Consecutive workgroup ids go round-robin over the 8 XCDs, each with its own L2: of `total` items every XCD takes an eighth
+// in a row.
+__device__ __forceinline__ bool xcd_item(uint32_t total, uint32_t& item) {
+    const uint32_t xcd = blockIdx.x & 7;
+    item = (uint32_t)((uint64_t)total * xcd >> 3) + (blockIdx.x >> 3);
+    return item < (uint32_t)((uint64_t)total * (xcd + 1) >> 3);  // the eighths differ by one item
+}
+static inline unsigned xcd_grid(int64_t total) { return (unsigned)(8 * ((total + 7) / 8)); }
+
+// Workgroup -> tile mapping.  The tiles (of all copies of the tile grid: token slices, parts of a contraction) are numbered in
+// bands of `a` tile rows, down the rows first, and every XCD takes an eighth of that sequence: what it runs at one time is a
+// block of a x (32 / a) tiles, so that its L2 fetches only those rows of the first operand and columns of the second, and the
+// XCDs' shares differ by one tile at most (super-blocks of whole rectangles left 252 tiles in two rounds: 7000 tokens of 1696 x 1696 62 -> 34 us).
 struct TileMap {
     int tiles_m, tiles_n, a, total;
 };
 
-__device__ __forceinline__ bool map_tile(const TileMap& tm, int bid, int& copy, int& tile_m, int& tile_n) {
-    const int xcd = bid & 7, slot = bid >> 3;
-    const int first = (int)((int64_t)tm.total * xcd >> 3), end = (int)((int64_t)tm.total * (xcd + 1) >> 3);
-    if (first + slot >= end) return false;
+__device__ __forceinline__ bool map_tile(const TileMap& tm, int& copy, int& tile_m, int& tile_n) {
+    uint32_t item;
+    if (!xcd_item((uint32_t)tm.total, item)) return false;
     const int tiles = tm.tiles_m * tm.tiles_n;
-    copy = (first + slot) / tiles;
-    const int idx = (first + slot) % tiles;
+    copy = (int)item / tiles;
+    const int idx = (int)item % tiles;
     const int band = idx / (tm.a * tm.tiles_n), within = idx % (tm.a * tm.tiles_n);
     const int height = min(tm.a, tm.tiles_m - band * tm.a);
     tile_m = band * tm.a + within % height;
@@ -46,8 +53,9 @@ __device__ __forceinline__ bool map_tile(const TileMap& tm, int bid, int& copy, 
 }
 
 // The band height that brings in the fewest operand bytes for the tiles that an XCD runs at one time; cost_m and cost_n:
-// bytes of a tile row and a tile column.  Returns the number of workgroups to launch.
-static inline unsigned make_tile_map(int tiles_m, int tiles_n, int copies, double cost_m, double cost_n, TileMap* out) {
+// bytes of a tile row and a tile column.  Up to `whole` times those bytes the band is all rows: an XCD then has an eighth of
+// the columns to itself.  Returns the number of workgroups to launch.
+static inline unsigned make_tile_map(int tiles_m, int tiles_n, int copies, double cost_m, double cost_n, double whole, TileMap* out) {
     const int64_t total = (int64_t)tiles_m * tiles_n * copies, share = (total + 7) / 8;
     const int cap = (int)(share < 32 ? share : 32);
     int best = 1;
@@ -56,13 +64,13 @@ static inline unsigned make_tile_map(int tiles_m, int tiles_n, int copies, doubl
         int b = (cap + a - 1) / a;
         if (b > tiles_n) b = tiles_n;
         const double cost = a * cost_m + b * cost_n;
-        if (a * b * 8 >= cap * 7 && cost < least) {  // (a block that is too small to be a share says nothing)
+        if (a * b * 8 >= cap * 7 && (cost < least || (a == tiles_m && cost <= whole * least))) {  // (a block that is too small to be a share says nothing)
             least = cost;
             best = a;
         }
     }
     *out = TileMap{tiles_m, tiles_n, best, (int)total};
-    return (unsigned)(8 * share);
+    return xcd_grid(total);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -77,6 +85,12 @@ __device__ __forceinline__ void store_word_frags(const float (&s)[32], u32x4* __
     }
 }
 
+// `columns`: in the product an XCD has an eighth of the column tiles to itself (make_tile_map), and the expansion's blocks on
+// that XCD write them: a fragment that another XCD holds in its L2 from the call before costs its next writer a trip there.
+// With one workspace kept from call to call (expansion and product, us, plain order / this one): 3072 x 1024, 550 tokens,
+// q = 1 17 / 12, input gradient of 2048 x 8192 at 65 tokens 33 / 18, of 6144 x 2048 at 86 40 / 29; workspaces in turn, where no
+// XCD holds them, 12.2 / 12.1, 18 / 18, 28 / 29.
+
 // expand for the forward: columns of the GEMM = rows n of W, contraction = k.
 // thread = (one row n, one packed word = 32 columns k) -> four 16-byte fragment slots; block = 8 rows x 32 words, so that it
 // reads whole 128-byte lines and stores whole 128-byte pieces (32 rows x 8 words, the lines shared by four blocks: 13.4 us
@@ -86,13 +100,16 @@ __device__ __forceinline__ void store_word_frags(const float (&s)[32], u32x4* __
 template <int Q>
 __global__ __launch_bounds__(256) void expand_fwd_kernel(const uint32_t* __restrict__ packed,
                                                          const float* __restrict__ alpha, int64_t N, int64_t K,
-                                                         int64_t g, int q, int64_t R16 /* padded K / 16 */,
+                                                         int64_t g, int q, int64_t R16 /* padded K / 16 */, int columns,
                                                          u32x4* __restrict__ frag) {
-    const int c = (threadIdx.x & 7) + 8 * (blockIdx.x & 3);
-    const int64_t ct = blockIdx.x >> 2;
+    const uint32_t runs = (uint32_t)((R16 / 2 + 31) / 32), tiles = (uint32_t)((N + 31) / 32);  // runs of 32 words
+    uint32_t item = blockIdx.x;
+    if (columns ? !xcd_item(tiles * runs * 4, item) : item >= tiles * runs * 4) return;
+    const int c = (threadIdx.x & 7) + 8 * (item & 3);
+    const int64_t ct = columns ? (item >> 2) / runs : (item >> 2) % tiles;
     const int64_t n = ct * 32 + c;
     const int64_t Kw = K / 32;
-    const int64_t w = (int64_t)blockIdx.y * 32 + (threadIdx.x >> 3);
+    const int64_t w = (int64_t)(columns ? (item >> 2) % runs : (item >> 2) / tiles) * 32 + (threadIdx.x >> 3);
     if (w * 2 >= R16) return;
     const bool live = (n < N) && (w < Kw);
     const int64_t G = K / g, grp = live ? (w * 32) / g : 0;  // a packed word lies in one scale group (g % 32 == 0)
@@ -137,13 +154,16 @@ __global__ __launch_bounds__(256) void expand_fwd_kernel(const uint32_t* __restr
 template <int Q>
 __global__ __launch_bounds__(256) void expand_bwd_rows_kernel(const uint32_t* __restrict__ packed,
                                                               const float* __restrict__ alpha, int64_t N, int64_t K,
-                                                              int64_t g, int64_t R16 /* padded N / 16 */,
+                                                              int64_t g, int64_t R16 /* padded N / 16 */, int columns,
                                                               u32x4* __restrict__ frag) {
     __shared__ __attribute__((aligned(16))) unsigned char tile[32 * 512];  // rows of 256 columns, in 32-byte pieces c ^ swz(row)
     const int r = threadIdx.x >> 3, wl = threadIdx.x & 7;
     const int64_t Kw = K / 32, G = K / g;
     const uint32_t row_tiles = (uint32_t)(R16 / 2);
-    const int64_t rt = blockIdx.x % row_tiles, wg = blockIdx.x / row_tiles;  // one grid dimension: neither N nor K is limited by it
+    uint32_t item = blockIdx.x;
+    const uint32_t items = row_tiles * (uint32_t)((Kw + 7) / 8);
+    if (columns ? !xcd_item(items, item) : item >= items) return;
+    const int64_t rt = item % row_tiles, wg = item / row_tiles;
     const int64_t n = rt * 32 + r, w = wg * 8 + wl;
     const bool live = n < N && w < Kw;
     float a[Q];
@@ -186,15 +206,21 @@ __global__ __launch_bounds__(256) void expand_bwd_rows_kernel(const uint32_t* __
 template <bool TWIN, bool SPLIT>
 __global__ __launch_bounds__(256) void expand_bwd_kernel(const uint32_t* __restrict__ planes,
                                                          const float* __restrict__ alpha, int64_t N, int64_t K,
-                                                         int64_t g, int q, int64_t R16 /* padded N / 16 */,
+                                                         int64_t g, int q, int64_t R16 /* padded N / 16 */, int columns,
                                                          u32x4* __restrict__ frag) {
     __shared__ float sa[8][256];
     const int c = threadIdx.x & 31, vl = threadIdx.x >> 5;
-    const int64_t ct = blockIdx.x;  // K / 32 column tiles, exactly one packed word wide
+    // the K / 32 column tiles (exactly one packed word wide), or the XCD's eighth of them, side by side: neighbours share the
+    // lines of scales and canonical words (one tile after the other 7680 x 2560, q = 8, g = 64 105 -> 190 us)
     const int64_t Kw = K / 32, Nw = N / 32;
-    const int64_t n_blk = (int64_t)blockIdx.y * 256;
+    const uint32_t first = columns ? (uint32_t)(Kw * (blockIdx.x & 7) >> 3) : 0u;
+    const uint32_t width = columns ? (uint32_t)(Kw * ((blockIdx.x & 7) + 1) >> 3) - first : (uint32_t)Kw;
+    const uint32_t slot = columns ? blockIdx.x >> 3 : blockIdx.x;
+    if (width == 0 || slot >= width * (uint32_t)((R16 / 2 + 7) / 8)) return;
+    const int64_t ct = first + slot % width;
+    const int64_t n_blk = (int64_t)(slot / width) * 256;
     const int64_t G = K / g, grp = (ct * 32) / g;  // the 32 columns of this block share one scale group
-    const int64_t v = (int64_t)blockIdx.y * 8 + vl;  // word index along n
+    const int64_t v = n_blk / 32 + vl;  // word index along n
     const int64_t k = ct * 32 + c;
     // all planes' scales and, with a twin, all words of this thread are requested before the first is used
     uint32_t twin[8];
@@ -325,7 +351,7 @@ __global__ __launch_bounds__(256) void pad_act_kernel(const bf16_t* __restrict__
 // as zeros from the buffer range check (zeros and no other finite or infinite value: an Inf times the zero weights there is NaN).
 //
 // Tile shapes: 256 x 256 has the fewest operand bytes per product; the smaller ones fill the chip where it would leave
-// compute units idle (launch_gemm).  NA, NB: stages of A and B, as many as 160 KiB hold.  KC: 64-column chunks per K-step, two
+// compute units idle (gemm_plan).  NA, NB: stages of A and B, as many as 160 KiB hold.  KC: 64-column chunks per K-step, two
 // for the smallest tiles, whose steps would otherwise be mostly barrier (about 360 cycles a step, beside BM BN / 32 of MFMA).
 template <int BM, int BN> struct GemmShape;
 template <> struct GemmShape<256, 256> { static constexpr int WM = 2, WN = 4, NA = 3, NB = 2, KC = 1; };
@@ -373,7 +399,7 @@ __global__ __launch_bounds__((64 * GemmCfg<BM, BN>::NW), 2) void gemm_kernel(
     const int wm = wave / WN, wn = wave % WN;
 
     int tile_m, tile_n, part;
-    if (!map_tile(tmap, blockIdx.x, part, tile_m, tile_n)) return;  // the eighths differ by one tile
+    if (!map_tile(tmap, part, tile_m, tile_n)) return;
     const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
     const int total = (int)((R + 64 * KC - 1) / (64 * KC));  // K-steps of the whole contraction
     const int first = part * per, last = min(total, first + per) - 1;
@@ -604,18 +630,23 @@ constexpr int RPAD = 128;  // contraction padding of the expanded operand: the l
 size_t mfma_fwd_workspace(int64_t N, int64_t K) { return (size_t)(round_up(N, 32) * round_up(K, RPAD) * 2); }
 size_t mfma_bwd_input_workspace(int64_t N, int64_t K) { return (size_t)(round_up(K, 32) * round_up(N, RPAD) * 2); }
 
+struct GemmPlan {
+    int shape;
+    unsigned wgs;
+    TileMap map;
+    bool columns() const { return map.a == map.tiles_m; }  // an XCD has an eighth of the column tiles to itself
+};
+
 template <int BM, int BN>
-static hipError_t launch_gemm_cfg(const bf16_t* A, int64_t lda, const u32x4* frag, bf16_t* C, int64_t ldc, int64_t M,
+static hipError_t launch_gemm_cfg(const GemmPlan& pl, const bf16_t* A, int64_t lda, const u32x4* frag, bf16_t* C, int64_t ldc, int64_t M,
                                   int64_t NC, int64_t R, int64_t R16, hipStream_t st) {
     using Cfg = GemmCfg<BM, BN>;
     static LdsLimit limit;
     hipError_t e = limit.ensure((const void*)gemm_kernel<BM, BN>, Cfg::LDS_B);
     if (e != hipSuccess) return e;
-    TileMap tmap;
-    const unsigned wgs = make_tile_map((int)((M + BM - 1) / BM), (int)((NC + BN - 1) / BN), 1, (double)BM, (double)BN, &tmap);
     const int steps = (int)((R + 64 * Cfg::KC - 1) / (64 * Cfg::KC));
-    BCQ_LAUNCH((gemm_kernel<BM, BN>), dim3(wgs), dim3(64 * Cfg::NW), Cfg::LDS_B, st, A, lda, frag, C, ldc, M, NC, R, R16,
-                       tmap, steps, (float*)nullptr);
+    BCQ_LAUNCH((gemm_kernel<BM, BN>), dim3(pl.wgs), dim3(64 * Cfg::NW), Cfg::LDS_B, st, A, lda, frag, C, ldc, M, NC, R, R16,
+                       pl.map, steps, (float*)nullptr);
     return hipGetLastError();
 }
 
@@ -645,37 +676,49 @@ static double gemm_estimate(int bm, int bn, int kc, int64_t M, int64_t NC, int64
                           (R + 63) / 64, 2600.0 + 4955.0 * bm * bn / 65536.0);
 }
 
-static hipError_t launch_gemm(const bf16_t* A, int64_t lda, const u32x4* frag, bf16_t* C, int64_t ldc, int64_t M,
-                              int64_t NC, int64_t R, int64_t R16, hipStream_t st) {
+static GemmPlan gemm_plan(int64_t M, int64_t NC, int64_t R) {
     static constexpr int shapes[][3] = {{256, 256, 1}, {256, 192, 1}, {256, 160, 1}, {256, 128, 1},
                                         {128, 160, 1}, {128, 128, 1}, {64, 128, 2}, {64, 64, 2}};
-    int best = 0;
+    GemmPlan pl = {};
     double least = 1e300;
     for (int i = 0; i < 8; ++i) {
         const double t = gemm_estimate(shapes[i][0], shapes[i][1], shapes[i][2], M, NC, R);
         if (t < least) {
             least = t;
-            best = i;
+            pl.shape = i;
         }
     }
-    switch (best) {
-        case 0: return launch_gemm_cfg<256, 256>(A, lda, frag, C, ldc, M, NC, R, R16, st);
-        case 1: return launch_gemm_cfg<256, 192>(A, lda, frag, C, ldc, M, NC, R, R16, st);
-        case 2: return launch_gemm_cfg<256, 160>(A, lda, frag, C, ldc, M, NC, R, R16, st);
-        case 3: return launch_gemm_cfg<256, 128>(A, lda, frag, C, ldc, M, NC, R, R16, st);
-        case 4: return launch_gemm_cfg<128, 160>(A, lda, frag, C, ldc, M, NC, R, R16, st);
-        case 5: return launch_gemm_cfg<128, 128>(A, lda, frag, C, ldc, M, NC, R, R16, st);
-        case 6: return launch_gemm_cfg<64, 128>(A, lda, frag, C, ldc, M, NC, R, R16, st);
-        default: return launch_gemm_cfg<64, 64>(A, lda, frag, C, ldc, M, NC, R, R16, st);
+    const int bm = shapes[pl.shape][0], bn = shapes[pl.shape][1];
+    // Bands of all rows: up to 3072 tokens always that an XCD's share has room for them (1024 x 1024, 786 tokens, with 1.36 times
+    // the operand bytes, kept workspace 11.1 -> 9.2 us, in turn 9.4 / 9.3; 3072 x 1024, 2600 tokens, 1.54 times, 30.0 -> 25.9
+    // and 25.2 / 25.4).  At 4096 tokens, with 1.5 times, they still save up to 4 us with a kept workspace, but cost 0.5 to 2.5
+    // with workspaces in turn (3840 x 1280 44.3 -> 41.4, 39.3 -> 40.1; 5120 x 1280 60 / 60, 57.5 -> 60.3).
+    const double whole = M <= 3072 ? 2.5 : 1.4;
+    pl.wgs = make_tile_map((int)((M + bm - 1) / bm), (int)((NC + bn - 1) / bn), 1, (double)bm, (double)bn, whole, &pl.map);
+    return pl;
+}
+
+static hipError_t launch_gemm(const GemmPlan& pl, const bf16_t* A, int64_t lda, const u32x4* frag, bf16_t* C, int64_t ldc, int64_t M,
+                              int64_t NC, int64_t R, int64_t R16, hipStream_t st) {
+    switch (pl.shape) {
+        case 0: return launch_gemm_cfg<256, 256>(pl, A, lda, frag, C, ldc, M, NC, R, R16, st);
+        case 1: return launch_gemm_cfg<256, 192>(pl, A, lda, frag, C, ldc, M, NC, R, R16, st);
+        case 2: return launch_gemm_cfg<256, 160>(pl, A, lda, frag, C, ldc, M, NC, R, R16, st);
+        case 3: return launch_gemm_cfg<256, 128>(pl, A, lda, frag, C, ldc, M, NC, R, R16, st);
+        case 4: return launch_gemm_cfg<128, 160>(pl, A, lda, frag, C, ldc, M, NC, R, R16, st);
+        case 5: return launch_gemm_cfg<128, 128>(pl, A, lda, frag, C, ldc, M, NC, R, R16, st);
+        case 6: return launch_gemm_cfg<64, 128>(pl, A, lda, frag, C, ldc, M, NC, R, R16, st);
+        default: return launch_gemm_cfg<64, 64>(pl, A, lda, frag, C, ldc, M, NC, R, R16, st);
     }
 }
 
 hipError_t launch_fwd_mfma(const uint32_t* packed, const float* alpha, const void* x, int64_t T, int64_t N,
                            int64_t K, int64_t g, int q, void* y, void* workspace, hipStream_t st) {
     const int64_t R16 = round_up(K, RPAD) / 16;
-    const int64_t ct = (N + 31) / 32;
-    dim3 grid((unsigned)(4 * ct), (unsigned)((R16 / 2 + 31) / 32));
-#define BCQ_EXPAND(Q) BCQ_LAUNCH(expand_fwd_kernel<Q>, grid, dim3(256), 0, st, packed, alpha, N, K, g, q, R16, (u32x4*)workspace)
+    const GemmPlan pl = gemm_plan(T, N, K);
+    const dim3 grid(xcd_grid((N + 31) / 32 * ((R16 / 2 + 31) / 32) * 4));
+#define BCQ_EXPAND(Q) \
+    BCQ_LAUNCH(expand_fwd_kernel<Q>, grid, dim3(256), 0, st, packed, alpha, N, K, g, q, R16, (int)pl.columns(), (u32x4*)workspace)
     switch (q) {
         case 1: BCQ_EXPAND(1); break;
         case 2: BCQ_EXPAND(2); break;
@@ -686,18 +729,20 @@ hipError_t launch_fwd_mfma(const uint32_t* packed, const float* alpha, const voi
 #undef BCQ_EXPAND
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_gemm((const bf16_t*)x, K, (const u32x4*)workspace, (bf16_t*)y, N, T, N, K, R16, st);
+    return launch_gemm(pl, (const bf16_t*)x, K, (const u32x4*)workspace, (bf16_t*)y, N, T, N, K, R16, st);
 }
 
-static dim3 expand_bwd_grid(int64_t K, int64_t R16) { return dim3((unsigned)(K / 32), (unsigned)((R16 / 2 + 7) / 8)); }
+static dim3 expand_bwd_grid(int64_t K, int64_t R16) { return dim3(xcd_grid(K / 32) * (unsigned)((R16 / 2 + 7) / 8)); }
 
 hipError_t launch_bwd_input_mfma(const uint32_t* packed, const uint32_t* packed_t, const float* alpha, const void* dy,
                                  int64_t T, int64_t N, int64_t K, int64_t g, int q, void* dx, void* workspace,
                                  hipStream_t st) {
     const int64_t R16 = round_up(N, RPAD) / 16;
     u32x4* frag = (u32x4*)workspace;
-    const dim3 rows_grid((unsigned)(R16 / 2 * ((K / 32 + 7) / 8)));
-#define BCQ_EXPAND(Q) BCQ_LAUNCH(expand_bwd_rows_kernel<Q>, rows_grid, dim3(256), 0, st, packed, alpha, N, K, g, R16, frag)
+    const GemmPlan pl = gemm_plan(T, K, N);
+    const int columns = pl.columns();
+    const dim3 rows_grid(xcd_grid(R16 / 2 * ((K / 32 + 7) / 8)));
+#define BCQ_EXPAND(Q) BCQ_LAUNCH(expand_bwd_rows_kernel<Q>, rows_grid, dim3(256), 0, st, packed, alpha, N, K, g, R16, columns, frag)
     switch (q) {
         case 1: BCQ_EXPAND(1); break;
         case 2: BCQ_EXPAND(2); break;
@@ -706,15 +751,15 @@ hipError_t launch_bwd_input_mfma(const uint32_t* packed, const uint32_t* packed_
         default:
             if (packed_t && N % 32 == 0)
                 BCQ_LAUNCH((expand_bwd_kernel<true, false>), expand_bwd_grid(K, R16), dim3(256), 0, st, packed_t, alpha, N, K, g, q,
-                           R16, frag);
+                           R16, columns, frag);
             else
                 BCQ_LAUNCH((expand_bwd_kernel<false, false>), expand_bwd_grid(K, R16), dim3(256), 0, st, packed, alpha, N, K, g, q,
-                           R16, frag);
+                           R16, columns, frag);
     }
 #undef BCQ_EXPAND
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_gemm((const bf16_t*)dy, N, frag, (bf16_t*)dx, K, T, K, N, R16, st);
+    return launch_gemm(pl, (const bf16_t*)dy, N, frag, (bf16_t*)dx, K, T, K, N, R16, st);
 }
 
 // Input gradient with fp32 weights for row counts that launch_bwd_input_mfma does not take and that have no twin (N % 32 != 0):
@@ -730,7 +775,9 @@ hipError_t launch_bwd_input_mfma_split(const uint32_t* packed, const float* alph
     const int64_t P = round_up(N, RPAD), R16 = P / 16;
     u32x4* frag = (u32x4*)workspace;
     u32x4* rows = frag + round_up(K, 32) * 3 * P / 8;
-    BCQ_LAUNCH((expand_bwd_kernel<false, true>), expand_bwd_grid(K, R16), dim3(256), 0, st, packed, alpha, N, K, g, q, R16, frag);
+    const int columns = gemm_plan(T < SPLIT_TOKENS ? T : SPLIT_TOKENS, K, 3 * P).columns();
+    BCQ_LAUNCH((expand_bwd_kernel<false, true>), expand_bwd_grid(K, R16), dim3(256), 0, st, packed, alpha, N, K, g, q, R16, columns,
+                       frag);
     hipError_t e = hipGetLastError();
     for (int64_t t0 = 0; t0 < T && e == hipSuccess; t0 += SPLIT_TOKENS) {
         const int64_t M = T - t0 < SPLIT_TOKENS ? T - t0 : SPLIT_TOKENS;
@@ -738,7 +785,7 @@ hipError_t launch_bwd_input_mfma_split(const uint32_t* packed, const float* alph
                            (const bf16_t*)dy + t0 * N, M, N, P, rows);
         e = hipGetLastError();
         if (e == hipSuccess)
-            e = launch_gemm((const bf16_t*)rows, 3 * P, frag, (bf16_t*)dx + t0 * K, K, M, K, 3 * P, 3 * R16, st);
+            e = launch_gemm(gemm_plan(M, K, 3 * P), (const bf16_t*)rows, 3 * P, frag, (bf16_t*)dx + t0 * K, K, M, K, 3 * P, 3 * R16, st);
     }
     return e;
 }
@@ -796,7 +843,7 @@ __global__ __launch_bounds__((64 * DalphaCfg<TILE>::NW), 2) void dalpha_kernel(
     const int wk = wave / WN, wn = wave % WN;
     const int tiles_k = tmap.tiles_m;
     int split, tile_k, tile_n;
-    if (!map_tile(tmap, blockIdx.x, split, tile_k, tile_n)) return;
+    if (!map_tile(tmap, split, tile_k, tile_n)) return;
     const int64_t k0 = (int64_t)tile_k * TILE, n0 = (int64_t)tile_n * TILE;
     const int64_t t_begin = (int64_t)split * tokens_per_split;  // a multiple of 64
     const int64_t t_end = (t_begin + tokens_per_split < T) ? t_begin + tokens_per_split : T;
@@ -1086,7 +1133,7 @@ struct DalphaPlan {
     size_t part_bytes;
 };
 
-// Tile and token slices by an estimate like that of launch_gemm: a step of 64 tokens 0.0117 ns per product and 1.25 ns per
+// Tile and token slices by an estimate like that of gemm_plan: a step of 64 tokens 0.0117 ns per product and 1.25 ns per
 // row and column, at least 490 ns; a round 6.4 us and 0.5 us per plane and 256 x 256 outputs; the partial sums, written and
 // read by the reduction, 2 ns a KB.  `budget` bounds those.  Fitted to 237 products of 64 to 16384 tokens, up to 14 slice
 // counts of both tiles timed: within 3 % of the fastest for 218, within 14 % for all (6144 x 2048 at 16384 tokens: 192 tiles
@@ -1165,7 +1212,7 @@ template <int TILE>
 static hipError_t launch_dalpha_tile(const uint32_t* packed, const bf16_t* x, const bf16_t* dy, int64_t dcols, int64_t T,
                                      int64_t N, int64_t K, int q_train, const DalphaPlan& pl, float* part, hipStream_t st) {
     TileMap tmap;
-    const unsigned wgs = make_tile_map(pl.tiles_k, pl.tiles_n, pl.splits, 1.0, 1.0, &tmap);
+    const unsigned wgs = make_tile_map(pl.tiles_k, pl.tiles_n, pl.splits, 1.0, 1.0, 0.0, &tmap);
     using Cfg = DalphaCfg<TILE>;
 #define BCQ_DA_LAUNCH(QTV, FV)                                                                                        \
     {                                                                                                                 \

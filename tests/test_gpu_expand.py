@@ -2,7 +2,8 @@
 
 With one-hot rows of activations every element of Y = X W^T and dX = dY W is one weight, rounded once to bf16 when the sum of
 the planes is stored and exact from there on.  Sizes are edges of the expansion's blocks: fewer rows than a fragment, rows
-that are no multiple of 8 or 32, one word, word counts below and above a block's 8 or 32, scale groups of one word.
+that are no multiple of 8 or 32, one word, word counts below and above a block's 8 or 32, scale groups of one word.  At 640
+tokens the blocks are ordered by the XCD that reads them in the product, fewer than 8 of them included, at 3200 they are not.
 """
 import pytest
 import torch
@@ -13,8 +14,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("q", [1, 2, 3, 4, 5, 8])
-@pytest.mark.parametrize("N,K,g", [(5, 32, 32), (32, 256, 32), (72, 288, 96), (264, 1056, 1056), (300, 2080, 32)])
-def test_expanded_weights_bit_exact(N, K, g, q):
+@pytest.mark.parametrize("N,K,g,T", [(5, 32, 32, 640), (32, 256, 32, 640), (72, 288, 96, 640), (264, 1056, 1056, 640),
+                                     (300, 2080, 32, 640), (264, 1056, 32, 3200), (40, 288, 288, 3200)])
+def test_expanded_weights_bit_exact(N, K, g, T, q):
     gen = torch.Generator().manual_seed(N * K + q)
     packed = torch.randint(-2**31, 2**31 - 1, (q, N, K // 32), dtype=torch.int32, generator=gen)
     alpha = torch.rand((q, N, K // g), generator=gen) - 0.3
@@ -28,7 +30,7 @@ def test_expanded_weights_bit_exact(N, K, g, q):
     twin = bcq.bcq_pack_transposed(packed) if N % 32 == 0 else None
 
     def rows(n):  # a row of the identity per token, and enough zero rows for the large-token route
-        x = torch.zeros((max(n, 640), n), dtype=torch.bfloat16, device="cuda")
+        x = torch.zeros((max(n, T), n), dtype=torch.bfloat16, device="cuda")
         x[:n] = torch.eye(n, dtype=torch.bfloat16, device="cuda")
         return x
 
