@@ -351,7 +351,9 @@ __global__ __launch_bounds__(256) void pad_act_kernel(const bf16_t* __restrict__
 // as zeros from the buffer range check (zeros and no other finite or infinite value: an Inf times the zero weights there is NaN).
 //
 // Tile shapes: 256 x 256 has the fewest operand bytes per product; the smaller ones fill the chip where it would leave
-// compute units idle (gemm_plan).  NA, NB: stages of A and B, as many as 160 KiB hold.  KC: 64-column chunks per K-step, two
+// compute units idle (gemm_plan).  NA, NB: stages of A and B, as many as 160 KiB hold, but three of 64 x 64 (two
+// more only hold up the first step, whose data the prologue's requests share the way with: 1024 x 1024 at 1024 tokens, expansion and product 10.4 -> 9.6 us, input
+// gradient of 4096 x 1024 at 309 21.0 -> 20.4, forward of 384 x 2688 at 1232 14.7 -> 14.0).  KC: 64-column chunks per K-step, two
 // for the smallest tiles, whose steps would otherwise be mostly barrier (about 360 cycles a step, beside BM BN / 32 of MFMA).
 template <int BM, int BN> struct GemmShape;
 template <> struct GemmShape<256, 256> { static constexpr int WM = 2, WN = 4, NA = 3, NB = 2, KC = 1; };
@@ -361,7 +363,7 @@ template <> struct GemmShape<256, 128> { static constexpr int WM = 4, WN = 2, NA
 template <> struct GemmShape<128, 160> { static constexpr int WM = 2, WN = 2, NA = 4, NB = 4, KC = 1; };
 template <> struct GemmShape<128, 128> { static constexpr int WM = 2, WN = 2, NA = 5, NB = 5, KC = 1; };
 template <> struct GemmShape<64, 128> { static constexpr int WM = 2, WN = 2, NA = 3, NB = 3, KC = 2; };
-template <> struct GemmShape<64, 64> { static constexpr int WM = 2, WN = 2, NA = 5, NB = 5, KC = 2; };
+template <> struct GemmShape<64, 64> { static constexpr int WM = 2, WN = 2, NA = 3, NB = 3, KC = 2; };
 
 template <int BM, int BN>
 struct GemmCfg : GemmShape<BM, BN> {
