@@ -12,12 +12,13 @@
 // larger pattern index (bit i of the pattern = plane i is +1).  Only the ORDER of the fp64 sums over the
 // elements is free.
 //
-// From five planes on (alternating_kernel) the vector (fp32) and one byte of sign pattern per element stay in LDS.  A round is
+// From five planes on, and with one plane above 1024 elements (alternating_kernel), the vector (fp32) and one byte of sign
+// pattern per element stay in LDS.  A round is
 // a chain of two barriers, a cross-lane fp64 sum, the solve (q dependent fp64 divisions) and q steps of bisection per
 // element; it makes ONE pass over the elements (the re-assignment and the next round's sums together), counts the
 // Gram matrix in integers from the pattern bytes (its entries are n - 2 * disagreements, exact) and only wave 0 solves.
 //
-// Up to four planes (alternating_reg_kernel) the elements stay in registers, up to 16 per lane, and a round compares no
+// Up to four planes (alternating_reg_kernel) the elements stay in registers, up to 32 per lane, and a round compares no
 // distances: the weights are fp32, so the place where the nearest level changes is one fp32 number per pair of
 // neighbouring levels, found by the distances themselves at the three floats around their middle.  The levels lie
 // symmetrically about zero, so |w| is compared with the 2^(q-1) - 1 thresholds of the positive half and the sign of w
@@ -52,6 +53,7 @@ struct AltShared {
 // index in range when x or a level is not finite.
 template <int LEVELS>
 __device__ __forceinline__ int nearest_level(const double* level, double x) {
+    if constexpr (LEVELS == 2) return fabs(x - level[1]) < fabs(x - level[0]) ? 1 : 0;
     int pos = 0;  // levels above x
 #pragma unroll
     for (int step = LEVELS / 2; step >= 1; step >>= 1) pos += level[pos + step - 1] > x ? step : 0;
@@ -720,14 +722,23 @@ static hipError_t launch_reg(const float* W, int64_t V, int n, int iters, float*
 // As many elements per lane as one wave's registers hold, then more waves.  q = 3, 15 rounds, us, one wave against one to four
 // with 4 / 8 / 16 elements per lane: 1024 vectors of 1024 27 against 52 / 38 / 31, 256 of them 26 against 27 / 28 / 30, 1024 of
 // 512 22 against 33 / 26 / 31, 4096 of 256 41 (with 8 and 16: 51, 73); 1024 of 2560 73 with 16 (112 through LDS).
+// Above 4096 elements 32 per lane and up to 8 waves: every wave solves and sorts for itself, so that 16 waves of 16 elements,
+// whose registers spill besides, were slower than LDS where vectors are many (918 of 4480, q = 2, 3, 4: through LDS 87, 166,
+// 302 us, with 16 waves 103, 235, 556, with 8 75, 126, 213; 500 of 16384, q = 4: 765, 692, 242).  With one plane there is
+// next to nothing to solve, and the registers only keep waves away: 918 of 4480 8 us through LDS, 14 to 16 from registers,
+// 3000 of 1120 9.4 and 10.9.
 template <int Q>
 static hipError_t launch_reg_q(const float* W, int64_t V, int n, int iters, float* alpha, uint32_t* packed, int8_t* planes,
                                int* status_word, hipStream_t st) {
     if (n <= 256) return launch_reg<Q, 1, 1>(W, V, n, iters, alpha, packed, planes, status_word, st);
     if (n <= 512) return launch_reg<Q, 2, 1>(W, V, n, iters, alpha, packed, planes, status_word, st);
     if (n <= 1024) return launch_reg<Q, 4, 1>(W, V, n, iters, alpha, packed, planes, status_word, st);
-    if (n <= 4096) return launch_reg<Q, 4, 4>(W, V, n, iters, alpha, packed, planes, status_word, st);
-    return launch_reg<Q, 4, 16>(W, V, n, iters, alpha, packed, planes, status_word, st);
+    if constexpr (Q == 1) {
+        return launch_q<1>(W, V, n, iters, alpha, packed, planes, status_word, st);
+    } else {
+        if (n <= 4096) return launch_reg<Q, 4, 4>(W, V, n, iters, alpha, packed, planes, status_word, st);
+        return launch_reg<Q, 8, 8>(W, V, n, iters, alpha, packed, planes, status_word, st);
+    }
 }
 
 hipError_t launch_quantize_alternating(const float* W, int64_t V, int64_t n, int q, int iters, float* alpha,

@@ -111,9 +111,9 @@ def test_alternating_bisection(bcq, oracle, q, N, K, g):
 
 
 @pytest.mark.parametrize("kind", ["normal", "small", "large"])
-@pytest.mark.parametrize("N,K", [(40, 32), (12, 256), (12, 288), (8, 512), (8, 544), (6, 1024), (6, 1056), (3, 4096), (2, 4128)])
+@pytest.mark.parametrize("N,K", [(40, 32), (12, 256), (12, 288), (8, 512), (8, 544), (6, 1024), (6, 1056), (3, 4096), (2, 4128), (2, 14336), (1, 16384)])
 def test_registers_and_thresholds(bcq, oracle, N, K, kind):
-    """One to sixteen waves with 4, 8 or 16 elements per lane, at and behind each limit.  Scaling by a power of two changes no
+    """One to eight waves with 4 to 32 elements per lane, at and behind each limit.  Scaling by a power of two changes no
     decision; above 1e30 every round compares distances (all levels) instead of thresholds.  (Elements far above or below
     the levels get there too, but are no input for this check: from 2^-30 of sum |alpha| down, an element's two nearest
     levels +l and -l differ in distance by less than the 1e-9 of it that make a vector robust.)"""
