@@ -1136,11 +1136,13 @@ struct DalphaPlan {
 };
 
 // Tile and token slices by an estimate like that of gemm_plan: a step of 64 tokens 0.0117 ns per product and 1.25 ns per
-// row and column, at least 490 ns; a round 6.4 us and 0.5 us per plane and 256 x 256 outputs; the partial sums, written and
-// read by the reduction, 2 ns a KB.  `budget` bounds those.  Fitted to 237 products of 64 to 16384 tokens, up to 14 slice
-// counts of both tiles timed: within 3 % of the fastest for 218, within 14 % for all (6144 x 2048 at 16384 tokens: 192 tiles
-// in one slice leave a quarter of the chip idle, 430 us; four slices 322).
-static DalphaPlan dalpha_plan(int64_t T, int64_t N, int64_t K, int64_t g, int q, int smallest, size_t budget) {
+// row and column, at least 490 ns; a round 6.4 us and 0.5 us per trained plane and 256 x 256 outputs; the partial sums,
+// written and read by the reduction, 1 ns a KB.  `budget` bounds those.  Of 6870 calls of 17 to 8192 tokens, q = 1 .. 8, one or all
+// planes trained, g = K, 32 .. 640, the pick is within 4 % of the fastest of up to ten tiles and slice counts for 96 %, within
+// 10 % for 98 % (6144 x 2048 at 16384 tokens: 192 tiles in one slice leave a quarter of the chip idle, 430 us; four slices 322.
+// With all planes counted, trained or not, and 2 ns a KB, which is dear where partial sums are kept per 32 columns, 128 x
+// 128 tiles were taken for groups of 128 and many planes: 10240 x 2560, q = 8, 22 tokens 124 us, now 76).
+static DalphaPlan dalpha_plan(int64_t T, int64_t N, int64_t K, int64_t g, int q_train, int smallest, size_t budget) {
     static const ShareTable share(0.112);
     DalphaPlan best = {};
     double least = 1e300;
@@ -1152,7 +1154,7 @@ static DalphaPlan dalpha_plan(int64_t T, int64_t N, int64_t K, int64_t g, int q,
         pl.tiles_n = (int)((N + tile - 1) / tile);
         pl.fine = (g != K) && (g % tile != 0);
         const int64_t tiles = (int64_t)pl.tiles_k * pl.tiles_n;
-        const size_t slice_bytes = (size_t)pl.tiles_k * q * N * sizeof(float) * (pl.fine ? tile / 32 : 1);
+        const size_t slice_bytes = (size_t)pl.tiles_k * q_train * N * sizeof(float) * (pl.fine ? tile / 32 : 1);
         int64_t before = 0;
         for (int64_t s = 1; s <= steps && s <= 64 && (s == 1 || s * tiles <= 2048); ++s) {
             const int64_t per = (steps + s - 1) / s, splits = (steps + per - 1) / per;
@@ -1161,7 +1163,7 @@ static DalphaPlan dalpha_plan(int64_t T, int64_t N, int64_t K, int64_t g, int q,
             const size_t bytes = (size_t)splits * slice_bytes;
             if (bytes > budget) break;  // (256 x 256 tiles in one slice always fit)
             const double t = round_estimate(0.0117 * tile * tile + 2.5 * tile, 490.0, share, tiles * splits, per,
-                                            6400.0 + 500.0 * q * tile * tile / 65536.0) + (double)bytes / 484.0;
+                                            6400.0 + 500.0 * q_train * tile * tile / 65536.0) + (double)bytes / 1000.0;
             if (t < least) {
                 least = t;
                 best = pl;
@@ -1199,9 +1201,9 @@ static DalphaScratch dalpha_scratch(int64_t T, int64_t N, int64_t K, int64_t g, 
     return s;
 }
 // One piece: any plan within the budget.  Several: 256 x 256 tiles for all, so that one reduction takes their partial sums.
-static DalphaPlan dalpha_piece_plan(int64_t M, int64_t T, int64_t N, int64_t K, int64_t g, int q) {
+static DalphaPlan dalpha_piece_plan(int64_t M, int64_t T, int64_t N, int64_t K, int64_t g, int q, int q_train) {
     const DalphaBudget b = dalpha_budget(M, N, K, g, q);
-    return M == T ? dalpha_plan(M, N, K, g, q, 128, b.copy + b.part) : dalpha_plan(M, N, K, g, q, 256, b.part);
+    return M == T ? dalpha_plan(M, N, K, g, q_train, 128, b.copy + b.part) : dalpha_plan(M, N, K, g, q_train, 256, b.part);
 }
 
 size_t mfma_bwd_alpha_workspace(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
@@ -1254,7 +1256,7 @@ hipError_t launch_bwd_alpha_mfma(const uint32_t* packed, const void* x, const vo
     int splits = 0;
     for (int64_t t0 = 0; t0 < T; t0 += piece) {
         const int64_t M = T - t0 < piece ? T - t0 : piece;
-        pl = dalpha_piece_plan(M, T, N, K, g, q);
+        pl = dalpha_piece_plan(M, T, N, K, g, q, q_train);
         const bf16_t* rows = (const bf16_t*)dy + t0 * N;
         if (sc.pad) {
             u32x4* padded = reinterpret_cast<u32x4*>(ws + sc.part);

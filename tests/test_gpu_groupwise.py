@@ -277,6 +277,12 @@ def test_grouped_q_train_and_grad_scale(bcq, oracle):
     _run_layer(bcq, oracle, 2, "out", 64, 256, 512, 128, 3, "f32", q_train=2, grad_scale=0.5)
 
 
+@pytest.mark.parametrize("q,q_train", [(8, 8), (7, 1)])
+def test_grouped_many_planes_over_whole_tiles(bcq, oracle, q, q_train):
+    """Groups of 128 columns, five planes and more: 256 x 256 tiles with partial sums per 32 columns, ragged in N and K."""
+    _run_layer(bcq, oracle, 2, "out", 20, 3592, 1152, 128, q, "bf16", q_train=q_train, grad_scale=1.0 / 128)
+
+
 def test_grouped_fp32_integer_case_is_exact(bcq, oracle):
     """Small-integer activations and power-of-two scales that differ between groups: every partial sum is exact
     in fp32, so the fp32 path must reproduce the oracle exactly (catches any slip in the group index)."""
