@@ -385,12 +385,10 @@ struct GemmCfg : GemmShape<BM, BN> {
 // gfx9 s_waitcnt immediate: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] at [15:14]; vmcnt alone
 constexpr int wait_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
 
-// sums != nullptr: the contraction is cut into parts of `per` K-steps (the tile map's copies), each workgroup stores its
-// fp32 tile to sums[part][M][NC rounded up to 4].
 template <int BM, int BN>
 __global__ __launch_bounds__((64 * GemmCfg<BM, BN>::NW), 2) void gemm_kernel(
     const bf16_t* __restrict__ A, int64_t lda, const u32x4* __restrict__ Bfrag, bf16_t* __restrict__ C, int64_t ldc,
-    int64_t M, int64_t NC, int64_t R, int64_t R16, TileMap tmap, int per, float* __restrict__ sums) {
+    int64_t M, int64_t NC, int64_t R, int64_t R16, TileMap tmap) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the buffer-resource builtins exist in the device pass only
     using Cfg = GemmCfg<BM, BN>;
     constexpr int WN = Cfg::WN, TM = Cfg::TM, TN = Cfg::TN, NA = Cfg::NA, NB = Cfg::NB, KC = Cfg::KC, SL = 2 * KC;
@@ -400,11 +398,10 @@ __global__ __launch_bounds__((64 * GemmCfg<BM, BN>::NW), 2) void gemm_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: keeps descriptors and LDS bases scalar
     const int wm = wave / WN, wn = wave % WN;
 
-    int tile_m, tile_n, part;
-    if (!map_tile(tmap, part, tile_m, tile_n)) return;
+    int tile_m, tile_n, only;
+    if (!map_tile(tmap, only, tile_m, tile_n)) return;
     const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
-    const int total = (int)((R + 64 * KC - 1) / (64 * KC));  // K-steps of the whole contraction
-    const int first = part * per, last = min(total, first + per) - 1;
+    const int last = (int)((R + 64 * KC - 1) / (64 * KC)) - 1;  // K-step
 
     f32x4 acc[TN][TM];  // [weight tile][token tile]
 #pragma unroll
@@ -423,7 +420,7 @@ __global__ __launch_bounds__((64 * GemmCfg<BM, BN>::NW), 2) void gemm_kernel(
         (void*)(A + (left > 0 ? wrow0 * lda : 0)), 0, (int)(left > 0 ? (left < 0x7fffffffll ? left : 0x7fffffffll) : 0),
         0x00020000);
     const int drow = lane >> 3, dslot = lane & 7;
-    const bool ragged = (int64_t)total * 64 * KC > R;
+    const bool ragged = (int64_t)(last + 1) * 64 * KC > R;
     uint32_t avoff[JA], atail[KC][2];  // lane offsets; what the last step, which may reach beyond R, adds to them
 #pragma unroll
     for (int j = 0; j < JA; ++j) avoff[j] = (uint32_t)((j * 8 + drow) * lda * 2 + (dslot ^ drow ^ (j & 1)) * 16);
@@ -431,12 +428,12 @@ __global__ __launch_bounds__((64 * GemmCfg<BM, BN>::NW), 2) void gemm_kernel(
     for (int c = 0; c < KC; ++c)
 #pragma unroll
         for (int v = 0; v < 2; ++v) {  // chunks beyond R are sent beyond every descriptor: zeros, as the weights they meet
-            const int64_t k = (int64_t)(total - 1) * 64 * KC + c * 64 + (dslot ^ drow ^ v) * 8;
+            const int64_t k = (int64_t)last * 64 * KC + c * 64 + (dslot ^ drow ^ v) * 8;
             atail[c][v] = k < R ? 0u : 0x80000000u;
         }
     auto dma_a = [&](int step, int slot, int d) {  // request d of a stage; steps beyond the last repeat it
         step = step < last ? step : last;
-        const uint32_t tail = ragged && step == total - 1 ? ~0u : 0u;
+        const uint32_t tail = ragged && step == last ? ~0u : 0u;
         const int c = d / JA, j = d % JA;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             ra, (void __attribute__((address_space(3)))*)(smem + slot * A_B + c * Cfg::CA + (wave * JA + j) * 1024), 16,
@@ -521,10 +518,10 @@ __global__ __launch_bounds__((64 * GemmCfg<BM, BN>::NW), 2) void gemm_kernel(
 #pragma unroll
     for (int p = 0; p < NA; ++p) {
 #pragma unroll
-        for (int d = 0; d < DA; ++d) dma_a(first + p, p, d);
+        for (int d = 0; d < DA; ++d) dma_a(p, p, d);
         if (p < NB) {
 #pragma unroll
-            for (int d = 0; d < DB; ++d) dma_b(first + p, p, d);
+            for (int d = 0; d < DB; ++d) dma_b(p, p, d);
         }
     }
     asm volatile("s_waitcnt %0" ::"n"(wait_vm((NA - 1) * DA + (NB - 1) * DB)) : "memory");
@@ -537,7 +534,7 @@ __global__ __launch_bounds__((64 * GemmCfg<BM, BN>::NW), 2) void gemm_kernel(
     __builtin_amdgcn_sched_barrier(0);
 
     int sa = 0, sb = 0;  // stages of step s
-    for (int s = first; s <= last; ++s) {
+    for (int s = 0; s <= last; ++s) {
         const int sa_next = sa + 1 == NA ? 0 : sa + 1, sb_next = sb + 1 == NB ? 0 : sb + 1;
         const uint32_t ab = (uint32_t)(sa * A_B), bb = (uint32_t)(sb * B_B);
         auto nothing = [](int) {};
@@ -576,20 +573,6 @@ __global__ __launch_bounds__((64 * GemmCfg<BM, BN>::NW), 2) void gemm_kernel(
     // consecutive bytes of a token in the four lanes that share it: 16-byte stores without a trip through LDS (which
     // took 3.6 us instead of 1.9 per 256 x 256 tile).
     const int h = lane >> 4;
-    if (sums) {
-        const int64_t lds_ = (NC + 3) / 4 * 4;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int64_t t = m0 + (wm * TM + i) * 16 + (lane & 15);
-            float* row = sums + ((int64_t)part * M + t) * lds_;
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int64_t n = n0 + (wn * TN + j) * 16 + 4 * h;
-                if (t < M && n < NC) *reinterpret_cast<f32x4*>(row + n) = acc[j][i];
-            }
-        }
-        return;
-    }
     const bool vec_ok = (ldc % 8 == 0);
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -646,9 +629,8 @@ static hipError_t launch_gemm_cfg(const GemmPlan& pl, const bf16_t* A, int64_t l
     static LdsLimit limit;
     hipError_t e = limit.ensure((const void*)gemm_kernel<BM, BN>, Cfg::LDS_B);
     if (e != hipSuccess) return e;
-    const int steps = (int)((R + 64 * Cfg::KC - 1) / (64 * Cfg::KC));
     BCQ_LAUNCH((gemm_kernel<BM, BN>), dim3(pl.wgs), dim3(64 * Cfg::NW), Cfg::LDS_B, st, A, lda, frag, C, ldc, M, NC, R, R16,
-                       pl.map, steps, (float*)nullptr);
+                       pl.map);
     return hipGetLastError();
 }
 
@@ -1132,7 +1114,6 @@ struct DalphaPlan {
     int tile, tiles_k, tiles_n, splits;
     int64_t per_split;
     bool fine;  // groups that are not whole k tiles need per-32-column partials
-    size_t part_bytes;
 };
 
 // Tile and token slices by an estimate like that of gemm_plan: a step of 64 tokens 0.0117 ns per product and 1.25 ns per
@@ -1169,7 +1150,6 @@ static DalphaPlan dalpha_plan(int64_t T, int64_t N, int64_t K, int64_t g, int q_
                 best = pl;
                 best.splits = (int)splits;
                 best.per_split = per * 64;
-                best.part_bytes = bytes;
             }
         }
     }
