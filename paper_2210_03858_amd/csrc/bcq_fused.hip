@@ -238,6 +238,14 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(const float* __restrict_
 static size_t order_bytes(int64_t T, int64_t K) { return T <= 32 ? 0 : (size_t)((T + 31) / 32 * 32 * K * 2); }
 static size_t sums_bytes(int64_t T, int64_t N, int parts) { return (size_t)parts * T * ((N + 3) / 4 * 4) * 4; }
 
+// 128 tokens per workgroup read and expand every plane half as often, 64 make twice as many workgroups: measured
+// (256 tokens, q = 4) 7680 x 2560 27 against 31 us, 10240 x 2560 35 / 38, 2560 x 2560 17 / 17, 1024 x 1024 10 / 8, and
+// with the contraction split 2560 x 10240 48 / 53.
+static bool wide_tokens(int64_t T, int64_t N, int64_t K) {
+    const int64_t tiles = (N + 31) / 32 * ((T + 127) / 128), units = (K + 127) / 128;
+    return T > 64 && (tiles >= 256 || (tiles >= 64 && units >= 64));
+}
+
 template <int Q, bool GROUPED>
 static hipError_t launch_q(const uint32_t* packed, const float* alpha, const bf16_t* x, int64_t T, int64_t N, int64_t K,
                            int64_t g, bf16_t* y, void* workspace, hipStream_t st) {
@@ -251,11 +259,7 @@ static hipError_t launch_q(const uint32_t* packed, const float* alpha, const bf1
         if (e != hipSuccess) return e;
         xo = (const bf16_t*)workspace;
     }
-    // 128 tokens per workgroup read and expand every plane half as often, 64 make twice as many workgroups: measured
-    // (256 tokens, q = 4) 7680 x 2560 27 against 31 us, 10240 x 2560 35 / 38, 2560 x 2560 17 / 17, 1024 x 1024 10 / 8, and
-    // with the contraction split 2560 x 10240 48 / 53.
-    const int64_t wide_tiles = (int64_t)cols * ((T + 127) / 128);
-    const bool wide = T > 64 && (wide_tiles >= 256 || (wide_tiles >= 64 && units >= 64));
+    const bool wide = wide_tokens(T, N, K);
     const int W = T <= 32 ? 8 : 4, tile = T <= 32 ? 32 : wide ? 128 : 64;
     const unsigned tiles = (unsigned)((T + tile - 1) / tile);
     // Few rows and a long contraction: parts of it go to workgroups of their own while they still find an idle compute
@@ -284,23 +288,40 @@ static hipError_t launch_q(const uint32_t* packed, const float* alpha, const bf1
     return hipGetLastError();
 }
 
-// Where one kernel is faster than expanding What and multiplying.  Row-wise scales, 7528 calls of 22 and more layers of 0.05
-// to 100 million weights, q = 1 .. 4, 81 to 384 tokens timed on both sides (one kernel / two, us ratio): up to 128 tokens
-// everywhere (50257 x 1024, q = 4: 0.86); above that the planes are expanded again for every 128 tokens, which costs more
-// than writing What once where the product alone fills the chip: 50257 x 1024 at 144 to 256 tokens 1.01 (q = 1) to 1.24
-// (q = 4), at 384 1.10 to 1.30, and with four planes above 256 tokens from 8 million weights on (10240 x 2560 at 288 tokens
-// 1.17, 8192 x 2048 at 320 1.01; 4096 x 1024 0.89).  Above 384 tokens two kernels.  The rule is more than 4 % slower than the
-// faster side in 4.5 % of these calls; one kernel up to 384 tokens for all of them was in 8.7 %.
-// Group-wise scales (timed against an earlier product kernel): a unit of 128 columns also builds 2 tables of q loads and
-// 2^(q - 1) sums, 4 when groups hold an odd number of words, for every 128 tokens (64 in small layers) again, so the line moves down with q and that parity
-// (`level`), and less so where N K T is small and leaves the matrix product with few workgroups: 10240 x 2560, g = 64,
-// one kernel against two: q = 2, 256 tokens 34 / 42, 384 tokens 47 / 41; q = 4, 128 tokens 27 / 30, 192 tokens 51 / 38.
-// The rule keeps within 4 % of the faster side in 95 % of the 3380 group-wise calls timed and within 10 % in 98 %.
+// Row-wise scales, 129 to 384 tokens, large layers: whether the workgroups of the one-kernel forward run in one round and
+// fill it (two of 128 tokens or one of 64 to a compute unit at a time).  A round that is half empty, or a second one, goes
+// to two kernels; so do three tiles of 128 tokens.
+static bool one_full_round(int64_t T, int64_t N, int64_t K, int q) {
+    const int64_t cols = (N + 31) / 32;
+    if (!wide_tokens(T, N, K)) return cols * ((T + 63) / 64) <= 256;
+    const int64_t tiles = cols * ((T + 127) / 128);
+    return T <= 256 && tiles <= 512 && tiles > (q == 4 ? 384 : 320);
+}
+
+// Where one kernel is faster than expanding What and multiplying.  Row-wise scales (65000 timings of both sides, 81 to 384 tokens,
+// 0.05 to 100 million weights, q = 1 .. 4): up to 128 tokens one kernel.  Above that the planes are expanded again for
+// every 128 tokens, which costs more than writing What once where the product alone fills the chip: above 40 million weights,
+// and with four planes above 256 tokens from 8 million on, unless one_full_round (one kernel / two, us: 50257 x 1024 at 144
+// tokens 64 / 53 (q = 1) and 76 / 57 (q = 4), 10240 x 2560, q = 4, 288 tokens 42 / 33; one full round 8191 x 7072, q = 2,
+// 160 tokens 53 / 60, 1615 x 5120, q = 4, 320 tokens 25 / 28, and just beyond 1664 x 5120 29 / 25), and up to 100 million, from
+// where What no longer fits the 256 MB cache in front of HBM (12288 x 12288, q = 3, 200 tokens 126 / 211, 16384 x 8192, q = 4,
+// 256 tokens 119 / 161).  Of the 3574 timed calls beyond the first two sizes 22 go to the side that is more than 4 % slower
+// (worst 1.17).  Below them one kernel is more than 4 %
+// slower in 3 % of the calls up to 128 tokens, in 15 % up to 256 and in 48 % above (3072 x 1024, q = 4, 128 tokens 8.6 / 10.4,
+// 256 12.0 / 10.5, 384 15.0 / 12.2).  Above 384 tokens two kernels.
+// Group-wise scales: a unit of 128 columns also builds 2 tables of q loads and 2^(q - 1) sums, 4 when groups hold an odd
+// number of words, for every 128 tokens (64 in small layers) again, so the line moves down with q and that parity (`level`),
+// and less so where N K T is small and leaves the matrix product with few workgroups.  The line was set against an earlier,
+// slower product: against the present one it takes the side that is more than 4 % slower in 26 % of 34440 calls and more than
+// 10 % in 19 %, nearly always one kernel (10240 x 2560, g = 64, q = 2, 128 tokens 25 / 27, 256 37 / 31; q = 4, 128 tokens 36 / 29).
 // The re-ordered activations of more than 32 tokens take the place of the expanded weights in the workspace.
 bool fused_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
     if (q > 4 || T > 384 || order_bytes(T, K) > mfma_fwd_workspace(N, K)) return false;
     if (T <= 16) return true;
-    if (g == K) return !(T > 128 && N * K > 40000000) && !(T > 256 && q == 4 && N * K > 8000000);
+    if (g == K) {
+        const bool large = (T > 128 && N * K > 40000000) || (T > 256 && q == 4 && N * K > 8000000);
+        return !large || N * K > 100000000 || one_full_round(T, N, K, q);
+    }
     const bool odd = (g / 32) % 2 != 0;
     const int level = q + (odd ? 1 : 0);
     const int64_t work = N * K * T;

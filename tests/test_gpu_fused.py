@@ -99,6 +99,27 @@ def test_rows_beyond_the_size_line(oracle, T, N, K, q):
         assert nmax_err(to_host(y), ref[:tokens]) <= 1e-2
 
 
+@pytest.mark.parametrize("T,N,K,q,one", [(320, 1632, 5056, 4, True), (320, 1664, 5056, 4, False),
+                                         (160, 8192, 4896, 2, True), (160, 8224, 4896, 2, False),
+                                         (160, 5120, 7840, 1, False), (288, 5120, 8000, 3, False), (130, 25024, 4000, 1, True)])
+def test_large_layers_in_one_full_round(T, N, K, q, one):
+    """Row-wise scales beyond the size line take one kernel where its workgroups fill one round: 255 against 260 of 64 tokens,
+    512 against 514 of 128 tokens, 320 and three tiles of 128 tokens; above 100 million weights always.  Same bound as above,
+    against fp32 products."""
+    import torch
+    import paper_2210_03858_amd as bcq
+    gen = torch.Generator(device="cuda").manual_seed(N + K)
+    packed = torch.randint(-2**31, 2**31 - 1, (q, N, K // 32), dtype=torch.int32, device="cuda", generator=gen)
+    alpha = torch.rand((q, N, 1), device="cuda", generator=gen) + 0.1
+    x = torch.randn((T, K), device="cuda", generator=gen).bfloat16()
+    bits = torch.arange(32, dtype=torch.int32, device="cuda")
+    w = sum((2 * ((packed[i].unsqueeze(-1) >> bits) & 1) - 1).reshape(N, K) * alpha[i] for i in range(q))
+    ws = _workspace(bcq, T, N, K, K, q)
+    y = bcq.bcq_linear_fwd_grouped(packed, alpha, x, K, workspace=ws)
+    assert _one_kernel(ws) == one
+    assert nmax_err(to_host(y), (x.float() @ w.t()).cpu().numpy()) <= 1e-2
+
+
 @pytest.mark.parametrize("T,N,K,g,q", [(8, 40, 96, 32, 2), (40, 40, 96, 32, 1), (100, 200, 160, 160, 1), (300, 8200, 160, 160, 3)])
 def test_infinite_scale_stays_in_its_row(oracle, T, N, K, g, q):
     """Columns beyond an odd number of words are zero activations: an infinite scale must not meet them."""
