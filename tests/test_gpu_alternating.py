@@ -123,15 +123,56 @@ def test_registers_and_thresholds(bcq, oracle, N, K, kind):
         _check(bcq, oracle, W, q, iters=6)
 
 
-def test_ties_at_floats(bcq, oracle):
-    """Weights on a coarse grid put levels' middles on floats; the distances decide there, so that the error is no worse."""
-    rng = np.random.default_rng(5)
-    W = (rng.integers(-6, 7, size=(64, 256)) / 64.0).astype(np.float32)
-    for q in (2, 3, 4):
+@pytest.mark.parametrize("K", [64, 256, 1024, 4096, 16384])
+def test_ties_at_floats(bcq, oracle, K):
+    """Levels at the odd multiples of 1 / 64 up to 2^q - 1 of them, elements on every level and one step below it, which is
+    the middle of two levels, on both sides of zero: the greedy start already ends there, the refit returns the same
+    scales exactly (powers of four for K: the oracle's solve takes its square root), and every tie has to go to the larger
+    level for the planes to stay as they are."""
+    rng = np.random.default_rng(K)
+    for q in (1, 2, 3, 4):
+        levels = np.arange(-(2 ** q - 1), 2 ** q, 2)
+        vector = np.tile(np.concatenate((levels, levels - 1)), K // (2 * 2 ** q))
+        W = np.stack([rng.permutation(vector) for _ in range(6)]).astype(np.float32) / 64.0
         alpha, packed, _ = bcq.bcq_quantize_alternating(to_dev(W), q, iters=15)
-        a = alpha.cpu().numpy().reshape(q, 64, 1).astype(np.float64)
-        b = oracle.unpack(packed_to_host(packed), 256).reshape(q, 64, 256)
+        want = np.array([2.0 ** (q - 1 - i) / 64.0 for i in range(q)], dtype=np.float32)
+        assert np.array_equal(alpha.cpu().numpy().reshape(q, 6), np.repeat(want[:, None], 6, axis=1))
+        planes = oracle.unpack(packed_to_host(packed), K).reshape(q, 6, K)
+        assert np.array_equal((planes * want[:, None, None]).sum(axis=0), (W * 64.0 + (W * 64.0 % 2 == 0)) / 64.0)
         a_ref, b_ref = oracle.quantize_alternating(W, q, iters=15)[:2]
-        e_gpu = ((W - (a * b).sum(0)) ** 2).sum()
-        e_ref = ((W - (a_ref.reshape(q, 64, 1).astype(np.float64) * b_ref.reshape(q, 64, 256)).sum(0)) ** 2).sum()
-        assert e_gpu <= 1.02 * e_ref + 1e-12
+        assert np.array_equal(planes, b_ref.reshape(q, 6, K)) and np.array_equal(alpha.cpu().numpy().reshape(q, 6), a_ref.reshape(q, 6))
+
+
+@pytest.mark.parametrize("K", [64, 1024, 2048, 6144])
+@pytest.mark.parametrize("factor", [2.0 ** -60, 2.0 ** 22])
+def test_elements_far_from_the_levels(bcq, oracle, K, factor):
+    """One element of every vector far below or above the levels takes the rounds to the fp64 distances.  Its own decision may hang
+    on the last bit of a scale, the vector's error may not: 1e-6 of it is far above what one such element can change."""
+    for q in (2, 3, 4):
+        W = synth.weights(1, "out", 6, K, extra=K + q)
+        W[:, K - 5] = np.where(W[:, K - 5] == 0, 0.01, W[:, K - 5]) * np.float32(factor)
+        alpha, packed, _ = bcq.bcq_quantize_alternating(to_dev(W), q, iters=15)
+        a = alpha.cpu().numpy().reshape(q, 6, 1).astype(np.float64)
+        b = oracle.unpack(packed_to_host(packed), K).reshape(q, 6, K)
+        a_ref, b_ref = oracle.quantize_alternating(W, q, iters=15)[:2]
+        w64 = W.astype(np.float64)
+        e_gpu = ((w64 - (a * b).sum(0)) ** 2).sum(1)
+        e_ref = ((w64 - (a_ref.reshape(q, 6, 1).astype(np.float64) * b_ref.reshape(q, 6, K)).sum(0)) ** 2).sum(1)
+        assert (e_gpu <= (1.0 + 1e-6) * e_ref).all() and (e_ref <= (1.0 + 1e-6) * e_gpu).all(), (e_gpu / e_ref)
+
+
+@pytest.mark.parametrize("K", [1056, 4096, 16384])
+def test_nonfinite_vectors_of_several_waves(bcq, oracle, K):
+    """An infinity in the first wave's elements and a NaN in the last one's: both counted, the other vectors as ever."""
+    import torch
+    for q in (1, 3, 4):
+        W = synth.weights(1, "out", 5, K, extra=q)
+        clean = W.copy()
+        W[1, 3], W[3, K - 1] = np.inf, np.nan
+        ws = torch.zeros((4,), dtype=torch.int32, device="cuda")
+        alpha, packed, _ = bcq.bcq_quantize_alternating(to_dev(W), q, workspace=ws)
+        assert int(ws[0].item()) == 2
+        alpha_c, packed_c, _ = bcq.bcq_quantize_alternating(to_dev(clean), q)
+        keep = [0, 2, 4]
+        assert torch.equal(alpha.reshape(q, 5)[:, keep], alpha_c.reshape(q, 5)[:, keep])
+        assert torch.equal(packed.reshape(q, 5, -1)[:, keep], packed_c.reshape(q, 5, -1)[:, keep])

@@ -80,11 +80,11 @@ def _sampled_layer(bcq, oracle, config, kind, T, q, dtype, outliers=False, full=
 @pytest.mark.parametrize("T,N,K", [
     (4000, 4040, 160),    # forward: 16 x 16 tiles of 256 x 256, ragged in T and N, last K-step beyond K
     (4000, 160, 4032),    # the same for the input gradient (256 x 256 tiles over T x K, contraction N = 160)
-    (2000, 3000, 1056),   # forward: 128 x 128 tiles, ragged in T and N, K / 32 odd
+    (2000, 3000, 1056),   # forward: 256 x 128 tiles, ragged in T and N, K / 32 odd; input gradient: 128 x 128
 ])
 def test_large_tiles_ragged_edges(bcq, oracle, T, N, K):
     """The workloads' shapes are multiples of 256, so the large tiles of the matrix-core kernels see ragged token rows,
-    ragged output columns and a contraction that ends inside a K-step only here.  Sampled outputs (random entries, the
+    ragged output columns and a contraction that ends inside a K-step only here and in test_gpu_tiles.py.  Sampled outputs (random entries, the
     last token rows and the last output columns in full) against the oracle; scale gradient on sampled rows incl. the
     last ones."""
     import torch

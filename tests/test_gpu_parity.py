@@ -195,13 +195,14 @@ def test_small_shapes_ragged(bcq, oracle, dtype, T, N, K, q):
 
 
 @pytest.mark.parametrize("T,N,K,q", [
-    (130, 8448, 256, 2),   # forward: 3 x 66 tiles of 64 x 128 tokens x outputs; input gradient: 64 x 64 tiles
-    (130, 256, 8448, 3),   # the reverse
-    (200, 2560, 2560, 4),  # 64 x 128 tiles in both, ragged last token tile
+    (130, 8448, 256, 2),   # input gradient: 3 x 4 tiles of 64 x 64 tokens x columns over a long contraction
+    (130, 256, 8448, 3),   # input gradient: 3 x 66 tiles of 64 x 128
+    (200, 2560, 2560, 4),  # input gradient: 4 x 40 tiles of 64 x 64, ragged last token tile
     (97, 1000, 4128, 4),   # N % 32 != 0 (no twin), K / 32 not a multiple of 4
 ])
 def test_few_hundred_tokens_small_gemm_tiles(bcq, oracle, T, N, K, q):
-    """At a few hundred tokens the matrix-core path picks 64-token tiles so that the compute units have work."""
+    """At a few hundred tokens the product picks 64-token tiles so that the compute units have work; the forward of these
+    layers takes one kernel."""
     _run_layer(bcq, oracle, 3, "mlp_up", T, N, K, q, "bf16", workspace=True, twin=(N % 32 == 0))
 
 
