@@ -240,7 +240,8 @@ bcq_status bcq_linear_fwd_grouped(const uint32_t* packed, const float* alpha, co
  *   packed [q][N][K/32] in; packed_t [q][K][N/32] in, may be NULL (non-NULL needs N % 32 == 0); alpha [q][N] in;
  *   dy [T][N] `dtype` in; dx [T][K] `dtype` out.
  * Up to 48 tokens the fast path streams the twin and needs BOTH packed_t and the workspace; from 32 tokens on the
- * tiled path needs the workspace only and uses packed_t when given.  Without them a slower path reads `packed`. */
+ * tiled path needs the workspace only and reads packed_t, when given, from five planes on, else `packed`.  Without
+ * them a slower path reads `packed`. */
 bcq_status bcq_linear_bwd_input(const uint32_t* packed, const uint32_t* packed_t, const float* alpha,
                                 const void* dy, int dtype, int64_t T, int64_t N, int64_t K, int q, void* dx,
                                 void* workspace, size_t workspace_bytes, void* stream);

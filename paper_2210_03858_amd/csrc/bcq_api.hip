@@ -68,10 +68,11 @@ bool small_bwd_alpha_ok(int64_t T, bool rowwise, int dtype) { return dtype == BC
 
 // Streaming kernels (need a workspace): row-wise scales, or group-wise scales whose groups are whole 512-column
 // segments (forward, scale gradient); the input gradient takes any group size (one activation set per plane and
-// group, at most kStreamMaxSets of them).  They take one pass over the planes per 16-token tile, and up to the
-// token counts below that is still faster than expanding the weights for the tiled matrix-core kernels, whose few
-// token tiles leave most of the chip idle (measured on 7680 x 2560, 10240 x 2560, 2560 x 10240: forward 17 - 39 us
-// against 41 - 100 us at 32 - 80 tokens, input gradient 33 - 50 us against 43 - 102 us at 32 - 48 tokens).
+// group, at most kStreamMaxSets of them).  They take one pass over the planes per 16-token tile, and the token counts below
+// were the line against expanding the weights for the tiled kernels of that time.  Against the present ones, streaming / other
+// path, us: forward of 7680 x 2560, q = 4, at 17 tokens 16 / 22, at 32 16 / 9 (one kernel), at 80 28 / 15; of 2560 x 10240, q = 1,
+// at 17, 48 and 80 tokens 14 / 26, 16 / 19 and 22 / 25; input gradient at 32 and 48 tokens, q = 4, of 10240 x 2560 39 / 49 and
+// 41 / 49, of 2560 x 10240 31 / 24 and 46 / 24, with q = 1 11 / 21 and 15 / 22: with several planes the lines are late.
 constexpr int64_t kStreamMaxSets = 256;
 constexpr int64_t kStreamFwdMaxTokens = 80;
 constexpr int64_t kStreamDxMaxTokens = 48;
@@ -97,10 +98,10 @@ bool mfma_bwd_alpha_ok(int64_t T, int64_t N, int64_t K, bool rowwise, int dtype)
 }
 
 // Calls that neither the streaming nor the aligned matrix-core kernels take (row counts that are no multiple of 8 or, with
-// few tokens, of 32) have single kernels on the fp64 matrix cores; the padded bf16 forms take two or three launches more
-// and go from where both were measured equal.  Scale gradient (fp64: 16 rows per compute unit against all tokens and
-// columns): 1500 x 1056 at 130 tokens 27 / 27 us, at 333 70 -> 29.  Input gradient: 1500 x 1056 at 200 tokens 32 -> 39,
-// at 333 52 -> 40, 2999 x 3008 at 1000 tokens 115.
+// few tokens, of 32) have single kernels on the fp64 matrix cores; the padded bf16 forms take two or three launches more.
+// fp64 / padded, us: input gradient of 1500 x 1056 at 64 tokens 20 / 28, at 200 30 / 31, at 333 51 / 32, of 2999 x 3008 at
+// 1000 570 / 89.  Scale gradient (fp64: 16 rows per compute unit against all tokens and columns) of 1500 x 1056 at 64 tokens
+// 20 / 13, at 130 33 / 15, at 333 69 / 16: its line, set against a slower kernel, could lie lower.
 bool unaligned_bwd_alpha_ok(int64_t T, int64_t N, int64_t K, bool rowwise, int dtype) {
     return dtype == BCQ_BF16 && (T > 16 || !rowwise) && N % 8 != 0 && T * K * (N > 4096 ? N : 4096) >= ((int64_t)1 << 29);
 }

@@ -4,7 +4,8 @@
 // positive-last-plane values fit the eight bytes that v_perm_b32 selects from (low bytes and high bytes apart).  Selectors for
 // four columns at a time are bits s, s + 8, s + 16, s + 24 of the planes, XNORed with the last plane, whose complement is the
 // sign.  2.6 (q = 3) to 3.2 (q = 4) vector operations per weight instead of about 3 q + 0.5 for signed sums.  The table is the
-// same chain of fp32 sums and one rounding as a signed sum, and negation commutes with both: the same weights bit for bit.
+// same chain of fp32 sums and one rounding as a signed sum, and negation commutes with both: the same weights bit for bit (but
+// for the sign of a zero, which no sum of products keeps).
 #pragma once
 #include "bcq_internal.h"
 

@@ -343,8 +343,9 @@ __global__ __launch_bounds__(256) void pad_act_kernel(const bf16_t* __restrict__
 // so that what a product costs in energy is what bounds the kernel: 6144 x 2048 at 16384 tokens 393 -> 312 us, 2048 x 8192
 // 432 -> 372 us (1.32 and 1.48 PFLOP/s; weights expanded beforehand).
 //
-// Eight or four waves in a WM x WN grid, each TM x TN tiles of 16 x 16: two waves per vector unit hide each other's waits,
-// and a wave keeps within 256 registers (accumulators in the other half of the file would be moved back and forth).  Per
+// Eight or four waves in a WM x WN grid, each TM x TN tiles of 16 x 16: with eight, two waves per vector unit hide each other's
+// waits (the four-wave shapes' LDS admits one workgroup too, so that there one wave stands alone), and a wave keeps within 256
+// registers (accumulators in the other half of the file would be moved back and forth).  Per
 // K-step one barrier: behind it every wave has the step's last fragments in registers, so the step's LDS is requested
 // anew at once, and the first fragments of the next step are read under the MFMAs of the last slice.
 // Nothing branches on the ragged edges: activation rows beyond M, their columns beyond R and column tiles beyond NC come back
