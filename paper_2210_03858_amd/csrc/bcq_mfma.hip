@@ -102,14 +102,19 @@ __global__ __launch_bounds__(256) void expand_fwd_kernel(const uint32_t* __restr
                                                          const float* __restrict__ alpha, int64_t N, int64_t K,
                                                          int64_t g, int q, int64_t R16 /* padded K / 16 */, int columns,
                                                          u32x4* __restrict__ frag) {
-    const uint32_t runs = (uint32_t)((R16 / 2 + 31) / 32), tiles = (uint32_t)((N + 31) / 32);  // runs of 32 words
-    uint32_t item = blockIdx.x;
-    if (columns ? !xcd_item(tiles * runs * 4, item) : item >= tiles * runs * 4) return;
-    const int c = (threadIdx.x & 7) + 8 * (item & 3);
-    const int64_t ct = columns ? (item >> 2) / runs : (item >> 2) % tiles;
+    uint32_t block = blockIdx.x, run = blockIdx.y;  // plain: 8 rows x a run of 32 words (the divisions cost 0.4 us of 5)
+    if (columns) {
+        const uint32_t runs = (uint32_t)((R16 / 2 + 31) / 32);
+        uint32_t item;
+        if (!xcd_item((uint32_t)((N + 31) / 32) * runs * 4, item)) return;
+        run = (item >> 2) % runs;
+        block = (item >> 2) / runs * 4 + (item & 3);
+    }
+    const int c = (threadIdx.x & 7) + 8 * (block & 3);
+    const int64_t ct = block >> 2;
     const int64_t n = ct * 32 + c;
     const int64_t Kw = K / 32;
-    const int64_t w = (int64_t)(columns ? (item >> 2) % runs : (item >> 2) / tiles) * 32 + (threadIdx.x >> 3);
+    const int64_t w = (int64_t)run * 32 + (threadIdx.x >> 3);
     if (w * 2 >= R16) return;
     const bool live = (n < N) && (w < Kw);
     const int64_t G = K / g, grp = live ? (w * 32) / g : 0;  // a packed word lies in one scale group (g % 32 == 0)
@@ -339,9 +344,10 @@ __global__ __launch_bounds__(256) void pad_act_kernel(const bf16_t* __restrict__
 // K-steps ahead, and come back as v_mfma_f32_16x16x32_bf16 operands, one 32-column slice ahead of their use.  Against weight
 // fragments loaded straight into registers (one K-step ahead, twice per workgroup) this takes a third of the vector-memory
 // traffic away and covers the latency of HBM; against v_mfma_f32_32x32x16_bf16 the 16 x 16 x 32 form reads and writes half
-// the accumulator bits per product.  With all compute units busy the chip is at its power limit (1.7 GHz instead of 2.4),
-// so that what a product costs in energy is what bounds the kernel: 6144 x 2048 at 16384 tokens 393 -> 312 us, 2048 x 8192
-// 432 -> 372 us (1.32 and 1.48 PFLOP/s; weights expanded beforehand).
+// the accumulator bits per product.  With all compute units busy the clock falls (1.9 GHz on average at 16384 tokens, 2.5 to
+// 2.7 where tiles are few), so that what a product costs in energy counts as much as its cycles: 6144 x 2048 at 16384 tokens
+// 393 -> 312 us, 2048 x 8192 432 -> 372 us (1.32 and 1.48 PFLOP/s; weights expanded beforehand).  The matrix cores work in 75 %
+// of the busy cycles there; of the LDS cycles 40 % are bank conflicts.
 //
 // Eight or four waves in a WM x WN grid, each TM x TN tiles of 16 x 16: with eight, two waves per vector unit hide each other's
 // waits (the four-wave shapes' LDS admits one workgroup too, so that there one wave stands alone), and a wave keeps within 256
@@ -411,8 +417,8 @@ __global__ __launch_bounds__((64 * GemmCfg<BM, BN>::NW), 2) void gemm_kernel(
         for (int i = 0; i < TM; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // A: one wave instruction fills 1 KiB of LDS = 8 tile rows of 128 bytes; lane l lands in row l / 8, 16-byte slot l % 8
-    // and fetches the chunk that the swizzle assigns to that slot, slot = chunk ^ (r & 7) ^ ((r >> 3) & 1), so that the
-    // fragment reads (one chunk index of 16 consecutive rows) are bank-conflict free without padding.  Each wave has one
+    // and fetches the chunk that the swizzle assigns to that slot, slot = chunk ^ (r & 7) ^ ((r >> 3) & 1), so that one
+    // chunk index of 16 consecutive rows touches every bank once without padding.  Each wave has one
     // buffer descriptor, based at the first of its rows and ending at the end of A; rows advance through the lane offset
     // (below 2^31: lda < 2^24 and at most 64 rows), K-steps through the scalar offset.
     const int64_t wrow0 = m0 + wave * JA * 8;
@@ -701,7 +707,8 @@ hipError_t launch_fwd_mfma(const uint32_t* packed, const float* alpha, const voi
                            int64_t K, int64_t g, int q, void* y, void* workspace, hipStream_t st) {
     const int64_t R16 = round_up(K, RPAD) / 16;
     const GemmPlan pl = gemm_plan(T, N, K);
-    const dim3 grid(xcd_grid((N + 31) / 32 * ((R16 / 2 + 31) / 32) * 4));
+    const int64_t blocks = (N + 31) / 32 * 4, runs = (R16 / 2 + 31) / 32;
+    const dim3 grid = pl.columns() ? dim3(xcd_grid(blocks * runs)) : dim3((unsigned)blocks, (unsigned)runs);
 #define BCQ_EXPAND(Q) \
     BCQ_LAUNCH(expand_fwd_kernel<Q>, grid, dim3(256), 0, st, packed, alpha, N, K, g, q, R16, (int)pl.columns(), (u32x4*)workspace)
     switch (q) {
