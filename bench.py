@@ -274,15 +274,15 @@ def run_large(args, env, config, T, q, steps, warmup, custom=None, context=True,
                        "frac_of_peak": round(fam_flops / (fam_ms[op] * 1e-3) / 1e12 / PEAK_BF16_MFMA_TFLOPS, 4)}
                   for op in ops}
         # Kernel families of a step: gemm_kernel serves the forward and the input gradient (two calls per layer, each with
-        # its short expand kernel), dalpha_kernel the scale gradient (one call per layer, with its transpose and reduce
-        # kernels).  `roofline` is the family with the largest share of the step's time; the slowest single operation
+        # its short expand kernel), dalpha_kernel the scale gradient (one call per layer, with its reduce
+        # kernel).  `roofline` is the family with the largest share of the step's time; the slowest single operation
         # family is reported beside it.
         kern = {"gemm": ("fwd", "bwd_input"), "dalpha": ("bwd_alpha",)}
         kern_ms = {k: sum(fam_ms[o] for o in v) for k, v in kern.items()}
         domk = max(kern_ms, key=lambda k: kern_ms[k])
         slow = max(fam_ms, key=lambda k: fam_ms[k])
-        names = {"gemm": "gemm_kernel (+ expand_fwd_kernel / expand_bwd_kernel)",
-                 "dalpha": "dalpha_kernel (+ transpose_frag_kernel, dalpha_reduce_kernel)"}
+        names = {"gemm": "gemm_kernel (+ expand_fwd_kernel / expand_bwd_rows_kernel)",
+                 "dalpha": "dalpha_kernel (+ dalpha_reduce_kernel)"}
         bound, peak = "mfma", PEAK_BF16_MFMA_TFLOPS
         if dtype != "bf16":
             # fp32 activations take the any-shape fp64 kernels, one product of 2 T N K flops per call: priced against the
@@ -670,7 +670,8 @@ def main():
         "setup_ops": setup_ops,
         "regimes": regimes,
         "targets": {"large_token": ">= 0.50 of the bf16 MFMA peak at >= 2048 tokens", "small_token": ">= 0.70 of the HBM peak "
-                    "at <= 8 tokens", "status": "both open: see roofline.frac of the headline and of the regimes"},
+                    "at <= 8 tokens", "status": "large_token reached on the headline workload, open on the smaller ones; small_token open: see "
+                    "roofline.frac of the headline and of the regimes"},
     }
     print(json.dumps(out))
 
