@@ -31,7 +31,7 @@ __device__ __forceinline__ bool xcd_item(uint32_t total, uint32_t& item) {
 }
 static inline unsigned xcd_grid(int64_t total) { return (unsigned)(8 * ((total + 7) / 8)); }
 
-// Workgroup -> tile mapping.  The tiles (of all copies of the tile grid: token slices, parts of a contraction) are numbered in
+// Workgroup -> tile mapping.  The tiles (of all copies of the tile grid, one per token slice) are numbered in
 // bands of `a` tile rows, down the rows first, and every XCD takes an eighth of that sequence: what it runs at one time is a
 // block of a x (32 / a) tiles, so that its L2 fetches only those rows of the first operand and columns of the second, and the
 // XCDs' shares differ by one tile at most (super-blocks of whole rectangles left 252 tiles in two rounds: 7000 tokens of 1696 x 1696 62 -> 34 us).
