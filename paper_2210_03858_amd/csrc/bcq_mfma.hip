@@ -680,11 +680,13 @@ static GemmPlan gemm_plan(int64_t M, int64_t NC, int64_t R) {
         }
     }
     const int bm = shapes[pl.shape][0], bn = shapes[pl.shape][1];
-    // Bands of all rows: up to 3072 tokens always that an XCD's share has room for them (1024 x 1024, 786 tokens, with 1.36 times
-    // the operand bytes, kept workspace 11.1 -> 9.2 us, in turn 9.4 / 9.3; 3072 x 1024, 2600 tokens, 1.54 times, 30.0 -> 25.9
-    // and 25.2 / 25.4).  At 4096 tokens, with 1.5 times, they still save up to 4 us with a kept workspace, but cost 0.5 to 2.5
-    // with workspaces in turn (3840 x 1280 44.3 -> 41.4, 39.3 -> 40.1; 5120 x 1280 60 / 60, 57.5 -> 60.3).
-    const double whole = M <= 3072 ? 2.5 : 1.4;
+    // Bands of all rows: up to 2048 tokens always that an XCD's share has room for them (1024 x 1024, 786 tokens, with 1.36 times
+    // the operand bytes, kept workspace 11.1 -> 9.2 us, in turn 9.4 / 9.3), up to 3072 for up to 3.5 million weights with more
+    // columns than contraction (forward of 3072 x 1024, 2600 tokens, 1.54 times, kept 28.6 -> 25.0, in turn 24.5 / 24.3).  Beyond that
+    // they still save 1 to 4 us with a kept workspace, but cost as much with workspaces in turn, as in training (input gradient of
+    // 2016 x 2016, 2477 tokens, kept 33.9 -> 31.1, in turn 29.8 -> 31.1; forward of 1024 x 3072, 2600 tokens, 30.4 -> 29.3, 27.2 ->
+    // 29.1; input gradient of 7680 x 2560, 2300 tokens, 92.9 -> 96.3, 92.3 -> 93.7; 3840 x 1280, 4096 tokens, 44.3 -> 41.4, 39.3 -> 40.1).
+    const double whole = M <= 2048 || (M <= 3072 && NC * R <= 3500000 && NC > R) ? 2.5 : 1.4;
     pl.wgs = make_tile_map((int)((M + bm - 1) / bm), (int)((NC + bn - 1) / bn), 1, (double)bm, (double)bn, whole, &pl.map);
     return pl;
 }
