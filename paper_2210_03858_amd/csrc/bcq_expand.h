@@ -25,6 +25,15 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 }
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
+// Consecutive workgroup ids go round-robin over the 8 XCDs, each with its own L2: of `total` items every XCD takes an eighth
+// in a row.
+__device__ __forceinline__ bool xcd_item(uint32_t total, uint32_t& item) {
+    const uint32_t xcd = blockIdx.x & 7;
+    item = (uint32_t)((uint64_t)total * xcd >> 3) + (blockIdx.x >> 3);
+    return item < (uint32_t)((uint64_t)total * (xcd + 1) >> 3);  // the eighths differ by one item
+}
+static inline unsigned xcd_grid(int64_t total) { return (unsigned)(8 * ((total + 7) / 8)); }
+
 // The positive-last-plane weights of one row and scale group: bit i of the index = plane i is +1, i < Q - 1.
 template <int Q>
 struct LevelTable {

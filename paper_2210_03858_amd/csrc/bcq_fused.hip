@@ -1,52 +1,33 @@
 // Forward of the BCQ linear layer for a few hundred tokens at most, in one kernel (bf16 in, fp32 accumulate, q <= 4).
 //
 // AlphaTuning Eq. 2 as one contraction with What = sum_i alpha_i B_i rounded once to bf16 (Eq. 1), like the two-kernel
-// path of bcq_mfma.hip, but What never reaches memory: every wave expands the sign planes of its 32 rows straight into
-// the registers of v_mfma_f32_32x32x16_bf16 and multiplies them with all the tokens of its tile.  At these token counts
-// the two-kernel path is bound by writing and re-reading 16 bits per weight, here a weight costs q bits.
+// path of bcq_mfma.hip, but What never reaches memory: every wave expands the sign planes of its rows straight into
+// the registers of the matrix instructions (by table, bcq_expand.h).  At these token counts the two-kernel path is bound by
+// writing and re-reading 16 bits per weight, here a weight costs q bits.
 //
-// Expansion by table (bcq_expand.h): from 64 tokens on the matrix instructions take longer than it.
-//
-// Split: a workgroup owns 32 rows x 32 TT tokens; its W waves take runs of 128 columns in turn and add their tiles
-// through LDS in wave order (deterministic).  Up to 32 tokens are read from their rows; more are first rewritten in
-// operand order, because a wave's 16-byte pieces of 32 rows would touch 32 cache lines per load (256 tokens of
-// 10240 x 2560: 80 us from the rows, 41 us in order).  What bounds it: up to 32 tokens the planes' scattered rows and launch
-// latency (6144 x 2048, groups of 128, 4 tokens: 26 -> 9 us against two kernels), above that the activation fragments,
-// which every 32 rows read again from L2 through the vector memory path.
+// Two forms: fused_fwd_kernel up to 32 tokens (32 rows to a workgroup, its waves share the contraction), tile_fwd_kernel above.
+#include <type_traits>
+
 #include "bcq_expand.h"
 
 namespace bcq {
 
 typedef __attribute__((ext_vector_type(16))) float fu_f32x16;
 
-// Activations -> the order the matrix instruction reads them in: for every 32-token tile, 32-column word and half slice
-// one contiguous KiB, lane (t, h) holding columns 16 h + 8 sub .. + 7 of the word.  Tokens beyond T become zeros.
-// A wave takes 8 tokens x 128 bytes: whole lines in, 128-byte runs out.
-__global__ __launch_bounds__(256) void order_act_kernel(const bf16_t* __restrict__ x, int64_t T, int64_t K,
-                                                        u32x4* __restrict__ xfrag) {
-    const int lane = threadIdx.x & 63;
-    const int64_t Kw = K / 32, pairs = (Kw + 1) / 2;
-    const int64_t job = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // (eight tokens, two words)
-    const int64_t t = (job / pairs) * 8 + (lane & 7), w = (job % pairs) * 2 + (lane >> 5);
-    const int chunk = (lane >> 3) & 3;
-    if (w >= Kw || t >= (T + 31) / 32 * 32) return;
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (t < T) v = *reinterpret_cast<const u32x4*>(x + t * K + 32 * w + 8 * chunk);
-    xfrag[(((t / 32) * Kw + w) * 2 + (chunk & 1)) * 64 + (t % 32) + 32 * (chunk >> 1)] = v;
-}
-
-// GROUPED: group-wise scales (the table follows the group); else one table per row.
-// ORDERED: x is the output of order_act_kernel; else row-major.
-template <int Q, int TT, int W, bool GROUPED, bool ORDERED>
-__global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __restrict__ packed,
-                                                           const float* __restrict__ alpha, const bf16_t* __restrict__ x,
-                                                           bf16_t* __restrict__ y, int64_t T, int64_t N, int64_t K,
-                                                           int64_t g, int per, float* __restrict__ sums) {
-    __shared__ f32x4 part[2][W][4][64];
+// Up to 32 tokens.  A workgroup owns 32 rows; its eight waves take runs of 128 columns in turn and add their tiles through LDS
+// in wave order (deterministic).  What bounds it: the planes' scattered rows and launch latency (6144 x 2048, groups of 128,
+// 4 tokens: 26 -> 9 us against two kernels).
+template <int Q>
+__global__ __launch_bounds__(512) void fused_fwd_kernel(const uint32_t* __restrict__ packed,
+                                                        const float* __restrict__ alpha, const bf16_t* __restrict__ x,
+                                                        bf16_t* __restrict__ y, int64_t T, int64_t N, int64_t K,
+                                                        int64_t g, int per, float* __restrict__ sums) {
+    constexpr int W = 8;
+    __shared__ f32x4 part[W][4][64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 31, h = lane >> 5;
-    const int64_t n0 = (int64_t)blockIdx.x * 32, t0 = (int64_t)blockIdx.y * (32 * TT);
+    const int64_t n0 = (int64_t)blockIdx.x * 32, t0 = (int64_t)blockIdx.y * 32;
     const int64_t n = n0 + col < N ? n0 + col : N - 1;  // rows and tokens beyond the edge are computed, never stored
     const int Kw = (int)(K / 32), G = (int)(K / g), gw = (int)(g / 32);
     // this workgroup's units of 128 columns: part blockIdx.z of `per` each (all of them when the contraction is not split)
@@ -61,90 +42,68 @@ __global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __res
         arow[i] = alpha + ((int64_t)i * N + n) * G;
     }
     // of a 32-column word, lane half h contracts over columns 16 h .. 16 h + 15
-    const bf16_t* xrow[TT];
+    const bf16_t* const xrow = x + (t0 + col < T ? t0 + col : T - 1) * K + 16 * h;
+    fu_f32x16 acc;
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        if (ORDERED) {
-            const int64_t tile = t0 / 32 + tt, tiles = (T + 31) / 32;
-            xrow[tt] = x + (tile < tiles ? tile : tiles - 1) * K * 32 + lane * 8;
-        } else {
-            const int64_t t = t0 + tt * 32 + col;
-            xrow[tt] = x + (t < T ? t : T - 1) * K + 16 * h;
-        }
-    }
-    fu_f32x16 acc[TT];
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[tt][v] = 0.f;
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 
-    // In flight per wave: the planes (and scales of group-wise calls) D units ahead, the activations XW words ahead.
-    // One token tile: one unit, so that four waves fit a SIMD (two units ahead: 8.7 -> 12 us for 6144 x 2048 at 4 tokens).
-    constexpr int D = TT == 1 ? 1 : 2, XW = TT == 2 ? 4 : 2;
-    uint32_t bits[D][Q][4];
-    float a[D][2][Q];  // [unit][pair of words]
-    auto load_bits = [&](int u, int buf) {
+    // In flight per wave: the planes (and scales of group-wise calls) one unit ahead, so that four waves fit a SIMD (two units
+    // ahead: 8.7 -> 12 us for 6144 x 2048 at 4 tokens), the activations two words ahead.
+    uint32_t bits[Q][4];
+    float a[2][Q];  // [pair of words]
+    auto load_bits = [&](int u) {
         if (4 * u + 4 <= Kw) {
 #pragma unroll
-            for (int i = 0; i < Q; ++i) __builtin_memcpy(bits[buf][i], prow[i] + 4 * u, 16);
+            for (int i = 0; i < Q; ++i) __builtin_memcpy(bits[i], prow[i] + 4 * u, 16);
         } else {
 #pragma unroll
             for (int i = 0; i < Q; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) bits[buf][i][j] = 4 * u + j < Kw ? prow[i][4 * u + j] : 0u;
+                for (int j = 0; j < 4; ++j) bits[i][j] = 4 * u + j < Kw ? prow[i][4 * u + j] : 0u;
         }
     };
     auto load_alpha = [&](int w, float (&dst)[Q]) {
-        const int grp = GROUPED ? (w < Kw ? w : Kw - 1) / gw : 0;
+        const int grp = (w < Kw ? w : Kw - 1) / gw;
 #pragma unroll
         for (int i = 0; i < Q; ++i) dst[i] = arow[i][grp];
     };
-    auto load_unit = [&](int u, int buf) {
-        load_bits(u, buf);
-        if (GROUPED) {
-            load_alpha(4 * u, a[buf][0]);
-            load_alpha(4 * u + 2, a[buf][1]);
-        }
+    auto load_unit = [&](int u) {
+        load_bits(u);
+        load_alpha(4 * u, a[0]);
+        load_alpha(4 * u + 2, a[1]);
     };
-    u32x4 xf[XW][2][TT];  // [word][slice][token tile]
+    u32x4 xf[2][2];  // [word][slice]
     const u32x4 zero = {0u, 0u, 0u, 0u};
     auto load_x = [&](int w, int slot) {  // words beyond K contribute nothing
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-            for (int tt = 0; tt < TT; ++tt)
-                xf[slot][sub][tt] = w < Kw ? *reinterpret_cast<const u32x4*>(
-                                                 xrow[tt] + (ORDERED ? (2 * w + sub) * 512 : 32 * w + 8 * sub)) : zero;
+            xf[slot][sub] = w < Kw ? *reinterpret_cast<const u32x4*>(xrow + 32 * w + 8 * sub) : zero;
     };
-    LevelTable<Q> table;
     // the two words of a pair may lie in two groups (g = 32): then the table is rebuilt between them
-    const bool split = GROUPED && (gw & 1);
+    const bool split = (gw & 1) != 0;
     const uint32_t half_sel = h ? 0x07060302u : 0x05040100u;
 
     auto clamp_unit = [&](int u) { return u < units ? u : units - 1; };
-    load_unit(clamp_unit(first), 0);
-    if (!GROUPED) load_alpha(0, a[0][0]);
+    load_unit(clamp_unit(first));
 #pragma unroll
-    for (int j = 0; j < XW; ++j) load_x(4 * clamp_unit(first) + j, j);
-    if (D == 2) load_unit(clamp_unit(first + W), D - 1);
-    if (!GROUPED) table.build(a[0][0]);
+    for (int j = 0; j < 2; ++j) load_x(4 * clamp_unit(first) + j, j);
 
-    auto unit = [&](int u, int buf) {
+    for (int u = first; u < units; u += W) {
         uint32_t own[2][Q];  // this lane half's 2 x 16 signs of each pair of words
         LevelTable<Q> tables[2];
 #pragma unroll
         for (int pr = 0; pr < 2; ++pr) {
 #pragma unroll
             for (int i = 0; i < Q; ++i)
-                own[pr][i] = __builtin_amdgcn_perm(bits[buf][i][2 * pr + 1], bits[buf][i][2 * pr], half_sel);
-            if (GROUPED) tables[pr].build(a[buf][pr]);
+                own[pr][i] = __builtin_amdgcn_perm(bits[i][2 * pr + 1], bits[i][2 * pr], half_sel);
+            tables[pr].build(a[pr]);
         }
-        load_unit(clamp_unit(u + D * W), buf);
+        load_unit(clamp_unit(u + W));
 #pragma unroll
         for (int pr = 0; pr < 2; ++pr) {
             if (4 * u + 2 * pr < Kw) {
                 u32x4 frag[4];
-                expand32<Q>(own[pr], GROUPED ? tables[pr] : table, frag);
+                expand32<Q>(own[pr], tables[pr], frag);
                 if (split) {
                     u32x4 second[4];
                     float as[Q];
@@ -153,67 +112,398 @@ __global__ __launch_bounds__(64 * W) void fused_fwd_kernel(const uint32_t* __res
 #pragma unroll
                         for (int i = 0; i < Q; ++i) as[i] = 0.f;
                     }
+                    LevelTable<Q> table;
                     table.build(as);
                     expand32<Q>(own[pr], table, second);
                     frag[2] = second[2];
                     frag[3] = second[3];
                 }
-                if (!GROUPED && 4 * u + 2 * pr + 1 >= Kw) {  // the same for row-wise scales
-                    frag[2] = zero;
-                    frag[3] = zero;
-                }
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
-                    constexpr int MASK = XW - 1;
-                    const int slot = (2 * pr + j) & MASK;
 #pragma unroll
                     for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-                        for (int tt = 0; tt < TT; ++tt)
-                            acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                __builtin_bit_cast(bf16x8, frag[2 * j + sub]),
-                                __builtin_bit_cast(bf16x8, xf[slot][sub][tt]), acc[tt], 0, 0, 0);
-                    if (XW == 2 && pr == 0)
-                        load_x(4 * u + 2 + j, slot);
-                    else
-                        load_x(4 * clamp_unit(u + W) + 2 * pr + j - (XW == 2 ? 2 : 0), slot);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, frag[2 * j + sub]),
+                                                                      __builtin_bit_cast(bf16x8, xf[j][sub]), acc, 0, 0, 0);
+                    load_x(pr == 0 ? 4 * u + 2 + j : 4 * clamp_unit(u + W) + j, j);
                 }
             }
         }
-    };
-    for (int u = first; u < units; u += D * W) {
-        unit(u, 0);
-        if (D == 2 && u + W < units) unit(u + W, D - 1);
     }
 
     // accumulator register 4 gg + e of lane l: row n0 + 8 gg + 4 (l / 32) + e, token l % 32
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
+    for (int gg = 0; gg < 4; ++gg) part[wave][gg][lane] = f32x4{acc[4 * gg], acc[4 * gg + 1], acc[4 * gg + 2], acc[4 * gg + 3]};
+    __syncthreads();
+    if (threadIdx.x >= 256) return;
+    const int gg = threadIdx.x >> 6;
+    f32x4 s = part[0][gg][lane];
 #pragma unroll
-        for (int gg = 0; gg < 4; ++gg)
-            part[tt & 1][wave][gg][lane] = f32x4{acc[tt][4 * gg], acc[tt][4 * gg + 1], acc[tt][4 * gg + 2], acc[tt][4 * gg + 3]};
-        __syncthreads();  // two buffers: the sums of tile tt are read while tile tt + 1 is written
-        if (threadIdx.x < 256) {
-            const int gg = threadIdx.x >> 6;
-            f32x4 s = part[tt & 1][0][gg][lane];
+    for (int w = 1; w < W; ++w) s += part[w][gg][lane];
+    const int64_t t = t0 + col, nn = n0 + 8 * gg + 4 * h;
+    if (t >= T) return;
+    if (sums) {  // split contraction: sum_parts_kernel adds the parts
+        if (nn < N) *reinterpret_cast<f32x4*>(sums + ((int64_t)blockIdx.z * T + t) * ((N + 3) / 4 * 4) + nn) = s;
+        return;
+    }
+    bf16_t* dst = y + t * N + nn;
+    if (nn + 3 < N && (N & 3) == 0) {
+        *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3]));
+    } else {
 #pragma unroll
-            for (int w = 1; w < W; ++w) s += part[tt & 1][w][gg][lane];
-            const int64_t t = t0 + tt * 32 + col, nn = n0 + 8 * gg + 4 * h;
-            if (sums) {  // split contraction: sum_parts_kernel adds the parts
-                if (t < T && nn < N)
-                    *reinterpret_cast<f32x4*>(sums + ((int64_t)blockIdx.z * T + t) * ((N + 3) / 4 * 4) + nn) = s;
-            } else if (t < T) {
-                bf16_t* dst = y + t * N + nn;
-                if (nn + 3 < N && (N & 3) == 0) {
-                    *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3]));
-                } else {
+        for (int e = 0; e < 4; ++e)
+            if (nn + e < N) dst[e] = f32_to_bf16(s[e]);
+    }
+}
+
+// ---- 33 tokens and more ---------------------------------------------------------------------------------------------
+// 4 x 4 transposition of words over the four rows of 16 lanes: lane row h, word u  <->  lane row u, word h
+__device__ __forceinline__ void transpose_rows(uint32_t (&w)[4]) {
+    const auto a = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+    const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+    const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+    w[0] = c[0];
+    w[1] = c[1];
+    w[2] = d[0];
+    w[3] = d[1];
+}
+
+// expand32 in steps of eight columns of each byte pair, so that they can stand between matrix instructions
+template <int Q>
+struct Expansion {
+    uint32_t neg, even, odd, c[Q > 1 ? Q - 1 : 1];
+    __device__ __forceinline__ void begin(const uint32_t (&w)[Q]) {
+        neg = ~w[Q - 1];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (nn + e < N) dst[e] = f32_to_bf16(s[e]);
+        for (int i = 0; i + 1 < Q; ++i) c[i] = w[i] ^ neg;
+        even = odd = 0u;  // two-bit codes of the even and the odd columns
+        if constexpr (Q >= 3) {
+            even = (c[0] & 0x55555555u) | ((c[1] & 0x55555555u) << 1);
+            odd = ((c[0] >> 1) & 0x55555555u) | (c[1] & 0xAAAAAAAAu);
+        }
+    }
+    // register p of all four fragments (columns 2 p and 2 p + 1 of each byte)
+    __device__ __forceinline__ void step(int p, const LevelTable<Q>& t, uint32_t (&frag)[4][4]) const {
+        uint32_t ab[2], cd[2];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            const int s = 2 * p + o;
+            uint32_t sel = 0u;
+            if constexpr (Q == 2) sel = (c[0] >> s) & 0x01010101u;
+            if constexpr (Q >= 3) sel = ((o ? odd : even) >> (s & 6)) & 0x03030303u;
+            if constexpr (Q == 4) sel |= (s >= 2 ? c[2] >> (s - 2) : c[2] << (2 - s)) & 0x04040404u;
+            const uint32_t l = __builtin_amdgcn_perm(t.lo[1], t.lo[0], sel);
+            const uint32_t h = __builtin_amdgcn_perm(t.hi[1], t.hi[0], sel) ^ ((neg << (7 - s)) & 0x80808080u);
+            ab[o] = __builtin_amdgcn_perm(h, l, 0x05010400u);
+            cd[o] = __builtin_amdgcn_perm(h, l, 0x07030602u);
+        }
+        frag[0][p] = __builtin_amdgcn_perm(ab[1], ab[0], 0x05040100u);
+        frag[1][p] = __builtin_amdgcn_perm(ab[1], ab[0], 0x07060302u);
+        frag[2][p] = __builtin_amdgcn_perm(cd[1], cd[0], 0x05040100u);
+        frag[3][p] = __builtin_amdgcn_perm(cd[1], cd[0], 0x07060302u);
+    }
+};
+
+constexpr int tile_wait(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }  // s_waitcnt vmcnt(n)
+
+template <int TM, int KG>
+constexpr int tile_stages() { return TM * KG <= 4 ? 3 : TM * KG <= 8 ? 4 : 2; }
+template <int TM, int KG>
+constexpr int tile_lds_bytes() { return KG * tile_stages<TM, KG>() * TM * 16 * 256; }
+
+// A workgroup owns 64 TN rows x 16 TM tokens; its waves are four rows of 16 TN rows each, times KG parts of the contraction whose
+// sums meet in LDS.  The activations of a unit of 128 columns go global -> LDS directly, NS - 1 units ahead, and come back as
+// v_mfma_f32_16x16x32_bf16 operands; each wave expands the weights of the next unit between the matrix instructions of this one.
+// A wave reads 16 bytes of a row and plane at a time, four lanes to a 64-byte piece, and a 4 x 4 transposition over the rows of
+// lanes hands every lane the one word of each unit whose 32 columns it contracts over: slice f of a unit is columns
+// 32 h + 8 f .. + 7 of lane row h on both sides.
+//
+// What bounds it: vector operations.  Expanding costs 22 (q = 1) to 110 (q = 4) of them per 32 weights, 4 cycles each, repeated for
+// every 16 TM tokens, and beside a 16-cycle matrix instruction only two are free (7.2 ns alone and with two, 10.5 with four, 17 with
+// eight).  Against activations re-ordered in memory and read from L2 by every 32 rows (us, with that kernel's re-ordering): 256 tokens,
+// q = 4, of 7680 x 2560 27 -> 22, 2560 x 10240 44 -> 34, 10240 x 2560 35 -> 33; 149 tokens of 2560 x 10240, q = 1, 38 -> 21; groups
+// of 32: 72 tokens of 8192 x 2048, q = 3, 26 -> 16.  Of 168 random calls up to 384 tokens the median is 0.84 of the time, 14 are more
+// than 4 % slower (worst 1.17: 320 tokens of 1632 x 5056, q = 4, 22 -> 26).
+//
+// Shapes (TM, TN, KG): (4, 1, 1), of which a compute unit holds three by their LDS and hides one's waits behind another's, and
+// (8, 1, 2), which expands half as often.  128 rows to a workgroup (TN = 2), 128 or 256 tokens without the parts, and more stages
+// for one workgroup less were slower or no more than 2 % faster over 74 shapes.
+template <int Q, int TM, int KG, bool GROUPED>
+__global__ __launch_bounds__(256 * KG, KG) void tile_fwd_kernel(const uint32_t* __restrict__ packed, const float* __restrict__ alpha,
+                                                          const bf16_t* __restrict__ x, bf16_t* __restrict__ y, int64_t T,
+                                                          int64_t N, int64_t K, int64_t g, int per, int token_tiles, int parts,
+                                                          int items, float* __restrict__ sums) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the buffer-resource builtins exist in the device pass only
+    constexpr int TN = 1, BM = 16 * TM, STAGE = BM * 256, NS = tile_stages<TM, KG>(), KD = BM / 16;  // KD: requests per wave and stage
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int lane = threadIdx.x & 63, r = lane & 15, h = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kg = wave >> 2, wr = wave & 3;
+    uint32_t item;
+    if (!xcd_item((uint32_t)items, item)) return;
+    // (divisions are done by the vector ALU: without readfirstlane the compiler takes everything after them for lane values)
+    const int rest = __builtin_amdgcn_readfirstlane((int)(item / (uint32_t)token_tiles));
+    const int row_tile = __builtin_amdgcn_readfirstlane((int)((uint32_t)rest / (uint32_t)parts)), part = rest - row_tile * parts;
+    const int64_t t0 = (int64_t)((int)item - rest * token_tiles) * BM;
+    const int64_t n0 = (int64_t)row_tile * (64 * TN) + wr * (16 * TN);
+    const int Kw = (int)(K / 32), G = (int)(K / g), gw = (int)(g / 32);
+    const int units = (Kw + 3) / 4, first = (part * KG + kg) * per;  // this wave's units of 128 columns: first .. first + per - 1
+
+    // rows and tokens beyond the edge are computed, never stored; addresses are a uniform base and a 32-bit lane offset
+    const int64_t nb = n0 < N ? n0 : N - 1;
+    uint32_t roff[TN], aoff[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int64_t left = N - 1 - nb, row = 16 * j + r;
+        roff[j] = (uint32_t)((row < left ? row : left) * Kw);
+        aoff[j] = (uint32_t)((row < left ? row : left) * G);
+    }
+    const uint32_t* const prow = packed + nb * Kw;
+    const float* const arow = alpha + nb * G;
+    const int64_t plane = N * Kw, splane = N * G;
+
+    // Activations: unit -> LDS as rows of 256 bytes, chunk (h, f) = columns 32 h + 8 f .. + 7 at 16-byte slot (h + 4 f) ^ (token & 15):
+    // the fragment reads below then touch every bank once.
+    __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)x, 0, (int)(T * K * 2), 0x00020000);
+    uint32_t voff[KD];
+    const int row4 = 4 * wr + h, code = r ^ row4;  // token of the request modulo 16; its chunk
+    const int ccol = 32 * (code & 3) + 8 * (code >> 2);
+#pragma unroll
+    for (int k = 0; k < KD; ++k) {
+        const int64_t t = t0 + 16 * k + row4;
+        voff[k] = (uint32_t)((t < T ? t : T - 1) * K * 2 + 2 * ccol);
+    }
+    const uint32_t tail = (int64_t)(units - 1) * 128 + ccol < K ? 0u : 0x80000000u;  // beyond the descriptor: zeros
+    auto dma = [&](int v, int slot) {  // (requests beyond this wave's units go nowhere: the waits count them)
+        const int u = first + v;
+        const uint32_t off = u >= units || v >= per ? 0x80000000u : u == units - 1 ? tail : 0u;
+        const int soff = __builtin_amdgcn_readfirstlane(u < units ? u * 256 : 0);
+#pragma unroll
+        for (int k = 0; k < KD; ++k)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rx, (void __attribute__((address_space(3)))*)(smem + (kg * NS + slot) * STAGE + (4 * k + wr) * 1024), 16,
+                voff[k] + off, soff, 0, 0);
+    };
+    // signs: lane row h reads words 4 h .. + 3 of 16, and keeps word h of each unit after the transposition
+    uint32_t bits[TN][Q][4];
+    const bool quad = (Kw & 3) == 0;
+    auto load_bits = [&](int v) {
+        const int w0 = 4 * (first + v) + 4 * h;  // words beyond K meet zero weights
+        if (quad) {
+            const uint32_t w = (uint32_t)(w0 < Kw ? w0 : Kw - 4);
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int i = 0; i < Q; ++i) __builtin_memcpy(bits[j][i], prow + i * plane + (roff[j] + w), 16);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t w = (uint32_t)(w0 + e < Kw ? w0 + e : Kw - 1);
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int i = 0; i < Q; ++i) bits[j][i][e] = prow[i * plane + (roff[j] + w)];
+            }
+        }
+    };
+    float a[TN][Q];
+    auto load_alpha = [&](int v) {
+        const int w = 4 * (first + v) + h, grp = GROUPED ? (w < Kw ? w : Kw - 1) / gw : 0;
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int i = 0; i < Q; ++i) a[j][i] = arow[i * splane + (aoff[j] + (uint32_t)grp)];
+    };
+    LevelTable<Q> table[TN];
+    auto tables = [&](int v) {  // of unit v; words beyond K have zero weights, as Inf times a zero activation is NaN
+        if (GROUPED) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) table[j].build(a[j]);
+        }
+        if (4 * (first + v) + 4 > Kw) {  // (and so have all units from here on)
+            const uint32_t live = 4 * (first + v) + h < Kw ? ~0u : 0u;
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    table[j].lo[e] &= live;
+                    table[j].hi[e] &= live;
                 }
+        }
+    };
+
+    f32x4 acc[TN][TM];
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    uint32_t frag[2][TN][4][4];  // [buffer][row tile][slice][register]
+    u32x4 xf[2][4];
+    uint32_t xoff[4];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) xoff[f] = (uint32_t)(kg * NS * STAGE + r * 256 + (((h + 4 * f) ^ r) * 16));
+    auto read_x = [&](int slot, int grp) {  // group of four token tiles of a slice: slice grp / (TM / 4)
+        const int f = grp / (TM / 4), i0 = grp % (TM / 4) * 4;
+        const uint32_t addr = xoff[f] + (uint32_t)(slot * STAGE);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(xf[grp & 1][i]) : "v"(addr), "n"((i0 + i) * 4096));
+    };
+    auto arrived = [&](int p) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(xf[p][i]));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    Expansion<Q> ex[TN];
+    uint32_t pair[TN][Q][2];  // the words of an even unit and the one after it
+    auto take = [&](int at) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int i = 0; i < Q; ++i)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) pair[j][i][e] = bits[j][i][at + e];
+    };
+    auto turn = [&] {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int i = 0; i < Q; ++i) transpose_rows(bits[j][i]);
+    };
+    auto begin = [&](int e) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            uint32_t w[Q];
+#pragma unroll
+            for (int i = 0; i < Q; ++i) w[i] = pair[j][i][e];
+            ex[j].begin(w);
+        }
+    };
+    auto handover = [&] {
+        asm volatile("s_waitcnt %0" ::"n"(tile_wait((NS - 2) * KD)) : "memory");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto keep_frag = [&](int b, int j, int p) {  // computed here, not moved behind a branch to where it is used
+#pragma unroll
+        for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(frag[b][j][e][p]));
+    };
+    // Unit v: multiply with its weights (buffer `cur`) while those of unit v + 1 are expanded between the matrix instructions.
+    auto unit = [&](int slot, auto CUR) {
+        constexpr int cur = decltype(CUR)::value, nxt = 1 - cur;
+        constexpr int NGRP = TM, NP = 4 * TN;
+#pragma unroll
+        for (int grp = 0; grp < NGRP; ++grp) {
+            arrived(grp & 1);
+            if (grp + 1 < NGRP) read_x(slot, grp + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            const int f = grp / (TM / 4), i0 = grp % (TM / 4) * 4;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[j][i0 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        as_bf16x8(u32x4{frag[cur][j][f][0], frag[cur][j][f][1], frag[cur][j][f][2], frag[cur][j][f][3]}),
+                        as_bf16x8(xf[grp & 1][i]), acc[j][i0 + i], 0, 0, 0);
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+                if (p * NGRP / NP == grp) {
+                    ex[p / 4].step(p % 4, table[p / 4], frag[nxt][p / 4]);
+                    keep_frag(nxt, p / 4, p % 4);
+                }
+#pragma unroll
+            for (int m = 0; m < 4 * TN; ++m) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x2, 4, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        handover();
+    };
+
+#pragma unroll
+    for (int v = 0; v < NS - 1; ++v) dma(v, v);
+    load_bits(0);
+    load_alpha(0);
+    if (!GROUPED) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) table[j].build(a[j]);
+    }
+    turn();
+    take(0);
+    tables(0);
+    if (GROUPED) load_alpha(1);
+    begin(0);
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int p = 0; p < 4; ++p) ex[j].step(p, table[j], frag[0][j]);
+    handover();
+    auto after = [](int slot) { return slot + 1 == NS ? 0 : slot + 1; };
+    int s0 = 0, s1 = after(0), last = NS - 1;  // stages of units v, v + 1, v - 1
+    for (int v = 0; v < per; v += 2) {
+        read_x(s0, 0);
+        dma(v + NS - 1, last);
+        if (v & 2) load_bits(v + 2);
+        tables(v + 1);
+        if (GROUPED) load_alpha(v + 2);
+        begin(1);
+        unit(s0, std::integral_constant<int, 0>{});
+        read_x(s1, 0);
+        dma(v + NS, s0);
+        if (v & 2) {
+            turn();
+            take(0);
+        } else {
+            take(2);
+        }
+        tables(v + 2);
+        if (GROUPED) load_alpha(v + 3);
+        begin(0);
+        unit(s1, std::integral_constant<int, 1>{});
+        last = s1;
+        s0 = after(s1);
+        s1 = after(s0);
+    }
+
+    // The two halves of the contraction: each keeps half of the token tiles and hands its sums of the others over.
+    constexpr int TE = TM / KG;
+    asm volatile("s_waitcnt %0" ::"n"(tile_wait(0)) : "memory");
+    if (KG == 2) __syncthreads();
+    f32x4* const swap = reinterpret_cast<f32x4*>(smem) + lane;
+    auto at = [&](int half, int i, int j) { return ((half * 4 + wr) * TE + i) * TN + j; };
+    if constexpr (KG == 2) {
+#pragma unroll
+        for (int i = 0; i < TE; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) swap[at(kg, i, j) * 64] = kg ? acc[j][i] : acc[j][TE + i];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < TE; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[j][i] = (kg ? acc[j][TE + i] : acc[j][i]) + swap[at(1 - kg, i, j) * 64];
+    }
+    const bool vec = (N & 3) == 0;
+#pragma unroll
+    for (int i = 0; i < TE; ++i) {
+        const int64_t t = t0 + 16 * (kg * TE + i) + r;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const f32x4 s = acc[j][i];
+            const int64_t n = n0 + 16 * j + 4 * h;
+            if (t >= T || n >= N) continue;
+            if (sums) {  // split contraction: sum_parts_kernel adds the parts
+                *reinterpret_cast<f32x4*>(sums + ((int64_t)part * T + t) * ((N + 3) / 4 * 4) + n) = s;
+            } else if (vec) {
+                *reinterpret_cast<uint2*>(y + t * N + n) = make_uint2(pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3]));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < N) y[t * N + n + e] = f32_to_bf16(s[e]);
             }
         }
     }
+#endif
 }
 
 // y[t][n] = sum of the parts, in order; a thread adds four rows n of one token
@@ -235,9 +525,6 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(const float* __restrict_
     }
 }
 
-static size_t order_bytes(int64_t T, int64_t K) { return T <= 32 ? 0 : (size_t)((T + 31) / 32 * 32 * K * 2); }
-static size_t sums_bytes(int64_t T, int64_t N, int parts) { return (size_t)parts * T * ((N + 3) / 4 * 4) * 4; }
-
 // 128 tokens per workgroup read and expand every plane half as often, 64 make twice as many workgroups: measured
 // (256 tokens, q = 4) 7680 x 2560 27 against 31 us, 10240 x 2560 35 / 38, 2560 x 2560 17 / 17, 1024 x 1024 10 / 8, and
 // with the contraction split 2560 x 10240 48 / 53.
@@ -246,85 +533,116 @@ static bool wide_tokens(int64_t T, int64_t N, int64_t K) {
     return T > 64 && (tiles >= 256 || (tiles >= 64 && units >= 64));
 }
 
-template <int Q, bool GROUPED>
-static hipError_t launch_q(const uint32_t* packed, const float* alpha, const bf16_t* x, int64_t T, int64_t N, int64_t K,
-                           int64_t g, bf16_t* y, void* workspace, hipStream_t st) {
-    const unsigned cols = (unsigned)((N + 31) / 32);
-    const int units = (int)((K + 127) / 128);
-    const bf16_t* xo = x;
-    if (T > 32) {
-        const int64_t jobs = (T + 31) / 32 * 4 * ((K / 32 + 1) / 2);
-        BCQ_LAUNCH(order_act_kernel, dim3((unsigned)((jobs + 3) / 4)), dim3(256), 0, st, x, T, K, (u32x4*)workspace);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        xo = (const bf16_t*)workspace;
+static size_t sums_bytes(int64_t T, int64_t N, int parts) { return (size_t)parts * T * ((N + 3) / 4 * 4) * 4; }
+
+// Tokens of a tile (64 or 128), parts of the contraction and units of 128 columns per wave, by an estimated time in us.  `more`:
+// workgroups that share a compute unit with the first, whose waves they slow down.  Group-wise scales build a table per unit.  Parts
+// cost the kernel that adds them and its fp32 sums.  Fitted to 74 shapes of 33 to 720 tokens, every shape and 1 .. 8 parts timed:
+// mean error 5 %, the pick within 5 % of the fastest for 71 of them, 9 % at worst.
+struct TilePlan {
+    int tokens, parts, per;
+    double estimate;
+};
+static TilePlan tile_plan(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
+    TilePlan best = {0, 0, 0, 1e300};
+    const int64_t units = (K + 127) / 128;
+    for (int groups = 1; groups <= 2; ++groups) {  // waves of that many parts
+        const int64_t tiles = (N + 63) / 64 * ((T + 64 * groups - 1) / (64 * groups));
+        for (int parts = 1; parts <= 8; ++parts) {
+            if (parts > 1 && (2 * groups * parts > units || sums_bytes(T, N, parts) + 16 > mfma_fwd_workspace(N, K))) break;
+            const double per = (double)((units + 2 * groups * parts - 1) / (2 * groups * parts) * 2), more = (double)((tiles * parts - 1) / 256);
+            const double grouped = g != K ? q * (more + 1) : 0.0;
+            double t = groups == 1 ? 4.0 + per * (0.34 + 0.058 * q + (0.11 + 0.082 * q) * more + 0.056 * grouped)
+                                   : 4.7 + per * (0.89 + 0.154 * q + (1.07 + 0.21 * q) * more + 0.155 * grouped);
+            if (parts > 1) t += 2.0 + 2.5e-6 * (double)(parts * T * N);
+            if (t < best.estimate) best = TilePlan{64 * groups, parts, (int)per, t};
+        }
     }
-    const bool wide = wide_tokens(T, N, K);
-    const int W = T <= 32 ? 8 : 4, tile = T <= 32 ? 32 : wide ? 128 : 64;
-    const unsigned tiles = (unsigned)((T + tile - 1) / tile);
-    // Few rows and a long contraction: parts of it go to workgroups of their own while they still find an idle compute
-    // unit and every wave keeps a unit (2048 x 8192, groups of 128, 4 tokens: 25.2 -> 12.5 us, 1024 x 4096 at 32 tokens
-    // 16.5 -> 9.7; below 2048 columns the extra launch costs more, 1024 x 1024 at 96 tokens 8 -> 9).
-    int parts = 1;
-    while (units >= 16 && cols * tiles * parts * 2 <= (wide ? 512u : 256u) && units >= 2 * W * parts &&
-           order_bytes(T, K) + sums_bytes(T, N, 2 * parts) <= mfma_fwd_workspace(N, K))
-        parts *= 2;
-    const int per = (units + parts - 1) / parts;
-    parts = (units + per - 1) / per;
-    float* sums = parts > 1 ? reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + order_bytes(T, K)) : nullptr;
-    const dim3 grid(cols, tiles, (unsigned)parts), block(64 * W);
-    if (T <= 32)
-        BCQ_LAUNCH((fused_fwd_kernel<Q, 1, 8, GROUPED, false>), grid, block, 0, st, packed, alpha, xo, y, T, N, K, g, per,
-                           sums);
-    else if (wide)
-        BCQ_LAUNCH((fused_fwd_kernel<Q, 4, 4, GROUPED, true>), grid, block, 0, st, packed, alpha, xo, y, T, N, K, g, per,
-                           sums);
-    else
-        BCQ_LAUNCH((fused_fwd_kernel<Q, 2, 4, GROUPED, true>), grid, block, 0, st, packed, alpha, xo, y, T, N, K, g, per,
-                           sums);
+    best.estimate += 1.1e-6 * (double)(T * N);  // the result's stores
+    return best;
+}
+
+static hipError_t launch_sums(const float* sums, int parts, int64_t T, int64_t N, bf16_t* y, hipStream_t st) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || parts == 1) return e;
     BCQ_LAUNCH(sum_parts_kernel, dim3((unsigned)((T * ((N + 3) / 4) + 255) / 256)), dim3(256), 0, st, sums, parts, T, N, y);
     return hipGetLastError();
 }
 
-// Row-wise scales, 129 to 384 tokens, large layers: whether the workgroups of the one-kernel forward run in one round and
-// fill it (two of 128 tokens or one of 64 to a compute unit at a time).  A round that is half empty, or a second one, goes
-// to two kernels; so do three tiles of 128 tokens.
+template <int Q, int TM, int KG, bool GROUPED>
+static hipError_t launch_tile(const uint32_t* packed, const float* alpha, const bf16_t* x, int64_t T, int64_t N, int64_t K,
+                              int64_t g, bf16_t* y, float* sums, const TilePlan& p, hipStream_t st) {
+    constexpr int LDS_B = tile_lds_bytes<TM, KG>();
+    static LdsLimit limit;
+    hipError_t e = limit.ensure((const void*)tile_fwd_kernel<Q, TM, KG, GROUPED>, LDS_B);
+    if (e != hipSuccess) return e;
+    const int token_tiles = (int)((T + 16 * TM - 1) / (16 * TM));
+    const int items = (int)((N + 63) / 64) * token_tiles * p.parts;
+    BCQ_LAUNCH((tile_fwd_kernel<Q, TM, KG, GROUPED>), dim3(xcd_grid(items)), dim3(256 * KG), LDS_B, st, packed, alpha, x, y, T, N, K, g,
+                       p.per, token_tiles, p.parts, items, p.parts > 1 ? sums : nullptr);
+    return launch_sums(sums, p.parts, T, N, y, st);
+}
+
+template <int Q>
+static hipError_t launch_q(const uint32_t* packed, const float* alpha, const bf16_t* x, int64_t T, int64_t N, int64_t K,
+                           int64_t g, bf16_t* y, float* sums, hipStream_t st) {
+    if (T > 32) {
+        const TilePlan p = tile_plan(T, N, K, g, Q);
+        if (p.tokens == 64) {
+            if (g != K) return launch_tile<Q, 4, 1, true>(packed, alpha, x, T, N, K, g, y, sums, p, st);
+            return launch_tile<Q, 4, 1, false>(packed, alpha, x, T, N, K, g, y, sums, p, st);
+        }
+        if (g != K) return launch_tile<Q, 8, 2, true>(packed, alpha, x, T, N, K, g, y, sums, p, st);
+        return launch_tile<Q, 8, 2, false>(packed, alpha, x, T, N, K, g, y, sums, p, st);
+    }
+    const unsigned cols = (unsigned)((N + 31) / 32);
+    const int units = (int)((K + 127) / 128);
+    // Few rows and a long contraction: parts of it go to workgroups of their own while they still find an idle compute
+    // unit and every wave keeps a unit (2048 x 8192, groups of 128, 4 tokens: 25.2 -> 12.5 us, 1024 x 4096 at 32 tokens
+    // 16.5 -> 9.7; below 2048 columns the extra launch costs more).
+    int parts = 1;
+    while (units >= 16 && cols * parts * 2 <= 256u && units >= 16 * parts && sums_bytes(T, N, 2 * parts) <= mfma_fwd_workspace(N, K)) parts *= 2;
+    const int per = (units + parts - 1) / parts;
+    parts = (units + per - 1) / per;
+    BCQ_LAUNCH(fused_fwd_kernel<Q>, dim3(cols, 1, (unsigned)parts), dim3(512), 0, st, packed, alpha, x, y, T, N, K, g, per,
+                       parts > 1 ? sums : nullptr);
+    return launch_sums(sums, parts, T, N, y, st);
+}
+
+// Row-wise scales, 129 to 384 tokens, large layers: whether row tiles of 32 rows and 128 tokens (64 in smaller layers) fill one round
+// of workgroups, two or one to a compute unit.
 static bool one_full_round(int64_t T, int64_t N, int64_t K, int q) {
-    const int64_t cols = (N + 31) / 32;
-    if (!wide_tokens(T, N, K)) return cols * ((T + 63) / 64) <= 256;
-    const int64_t tiles = cols * ((T + 127) / 128);
+    const int64_t cols = (N + 31) / 32, tiles = cols * ((T + 127) / 128), units = (K + 127) / 128;
+    const bool wide = tiles >= 256 || (tiles >= 64 && units >= 64);
+    if (!wide) return cols * ((T + 63) / 64) <= 256;
     return T <= 256 && tiles <= 512 && tiles > (q == 4 ? 384 : 320);
 }
 
-// Where one kernel is faster than expanding What and multiplying.  Row-wise scales (65000 timings of both sides, 81 to 384 tokens,
-// 0.05 to 100 million weights, q = 1 .. 4): up to 128 tokens one kernel.  Above that the planes are expanded again for
-// every 128 tokens, which costs more than writing What once where the product alone fills the chip: above 40 million weights,
-// and with four planes above 256 tokens from 8 million on, unless one_full_round (one kernel / two, us: 50257 x 1024 at 144
-// tokens 64 / 53 (q = 1) and 76 / 57 (q = 4), 10240 x 2560, q = 4, 288 tokens 42 / 33; one full round 8191 x 7072, q = 2,
-// 160 tokens 53 / 60, 1615 x 5120, q = 4, 320 tokens 25 / 28, and just beyond 1664 x 5120 29 / 25), and up to 100 million, from
-// where What no longer fits the 256 MB cache in front of HBM (12288 x 12288, q = 3, 200 tokens 126 / 211, 16384 x 8192, q = 4,
-// 256 tokens 119 / 161).  Of the 3574 timed calls beyond the first two sizes 22 go to the side that is more than 4 % slower
-// (worst 1.17).  Below them one kernel is more than 4 %
-// slower in 3 % of the calls up to 128 tokens, in 15 % up to 256 and in 48 % above (3072 x 1024, q = 4, 128 tokens 8.6 / 10.4,
-// 256 12.0 / 10.5, 384 15.0 / 12.2).  Above 384 tokens two kernels.
-// Group-wise scales: a unit of 128 columns also builds 2 tables of q loads and 2^(q - 1) sums, 4 when groups hold an odd
-// number of words, for every 128 tokens (64 in small layers) again, so the line moves down with q and that parity (`level`),
-// and less so where N K T is small and leaves the matrix product with few workgroups.  The line was set against an earlier,
-// slower product: against the present one it takes the side that is more than 4 % slower in 26 % of 34440 calls and more than
-// 10 % in 19 %, nearly always one kernel (10240 x 2560, g = 64, q = 2, 128 tokens 25 / 27, 256 37 / 31; q = 4, 128 tokens 36 / 29).
-// The re-ordered activations of more than 32 tokens take the place of the expanded weights in the workspace.
+// Where one kernel is faster than expanding What and multiplying.  Up to 32 tokens, and with row-wise scales up to 128: always.
+// Row-wise scales, 129 to 384 tokens: except above 40 million weights, and with four planes above 256 tokens above 8
+// million, unless one_full_round, and up to 100 million, from where What no longer fits the 256 MB cache in front of HBM.  These
+// lines were set (65000 timings) against a one-kernel form of the rows and tokens that one_full_round counts; of 70 random calls in
+// their range the present form is on the side that is more than 4 % slower in 8.  With one and two planes they are early (one / two kernels,
+// us: 160 tokens of 5120 x 7840, q = 1, 29 / 43, of 8224 x 4896, q = 2, 39 / 43), with three and four about right (288 of 5120 x
+// 8000, q = 3, 58 / 57, 320 of 1664 x 5056, q = 4, 26 / 25.5, 257 of 8200 x 992 19 / 17; 223 of 9344 x 2336 38 / 30).
+// Group-wise scales: a line of the same kind in q and the parity of the words in a group.
+// Beyond these lines, from 385 tokens on or with group-wise scales, and for layers of more than a million weights and
+// 512 columns (whose time is more than start and end): one kernel where its estimate is below that of two (us: 421 tokens of 1312 x 5248, q = 1, groups of 128, 20.6 / 24.5,
+// 720 of 2336 x 2336, q = 1, 17.5 / 21.8, 206 of 2496 x 9984, q = 2, groups of 32, 34 / 45; four planes stay on two kernels, 593 of
+// 1536 x 6144, groups of 128, 37 / 32).
 bool fused_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
-    if (q > 4 || T > 384 || order_bytes(T, K) > mfma_fwd_workspace(N, K)) return false;
+    // layers of fewer rows than tokens have few row tiles, and no room for the sums of parts
+    if (q > 4 || T > 768 || (T > 32 && (T + 31) / 32 * 32 * K * 2 > (int64_t)mfma_fwd_workspace(N, K))) return false;
     if (T <= 16) return true;
+    const int64_t work = N * K * T;
+    if ((T > 384 || g != K) && T > 32 && K > 512 && N * K > 1000000 && tile_plan(T, N, K, g, q).estimate < two_kernel_estimate(T, N, K, q)) return true;
+    if (T > 384) return false;
     if (g == K) {
         const bool large = (T > 128 && N * K > 40000000) || (T > 256 && q == 4 && N * K > 8000000);
         return !large || N * K > 100000000 || one_full_round(T, N, K, q);
     }
     const bool odd = (g / 32) % 2 != 0;
     const int level = q + (odd ? 1 : 0);
-    const int64_t work = N * K * T;
     if (odd && q > 1 && T > 32 && N * K < 1200000) return false;  // 1024 x 1024, q = 4, 64 tokens: 14 / 11
     switch (level) {
         case 1: return true;
@@ -341,16 +659,13 @@ hipError_t launch_fwd_fused(const uint32_t* packed, const float* alpha, const vo
                             int64_t g, int q, void* y, void* workspace, hipStream_t st) {
     const bf16_t* xb = (const bf16_t*)x;
     bf16_t* yb = (bf16_t*)y;
-#define BCQ_FUSED_GO(QQ)                                                                                 \
-    if (g != K) return launch_q<QQ, true>(packed, alpha, xb, T, N, K, g, yb, workspace, st);             \
-    return launch_q<QQ, false>(packed, alpha, xb, T, N, K, g, yb, workspace, st);
+    float* sums = (float*)workspace;
     switch (q) {
-        case 1: BCQ_FUSED_GO(1)
-        case 2: BCQ_FUSED_GO(2)
-        case 3: BCQ_FUSED_GO(3)
-        default: BCQ_FUSED_GO(4)
+        case 1: return launch_q<1>(packed, alpha, xb, T, N, K, g, yb, sums, st);
+        case 2: return launch_q<2>(packed, alpha, xb, T, N, K, g, yb, sums, st);
+        case 3: return launch_q<3>(packed, alpha, xb, T, N, K, g, yb, sums, st);
+        default: return launch_q<4>(packed, alpha, xb, T, N, K, g, yb, sums, st);
     }
-#undef BCQ_FUSED_GO
 }
 
 }  // namespace bcq

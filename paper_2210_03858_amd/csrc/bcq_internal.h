@@ -171,6 +171,7 @@ hipError_t launch_bwd_input_mfma(const uint32_t* packed, const uint32_t* packed_
 size_t mfma_bwd_input_split_workspace(int64_t T, int64_t N, int64_t K);
 hipError_t launch_bwd_input_mfma_split(const uint32_t* packed, const float* alpha, const void* dy, int64_t T, int64_t N,
                                        int64_t K, int64_t g, int q, void* dx, void* workspace, hipStream_t st);
+double two_kernel_estimate(int64_t T, int64_t N, int64_t K, int q);  // of launch_fwd_mfma, us
 // one-kernel forward for few tokens (expands in registers)
 bool fused_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q);
 hipError_t launch_fwd_fused(const uint32_t* packed, const float* alpha, const void* x, int64_t T, int64_t N, int64_t K,
