@@ -281,6 +281,8 @@ bcq_status bcq_linear_fwd_grouped(const uint32_t* packed, const float* alpha, co
     if (workspace && stream_fwd_ok(T, K, g, dtype))
         return done(bcq::launch_fwd_stream(packed, alpha, x, T, N, K, g, q, y, workspace, st));
     if (small_fwd_ok(T, rowwise, dtype)) return done(bcq::launch_fwd_small(packed, alpha, x, T, N, K, q, y, st));
+    if (workspace && !rowwise && dtype == BCQ_BF16 && bcq::few_fwd_ok(T, N, K, g, q))
+        return done(bcq::launch_fwd_few(packed, alpha, x, T, N, K, g, q, y, st));
     if (workspace && mfma_fwd_ok(T, rowwise, dtype) && bcq::fused_fwd_ok(T, N, K, g, q))
         return done(bcq::launch_fwd_fused(packed, alpha, x, T, N, K, g, q, y, workspace, st));
     if (workspace && mfma_fwd_ok(T, rowwise, dtype))

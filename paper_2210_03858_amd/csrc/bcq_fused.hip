@@ -156,18 +156,6 @@ __global__ __launch_bounds__(512) void fused_fwd_kernel(const uint32_t* __restri
 }
 
 // ---- 33 tokens and more ---------------------------------------------------------------------------------------------
-// 4 x 4 transposition of words over the four rows of 16 lanes: lane row h, word u  <->  lane row u, word h
-__device__ __forceinline__ void transpose_rows(uint32_t (&w)[4]) {
-    const auto a = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
-    const auto b = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
-    const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
-    const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
-    w[0] = c[0];
-    w[1] = c[1];
-    w[2] = d[0];
-    w[3] = d[1];
-}
-
 // expand32 in steps of eight columns of each byte pair, so that they can stand between matrix instructions
 template <int Q>
 struct Expansion {

@@ -48,6 +48,18 @@ __device__ __forceinline__ double dpp_move(double v) {
     return __hiloint2double((int)dpp_move<CTRL>((uint32_t)__double2hiint(v)), (int)dpp_move<CTRL>((uint32_t)__double2loint(v)));
 }
 
+// 4 x 4 transposition of words over the four rows of 16 lanes: lane row h, word u  <->  lane row u, word h
+__device__ __forceinline__ void transpose_rows(uint32_t (&w)[4]) {
+    const auto a = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+    const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+    const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+    w[0] = c[0];
+    w[1] = c[1];
+    w[2] = d[0];
+    w[3] = d[1];
+}
+
 // sum over the 64 lanes of a wave, the same value in every lane: four exchange steps inside each row of 16, then
 // the four row sums through scalar registers
 __device__ __forceinline__ double wave_sum(double s) {
@@ -197,6 +209,10 @@ hipError_t launch_fwd_stream(const uint32_t* packed, const float* alpha, const v
                              int64_t K, int64_t g, int q, void* y, void* workspace, hipStream_t st);
 hipError_t launch_fwd_stream_decode(const uint32_t* tiled, const float* alpha, const void* x, int64_t T, int64_t N,
                                     int64_t K, int64_t g, int q, void* y, void* workspace, hipStream_t st);
+// forward of at most 8 tokens in one kernel (row-wise scales or groups of whole 64 columns); needs no workspace
+bool few_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q);
+hipError_t launch_fwd_few(const uint32_t* packed, const float* alpha, const void* x, int64_t T, int64_t N, int64_t K, int64_t g, int q,
+                          void* y, hipStream_t st);
 size_t decode_layout_bytes(int64_t N, int64_t K, int q);
 hipError_t launch_pack_decode(const uint32_t* packed, int64_t N, int64_t K, int q, uint32_t* tiled, hipStream_t st);
 hipError_t launch_bwd_alpha_stream(const uint32_t* packed, const void* x, const void* dy, int64_t T, int64_t N,

@@ -164,18 +164,9 @@ static hipError_t launch_lds(const uint32_t* planes, const unsigned char* xq, co
 // 5120 x 1280 gain 2.3 - 2.7 us per call, 7680 x 2560 loses 1.7 us, 10240 x 2560 loses 8 us)
 constexpr int FUSED_MAX_SEGS = 1;
 constexpr int64_t FUSED_MAX_WAVES = 1024;
-// From the decode layout the two-kernel form is faster than from the canonical planes, so the single kernel pays only
-// while no compute unit re-codes for two row tiles or more than four segments: at 1 / 8 tokens 3072 x 1024 6.2 -> 5.5 /
-// 6.3 -> 5.8 us, 4096 x 2048 6.7 -> 6.0 / 6.7 -> 6.3, but 5120 x 1280 (320 workgroups) 6.7 -> 6.6 / 6.7 -> 7.4 and
-// 2560 x 2560 (five waves) 6.8 -> 6.7 / 6.9 -> 7.4; more than 8 tokens re-code twice as much (3072 x 1024, 16: 6.6 -> 7.6).
+// From the decode layout (where only calls of more than four planes come here, few_fwd_kernel takes the others) it pays for one wave and
+// row-wise scales: 512 x 512, q = 8 7.2 -> 6.6 us, but 4096 x 2048 8.2 -> 9.3.
 constexpr unsigned FUSED_TILED_MAX_WGS = 256;
-// More than four planes run the kernel of eight, whose sums leave room for few waves: 512 x 512, q = 8 7.2 -> 6.6 us, but
-// 4096 x 2048 8.2 -> 9.3.  Group-wise scales cost the single kernel more from three planes and four tokens on (4096 x 2048,
-// groups of 512, q = 4: one token 7.0 -> 6.9, eight 7.0 -> 7.3).
-static int fused_tiled_max_waves(int q, bool grouped, int64_t T) {
-    if (q > 4) return grouped ? 0 : 1;
-    return grouped && q > 2 && T > 4 ? 3 : 4;
-}
 
 template <int MODE, int QP, bool TWO, bool TILED>
 static hipError_t launch_fused_cfg(const uint32_t* planes, const bf16_t* act, const float* alpha, const bf16_t* dy,
@@ -201,6 +192,11 @@ static hipError_t launch_fused(const uint32_t* planes, const bf16_t* act, const 
     if (p.halves == 2)                                                                                                 \
         return launch_fused_cfg<MODE, QQ, true, TILED>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st); \
     return launch_fused_cfg<MODE, QQ, false, TILED>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st);
+    if constexpr (MODE == STREAM_FWD) {
+        if (p.halves == 1) return q_used > 4 ? launch_fused_cfg<MODE, 8, false, TILED>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st)
+                                             : hipErrorInvalidConfiguration;  // few_fwd_kernel
+    }
+    if constexpr (TILED) return hipErrorInvalidConfiguration;
     switch (q_used <= 4 ? q_used : 8) {
         case 1: BCQ_FUSED_Q(1)
         case 2: BCQ_FUSED_Q(2)
@@ -211,6 +207,84 @@ static hipError_t launch_fused(const uint32_t* planes, const bf16_t* act, const 
 #undef BCQ_FUSED_Q
 }
 
+// ---- forward of at most 8 tokens in one kernel ------------------------------------------------------------------------
+// Segments (W) and row tiles (R) of a workgroup.  Sharing the re-coded activations between R row tiles saves 0.27 us per token and row tile
+// where there are several tokens (8 tokens, q = 4, of 7680 x 2560: 10.0 -> 7.2 us), and costs up to 1.5 us where it leaves compute units without a
+// workgroup or puts 16 waves into one (1024 x 4096, q = 3, one token 4.2 -> 5.3).  More than 512 row tiles: three, which keeps the workgroups
+// to one round (10240 x 2560, q = 4, 8 tokens: two 12.3, three 8.4).
+struct FewPlan {
+    int W, R;
+};
+static FewPlan few_plan(int64_t T, int64_t rows, int segs, bool rowwise) {
+    FewPlan p;
+    const int most = segs < 8 ? segs : 8, turns = (segs + most - 1) / most;
+    p.W = (segs + turns - 1) / turns;
+    const int64_t tiles = (rows + 15) / 16;
+    bool share = T >= 3 && p.W < 8;
+    if (!rowwise) share = share && tiles > (T <= 4 ? 256 : p.W <= 3 ? 0 : 128);
+    p.R = !share ? 1 : tiles > 512 && p.W <= 5 ? 3 : 2;
+    return p;
+}
+
+// Where it is faster than re-coding in a kernel of its own (row-wise scales and groups of 512; the re-coding is repeated by every R row
+// tiles) or than the bf16 kernel of few tokens (other groups): us, that / this: one token of 1024 x 1024, q = 3, 5.3 / 3.3, 10240 x 2560,
+// q = 4, 12.1 / 7.0, 2560 x 10240 10.6 / 7.8; four tokens 5.4 / 4.0, 12.2 / 7.2, 10.8 / 11.6, 2048 x 8192, q = 3, 8.1 / 8.0; eight tokens 5.6 / 4.4,
+// 12.3 / 8.4, 1024 x 4096 7.2 / 7.3, 1280 x 5120 7.3 / 8.9.  Groups of 128: four tokens of 6144 x 2048, q = 3, 9.9 / 6.6, 2048 x 8192
+// 12.6 / 11.7, eight 12.9 / 15.2; groups of 64, eight tokens 10.3 / 8.2.  Groups of 32 (four products for one) are as often slower.
+bool few_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
+    if (T > 8 || q > 4 || N * K > 32000000) return false;
+    if (g == K) return K <= (T <= 2 ? 12288 : T <= 4 ? 8192 : 4096);
+    return g % 64 == 0 && K <= (T > 4 ? 4096 : g % 128 == 0 ? 10240 : 4096);
+}
+
+template <int QP, int NT, bool TILED, int SUB>
+static hipError_t launch_few_cfg(const uint32_t* planes, const bf16_t* act, const float* alpha, bf16_t* y, int64_t T, int64_t rows, int64_t cw,
+                                 int64_t g, int segs, const FewPlan& p, hipStream_t st) {
+    const size_t lds = (size_t)p.W * FEW_STAGE + (size_t)p.W * p.R * few_scale_bytes<QP, SUB>();
+    static_assert(8 * FEW_STAGE + 16 * few_scale_bytes<QP, SUB>() <= 160 * 1024, "at most 16 waves");
+    static LdsLimit limit;
+    hipError_t e = limit.ensure((const void*)few_fwd_kernel<QP, NT, TILED, SUB>, lds);
+    if (e != hipSuccess) return e;
+    BCQ_LAUNCH((few_fwd_kernel<QP, NT, TILED, SUB>), dim3((unsigned)((rows + 16 * p.R - 1) / (16 * p.R))), dim3((unsigned)(64 * p.W * p.R)), lds, st,
+                       planes, act, alpha, y, (int)T, rows, (int)cw, segs, (int)(g / 32), (int)(cw * 32 / g), p.W, p.R);
+    return hipGetLastError();
+}
+
+template <bool TILED>
+static hipError_t launch_few(const uint32_t* planes, const bf16_t* act, const float* alpha, bf16_t* y, int64_t T, int64_t rows, int64_t cw, int q,
+                             int64_t g, hipStream_t st) {
+    const int segs = (int)((cw + 15) / 16), sub = g == cw * 32 ? 0 : g % 128 == 0 ? 1 : 2;
+    const FewPlan p = few_plan(T, rows, segs, sub == 0);
+    const int64_t NT = (T + p.R - 1) / p.R;
+    if (T > 8 || p.W * p.R > 16 || p.W * p.R < 1) return hipErrorInvalidConfiguration;
+#define BCQ_FEW(QQ, TT, SS) return launch_few_cfg<QQ, TT, TILED, SS>(planes, act, alpha, y, T, rows, cw, g, segs, p, st);
+#define BCQ_FEW_T(QQ, SS)          \
+    if (NT > 4) BCQ_FEW(QQ, 8, SS) \
+    if (NT > 2) BCQ_FEW(QQ, 4, SS) \
+    if (NT > 1) BCQ_FEW(QQ, 2, SS) \
+    BCQ_FEW(QQ, 1, SS)
+#define BCQ_FEW_S(QQ)                  \
+    if (sub == 0) { BCQ_FEW_T(QQ, 0) } \
+    if constexpr (!TILED) {            \
+        if (sub == 2) { BCQ_FEW_T(QQ, 2) } \
+    }                                  \
+    BCQ_FEW_T(QQ, 1)
+    switch (q) {
+        case 1: { BCQ_FEW_S(1) }
+        case 2: { BCQ_FEW_S(2) }
+        case 3: { BCQ_FEW_S(3) }
+        default: { BCQ_FEW_S(4) }
+    }
+#undef BCQ_FEW_S
+#undef BCQ_FEW_T
+#undef BCQ_FEW
+}
+
+hipError_t launch_fwd_few(const uint32_t* packed, const float* alpha, const void* x, int64_t T, int64_t N, int64_t K, int64_t g, int q, void* y,
+                          hipStream_t st) {
+    return launch_few<false>(packed, (const bf16_t*)x, alpha, (bf16_t*)y, T, N, K / 32, q, g, st);
+}
+
 template <int MODE, bool TILED = false>
 static hipError_t launch_stream(const uint32_t* planes, const bf16_t* act, const float* alpha, const bf16_t* dy, void* out,
                                 int64_t T, int64_t rows, int64_t cw, int q, int q_used, float scale, void* workspace,
@@ -219,9 +293,12 @@ static hipError_t launch_stream(const uint32_t* planes, const bf16_t* act, const
     const int G = (int)(layer_k / g);
     const int gsegs = (grouped && MODE != STREAM_DX) ? (int)(g / 512) : 0;  // needs g % 512 == 0 (checked by the caller)
     const StreamPlan p = stream_plan(T, rows, cw, gsegs);
+    if constexpr (MODE == STREAM_FWD) {
+        if (few_fwd_ok(T, rows, layer_k, g, q)) return launch_few<TILED>(planes, act, alpha, (bf16_t*)out, T, rows, cw, q, g, st);
+    }
     if (p.W < 1 || p.W > 8 || p.R != 1) return hipErrorInvalidConfiguration;  // compiled for at most 512 threads, R = 1
     if constexpr (MODE != STREAM_DX) {
-        const bool fits = TILED ? p.halves == 1 && p.grid_x <= FUSED_TILED_MAX_WGS && p.W <= fused_tiled_max_waves(q_used, grouped, T)
+        const bool fits = TILED ? p.halves == 1 && p.grid_x <= FUSED_TILED_MAX_WGS && p.W == 1 && q_used > 4 && !grouped
                                 : (int64_t)p.grid_x * p.tiles * p.W <= FUSED_MAX_WAVES;
         if (p.segs_per_wave <= FUSED_MAX_SEGS && fits)
             return launch_fused<MODE, TILED>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st);

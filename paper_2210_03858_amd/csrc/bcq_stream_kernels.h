@@ -1219,4 +1219,229 @@ __global__ __launch_bounds__(512) void stream_fused_kernel(const uint32_t* __res
                                  q_used, scale, out);
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// Forward of at most 8 tokens in ONE kernel, without workspace: every wave re-codes the activations of its own segments into a
+// wave-private LDS area and multiplies from there.  (At the layer sizes of one model a call of two kernels is launches, and
+// the second waits for the first.)
+//
+// Re-coding together: a lane takes 8 columns of a token (16 bytes, the wave one KiB in a row), four lanes share a block of 32.
+// The block's largest magnitude is a packed 16-bit maximum and two lane moves; the four lanes then exchange their bytes so that each
+// stores one of the block's four 16-byte pieces (two terms x two chunks).  About 100 vector operations and 2 LDS stores a token and
+// segment, where one lane per block takes 480 operations for up to 8 tokens however few there are.  Same scales, terms and places as
+// recode_unit, but for the order of the 16 columns (256 bytes) of an operand row: column t lies at slot (t + rot) & 15, so that the
+// pieces stored at a time lie in different banks.
+//
+// SUB = 0: row-wise scales, applied to the sums of all of K.  SUB = 1, 2: group-wise scales of whole 128 or 64 columns: the words
+// are turned over the rows of lanes so that instruction i contracts over columns 128 i .. + 127, its sums (for SUB = 2 of one half, the
+// other's signs being zero) are folded into y with the scales of their group, which lie in LDS in the order of the rows.
+// Columns of tokens beyond T hold anything: a column of the result depends on no other.  TILED: decode layout.
+// What bounds it: launch, one trip to memory and the re-coding's 4-cycle vector operations.  1024 x 1024, q = 3: 5.3 -> 3.3 us at one token, 5.6 -> 4.4
+// at eight; 1024 x 4096 (two kernels before) 7.1 -> 4.2; 6144 x 2048, groups of 128, four tokens 9.9 -> 6.6.
+
+// This lane's piece: lane b of the four holds term b >> 1, chunk b & 1; the scale bytes of both terms.
+__device__ __forceinline__ q_u32x4 recode_eight(q_u32x4 raw, int b, int& scale1, int& scale2) {
+    typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
+    auto mag = [](uint32_t r) { return __builtin_bit_cast(u16x2, r & 0x7FFF7FFFu); };
+    const u16x2 m2 = __builtin_elementwise_max(__builtin_elementwise_max(mag(raw[0]), mag(raw[1])),
+                                               __builtin_elementwise_max(mag(raw[2]), mag(raw[3])));
+    uint32_t m = m2[0] > m2[1] ? m2[0] : m2[1];
+    uint32_t o = dpp_move<DPP_XOR1>(m);
+    m = m > o ? m : o;
+    o = dpp_move<DPP_XOR2>(m);
+    m = m > o ? m : o;
+    const bool finite = m <= 0x7F61u;  // 3.0e38, as in recode_unit
+    // smallest power of two 2^E with amax / 2^E <= 448; scale byte = E + 127
+    int sb1 = (int)(m >> 7) - ((m & 0x7Fu) <= 0x60u ? 8 : 7);
+    sb1 = m == 0u || !finite ? 127 : sb1 < 0 ? 0 : sb1;
+    const int sb2 = sb1 >= 4 ? sb1 - 4 : 0;
+    const float inv1 = __uint_as_float((uint32_t)(254 - sb1) << 23), up2 = __uint_as_float((uint32_t)(127 + sb1 - sb2) << 23);
+    scale1 = finite ? sb1 : 255;  // a block with an Inf or a NaN: the NaN scale
+    scale2 = finite ? sb2 : 255;
+    auto value = [&](int e) { return __uint_as_float((e & 1) ? raw[e >> 1] & 0xFFFF0000u : raw[e >> 1] << 16) * inv1; };
+    int d[4];  // [2 term + chunk]: halves s = 2 chunk and 2 chunk + 1, each of columns 3 - s and 7 - s
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const float x0 = value(3 - 2 * c), x1 = value(7 - 2 * c), x2 = value(2 - 2 * c), x3 = value(6 - 2 * c);
+        d[c] = __builtin_amdgcn_cvt_pk_fp8_f32(x0, x1, 0, false);
+        d[c] = __builtin_amdgcn_cvt_pk_fp8_f32(x2, x3, d[c], true);
+        const q_f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8(d[c], false), hi = __builtin_amdgcn_cvt_pk_f32_fp8(d[c], true);
+        d[2 + c] = __builtin_amdgcn_cvt_pk_fp8_f32((x0 - lo[0]) * up2, (x1 - lo[1]) * up2, 0, false);
+        d[2 + c] = __builtin_amdgcn_cvt_pk_fp8_f32((x2 - hi[0]) * up2, (x3 - hi[1]) * up2, d[2 + c], true);
+    }
+    // 4 x 4 transposition over the four lanes: lane b receives d[b] of lanes 0 .. 3
+    auto exchange = [](bool up, int& lo, int& hi, auto move) {
+        const int got = move(up ? lo : hi);
+        (up ? lo : hi) = got;
+    };
+    auto by1 = [](int v) { return (int)dpp_move<DPP_XOR1>((uint32_t)v); };
+    auto by2 = [](int v) { return (int)dpp_move<DPP_XOR2>((uint32_t)v); };
+    const bool b0 = (b & 1) != 0, b1 = (b & 2) != 0;
+    exchange(b0, d[0], d[1], by1);
+    exchange(b0, d[2], d[3], by1);
+    exchange(b1, d[0], d[2], by2);
+    exchange(b1, d[1], d[3], by2);
+    auto join = [](int lo, int hi, uint32_t sel) { return __builtin_amdgcn_perm((uint32_t)hi, (uint32_t)lo, sel); };
+    return q_u32x4{join(d[0], d[1], 0x05040100u), join(d[2], d[3], 0x05040100u), join(d[0], d[1], 0x07060302u), join(d[2], d[3], 0x07060302u)};
+}
+
+constexpr int FEW_STAGE = 4 * QBLK + QSCL;  // re-coded activations of a segment
+template <int QP, int SUB>
+constexpr int few_scale_bytes() { return 4 * SUB * QP * 64; }  // of a wave
+
+// A workgroup has W waves for as many segments at a time, times R row tiles that share their re-coded activations: wave (s, r) re-codes
+// tokens r, r + R, .. (NT of them, T / R rounded up; beyond T the last one again, the same bytes) of segment s.
+template <int QP, int NT, bool TILED, int SUB>
+__global__ __launch_bounds__(1024) void few_fwd_kernel(const uint32_t* __restrict__ planes, const bf16_t* __restrict__ act,
+                                                      const float* __restrict__ alpha, bf16_t* __restrict__ y, int T, int64_t rows,
+                                                      int cw, int segs, int group_words, int G, int W, int R) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = __builtin_amdgcn_readfirstlane(wave / W), s = wave - r * W;
+    const int rl = lane & 15, g = lane >> 4;
+    // row tiles beyond the last one repeat it
+    const int64_t tile = (int64_t)blockIdx.x * R + r, tiles = (rows + 15) >> 4, rt = tile < tiles ? tile : tiles - 1;
+    const int64_t row0 = rt * 16, C = (int64_t)cw * 32;
+    unsigned char* const stage = lds + s * FEW_STAGE;
+    float* const scales = reinterpret_cast<float*>(lds + W * FEW_STAGE + wave * few_scale_bytes<QP, SUB>());  // [entry][plane][16 rows]
+    const int64_t left = rows - 1 - row0;
+    const uint32_t roff = (uint32_t)((rl < left ? rl : left) * cw);  // rows beyond the matrix give outputs that are never stored
+    const uint32_t* const base = planes + row0 * cw;
+    const int64_t plane_stride = rows * cw;
+
+    float ep[QP][4];
+    if (SUB == 0) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int i = 0; i < QP; ++i) ep[i][v] = alpha[(int64_t)i * rows + row0 + (4 * g + v < left ? 4 * g + v : left)];
+    }
+    q_f32x4 acc[QP];
+#pragma unroll
+    for (int i = 0; i < QP; ++i) acc[i] = q_f32x4{0.f, 0.f, 0.f, 0.f};
+    q_f32x4 yv = {0.f, 0.f, 0.f, 0.f};
+
+    constexpr int ENTRIES = SUB ? 4 * SUB : 1, NA = SUB ? (ENTRIES * QP * 16 + 63) / 64 : 1;
+    // block of this lane's 8 columns: word 4 G + j (row-wise) or 4 j + G (groups) of the segment
+    const int Gb = SUB ? (lane >> 2) & 3 : lane >> 4, jb = SUB ? lane >> 4 : (lane >> 2) & 3, b = lane & 3;
+    const int rot = ((lane >> 2) & 3) + 4 * (b & 1);
+    unsigned char* const mine = stage + jb * QBLK + (Gb >> 1) * (QBLK / 2) + ((2 * Gb + (b & 1)) & 3) * 256;
+    unsigned char* const mine_s = stage + 4 * QBLK + (16 * Gb + 8 * b) * 4 + jb;  // lanes 0 and 1 store the scale bytes of the two terms
+    for (int seg0 = 0; seg0 < segs; seg0 += W) {
+        const bool live = seg0 + s < segs;  // (a wave without a segment repeats the last one and drops it)
+        const int seg = live ? seg0 + s : segs - 1;
+        // everything that the segment needs is requested before the first of it is used
+        const bool in = seg * 512 + 8 * lane < C;
+        const bf16_t* src = act + (in ? seg * 512 + 8 * lane : 0);
+        q_u32x4 raw[NT];
+#pragma unroll
+        for (int k = 0; k < NT; ++k) raw[k] = *reinterpret_cast<const q_u32x4*>(src + (r + k * R < T ? r + k * R : T - 1) * C);
+        uint32_t bits[QP][4];
+        if (TILED) {  // the KiB that a wave reads per plane is one contiguous run
+            const uint32_t* tb = planes + (rt * segs + seg) * (QP * 256) + lane * 4;
+#pragma unroll
+            for (int i = 0; i < QP; ++i) __builtin_memcpy(bits[i], tb + i * 256, 16);
+        } else if ((cw & 3) == 0) {  // words beyond the row meet zero activations
+            const uint32_t w0 = (uint32_t)(seg * 16 + 4 * g < cw ? seg * 16 + 4 * g : cw - 4);
+#pragma unroll
+            for (int i = 0; i < QP; ++i) __builtin_memcpy(bits[i], base + i * plane_stride + (roff + w0), 16);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t w = (uint32_t)(seg * 16 + 4 * g + e < cw ? seg * 16 + 4 * g + e : cw - 1);
+#pragma unroll
+                for (int i = 0; i < QP; ++i) bits[i][e] = base[i * plane_stride + (roff + w)];
+            }
+        }
+        float sc[NA];
+        if (SUB) {  // scale of (entry e, plane, row): entries run fastest over the lanes, as in memory
+#pragma unroll
+            for (int a = 0; a < NA; ++a) {
+                const int idx = lane + 64 * a, e = idx % ENTRIES, row = idx / ENTRIES % 16, pl = idx / (16 * ENTRIES);
+                const int word = seg * 16 + e * (16 / ENTRIES);
+                sc[a] = pl < QP && word < cw ? alpha[((int64_t)pl * rows + row0 + (row < left ? row : left)) * G + word / group_words] : 0.f;
+            }
+        }
+        if (seg0 > 0) __syncthreads();  // everybody has read the segment before
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+            const int t = r + k * R < T ? r + k * R : T - 1;
+            const q_u32x4 zero = {0u, 0u, 0u, 0u};
+            int scale1, scale2;
+            const q_u32x4 piece = recode_eight(in ? raw[k] : zero, b, scale1, scale2);
+            *reinterpret_cast<q_u32x4*>(mine + (((t + rot) & 15) ^ (b >> 1 << 3)) * 16) = piece;  // the second term is column t + 8
+            if (b < 2) mine_s[t * 4] = (unsigned char)(b ? scale2 : scale1);
+        }
+        if (SUB) {
+#pragma unroll
+            for (int a = 0; a < NA; ++a) {
+                const int idx = lane + 64 * a, e = idx % ENTRIES, row = idx / ENTRIES % 16, pl = idx / (16 * ENTRIES);
+                if (pl < QP) scales[(e * QP + pl) * 16 + row] = sc[a];
+            }
+#pragma unroll
+            for (int i = 0; i < QP; ++i) transpose_rows(bits[i]);
+        }
+        __syncthreads();
+        if (!live) continue;
+        const int sv = *reinterpret_cast<const int*>(stage + 4 * QBLK + lane * 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            // operand row (j, half hh, lane row g) is chunk 4 hh + g of its block of 8, written by lanes of G = 2 hh + g / 2
+            const unsigned char* bp = stage + j * QBLK + g * 256;
+            const int slot = rl + 4 * (g & 1) + (SUB ? g >> 1 : j);
+            const q_u32x4 lo = *reinterpret_cast<const q_u32x4*>(bp + (slot & 15) * 16);
+            const q_u32x4 hi = *reinterpret_cast<const q_u32x4*>(bp + QBLK / 2 + ((slot + (SUB ? 2 : 0)) & 15) * 16);
+            const q_i32x8 bo = {(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+            auto multiply = [&](const q_i32x8& a, q_f32x4 c) {
+                // the instruction picks byte j of the scale register (its op_sel): j must be a constant
+                if (j == 0) return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, bo, c, 4, 0, 0, 127, 0, sv);
+                if (j == 1) return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, bo, c, 4, 0, 0, 127, 1, sv);
+                if (j == 2) return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, bo, c, 4, 0, 0, 127, 2, sv);
+                return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, bo, c, 4, 0, 0, 127, 3, sv);
+            };
+            q_i32x8 aop[QP];
+#pragma unroll
+            for (int i = 0; i < QP; ++i) expand_one(bits[i][j], aop[i]);
+            if constexpr (SUB == 0) {
+#pragma unroll
+                for (int i = 0; i < QP; ++i) acc[i] = multiply(aop[i], acc[i]);
+            } else {
+#pragma unroll
+                for (int part = 0; part < SUB; ++part) {
+                    const int keep = SUB == 1 || g / (4 / SUB) == part ? -1 : 0;
+#pragma unroll
+                    for (int i = 0; i < QP; ++i) {
+                        q_i32x8 a = aop[i];
+                        if (SUB > 1) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) a[e] &= keep;
+                        }
+                        acc[i] = multiply(a, q_f32x4{0.f, 0.f, 0.f, 0.f});
+                    }
+#pragma unroll
+                    for (int i = 0; i < QP; ++i) {
+                        const q_f32x4 al = *reinterpret_cast<const q_f32x4*>(scales + ((j * SUB + part) * QP + i) * 16 + 4 * g);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) yv[v] += al[v] * acc[i][v];
+                    }
+                }
+            }
+        }
+    }
+    if (SUB) {  // continue with y in place of the plane sums
+        acc[0] = yv;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) ep[0][v] = 1.f;
+#pragma unroll
+        for (int i = 1; i < QP; ++i) {
+            acc[i] = q_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) ep[i][v] = 0.f;
+        }
+    }
+    __syncthreads();  // the cross-wave sum reuses the staging areas
+    const int tcol = rl & 7;
+    stream_finish<STREAM_FWD, QP, false>(acc, ep, reinterpret_cast<float*>(lds), W, s, R, r, lane, row0, rows, tcol < T ? tcol : T - 1,
+                                       tcol < T, QP, 1.f, y);
+}
+
 }  // namespace bcq

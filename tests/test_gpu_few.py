@@ -1,0 +1,72 @@
+"""The forward of at most 8 tokens in one kernel, from both plane layouts, at the edges of its tiles: row counts of less than a
+tile and beyond one, word counts that are no multiple of 4 or 16, one to several segments per wave, row tiles shared by two and three
+to a workgroup, groups of one, two and more halves of an instruction.
+
+Signs and scales are exact and the activations are bf16 within 2^-13 of their block's largest, so only the fp32 sums and the one
+rounding of the result (2^-9 of its value) differ from fp64: 2^-8 of every value and 1e-5 of the largest.  The profiler names the
+kernel that ran.
+"""
+import pytest
+import torch
+from torch.profiler import ProfilerActivity, profile
+
+import paper_2210_03858_amd as bcq
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(q, N, K, g, T, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    packed = torch.randint(-2**31, 2**31 - 1, (q, N, K // 32), dtype=torch.int32, device="cuda", generator=gen)
+    alpha = torch.rand((q, N, K // g), device="cuda", generator=gen) + 0.1
+    x = torch.randn((T, K), device="cuda", generator=gen).bfloat16()
+    bits = torch.arange(32, dtype=torch.int32, device="cuda")
+    w = sum((2 * ((packed[i].unsqueeze(-1) >> bits) & 1) - 1).reshape(N, K).double() * alpha[i].double().repeat_interleave(g, dim=1)
+            for i in range(q))
+    return packed, alpha, x, w
+
+
+def _run(layout, packed, alpha, x, g):
+    q, N, _ = packed.shape
+    T, K = x.shape
+    ws = torch.empty(max(16, bcq.workspace_bytes_grouped(1, T, N, K, g, q, 1)), dtype=torch.uint8, device="cuda")
+    y = torch.full((T + 1, N), 77.0, dtype=torch.bfloat16, device="cuda")  # a row behind the result stays as it is
+    planes = bcq.bcq_pack_decode(packed) if layout == "decode" else packed
+    call = bcq.bcq_linear_fwd_decode if layout == "decode" else bcq.bcq_linear_fwd_grouped
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call(planes, alpha, x, g, y=y[:T], workspace=ws)
+        torch.cuda.synchronize()
+    assert any("few_fwd_kernel" in e.key for e in prof.key_averages())
+    assert (y[T] == 77.0).all()
+    return y[:T]
+
+
+@pytest.mark.parametrize("layout,T,N,K,g,q", [
+    ("decode", 1, 1024, 1024, 1024, 3), ("decode", 8, 33, 32, 32, 1), ("decode", 5, 1000, 1056, 1056, 4), ("decode", 3, 8208, 544, 544, 2),
+    ("decode", 8, 8209, 2528, 2528, 4), ("decode", 2, 200, 12288, 12288, 1), ("decode", 4, 100, 8192, 8192, 3), ("decode", 8, 70, 4096, 4096, 2),
+    ("decode", 8, 300, 2048, 512, 4), ("decode", 1, 300, 1536, 512, 3), ("canonical", 1, 1, 160, 160, 2), ("canonical", 7, 5000, 1056, 1056, 2),
+    ("canonical", 6, 131, 3104, 3104, 3), ("canonical", 4, 2048, 2048, 128, 3), ("canonical", 1, 35, 1152, 128, 4), ("canonical", 8, 2100, 2304, 64, 1),
+    ("canonical", 3, 4200, 1024, 64, 4), ("canonical", 2, 17, 960, 192, 2), ("canonical", 8, 8300, 1280, 256, 1), ("canonical", 4, 40, 10240, 128, 1),
+    ("canonical", 5, 4100, 3968, 64, 3), ("canonical", 2, 64, 640, 320, 4)])
+def test_few_tokens_in_one_kernel(layout, T, N, K, g, q):
+    packed, alpha, x, w = _layer(q, N, K, g, T, T + N + K)
+    y = _run(layout, packed, alpha, x, g).double()
+    ref = x.double() @ w.t()
+    assert ((y - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * ref.abs().max()).all()
+
+
+@pytest.mark.parametrize("layout,T,N,K,g,q", [("decode", 8, 600, 1056, 1056, 3), ("canonical", 5, 4200, 1024, 128, 2), ("canonical", 4, 100, 1152, 64, 4)])
+def test_non_finite_token_and_zero_blocks(layout, T, N, K, g, q):
+    """A non-finite activation makes its own token's results NaN; blocks of zeros, a block of subnormals and one of large values
+    re-code exactly."""
+    packed, alpha, x, w = _layer(q, N, K, g, T, N)
+    x[0, 32:64], x[1, 64:96], x[2, :32] = 0.0, 1e-39, 2.0 ** 100
+    clean = _run(layout, packed, alpha, x, g)
+    ref = x.double() @ w.t()
+    assert ((clean.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * ref.abs().max(dim=1, keepdim=True).values).all()
+    x[3, 5], x[3, K - 1] = float("inf"), float("nan")
+    y = _run(layout, packed, alpha, x, g)
+    assert y[3].isnan().all()
+    keep = torch.arange(T, device="cuda") != 3
+    assert torch.equal(y[keep], clean[keep])
