@@ -35,7 +35,8 @@ struct BatchHeader {  // 128 bytes
     float scale;
     uint32_t pre_blocks, pre_sets;   // grid of the pre-kernel: (segments of all layers, activation sets per layer)
     uint32_t tile_blocks;            // workgroups (= pieces) of the main kernel
-    uint32_t pad0[2];
+    uint32_t tail;                   // 1: the main kernel leaves out the padding at the rows' ends
+    uint32_t pad0;
     uint64_t layers_off, pre_map_off, tile_map_off;
     uint64_t table_bytes, workspace_bytes;
     uint64_t plane_bytes;            // sum of q N K / 8 over the layers (for reporting)
@@ -156,7 +157,7 @@ __device__ __forceinline__ float row16_sum(float x) {
     return x;
 }
 
-template <int MODE, int QP, int RT, bool TWO>
+template <int MODE, int QP, int RT, bool TWO, bool TAIL>
 __global__ __launch_bounds__(TILE_THREADS, (TILE_WAVES <= 4 ? 2 : 1)) void stream_tile_batched_kernel(const BatchLayerDev* __restrict__ layers,
                                                                       const BatchPiece* __restrict__ pieces,
                                                                       const unsigned char* __restrict__ ws, int T,
@@ -257,7 +258,13 @@ __global__ __launch_bounds__(TILE_THREADS, (TILE_WAVES <= 4 ? 2 : 1)) void strea
     uint32_t bits[TILE_RING][PR][4];
     // decode layout: row tile rt, segment vseg, plane i -> 1 KiB at ((rt * segs + vseg) * q_mem + i) KiB, 16 B per lane
     const uint32_t lane4 = (uint32_t)lane * 4u;
+    // TAIL: rows whose last segment is not full end in padding, whole 256-byte runs of 16 lanes from run `runs` on.  Their
+    // lanes read the segment's first run again (these words meet zero activations), so no padding leaves memory.
+    const int tail_seg = segs - (DX ? L.seg_mul : 1);  // first (virtual) segment that holds the end of the rows
+    const int runs = ((int)L.cw - 1) / 4 % 4 + 1;
+    const uint32_t lane4_tail = (uint32_t)(g < runs ? lane : rl) * 4u;
     auto load_unit = [&](int slot, int rtg, int vseg) {
+        const uint32_t lo = TAIL && vseg >= tail_seg ? lane4_tail : lane4;
 #pragma unroll
         for (int r = 0; r < RT; ++r) {
             int rt = rtg * RT + r;
@@ -265,7 +272,7 @@ __global__ __launch_bounds__(TILE_THREADS, (TILE_WAVES <= 4 ? 2 : 1)) void strea
             BCQ_GLOBAL const uint32_t* const tb = planes + ((int64_t)rt * segs + vseg) * ((int64_t)q_mem * 256);
 #pragma unroll
             for (int i = 0; i < QP; ++i) {
-                const q_u32x4 v4 = *(BCQ_GLOBAL const q_u32x4*)(tb + i * 256 + lane4);
+                const q_u32x4 v4 = *(BCQ_GLOBAL const q_u32x4*)(tb + i * 256 + lo);
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) bits[slot][r * QP + i][jj] = v4[jj];
             }
@@ -601,21 +608,28 @@ struct BatchTotals {
     uint64_t pre_blocks = 0, pieces = 0;
     size_t table_bytes = 0, workspace_bytes = 0;
     uint64_t plane_bytes = 0;
+    bool tail = false;
 };
 
 static BatchTotals batch_totals(int op, const bcq_batch_layer* layers, int64_t count, int64_t T, int q, int q_used) {
     BatchTotals t;
+    uint64_t runs = 0, padding = 0;  // of 256 bytes, in the decode layouts that the call reads
     t.piece_units = choose_piece_units(op, layers, count, T, q, q_used);
     for (int64_t l = 0; l < count; ++l) {
         const BatchShape s = batch_shape(op, T, layers[l].N, layers[l].K, q, q_used, t.piece_units);
         t.pre_blocks += (uint64_t)s.segs_act;
         t.pieces += s.pieces;
+        runs += (uint64_t)s.nrt * s.segs_act * 4;
+        padding += (uint64_t)s.nrt * (s.segs_act * 4 - (s.cw + 3) / 4);
         t.workspace_bytes += align_up(s.xq_bytes, 256) + align_up(s.sq_bytes, 256);
         t.plane_bytes += (uint64_t)q * (uint64_t)layers[l].N * (uint64_t)layers[l].K / 8;
     }
     t.table_bytes = sizeof(BatchHeader) + (size_t)count * sizeof(BatchLayerDev) + (size_t)t.pre_blocks * sizeof(uint2) +
                     (size_t)t.pieces * sizeof(BatchPiece);
     t.table_bytes = align_up(t.table_bytes, 256);
+    // 1280-wide stacks (0.54 GB of planes, 7 to 13 % padding on top) at 8 tokens 445 -> 416 us for the three calls; without
+    // padding the choice of the lane offset costs 0.7 % (2560-wide, one token: 111.0 / 111.75).
+    t.tail = padding * 50 >= runs;
     return t;
 }
 
@@ -658,15 +672,21 @@ static hipError_t launch_pre(const BatchHeader& h, const unsigned char* dev, uns
     return hipGetLastError();
 }
 
-template <int MODE, int QP, int RT, bool TWO>
-static hipError_t launch_main_cfg(const BatchHeader& h, const unsigned char* dev, const unsigned char* ws, hipStream_t st) {
+template <int MODE, int QP, int RT, bool TWO, bool TAIL>
+static hipError_t launch_main_form(const BatchHeader& h, const unsigned char* dev, const unsigned char* ws, hipStream_t st) {
     static LdsLimit limit;
-    hipError_t e = limit.ensure((const void*)stream_tile_batched_kernel<MODE, QP, RT, TWO>, TILE_LDS);
+    hipError_t e = limit.ensure((const void*)stream_tile_batched_kernel<MODE, QP, RT, TWO, TAIL>, TILE_LDS);
     if (e != hipSuccess) return e;
-    BCQ_LAUNCH((stream_tile_batched_kernel<MODE, QP, RT, TWO>), dim3(h.tile_blocks), dim3(64 * TILE_WAVES), TILE_LDS,
+    BCQ_LAUNCH((stream_tile_batched_kernel<MODE, QP, RT, TWO, TAIL>), dim3(h.tile_blocks), dim3(64 * TILE_WAVES), TILE_LDS,
                        st, reinterpret_cast<const BatchLayerDev*>(dev + h.layers_off),
                        reinterpret_cast<const BatchPiece*>(dev + h.tile_map_off), ws, h.T, h.scale);
     return hipGetLastError();
+}
+
+template <int MODE, int QP, int RT, bool TWO>
+static hipError_t launch_main_cfg(const BatchHeader& h, const unsigned char* dev, const unsigned char* ws, hipStream_t st) {
+    return h.tail ? launch_main_form<MODE, QP, RT, TWO, true>(h, dev, ws, st)
+                  : launch_main_form<MODE, QP, RT, TWO, false>(h, dev, ws, st);
 }
 
 template <int MODE, bool TWO>
@@ -733,6 +753,7 @@ bcq_status bcq_batch_plan(int op, const bcq_batch_layer* layers, int64_t count, 
     h.pre_blocks = (uint32_t)t.pre_blocks;
     h.pre_sets = (op == BCQ_OP_BWD_INPUT) ? (uint32_t)q : 1u;
     h.tile_blocks = (uint32_t)t.pieces;
+    h.tail = t.tail ? 1u : 0u;
     h.layers_off = sizeof(BatchHeader);
     h.pre_map_off = h.layers_off + (uint64_t)count * sizeof(BatchLayerDev);
     h.tile_map_off = h.pre_map_off + t.pre_blocks * sizeof(uint2);

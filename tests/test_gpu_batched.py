@@ -85,6 +85,23 @@ def test_batched_input_gradient_mixed_shapes(bcq, oracle, T, q):
     _check_batch(bcq, oracle, layers, T, q, ops=(OP_DX,))
 
 
+@pytest.mark.parametrize("T,q", [(2, 1), (8, 2), (16, 3), (7, 4)])
+@pytest.mark.parametrize("words", [1, 4, 5, 11, 12, 13, 16, 17, 40, 60])
+def test_batched_ends_of_rows(bcq, oracle, words, T, q):
+    """Rows that end in every run of 128 columns of their last segment, in a batch of their own: all-ones words stand where the
+    decode layout has its padding, which nothing may read into a result."""
+    shapes = [("out", 32 * words, 32 * words, 0), ("qkv", 96, 32 * words, 1), ("mlp_up", 32 * words, 96, 2)]
+    layers = _make_batch(bcq, oracle, 3, shapes, T, q)
+    for L in layers:
+        for name, rows, cols in (("tiled", L["N"], L["K"]), ("tiled_t", L["K"], L["N"])):
+            segs = (cols + 511) // 512
+            lane = np.arange(64)[:, None] // 16 * 4 + np.arange(4)
+            pad = (np.arange(segs)[:, None, None] * 16 + lane >= cols // 32)[None, :, None]
+            tiled = to_host(L[name]).reshape((rows + 15) // 16, segs, q, 64, 4)
+            L[name] = to_dev(np.where(pad, np.int32(-1), tiled).astype(np.int32).ravel())
+    _check_batch(bcq, oracle, layers, T, q)
+
+
 def test_batched_q_train_and_grad_scale(bcq, oracle):
     T, q = 7, 4
     layers = _make_batch(bcq, oracle, 3, MIXED[:3], T, q)
