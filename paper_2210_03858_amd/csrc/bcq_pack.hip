@@ -61,35 +61,53 @@ __device__ __forceinline__ void transpose32(uint32_t (&a)[32]) {
     }
 }
 
-// Tile: TR_VB row blocks of 32 rows of W x TR_WB words of 32 columns.  Thread (vb, wb) transposes one 32 x 32 block
-// read with lanes running along the words of a row (coalesced); results pass through LDS so that the writes
-// run along the words of a packed_t row.
-template <int TR_VB, int TR_WB>
-__global__ __launch_bounds__(TR_VB * TR_WB) void transpose_kernel(const uint32_t* __restrict__ packed, int64_t N, int64_t K,
-                                                        uint32_t* __restrict__ packed_t) {
-    __shared__ uint32_t tile[TR_WB * 32][TR_VB + 1];
+// Tile: 16 row blocks of 32 rows of W x 16 words of 32 columns.  Thread (vb, wb) transposes one 32 x 32 block read with
+// lanes running along the words of a row (64-byte pieces); results pass through LDS so that the writes run along the words
+// of a packed_t row.  Bound by latency: one memory trip in, some 500 ALU instructions, one trip out.  The LDS pitches (20
+// words per wb, 336 per row of a block) put the 64 lanes of a write, and the 16 lanes of a 16-byte read, on 64 different
+// banks; a tile of [512][17] had 16 lanes on one bank (10240 x 2560, q = 4: 12.3 us; 9.3 without the conflicts, 7.8 with
+// 16-byte reads and stores as well; a copy of its 26 MB takes 4.9).  Tiles of 8 x 8 and 16 x 8 words were up to 0.3 us faster
+// (1024 x 1024, q = 3: 3.3 / 3.1) or up to 5 us slower, 32 x 16 from 0.2 us faster to 0.9 slower.
+// QUAD: rows of packed_t of whole 16-byte units (N % 128 == 0), four words per lane on the way out.
+constexpr int TR_B = 16, TR_P2 = TR_B + 4, TR_P1 = TR_B * TR_P2 + 16;
+
+template <bool QUAD>
+__global__ __launch_bounds__(TR_B * TR_B) void transpose_kernel(const uint32_t* __restrict__ packed, int64_t N, int64_t K,
+                                                                uint32_t* __restrict__ packed_t) {
+    __shared__ __attribute__((aligned(16))) uint32_t tile[32 * TR_P1];
     const int64_t Kw = K / 32, Nw = N / 32;
     const int plane = blockIdx.z;
-    const uint32_t* src = packed + (int64_t)plane * N * Kw;
-    uint32_t* dst = packed_t + (int64_t)plane * K * Nw;
-    const int wb = threadIdx.x % TR_WB, vb = threadIdx.x / TR_WB;
-    const int64_t w = (int64_t)blockIdx.x * TR_WB + wb, v = (int64_t)blockIdx.y * TR_VB + vb;
+    const int wb = threadIdx.x % TR_B, vb = threadIdx.x / TR_B;
+    const int64_t w = (int64_t)blockIdx.x * TR_B + wb, v = (int64_t)blockIdx.y * TR_B + vb;
     uint32_t a[32];
     const bool live = (w < Kw) && (v < Nw);
+    const uint32_t* src = packed + ((int64_t)plane * N + 32 * v) * Kw + w;
 #pragma unroll
-    for (int r = 0; r < 32; ++r) a[r] = live ? src[(32 * v + r) * Kw + w] : 0u;
+    for (int r = 0; r < 32; ++r) a[r] = 0u;
+    if (live) {
+#pragma unroll
+        for (int r = 0; r < 32; ++r) a[r] = src[(uint32_t)r * (uint32_t)Kw];
+    }
     transpose32(a);
 #pragma unroll
-    for (int r = 0; r < 32; ++r) tile[wb * 32 + r][vb] = a[r];
+    for (int r = 0; r < 32; ++r) tile[r * TR_P1 + wb * TR_P2 + vb] = a[r];
     __syncthreads();
-    // 32 TR_WB output rows (columns k of W) x TR_VB words each; a thread handles one word of 32 of them
-    const int ov = threadIdx.x % TR_VB;
-    const int64_t gv = (int64_t)blockIdx.y * TR_VB + ov;
+    // 512 output rows (columns k of W) x 16 words each, E words to a lane
+    constexpr int E = QUAD ? 4 : 1, LANES = TR_B / E, ROWS = TR_B * TR_B / LANES;
+    uint32_t* dst = packed_t + (int64_t)plane * K * Nw;
+    const int ov = threadIdx.x % LANES * E;
+    const int64_t gv = (int64_t)blockIdx.y * TR_B + ov;
 #pragma unroll
-    for (int pass = 0; pass < 32; ++pass) {
-        const int row = threadIdx.x / TR_VB + TR_WB * pass;
-        const int64_t k = (int64_t)blockIdx.x * TR_WB * 32 + row;
-        if (k < K && gv < Nw) dst[k * Nw + gv] = tile[row][ov];
+    for (int pass = 0; pass < 32 * TR_B / ROWS; ++pass) {
+        const int row = threadIdx.x / LANES + ROWS * pass;
+        const int64_t k = (int64_t)blockIdx.x * (32 * TR_B) + row;
+        if (k < K && gv < Nw) {
+            const uint32_t* t = tile + row % 32 * TR_P1 + row / 32 * TR_P2 + ov;
+            if (QUAD)
+                *reinterpret_cast<uint4*>(dst + k * Nw + gv) = *reinterpret_cast<const uint4*>(t);
+            else
+                dst[k * Nw + gv] = *t;
+        }
     }
 }
 
@@ -110,14 +128,11 @@ hipError_t launch_unpack(const uint32_t* packed, int64_t total_words, int8_t* pl
 hipError_t launch_pack_transposed(const uint32_t* packed, int64_t N, int64_t K, int q, uint32_t* packed_t,
                                   hipStream_t st) {
     const int64_t Kw = K / 32, Nw = N / 32;
-    // Tiles of 16 x 16 words move 64-byte pieces both ways; tiles of 8 x 8 are faster while they leave many compute units
-    // without one (2560 x 2560 at q = 4 7.3 / 6.5 us, 1024 x 1024 at q = 3 6.8 / 5.2), up to about 190 tiles: 180 (3072 x
-    // 3072, q = 5) 7.7 / 8.1, 192 (8192 x 1536, q = 4; 4096 x 4096, q = 3) 7.6 / 9.3 and 7.6 / 6.8, 240 7.9 / 11.1.
-    const auto blocks = [&](int t) { return dim3((unsigned)((Kw + t - 1) / t), (unsigned)((Nw + t - 1) / t), (unsigned)q); };
-    if ((Kw + 15) / 16 * ((Nw + 15) / 16) * q >= 192)
-        BCQ_LAUNCH((transpose_kernel<16, 16>), blocks(16), dim3(256), 0, st, packed, N, K, packed_t);
+    const dim3 grid((unsigned)((Kw + TR_B - 1) / TR_B), (unsigned)((Nw + TR_B - 1) / TR_B), (unsigned)q);
+    if (Nw % 4 == 0)
+        BCQ_LAUNCH((transpose_kernel<true>), grid, dim3(TR_B * TR_B), 0, st, packed, N, K, packed_t);
     else
-        BCQ_LAUNCH((transpose_kernel<8, 8>), blocks(8), dim3(64), 0, st, packed, N, K, packed_t);
+        BCQ_LAUNCH((transpose_kernel<false>), grid, dim3(TR_B * TR_B), 0, st, packed, N, K, packed_t);
     return hipGetLastError();
 }
 

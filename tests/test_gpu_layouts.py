@@ -20,3 +20,10 @@ def test_twin_and_decode_layout(q, N, K):
         bits = np.unpackbits(packed.view(np.uint8), axis=2, bitorder="little")           # [q][N][K]
         twin = np.packbits(bits.transpose(0, 2, 1).copy(), axis=2, bitorder="little").view(np.uint32)
         assert np.array_equal(packed_to_host(bcq.bcq_pack_transposed(dev)), twin)
+
+
+@pytest.mark.parametrize("q,N,K", [(1, 128, 32), (3, 512, 512), (5, 640, 544), (2, 544, 1056), (7, 1152, 480), (1, 32, 16384),
+                                   (2, 16384, 32)])
+def test_twin_and_decode_layout_around_one_tile(q, N, K):
+    """Tiles of 16 x 16 words, whole and in part, rows of packed_t of whole 16-byte units and others, odd plane counts."""
+    test_twin_and_decode_layout(q, N, K)
