@@ -2,6 +2,7 @@
 #include "../../include/bcq.h"
 
 #include "bcq_internal.h"
+#include "bcq_node.h"
 
 #include <math.h>
 #include <string.h>
@@ -262,9 +263,9 @@ bcq_status bcq_pack_transposed(const uint32_t* packed, int64_t N, int64_t K, int
     return done(bcq::launch_pack_transposed(packed, N, K, q, packed_t, (hipStream_t)stream));
 }
 
-bcq_status bcq_linear_fwd_grouped(const uint32_t* packed, const float* alpha, const void* x, int dtype, int64_t T,
-                                  int64_t N, int64_t K, int64_t g, int q, void* y, void* workspace,
-                                  size_t workspace_bytes, void* stream) {
+// parts != nullptr: `alpha` is written from them before anything reads it
+static bcq_status fwd_impl(const uint32_t* packed, const float* alpha, const bcq::ScaleParts* parts, const void* x, int dtype, int64_t T,
+                           int64_t N, int64_t K, int64_t g, int q, void* y, void* workspace, size_t workspace_bytes, void* stream) {
     if (!packed || !alpha || !x || !y) return BCQ_ERR_NULL;
     bcq_status s = check_shape(T, N, K, q);
     if (s != BCQ_OK) return s;
@@ -278,16 +279,41 @@ bcq_status bcq_linear_fwd_grouped(const uint32_t* packed, const float* alpha, co
     if (s != BCQ_OK) return s;
     const bool rowwise = (g == K);
     hipStream_t st = (hipStream_t)stream;
-    if (workspace && stream_fwd_ok(T, K, g, dtype))
+    // the expansion reads the parts and joins them itself
+    const bool streams = workspace && stream_fwd_ok(T, K, g, dtype);
+    const bool few = workspace && !rowwise && dtype == BCQ_BF16 && bcq::few_fwd_ok(T, N, K, g, q);
+    const bool expands = workspace && !streams && !small_fwd_ok(T, rowwise, dtype) && !few && mfma_fwd_ok(T, rowwise, dtype) &&
+                         !bcq::fused_fwd_ok(T, N, K, g, q);
+    if (expands)
+        return done(bcq::launch_fwd_mfma(packed, parts ? *parts : bcq::ScaleParts{alpha, nullptr, q, nullptr}, x, T, N, K, g, q, y,
+                                         workspace, st));
+    if (parts) {
+        const hipError_t e = bcq::launch_join_scales(*parts, N * (K / g), q, st);
+        if (e != hipSuccess) return done(e);
+    }
+    if (streams)
         return done(bcq::launch_fwd_stream(packed, alpha, x, T, N, K, g, q, y, workspace, st));
     if (small_fwd_ok(T, rowwise, dtype)) return done(bcq::launch_fwd_small(packed, alpha, x, T, N, K, q, y, st));
-    if (workspace && !rowwise && dtype == BCQ_BF16 && bcq::few_fwd_ok(T, N, K, g, q))
+    if (few)
         return done(bcq::launch_fwd_few(packed, alpha, x, T, N, K, g, q, y, st));
-    if (workspace && mfma_fwd_ok(T, rowwise, dtype) && bcq::fused_fwd_ok(T, N, K, g, q))
-        return done(bcq::launch_fwd_fused(packed, alpha, x, T, N, K, g, q, y, workspace, st));
     if (workspace && mfma_fwd_ok(T, rowwise, dtype))
-        return done(bcq::launch_fwd_mfma(packed, alpha, x, T, N, K, g, q, y, workspace, st));
+        return done(bcq::launch_fwd_fused(packed, alpha, x, T, N, K, g, q, y, workspace, st));
     return done(bcq::launch_fwd_generic(packed, alpha, x, dtype, T, N, K, g, q, y, st));
+}
+
+bcq_status bcq_linear_fwd_grouped(const uint32_t* packed, const float* alpha, const void* x, int dtype, int64_t T,
+                                  int64_t N, int64_t K, int64_t g, int q, void* y, void* workspace,
+                                  size_t workspace_bytes, void* stream) {
+    return fwd_impl(packed, alpha, nullptr, x, dtype, T, N, K, g, q, y, workspace, workspace_bytes, stream);
+}
+
+bcq_status bcq_node_forward(const uint32_t* packed, const float* alpha_first, int q_first, const float* alpha_rest, float* alpha,
+                            const void* x, int dtype, int64_t T, int64_t N, int64_t K, int64_t g, int q, void* y, void* workspace,
+                            size_t workspace_bytes, void* stream) {
+    if (!alpha_first || !alpha_rest) return BCQ_ERR_NULL;
+    if (q_first < 1 || q_first >= q) return BCQ_ERR_SHAPE;
+    const bcq::ScaleParts parts = {alpha_first, alpha_rest, q_first, alpha};
+    return fwd_impl(packed, alpha, &parts, x, dtype, T, N, K, g, q, y, workspace, workspace_bytes, stream);
 }
 
 bcq_status bcq_decode_layout_bytes(int64_t N, int64_t K, int q, size_t* out) {
@@ -474,6 +500,32 @@ bcq_status bwd_alpha_impl(const uint32_t* packed, const void* x, const void* dy,
 }  // namespace
 
 extern "C" {
+
+bcq_status bcq_node_backward(const uint32_t* packed, const uint32_t* packed_t, const float* alpha, const void* x, const void* dy,
+                             int dtype, int64_t T, int64_t N, int64_t K, int64_t g, int q, int q_train, float grad_scale, void* dx,
+                             void* input_workspace, size_t input_bytes, float* dalpha, void* alpha_workspace, size_t alpha_bytes,
+                             void* stream) {
+    const bool rowwise = (g == K);
+    // One launch less where both gradients run on the tiled kernels and the input gradient expands by table; every other call,
+    // and one that the checks refuse, is the two calls.
+    const bool joint = packed && alpha && x && dy && dx && dalpha && input_workspace && alpha_workspace &&
+                       check_shape(T, N, K, q) == BCQ_OK && check_group(K, g) == BCQ_OK && q <= 4 && q_train >= 1 && q_train <= q &&
+                       !(packed_t && stream_bwd_input_ok(T, N, K, g, q, dtype)) && mfma_bwd_input_ok(T, N, rowwise, dtype) &&
+                       !stream_bwd_alpha_ok(T, K, g, dtype) && mfma_bwd_alpha_ok(T, N, K, rowwise, dtype) &&
+                       !misaligned(packed) && !misaligned(alpha) && !misaligned(x) && !misaligned(dy) && !misaligned(dx) &&
+                       !misaligned(dalpha) &&
+                       check_workspace(input_workspace, input_bytes, workspace_least(BCQ_OP_BWD_INPUT, T, N, K, g, q, dtype)) == BCQ_OK &&
+                       check_workspace(alpha_workspace, alpha_bytes, workspace_least(BCQ_OP_BWD_ALPHA, T, N, K, g, q, dtype)) == BCQ_OK &&
+                       check_device() == BCQ_OK;
+    if (joint)
+        return done(bcq::launch_bwd_mfma(packed, alpha, x, dy, T, N, K, g, q, q_train, grad_scale, dx, input_workspace, dalpha,
+                                         alpha_workspace, (hipStream_t)stream));
+    const bcq_status s = bcq_linear_bwd_input_grouped(packed, packed_t, alpha, dy, dtype, T, N, K, g, q, dx, input_workspace,
+                                                      input_bytes, stream);
+    if (s != BCQ_OK) return s;
+    return bcq_linear_bwd_alpha_grouped(packed, x, dy, dtype, T, N, K, g, q, q_train, grad_scale, dalpha, alpha_workspace,
+                                        alpha_bytes, stream);
+}
 
 bcq_status bcq_linear_bwd_alpha(const uint32_t* packed, const void* x, const void* dy, int dtype, int64_t T,
                                 int64_t N, int64_t K, int q, int q_train, float grad_scale, float* dalpha,

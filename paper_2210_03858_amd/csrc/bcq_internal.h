@@ -174,7 +174,15 @@ hipError_t launch_bwd_alpha_generic(const uint32_t* packed, const void* x, const
 // ---- matrix-core kernels (bf16 activations, need the caller's workspace) ---------------------
 size_t mfma_fwd_workspace(int64_t N, int64_t K);
 size_t mfma_bwd_input_workspace(int64_t N, int64_t K);
-hipError_t launch_fwd_mfma(const uint32_t* packed, const float* alpha, const void* x, int64_t T, int64_t N,
+// The scales of a call: planes 0 .. q_first - 1 in `first`, the others in `rest`; joined != nullptr takes a copy of them all.
+struct ScaleParts {
+    const float* first;
+    const float* rest;
+    int64_t q_first;
+    float* joined;
+};
+hipError_t launch_join_scales(const ScaleParts& a, int64_t per_plane, int q, hipStream_t st);
+hipError_t launch_fwd_mfma(const uint32_t* packed, const ScaleParts& alpha, const void* x, int64_t T, int64_t N,
                            int64_t K, int64_t g, int q, void* y, void* workspace, hipStream_t st);
 hipError_t launch_bwd_input_mfma(const uint32_t* packed, const uint32_t* packed_t, const float* alpha, const void* dy,
                                  int64_t T, int64_t N, int64_t K, int64_t g, int q, void* dx, void* workspace,
@@ -193,6 +201,10 @@ size_t mfma_bwd_alpha_workspace(int64_t T, int64_t N, int64_t K, int64_t g, int 
 hipError_t launch_bwd_alpha_mfma(const uint32_t* packed, const void* x, const void* dy, int64_t T, int64_t N,
                                  int64_t K, int64_t g, int q, int q_train, float grad_scale, float* dalpha,
                                  void* workspace, const AdamWArgs* opt, hipStream_t st);
+// both gradients of up to four planes, the reduction of the second in the launch of the first's expansion
+hipError_t launch_bwd_mfma(const uint32_t* packed, const float* alpha, const void* x, const void* dy, int64_t T, int64_t N, int64_t K,
+                           int64_t g, int q, int q_train, float grad_scale, void* dx, void* input_workspace, float* dalpha,
+                           void* alpha_workspace, hipStream_t st);
 
 // ---- small-token kernels without workspace (bf16, at most 16 tokens per tile; plane-by-plane, bf16 MFMA) ----
 hipError_t launch_fwd_small(const uint32_t* packed, const float* alpha, const void* x, int64_t T, int64_t N,

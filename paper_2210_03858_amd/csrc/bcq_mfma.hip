@@ -88,11 +88,36 @@ __device__ __forceinline__ void store_word_frags(const float (&s)[32], u32x4* __
 // instead of 12.1).  Q planes by table up to four, else (Q = 0) q of them as signed sums.  What bounds it is the 16 bits per
 // weight that it writes (5.4 TB/s with its reads); by signed sums four planes were bound by vector operations.  Measured:
 // 10240 x 2560, q = 4 17.7 -> 12.5 us, 2560 x 10240 17.5 -> 11.8, 8192 x 2048, q = 3 10.8 -> 8.4, 4096 x 1024 5.6 -> 5.2.
+//
+// The scales of a layer in training lie in two tensors (ScaleParts), and its backward pass wants them in one: blocks beyond
+// the expansion's write that (a concatenation before the expansion was a launch of 4 to 6 us).
+__device__ __forceinline__ void join_scales(const ScaleParts& a, int64_t per_plane, int q, uint32_t chunk) {
+    const int64_t split = a.q_first * per_plane, total = q * per_plane;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int64_t idx = (int64_t)chunk * 2048 + e * 256 + threadIdx.x;
+        if (idx < total) a.joined[idx] = idx < split ? a.first[idx] : a.rest[idx - split];
+    }
+}
+
+__global__ __launch_bounds__(256) void join_scales_kernel(ScaleParts a, int64_t per_plane, int q) {
+    join_scales(a, per_plane, q, blockIdx.x);
+}
+
+hipError_t launch_join_scales(const ScaleParts& a, int64_t per_plane, int q, hipStream_t st) {
+    BCQ_LAUNCH(join_scales_kernel, dim3((unsigned)((q * per_plane + 2047) / 2048)), dim3(256), 0, st, a, per_plane, q);
+    return hipGetLastError();
+}
+
 template <int Q>
-__global__ __launch_bounds__(256) void expand_fwd_kernel(const uint32_t* __restrict__ packed,
-                                                         const float* __restrict__ alpha, int64_t N, int64_t K,
-                                                         int64_t g, int q, int64_t R16 /* padded K / 16 */, int columns,
+__global__ __launch_bounds__(256) void expand_fwd_kernel(const uint32_t* __restrict__ packed, ScaleParts alpha, uint32_t blocks,
+                                                         int64_t N, int64_t K, int64_t g, int q,
+                                                         int64_t R16 /* padded K / 16 */, int columns,
                                                          u32x4* __restrict__ frag) {
+    if (blockIdx.x >= blocks) {
+        join_scales(alpha, N * (K / g), q, (blockIdx.x - blocks) * gridDim.y + blockIdx.y);
+        return;
+    }
     uint32_t block = blockIdx.x, run = blockIdx.y;  // plain: 8 rows x a run of 32 words (the divisions cost 0.4 us of 5)
     if (columns) {
         const uint32_t runs = (uint32_t)((R16 / 2 + 31) / 32);
@@ -116,7 +141,8 @@ __global__ __launch_bounds__(256) void expand_fwd_kernel(const uint32_t* __restr
 #pragma unroll
     for (int i = 0; i < P; ++i) {
         if (Q || i < q) {
-            a[i] = live ? alpha[((int64_t)i * N + n) * G + grp] : 0.f;
+            const float* scales = i < alpha.q_first ? alpha.first + i * N * G : alpha.rest + (i - alpha.q_first) * N * G;
+            a[i] = live ? scales[n * G + grp] : 0.f;
             bits[i] = live ? packed[((int64_t)i * N + n) * Kw + w] : 0u;
         }
     }
@@ -142,17 +168,74 @@ __global__ __launch_bounds__(256) void expand_fwd_kernel(const uint32_t* __restr
     }
 }
 
+// dalpha[pn][grp] = scale * sum over token slices and over the k tiles of group grp of part[slice][tile][pn],
+// pn = plane * N + n; `run` consecutive k tiles form one scale group (row-wise: all of them, G = 1).  Fine: partials
+// part[slice][pn][per_slice] (one value per 32 columns), a group is a run of `run` consecutive values.
+// A workgroup owns 64 consecutive outputs; its four waves each add a quarter of the partial sums (every fourth one,
+// eight loads in flight) and wave 0 adds the four quarters in wave order: a fixed order, bit-reproducible.
+struct DalphaSums {
+    const float* part;
+    float* dalpha;
+    int64_t rows /* q_train * N */, G, per_slice /* k tiles, or 32-column values */;
+    int splits, run;
+    float scale;
+    bool fine;
+    AdamWArgs opt;
+};
+__device__ __forceinline__ void dalpha_reduce(const DalphaSums& a, uint32_t block, float (*quarter)[64]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, run = a.run;
+    const int64_t idx = (int64_t)block * 64 + lane;
+    const bool live = idx < a.rows * a.G;
+    const int64_t pn = live ? idx / a.G : 0, grp = live ? idx % a.G : 0;
+    const int items = a.splits * run;  // item it = (slice it / run, value it % run of the group)
+    float s = 0.f;
+    int it = wave;
+    if (a.fine) {
+        for (; it < items; it += 4) s += a.part[((int64_t)(it / run) * a.rows + pn) * a.per_slice + grp * run + it % run];
+    } else {
+        for (; it + 28 < items; it += 32) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int iu = it + 4 * u;
+                v[u] = a.part[((int64_t)(iu / run) * a.per_slice + grp * run + iu % run) * a.rows + pn];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+        for (; it < items; it += 4) s += a.part[((int64_t)(it / run) * a.per_slice + grp * run + it % run) * a.rows + pn];
+    }
+    quarter[wave][lane] = s;
+    __syncthreads();
+    if (wave != 0 || !live) return;
+    const float total = a.scale * ((quarter[0][lane] + quarter[1][lane]) + (quarter[2][lane] + quarter[3][lane]));
+    a.dalpha[idx] = total;
+    if (a.opt.alpha) adamw_apply(a.opt, idx, total);
+}
+
+__global__ __launch_bounds__(256) void dalpha_reduce_kernel(DalphaSums a) {
+    __shared__ float quarter[4][64];
+    dalpha_reduce(a, blockIdx.x, quarter);
+}
+static unsigned dalpha_reduce_blocks(const DalphaSums& a) { return (unsigned)((a.rows * a.G + 63) / 64); }
+
 // The same for the input gradient (columns of the GEMM = columns k, contraction = n), up to four planes: a thread expands 32
 // columns of one row n with that row's table, the tile of 32 rows x 256 columns goes through LDS, and ds_read_b64_tr_b16
 // returns it with the rows innermost.  (With the bits running along n, as in the twin, every weight of a word has scales of
 // its own: signed sums, 12.5 operations per weight.  10240 x 2560, q = 4: 18.1 -> 11.8 us, 8192 x 2048, q = 3 11.2 -> 8.0,
 // 4096 x 1024 6.8 -> 6.4.)
+// Blocks from `blocks` on reduce the scale gradient of the same backward pass, whose partial sums the launch before left:
+// that is 4 to 5 us of two dependent trips to memory by a few workgroups, in a launch of its own or hidden in this one.
 template <int Q>
 __global__ __launch_bounds__(256) void expand_bwd_rows_kernel(const uint32_t* __restrict__ packed,
                                                               const float* __restrict__ alpha, int64_t N, int64_t K,
                                                               int64_t g, int64_t R16 /* padded N / 16 */, int columns,
-                                                              u32x4* __restrict__ frag) {
+                                                              u32x4* __restrict__ frag, uint32_t blocks, DalphaSums sums) {
     __shared__ __attribute__((aligned(16))) unsigned char tile[32 * 512];  // rows of 256 columns, in 32-byte pieces c ^ swz(row)
+    if (blockIdx.x >= blocks) {
+        dalpha_reduce(sums, blockIdx.x - blocks, reinterpret_cast<float(*)[64]>(tile));
+        return;
+    }
     const int r = threadIdx.x >> 3, wl = threadIdx.x & 7;
     const int64_t Kw = K / 32, G = K / g;
     const uint32_t row_tiles = (uint32_t)(R16 / 2);
@@ -704,14 +787,16 @@ static hipError_t launch_gemm(const GemmPlan& pl, const bf16_t* A, int64_t lda, 
     }
 }
 
-hipError_t launch_fwd_mfma(const uint32_t* packed, const float* alpha, const void* x, int64_t T, int64_t N,
+hipError_t launch_fwd_mfma(const uint32_t* packed, const ScaleParts& alpha, const void* x, int64_t T, int64_t N,
                            int64_t K, int64_t g, int q, void* y, void* workspace, hipStream_t st) {
     const int64_t R16 = round_up(K, RPAD) / 16;
     const GemmPlan pl = gemm_plan(T, N, K);
     const int64_t blocks = (N + 31) / 32 * 4, runs = (R16 / 2 + 31) / 32;
-    const dim3 grid = pl.columns() ? dim3(xcd_grid(blocks * runs)) : dim3((unsigned)blocks, (unsigned)runs);
+    dim3 grid = pl.columns() ? dim3(xcd_grid(blocks * runs)) : dim3((unsigned)blocks, (unsigned)runs);
+    const unsigned expand_blocks = grid.x;
+    if (alpha.joined) grid.x += (unsigned)(((int64_t)q * N * (K / g) + 2048 * grid.y - 1) / (2048 * grid.y));
 #define BCQ_EXPAND(Q) \
-    BCQ_LAUNCH(expand_fwd_kernel<Q>, grid, dim3(256), 0, st, packed, alpha, N, K, g, q, R16, (int)pl.columns(), (u32x4*)workspace)
+    BCQ_LAUNCH(expand_fwd_kernel<Q>, grid, dim3(256), 0, st, packed, alpha, expand_blocks, N, K, g, q, R16, (int)pl.columns(), (u32x4*)workspace)
     switch (q) {
         case 1: BCQ_EXPAND(1); break;
         case 2: BCQ_EXPAND(2); break;
@@ -730,15 +815,20 @@ static dim3 expand_bwd_grid(int64_t K, int64_t R16) { return dim3(xcd_grid(K / 3
 // q = 5, 10002 rows: 20.5 us in plain order, 26 with eighths of two and three).
 static bool even_eighths(int64_t K) { return (K / 32 + 7) / 8 * 8 * 15 <= K / 32 * 16; }
 
-hipError_t launch_bwd_input_mfma(const uint32_t* packed, const uint32_t* packed_t, const float* alpha, const void* dy,
-                                 int64_t T, int64_t N, int64_t K, int64_t g, int q, void* dx, void* workspace,
-                                 hipStream_t st) {
+// sums != nullptr (up to four planes): the expansion's launch also reduces a scale gradient
+static hipError_t launch_input_product(const uint32_t* packed, const uint32_t* packed_t, const float* alpha, const void* dy,
+                                       int64_t T, int64_t N, int64_t K, int64_t g, int q, void* dx, void* workspace,
+                                       const DalphaSums* sums, hipStream_t st) {
     const int64_t R16 = round_up(N, RPAD) / 16;
     u32x4* frag = (u32x4*)workspace;
     const GemmPlan pl = gemm_plan(T, K, N);
     const int columns = pl.columns();
-    const dim3 rows_grid(xcd_grid(R16 / 2 * ((K / 32 + 7) / 8)));
-#define BCQ_EXPAND(Q) BCQ_LAUNCH(expand_bwd_rows_kernel<Q>, rows_grid, dim3(256), 0, st, packed, alpha, N, K, g, R16, columns, frag)
+    const unsigned rows_blocks = xcd_grid(R16 / 2 * ((K / 32 + 7) / 8));
+    const DalphaSums reduce = sums ? *sums : DalphaSums{};
+    const dim3 rows_grid(rows_blocks + (sums ? dalpha_reduce_blocks(reduce) : 0u));
+#define BCQ_EXPAND(Q)                                                                                                      \
+    BCQ_LAUNCH(expand_bwd_rows_kernel<Q>, rows_grid, dim3(256), 0, st, packed, alpha, N, K, g, R16, columns, frag, rows_blocks, \
+               reduce)
     switch (q) {
         case 1: BCQ_EXPAND(1); break;
         case 2: BCQ_EXPAND(2); break;
@@ -756,6 +846,12 @@ hipError_t launch_bwd_input_mfma(const uint32_t* packed, const uint32_t* packed_
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_gemm(pl, (const bf16_t*)dy, N, frag, (bf16_t*)dx, K, T, K, N, R16, st);
+}
+
+hipError_t launch_bwd_input_mfma(const uint32_t* packed, const uint32_t* packed_t, const float* alpha, const void* dy,
+                                 int64_t T, int64_t N, int64_t K, int64_t g, int q, void* dx, void* workspace,
+                                 hipStream_t st) {
+    return launch_input_product(packed, packed_t, alpha, dy, T, N, K, g, q, dx, workspace, nullptr, st);
 }
 
 // Input gradient with fp32 weights for row counts that launch_bwd_input_mfma does not take and that have no twin (N % 32 != 0):
@@ -800,7 +896,7 @@ hipError_t launch_bwd_input_mfma_split(const uint32_t* packed, const float* alph
 //      those of gemm_kernel, and so is what bounds it: power with all compute units busy (8192 x 2048 at 16384 tokens,
 //      q = 3, the whole call 490 -> 404 us, 6144 x 2048 463 -> 322, 3072 x 1024 at 4096 tokens 41 -> 33).  The epilogue forms the signed sums
 //      over k for every trained plane.
-//   2. dalpha_reduce_kernel adds the partial sums of all (token slice, k tile) pairs in a fixed order (no
+//   2. dalpha_reduce adds the partial sums of all (token slice, k tile) pairs in a fixed order (no
 //      floating-point atomics, bit-reproducible).
 
 // Rows of 64 tokens, BK or BN columns wide, in 32-byte pieces (16 columns) with piece c of token t at c ^ da_swizzle(t): the
@@ -824,7 +920,7 @@ struct DalphaCfg : DalphaShape<TILE> {
 
 // QT: planes summed in the epilogue (q_train rounded up to 1, 2, 3, 4 or 8; extra planes are computed, not stored).
 // FINE: partial sums are kept per 32 columns k (for scale groups that are not whole tiles) instead of per tile; they
-//       go to part[split][plane][n][TILE / 32 tiles_k] and dalpha_reduce_fine_kernel adds each group's run.
+//       go to part[split][plane][n][TILE / 32 tiles_k] and the reduction adds each group's run.
 template <int TILE, int QT, bool FINE>
 __global__ __launch_bounds__((64 * DalphaCfg<TILE>::NW), 2) void dalpha_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy, int64_t ldy, const uint32_t* __restrict__ packed,
@@ -1047,63 +1143,6 @@ __global__ __launch_bounds__((64 * DalphaCfg<TILE>::NW), 2) void dalpha_kernel(
 #endif
 }
 
-// dalpha[pn][grp] = scale * sum over token slices and over the k tiles of group grp of part[slice][tile][pn],
-// pn = plane * N + n; `tpg` consecutive k tiles form one scale group (row-wise: all of them, G = 1).
-// A workgroup owns 64 consecutive outputs; its four waves each add a quarter of the partial sums (every fourth one,
-// eight loads in flight) and wave 0 adds the four quarters in wave order: a fixed order, bit-reproducible.
-__global__ __launch_bounds__(256) void dalpha_reduce_kernel(const float* __restrict__ part, float* __restrict__ dalpha,
-                                                            int64_t rows /* q_train * N */, int64_t G, int splits,
-                                                            int tiles_k, int tpg, float scale, AdamWArgs opt) {
-    __shared__ float quarter[4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t idx = (int64_t)blockIdx.x * 64 + lane;
-    const bool live = idx < rows * G;
-    const int64_t pn = live ? idx / G : 0, grp = live ? idx % G : 0;
-    const int items = splits * tpg;  // item it = (slice it / tpg, tile it % tpg of the group)
-    float s = 0.f;
-    int it = wave;
-    for (; it + 28 < items; it += 32) {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int iu = it + 4 * u;
-            v[u] = part[((int64_t)(iu / tpg) * tiles_k + grp * tpg + iu % tpg) * rows + pn];
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) s += v[u];
-    }
-    for (; it < items; it += 4) s += part[((int64_t)(it / tpg) * tiles_k + grp * tpg + it % tpg) * rows + pn];
-    quarter[wave][lane] = s;
-    __syncthreads();
-    if (wave != 0 || !live) return;
-    const float total = scale * ((quarter[0][lane] + quarter[1][lane]) + (quarter[2][lane] + quarter[3][lane]));
-    dalpha[idx] = total;
-    if (opt.alpha) adamw_apply(opt, idx, total);
-}
-
-// Fine partials part[slice][pn][Kc] (one value per 32 columns): a group is a run of cpg consecutive values.
-// Same split of the work as above: item it = (slice it / cpg, value it % cpg of the run).
-__global__ __launch_bounds__(256) void dalpha_reduce_fine_kernel(const float* __restrict__ part,
-                                                                 float* __restrict__ dalpha, int64_t rows, int64_t G,
-                                                                 int splits, int64_t Kc, int cpg, float scale,
-                                                                 AdamWArgs opt) {
-    __shared__ float quarter[4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t idx = (int64_t)blockIdx.x * 64 + lane;
-    const bool live = idx < rows * G;
-    const int64_t pn = live ? idx / G : 0, grp = live ? idx % G : 0;
-    const int items = splits * cpg;
-    float s = 0.f;
-    for (int it = wave; it < items; it += 4)
-        s += part[((int64_t)(it / cpg) * rows + pn) * Kc + grp * cpg + it % cpg];
-    quarter[wave][lane] = s;
-    __syncthreads();
-    if (wave != 0 || !live) return;
-    const float total = scale * ((quarter[0][lane] + quarter[1][lane]) + (quarter[2][lane] + quarter[3][lane]));
-    dalpha[idx] = total;
-    if (opt.alpha) adamw_apply(opt, idx, total);
-}
-
 // Bytes of scratch that a call may use for its partial sums: what callers have been told since the kernel also kept a
 // transposed copy of the smaller activation there (which bounds the token slices only where T or both dimensions are small).
 struct DalphaBudget {
@@ -1236,9 +1275,10 @@ static hipError_t launch_dalpha_tile(const uint32_t* packed, const bf16_t* x, co
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_alpha_mfma(const uint32_t* packed, const void* x, const void* dy, int64_t T, int64_t N,
-                                 int64_t K, int64_t g, int q, int q_train, float grad_scale, float* dalpha,
-                                 void* workspace, const AdamWArgs* opt, hipStream_t st) {
+// Partial sums of all tokens into the workspace; *out: what is left to reduce
+static hipError_t launch_dalpha_sums(const uint32_t* packed, const void* x, const void* dy, int64_t T, int64_t N, int64_t K,
+                                     int64_t g, int q, int q_train, float grad_scale, float* dalpha, void* workspace,
+                                     DalphaSums* out, hipStream_t st) {
     const DalphaScratch sc = dalpha_scratch(T, N, K, g, q);
     const int64_t piece = dalpha_piece(T, N), dcols = sc.pad ? round_up(N, 8) : N;
     unsigned char* ws = static_cast<unsigned char*>(workspace);
@@ -1265,17 +1305,37 @@ hipError_t launch_bwd_alpha_mfma(const uint32_t* packed, const void* x, const vo
         next += (int64_t)pl.splits * pl.tiles_k * q_train * N * (pl.fine ? pl.tile / 32 : 1);
         splits += pl.splits;
     }
-    const int64_t rows = (int64_t)q_train * N, G = K / g;
-    const dim3 rgrid((unsigned)((rows * G + 63) / 64));
-    AdamWArgs oa = {};
-    if (opt) oa = *opt;
-    if (pl.fine)
-        BCQ_LAUNCH(dalpha_reduce_fine_kernel, rgrid, dim3(256), 0, st, (const float*)part, dalpha, rows, G,
-                           splits, (int64_t)pl.tiles_k * (pl.tile / 32), (int)(g / 32), grad_scale, oa);
-    else
-        BCQ_LAUNCH(dalpha_reduce_kernel, rgrid, dim3(256), 0, st, (const float*)part, dalpha, rows, G,
-                           splits, pl.tiles_k, (int)(g == K ? pl.tiles_k : g / pl.tile), grad_scale, oa);
+    *out = {};
+    out->part = part;
+    out->dalpha = dalpha;
+    out->rows = (int64_t)q_train * N;
+    out->G = K / g;
+    out->splits = splits;
+    out->scale = grad_scale;
+    out->fine = pl.fine;
+    out->per_slice = pl.fine ? (int64_t)pl.tiles_k * (pl.tile / 32) : pl.tiles_k;
+    out->run = pl.fine ? (int)(g / 32) : (int)(g == K ? pl.tiles_k : g / pl.tile);
+    return hipSuccess;
+}
+
+hipError_t launch_bwd_alpha_mfma(const uint32_t* packed, const void* x, const void* dy, int64_t T, int64_t N,
+                                 int64_t K, int64_t g, int q, int q_train, float grad_scale, float* dalpha,
+                                 void* workspace, const AdamWArgs* opt, hipStream_t st) {
+    DalphaSums sums;
+    hipError_t e = launch_dalpha_sums(packed, x, dy, T, N, K, g, q, q_train, grad_scale, dalpha, workspace, &sums, st);
+    if (e != hipSuccess) return e;
+    if (opt) sums.opt = *opt;
+    BCQ_LAUNCH(dalpha_reduce_kernel, dim3(dalpha_reduce_blocks(sums)), dim3(256), 0, st, sums);
     return hipGetLastError();
+}
+
+hipError_t launch_bwd_mfma(const uint32_t* packed, const float* alpha, const void* x, const void* dy, int64_t T, int64_t N, int64_t K,
+                           int64_t g, int q, int q_train, float grad_scale, void* dx, void* input_workspace, float* dalpha,
+                           void* alpha_workspace, hipStream_t st) {
+    DalphaSums sums;
+    hipError_t e = launch_dalpha_sums(packed, x, dy, T, N, K, g, q, q_train, grad_scale, dalpha, alpha_workspace, &sums, st);
+    if (e != hipSuccess) return e;
+    return launch_input_product(packed, nullptr, alpha, dy, T, N, K, g, q, dx, input_workspace, &sums, st);
 }
 
 }  // namespace bcq

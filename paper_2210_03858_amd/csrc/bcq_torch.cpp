@@ -17,6 +17,7 @@
 #include <torch/extension.h>
 
 #include "../../include/bcq.h"
+#include "bcq_node.h"
 
 namespace {
 
@@ -169,7 +170,11 @@ struct BCQLinearNode : public torch::autograd::Function<BCQLinearNode> {
     static Tensor forward(torch::autograd::AutogradContext* ctx, const Tensor& x, const Tensor& alpha_train,
                           const Frozen& f) {
         const Shape s = layer_shape(f.packed, f.g);
-        const Tensor alpha = (f.alpha.defined() ? at::cat({alpha_train, f.alpha}, 0) : alpha_train).contiguous();
+        // scales in two plain tensors are joined by the forward's kernels
+        const bool parts = f.alpha.defined() && s.ok && f.q_train >= 1 && f.q_train < s.q && !alpha_train.is_neg() && !f.alpha.is_neg() &&
+                           plain(alpha_train, at::kFloat, {f.q_train, s.N, s.G}) && plain(f.alpha, at::kFloat, {s.q - f.q_train, s.N, s.G});
+        const Tensor alpha = parts ? at::empty({s.q, s.N, s.G}, f.alpha.options())
+                                   : (f.alpha.defined() ? at::cat({alpha_train, f.alpha}, 0) : alpha_train).contiguous();
         const Tensor x2 = x.reshape({-1, s.K}).contiguous();
         const int64_t T = x2.size(0);
         const int code = act_code(x2);
@@ -179,8 +184,13 @@ struct BCQLinearNode : public torch::autograd::Function<BCQLinearNode> {
         const Tensor ws = scratch(BCQ_OP_FWD, T, s, f.g, code, x2, &st);
         if (st != BCQ_OK) throw Refused{};
         Tensor y = at::empty({T, s.N}, x2.options());
-        st = bcq_linear_fwd_grouped(words(f.packed), alpha.data_ptr<float>(), x2.data_ptr(), code, T, s.N, s.K, f.g,
-                                    (int)s.q, y.data_ptr(), ws.data_ptr(), (size_t)ws.numel(), current_stream());
+        if (parts)
+            st = bcq_node_forward(words(f.packed), alpha_train.data_ptr<float>(), (int)f.q_train, f.alpha.data_ptr<float>(),
+                                  alpha.data_ptr<float>(), x2.data_ptr(), code, T, s.N, s.K, f.g, (int)s.q, y.data_ptr(),
+                                  ws.data_ptr(), (size_t)ws.numel(), current_stream());
+        else
+            st = bcq_linear_fwd_grouped(words(f.packed), alpha.data_ptr<float>(), x2.data_ptr(), code, T, s.N, s.K, f.g,
+                                        (int)s.q, y.data_ptr(), ws.data_ptr(), (size_t)ws.numel(), current_stream());
         if (st != BCQ_OK) throw Refused{};
         ctx->save_for_backward({x2, alpha});
         ctx->saved_data["packed"] = f.packed;
@@ -207,30 +217,37 @@ struct BCQLinearNode : public torch::autograd::Function<BCQLinearNode> {
         TORCH_CHECK_VALUE(s.ok && code >= 0 && plain(dy, x2.scalar_type(), {T, s.N}) &&
                               plain(x2, x2.scalar_type(), {T, s.K}) && plain(alpha, at::kFloat, {s.q, s.N, s.G}),
                           "dy must be a contiguous cuda tensor of the activations' dtype");
-        Tensor dx, dalpha;
+        const auto twin = ctx->saved_data.find("twin");
+        const uint32_t* packed_t = twin == ctx->saved_data.end() ? nullptr : words(twin->second.toTensor());
+        const float grad_scale = (float)ctx->saved_data["grad_scale"].toDouble();
+        Tensor dx, dalpha, ws_x, ws_alpha;
         bcq_status st = BCQ_OK;
         if (ctx->needs_input_grad(0)) {
-            const auto twin = ctx->saved_data.find("twin");
-            const Tensor ws = scratch(BCQ_OP_BWD_INPUT, T, s, g, code, dy, &st);
+            ws_x = scratch(BCQ_OP_BWD_INPUT, T, s, g, code, dy, &st);
             if (st != BCQ_OK) raise_bcq_error(st, "bcq_workspace_bytes_grouped");
             dx = at::empty({T, s.K}, dy.options());
-            st = bcq_linear_bwd_input_grouped(words(packed),
-                                              twin == ctx->saved_data.end() ? nullptr : words(twin->second.toTensor()),
-                                              alpha.data_ptr<float>(), dy.data_ptr(), code, T, s.N, s.K, g, (int)s.q,
-                                              dx.data_ptr(), ws.data_ptr(), (size_t)ws.numel(), current_stream());
-            if (st != BCQ_OK) raise_bcq_error(st, "bcq_linear_bwd_input_grouped");
-            dx = dx.reshape(ctx->saved_data["x_shape"].toIntVector());
         }
         if (ctx->needs_input_grad(1)) {
-            const Tensor ws = scratch(BCQ_OP_BWD_ALPHA, T, s, g, code, dy, &st);
+            ws_alpha = scratch(BCQ_OP_BWD_ALPHA, T, s, g, code, dy, &st);
             if (st != BCQ_OK) raise_bcq_error(st, "bcq_workspace_bytes_grouped");
             dalpha = at::empty({q_train, s.N, s.G}, dy.options().dtype(at::kFloat));
+        }
+        if (dx.defined() && dalpha.defined()) {
+            st = bcq_node_backward(words(packed), packed_t, alpha.data_ptr<float>(), x2.data_ptr(), dy.data_ptr(), code, T, s.N, s.K,
+                                   g, (int)s.q, (int)q_train, grad_scale, dx.data_ptr(), ws_x.data_ptr(), (size_t)ws_x.numel(),
+                                   dalpha.data_ptr<float>(), ws_alpha.data_ptr(), (size_t)ws_alpha.numel(), current_stream());
+            if (st != BCQ_OK) raise_bcq_error(st, "bcq_linear_bwd");
+        } else if (dx.defined()) {
+            st = bcq_linear_bwd_input_grouped(words(packed), packed_t, alpha.data_ptr<float>(), dy.data_ptr(), code, T, s.N, s.K, g,
+                                              (int)s.q, dx.data_ptr(), ws_x.data_ptr(), (size_t)ws_x.numel(), current_stream());
+            if (st != BCQ_OK) raise_bcq_error(st, "bcq_linear_bwd_input_grouped");
+        } else if (dalpha.defined()) {
             st = bcq_linear_bwd_alpha_grouped(words(packed), x2.data_ptr(), dy.data_ptr(), code, T, s.N, s.K, g, (int)s.q,
-                                              (int)q_train, (float)ctx->saved_data["grad_scale"].toDouble(),
-                                              dalpha.data_ptr<float>(), ws.data_ptr(), (size_t)ws.numel(),
-                                              current_stream());
+                                              (int)q_train, grad_scale, dalpha.data_ptr<float>(), ws_alpha.data_ptr(),
+                                              (size_t)ws_alpha.numel(), current_stream());
             if (st != BCQ_OK) raise_bcq_error(st, "bcq_linear_bwd_alpha_grouped");
         }
+        if (dx.defined()) dx = dx.reshape(ctx->saved_data["x_shape"].toIntVector());
         return {dx, dalpha, Tensor()};
     }
 };
