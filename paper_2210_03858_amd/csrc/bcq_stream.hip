@@ -212,14 +212,20 @@ static hipError_t launch_fused(const uint32_t* planes, const bf16_t* act, const 
 // where there are several tokens (8 tokens, q = 4, of 7680 x 2560: 10.0 -> 7.2 us), and costs up to 1.5 us where it leaves compute units without a
 // workgroup or puts 16 waves into one (1024 x 4096, q = 3, one token 4.2 -> 5.3).  More than 512 row tiles: three, which keeps the workgroups
 // to one round (10240 x 2560, q = 4, 8 tokens: two 12.3, three 8.4).
+// Up to 256 row tiles take up to 16 segments at a time instead of 8: a turn is a whole trip to memory and through the re-coding (one token of 1280 x
+// 5120, q = 4, 5.3 -> 4.7 us, four 7.6 -> 6.5; groups of 128 11.5 -> 9.8, 2048 x 8192, q = 3, 12.3 -> 11.2).  Beyond them the larger workgroups
+// take a second round (5120 x 5120, groups of 128, four tokens 7.4 -> 10.5); 15 and 16 waves gain nothing at one token
+// (2048 x 8192, q = 4, 6.2 -> 6.4).
 struct FewPlan {
     int W, R;
 };
-static FewPlan few_plan(int64_t T, int64_t rows, int segs, bool rowwise) {
+static FewPlan few_plan(int64_t T, int64_t rows, int segs, bool rowwise, int scale_bytes) {
     FewPlan p;
-    const int most = segs < 8 ? segs : 8, turns = (segs + most - 1) / most;
-    p.W = (segs + turns - 1) / turns;
     const int64_t tiles = (rows + 15) / 16;
+    const auto waves = [&](int most) { const int turns = (segs + most - 1) / most; return (segs + turns - 1) / turns; };
+    p.W = waves(8);
+    const bool room = tiles <= 256 && 16 * (FEW_STAGE + scale_bytes) <= 160 * 1024;
+    if (room && !(rowwise && T == 1 && waves(16) > 14)) p.W = waves(16);
     bool share = T >= 3 && p.W < 8;
     if (!rowwise) share = share && tiles > (T <= 4 ? 256 : p.W <= 3 ? 0 : 128);
     p.R = !share ? 1 : tiles > 512 && p.W <= 5 ? 3 : 2;
@@ -241,7 +247,7 @@ template <int QP, int NT, bool TILED, int SUB>
 static hipError_t launch_few_cfg(const uint32_t* planes, const bf16_t* act, const float* alpha, bf16_t* y, int64_t T, int64_t rows, int64_t cw,
                                  int64_t g, int segs, const FewPlan& p, hipStream_t st) {
     const size_t lds = (size_t)p.W * FEW_STAGE + (size_t)p.W * p.R * few_scale_bytes<QP, SUB>();
-    static_assert(8 * FEW_STAGE + 16 * few_scale_bytes<QP, SUB>() <= 160 * 1024, "at most 16 waves");
+    if (lds > 160 * 1024) return hipErrorInvalidConfiguration;
     static LdsLimit limit;
     hipError_t e = limit.ensure((const void*)few_fwd_kernel<QP, NT, TILED, SUB>, lds);
     if (e != hipSuccess) return e;
@@ -254,7 +260,7 @@ template <bool TILED>
 static hipError_t launch_few(const uint32_t* planes, const bf16_t* act, const float* alpha, bf16_t* y, int64_t T, int64_t rows, int64_t cw, int q,
                              int64_t g, hipStream_t st) {
     const int segs = (int)((cw + 15) / 16), sub = g == cw * 32 ? 0 : g % 128 == 0 ? 1 : 2;
-    const FewPlan p = few_plan(T, rows, segs, sub == 0);
+    const FewPlan p = few_plan(T, rows, segs, sub == 0, 256 * sub * q);
     const int64_t NT = (T + p.R - 1) / p.R;
     if (T > 8 || p.W * p.R > 16 || p.W * p.R < 1) return hipErrorInvalidConfiguration;
 #define BCQ_FEW(QQ, TT, SS) return launch_few_cfg<QQ, TT, TILED, SS>(planes, act, alpha, y, T, rows, cw, g, segs, p, st);

@@ -56,6 +56,14 @@ def test_few_tokens_in_one_kernel(layout, T, N, K, g, q):
     assert ((y - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * ref.abs().max()).all()
 
 
+@pytest.mark.parametrize("layout,T,N,K,g,q", [
+    ("decode", 1, 40, 7168, 7168, 4), ("decode", 1, 40, 7200, 7200, 3), ("decode", 2, 4096, 7712, 7712, 4), ("decode", 2, 4112, 7712, 7712, 4),
+    ("canonical", 4, 100, 8192, 128, 4), ("canonical", 1, 4112, 4608, 384, 2), ("canonical", 2, 4080, 4224, 128, 1)])
+def test_up_to_sixteen_segments_at_a_time(layout, T, N, K, g, q):
+    """Both sides of the lines between 8 and 16 waves, and the largest workgroup."""
+    test_few_tokens_in_one_kernel(layout, T, N, K, g, q)
+
+
 @pytest.mark.parametrize("layout,T,N,K,g,q", [("decode", 8, 600, 1056, 1056, 3), ("canonical", 5, 4200, 1024, 128, 2), ("canonical", 4, 100, 1152, 64, 4)])
 def test_non_finite_token_and_zero_blocks(layout, T, N, K, g, q):
     """A non-finite activation makes its own token's results NaN; blocks of zeros, a block of subnormals and one of large values
