@@ -403,20 +403,22 @@ hipError_t launch_fwd_stream_decode(const uint32_t* tiled, const float* alpha, c
 
 // canonical packed[q][N][K/32] -> decode layout [N/16 up][K/512 up][q][64 lanes][4 words]; lane = (n % 16) + 16 g holds
 // words 16 seg + 4 g .. + 3 of row n; rows and columns beyond the matrix read as 0 bits
-// A wave writes one KiB (row tile, segment, plane) of each of two planes; the grid is (four segments, row tile, pair of planes),
-// so that no lane divides.  The stores are nontemporal: nothing reads the layout soon (10240 x 2560, q = 4: 6.9 -> 6.6 us, 2560 x
-// 10240 5.7 -> 4.9; one plane to a wave 6.7 and 5.4, four 6.3 and 5.2, plain stores with any of them as before; a copy of the 26 MB
-// takes 4.9).  Rows of one or two segments put 1 << tiles_log2 row tiles into a workgroup instead: it is the workgroups' launch rate
-// that bounds them (131072 x 64, q = 8: 14 us with a division per lane, 31 us with one busy wave to a workgroup, of 64 or of
-// 256 threads, 13 us so).  QUAD: rows of whole 16-byte units (cw % 4 == 0), one load per lane.
+// A wave writes one KiB (row tile, segment, plane) of each of two planes.  The units (row tile, segment) are counted through, four to a
+// workgroup, so that no wave is left without one (with a grid over segments and row tiles 3 of 8 waves were, at 5 segments: 10240 x 2560,
+// q = 4, 7.0 us, now 5.9; 7680 x 2560 5.4 / 5.0; 15 segments, whose rows now straddle workgroups, 4.8 / 5.0).  unit / segs is the high word of unit * inverse, the inverse 2^32 / segs rounded up, exact for units below
+// 2^24 (0 stands for 2^32).  The stores are nontemporal: nothing reads the layout soon (10240 x 2560, q = 4: 6.9 -> 6.6 us,
+// 2560 x 10240 5.7 -> 4.9; one plane to a wave 6.7 and 5.4, four 6.3 and 5.2, plain stores with any of them as before; a copy of the
+// 26 MB takes 4.9).  QUAD: rows of whole 16-byte units (cw % 4 == 0), one load per lane.
 template <bool QUAD>
-__global__ __launch_bounds__(256) void pack_decode_kernel(const uint32_t* __restrict__ packed, int64_t N, int cw, int segs, int tiles_log2,
-                                                          int q, q_u32x4* __restrict__ tiled) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, segs_log2 = 2 - tiles_log2;
-    const int seg = (int)(blockIdx.x << segs_log2) + (wave & ((1 << segs_log2) - 1));
-    const int64_t rt = ((int64_t)blockIdx.y << tiles_log2) + (wave >> segs_log2), n = rt * 16 + (lane & 15);
-    if (seg >= segs || rt * 16 >= N) return;
-    const int w0 = 16 * seg + 4 * (lane >> 4), i0 = 2 * (int)blockIdx.z;
+__global__ __launch_bounds__(256) void pack_decode_kernel(const uint32_t* __restrict__ packed, int64_t N, int cw, uint32_t segs, uint32_t inverse,
+                                                          uint32_t units, int q, q_u32x4* __restrict__ tiled) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t unit = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (unit >= units) return;
+    const uint32_t rt = inverse ? __umulhi(unit, inverse) : unit;
+    const int seg = (int)(unit - rt * segs);
+    const int64_t n = (int64_t)rt * 16 + (lane & 15);
+    const int w0 = 16 * seg + 4 * (lane >> 4), i0 = 2 * (int)blockIdx.y;
     q_u32x4 v[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
     if (n < N) {
 #pragma unroll
@@ -432,7 +434,7 @@ __global__ __launch_bounds__(256) void pack_decode_kernel(const uint32_t* __rest
             }
         }
     }
-    q_u32x4* dst = tiled + ((rt * segs + seg) * q + i0) * 64 + lane;
+    q_u32x4* dst = tiled + ((int64_t)unit * q + i0) * 64 + lane;
 #pragma unroll
     for (int p = 0; p < 2; ++p)
         if (i0 + p < q) __builtin_nontemporal_store(v[p], dst + p * 64);
@@ -443,13 +445,14 @@ size_t decode_layout_bytes(int64_t N, int64_t K, int q) {
 }
 
 hipError_t launch_pack_decode(const uint32_t* packed, int64_t N, int64_t K, int q, uint32_t* tiled, hipStream_t st) {
-    const int segs = (int)((K + 511) / 512), cw = (int)(K / 32);
-    const int tl = segs == 1 ? 2 : segs == 2 ? 1 : 0, rows = 16 << tl;
-    const dim3 grid((unsigned)((segs + 3) / 4), (unsigned)((N + rows - 1) / rows), (unsigned)((q + 1) / 2));
+    const int cw = (int)(K / 32);
+    const uint32_t segs = (uint32_t)((K + 511) / 512), units = (uint32_t)((N + 15) / 16) * segs;  // at most 2^13 * 2^8
+    const uint32_t inverse = (uint32_t)((((uint64_t)1 << 32) + segs - 1) / segs);
+    const dim3 grid((units + 3) / 4, (unsigned)((q + 1) / 2));
     if (cw % 4 == 0)
-        BCQ_LAUNCH(pack_decode_kernel<true>, grid, dim3(256), 0, st, packed, N, cw, segs, tl, q, reinterpret_cast<q_u32x4*>(tiled));
+        BCQ_LAUNCH(pack_decode_kernel<true>, grid, dim3(256), 0, st, packed, N, cw, segs, inverse, units, q, reinterpret_cast<q_u32x4*>(tiled));
     else
-        BCQ_LAUNCH(pack_decode_kernel<false>, grid, dim3(256), 0, st, packed, N, cw, segs, tl, q, reinterpret_cast<q_u32x4*>(tiled));
+        BCQ_LAUNCH(pack_decode_kernel<false>, grid, dim3(256), 0, st, packed, N, cw, segs, inverse, units, q, reinterpret_cast<q_u32x4*>(tiled));
     return hipGetLastError();
 }
 
