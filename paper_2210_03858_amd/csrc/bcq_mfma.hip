@@ -93,11 +93,16 @@ __device__ __forceinline__ void store_word_frags(const float (&s)[32], u32x4* __
 // the expansion's write that (a concatenation before the expansion was a launch of 4 to 6 us).
 __device__ __forceinline__ void join_scales(const ScaleParts& a, int64_t per_plane, int q, uint32_t chunk) {
     const int64_t split = a.q_first * per_plane, total = q * per_plane;
+    const int64_t idx0 = (int64_t)chunk * 2048 + threadIdx.x;
+    float v[8];  // all requested before the first is stored: one trip to memory
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const int64_t idx = (int64_t)chunk * 2048 + e * 256 + threadIdx.x;
-        if (idx < total) a.joined[idx] = idx < split ? a.first[idx] : a.rest[idx - split];
+        const int64_t idx = idx0 + e * 256;
+        if (idx < total) v[e] = idx < split ? a.first[idx] : a.rest[idx - split];
     }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        if (idx0 + e * 256 < total) a.joined[idx0 + e * 256] = v[e];
 }
 
 __global__ __launch_bounds__(256) void join_scales_kernel(ScaleParts a, int64_t per_plane, int q) {
