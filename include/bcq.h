@@ -46,7 +46,7 @@
  *   - Numerics of the bf16 paths (fp32 accumulation throughout; the bar of the tests is 2e-2 of the largest output):
  *     the matrix-core path (32 tokens and more, workspace given) first sums the planes into What = sum_i alpha_i B_i
  *     and rounds What to bf16 once (relative 2^-9 per weight) - a rounding Eq. 2 / Eq. 3 do not contain; alpha itself
- *     stays fp32.  The streaming paths (few tokens; at most 8 also with groups of whole 64 columns) multiply exact signs with activations split into two FP8 terms:
+ *     stays fp32.  The streaming paths (few tokens) multiply exact signs with activations split into two FP8 terms:
  *     exact for bf16 activations within 2^-13 of the largest of their 32-element block (forward, scale gradient); the
  *     input gradient re-codes the fp32 product dy * alpha_i and keeps 8 significant bits of it (relative 2^-9 per
  *     term).  No such rounding happens for fp32 activations and without a workspace: those sums are fp64, except that

@@ -281,8 +281,7 @@ static bcq_status fwd_impl(const uint32_t* packed, const float* alpha, const bcq
     hipStream_t st = (hipStream_t)stream;
     // the expansion reads the parts and joins them itself
     const bool streams = workspace && stream_fwd_ok(T, K, g, dtype);
-    const bool few = workspace && !rowwise && dtype == BCQ_BF16 && bcq::few_fwd_ok(T, N, K, g, q);
-    const bool expands = workspace && !streams && !small_fwd_ok(T, rowwise, dtype) && !few && mfma_fwd_ok(T, rowwise, dtype) &&
+    const bool expands = workspace && !streams && !small_fwd_ok(T, rowwise, dtype) && mfma_fwd_ok(T, rowwise, dtype) &&
                          !bcq::fused_fwd_ok(T, N, K, g, q);
     if (expands)
         return done(bcq::launch_fwd_mfma(packed, parts ? *parts : bcq::ScaleParts{alpha, nullptr, q, nullptr}, x, T, N, K, g, q, y,
@@ -294,8 +293,6 @@ static bcq_status fwd_impl(const uint32_t* packed, const float* alpha, const bcq
     if (streams)
         return done(bcq::launch_fwd_stream(packed, alpha, x, T, N, K, g, q, y, workspace, st));
     if (small_fwd_ok(T, rowwise, dtype)) return done(bcq::launch_fwd_small(packed, alpha, x, T, N, K, q, y, st));
-    if (few)
-        return done(bcq::launch_fwd_few(packed, alpha, x, T, N, K, g, q, y, st));
     if (workspace && mfma_fwd_ok(T, rowwise, dtype))
         return done(bcq::launch_fwd_fused(packed, alpha, x, T, N, K, g, q, y, workspace, st));
     return done(bcq::launch_fwd_generic(packed, alpha, x, dtype, T, N, K, g, q, y, st));

@@ -221,10 +221,6 @@ hipError_t launch_fwd_stream(const uint32_t* packed, const float* alpha, const v
                              int64_t K, int64_t g, int q, void* y, void* workspace, hipStream_t st);
 hipError_t launch_fwd_stream_decode(const uint32_t* tiled, const float* alpha, const void* x, int64_t T, int64_t N,
                                     int64_t K, int64_t g, int q, void* y, void* workspace, hipStream_t st);
-// forward of at most 8 tokens in one kernel (row-wise scales or groups of whole 64 columns); needs no workspace
-bool few_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q);
-hipError_t launch_fwd_few(const uint32_t* packed, const float* alpha, const void* x, int64_t T, int64_t N, int64_t K, int64_t g, int q,
-                          void* y, hipStream_t st);
 size_t decode_layout_bytes(int64_t N, int64_t K, int q);
 hipError_t launch_pack_decode(const uint32_t* packed, int64_t N, int64_t K, int q, uint32_t* tiled, hipStream_t st);
 hipError_t launch_bwd_alpha_stream(const uint32_t* packed, const void* x, const void* dy, int64_t T, int64_t N,

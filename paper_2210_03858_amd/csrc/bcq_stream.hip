@@ -213,9 +213,8 @@ static hipError_t launch_fused(const uint32_t* planes, const bf16_t* act, const 
 // workgroup or puts 16 waves into one (1024 x 4096, q = 3, one token 4.2 -> 5.3).  More than 512 row tiles: three, which keeps the workgroups
 // to one round (10240 x 2560, q = 4, 8 tokens: two 12.3, three 8.4).
 // Up to 256 row tiles take up to 16 segments at a time instead of 8: a turn is a whole trip to memory and through the re-coding (one token of 1280 x
-// 5120, q = 4, 5.3 -> 4.7 us, four 7.6 -> 6.5; groups of 128 11.5 -> 9.8, 2048 x 8192, q = 3, 12.3 -> 11.2).  Beyond them the larger workgroups
-// take a second round (5120 x 5120, groups of 128, four tokens 7.4 -> 10.5); 15 and 16 waves gain nothing at one token
-// (2048 x 8192, q = 4, 6.2 -> 6.4).
+// 5120, q = 4, 5.3 -> 4.7 us, four 7.6 -> 6.5).  Beyond them the larger workgroups take a second round (320 tiles: 1.1 to 1.4 times the
+// time); 15 and 16 waves gain nothing at one token (2048 x 8192, q = 4, 6.2 -> 6.4).
 struct FewPlan {
     int W, R;
 };
@@ -232,26 +231,24 @@ static FewPlan few_plan(int64_t T, int64_t rows, int segs, bool rowwise, int sca
     return p;
 }
 
-// Where it is faster than re-coding in a kernel of its own (row-wise scales and groups of 512; the re-coding is repeated by every R row
-// tiles) or than the bf16 kernel of few tokens (other groups): us, that / this: one token of 1024 x 1024, q = 3, 5.3 / 3.3, 10240 x 2560,
-// q = 4, 12.1 / 7.0, 2560 x 10240 10.6 / 7.8; four tokens 5.4 / 4.0, 12.2 / 7.2, 10.8 / 11.6, 2048 x 8192, q = 3, 8.1 / 8.0; eight tokens 5.6 / 4.4,
-// 12.3 / 8.4, 1024 x 4096 7.2 / 7.3, 1280 x 5120 7.3 / 8.9.  Groups of 128: four tokens of 6144 x 2048, q = 3, 9.9 / 6.6, 2048 x 8192
-// 12.6 / 11.7, eight 12.9 / 15.2; groups of 64, eight tokens 10.3 / 8.2.  Groups of 32 (four products for one) are as often slower.
-bool few_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
+// Where it is faster than re-coding in a kernel of its own (the re-coding is repeated by every R row tiles); groups are whole segments here.
+// us, that / this: one token of 1024 x 1024, q = 3, 5.3 / 3.3, 10240 x 2560, q = 4, 12.1 / 7.0, 2560 x 10240 10.6 / 7.8; four tokens 5.4 / 4.0,
+// 12.2 / 7.2, 10.8 / 11.6, 2048 x 8192, q = 3, 8.1 / 8.0; eight tokens 5.6 / 4.4, 12.3 / 8.4, 1024 x 4096 7.2 / 7.3, 1280 x 5120 7.3 / 8.9.
+static bool few_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
     if (T > 8 || q > 4 || N * K > 32000000) return false;
     if (g == K) return K <= (T <= 2 ? 12288 : T <= 4 ? 8192 : 4096);
-    return g % 64 == 0 && K <= (T > 4 ? 4096 : g % 128 == 0 ? 10240 : 4096);
+    return K <= (T > 4 ? 4096 : 10240);
 }
 
-template <int QP, int NT, bool TILED, int SUB>
+template <int QP, int NT, bool TILED, bool GROUPED>
 static hipError_t launch_few_cfg(const uint32_t* planes, const bf16_t* act, const float* alpha, bf16_t* y, int64_t T, int64_t rows, int64_t cw,
                                  int64_t g, int segs, const FewPlan& p, hipStream_t st) {
-    const size_t lds = (size_t)p.W * FEW_STAGE + (size_t)p.W * p.R * few_scale_bytes<QP, SUB>();
+    const size_t lds = (size_t)p.W * FEW_STAGE + (size_t)p.W * p.R * few_scale_bytes(QP, GROUPED);
     if (lds > 160 * 1024) return hipErrorInvalidConfiguration;
     static LdsLimit limit;
-    hipError_t e = limit.ensure((const void*)few_fwd_kernel<QP, NT, TILED, SUB>, lds);
+    hipError_t e = limit.ensure((const void*)few_fwd_kernel<QP, NT, TILED, GROUPED>, lds);
     if (e != hipSuccess) return e;
-    BCQ_LAUNCH((few_fwd_kernel<QP, NT, TILED, SUB>), dim3((unsigned)((rows + 16 * p.R - 1) / (16 * p.R))), dim3((unsigned)(64 * p.W * p.R)), lds, st,
+    BCQ_LAUNCH((few_fwd_kernel<QP, NT, TILED, GROUPED>), dim3((unsigned)((rows + 16 * p.R - 1) / (16 * p.R))), dim3((unsigned)(64 * p.W * p.R)), lds, st,
                        planes, act, alpha, y, (int)T, rows, (int)cw, segs, (int)(g / 32), (int)(cw * 32 / g), p.W, p.R);
     return hipGetLastError();
 }
@@ -259,36 +256,29 @@ static hipError_t launch_few_cfg(const uint32_t* planes, const bf16_t* act, cons
 template <bool TILED>
 static hipError_t launch_few(const uint32_t* planes, const bf16_t* act, const float* alpha, bf16_t* y, int64_t T, int64_t rows, int64_t cw, int q,
                              int64_t g, hipStream_t st) {
-    const int segs = (int)((cw + 15) / 16), sub = g == cw * 32 ? 0 : g % 128 == 0 ? 1 : 2;
-    const FewPlan p = few_plan(T, rows, segs, sub == 0, 256 * sub * q);
+    const int segs = (int)((cw + 15) / 16);
+    const bool grouped = g != cw * 32;
+    const FewPlan p = few_plan(T, rows, segs, !grouped, few_scale_bytes(q, grouped));
     const int64_t NT = (T + p.R - 1) / p.R;
     if (T > 8 || p.W * p.R > 16 || p.W * p.R < 1) return hipErrorInvalidConfiguration;
-#define BCQ_FEW(QQ, TT, SS) return launch_few_cfg<QQ, TT, TILED, SS>(planes, act, alpha, y, T, rows, cw, g, segs, p, st);
-#define BCQ_FEW_T(QQ, SS)          \
-    if (NT > 4) BCQ_FEW(QQ, 8, SS) \
-    if (NT > 2) BCQ_FEW(QQ, 4, SS) \
-    if (NT > 1) BCQ_FEW(QQ, 2, SS) \
-    BCQ_FEW(QQ, 1, SS)
-#define BCQ_FEW_S(QQ)                  \
-    if (sub == 0) { BCQ_FEW_T(QQ, 0) } \
-    if constexpr (!TILED) {            \
-        if (sub == 2) { BCQ_FEW_T(QQ, 2) } \
-    }                                  \
-    BCQ_FEW_T(QQ, 1)
+#define BCQ_FEW(QQ, TT, GR) return launch_few_cfg<QQ, TT, TILED, GR>(planes, act, alpha, y, T, rows, cw, g, segs, p, st);
+#define BCQ_FEW_T(QQ, GR)          \
+    if (NT > 4) BCQ_FEW(QQ, 8, GR) \
+    if (NT > 2) BCQ_FEW(QQ, 4, GR) \
+    if (NT > 1) BCQ_FEW(QQ, 2, GR) \
+    BCQ_FEW(QQ, 1, GR)
+#define BCQ_FEW_G(QQ)                     \
+    if (grouped) { BCQ_FEW_T(QQ, true) } \
+    BCQ_FEW_T(QQ, false)
     switch (q) {
-        case 1: { BCQ_FEW_S(1) }
-        case 2: { BCQ_FEW_S(2) }
-        case 3: { BCQ_FEW_S(3) }
-        default: { BCQ_FEW_S(4) }
+        case 1: { BCQ_FEW_G(1) }
+        case 2: { BCQ_FEW_G(2) }
+        case 3: { BCQ_FEW_G(3) }
+        default: { BCQ_FEW_G(4) }
     }
-#undef BCQ_FEW_S
+#undef BCQ_FEW_G
 #undef BCQ_FEW_T
 #undef BCQ_FEW
-}
-
-hipError_t launch_fwd_few(const uint32_t* packed, const float* alpha, const void* x, int64_t T, int64_t N, int64_t K, int64_t g, int q, void* y,
-                          hipStream_t st) {
-    return launch_few<false>(packed, (const bf16_t*)x, alpha, (bf16_t*)y, T, N, K / 32, q, g, st);
 }
 
 template <int MODE, bool TILED = false>

@@ -1231,12 +1231,12 @@ __global__ __launch_bounds__(512) void stream_fused_kernel(const uint32_t* __res
 // recode_unit, but for the order of the 16 columns (256 bytes) of an operand row: column t lies at slot (t + rot) & 15, so that the
 // pieces stored at a time lie in different banks.
 //
-// SUB = 0: row-wise scales, applied to the sums of all of K.  SUB = 1, 2: group-wise scales of whole 128 or 64 columns: the words
-// are turned over the rows of lanes so that instruction i contracts over columns 128 i .. + 127, its sums (for SUB = 2 of one half, the
-// other's signs being zero) are folded into y with the scales of their group, which lie in LDS in the order of the rows.
+// GROUPED = false: row-wise scales, applied to the sums of all of K.  GROUPED: group-wise scales of whole segments (groups that are
+// multiples of 512, as in the other streaming kernels): the words are turned over the rows of lanes so that instruction i contracts
+// over columns 128 i .. + 127, and its sums are folded into y with the scales of their group, which lie in LDS in the order of the rows.
 // Columns of tokens beyond T hold anything: a column of the result depends on no other.  TILED: decode layout.
 // What bounds it: launch, one trip to memory and the re-coding's 4-cycle vector operations.  1024 x 1024, q = 3: 5.3 -> 3.3 us at one token, 5.6 -> 4.4
-// at eight; 1024 x 4096 (two kernels before) 7.1 -> 4.2; 6144 x 2048, groups of 128, four tokens 9.9 -> 6.6.
+// at eight; 1024 x 4096 (two kernels before) 7.1 -> 4.2.
 
 // This lane's piece: lane b of the four holds term b >> 1, chunk b & 1; the scale bytes of both terms.
 __device__ __forceinline__ q_u32x4 recode_eight(q_u32x4 raw, int b, int& scale1, int& scale2) {
@@ -1285,12 +1285,11 @@ __device__ __forceinline__ q_u32x4 recode_eight(q_u32x4 raw, int b, int& scale1,
 }
 
 constexpr int FEW_STAGE = 4 * QBLK + QSCL;  // re-coded activations of a segment
-template <int QP, int SUB>
-constexpr int few_scale_bytes() { return 4 * SUB * QP * 64; }  // of a wave
+constexpr int few_scale_bytes(int q, bool grouped) { return grouped ? 4 * q * 64 : 0; }  // of a wave
 
 // A workgroup has W waves for as many segments at a time, times R row tiles that share their re-coded activations: wave (s, r) re-codes
 // tokens r, r + R, .. (NT of them, T / R rounded up; beyond T the last one again, the same bytes) of segment s.
-template <int QP, int NT, bool TILED, int SUB>
+template <int QP, int NT, bool TILED, bool GROUPED>
 __global__ __launch_bounds__(1024) void few_fwd_kernel(const uint32_t* __restrict__ planes, const bf16_t* __restrict__ act,
                                                       const float* __restrict__ alpha, bf16_t* __restrict__ y, int T, int64_t rows,
                                                       int cw, int segs, int group_words, int G, int W, int R) {
@@ -1302,14 +1301,14 @@ __global__ __launch_bounds__(1024) void few_fwd_kernel(const uint32_t* __restric
     const int64_t tile = (int64_t)blockIdx.x * R + r, tiles = (rows + 15) >> 4, rt = tile < tiles ? tile : tiles - 1;
     const int64_t row0 = rt * 16, C = (int64_t)cw * 32;
     unsigned char* const stage = lds + s * FEW_STAGE;
-    float* const scales = reinterpret_cast<float*>(lds + W * FEW_STAGE + wave * few_scale_bytes<QP, SUB>());  // [entry][plane][16 rows]
+    float* const scales = reinterpret_cast<float*>(lds + W * FEW_STAGE + wave * few_scale_bytes(QP, GROUPED));  // [entry][plane][16 rows]
     const int64_t left = rows - 1 - row0;
     const uint32_t roff = (uint32_t)((rl < left ? rl : left) * cw);  // rows beyond the matrix give outputs that are never stored
     const uint32_t* const base = planes + row0 * cw;
     const int64_t plane_stride = rows * cw;
 
     float ep[QP][4];
-    if (SUB == 0) {
+    if (!GROUPED) {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
 #pragma unroll
@@ -1320,9 +1319,9 @@ __global__ __launch_bounds__(1024) void few_fwd_kernel(const uint32_t* __restric
     for (int i = 0; i < QP; ++i) acc[i] = q_f32x4{0.f, 0.f, 0.f, 0.f};
     q_f32x4 yv = {0.f, 0.f, 0.f, 0.f};
 
-    constexpr int ENTRIES = SUB ? 4 * SUB : 1, NA = SUB ? (ENTRIES * QP * 16 + 63) / 64 : 1;
+    constexpr int ENTRIES = 4, NA = GROUPED ? QP : 1;  // scales of a row, plane and segment; of a lane
     // block of this lane's 8 columns: word 4 G + j (row-wise) or 4 j + G (groups) of the segment
-    const int Gb = SUB ? (lane >> 2) & 3 : lane >> 4, jb = SUB ? lane >> 4 : (lane >> 2) & 3, b = lane & 3;
+    const int Gb = GROUPED ? (lane >> 2) & 3 : lane >> 4, jb = GROUPED ? lane >> 4 : (lane >> 2) & 3, b = lane & 3;
     const int rot = ((lane >> 2) & 3) + 4 * (b & 1);
     unsigned char* const mine = stage + jb * QBLK + (Gb >> 1) * (QBLK / 2) + ((2 * Gb + (b & 1)) & 3) * 256;
     unsigned char* const mine_s = stage + 4 * QBLK + (16 * Gb + 8 * b) * 4 + jb;  // lanes 0 and 1 store the scale bytes of the two terms
@@ -1353,7 +1352,7 @@ __global__ __launch_bounds__(1024) void few_fwd_kernel(const uint32_t* __restric
             }
         }
         float sc[NA];
-        if (SUB) {  // scale of (entry e, plane, row): entries run fastest over the lanes, as in memory
+        if (GROUPED) {  // scale of (entry e, plane, row): entries run fastest over the lanes, as in memory
 #pragma unroll
             for (int a = 0; a < NA; ++a) {
                 const int idx = lane + 64 * a, e = idx % ENTRIES, row = idx / ENTRIES % 16, pl = idx / (16 * ENTRIES);
@@ -1371,7 +1370,7 @@ __global__ __launch_bounds__(1024) void few_fwd_kernel(const uint32_t* __restric
             *reinterpret_cast<q_u32x4*>(mine + (((t + rot) & 15) ^ (b >> 1 << 3)) * 16) = piece;  // the second term is column t + 8
             if (b < 2) mine_s[t * 4] = (unsigned char)(b ? scale2 : scale1);
         }
-        if (SUB) {
+        if (GROUPED) {
 #pragma unroll
             for (int a = 0; a < NA; ++a) {
                 const int idx = lane + 64 * a, e = idx % ENTRIES, row = idx / ENTRIES % 16, pl = idx / (16 * ENTRIES);
@@ -1387,9 +1386,9 @@ __global__ __launch_bounds__(1024) void few_fwd_kernel(const uint32_t* __restric
         for (int j = 0; j < 4; ++j) {
             // operand row (j, half hh, lane row g) is chunk 4 hh + g of its block of 8, written by lanes of G = 2 hh + g / 2
             const unsigned char* bp = stage + j * QBLK + g * 256;
-            const int slot = rl + 4 * (g & 1) + (SUB ? g >> 1 : j);
+            const int slot = rl + 4 * (g & 1) + (GROUPED ? g >> 1 : j);
             const q_u32x4 lo = *reinterpret_cast<const q_u32x4*>(bp + (slot & 15) * 16);
-            const q_u32x4 hi = *reinterpret_cast<const q_u32x4*>(bp + QBLK / 2 + ((slot + (SUB ? 2 : 0)) & 15) * 16);
+            const q_u32x4 hi = *reinterpret_cast<const q_u32x4*>(bp + QBLK / 2 + ((slot + (GROUPED ? 2 : 0)) & 15) * 16);
             const q_i32x8 bo = {(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
             auto multiply = [&](const q_i32x8& a, q_f32x4 c) {
                 // the instruction picks byte j of the scale register (its op_sel): j must be a constant
@@ -1401,33 +1400,22 @@ __global__ __launch_bounds__(1024) void few_fwd_kernel(const uint32_t* __restric
             q_i32x8 aop[QP];
 #pragma unroll
             for (int i = 0; i < QP; ++i) expand_one(bits[i][j], aop[i]);
-            if constexpr (SUB == 0) {
+            if constexpr (!GROUPED) {
 #pragma unroll
                 for (int i = 0; i < QP; ++i) acc[i] = multiply(aop[i], acc[i]);
             } else {
 #pragma unroll
-                for (int part = 0; part < SUB; ++part) {
-                    const int keep = SUB == 1 || g / (4 / SUB) == part ? -1 : 0;
+                for (int i = 0; i < QP; ++i) acc[i] = multiply(aop[i], q_f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-                    for (int i = 0; i < QP; ++i) {
-                        q_i32x8 a = aop[i];
-                        if (SUB > 1) {
+                for (int i = 0; i < QP; ++i) {
+                    const q_f32x4 al = *reinterpret_cast<const q_f32x4*>(scales + (j * QP + i) * 16 + 4 * g);
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) a[e] &= keep;
-                        }
-                        acc[i] = multiply(a, q_f32x4{0.f, 0.f, 0.f, 0.f});
-                    }
-#pragma unroll
-                    for (int i = 0; i < QP; ++i) {
-                        const q_f32x4 al = *reinterpret_cast<const q_f32x4*>(scales + ((j * SUB + part) * QP + i) * 16 + 4 * g);
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) yv[v] += al[v] * acc[i][v];
-                    }
+                    for (int v = 0; v < 4; ++v) yv[v] += al[v] * acc[i][v];
                 }
             }
         }
     }
-    if (SUB) {  // continue with y in place of the plane sums
+    if (GROUPED) {  // continue with y in place of the plane sums
         acc[0] = yv;
 #pragma unroll
         for (int v = 0; v < 4; ++v) ep[0][v] = 1.f;

@@ -1,6 +1,6 @@
 """The forward of at most 8 tokens in one kernel, from both plane layouts, at the edges of its tiles: row counts of less than a
 tile and beyond one, word counts that are no multiple of 4 or 16, one to several segments per wave, row tiles shared by two and three
-to a workgroup, groups of one, two and more halves of an instruction.
+to a workgroup, groups of one and more segments.
 
 Signs and scales are exact and the activations are bf16 within 2^-13 of their block's largest, so only the fp32 sums and the one
 rounding of the result (2^-9 of its value) differ from fp64: 2^-8 of every value and 1e-5 of the largest.  The profiler names the
@@ -46,9 +46,9 @@ def _run(layout, packed, alpha, x, g):
     ("decode", 1, 1024, 1024, 1024, 3), ("decode", 8, 33, 32, 32, 1), ("decode", 5, 1000, 1056, 1056, 4), ("decode", 3, 8208, 544, 544, 2),
     ("decode", 8, 8209, 2528, 2528, 4), ("decode", 2, 200, 12288, 12288, 1), ("decode", 4, 100, 8192, 8192, 3), ("decode", 8, 70, 4096, 4096, 2),
     ("decode", 8, 300, 2048, 512, 4), ("decode", 1, 300, 1536, 512, 3), ("canonical", 1, 1, 160, 160, 2), ("canonical", 7, 5000, 1056, 1056, 2),
-    ("canonical", 6, 131, 3104, 3104, 3), ("canonical", 4, 2048, 2048, 128, 3), ("canonical", 1, 35, 1152, 128, 4), ("canonical", 8, 2100, 2304, 64, 1),
-    ("canonical", 3, 4200, 1024, 64, 4), ("canonical", 2, 17, 960, 192, 2), ("canonical", 8, 8300, 1280, 256, 1), ("canonical", 4, 40, 10240, 128, 1),
-    ("canonical", 5, 4100, 3968, 64, 3), ("canonical", 2, 64, 640, 320, 4)])
+    ("canonical", 6, 131, 3104, 3104, 3), ("canonical", 4, 2048, 2048, 512, 3), ("canonical", 1, 35, 1536, 512, 4), ("canonical", 8, 2100, 2560, 512, 1),
+    ("canonical", 3, 4200, 1024, 512, 4), ("canonical", 2, 17, 3072, 1536, 2), ("canonical", 8, 8300, 1536, 512, 1), ("canonical", 4, 40, 10240, 512, 1),
+    ("canonical", 5, 4100, 4096, 1024, 3), ("canonical", 2, 64, 1024, 512, 4)])
 def test_few_tokens_in_one_kernel(layout, T, N, K, g, q):
     packed, alpha, x, w = _layer(q, N, K, g, T, T + N + K)
     y = _run(layout, packed, alpha, x, g).double()
@@ -58,13 +58,13 @@ def test_few_tokens_in_one_kernel(layout, T, N, K, g, q):
 
 @pytest.mark.parametrize("layout,T,N,K,g,q", [
     ("decode", 1, 40, 7168, 7168, 4), ("decode", 1, 40, 7200, 7200, 3), ("decode", 2, 4096, 7712, 7712, 4), ("decode", 2, 4112, 7712, 7712, 4),
-    ("canonical", 4, 100, 8192, 128, 4), ("canonical", 1, 4112, 4608, 384, 2), ("canonical", 2, 4080, 4224, 128, 1)])
+    ("canonical", 4, 100, 8192, 512, 4), ("canonical", 1, 4112, 4608, 512, 2), ("canonical", 2, 4080, 4608, 512, 1)])
 def test_up_to_sixteen_segments_at_a_time(layout, T, N, K, g, q):
     """Both sides of the lines between 8 and 16 waves, and the largest workgroup."""
     test_few_tokens_in_one_kernel(layout, T, N, K, g, q)
 
 
-@pytest.mark.parametrize("layout,T,N,K,g,q", [("decode", 8, 600, 1056, 1056, 3), ("canonical", 5, 4200, 1024, 128, 2), ("canonical", 4, 100, 1152, 64, 4)])
+@pytest.mark.parametrize("layout,T,N,K,g,q", [("decode", 8, 600, 1056, 1056, 3), ("canonical", 5, 4200, 1024, 512, 2), ("canonical", 4, 100, 1536, 512, 4)])
 def test_non_finite_token_and_zero_blocks(layout, T, N, K, g, q):
     """A non-finite activation makes its own token's results NaN; blocks of zeros, a block of subnormals and one of large values
     re-code exactly."""

@@ -390,3 +390,44 @@ def test_decode_forward_rejects_what_it_does_not_take(bcq):
         a = alpha if g == K else torch.ones((q, N, K // g), dtype=torch.float32, device="cuda")
         with pytest.raises(bcq.BcqError):
             bcq.bcq_linear_fwd_decode(tiled, a, x, g=g, workspace=w)
+
+
+@pytest.mark.parametrize("T,N,K,g,q", [(1, 40, 1024, 128, 3), (4, 130, 2048, 128, 2), (8, 33, 640, 64, 4), (3, 70, 1152, 192, 2),
+                                       (2, 50, 1280, 320, 2), (8, 100, 4096, 256, 2)])
+def test_few_tokens_keep_exact_activations(bcq, T, N, K, g, q):
+    """Groups that are no multiple of 512 multiply bf16 activations as they are with weights that hold their scales: an infinity
+    keeps its sign, the largest bf16 values and sums of planes beyond fp32 are no infinities, and small elements beside a large
+    one keep their bits.  Errors: the weights' and the result's rounding (2^-9 of every term each) and fp32 sums."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(T + N + K)
+    packed = torch.randint(-2**31, 2**31 - 1, (q, N, K // 32), dtype=torch.int32, device="cuda", generator=gen)
+    alpha = (torch.rand((q, N, K // g), device="cuda", generator=gen) + 0.1) * 1e-4
+    alpha[1] = alpha[0]
+    packed[1, :, 0] = packed[0, :, 0] ^ -1  # the first 32 columns have weights of zero from planes 0 and 1
+    alpha[2:] *= 0.25
+    alpha[2:, :, 0] = 0.0
+    bits = torch.arange(32, dtype=torch.int32, device="cuda")
+    w = sum((2 * ((packed[i].unsqueeze(-1) >> bits) & 1) - 1).reshape(N, K).double() * alpha[i].double().repeat_interleave(g, dim=1)
+            for i in range(q))
+
+    def run(x, packed=packed):
+        ws = torch.empty((max(bcq.workspace_bytes_grouped(1, T, N, K, g, q, 1), 16),), dtype=torch.uint8, device="cuda")
+        return bcq.bcq_linear_fwd_grouped(packed, alpha, x, g, workspace=ws)
+
+    x = torch.randn((T, K), device="cuda", generator=gen).bfloat16()
+    x[:, 3] = 2.0 ** 22      # beside elements 2^-22 of it, and with weights of zero
+    x[0, K - 7] = 3.2e38
+    y, ref = run(x).double(), x.double() @ w.t()
+    assert y.isfinite().all()
+    assert ((y - ref).abs() <= 2.0 ** -7 * (x.double().abs() @ w.abs().t())).all()
+
+    ones = torch.full_like(packed, -1)
+    large = torch.full_like(x, 1e38)
+    total = large.double() @ sum(alpha[i].double().repeat_interleave(g, dim=1) for i in range(q)).t()
+    y = run(large, ones).double()
+    assert ((y - total).abs() <= 2.0 ** -7 * total).all()
+
+    x[T - 1, K // 2] = -float("inf")
+    sign = w[:, K // 2].sign().float()
+    want = torch.where(sign == 0, torch.full_like(sign, float("nan")), -float("inf") * sign)
+    assert torch.equal(run(x)[T - 1].float().nan_to_num(7.0), want.nan_to_num(7.0))
