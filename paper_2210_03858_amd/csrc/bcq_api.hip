@@ -566,6 +566,8 @@ extern "C" bcq_status bcq_prepare(int op, int64_t T, int64_t N, int64_t K, int64
                 break;
             case BCQ_OP_FWD:
                 s = bcq_linear_fwd_grouped(pu, pf, p, dtype, T, N, K, g, q, p, w, wb, nullptr);
+                if (s == BCQ_OK && with_ws && stream_fwd_ok(T, K, g, dtype))
+                    s = bcq_linear_fwd_decode(pu, pf, p, dtype, T, N, K, g, q, p, w, wb, nullptr);
                 if (s == BCQ_OK && with_ws && g == K && dtype == BCQ_BF16 && T <= BCQ_STATIC_MAX_TOKENS &&
                     bcq::stream_fwd_workspace(T, K) <= (size_t)BCQ_STATIC_SCRATCH_BYTES)
                     s = bcq_linear_fwd_static(pu, pf, p, dtype, T, N, K, q, p, nullptr);

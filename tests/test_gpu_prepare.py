@@ -67,3 +67,43 @@ print("PREPARE_OK")
 def test_first_call_inside_a_graph_capture_after_prepare():
     r = subprocess.run([sys.executable, "-c", CHILD % ROOT], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and "PREPARE_OK" in r.stdout, (r.stdout[-2000:], r.stderr[-4000:])
+
+
+DECODE_CHILD = r'''
+import sys
+sys.path.insert(0, %r)
+import torch
+from torch.profiler import ProfilerActivity, profile
+import paper_2210_03858_amd as p
+p.load()
+
+
+def raises_a_limit(T, N, K, g, q, prepare):
+    packed = torch.randint(-2**31, 2**31 - 1, (q, N, K // 32), dtype=torch.int32, device="cuda")
+    alpha = torch.rand((q, N, K // g), device="cuda")
+    x = torch.randn((T, K), device="cuda").bfloat16()
+    tiled = p.bcq_pack_decode(packed)
+    ws = torch.empty((p.workspace_bytes_grouped(1, T, N, K, g, q, 1),), dtype=torch.uint8, device="cuda")
+    if prepare:
+        p.bcq_prepare(1, T, N, K, q, g=g)
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
+        a = p.bcq_linear_fwd_decode(tiled, alpha, x, g, workspace=ws)
+        b = p.bcq_linear_fwd_grouped(packed, alpha, x, g, workspace=ws)
+        torch.cuda.synchronize()
+    assert torch.equal(a, b)
+    return "hipFuncSetAttribute" in [e.key for e in prof.key_averages()]
+
+
+assert raises_a_limit(2, 512, 8192, 8192, 1, False)     # the profiler sees the call where nothing was prepared
+for shape in ((1, 2560, 10240, 10240, 4), (8, 512, 4096, 4096, 3), (4, 1024, 8192, 512, 2), (3, 14336, 4096, 4096, 2)):
+    assert not raises_a_limit(*shape, True), shape
+print("PREPARE_OK")
+'''
+
+
+def test_decode_layout_is_prepared():
+    """bcq_prepare of the forward covers both plane layouts, of the kernel for at most 8 tokens with 8 segments and more at a time
+    and of the shared-activation kernel: their first calls raise no LDS limit any more."""
+    r = subprocess.run([sys.executable, "-c", DECODE_CHILD % ROOT], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "PREPARE_OK" in r.stdout, (r.stdout[-2000:], r.stderr[-4000:])
