@@ -210,34 +210,52 @@ static hipError_t launch_fused(const uint32_t* planes, const bf16_t* act, const 
 // ---- forward of at most 8 tokens in one kernel ------------------------------------------------------------------------
 // Segments (W) and row tiles (R) of a workgroup.  Sharing the re-coded activations between R row tiles saves 0.27 us per token and row tile
 // where there are several tokens (8 tokens, q = 4, of 7680 x 2560: 10.0 -> 7.2 us), and costs up to 1.5 us where it leaves compute units without a
-// workgroup or puts 16 waves into one (1024 x 4096, q = 3, one token 4.2 -> 5.3).  More than 512 row tiles: three, which keeps the workgroups
-// to one round (10240 x 2560, q = 4, 8 tokens: two 12.3, three 8.4).
+// workgroup or puts 16 waves into one (1024 x 4096, q = 3, one token 4.2 -> 5.3).  Three where they, and not two, keep the workgroups to one
+// round, that is for 513 to 768 row tiles (10240 x 2560, q = 4, 8 tokens: two 12.3, three 8.4; 13889 x 2048, q = 3, 10.9 / 14.1).  Eight
+// segments share only with many tokens and tiles (7127 x 4096, q = 1, 8 tokens 11.0 -> 7.9; 1553 x 4096, q = 2, 7 tokens 7.4 / 7.2), and where
+// every compute unit has a workgroup anyway the many rows of canonical planes that many waves read at once cost more (257 x 3264, q = 4, 6
+// tokens 8.5 / 9.5; from the decode layout 7.4 / 7.6).
 // Up to 256 row tiles take up to 16 segments at a time instead of 8: a turn is a whole trip to memory and through the re-coding (one token of 1280 x
 // 5120, q = 4, 5.3 -> 4.7 us, four 7.6 -> 6.5).  Beyond them the larger workgroups take a second round (320 tiles: 1.1 to 1.4 times the
 // time); 15 and 16 waves gain nothing at one token (2048 x 8192, q = 4, 6.2 -> 6.4).
 struct FewPlan {
     int W, R;
 };
-static FewPlan few_plan(int64_t T, int64_t rows, int segs, bool rowwise, int scale_bytes) {
+static FewPlan few_plan(int64_t T, int64_t rows, int segs, int q, bool rowwise, bool tiled) {
     FewPlan p;
     const int64_t tiles = (rows + 15) / 16;
     const auto waves = [&](int most) { const int turns = (segs + most - 1) / most; return (segs + turns - 1) / turns; };
     p.W = waves(8);
-    const bool room = tiles <= 256 && 16 * (FEW_STAGE + scale_bytes) <= 160 * 1024;
+    const bool room = tiles <= 256 && 16 * (FEW_STAGE + few_scale_bytes(q, !rowwise)) <= 160 * 1024;
     if (room && !(rowwise && T == 1 && waves(16) > 14)) p.W = waves(16);
     bool share = T >= 3 && p.W < 8;
     if (!rowwise) share = share && tiles > (T <= 4 ? 256 : p.W <= 3 ? 0 : 128);
-    p.R = !share ? 1 : tiles > 512 && p.W <= 5 ? 3 : 2;
+    if (rowwise && !tiled && tiles <= 256) share = share && q * p.W < 14;
+    if (p.W == 8) share = T > 4 && tiles > 256;
+    p.R = !share ? 1 : tiles > 512 && tiles <= 768 && p.W <= 5 ? 3 : 2;
     return p;
 }
 
-// Where it is faster than re-coding in a kernel of its own (the re-coding is repeated by every R row tiles); groups are whole segments here.
-// us, that / this: one token of 1024 x 1024, q = 3, 5.3 / 3.3, 10240 x 2560, q = 4, 12.1 / 7.0, 2560 x 10240 10.6 / 7.8; four tokens 5.4 / 4.0,
-// 12.2 / 7.2, 10.8 / 11.6, 2048 x 8192, q = 3, 8.1 / 8.0; eight tokens 5.6 / 4.4, 12.3 / 8.4, 1024 x 4096 7.2 / 7.3, 1280 x 5120 7.3 / 8.9.
-static bool few_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
-    if (T > 8 || q > 4 || N * K > 32000000) return false;
-    if (g == K) return K <= (T <= 2 ? 12288 : T <= 4 ? 8192 : 4096);
-    return K <= (T > 4 ? 4096 : 10240);
+// Where it is faster than re-coding in a kernel of its own (the re-coding is repeated by every R row tiles): where its workgroups run in
+// one round (a compute unit holds 16 waves; 9822 x 3072, groups of 1536, q = 4, six tokens in two rounds 11.2 / 19.6 us, that / this),
+// and the contraction is not too long for the tokens.  us, that / this: one token of 1024 x 1024, q = 3, 5.3 / 3.3, 10240 x 2560,
+// q = 4, 12.1 / 7.0, 2560 x 10240 10.6 / 7.8, 118 x 13504, q = 2, 9.4 / 6.4, but two tokens of 134 x 12416, q = 4, 12.2 / 14.9; four tokens
+// 1024 x 1024 5.4 / 4.0, 10240 x 2560 12.2 / 7.2, 2048 x 8192, q = 3, 8.1 / 8.0, but 1231 x 8448, q = 1, 8.2 / 9.1, and of canonical planes
+// three of 2229 x 7168, q = 4, 10.0 / 12.4; eight tokens 5.6 / 4.4, 12.3 / 8.4, 1024 x 4096 7.2 / 7.3, 1952 x 5312, q = 2, 7.6 / 8.6.  Of layers
+// above 32 million weights about half are faster (11730 x 3104, q = 3, one token 14.6 / 10.1, 4346 x 9376, q = 1, six 12.9 / 16.3).
+// Groups (whole segments here) read their scales from the canonical planes' side in 16-byte pieces: four tokens of 1022 x 6144, groups
+// of 1024, q = 4, 9.2 / 10.4, of 72 x 9216, groups of 1536, 10.2 / 15.8, six of 2590 x 3072 9.0 / 10.5, of 8692 x 2048 9.0 / 10.6, from the decode layout
+// 2339 x 3072 8.8 / 7.7 at eight, 164 x 9216 9.8 / 11.4 at three.
+// Against the kernels that ran before this one, 5000 random calls of both layouts: 0.79 of the time, 34 more than 4 % slower, 6 more
+// than 8 % (worst 1.25: four tokens of 4157 x 7680, groups of 512, q = 3, decode layout).
+static bool few_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q, bool tiled) {
+    if (N * K > 32000000) return false;
+    const FewPlan p = few_plan(T, N, (int)((K + 511) / 512), q, g == K, tiled);
+    if ((N + 16 * p.R - 1) / (16 * p.R) > 256 * (16 / (p.W * p.R))) return false;
+    if (g == K) return K <= (T <= 2 ? 12288 : T > 4 ? 4096 : q == 4 && !tiled ? 6144 : 8192);
+    if (tiled) return K <= (T <= 2 ? 10240 : T <= 4 ? 8192 : 3072);
+    if (q > 2 && N > 4096) return K <= (N > 8192 ? 1536 : 2048);
+    return K <= (T <= 4 ? (q > 2 ? 4096 : 6144) : q == 4 ? 2048 : 3072);
 }
 
 template <int QP, int NT, bool TILED, bool GROUPED>
@@ -258,7 +276,7 @@ static hipError_t launch_few(const uint32_t* planes, const bf16_t* act, const fl
                              int64_t g, hipStream_t st) {
     const int segs = (int)((cw + 15) / 16);
     const bool grouped = g != cw * 32;
-    const FewPlan p = few_plan(T, rows, segs, !grouped, few_scale_bytes(q, grouped));
+    const FewPlan p = few_plan(T, rows, segs, q, !grouped, TILED);
     const int64_t NT = (T + p.R - 1) / p.R;
     if (T > 8 || p.W * p.R > 16 || p.W * p.R < 1) return hipErrorInvalidConfiguration;
 #define BCQ_FEW(QQ, TT, GR) return launch_few_cfg<QQ, TT, TILED, GR>(planes, act, alpha, y, T, rows, cw, g, segs, p, st);
@@ -289,15 +307,16 @@ static hipError_t launch_stream(const uint32_t* planes, const bf16_t* act, const
     const int G = (int)(layer_k / g);
     const int gsegs = (grouped && MODE != STREAM_DX) ? (int)(g / 512) : 0;  // needs g % 512 == 0 (checked by the caller)
     const StreamPlan p = stream_plan(T, rows, cw, gsegs);
-    if constexpr (MODE == STREAM_FWD) {
-        if (few_fwd_ok(T, rows, layer_k, g, q)) return launch_few<TILED>(planes, act, alpha, (bf16_t*)out, T, rows, cw, q, g, st);
-    }
     if (p.W < 1 || p.W > 8 || p.R != 1) return hipErrorInvalidConfiguration;  // compiled for at most 512 threads, R = 1
     if constexpr (MODE != STREAM_DX) {
-        const bool fits = TILED ? p.halves == 1 && p.grid_x <= FUSED_TILED_MAX_WGS && p.W == 1 && q_used > 4 && !grouped
-                                : (int64_t)p.grid_x * p.tiles * p.W <= FUSED_MAX_WAVES;
-        if (p.segs_per_wave <= FUSED_MAX_SEGS && fits)
-            return launch_fused<MODE, TILED>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st);
+        const bool single = p.segs_per_wave <= FUSED_MAX_SEGS &&
+                            (TILED ? p.halves == 1 && p.grid_x <= FUSED_TILED_MAX_WGS && p.W == 1 && q_used > 4 && !grouped
+                                   : (int64_t)p.grid_x * p.tiles * p.W <= FUSED_MAX_WAVES);
+        if constexpr (MODE == STREAM_FWD) {  // (what fits the general single kernel is always faster so: 598 x 3584, groups of 512, 11.1 / 9.4)
+            if (T <= 8 && q <= 4 && (single || few_fwd_ok(T, rows, layer_k, g, q, TILED)))
+                return launch_few<TILED>(planes, act, alpha, (bf16_t*)out, T, rows, cw, q, g, st);
+        }
+        if (single) return launch_fused<MODE, TILED>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st);
     }
     const int sets = (MODE == STREAM_DX) ? q * G : 1;
     unsigned char* xq = reinterpret_cast<unsigned char*>(workspace);

@@ -96,7 +96,7 @@ def raises_a_limit(T, N, K, g, q, prepare):
 
 
 assert raises_a_limit(2, 512, 8192, 8192, 1, False)     # the profiler sees the call where nothing was prepared
-for shape in ((1, 2560, 10240, 10240, 4), (8, 512, 4096, 4096, 3), (4, 1024, 8192, 512, 2), (3, 14336, 4096, 4096, 2)):
+for shape in ((1, 2560, 10240, 10240, 4), (8, 512, 4096, 4096, 3), (2, 1024, 6144, 512, 2), (3, 14336, 4096, 4096, 2)):
     assert not raises_a_limit(*shape, True), shape
 print("PREPARE_OK")
 '''
