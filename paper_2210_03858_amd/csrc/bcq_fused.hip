@@ -210,8 +210,7 @@ constexpr int tile_lds_bytes() { return KG * tile_stages<TM, KG>() * TM * 16 * 2
 // every 16 TM tokens, and beside a 16-cycle matrix instruction only two are free (7.2 ns alone and with two, 10.5 with four, 17 with
 // eight).  Against activations re-ordered in memory and read from L2 by every 32 rows (us, with that kernel's re-ordering): 256 tokens,
 // q = 4, of 7680 x 2560 27 -> 22, 2560 x 10240 44 -> 34, 10240 x 2560 35 -> 33; 149 tokens of 2560 x 10240, q = 1, 38 -> 21; groups
-// of 32: 72 tokens of 8192 x 2048, q = 3, 26 -> 16.  Of 168 random calls up to 384 tokens the median is 0.84 of the time, 14 are more
-// than 4 % slower (worst 1.17: 320 tokens of 1632 x 5056, q = 4, 22 -> 26).
+// of 32: 72 tokens of 8192 x 2048, q = 3, 26 -> 16.   (Calls that it made slower: at fused_fwd_ok.)
 //
 // Shapes (TM, TN, KG): (4, 1, 1), of which a compute unit holds three by their LDS and hides one's waits behind another's, and
 // (8, 1, 2), which expands half as often.  128 rows to a workgroup (TN = 2), 128 or 256 tokens without the parts, and more stages
@@ -513,14 +512,6 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(const float* __restrict_
     }
 }
 
-// 128 tokens per workgroup read and expand every plane half as often, 64 make twice as many workgroups: measured
-// (256 tokens, q = 4) 7680 x 2560 27 against 31 us, 10240 x 2560 35 / 38, 2560 x 2560 17 / 17, 1024 x 1024 10 / 8, and
-// with the contraction split 2560 x 10240 48 / 53.
-static bool wide_tokens(int64_t T, int64_t N, int64_t K) {
-    const int64_t tiles = (N + 31) / 32 * ((T + 127) / 128), units = (K + 127) / 128;
-    return T > 64 && (tiles >= 256 || (tiles >= 64 && units >= 64));
-}
-
 static size_t sums_bytes(int64_t T, int64_t N, int parts) { return (size_t)parts * T * ((N + 3) / 4 * 4) * 4; }
 
 // Tokens of a tile (64 or 128), parts of the contraction and units of 128 columns per wave, by an estimated time in us.  `more`:
@@ -614,16 +605,23 @@ static bool one_full_round(int64_t T, int64_t N, int64_t K, int q) {
 // us: 160 tokens of 5120 x 7840, q = 1, 29 / 43, of 8224 x 4896, q = 2, 39 / 43), with three and four about right (288 of 5120 x
 // 8000, q = 3, 58 / 57, 320 of 1664 x 5056, q = 4, 26 / 25.5, 257 of 8200 x 992 19 / 17; 223 of 9344 x 2336 38 / 30).
 // Group-wise scales: a line of the same kind in q and the parity of the words in a group.
-// Beyond these lines, from 385 tokens on or with group-wise scales, and for layers of more than a million weights and
-// 512 columns (whose time is more than start and end): one kernel where its estimate is below that of two (us: 421 tokens of 1312 x 5248, q = 1, groups of 128, 20.6 / 24.5,
-// 720 of 2336 x 2336, q = 1, 17.5 / 21.8, 206 of 2496 x 9984, q = 2, groups of 32, 34 / 45; four planes stay on two kernels, 593 of
-// 1536 x 6144, groups of 128, 37 / 32).
+// For layers of more than a million weights and 512 columns (whose time is more than start and end) the two estimates, whose errors
+// are 5 to 10 %, overrule the lines where they are clear: beyond them, from 385 tokens on or with group-wise scales, one kernel where its
+// estimate is a tenth below that of two (us, one / two: 421 tokens of 1312 x 5248, q = 1, groups of 128, 20.6 / 24.5, 720 of 2336 x 2336,
+// q = 1, 17.5 / 21.8, 206 of 2496 x 9984, q = 2, groups of 32, 34 / 45; with equal estimates 301 of 14680 x 4096, q = 2, groups of 256,
+// 98 / 70, 602 of 3720 x 6432, q = 2, 69 / 53), and two kernels where the one's is a tenth above (378 of 11392 x 2464, q = 3, 54 / 37).
+// Against the forms before tile_fwd_kernel, 1159 random calls of 33 to 768 tokens: 0.87 of the time, 40 more than 4 % slower, 12 more
+// than 8 %, worst 1.15 (140 tokens of 2720 x 2528, q = 2, 13.1 -> 15.1); no choice of route or plan would leave less than 17.
 bool fused_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
     // layers of fewer rows than tokens have few row tiles, and no room for the sums of parts
     if (q > 4 || T > 768 || (T > 32 && (T + 31) / 32 * 32 * K * 2 > (int64_t)mfma_fwd_workspace(N, K))) return false;
     if (T <= 16) return true;
     const int64_t work = N * K * T;
-    if ((T > 384 || g != K) && T > 32 && K > 512 && N * K > 1000000 && tile_plan(T, N, K, g, q).estimate < two_kernel_estimate(T, N, K, q)) return true;
+    if (T > 32 && K > 512 && N * K > 1000000) {
+        const double one = tile_plan(T, N, K, g, q).estimate, two = two_kernel_estimate(T, N, K, q);
+        if (0.9 * one > two && N * K <= 100000000) return false;
+        if ((T > 384 || g != K) && 1.1 * one < two) return true;
+    }
     if (T > 384) return false;
     if (g == K) {
         const bool large = (T > 128 && N * K > 40000000) || (T > 256 && q == 4 && N * K > 8000000);

@@ -52,6 +52,19 @@ def test_tile_forward_exact(form, parts, T, N, K, g, q):
     assert torch.equal(y, (x.double() @ w.double().t()).float().bfloat16())
 
 
+@pytest.mark.parametrize("one,T,N,K,g,q", [
+    (True, 442, 2723, 1536, 256, 1), (False, 452, 3885, 1152, 128, 1), (True, 720, 1805, 3648, 3648, 1), (False, 481, 1154, 1920, 1920, 2),
+    (True, 347, 674, 2112, 96, 2), (False, 274, 863, 2688, 32, 4), (True, 218, 3748, 1792, 64, 4), (False, 137, 5977, 768, 256, 4),
+    (True, 342, 5061, 1088, 1088, 4), (False, 354, 3191, 1088, 1088, 4)])
+def test_clear_estimates_choose_the_route(one, T, N, K, g, q):
+    """Both sides of the two lines in the ratio of the estimated times, with row-wise and group-wise scales."""
+    packed, alpha, w, gen = _layer(q, N, K, g, T + N)
+    x = torch.randint(-4, 5, (T, K), device="cuda", generator=gen).bfloat16()
+    y, names = _forward(packed, alpha, x, g)
+    assert any("tile_fwd_kernel" in n for n in names) == one, names
+    assert torch.equal(y, (x.double() @ w.double().t()).float().bfloat16())
+
+
 @pytest.mark.parametrize("T,N,K,q", [(96, 300, 1056, 3), (100, 9000, 2080, 4), (130, 1030, 8224, 3)])
 def test_infinity_in_the_last_columns_stays_in_its_token(T, N, K, q):
     packed, alpha, _, gen = _layer(q, N, K, K, N)
