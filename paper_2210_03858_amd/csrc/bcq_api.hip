@@ -498,30 +498,29 @@ bcq_status bwd_alpha_impl(const uint32_t* packed, const void* x, const void* dy,
 
 extern "C" {
 
-bcq_status bcq_node_backward(const uint32_t* packed, const uint32_t* packed_t, const float* alpha, const void* x, const void* dy,
-                             int dtype, int64_t T, int64_t N, int64_t K, int64_t g, int q, int q_train, float grad_scale, void* dx,
-                             void* input_workspace, size_t input_bytes, float* dalpha, void* alpha_workspace, size_t alpha_bytes,
-                             void* stream) {
+// Both gradients run on the tiled kernels and the input gradient expands by table.
+int bcq_node_backward_joint(int with_twin, int dtype, int64_t T, int64_t N, int64_t K, int64_t g, int q) {
     const bool rowwise = (g == K);
-    // One launch less where both gradients run on the tiled kernels and the input gradient expands by table; every other call,
-    // and one that the checks refuse, is the two calls.
-    const bool joint = packed && alpha && x && dy && dx && dalpha && input_workspace && alpha_workspace &&
-                       check_shape(T, N, K, q) == BCQ_OK && check_group(K, g) == BCQ_OK && q <= 4 && q_train >= 1 && q_train <= q &&
-                       !(packed_t && stream_bwd_input_ok(T, N, K, g, q, dtype)) && mfma_bwd_input_ok(T, N, rowwise, dtype) &&
-                       !stream_bwd_alpha_ok(T, K, g, dtype) && mfma_bwd_alpha_ok(T, N, K, rowwise, dtype) &&
-                       !misaligned(packed) && !misaligned(alpha) && !misaligned(x) && !misaligned(dy) && !misaligned(dx) &&
-                       !misaligned(dalpha) &&
-                       check_workspace(input_workspace, input_bytes, workspace_least(BCQ_OP_BWD_INPUT, T, N, K, g, q, dtype)) == BCQ_OK &&
-                       check_workspace(alpha_workspace, alpha_bytes, workspace_least(BCQ_OP_BWD_ALPHA, T, N, K, g, q, dtype)) == BCQ_OK &&
-                       check_device() == BCQ_OK;
-    if (joint)
-        return done(bcq::launch_bwd_mfma(packed, alpha, x, dy, T, N, K, g, q, q_train, grad_scale, dx, input_workspace, dalpha,
-                                         alpha_workspace, (hipStream_t)stream));
-    const bcq_status s = bcq_linear_bwd_input_grouped(packed, packed_t, alpha, dy, dtype, T, N, K, g, q, dx, input_workspace,
-                                                      input_bytes, stream);
+    return check_shape(T, N, K, q) == BCQ_OK && check_group(K, g) == BCQ_OK && q <= 4 &&
+           !(with_twin && stream_bwd_input_ok(T, N, K, g, q, dtype)) && mfma_bwd_input_ok(T, N, rowwise, dtype) &&
+           !stream_bwd_alpha_ok(T, K, g, dtype) && mfma_bwd_alpha_ok(T, N, K, rowwise, dtype);
+}
+
+bcq_status bcq_node_backward(const uint32_t* packed, const float* alpha, const void* x, const void* dy, int dtype, int64_t T, int64_t N,
+                             int64_t K, int64_t g, int q, int q_train, float grad_scale, void* dx, void* input_workspace,
+                             size_t input_bytes, float* dalpha, void* alpha_workspace, size_t alpha_bytes, void* stream) {
+    if (!packed || !alpha || !x || !dy || !dx || !dalpha || !input_workspace || !alpha_workspace) return BCQ_ERR_NULL;
+    if (!bcq_node_backward_joint(0, dtype, T, N, K, g, q) || q_train < 1 || q_train > q) return BCQ_ERR_SHAPE;
+    if (misaligned(packed) || misaligned(alpha) || misaligned(x) || misaligned(dy) || misaligned(dx) || misaligned(dalpha))
+        return BCQ_ERR_ALIGN;
+    bcq_status s = check_workspace(input_workspace, input_bytes, workspace_least(BCQ_OP_BWD_INPUT, T, N, K, g, q, dtype));
     if (s != BCQ_OK) return s;
-    return bcq_linear_bwd_alpha_grouped(packed, x, dy, dtype, T, N, K, g, q, q_train, grad_scale, dalpha, alpha_workspace,
-                                        alpha_bytes, stream);
+    s = check_workspace(alpha_workspace, alpha_bytes, workspace_least(BCQ_OP_BWD_ALPHA, T, N, K, g, q, dtype));
+    if (s != BCQ_OK) return s;
+    s = check_device();
+    if (s != BCQ_OK) return s;
+    return done(bcq::launch_bwd_mfma(packed, alpha, x, dy, T, N, K, g, q, q_train, grad_scale, dx, input_workspace, dalpha,
+                                     alpha_workspace, (hipStream_t)stream));
 }
 
 bcq_status bcq_linear_bwd_alpha(const uint32_t* packed, const void* x, const void* dy, int dtype, int64_t T,

@@ -220,32 +220,37 @@ struct BCQLinearNode : public torch::autograd::Function<BCQLinearNode> {
         const auto twin = ctx->saved_data.find("twin");
         const uint32_t* packed_t = twin == ctx->saved_data.end() ? nullptr : words(twin->second.toTensor());
         const float grad_scale = (float)ctx->saved_data["grad_scale"].toDouble();
-        Tensor dx, dalpha, ws_x, ws_alpha;
-        bcq_status st = BCQ_OK;
-        if (ctx->needs_input_grad(0)) {
-            ws_x = scratch(BCQ_OP_BWD_INPUT, T, s, g, code, dy, &st);
+        Tensor dx, dalpha;
+        const auto workspace = [&](int op) {
+            bcq_status st = BCQ_OK;
+            const Tensor ws = scratch(op, T, s, g, code, dy, &st);
             if (st != BCQ_OK) raise_bcq_error(st, "bcq_workspace_bytes_grouped");
-            dx = at::empty({T, s.K}, dy.options());
-        }
-        if (ctx->needs_input_grad(1)) {
-            ws_alpha = scratch(BCQ_OP_BWD_ALPHA, T, s, g, code, dy, &st);
-            if (st != BCQ_OK) raise_bcq_error(st, "bcq_workspace_bytes_grouped");
-            dalpha = at::empty({q_train, s.N, s.G}, dy.options().dtype(at::kFloat));
-        }
-        if (dx.defined() && dalpha.defined()) {
-            st = bcq_node_backward(words(packed), packed_t, alpha.data_ptr<float>(), x2.data_ptr(), dy.data_ptr(), code, T, s.N, s.K,
-                                   g, (int)s.q, (int)q_train, grad_scale, dx.data_ptr(), ws_x.data_ptr(), (size_t)ws_x.numel(),
-                                   dalpha.data_ptr<float>(), ws_alpha.data_ptr(), (size_t)ws_alpha.numel(), current_stream());
-            if (st != BCQ_OK) raise_bcq_error(st, "bcq_linear_bwd");
-        } else if (dx.defined()) {
-            st = bcq_linear_bwd_input_grouped(words(packed), packed_t, alpha.data_ptr<float>(), dy.data_ptr(), code, T, s.N, s.K, g,
-                                              (int)s.q, dx.data_ptr(), ws_x.data_ptr(), (size_t)ws_x.numel(), current_stream());
-            if (st != BCQ_OK) raise_bcq_error(st, "bcq_linear_bwd_input_grouped");
-        } else if (dalpha.defined()) {
-            st = bcq_linear_bwd_alpha_grouped(words(packed), x2.data_ptr(), dy.data_ptr(), code, T, s.N, s.K, g, (int)s.q,
-                                              (int)q_train, grad_scale, dalpha.data_ptr<float>(), ws_alpha.data_ptr(),
-                                              (size_t)ws_alpha.numel(), current_stream());
-            if (st != BCQ_OK) raise_bcq_error(st, "bcq_linear_bwd_alpha_grouped");
+            return ws;
+        };
+        if (ctx->needs_input_grad(0)) dx = at::empty({T, s.K}, dy.options());
+        if (ctx->needs_input_grad(1)) dalpha = at::empty({q_train, s.N, s.G}, dy.options().dtype(at::kFloat));
+        if (dx.defined() && dalpha.defined() && bcq_node_backward_joint(packed_t != nullptr, code, T, s.N, s.K, g, (int)s.q)) {
+            const Tensor ws_x = workspace(BCQ_OP_BWD_INPUT), ws_alpha = workspace(BCQ_OP_BWD_ALPHA);
+            const bcq_status st = bcq_node_backward(words(packed), alpha.data_ptr<float>(), x2.data_ptr(), dy.data_ptr(), code, T, s.N,
+                                                    s.K, g, (int)s.q, (int)q_train, grad_scale, dx.data_ptr(), ws_x.data_ptr(),
+                                                    (size_t)ws_x.numel(), dalpha.data_ptr<float>(), ws_alpha.data_ptr(),
+                                                    (size_t)ws_alpha.numel(), current_stream());
+            if (st != BCQ_OK) raise_bcq_error(st, "bcq_node_backward");
+        } else {  // one after the other: each call's scratch is given back before the next takes its own
+            if (dx.defined()) {
+                const Tensor ws = workspace(BCQ_OP_BWD_INPUT);
+                const bcq_status st = bcq_linear_bwd_input_grouped(words(packed), packed_t, alpha.data_ptr<float>(), dy.data_ptr(), code, T,
+                                                                   s.N, s.K, g, (int)s.q, dx.data_ptr(), ws.data_ptr(),
+                                                                   (size_t)ws.numel(), current_stream());
+                if (st != BCQ_OK) raise_bcq_error(st, "bcq_linear_bwd_input_grouped");
+            }
+            if (dalpha.defined()) {
+                const Tensor ws = workspace(BCQ_OP_BWD_ALPHA);
+                const bcq_status st = bcq_linear_bwd_alpha_grouped(words(packed), x2.data_ptr(), dy.data_ptr(), code, T, s.N, s.K, g,
+                                                                   (int)s.q, (int)q_train, grad_scale, dalpha.data_ptr<float>(),
+                                                                   ws.data_ptr(), (size_t)ws.numel(), current_stream());
+                if (st != BCQ_OK) raise_bcq_error(st, "bcq_linear_bwd_alpha_grouped");
+            }
         }
         if (dx.defined()) dx = dx.reshape(ctx->saved_data["x_shape"].toIntVector());
         return {dx, dalpha, Tensor()};

@@ -34,3 +34,24 @@ def test_step_equals_separate_calls(T, N, K, g, q, q_train, dtype):
     only_alpha, = torch.autograd.grad(layer(x.detach()), (layer.alpha_train,), dy)
     for got, ref in zip((y.detach(),) + both + (only_x, only_alpha), want + want[1:]):
         assert torch.equal(got, ref)
+
+
+# unaligned rows, more than four planes, few tokens: nothing is joined, and the second call's scratch may not be held beside the first's
+@pytest.mark.parametrize("T,N,K,g,q", [(1500, 5002, 1056, 1056, 3), (2048, 1024, 2048, 2048, 6), (40, 4096, 2048, 128, 2), (3000, 2001, 2048, 64, 4)])
+def test_separate_gradients_hold_one_scratch_at_a_time(T, N, K, g, q):
+    import torch
+    import paper_2210_03858_amd as bcq
+    from paper_2210_03858_amd.autograd import BCQLinear
+    layer = BCQLinear.from_weight(torch.randn((N, K), device="cuda"), q, g=g)
+    x = torch.randn((T, K), device="cuda").bfloat16().requires_grad_(True)
+    dy = torch.randn((T, N), device="cuda").bfloat16()
+    y = layer(x)
+    torch.autograd.grad(y, (x, layer.alpha_train), dy, retain_graph=True)
+    sizes = [max(bcq.workspace_bytes_grouped(op, T, N, K, g, q, bcq.binding.BCQ_BF16), 16) for op in (2, 3)]
+    torch.cuda.synchronize()
+    before = torch.cuda.memory_allocated()
+    torch.cuda.reset_peak_memory_stats()
+    grads = torch.autograd.grad(y, (x, layer.alpha_train), dy)
+    peak = torch.cuda.max_memory_allocated() - before
+    assert min(sizes) > 1 << 20
+    assert peak < max(sizes) + sum(t.numel() * t.element_size() for t in grads) + min(sizes) // 2
