@@ -55,3 +55,31 @@ def test_separate_gradients_hold_one_scratch_at_a_time(T, N, K, g, q):
     peak = torch.cuda.max_memory_allocated() - before
     assert min(sizes) > 1 << 20
     assert peak < max(sizes) + sum(t.numel() * t.element_size() for t in grads) + min(sizes) // 2
+
+
+# where the scales are joined: by the expansion, by a kernel of its own, or nothing to join; where the scale gradient is reduced: beside the
+# expansion, by a kernel of its own, or without partial sums
+@pytest.mark.parametrize("T,N,K,g,q,q_train,dtype,join,reduction", [
+    (4096, 1024, 1024, 1024, 4, 1, "bf16", "expansion", "expansion"), (2100, 1280, 1280, 256, 2, 1, "bf16", "expansion", "expansion"),
+    (900, 1000, 1056, 96, 4, 3, "bf16", "expansion", "expansion"), (770, 2048, 2048, 2048, 1, 1, "bf16", None, "expansion"),
+    (1024, 640, 640, 640, 6, 2, "bf16", "expansion", "kernel"), (333, 1500, 1056, 1056, 3, 1, "bf16", "kernel", "kernel"),
+    (100, 512, 512, 128, 3, 1, "bf16", "kernel", "expansion"), (3, 96, 128, 64, 4, 2, "bf16", "kernel", "kernel"),
+    (20, 256, 512, 512, 2, 1, "bf16", "kernel", "kernel"), (12, 256, 512, 512, 2, 1, "bf16", "kernel", None), (33, 200, 96, 32, 2, 1, "f32", "kernel", None)])
+def test_where_scales_are_joined_and_reduced(T, N, K, g, q, q_train, dtype, join, reduction):
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    from paper_2210_03858_amd.autograd import BCQLinear
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    layer = BCQLinear.from_weight(torch.randn((N, K), device="cuda"), q, g=g, q_train=q_train)
+    x = torch.randn((T, K), device="cuda").to(dt).requires_grad_(True)
+    dy = torch.randn((T, N), device="cuda").to(dt)
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        torch.autograd.grad(layer(x), (x, layer.alpha_train), dy)
+        torch.cuda.synchronize()
+    ran = lambda name: any(name in e.key for e in prof.key_averages())
+    assert ran("join_scales_kernel") == (join == "kernel")
+    assert ran("expand_fwd_kernel") or join != "expansion"
+    assert not ran("CatArray")
+    assert ran("dalpha_reduce_kernel") == (reduction == "kernel")
+    assert ran("expand_bwd_rows_kernel") or reduction != "expansion"
