@@ -198,7 +198,7 @@ struct Expansion {
 constexpr int tile_wait(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }  // s_waitcnt vmcnt(n)
 
 template <int TM, int KG>
-constexpr int tile_stages() { return TM * KG <= 4 ? 3 : TM * KG <= 8 ? 4 : 2; }
+constexpr int tile_stages() { return TM * KG <= 4 ? 3 : 2; }
 template <int TM, int KG>
 constexpr int tile_lds_bytes() { return KG * tile_stages<TM, KG>() * TM * 16 * 256; }
 

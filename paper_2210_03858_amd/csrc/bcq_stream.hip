@@ -188,23 +188,27 @@ template <int MODE, bool TILED>
 static hipError_t launch_fused(const uint32_t* planes, const bf16_t* act, const float* alpha, const bf16_t* dy, void* out,
                                int64_t T, int64_t rows, int64_t cw, int q_used, float scale, const StreamPlan& p,
                                int gsegs, int G, hipStream_t st) {
-#define BCQ_FUSED_Q(QQ)                                                                                                \
-    if (p.halves == 2)                                                                                                 \
-        return launch_fused_cfg<MODE, QQ, true, TILED>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st); \
-    return launch_fused_cfg<MODE, QQ, false, TILED>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st);
+#define BCQ_FUSED(QQ, TT) \
+    return launch_fused_cfg<MODE, QQ, TT, TILED>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st);
+#define BCQ_FUSED_Q(TT)              \
+    switch (q_used) {                \
+        case 1: BCQ_FUSED(1, TT)     \
+        case 2: BCQ_FUSED(2, TT)     \
+        case 3: BCQ_FUSED(3, TT)     \
+        case 4: BCQ_FUSED(4, TT)     \
+        default: BCQ_FUSED(8, TT)    \
+    }
+    // one half of a forward, and with it the decode layout: more than four planes only, the others are few_fwd_kernel's
+    if constexpr (!TILED) {
+        if (p.halves == 2) { BCQ_FUSED_Q(true) }
+        if constexpr (MODE != STREAM_FWD) { BCQ_FUSED_Q(false) }
+    }
     if constexpr (MODE == STREAM_FWD) {
-        if (p.halves == 1) return q_used > 4 ? launch_fused_cfg<MODE, 8, false, TILED>(planes, act, alpha, dy, out, T, rows, cw, q_used, scale, p, gsegs, G, st)
-                                             : hipErrorInvalidConfiguration;  // few_fwd_kernel
+        if (p.halves == 1 && q_used > 4) BCQ_FUSED(8, false)
     }
-    if constexpr (TILED) return hipErrorInvalidConfiguration;
-    switch (q_used <= 4 ? q_used : 8) {
-        case 1: BCQ_FUSED_Q(1)
-        case 2: BCQ_FUSED_Q(2)
-        case 3: BCQ_FUSED_Q(3)
-        case 4: BCQ_FUSED_Q(4)
-        default: BCQ_FUSED_Q(8)
-    }
+    return hipErrorInvalidConfiguration;
 #undef BCQ_FUSED_Q
+#undef BCQ_FUSED
 }
 
 // ---- forward of at most 8 tokens in one kernel ------------------------------------------------------------------------
