@@ -55,7 +55,9 @@
  *     any finite value; terms below 2^-126 may count as zero) and adds in fp32.
  *   - Non-finite activations: a token row of x or dy that holds an Inf or NaN makes the outputs of that token
  *     non-finite and leaves every other token's outputs untouched (the scale gradient sums over tokens and becomes
- *     non-finite as a whole); the streaming paths return NaN for every output of such a token.
+ *     non-finite as a whole); the streaming paths return NaN for every output of such a token, and count a magnitude above
+ *     3.0e38 as non-finite (its first FP8 term may round up to 2^128).  They also sum over a row or a group before they scale,
+ *     in fp32: sums beyond its range are infinite, even if the scaled result is not.
  *   - HIP graphs: every call only launches kernels on `stream` (no allocation, no memset, no
  *     synchronisation), so it can be recorded into a graph.  The first launch of a kernel that
  *     needs more than 64 KiB of LDS raises that kernel's limit (a host-side attribute call), so

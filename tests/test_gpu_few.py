@@ -97,3 +97,17 @@ def test_beyond_the_lines_two_kernels_run(layout, T, N, K, g, q):
     y = _run(layout, packed, alpha, x, g, kernel="stream_kernel").double()
     ref = x.double() @ w.t()
     assert ((y - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * ref.abs().max()).all()
+
+
+@pytest.mark.parametrize("layout,T,N,K,g,q,kernel", [("decode", 4, 100, 1056, 1056, 3, "few_fwd_kernel"), ("canonical", 4, 40, 2048, 1024, 2, "few_fwd_kernel"),
+                                                     ("canonical", 4, 300, 9216, 9216, 2, "stream_kernel"), ("canonical", 4, 70, 640, 640, 6, "stream_fused_kernel")])
+def test_largest_magnitudes(layout, T, N, K, g, q, kernel):
+    """1.75 x 2^127 is multiplied like any other activation; from 3.0e38 on a token counts as non-finite, and no other token does."""
+    packed, alpha, x, w = _layer(q, N, K, g, T, N)
+    alpha, w = alpha * 2.0 ** -10, w * 2.0 ** -10
+    x[1, 7], x[2, 9] = 1.75 * 2.0 ** 127, 3.2e38
+    y = _run(layout, packed, alpha, x, g, kernel=kernel).double()
+    ref = x.double() @ w.t()
+    ok = torch.tensor([0, 1, 3], device="cuda")
+    assert ((y - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * ref.abs().max(dim=1, keepdim=True).values)[ok].all()
+    assert y[2].isnan().all()
