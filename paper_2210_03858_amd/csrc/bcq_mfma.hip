@@ -82,15 +82,8 @@ __device__ __forceinline__ void store_word_frags(const float (&s)[32], u32x4* __
 // q = 1 17 / 12, input gradient of 2048 x 8192 at 65 tokens 33 / 18, of 6144 x 2048 at 86 40 / 29; workspaces in turn, where no
 // XCD holds them, 12.2 / 12.1, 18 / 18, 28 / 29.
 
-// expand for the forward: columns of the GEMM = rows n of W, contraction = k.
-// thread = (one row n, one packed word = 32 columns k) -> four 16-byte fragment slots; block = 8 rows x 32 words, so that it
-// reads whole 128-byte lines and stores whole 128-byte pieces (32 rows x 8 words, the lines shared by four blocks: 13.4 us
-// instead of 12.1).  Q planes by table up to four, else (Q = 0) q of them as signed sums.  What bounds it is the 16 bits per
-// weight that it writes (5.4 TB/s with its reads); by signed sums four planes were bound by vector operations.  Measured:
-// 10240 x 2560, q = 4 17.7 -> 12.5 us, 2560 x 10240 17.5 -> 11.8, 8192 x 2048, q = 3 10.8 -> 8.4, 4096 x 1024 5.6 -> 5.2.
-//
-// The scales of a layer in training lie in two tensors (ScaleParts), and its backward pass wants them in one: blocks beyond
-// the expansion's write that (a concatenation before the expansion was a launch of 4 to 6 us).
+// The scales of a layer in training lie in two tensors (ScaleParts), and its backward pass wants them in one: blocks beyond those of
+// the forward's expansion write that (a concatenation before the expansion was a launch of 4 to 6 us).
 __device__ __forceinline__ void join_scales(const ScaleParts& a, int64_t per_plane, int q, uint32_t chunk) {
     const int64_t split = a.q_first * per_plane, total = q * per_plane;
     const int64_t idx0 = (int64_t)chunk * 2048 + threadIdx.x;
@@ -114,6 +107,12 @@ hipError_t launch_join_scales(const ScaleParts& a, int64_t per_plane, int q, hip
     return hipGetLastError();
 }
 
+// expand for the forward: columns of the GEMM = rows n of W, contraction = k.
+// thread = (one row n, one packed word = 32 columns k) -> four 16-byte fragment slots; block = 8 rows x 32 words, so that it
+// reads whole 128-byte lines and stores whole 128-byte pieces (32 rows x 8 words, the lines shared by four blocks: 13.4 us
+// instead of 12.1).  Q planes by table up to four, else (Q = 0) q of them as signed sums.  What bounds it is the 16 bits per
+// weight that it writes (5.4 TB/s with its reads); by signed sums four planes were bound by vector operations.  Measured:
+// 10240 x 2560, q = 4 17.7 -> 12.5 us, 2560 x 10240 17.5 -> 11.8, 8192 x 2048, q = 3 10.8 -> 8.4, 4096 x 1024 5.6 -> 5.2.
 template <int Q>
 __global__ __launch_bounds__(256) void expand_fwd_kernel(const uint32_t* __restrict__ packed, ScaleParts alpha, uint32_t blocks,
                                                          int64_t N, int64_t K, int64_t g, int q,
