@@ -600,7 +600,8 @@ static bool one_full_round(int64_t T, int64_t N, int64_t K, int q) {
     return T <= 256 && tiles <= 512 && tiles > (q == 4 ? 384 : 320);
 }
 
-// Where one kernel is faster than expanding What and multiplying.  Up to 32 tokens, and with row-wise scales up to 128: always.
+// Where one kernel is faster than expanding What and multiplying.  Up to 16 tokens always, with row-wise scales up to
+// 128 unless the estimates below are clearly against it.
 // Row-wise scales, 129 to 384 tokens: except above 40 million weights, and with four planes above 256 tokens above 8
 // million, unless one_full_round, and up to 100 million, from where What no longer fits the 256 MB cache in front of HBM.  These
 // lines were set (65000 timings) against a one-kernel form of the rows and tokens that one_full_round counts; of 70 random calls in
@@ -613,8 +614,8 @@ static bool one_full_round(int64_t T, int64_t N, int64_t K, int q) {
 // estimate is a tenth below that of two (us, one / two: 421 tokens of 1312 x 5248, q = 1, groups of 128, 20.6 / 24.5, 720 of 2336 x 2336,
 // q = 1, 17.5 / 21.8, 206 of 2496 x 9984, q = 2, groups of 32, 34 / 45; with equal estimates 301 of 14680 x 4096, q = 2, groups of 256,
 // 98 / 70, 602 of 3720 x 6432, q = 2, 69 / 53), and two kernels where the one's is a tenth above (378 of 11392 x 2464, q = 3, 54 / 37).
-// Against the forms before tile_fwd_kernel, 1159 random calls of 33 to 768 tokens: 0.87 of the time, 40 more than 4 % slower, 12 more
-// than 8 %, worst 1.15 (140 tokens of 2720 x 2528, q = 2, 13.1 -> 15.1); no choice of route or plan would leave less than 17.
+// Against the forms before tile_fwd_kernel, 1159 random calls of 33 to 768 tokens: 0.87 of the time, 40 more than 4 % slower, 12 of them
+// more than 8 %, worst 1.15 (140 tokens of 2720 x 2528, q = 2, 13.1 -> 15.1); no choice of route or plan would leave less than 17.
 bool fused_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
     // layers of fewer rows than tokens have few row tiles, and no room for the sums of parts
     if (q > 4 || T > 768 || (T > 32 && (T + 31) / 32 * 32 * K * 2 > (int64_t)mfma_fwd_workspace(N, K))) return false;

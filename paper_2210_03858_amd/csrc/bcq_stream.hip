@@ -250,8 +250,8 @@ static FewPlan few_plan(int64_t T, int64_t rows, int segs, int q, bool rowwise, 
 // Groups (whole segments here) read their scales from the canonical planes' side in 16-byte pieces: four tokens of 1022 x 6144, groups
 // of 1024, q = 4, 9.2 / 10.4, of 72 x 9216, groups of 1536, 10.2 / 15.8, six of 2590 x 3072 9.0 / 10.5, of 8692 x 2048 9.0 / 10.6, from the decode layout
 // 2339 x 3072 8.8 / 7.7 at eight, 164 x 9216 9.8 / 11.4 at three.
-// Against the kernels that ran before this one, 5000 random calls of both layouts: 0.79 of the time, 34 more than 4 % slower, 6 more
-// than 8 % (worst 1.25: four tokens of 4157 x 7680, groups of 512, q = 3, decode layout).
+// Against the kernels that ran before this one, 5000 random calls of both layouts: 0.79 of the time, 34 more than 4 % slower, 6 of
+// them more than 8 % (worst 1.25: four tokens of 4157 x 7680, groups of 512, q = 3, decode layout).
 static bool few_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q, bool tiled) {
     if (N * K > 32000000) return false;
     const FewPlan p = few_plan(T, N, (int)((K + 511) / 512), q, g == K, tiled);
