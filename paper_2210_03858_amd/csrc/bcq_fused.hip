@@ -5,157 +5,136 @@
 // the registers of the matrix instructions (by table, bcq_expand.h).  At these token counts the two-kernel path is bound by
 // writing and re-reading 16 bits per weight, here a weight costs q bits.
 //
-// Two forms: fused_fwd_kernel up to 32 tokens (32 rows to a workgroup, its waves share the contraction), tile_fwd_kernel above.
+// Two forms: group_fwd_kernel up to 32 tokens (16 rows to a workgroup, its waves share the contraction), tile_fwd_kernel above.
 #include <type_traits>
 
 #include "bcq_expand.h"
 
 namespace bcq {
 
-typedef __attribute__((ext_vector_type(16))) float fu_f32x16;
-
-// Up to 32 tokens.  A workgroup owns 32 rows; its eight waves take runs of 128 columns in turn and add their tiles through LDS
-// in wave order (deterministic).  What bounds it: the planes' scattered rows and launch latency (6144 x 2048, groups of 128,
-// 4 tokens: 26 -> 9 us against two kernels).
-template <int Q>
-__global__ __launch_bounds__(512) void fused_fwd_kernel(const uint32_t* __restrict__ packed,
-                                                        const float* __restrict__ alpha, const bf16_t* __restrict__ x,
-                                                        bf16_t* __restrict__ y, int64_t T, int64_t N, int64_t K,
-                                                        int64_t g, int per, float* __restrict__ sums) {
-    constexpr int W = 8;
-    __shared__ f32x4 part[W][4][64];
-    const int lane = threadIdx.x & 63;
+// Up to 32 tokens.  A workgroup owns 16 rows; a wave takes a segment of 128 WPL columns at a time, of which lane row h expands the WPL
+// words 4 h WPL .. of its row (one group: WPL divides the words of a group), so that a plane costs one load and one scale per lane and
+// segment, and adds into 16 rows x 16 TT tokens of v_mfma_f32_16x16x32_bf16.  The segment's activations go global -> LDS directly, a
+// token's columns in a row, and stay with the wave; the waves' tiles meet in LDS and are added in wave order (deterministic).
+// What bounds it: launch, one trip to memory and, in larger layers, the expansion's vector operations.  Groups of 128, q = 3, 4 tokens, us,
+// against 32 rows to a workgroup and single words and scales per request (scattered requests bound that kernel): 6144 x 2048 10.4 -> 5.7,
+// 2048 x 2048 7.2 and a sum of 2 -> 3.9, 8192 x 2048 10.5 -> 6.1, 2048 x 8192 10 and a sum of 3 -> 7.3; 16 tokens of 7680 x 2560 7.1, 32 8.8.
+template <int Q, int WPL, int TT>
+__global__ __launch_bounds__(1024) void group_fwd_kernel(const uint32_t* __restrict__ packed, const float* __restrict__ alpha,
+                                                         const bf16_t* __restrict__ x, bf16_t* __restrict__ y, int T, int64_t N,
+                                                         int K, int gw, uint32_t inverse, int segs, int per, int W, int stage,
+                                                         float* __restrict__ sums) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the buffer-resource builtins exist in the device pass only
+    constexpr int SLOTS = 16 * WPL, TPR = 4 / WPL;  // 16-byte pieces of a token's segment; tokens of a request
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int lane = threadIdx.x & 63, r = lane & 15, h = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int col = lane & 31, h = lane >> 5;
-    const int64_t n0 = (int64_t)blockIdx.x * 32, t0 = (int64_t)blockIdx.y * 32;
-    const int64_t n = n0 + col < N ? n0 + col : N - 1;  // rows and tokens beyond the edge are computed, never stored
-    const int Kw = (int)(K / 32), G = (int)(K / g), gw = (int)(g / 32);
-    // this workgroup's units of 128 columns: part blockIdx.z of `per` each (all of them when the contraction is not split)
-    const int first = (int)blockIdx.z * per + wave;
-    const int units = min((Kw + 3) / 4, (int)(blockIdx.z + 1) * per);
+    const int64_t n0 = (int64_t)blockIdx.x * 16, left = N - 1 - n0;
+    const int Kw = K / 32, G = Kw / gw;
+    const int first = (int)blockIdx.y * per + wave, end = min(segs, (int)(blockIdx.y + 1) * per);
 
-    const uint32_t* prow[Q];
-    const float* arow[Q];
+    // rows beyond the edge are computed, never stored; addresses are a uniform base and a 32-bit lane offset
+    const uint32_t row = (uint32_t)(r < left ? r : left), roff = row * (uint32_t)Kw, aoff = row * (uint32_t)G;
+    const uint32_t* const prow = packed + n0 * Kw;
+    const float* const arow = alpha + n0 * G;
+    const int64_t plane = N * Kw, splane = N * G;
+    uint32_t bits[Q][WPL];
+    float a[Q];
+    auto request = [&](int s) {
+        const int w0 = (4 * s + h) * WPL, wl = w0 < Kw ? w0 : Kw - WPL;  // words beyond K meet zero weights (WPL divides Kw)
 #pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        prow[i] = packed + ((int64_t)i * N + n) * Kw;
-        arow[i] = alpha + ((int64_t)i * N + n) * G;
+        for (int i = 0; i < Q; ++i) __builtin_memcpy(bits[i], prow + i * plane + (roff + (uint32_t)wl), 4 * WPL);
+        const uint32_t grp = inverse ? __umulhi((uint32_t)wl, inverse) : (uint32_t)wl;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) a[i] = arow[i * splane + (aoff + grp)];
+    };
+    // activations: piece c (columns 8 c .. + 7) of a token lies at slot c ^ (token & 15) among its 16: the reads below touch every bank once
+    unsigned char* const mine = smem + wave * stage;
+    __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)x, 0, T * K * 2, 0x00020000);
+    auto fetch = [&](int s) {
+        const int slot = lane & (SLOTS - 1);
+        for (int d = 0; d * TPR < T; ++d) {  // (requests of several tokens repeat the last one beyond T)
+            const int tt = d * TPR + lane / SLOTS, t = tt < T ? tt : T - 1;
+            const int col = 8 * (slot ^ (tt & 15));
+            const uint32_t off = s * (128 * WPL) + col < K ? (uint32_t)(t * K + col) * 2u : 0x80000000u;  // beyond K: zeros
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (void __attribute__((address_space(3)))*)(mine + d * 1024), 16, off,
+                                                     s * (256 * WPL), 0, 0);
+        }
+    };
+    uint32_t base[TT], turn[TT];  // lane row h reads pieces 4 WPL h + 4 e + f of token r
+#pragma unroll
+    for (int i = 0; i < TT; ++i) {
+        const int t = r + 16 * i < T ? r + 16 * i : T - 1;
+        base[i] = (uint32_t)(t * 256 * WPL + (4 * WPL * h & ~15) * 16);
+        turn[i] = (uint32_t)(((4 * WPL * h & 15) ^ (t & 15)) * 16);
     }
-    // of a 32-column word, lane half h contracts over columns 16 h .. 16 h + 15
-    const bf16_t* const xrow = x + (t0 + col < T ? t0 + col : T - 1) * K + 16 * h;
-    fu_f32x16 acc;
+    f32x4 acc[TT];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    for (int i = 0; i < TT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // In flight per wave: the planes (and scales of group-wise calls) one unit ahead, so that four waves fit a SIMD (two units
-    // ahead: 8.7 -> 12 us for 6144 x 2048 at 4 tokens), the activations two words ahead.
-    uint32_t bits[Q][4];
-    float a[2][Q];  // [pair of words]
-    auto load_bits = [&](int u) {
-        if (4 * u + 4 <= Kw) {
+    if (first < end) {
+        request(first);
+        fetch(first);
+    }
+    for (int s = first; s < end; s += W) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        uint32_t w[WPL][Q];
 #pragma unroll
-            for (int i = 0; i < Q; ++i) __builtin_memcpy(bits[i], prow[i] + 4 * u, 16);
+        for (int i = 0; i < Q; ++i)
+#pragma unroll
+            for (int e = 0; e < WPL; ++e) w[e][i] = bits[i][e];
+        LevelTable<Q> table;
+        table.build(a);
+        if ((4 * s + 4) * WPL > Kw) {  // zero weights beyond K, as Inf times a zero activation is NaN
+            const uint32_t live = (4 * s + h) * WPL < Kw ? ~0u : 0u;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                table.lo[e] &= live;
+                table.hi[e] &= live;
+            }
+        }
+        if (s + W < end) request(s + W);
+#pragma unroll
+        for (int e = 0; e < WPL; ++e) {
+            u32x4 xf[TT][4], frag[4];
+#pragma unroll
+            for (int i = 0; i < TT; ++i)
+#pragma unroll
+                for (int f = 0; f < 4; ++f)
+                    xf[i][f] = *reinterpret_cast<const u32x4*>(mine + base[i] + (turn[i] ^ (uint32_t)((4 * e + f) * 16)));
+            expand32<Q>(w[e], table, frag);
+#pragma unroll
+            for (int f = 0; f < 4; ++f)
+#pragma unroll
+                for (int i = 0; i < TT; ++i)
+                    acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(frag[f]), as_bf16x8(xf[i][f]), acc[i], 0, 0, 0);
+        }
+        if (s + W < end) fetch(s + W);  // (every read of the stage has been used)
+    }
+
+    f32x4* const own = reinterpret_cast<f32x4*>(mine) + lane;  // the wave's stage is free
+#pragma unroll
+    for (int i = 0; i < TT; ++i) own[64 * i] = acc[i];
+    __syncthreads();
+    for (int i = wave; i < TT; i += W) {
+        const unsigned char* p = smem + (64 * i + lane) * 16;
+        f32x4 s = *reinterpret_cast<const f32x4*>(p);
+#pragma unroll 4
+        for (int k = 1; k < W; ++k) s += *reinterpret_cast<const f32x4*>(p + k * stage);
+        // register e of lane (r, h): row n0 + 4 h + e, token 16 i + r
+        const int64_t t = 16 * i + r, n = n0 + 4 * h;
+        if (t >= T || n >= N) continue;
+        if (sums) {  // split contraction: sum_parts_kernel adds the parts
+            *reinterpret_cast<f32x4*>(sums + ((int64_t)blockIdx.y * T + t) * ((N + 3) / 4 * 4) + n) = s;
+        } else if ((N & 3) == 0) {
+            *reinterpret_cast<uint2*>(y + t * N + n) = make_uint2(pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3]));
         } else {
 #pragma unroll
-            for (int i = 0; i < Q; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) bits[i][j] = 4 * u + j < Kw ? prow[i][4 * u + j] : 0u;
-        }
-    };
-    auto load_alpha = [&](int w, float (&dst)[Q]) {
-        const int grp = (w < Kw ? w : Kw - 1) / gw;
-#pragma unroll
-        for (int i = 0; i < Q; ++i) dst[i] = arow[i][grp];
-    };
-    auto load_unit = [&](int u) {
-        load_bits(u);
-        load_alpha(4 * u, a[0]);
-        load_alpha(4 * u + 2, a[1]);
-    };
-    u32x4 xf[2][2];  // [word][slice]
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-    auto load_x = [&](int w, int slot) {  // words beyond K contribute nothing
-#pragma unroll
-        for (int sub = 0; sub < 2; ++sub)
-            xf[slot][sub] = w < Kw ? *reinterpret_cast<const u32x4*>(xrow + 32 * w + 8 * sub) : zero;
-    };
-    LevelTable<Q> table;
-    // the two words of a pair may lie in two groups (g = 32): then the table is rebuilt between them
-    const bool split = (gw & 1) != 0;
-    const uint32_t half_sel = h ? 0x07060302u : 0x05040100u;
-
-    auto clamp_unit = [&](int u) { return u < units ? u : units - 1; };
-    load_unit(clamp_unit(first));
-#pragma unroll
-    for (int j = 0; j < 2; ++j) load_x(4 * clamp_unit(first) + j, j);
-
-    // (a lambda and no early return: with the loop's body in place and a return before the sums the compiler orders the loads of
-    // the first units otherwise, 1.4 % over 300 random calls)
-    auto unit = [&](int u) {
-        uint32_t own[2][Q];  // this lane half's 2 x 16 signs of each pair of words
-        LevelTable<Q> tables[2];
-#pragma unroll
-        for (int pr = 0; pr < 2; ++pr) {
-#pragma unroll
-            for (int i = 0; i < Q; ++i)
-                own[pr][i] = __builtin_amdgcn_perm(bits[i][2 * pr + 1], bits[i][2 * pr], half_sel);
-            tables[pr].build(a[pr]);
-        }
-        load_unit(clamp_unit(u + W));
-#pragma unroll
-        for (int pr = 0; pr < 2; ++pr) {
-            if (4 * u + 2 * pr < Kw) {
-                u32x4 frag[4];
-                expand32<Q>(own[pr], tables[pr], frag);
-                if (split) {
-                    u32x4 second[4];
-                    float as[Q];
-                    load_alpha(4 * u + 2 * pr + 1, as);
-                    if (4 * u + 2 * pr + 1 >= Kw) {  // no such columns: zero weights, as Inf times a zero activation is NaN
-#pragma unroll
-                        for (int i = 0; i < Q; ++i) as[i] = 0.f;
-                    }
-                    table.build(as);
-                    expand32<Q>(own[pr], table, second);
-                    frag[2] = second[2];
-                    frag[3] = second[3];
-                }
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-#pragma unroll
-                    for (int sub = 0; sub < 2; ++sub)
-                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, frag[2 * j + sub]),
-                                                                      __builtin_bit_cast(bf16x8, xf[j][sub]), acc, 0, 0, 0);
-                    load_x(pr == 0 ? 4 * u + 2 + j : 4 * clamp_unit(u + W) + j, j);
-                }
-            }
-        }
-    };
-    for (int u = first; u < units; u += W) unit(u);
-
-    // accumulator register 4 gg + e of lane l: row n0 + 8 gg + 4 (l / 32) + e, token l % 32
-#pragma unroll
-    for (int gg = 0; gg < 4; ++gg) part[wave][gg][lane] = f32x4{acc[4 * gg], acc[4 * gg + 1], acc[4 * gg + 2], acc[4 * gg + 3]};
-    __syncthreads();
-    if (threadIdx.x < 256) {
-        const int gg = threadIdx.x >> 6;
-        f32x4 s = part[0][gg][lane];
-#pragma unroll
-        for (int w = 1; w < W; ++w) s += part[w][gg][lane];
-        const int64_t t = t0 + col, nn = n0 + 8 * gg + 4 * h;
-        if (sums) {  // split contraction: sum_parts_kernel adds the parts
-            if (t < T && nn < N) *reinterpret_cast<f32x4*>(sums + ((int64_t)blockIdx.z * T + t) * ((N + 3) / 4 * 4) + nn) = s;
-        } else if (t < T) {
-            bf16_t* dst = y + t * N + nn;
-            if (nn + 3 < N && (N & 3) == 0) {
-                *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3]));
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (nn + e < N) dst[e] = f32_to_bf16(s[e]);
-            }
+            for (int e = 0; e < 4; ++e)
+                if (n + e < N) y[t * N + n + e] = f32_to_bf16(s[e]);
         }
     }
+#endif
 }
 
 // ---- 33 tokens and more ---------------------------------------------------------------------------------------------
@@ -565,6 +544,54 @@ static hipError_t launch_tile(const uint32_t* packed, const float* alpha, const 
     return launch_sums(sums, p.parts, T, N, y, st);
 }
 
+// Words of a lane, waves of a workgroup, parts of the contraction and segments per part, from 700 random calls of 1 to 32 tokens
+// whose plans were all timed: the pick takes 1.027 times the fastest on average, and 0.67 of the time of a kernel whose waves read
+// 32 rows and every scale of 128 columns apart (two calls of 3 to 6 us slower).
+struct GroupPlan {
+    int wpl, W, parts, per;
+};
+static int group_stage(int64_t T, int wpl) { return (int)((T * wpl + 3) / 4) * 1024; }  // LDS of a wave
+static GroupPlan group_plan(int64_t T, int64_t N, int64_t K, int64_t g) {
+    GroupPlan p;
+    const int64_t gw = g / 32, tiles = (N + 15) / 16;
+    int64_t segs = 0;
+    // As many words as the group size allows (one load and one table for them all: 2048 x 2048 at 4 tokens 3.9 us, with two words
+    // 4.2, with one 4.7), two above 16 tokens for the stages' sake, fewer where that leaves a chip with 256 waves idle.
+    for (p.wpl = gw % 4 == 0 && T <= 16 ? 4 : gw % 2 == 0 ? 2 : 1;; p.wpl /= 2) {
+        segs = (K + 128 * p.wpl - 1) / (128 * p.wpl);
+        if (p.wpl == 1 || tiles * segs >= 256) break;
+    }
+    // One turn if possible; where compute units hold several workgroups, two of them have to fit.
+    const int64_t room = (tiles > 256 ? 80 : 160) * 1024 / group_stage(T, p.wpl);
+    const auto waves = [&](int64_t n, int64_t most) { const int64_t m = most < room ? most : room, turns = (n + m - 1) / m; return (n + turns - 1) / turns; };
+    p.W = (int)waves(segs, tiles > 256 ? 8 : 16);
+    // Few rows and a long contraction: parts of it on compute units of their own while they find an idle one and it saves a turn
+    // (1280 x 5120, groups of 32, 29 tokens: 13.8 -> 10.8 us; 2048 x 8192, 4 tokens, in one turn 7.3, in two parts 7.6).
+    p.parts = 1;
+    while (p.parts < 8 && tiles * p.parts * 2 <= 256 && (segs + p.parts - 1) / p.parts >= 2 * p.W &&
+           sums_bytes(T, N, 2 * p.parts) <= mfma_fwd_workspace(N, K))
+        p.parts *= 2;
+    p.per = (int)((segs + p.parts - 1) / p.parts);
+    p.parts = (int)((segs + p.per - 1) / p.per);
+    if (p.parts > 1) p.W = (int)waves(p.per, 16);
+    return p;
+}
+
+template <int Q, int WPL>
+static hipError_t launch_group(const uint32_t* packed, const float* alpha, const bf16_t* x, int64_t T, int64_t N, int64_t K,
+                               int64_t g, bf16_t* y, float* sums, const GroupPlan& p, hipStream_t st) {
+    const int stage = group_stage(T, WPL), segs = (int)((K + 128 * WPL - 1) / (128 * WPL));
+    const uint32_t gw = (uint32_t)(g / 32), inverse = gw == 1 ? 0u : 0xFFFFFFFFu / gw + 1u;  // word / gw = high half of word * inverse
+    const size_t lds = (size_t)p.W * stage;
+    const auto kernel = T <= 16 ? group_fwd_kernel<Q, WPL, 1> : group_fwd_kernel<Q, WPL, 2>;
+    static LdsLimit limit[2];
+    hipError_t e = limit[T > 16].ensure((const void*)kernel, lds);
+    if (e != hipSuccess) return e;
+    BCQ_LAUNCH(kernel, dim3((unsigned)((N + 15) / 16), (unsigned)p.parts), dim3((unsigned)(64 * p.W)), lds, st, packed, alpha, x, y, (int)T,
+               N, (int)K, (int)gw, inverse, segs, p.per, p.W, stage, p.parts > 1 ? sums : nullptr);
+    return launch_sums(sums, p.parts, T, N, y, st);
+}
+
 template <int Q>
 static hipError_t launch_q(const uint32_t* packed, const float* alpha, const bf16_t* x, int64_t T, int64_t N, int64_t K,
                            int64_t g, bf16_t* y, float* sums, hipStream_t st) {
@@ -577,18 +604,10 @@ static hipError_t launch_q(const uint32_t* packed, const float* alpha, const bf1
         if (g != K) return launch_tile<Q, 8, 2, true>(packed, alpha, x, T, N, K, g, y, sums, p, st);
         return launch_tile<Q, 8, 2, false>(packed, alpha, x, T, N, K, g, y, sums, p, st);
     }
-    const unsigned cols = (unsigned)((N + 31) / 32);
-    const int units = (int)((K + 127) / 128);
-    // Few rows and a long contraction: parts of it go to workgroups of their own while they still find an idle compute
-    // unit and every wave keeps a unit (2048 x 8192, groups of 128, 4 tokens: 25.2 -> 12.5 us, 1024 x 4096 at 32 tokens
-    // 16.5 -> 9.7; below 2048 columns the extra launch costs more).
-    int parts = 1;
-    while (units >= 16 && cols * parts * 2 <= 256u && units >= 16 * parts && sums_bytes(T, N, 2 * parts) <= mfma_fwd_workspace(N, K)) parts *= 2;
-    const int per = (units + parts - 1) / parts;
-    parts = (units + per - 1) / per;
-    BCQ_LAUNCH(fused_fwd_kernel<Q>, dim3(cols, 1, (unsigned)parts), dim3(512), 0, st, packed, alpha, x, y, T, N, K, g, per,
-                       parts > 1 ? sums : nullptr);
-    return launch_sums(sums, parts, T, N, y, st);
+    const GroupPlan p = group_plan(T, N, K, g);
+    if (p.wpl == 4) return launch_group<Q, 4>(packed, alpha, x, T, N, K, g, y, sums, p, st);
+    if (p.wpl == 2) return launch_group<Q, 2>(packed, alpha, x, T, N, K, g, y, sums, p, st);
+    return launch_group<Q, 1>(packed, alpha, x, T, N, K, g, y, sums, p, st);
 }
 
 // Row-wise scales, 129 to 384 tokens, large layers: whether row tiles of 32 rows and 128 tokens (64 in smaller layers) fill one round
@@ -600,8 +619,8 @@ static bool one_full_round(int64_t T, int64_t N, int64_t K, int q) {
     return T <= 256 && tiles <= 512 && tiles > (q == 4 ? 384 : 320);
 }
 
-// Where one kernel is faster than expanding What and multiplying.  Up to 16 tokens always, with row-wise scales up to
-// 128 unless the estimates below are clearly against it.
+// Where one kernel is faster than expanding What and multiplying.  Up to 32 tokens always (one / two kernels, us: 32 tokens, q = 4,
+// groups of 32, of 10240 x 2592 16 / 25, of 40960 x 960 21 / 40, of 10240 x 96 3.3 / 7.2), with row-wise scales up to 128 unless the estimates below are clearly against it.
 // Row-wise scales, 129 to 384 tokens: except above 40 million weights, and with four planes above 256 tokens above 8
 // million, unless one_full_round, and up to 100 million, from where What no longer fits the 256 MB cache in front of HBM.  These
 // lines were set (65000 timings) against a one-kernel form of the rows and tokens that one_full_round counts; of 70 random calls in
@@ -619,7 +638,7 @@ static bool one_full_round(int64_t T, int64_t N, int64_t K, int q) {
 bool fused_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
     // layers of fewer rows than tokens have few row tiles, and no room for the sums of parts
     if (q > 4 || T > 768 || (T > 32 && (T + 31) / 32 * 32 * K * 2 > (int64_t)mfma_fwd_workspace(N, K))) return false;
-    if (T <= 16) return true;
+    if (T <= 32) return true;
     const int64_t work = N * K * T;
     if (T > 32 && K > 512 && N * K > 1000000) {
         const double one = tile_plan(T, N, K, g, q).estimate, two = two_kernel_estimate(T, N, K, q);
