@@ -28,6 +28,16 @@
 // which every wave does for itself, so that a vector of one wave meets no barrier and any other one per round.  Measured:
 // 15 rounds of 1024 x 1024: q = 3 72 -> 27 us, q = 4 119 -> 38 (against four waves, the vector in LDS and 2^q fp64
 // distances per element).
+//
+// Vectors of one wave and at least 8 rounds (RANKED): all that a round needs of the elements is how many lie below each threshold and their
+// sum, as every sum is a combination of those of the cells between the thresholds.  So the wave sorts the |w| once (6000
+// cycles, about 1400 operations) and keeps the sums of the first of them; a threshold is then found by one comparison of the lanes'
+// smallest elements and one of 16 elements, and the greedy start is found the same way.  A round of q = 3 takes 1800 cycles for 3450: solve
+// 530, levels and thresholds 400 (1020 with sorting them anew: the last order is only confirmed), the search 600 where the
+// elements took 1880; far code out of the loop's way is worth 500 of it, a lone wave waits for every jump.  15 rounds, us, 1024
+// vectors of 1024, q = 2, 3, 4: 17.8, 26.6, 38 -> 15.3, 19.4, 29.6; 4096 of them 40, 71, 108 -> 33, 49, 77; 8192 of 256 30, 74,
+// 116 -> 27, 56, 102.  Below 8 rounds the sorting costs more than it saves (4096 of 1024, q = 2, 4 rounds 18 / 23, 8 28.5 / 27.8; q = 4
+// 39 / 44, 64 / 57).  Of several waves, which exchange their sums at a barrier, 1024 of 2560 take 73 us either way.
 #include <type_traits>
 
 #include "bcq_internal.h"
@@ -35,6 +45,7 @@
 namespace bcq {
 
 constexpr int ALT_MAX_WAVES = 4;
+constexpr int ALT_SORT_ROUNDS = 8;  // (figures above)
 
 template <int Q>
 struct AltShared {
@@ -330,24 +341,142 @@ __device__ __forceinline__ void wave_sums(double (&v)[NV]) {
     }
 }
 
+// Ascending order of the NE values of a lane, by odd-even merges (Batcher).
+template <int NE>
+__device__ __forceinline__ void sort_lane(uint32_t (&m)[NE]) {
+#pragma unroll
+    for (int p = 1; p < NE; p *= 2)
+#pragma unroll
+        for (int k = p; k >= 1; k /= 2)
+#pragma unroll
+            for (int j = k % p; j + k < NE; j += 2 * k)
+#pragma unroll
+                for (int i = 0; i < k; ++i)
+                    if (i + j + k < NE && (i + j) / (2 * p) == (i + j + k) / (2 * p)) {
+                        const uint32_t lo = m[i + j], hi = m[i + j + k];
+                        m[i + j] = lo < hi ? lo : hi;
+                        m[i + j + k] = lo < hi ? hi : lo;
+                    }
+}
+
+// Ascending order of the 64 NE values of a wave (lane l ends with values NE l .. + NE - 1): the lanes' sorted runs are merged in pairs,
+// a run with the mirror image of the next one first (which needs no descending runs), then at half the distance and so on.  The values
+// are bits of non-negative floats: the smaller of two is their median with 0, the larger that with infinity, so that a lane keeps its
+// side of an exchange in one operation.
+template <int NE>
+__device__ __forceinline__ void sort_wave(uint32_t (&m)[NE]) {
+    const int lane = threadIdx.x & 63;
+    const auto keep = [](uint32_t a, uint32_t b, float side) {
+        return __float_as_uint(__builtin_amdgcn_fmed3f(__uint_as_float(a), __uint_as_float(b), side));
+    };
+    const auto side_of = [&](int bit) { return __uint_as_float((lane & bit) != 0 ? 0x7F800000u : 0u); };
+    const auto swap16 = [](uint32_t a) { return __builtin_amdgcn_permlane16_swap(a, a, false, false); };
+    const auto swap32 = [](uint32_t a) { return __builtin_amdgcn_permlane32_swap(a, a, false, false); };
+    sort_lane(m);
+#pragma unroll
+    for (int block = 2; block <= 64; block *= 2) {  // lanes of a merged run
+        const float upper = side_of(block / 2);
+        uint32_t other[NE];
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {  // of lane ^ (block - 1)
+            const uint32_t v = m[NE - 1 - i];
+            uint32_t o = block == 2 ? dpp_move<DPP_XOR1>(v) : block == 4 ? dpp_move<DPP_QUAD_REVERSE>(v)
+                       : block == 8 ? dpp_move<DPP_HALF_MIRROR>(v) : dpp_move<DPP_MIRROR>(v);
+            if (block >= 32) {
+                const auto s = swap16(o);
+                o = (lane & 16) ? s[0] : s[1];
+            }
+            if (block >= 64) {
+                const auto s = swap32(o);
+                o = (lane & 32) ? s[0] : s[1];
+            }
+            other[i] = o;
+        }
+#pragma unroll
+        for (int i = 0; i < NE; ++i) m[i] = keep(m[i], other[i], upper);
+#pragma unroll
+        for (int d = block / 4; d >= 1; d /= 2) {
+            const float side = side_of(d);
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                const uint32_t v = m[i];
+                if (d >= 16) {  // (both values of the exchange in every lane)
+                    const auto s = d == 32 ? swap32(v) : swap16(v);
+                    m[i] = keep(s[0], s[1], side);
+                } else {
+                    constexpr int ROR8 = 0x128;
+                    const uint32_t o = d == 8 ? dpp_move<ROR8>(v) : d == 4 ? dpp_move<DPP_QUAD_REVERSE>(dpp_move<DPP_HALF_MIRROR>(v))
+                                     : d == 2 ? dpp_move<DPP_XOR2>(v) : dpp_move<DPP_XOR1>(v);
+                    m[i] = keep(v, o, side);
+                }
+            }
+        }
+#pragma unroll
+        for (int d = NE / 2; d >= 1; d /= 2)
+#pragma unroll
+            for (int i = 0; i < NE; ++i)
+                if ((i & d) == 0) {
+                    const uint32_t lo = m[i], hi = m[i + d];
+                    m[i] = lo < hi ? lo : hi;
+                    m[i + d] = lo < hi ? hi : lo;
+                }
+    }
+}
+
+// the largest of the lanes' values, in every lane
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+    const auto larger = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+    v = larger(v, dpp_move<DPP_XOR1>(v));
+    v = larger(v, dpp_move<DPP_XOR2>(v));
+    v = larger(v, dpp_move<DPP_HALF_MIRROR>(v));
+    v = larger(v, dpp_move<DPP_MIRROR>(v));
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = larger(a[0], a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return larger(b[0], b[1]);
+}
+
+// Sum of the values of the lanes before this one.
+__device__ __forceinline__ double sum_before(double v) {
+    using std::integral_constant;
+    constexpr int SHR = 0x110;  // from the lane n places down in the row of 16, zero where there is none
+    const auto from = [](double x, auto N) {
+        constexpr int c = SHR + decltype(N)::value;
+        return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), c, 0xF, 0xF, true),
+                                __builtin_amdgcn_update_dpp(0, __double2loint(x), c, 0xF, 0xF, true));
+    };
+    v += from(v, integral_constant<int, 1>{});
+    v += from(v, integral_constant<int, 2>{});
+    v += from(v, integral_constant<int, 4>{});
+    v += from(v, integral_constant<int, 8>{});
+    const auto at = [&](int l) {
+        return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+    };
+    const double r0 = at(15), r1 = r0 + at(31), r2 = r1 + at(47);
+    const int row = (threadIdx.x & 63) >> 4;
+    return from(v, integral_constant<int, 1>{}) + (row == 0 ? 0.0 : row == 1 ? r0 : row == 2 ? r1 : r2);
+}
+
 template <int Q, int MW>
 struct AltRegShared {
     static constexpr int LEVELS = 1 << Q, PAIRS = Q * (Q - 1) / 2, SUMS = Q + (PAIRS + 2) / 3;
     double part[2][MW][SUMS];                 // waves' totals of a round, rounds in turn
     double level[MW][LEVELS], raw[MW][LEVELS];  // every wave sorts for itself
     uint32_t changed[2][MW];
-    float extreme[MW][2];                     // smallest non-zero and largest |w|
+    uint32_t extreme[MW][2];                  // `low` and `high` of the waves
     uint8_t pattern[MW][LEVELS];
 };
 
-// QL: quads of elements per lane; MW: waves at most.
-template <int Q, int QL, int MW>
+// QL: quads of elements per lane; MW: waves at most; RANKED: rounds from the sorted elements (vectors of one wave).
+template <int Q, int QL, int MW, bool RANKED>
 __global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* __restrict__ W, int64_t V, int n, int iters,
                                                                   float* __restrict__ alpha, uint32_t* __restrict__ packed,
                                                                   int8_t* __restrict__ planes, int* __restrict__ status_word) {
     using Shared = AltRegShared<Q, MW>;
     constexpr int PAIRS = Shared::PAIRS, LEVELS = Shared::LEVELS, HALF = LEVELS / 2, SUMS = Shared::SUMS;
     constexpr int NV = SUMS <= 1 ? 1 : SUMS <= 2 ? 2 : SUMS <= 4 ? 4 : 8;
+    constexpr int NE = 4 * QL, TH = HALF > 1 ? HALF - 1 : 1;
+    static_assert(!RANKED || (Q > 1 && MW == 1), "one wave");
     extern __shared__ __attribute__((aligned(16))) unsigned char alt_smem[];
     Shared& sh = *reinterpret_cast<Shared*>(alt_smem);
     uint32_t* code4 = reinterpret_cast<uint32_t*>(alt_smem + (sizeof(Shared) + 15) / 16 * 16);  // [n / 4], for the output
@@ -372,62 +501,62 @@ __global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* _
         x[u][3] = f.w + 0.f;
     }
 
-    // ---- greedy start: plane i takes the sign of the residual w - sum_{j<i} alpha_j b_j (each element's residual
-    // is rebuilt from its pattern so far, by the same chain of fp64 subtractions), alpha_i = fp32(mean |residual|).
-    double a[Q];
-#pragma unroll
-    for (int i = 0; i < Q; ++i) a[i] = 0.0;
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        double s = 0.0;
-#pragma unroll
-        for (int u = 0; u < QL; ++u) {
-            uint32_t c = code[u];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                double r = (double)x[u][e];
-#pragma unroll
-                for (int j = 0; j < i; ++j) r = ((c >> (8 * e + j)) & 1u) ? r - a[j] : r + a[j];
-                s += mask[u] ? fabs(r) : 0.0;
-                c |= (r >= 0.0 ? 1u : 0u) << (8 * e + i);
-            }
-            code[u] = c & mask[u];
-        }
-        s = wave_sum(s);
-        if (MW > 1) {
-            if (lane == 0) sh.part[i & 1][wave][0] = s;
-            __syncthreads();
-            s = 0.0;
-            for (int u = 0; u < waves; ++u) s += sh.part[i & 1][u][0];
-        }
-        if (i == 0 && tid == 0 && status_word && !(fabs(s) <= 1.79769313486231570e308)) atomicAdd(status_word, 1);
-        a[i] = (double)(float)(s / (double)n);
-    }
-    float smallest = 3.402823466e38f, largest = 0.f;
+    const auto of_lane = [](double v, int l) {
+        return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+    };
+
+    // Smallest non-zero and largest |w| as bits, which order like the numbers (0 - 1 and so zeros come last).
+    uint32_t low = 0u, high = 0u;
 #pragma unroll
     for (int u = 0; u < QL; ++u)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const float m = fabsf(x[u][e]);
-            smallest = m > 0.f ? fminf(smallest, m) : smallest;
-            largest = fmaxf(largest, m);
+            const uint32_t m = __float_as_uint(x[u][e]) & 0x7FFFFFFFu;
+            low = ~m + 1u > low ? ~m + 1u : low;
+            high = m > high ? m : high;
         }
+    low = wave_max(low);
+    high = wave_max(high);
+    // Sorted |w| of the wave (beyond the vector above every threshold), at lane * (NE + 1) + i, and the sums of the first of them, that of
+    // the first NE l + i at 65 i + l: all that a round needs of the elements is how many lie below each threshold, and their sum.
+    double* const prefix = reinterpret_cast<double*>(alt_smem + (sizeof(Shared) + 15) / 16 * 16 + (n + 15) / 16 * 16);
+    uint32_t* const sorted = reinterpret_cast<uint32_t*>(prefix + 65 * NE);
+    uint32_t lane_first = 0u;  // the smallest of the lane's NE
+    double absolute = 0.0;
+    if constexpr (RANKED) {
+        uint32_t m[NE];
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        smallest = fminf(smallest, __shfl_xor(smallest, d));
-        largest = fmaxf(largest, __shfl_xor(largest, d));
+        for (int u = 0; u < QL; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) m[4 * u + e] = mask[u] ? __float_as_uint(x[u][e]) & 0x7FFFFFFFu : 0x7F800000u;
+        sort_wave(m);
+        lane_first = m[0];
+        double upto[NE + 1];
+        upto[0] = 0.0;
+#pragma unroll
+        for (int i = 0; i < NE; ++i) upto[i + 1] = upto[i] + (m[i] < 0x7F800000u ? (double)__uint_as_float(m[i]) : 0.0);
+        const double before = sum_before(upto[NE]);
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            sorted[lane * (NE + 1) + i] = m[i];
+            prefix[65 * i + lane] = before + upto[i];
+        }
+        if (lane == 63) prefix[64] = before + upto[NE];
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        absolute = of_lane(before + upto[NE], 63);
     }
     if (MW > 1) {
         if (lane == 0) {
-            sh.extreme[wave][0] = smallest;
-            sh.extreme[wave][1] = largest;
+            sh.extreme[wave][0] = low;
+            sh.extreme[wave][1] = high;
         }
         __syncthreads();
         for (int u = 0; u < waves; ++u) {
-            smallest = fminf(smallest, sh.extreme[u][0]);
-            largest = fmaxf(largest, sh.extreme[u][1]);
+            low = sh.extreme[u][0] > low ? sh.extreme[u][0] : low;
+            high = sh.extreme[u][1] > high ? sh.extreme[u][1] : high;
         }
     }
+    const float smallest = low ? __uint_as_float(0u - low) : 3.402823466e38f, largest = __uint_as_float(high);
 
     // B^T w and, three counts of at most 16384 to a double, the disagreeing signs of pairs of planes
     double sum[NV];
@@ -462,10 +591,192 @@ __global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* _
         for (int p = 0; p < PAIRS; ++p) sum[Q + p / 3] += (double)dis[p] * (double)(1ll << (16 * (p % 3)));
         wave_sums(sum);
     };
-    if (iters > 0) form_sums();
+    // the pattern of every element from the thresholds of |w| and the patterns between them; non-zero where one changes
+    auto assign = [&](const float (&thr)[HALF], uint64_t lut) {
+        const uint32_t lo = (uint32_t)lut, hi = (uint32_t)(lut >> 32);
+        uint32_t diff = 0u;
+#pragma unroll
+        for (int u = 0; u < QL; ++u) {
+            uint32_t sel = 0u, neg = 0u;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float m = fabsf(x[u][e]);
+                uint32_t idx = 0u;  // thresholds above |w|
+                if constexpr (HALF == 8) {
+                    const bool far = m < thr[3];
+                    const float second = far ? thr[5] : thr[1];
+                    const bool b = m < second;
+                    const float third = far ? (b ? thr[6] : thr[4]) : (b ? thr[2] : thr[0]);
+                    idx = (far ? 4u : 0u) + (b ? 2u : 0u) + (m < third ? 1u : 0u);
+                } else {
+#pragma unroll
+                    for (int k = 0; k + 1 < HALF; ++k) idx += m < thr[k] ? 1u : 0u;
+                }
+                sel |= idx << (8 * e);
+                neg |= (uint32_t)((int)__float_as_uint(x[u][e]) >> 31) & ((uint32_t)(LEVELS - 1) << (8 * e));
+            }
+            const uint32_t c4 = (__builtin_amdgcn_perm(hi, lo, sel) ^ neg) & mask[u];
+            diff |= c4 ^ code[u];
+            code[u] = c4;
+        }
+        return diff;
+    };
+    // Of the last round, while `known`: its thresholds, patterns (outermost first) and the elements and sums below the thresholds; of
+    // the patterns, the planes of lane k's level and of the one below it as sign flips, and lane p's part in the sums: the p-th
+    // of B^T w, then of the elements of B^T B off its diagonal, as combination of the sums (counts) below the thresholds.  `owed`:
+    // the codes are still to be assigned from thresholds and patterns.
+    float thr[HALF];
+    uint64_t lut = 0u;
+    uint32_t flip_up[Q], flip_down[Q];
+    double part[HALF];
+    int under[TH];
+    double below[TH];
+    bool known = false, owed = false, from_below = false;
+#pragma unroll
+    for (int k = 0; k < TH; ++k) {
+        under[k] = 0;
+        below[k] = 0.0;
+    }
+    const auto flipped = [](double v, uint32_t flip) { return __hiloint2double(__double2hiint(v) ^ (int)flip, __double2loint(v)); };
+    uint32_t planes_of_lane = 1u;  // one plane, or two
+    {
+        int p = 0;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            planes_of_lane = lane == i ? 1u << i : planes_of_lane;
+#pragma unroll
+            for (int j = 0; j < i; ++j, ++p) planes_of_lane = lane == Q + p ? (1u << i) | (1u << j) : planes_of_lane;
+        }
+    }
+    const uint32_t pair = lane >= Q ? 1u : 0u;
+
+    const auto describe = [&] {  // flips and parts of the patterns
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {  // (lanes beyond the last level repeat it)
+            const int k = lane < HALF - 1 ? lane : HALF - 1;
+            const uint32_t mirrored = k == HALF - 1 ? 1u : 0u, next = (uint32_t)(lut >> (8 * (k + 1 - (int)mirrored)));
+            flip_up[i] = ~(uint32_t)(lut >> (8 * k + i)) << 31;
+            flip_down[i] = ((next >> i) ^ mirrored ^ 1u) << 31;
+        }
+        double sign = 0.0;
+#pragma unroll
+        for (int c = 0; c < HALF; ++c) {  // a plane counts with its sign, a pair with the product of its signs
+            const double next = ((uint32_t)__popc((uint32_t)(lut >> (8 * c)) & planes_of_lane) & 1u) != pair ? 1.0 : -1.0;
+            part[c] = next - sign;
+            sign = next;
+        }
+    };
+    // Of the sorted elements: the last lane whose smallest lies below threshold k, its elements, and the sums up to them; then the number
+    // and the sum of all elements below the threshold.
+    int first[TH];
+    uint32_t near[TH];
+    double sums[TH];
+    const auto look = [&](int k) {
+        const int lanes = __popcll(__ballot(lane_first < __float_as_uint(thr[k])));
+        first[k] = lanes > 1 ? lanes - 1 : 0;
+        near[k] = sorted[first[k] * (NE + 1) + (lane & (NE - 1))];
+        sums[k] = prefix[first[k] + (lane < NE ? 65 * lane : 1)];
+    };
+    const auto count = [&](int k) {
+        const int in = __popcll(__ballot(near[k] < __float_as_uint(thr[k])) & ((1ull << NE) - 1ull));
+        below[k] = of_lane(sums[k], in);
+        return first[k] * NE + in;
+    };
+    // ---- greedy start, from the sorted elements: the sign of plane i changes, in every cell of the planes before it, at the cell's level
+    // (the sum of their scales with its signs), and alpha_i is the mean distance from there.  Not where an element lies as close
+    // to that place as the rounding of the residuals, or all of them do nearly.
+    double a[Q];
+    bool started = false;
+    if constexpr (RANKED) {
+        if (high < 0x7F800000u) {
+            a[0] = (double)(float)(absolute / (double)n);
+            double level[HALF];  // of the cells so far, uppermost first
+            level[0] = a[0];
+            bool close = false;
+#pragma unroll
+            for (int i = 1; i < Q; ++i) {
+                constexpr int none = -1;
+                const int step = 1 << (Q - 1 - i), cells = 1 << (i - 1);
+                double total = 0.0;
+#pragma unroll
+                for (int c = 0; c < cells; ++c) {
+                    const int k = (2 * c + 1) * step - 1, above = c > 0 ? k - step : none, beneath = c + 1 < cells ? k + step : none;
+                    const float f = (float)level[c];
+                    float t = (double)f < level[c] ? __uint_as_float(__float_as_uint(f) + 1u) : f;
+                    t = level[c] > 0.0 ? t : 0.f;
+                    if (above != none) t = fminf(t, thr[above]);
+                    if (beneath != none) t = fmaxf(t, thr[beneath]);
+                    thr[k] = t;
+                    look(k);
+                }
+#pragma unroll
+                for (int c = 0; c < cells; ++c) {
+                    const int k = (2 * c + 1) * step - 1, above = c > 0 ? k - step : none, beneath = c + 1 < cells ? k + step : none;
+                    under[k] = count(k);
+                    const double m = level[c], eps = 1e-14 * a[0];
+                    close = close || fabs((double)__uint_as_float(near[k]) - m) <= eps || fabs((double)__uint_as_float(lane_first) - m) <= eps;
+                    const int n_above = (above == none ? n : under[above]) - under[k], n_beneath = under[k] - (beneath == none ? 0 : under[beneath]);
+                    const double s_above = (above == none ? absolute : below[above]) - below[k], s_beneath = below[k] - (beneath == none ? 0.0 : below[beneath]);
+                    total += (s_above - m * (double)n_above) + (m * (double)n_beneath - s_beneath);
+                }
+                close = close || !(total >= 1e-3 * absolute);  // (their differences keep 2^-40 of it)
+                a[i] = (double)(float)(total / (double)n);
+#pragma unroll
+                for (int c = cells - 1; c >= 0; --c) {
+                    const double m = level[c];
+                    level[2 * c] = m + a[i];
+                    level[2 * c + 1] = m - a[i];
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < HALF; ++c) {
+                uint64_t pattern = 1u;
+#pragma unroll
+                for (int i = 1; i < Q; ++i) pattern |= (uint64_t)(((c >> (Q - 1 - i)) & 1) ^ 1) << i;
+                lut |= pattern << (8 * c);
+            }
+            started = __all(!close);
+            known = owed = from_below = started;
+            describe();
+        }
+    }
+    // ---- greedy start, element by element: plane i takes the sign of the residual w - sum_{j<i} alpha_j b_j (each element's residual
+    // is rebuilt from its pattern so far, by the same chain of fp64 subtractions), alpha_i = fp32(mean |residual|).
+    if (!started) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) a[i] = 0.0;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            double s = 0.0;
+#pragma unroll
+            for (int u = 0; u < QL; ++u) {
+                uint32_t c = code[u];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    double r = (double)x[u][e];
+#pragma unroll
+                    for (int j = 0; j < i; ++j) r = ((c >> (8 * e + j)) & 1u) ? r - a[j] : r + a[j];
+                    s += mask[u] ? fabs(r) : 0.0;
+                    c |= (r >= 0.0 ? 1u : 0u) << (8 * e + i);
+                }
+                code[u] = c & mask[u];
+            }
+            s = wave_sum(s);
+            if (MW > 1) {
+                if (lane == 0) sh.part[i & 1][wave][0] = s;
+                __syncthreads();
+                s = 0.0;
+                for (int u = 0; u < waves; ++u) s += sh.part[i & 1][u][0];
+            }
+            if (i == 0 && tid == 0 && status_word && !(fabs(s) <= 1.79769313486231570e308)) atomicAdd(status_word, 1);
+            a[i] = (double)(float)(s / (double)n);
+        }
+        if (iters > 0) form_sums();
+    }
 
     for (int it = 0; it < iters; ++it) {
         bool changed_elsewhere = false;
+
         if (MW > 1) {  // totals over the waves, in wave order; every wave leaves the loop with the others
             const int turn = it & 1;
             if (lane == 0) {
@@ -482,36 +793,48 @@ __global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* _
             }
             if (it > 0 && !changed_elsewhere) break;
         }
+        // B^T w and the elements of B^T B off its diagonal
+        double rhs[Q], gram[PAIRS + 1];
+        if (RANKED && from_below) {
+            double v = part[0] * (pair ? (double)n : absolute);
+#pragma unroll
+            for (int k = 0; k + 1 < HALF; ++k) v = __builtin_fma(part[k + 1], pair ? (double)under[k] : below[k], v);
+#pragma unroll
+            for (int i = 0; i < Q; ++i) rhs[i] = of_lane(v, i);
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p) gram[p] = of_lane(v, Q + p);
+        } else {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) rhs[i] = sum[i];
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p) {
+                const uint64_t counts = (uint64_t)__double_as_longlong(sum[Q + p / 3] + 4503599627370496.0);  // 2^52: an integer in the mantissa
+                gram[p] = (double)(n - 2 * (int)((counts >> (16 * (p % 3))) & 0xFFFFu));
+            }
+        }
         // ---- (1) Eq. ap4: L D L^T of the Gram matrix B^T B (diagonal = n), all lanes on the same numbers
         double L[Q][Q], M[Q][Q], inv[Q], z[Q];  // G = L D L^T with unit diagonal in L, M = L D, inv = 1 / D
         bool singular = false;
 #pragma unroll
         for (int j = 0; j < Q; ++j) {
-            if (!singular) {
-                double d = (double)n;
+            double d = (double)n;
 #pragma unroll
-                for (int p = 0; p < j; ++p) d -= M[j][p] * L[j][p];
-                if (!(d > 1e-9 * (double)n)) {
-                    singular = true;
-                } else {
-                    inv[j] = 1.0 / d;
+            for (int p = 0; p < j; ++p) d -= M[j][p] * L[j][p];
+            singular |= !(d > 1e-9 * (double)n);
+            inv[j] = 1.0 / d;
 #pragma unroll
-                    for (int i = j + 1; i < Q; ++i) {
-                        const int pr = i * (i - 1) / 2 + j;
-                        const uint64_t counts = (uint64_t)__double_as_longlong(sum[Q + pr / 3] + 4503599627370496.0);  // 2^52: an integer in the mantissa
-                        double s = (double)(n - 2 * (int)((counts >> (16 * (pr % 3))) & 0xFFFFu));
+            for (int i = j + 1; i < Q; ++i) {
+                double s = gram[i * (i - 1) / 2 + j];
 #pragma unroll
-                        for (int p = 0; p < j; ++p) s -= M[i][p] * L[j][p];
-                        M[i][j] = s;
-                        L[i][j] = s * inv[j];
-                    }
-                }
+                for (int p = 0; p < j; ++p) s -= M[i][p] * L[j][p];
+                M[i][j] = s;
+                L[i][j] = s * inv[j];
             }
         }
-        if (singular) break;
+        if (__builtin_expect(singular, 0)) break;
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
-            z[i] = sum[i];
+            z[i] = rhs[i];
 #pragma unroll
             for (int p = 0; p < i; ++p) z[i] -= L[i][p] * z[p];
         }
@@ -526,82 +849,100 @@ __global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* _
         double size = 0.0;
 #pragma unroll
         for (int i = 0; i < Q; ++i) size += fabs(a[i]);
-        double own = 0.0;
-#pragma unroll
-        for (int i = 0; i < Q; ++i) own += (i == Q - 1 || ((lane >> i) & 1)) ? a[i] : -a[i];
-        const uint32_t own_pattern = ((uint32_t)(lane & (HALF - 1)) | (uint32_t)HALF) ^ (own < 0.0 ? (uint32_t)(LEVELS - 1) : 0u);
-        own = fabs(own);
-        int rank = 0;
-        double lv[HALF];
-#pragma unroll
-        for (int c = 0; c < HALF; ++c) {
-            lv[c] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(own), c), __builtin_amdgcn_readlane(__double2loint(own), c));
-            rank += lv[c] > own ? 1 : 0;
-        }
-        // sorted downwards: level k is the one of rank k (all different, or `clear` fails below)
+        bool clear = (size < 1e30) & (size > 1e-25) & ((double)largest <= 1048576.0 * size) & ((double)smallest >= 9.3e-10 * size);
         double up = 0.0, down = 0.0;  // of lane k: level k and level k + 1, the one below the last being its mirror
-        uint64_t lut = 0u;            // patterns of the positive levels, outermost first
-        float thr[HALF];
-        bool clear = size < 1e30 && size > 1e-25 && (double)largest <= 1048576.0 * size && (double)smallest >= 9.3e-10 * size;
-        uint32_t found = 0u;
+        float mine = 0.f;             // lane k < HALF - 1: the first float that is nearer to level k than to level k + 1
+        uint64_t patterns = lut;      // of the positive levels, outermost first
+        // As long as the last round's order still is one, nothing has to be sorted; and where no float lies as close to the middle of two
+        // levels as the rounding of the distances (2^-52 of them), the next one above it is the threshold.
+        bool ordered = false;
+        if (RANKED && known) {
 #pragma unroll
-        for (int c = 0; c < HALF; ++c) {
-            const int r = __builtin_amdgcn_readlane(rank, c);
-            const uint32_t pat = (uint32_t)__builtin_amdgcn_readlane((int)own_pattern, c);
-            lut |= (uint64_t)pat << (8 * r);
-            found |= 1u << r;
-            up = lane == r ? lv[c] : up;
-            down = lane + 1 == r ? lv[c] : down;
-        }
-        clear = clear && found == (1u << HALF) - 1u;
-        if (lane == HALF - 1) down = -up;
-        if (lane < HALF) clear = clear && up - down >= 1e-9 * size;
-        float mine = 0.f;
-        if (HALF > 1) {  // lane k < HALF - 1: the first float that is nearer to level k than to level k + 1
+            for (int i = 0; i < Q; ++i) {
+                up += flipped(a[i], flip_up[i]);
+                down += flipped(a[i], flip_down[i]);
+            }
             const double mid = 0.5 * (up + down);
             const float f = (float)mid;
-            const float t[3] = {__uint_as_float(__float_as_uint(f) - 1u), f, __uint_as_float(__float_as_uint(f) + 1u)};
-            bool outer[3], tie = false;
+            const double past = (double)f - mid;
+            mine = past > 0.0 ? f : __uint_as_float(__float_as_uint(f) + 1u);
+            const bool sure = (lane + 1 >= HALF) | ((mid >= 9.6e-7 * size) & (fabs(past) > 1e-14 * size));
+            ordered = __all(clear & (up - down >= 1e-9 * size) & sure);
+        }
+        if (__builtin_expect(!ordered, 0)) {
+            double own = 0.0;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const double du = fabs((double)t[c] - up), dd = fabs((double)t[c] - down);
-                outer[c] = du < dd;
-                tie = tie || du == dd;  // there the two signs of w part
+            for (int i = 0; i < Q; ++i) own += (i == Q - 1 || ((lane >> i) & 1)) ? a[i] : -a[i];
+            const uint32_t own_pattern = ((uint32_t)(lane & (HALF - 1)) | (uint32_t)HALF) ^ (own < 0.0 ? (uint32_t)(LEVELS - 1) : 0u);
+            own = fabs(own);
+            int rank = 0;
+            double lv[HALF];
+#pragma unroll
+            for (int c = 0; c < HALF; ++c) {
+                lv[c] = of_lane(own, c);
+                rank += lv[c] > own ? 1 : 0;
             }
-            if (lane + 1 < HALF) clear = clear && mid >= 9.6e-7 * size && !tie && !outer[0] && outer[2];
-            mine = outer[1] ? t[1] : t[2];
+            // sorted downwards: level k is the one of rank k (all different, or `clear` fails below)
+            up = down = 0.0;
+            patterns = 0u;
+            uint32_t found = 0u;
+#pragma unroll
+            for (int c = 0; c < HALF; ++c) {
+                const int r = __builtin_amdgcn_readlane(rank, c);
+                const uint32_t pat = (uint32_t)__builtin_amdgcn_readlane((int)own_pattern, c);
+                patterns |= (uint64_t)pat << (8 * r);
+                found |= 1u << r;
+                up = lane == r ? lv[c] : up;
+                down = lane + 1 == r ? lv[c] : down;
+            }
+            clear = clear && found == (1u << HALF) - 1u;
+            if (lane == HALF - 1) down = -up;
+            if (lane < HALF) clear = clear && up - down >= 1e-9 * size;
+            if (HALF > 1) {
+                const double mid = 0.5 * (up + down);
+                const float f = (float)mid;
+                const float t[3] = {__uint_as_float(__float_as_uint(f) - 1u), f, __uint_as_float(__float_as_uint(f) + 1u)};
+                bool outer[3], tie = false;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const double du = fabs((double)t[c] - up), dd = fabs((double)t[c] - down);
+                    outer[c] = du < dd;
+                    tie = tie || du == dd;  // there the two signs of w part
+                }
+                if (lane + 1 < HALF) clear = clear && mid >= 9.6e-7 * size && !tie && !outer[0] && outer[2];
+                mine = outer[1] ? t[1] : t[2];
+            }
+            clear = __all(clear);
         }
         // ---- (2) the nearest level for every element
         uint32_t diff = 0u;
-        if (__all(clear)) {
+        if (__builtin_expect(ordered || clear, 1)) {
+            // While the patterns stay in their order an element changes where a count does; its pattern can wait until the end or
+            // until a round that needs it.
+            const bool same = ordered || (RANKED && known && patterns == lut);
+            if (RANKED && __builtin_expect(!same && owed, 0)) assign(thr, lut);
 #pragma unroll
             for (int k = 0; k + 1 < HALF; ++k) thr[k] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(mine), k));
-            const uint32_t lo = (uint32_t)lut, hi = (uint32_t)(lut >> 32);
-#pragma unroll
-            for (int u = 0; u < QL; ++u) {
-                uint32_t sel = 0u, neg = 0u;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float m = fabsf(x[u][e]);
-                    uint32_t idx = 0u;  // thresholds above |w|
-                    if constexpr (HALF == 8) {
-                        const bool far = m < thr[3];
-                        const float second = far ? thr[5] : thr[1];
-                        const bool b = m < second;
-                        const float third = far ? (b ? thr[6] : thr[4]) : (b ? thr[2] : thr[0]);
-                        idx = (far ? 4u : 0u) + (b ? 2u : 0u) + (m < third ? 1u : 0u);
-                    } else {
-#pragma unroll
-                        for (int k = 0; k + 1 < HALF; ++k) idx += m < thr[k] ? 1u : 0u;
-                    }
-                    sel |= idx << (8 * e);
-                    neg |= (uint32_t)((int)__float_as_uint(x[u][e]) >> 31) & ((uint32_t)(LEVELS - 1) << (8 * e));
-                }
-                const uint32_t c4 = (__builtin_amdgcn_perm(hi, lo, sel) ^ neg) & mask[u];
-                diff |= c4 ^ code[u];
-                code[u] = c4;
+            if (__builtin_expect(!same, 0)) {
+                diff = assign(thr, patterns);
+                lut = patterns;
+                if (RANKED) describe();
             }
+            if constexpr (RANKED) {
+#pragma unroll
+                for (int k = 0; k < TH; ++k) look(k);
+#pragma unroll
+                for (int k = 0; k < TH; ++k) {
+                    const int elements = count(k);
+                    if (same) diff |= (uint32_t)(elements ^ under[k]);
+                    under[k] = elements;
+                }
+            }
+            owed = same;
+            known = RANKED;
         } else {
+            if (RANKED && owed) assign(thr, lut);
+            known = owed = false;
             // distances to all levels, sorted by (level, pattern) downwards: the first of the smallest ones is the one the tie
             // rules ask for.  The slots are filled in pattern order first: with non-finite levels the ranks need not be a
             // permutation.  (One wave's LDS instructions execute in order.)
@@ -661,8 +1002,10 @@ __global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* _
         const bool changed = __any(diff != 0u);
         if (MW == 1 && !changed) break;
         if (MW > 1 && lane == 0) sh.changed[it & 1][wave] = changed ? 1u : 0u;
-        form_sums();
+        from_below = known;
+        if (!from_below) form_sums();
     }
+    if (RANKED && owed) assign(thr, lut);
 #pragma unroll
     for (int u = 0; u < QL; ++u)
         if (mask[u]) code4[tid + u * 64 * waves] = code[u];
@@ -706,17 +1049,27 @@ static hipError_t launch_q(const float* W, int64_t V, int n, int iters, float* a
     return hipGetLastError();
 }
 
+template <int Q, int QL, int MW, bool RANKED>
+static hipError_t launch_reg_form(const float* W, int64_t V, int n, int iters, float* alpha, uint32_t* packed, int8_t* planes,
+                                  int* status_word, hipStream_t st) {
+    const size_t sorted = RANKED ? 65 * 4 * QL * 8 + 64 * (4 * QL + 1) * 4 : 0;
+    const size_t lds = (sizeof(AltRegShared<Q, MW>) + 15) / 16 * 16 + (size_t)(n + 15) / 16 * 16 + sorted;
+    static LdsLimit limit;
+    hipError_t e = limit.ensure((const void*)alternating_reg_kernel<Q, QL, MW, RANKED>, lds);
+    if (e != hipSuccess) return e;
+    const int waves = (n / 4 + 64 * QL - 1) / (64 * QL);
+    BCQ_LAUNCH((alternating_reg_kernel<Q, QL, MW, RANKED>), dim3((unsigned)V), dim3(64 * waves), lds, st, W, V, n, iters, alpha, packed,
+                       planes, status_word);
+    return hipGetLastError();
+}
+
 template <int Q, int QL, int MW>
 static hipError_t launch_reg(const float* W, int64_t V, int n, int iters, float* alpha, uint32_t* packed, int8_t* planes,
                              int* status_word, hipStream_t st) {
-    const size_t lds = (sizeof(AltRegShared<Q, MW>) + 15) / 16 * 16 + (size_t)n;
-    static LdsLimit limit;
-    hipError_t e = limit.ensure((const void*)alternating_reg_kernel<Q, QL, MW>, lds);
-    if (e != hipSuccess) return e;
-    const int waves = (n / 4 + 64 * QL - 1) / (64 * QL);
-    BCQ_LAUNCH((alternating_reg_kernel<Q, QL, MW>), dim3((unsigned)V), dim3(64 * waves), lds, st, W, V, n, iters, alpha, packed,
-                       planes, status_word);
-    return hipGetLastError();
+    if constexpr (Q > 1 && MW == 1) {
+        if (iters >= ALT_SORT_ROUNDS) return launch_reg_form<Q, QL, MW, true>(W, V, n, iters, alpha, packed, planes, status_word, st);
+    }
+    return launch_reg_form<Q, QL, MW, false>(W, V, n, iters, alpha, packed, planes, status_word, st);
 }
 
 // As many elements per lane as one wave's registers hold, then more waves.  q = 3, 15 rounds, us, one wave against one to four

@@ -176,3 +176,22 @@ def test_nonfinite_vectors_of_several_waves(bcq, oracle, K):
         keep = [0, 2, 4]
         assert torch.equal(alpha.reshape(q, 5)[:, keep], alpha_c.reshape(q, 5)[:, keep])
         assert torch.equal(packed.reshape(q, 5, -1)[:, keep], packed_c.reshape(q, 5, -1)[:, keep])
+
+
+@pytest.mark.parametrize("kind", ["normal", "heavy", "grid", "two"])
+@pytest.mark.parametrize("N,K", [(9, 32), (9, 96), (6, 256), (6, 288), (5, 480), (5, 544), (5, 992), (5, 1024)])
+def test_rounds_from_the_sorted_elements(bcq, oracle, N, K, kind):
+    """Vectors of one wave, with idle lanes and none, one round below and at the line from which their elements are sorted: normal
+    and heavy-tailed weights (levels that change their order, counts that stay), weights on a coarse grid (ties with the greedy levels
+    and equal elements on both sides of a threshold) and two magnitudes (the later planes have next to nothing left).  Same bar."""
+    rng = np.random.default_rng(K + N)
+    for q in (2, 3, 4):
+        W = rng.standard_normal((N, K)).astype(np.float32)
+        if kind == "heavy":
+            W = np.sign(W) * (np.abs(W) ** 3 + 0.01)  # (elements next to zero are as near to +l as to -l: no robust vectors)
+        if kind == "grid":
+            W = np.round(W * 8 + 0.25) / 8 + np.float32(1e-3) * rng.standard_normal((N, 1)).astype(np.float32)
+        if kind == "two":
+            W = np.where(np.abs(W) > 0.6, 0.7, 0.3) * np.sign(W) + np.float32(1e-6) * W
+        for iters in (7, 8, 15):
+            _check(bcq, oracle, W.astype(np.float32), q, iters=iters)
