@@ -326,10 +326,9 @@ static hipError_t launch_stream(const uint32_t* planes, const bf16_t* act, const
     unsigned char* xq = reinterpret_cast<unsigned char*>(workspace);
     unsigned char* sq = xq + (size_t)sets * p.xq_bytes;
     {
-        const int64_t threads = (int64_t)p.tiles * p.segs * 256;
-        const dim3 grid((unsigned)((threads + 255) / 256), (unsigned)sets);
-        BCQ_LAUNCH((quant_act_kernel<MODE>), grid, dim3(256), 0, st, act, alpha, T, cw * 32, p.segs, p.halves,
-                           p.tiles, xq, sq, p.xq_bytes, p.sq_bytes, G);
+        const dim3 grid((unsigned)(p.tiles * p.segs), (unsigned)sets);
+        BCQ_LAUNCH((quant_act_kernel<MODE>), grid, dim3(p.halves == 1 ? 128 : 256), 0, st, act, alpha, T, cw * 32, p.segs, p.halves,
+                           xq, sq, p.xq_bytes, p.sq_bytes, G);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

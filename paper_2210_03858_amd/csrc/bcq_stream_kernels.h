@@ -71,19 +71,18 @@ __device__ __forceinline__ uint32_t q_pack_bf16x2(float lo, float hi) {
 // instruction j (xb: [half][2 KiB]) and the scales of the segment (sb: [half][256 B]); global memory or LDS.
 __device__ __forceinline__ void recode_unit(const float (&v)[32], int tl, int G, int j, bool one_half, unsigned char* xb,
                                             unsigned char* sb) {
-    float amax = 0.f;
-    bool finite = true;
+    uint32_t amax = 0u;  // magnitudes order like their bits
 #pragma unroll
     for (int e = 0; e < 32; ++e) {
-        amax = fmaxf(amax, fabsf(v[e]));
-        finite = finite && (fabsf(v[e]) <= 3.0e38f);  // false for Inf and NaN
+        const uint32_t u = __float_as_uint(v[e]) & 0x7FFFFFFFu;
+        amax = u > amax ? u : amax;
     }
+    const bool finite = amax <= 0x7F61B1E6u;  // 3.0e38: false for Inf and NaN
     // smallest power of two 2^E with amax / 2^E <= 448 (largest e4m3 value = 1.75 * 2^8); scale byte = E + 127
     int sb1 = 127;
-    if (amax > 0.f && finite) {
-        const uint32_t u = __float_as_uint(amax);
-        const int e = (int)(u >> 23) - 127;
-        const int E = ((u & 0x7FFFFFu) <= 0x600000u) ? e - 8 : e - 7;
+    if (amax > 0u && finite) {
+        const int e = (int)(amax >> 23) - 127;
+        const int E = ((amax & 0x7FFFFFu) <= 0x600000u) ? e - 8 : e - 7;
         sb1 = E + 127;
         sb1 = sb1 < 0 ? 0 : sb1;
     }
@@ -129,9 +128,14 @@ __device__ __forceinline__ void recode_unit(const float (&v)[32], int tl, int G,
     sb[half2 * QSCL + (col2 + 16 * G) * 4 + j] = (unsigned char)sbw2;
 }
 
+// A pointer read from the plan is a generic pointer to the compiler, and loads through it become FLAT loads (which
+// also count as LDS operations and serialise with them).  All plan pointers are device-memory pointers: the kernels
+// cast them to the global address space explicitly.
+#define BCQ_GLOBAL __attribute__((address_space(1)))
+
 // 32 bf16 values -> fp32
-__device__ __forceinline__ void load_unit(const bf16_t* src, float (&v)[32]) {
-    const q_u32x4* s4 = reinterpret_cast<const q_u32x4*>(src);
+__device__ __forceinline__ void load_unit(const BCQ_GLOBAL bf16_t* src, float (&v)[32]) {
+    const BCQ_GLOBAL q_u32x4* s4 = reinterpret_cast<const BCQ_GLOBAL q_u32x4*>(src);
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
         const q_u32x4 r = s4[b];
@@ -143,42 +147,39 @@ __device__ __forceinline__ void load_unit(const bf16_t* src, float (&v)[32]) {
     }
 }
 
-// bx, by: the block indices the launch geometry of the single-layer kernel gives (a batched launch looks them up)
+// A workgroup's units: one segment of one token tile, 4 blocks x 16 tokens x 4 instructions; with one half (at most 8 tokens, the
+// columns 8 .. 15 belong to the second terms) half as many, and half the threads.
 template <int MODE>
-__device__ __forceinline__ void quant_act_body(const bf16_t* __restrict__ act, const float* __restrict__ alpha,
-                                               int64_t T, int64_t C, int64_t segs, int halves, int tiles,
+__device__ __forceinline__ void quant_act_body(const BCQ_GLOBAL bf16_t* __restrict__ act, const BCQ_GLOBAL float* __restrict__ alpha,
+                                               int64_t T, int64_t C, int64_t segs, int halves, uint32_t tile, uint32_t seg,
                                                unsigned char* __restrict__ xq, unsigned char* __restrict__ sq,
-                                               size_t xq_plane, size_t sq_plane, int NG, int seg_mul, uint32_t bx,
-                                               uint32_t by) {
-    const int64_t idx = (int64_t)bx * 256 + threadIdx.x;
-    const bool one_half_map = (halves == 1);
-    // two halves: 4 blocks x 16 tokens x 4 instructions = 256 units per (tile, segment).  One half: only tokens 0 .. 7
-    // have units; they are mapped onto the first 128 threads so that two waves work with all lanes instead of four
-    // waves with half of them.
-    if (one_half_map && (threadIdx.x & 255) >= 128) return;
+                                               size_t xq_plane, size_t sq_plane, int NG, int seg_mul, int set0, int set1) {
+    const bool one_half = (halves == 1);
+    const int tid = threadIdx.x;
     // the token index runs fastest over the lanes: the 16-byte stores of neighbouring lanes are then neighbours in the
     // operand block (column = token), 128 or 256 bytes in a row instead of one piece per lane
-    const int tl = one_half_map ? (int)(idx & 7) : (int)(idx & 15);
-    const int G = one_half_map ? (int)((idx >> 3) & 3) : (int)((idx >> 4) & 3);
-    const int j = one_half_map ? (int)((idx >> 5) & 3) : (int)((idx >> 6) & 3);
-    const int64_t seg = (idx >> 8) % segs, tile = (idx >> 8) / segs;
-    if (tile >= tiles) return;
-    const int plane = (int)by;
-    xq += (size_t)plane * xq_plane;
-    sq += (size_t)plane * sq_plane;
-    const int64_t t = tile * 16 + tl;
-    const bool one_half = (halves == 1);
-    if (one_half && tl >= 8) return;  // columns 8 .. 15 of the single half belong to the second term of tokens 0 .. 7
-    const int64_t word = seg * 16 + 4 * G + j;  // 32 columns of the contraction axis
+    const int tl = one_half ? tid & 7 : tid & 15;
+    const int G = one_half ? (tid >> 3) & 3 : (tid >> 4) & 3;
+    const int j = one_half ? (tid >> 5) & 3 : (tid >> 6) & 3;
+    const int64_t t = (int64_t)tile * 16 + tl;
+    const int64_t word = (int64_t)seg * 16 + 4 * G + j;  // 32 columns of the contraction axis
     const bool live = (t < T) && (word * 32 < C);
-    float v[32];
-    if (live) {
-        load_unit(act + t * C + word * 32, v);
-        if (MODE == STREAM_DX) {
-            const int pl_i = plane / NG, grp = plane % NG;
-            const float* a = alpha + ((int64_t)pl_i * C + word * 32) * NG + grp;  // alpha[i][n][grp], n = 32 word + e
+    // seg_mul > 1 interleaves the sets: block (segment, set) at index segment * seg_mul + set (xq_plane, sq_plane = one block)
+    unsigned char* xb = xq + ((size_t)(tile * segs + seg) * seg_mul * 4 + j) * halves * QBLK + (size_t)set0 * xq_plane;
+    unsigned char* sb = sq + (size_t)(tile * segs + seg) * seg_mul * halves * QSCL + (size_t)set0 * sq_plane;
+    float x[32];
+#pragma unroll
+    for (int e = 0; e < 32; ++e) x[e] = 0.f;
+    if (live) load_unit(act + t * C + word * 32, x);
+    for (int set = set0; set < set1; ++set, xb += xq_plane, sb += sq_plane) {
+        float v[32];
+#pragma unroll
+        for (int e = 0; e < 32; ++e) v[e] = x[e];
+        if (MODE == STREAM_DX && live) {
+            const int pl_i = set / NG, grp = set % NG;
+            const BCQ_GLOBAL float* a = alpha + ((int64_t)pl_i * C + word * 32) * NG + grp;  // alpha[i][n][grp], n = 32 word + e
             if (NG == 1) {  // row-wise scales: 32 consecutive floats, 128-byte aligned (C is a multiple of 32)
-                const q_f32x4* a4 = reinterpret_cast<const q_f32x4*>(a);
+                const BCQ_GLOBAL q_f32x4* a4 = reinterpret_cast<const BCQ_GLOBAL q_f32x4*>(a);
 #pragma unroll
                 for (int b = 0; b < 8; ++b) {
                     const q_f32x4 av = a4[b];
@@ -190,21 +191,18 @@ __device__ __forceinline__ void quant_act_body(const bf16_t* __restrict__ act, c
                 for (int e = 0; e < 32; ++e) v[e] *= a[(int64_t)e * NG];
             }
         }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 32; ++e) v[e] = 0.f;
+        recode_unit(v, tl, G, j, one_half, xb, sb);
     }
-    // seg_mul > 1 interleaves the sets: block (segment, set) at index segment * seg_mul + set (xq_plane, sq_plane = one block)
-    recode_unit(v, tl, G, j, one_half, xq + ((size_t)(tile * segs + seg) * seg_mul * 4 + j) * halves * QBLK,
-                sq + (size_t)(tile * segs + seg) * seg_mul * halves * QSCL);
 }
 
 template <int MODE>
 __global__ __launch_bounds__(256) void quant_act_kernel(const bf16_t* __restrict__ act, const float* __restrict__ alpha,
-                                                        int64_t T, int64_t C, int64_t segs, int halves, int tiles,
+                                                        int64_t T, int64_t C, int64_t segs, int halves,
                                                         unsigned char* __restrict__ xq, unsigned char* __restrict__ sq,
                                                         size_t xq_plane, size_t sq_plane, int NG) {
-    quant_act_body<MODE>(act, alpha, T, C, segs, halves, tiles, xq, sq, xq_plane, sq_plane, NG, 1, blockIdx.x, blockIdx.y);
+    const uint32_t tile = blockIdx.x / (uint32_t)segs;
+    quant_act_body<MODE>((const BCQ_GLOBAL bf16_t*)act, (const BCQ_GLOBAL float*)alpha, T, C, segs, halves, tile, blockIdx.x - tile * (uint32_t)segs, xq, sq, xq_plane, sq_plane, NG, 1,
+                         (int)blockIdx.y, (int)blockIdx.y + 1);
 }
 
 // ---------------------------------------------------------------------------------------------------------
