@@ -225,6 +225,9 @@ def bcq_unpack(packed, planes_i8=None):
 
 
 def bcq_pack_transposed(packed, packed_t=None):
+    out = _try_native("pack_transposed", packed, packed_t)
+    if out is not None:
+        return out
     q, N, Kw = packed.shape
     _need(packed, torch.int32, (q, N, Kw), "packed")
     K = Kw * 32
@@ -242,6 +245,9 @@ def decode_layout_bytes(N, K, q):
 
 def bcq_pack_decode(packed, tiled=None):
     """canonical packed[q,N,K/32] -> decode layout (flat int32 tensor of decode_layout_bytes(N, K, q) bytes)."""
+    out = _try_native("pack_decode", packed, tiled)
+    if out is not None:
+        return out
     q, N, Kw = packed.shape
     _need(packed, torch.int32, (q, N, Kw), "packed")
     K = Kw * 32
@@ -369,6 +375,10 @@ def bcq_linear_bwd_alpha(packed, x, dy, q_train=None, grad_scale=1.0, dalpha=Non
 
 def bcq_quantize_grouped(W, q, g, alpha=None, packed=None, planes_i8=None, want_planes=False, workspace=None):
     """Greedy BCQ of every length-g vector of W[N,K] -> (alpha[q,N,K/g] f32, packed[q,N,K/32], planes_i8 or None)."""
+    if planes_i8 is None and not want_planes:
+        out = _try_native("quantize_grouped", W, q, int(g), alpha, packed, workspace)
+        if out is not None:
+            return out[0], out[1], None
     N, K = W.shape
     g = int(g)
     G = K // max(g, 1)

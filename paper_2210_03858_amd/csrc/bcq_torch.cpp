@@ -138,6 +138,44 @@ py::object bwd_alpha_grouped(const Tensor& packed, const Tensor& x, const Tensor
     return st == BCQ_OK ? py::cast(*dalpha) : py::none();
 }
 
+// ---- quantizing and laying out a layer's weights: calls of 5 to 25 us, several per layer
+py::object quantize_grouped(const Tensor& W, int64_t q, int64_t g, OptTensor alpha, OptTensor packed, const OptTensor& workspace) {
+    if (W.dim() != 2 || q < 1 || q > 8 || g < 32) return py::none();
+    const int64_t N = W.size(0), K = W.size(1), G = K / g;
+    if (!plain(W, at::kFloat, {N, K}) || (alpha && !plain(*alpha, at::kFloat, {q, N, G})) ||
+        (packed && !plain(*packed, at::kInt, {q, N, K / 32})) || !plain_workspace(workspace))
+        return py::none();
+    if (!alpha) alpha = at::empty({q, N, G}, W.options());
+    if (!packed) packed = at::empty({q, N, K / 32}, W.options().dtype(at::kInt));
+    const bcq_status st = unlocked([&] {
+        return bcq_quantize_grouped(W.data_ptr<float>(), N, K, g, (int)q, alpha->data_ptr<float>(), static_cast<uint32_t*>(packed->data_ptr()),
+                                    nullptr, ptr(workspace), bytes(workspace), current_stream());
+    });
+    return st == BCQ_OK ? py::object(py::make_tuple(*alpha, *packed)) : py::none();
+}
+
+py::object pack_transposed(const Tensor& packed, OptTensor packed_t) {
+    const Shape s = layer_shape(packed, 32);
+    if (!s.ok || s.N % 32 != 0 || (packed_t && !plain(*packed_t, at::kInt, {s.q, s.K, s.N / 32}))) return py::none();
+    if (!packed_t) packed_t = at::empty({s.q, s.K, s.N / 32}, packed.options());
+    const bcq_status st = unlocked([&] {
+        return bcq_pack_transposed(words(packed), s.N, s.K, (int)s.q, static_cast<uint32_t*>(packed_t->data_ptr()), current_stream());
+    });
+    return st == BCQ_OK ? py::cast(*packed_t) : py::none();
+}
+
+py::object pack_decode(const Tensor& packed, OptTensor tiled) {
+    const Shape s = layer_shape(packed, 32);
+    size_t need = 0;
+    if (!s.ok || bcq_decode_layout_bytes(s.N, s.K, (int)s.q, &need) != BCQ_OK || (tiled && !plain(*tiled, at::kInt, {(int64_t)(need / 4)})))
+        return py::none();
+    if (!tiled) tiled = at::empty({(int64_t)(need / 4)}, packed.options());
+    const bcq_status st = unlocked([&] {
+        return bcq_pack_decode(words(packed), s.N, s.K, (int)s.q, static_cast<uint32_t*>(tiled->data_ptr()), current_stream());
+    });
+    return st == BCQ_OK ? py::cast(*tiled) : py::none();
+}
+
 // ---- autograd ---------------------------------------------------------------------------------------------------
 // The frozen state of a layer, passed to the node beside its two differentiable inputs.
 struct Frozen {
@@ -303,5 +341,8 @@ PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
     define(m, "fwd_decode", &fwd_decode);
     define(m, "bwd_input_grouped", &bwd_input_grouped);
     define(m, "bwd_alpha_grouped", &bwd_alpha_grouped);
+    define(m, "quantize_grouped", &quantize_grouped);
+    define(m, "pack_transposed", &pack_transposed);
+    define(m, "pack_decode", &pack_decode);
     define(m, "linear", &linear);
 }

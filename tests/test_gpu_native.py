@@ -209,3 +209,38 @@ def test_two_threads_on_two_streams(layer):
     for t in threads:
         t.join()
     assert not wrong and all(not t.is_alive() for t in threads)
+
+
+@pytest.mark.parametrize("N,K,g,q", [(96, 256, 64, 3), (33, 96, 96, 1), (64, 1056, 32, 8)])
+def test_quantizer_and_layouts_equal_the_python_path(monkeypatch, N, K, g, q):
+    """Same words and scales from both host paths, with outputs made and given; what the native one does not take is refused as ever."""
+    import torch
+    import paper_2210_03858_amd as bcq
+    from paper_2210_03858_amd import binding
+    W = torch.randn((N, K), device="cuda")
+
+    def run():
+        alpha, packed, planes = bcq.bcq_quantize_grouped(W, q, g)
+        assert planes is None
+        given = bcq.bcq_quantize_grouped(W, q, g, alpha=torch.zeros_like(alpha), packed=torch.zeros_like(packed),
+                                         workspace=torch.zeros(4, dtype=torch.int32, device="cuda"))
+        assert torch.equal(given[0], alpha) and torch.equal(given[1], packed)
+        out = [alpha, packed, bcq.bcq_pack_decode(packed), bcq.bcq_pack_decode(packed, torch.zeros_like(bcq.bcq_pack_decode(packed)))]
+        if N % 32 == 0:
+            out += [bcq.bcq_pack_transposed(packed), bcq.bcq_pack_transposed(packed, torch.zeros_like(bcq.bcq_pack_transposed(packed)))]
+        else:
+            with pytest.raises(bcq.BcqError):
+                bcq.bcq_pack_transposed(packed)
+        for call in (lambda: bcq.bcq_quantize_grouped(W.t(), q, g), lambda: bcq.bcq_pack_decode(packed.float()),
+                     lambda: bcq.bcq_pack_decode(packed, torch.zeros(4, dtype=torch.int32, device="cuda"))):
+            with pytest.raises(ValueError):
+                call()
+        with pytest.raises(bcq.BcqError):
+            bcq.bcq_quantize_grouped(W, 9, g)
+        return out
+
+    assert binding.native()
+    native = run()
+    monkeypatch.setattr(binding, "_try_native", lambda *args: None)
+    for a, b in zip(native, run()):
+        assert a.dtype == b.dtype and torch.equal(a, b)
