@@ -29,7 +29,7 @@
 // 15 rounds of 1024 x 1024: q = 3 72 -> 27 us, q = 4 119 -> 38 (against four waves, the vector in LDS and 2^q fp64
 // distances per element).
 //
-// Vectors of one wave and at least 8 rounds (RANKED): all that a round needs of the elements is how many lie below each threshold and their
+// Vectors of one wave and at least 8 rounds, with three planes of up to four waves and at least 12 (RANKED): all that a round needs of the elements is how many lie below each threshold and their
 // sum, as every sum is a combination of those of the cells between the thresholds.  So the wave sorts the |w| once (6000
 // cycles, about 1400 operations) and keeps the sums of the first of them; a threshold is then found by one comparison of the lanes'
 // smallest elements and one of 16 elements, and the greedy start is found the same way.  A round of q = 3 takes 1800 cycles for 3450: solve
@@ -37,7 +37,9 @@
 // elements took 1880; far code out of the loop's way is worth 500 of it, a lone wave waits for every jump.  15 rounds, us, 1024
 // vectors of 1024, q = 2, 3, 4: 17.8, 26.6, 38 -> 15.3, 19.4, 29.6; 4096 of them 40, 71, 108 -> 33, 49, 77; 8192 of 256 30, 74,
 // 116 -> 27, 56, 102.  Below 8 rounds the sorting costs more than it saves (4096 of 1024, q = 2, 4 rounds 18 / 23, 8 28.5 / 27.8; q = 4
-// 39 / 44, 64 / 57).  Of several waves, which exchange their sums at a barrier, 1024 of 2560 take 73 us either way.
+// 39 / 44, 64 / 57).  Several waves sort apart and add their sums and counts at the round's barrier: q = 3, 15 rounds, 1024 vectors of
+// 1280, 2560, 4096 48.6, 73, 84 -> 36, 63, 75, 8 rounds of 4096 50.6 / 51.6.  With two planes a round has too little to save (1024 of 2560 44
+// / 47), with four the registers for three waves to a vector unit do not hold it (129 / 200).
 #include <type_traits>
 
 #include "bcq_internal.h"
@@ -45,7 +47,7 @@
 namespace bcq {
 
 constexpr int ALT_MAX_WAVES = 4;
-constexpr int ALT_SORT_ROUNDS = 8;  // (figures above)
+constexpr int ALT_SORT_ROUNDS = 8, ALT_SORT_ROUNDS_WAVES = 12;  // (figures above)
 
 template <int Q>
 struct AltShared {
@@ -459,24 +461,26 @@ __device__ __forceinline__ double sum_before(double v) {
 
 template <int Q, int MW>
 struct AltRegShared {
-    static constexpr int LEVELS = 1 << Q, PAIRS = Q * (Q - 1) / 2, SUMS = Q + (PAIRS + 2) / 3;
-    double part[2][MW][SUMS];                 // waves' totals of a round, rounds in turn
+    static constexpr int LEVELS = 1 << Q, PAIRS = Q * (Q - 1) / 2, SUMS = Q + (PAIRS + 2) / 3, TH = LEVELS > 2 ? LEVELS / 2 - 1 : 1;
+    double part[2][MW][SUMS > TH ? SUMS : TH];  // waves' totals of a round, rounds in turn: sums, or those below the thresholds
+    uint32_t under[2][MW][TH];                // and the elements below them
+    double absolute[MW];                      // sums of |w|
     double level[MW][LEVELS], raw[MW][LEVELS];  // every wave sorts for itself
     uint32_t changed[2][MW];
     uint32_t extreme[MW][2];                  // `low` and `high` of the waves
     uint8_t pattern[MW][LEVELS];
 };
 
-// QL: quads of elements per lane; MW: waves at most; RANKED: rounds from the sorted elements (vectors of one wave).
+// QL: quads of elements per lane; MW: waves at most; RANKED: rounds from the sorted elements.
 template <int Q, int QL, int MW, bool RANKED>
-__global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* __restrict__ W, int64_t V, int n, int iters,
+__global__ __launch_bounds__(64 * MW, RANKED && MW > 1 ? 3 : 1) void alternating_reg_kernel(const float* __restrict__ W, int64_t V, int n, int iters,
                                                                   float* __restrict__ alpha, uint32_t* __restrict__ packed,
                                                                   int8_t* __restrict__ planes, int* __restrict__ status_word) {
     using Shared = AltRegShared<Q, MW>;
     constexpr int PAIRS = Shared::PAIRS, LEVELS = Shared::LEVELS, HALF = LEVELS / 2, SUMS = Shared::SUMS;
     constexpr int NV = SUMS <= 1 ? 1 : SUMS <= 2 ? 2 : SUMS <= 4 ? 4 : 8;
-    constexpr int NE = 4 * QL, TH = HALF > 1 ? HALF - 1 : 1;
-    static_assert(!RANKED || (Q > 1 && MW == 1), "one wave");
+    constexpr int NE = 4 * QL, TH = Shared::TH;
+    static_assert(!RANKED || (Q > 1 && QL <= 4), "16 elements of a lane to a search");
     extern __shared__ __attribute__((aligned(16))) unsigned char alt_smem[];
     Shared& sh = *reinterpret_cast<Shared*>(alt_smem);
     uint32_t* code4 = reinterpret_cast<uint32_t*>(alt_smem + (sizeof(Shared) + 15) / 16 * 16);  // [n / 4], for the output
@@ -519,8 +523,9 @@ __global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* _
     high = wave_max(high);
     // Sorted |w| of the wave (beyond the vector above every threshold), at lane * (NE + 1) + i, and the sums of the first of them, that of
     // the first NE l + i at 65 i + l: all that a round needs of the elements is how many lie below each threshold, and their sum.
-    double* const prefix = reinterpret_cast<double*>(alt_smem + (sizeof(Shared) + 15) / 16 * 16 + (n + 15) / 16 * 16);
-    uint32_t* const sorted = reinterpret_cast<uint32_t*>(prefix + 65 * NE);
+    double* const prefixes = reinterpret_cast<double*>(alt_smem + (sizeof(Shared) + 15) / 16 * 16 + (n + 15) / 16 * 16);
+    double* const prefix = prefixes + wave * (65 * NE);
+    uint32_t* const sorted = reinterpret_cast<uint32_t*>(prefixes + waves * (65 * NE)) + wave * (64 * (NE + 1));
     uint32_t lane_first = 0u;  // the smallest of the lane's NE
     double absolute = 0.0;
     if constexpr (RANKED) {
@@ -549,9 +554,12 @@ __global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* _
         if (lane == 0) {
             sh.extreme[wave][0] = low;
             sh.extreme[wave][1] = high;
+            sh.absolute[wave] = absolute;
         }
         __syncthreads();
+        absolute = 0.0;
         for (int u = 0; u < waves; ++u) {
+            absolute += sh.absolute[u];
             low = sh.extreme[u][0] > low ? sh.extreme[u][0] : low;
             high = sh.extreme[u][1] > high ? sh.extreme[u][1] : high;
         }
@@ -594,6 +602,12 @@ __global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* _
     // the pattern of every element from the thresholds of |w| and the patterns between them; non-zero where one changes
     auto assign = [&](const float (&thr)[HALF], uint64_t lut) {
         const uint32_t lo = (uint32_t)lut, hi = (uint32_t)(lut >> 32);
+        float t[HALF];  // (values: of elements of the array the compiler makes branches)
+#pragma unroll
+        for (int k = 0; k + 1 < HALF; ++k) {
+            t[k] = thr[k];
+            asm("" : "+v"(t[k]));
+        }
         uint32_t diff = 0u;
 #pragma unroll
         for (int u = 0; u < QL; ++u) {
@@ -603,14 +617,14 @@ __global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* _
                 const float m = fabsf(x[u][e]);
                 uint32_t idx = 0u;  // thresholds above |w|
                 if constexpr (HALF == 8) {
-                    const bool far = m < thr[3];
-                    const float second = far ? thr[5] : thr[1];
+                    const bool far = m < t[3];
+                    const float second = far ? t[5] : t[1], near = far ? t[4] : t[0], other = far ? t[6] : t[2];
                     const bool b = m < second;
-                    const float third = far ? (b ? thr[6] : thr[4]) : (b ? thr[2] : thr[0]);
+                    const float third = b ? other : near;
                     idx = (far ? 4u : 0u) + (b ? 2u : 0u) + (m < third ? 1u : 0u);
                 } else {
 #pragma unroll
-                    for (int k = 0; k + 1 < HALF; ++k) idx += m < thr[k] ? 1u : 0u;
+                    for (int k = 0; k + 1 < HALF; ++k) idx += m < t[k] ? 1u : 0u;
                 }
                 sel |= idx << (8 * e);
                 neg |= (uint32_t)((int)__float_as_uint(x[u][e]) >> 31) & ((uint32_t)(LEVELS - 1) << (8 * e));
@@ -693,6 +707,8 @@ __global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* _
             double level[HALF];  // of the cells so far, uppermost first
             level[0] = a[0];
             bool close = false;
+            int all_under[TH];  // of all waves
+            double all_below[TH];
 #pragma unroll
             for (int i = 1; i < Q; ++i) {
                 constexpr int none = -1;
@@ -711,12 +727,36 @@ __global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* _
                 }
 #pragma unroll
                 for (int c = 0; c < cells; ++c) {
-                    const int k = (2 * c + 1) * step - 1, above = c > 0 ? k - step : none, beneath = c + 1 < cells ? k + step : none;
-                    under[k] = count(k);
+                    const int k = (2 * c + 1) * step - 1;
                     const double m = level[c], eps = 1e-14 * a[0];
                     close = close || fabs((double)__uint_as_float(near[k]) - m) <= eps || fabs((double)__uint_as_float(lane_first) - m) <= eps;
-                    const int n_above = (above == none ? n : under[above]) - under[k], n_beneath = under[k] - (beneath == none ? 0 : under[beneath]);
-                    const double s_above = (above == none ? absolute : below[above]) - below[k], s_beneath = below[k] - (beneath == none ? 0.0 : below[beneath]);
+                    all_under[k] = under[k] = count(k);
+                    all_below[k] = below[k];
+                    if (MW > 1 && lane == 0) {
+                        sh.part[i & 1][wave][k] = below[k];
+                        sh.under[i & 1][wave][k] = (uint32_t)under[k];
+                    }
+                }
+                if (MW > 1) {  // over the waves, in wave order
+                    __syncthreads();
+#pragma unroll
+                    for (int c = 0; c < cells; ++c) {
+                        const int k = (2 * c + 1) * step - 1;
+                        all_under[k] = 0;
+                        all_below[k] = 0.0;
+                        for (int u = 0; u < waves; ++u) {
+                            all_under[k] += (int)sh.under[i & 1][u][k];
+                            all_below[k] += sh.part[i & 1][u][k];
+                        }
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < cells; ++c) {
+                    const int k = (2 * c + 1) * step - 1, above = c > 0 ? k - step : none, beneath = c + 1 < cells ? k + step : none;
+                    const double m = level[c];
+                    const int n_above = (above == none ? n : all_under[above]) - all_under[k], n_beneath = all_under[k] - (beneath == none ? 0 : all_under[beneath]);
+                    const double s_above = (above == none ? absolute : all_below[above]) - all_below[k];
+                    const double s_beneath = all_below[k] - (beneath == none ? 0.0 : all_below[beneath]);
                     total += (s_above - m * (double)n_above) + (m * (double)n_beneath - s_beneath);
                 }
                 close = close || !(total >= 1e-3 * absolute);  // (their differences keep 2^-40 of it)
@@ -735,7 +775,7 @@ __global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* _
                 for (int i = 1; i < Q; ++i) pattern |= (uint64_t)(((c >> (Q - 1 - i)) & 1) ^ 1) << i;
                 lut |= pattern << (8 * c);
             }
-            started = __all(!close);
+            started = MW == 1 ? __all(!close) : __syncthreads_and(!close);
             known = owed = from_below = started;
             describe();
         }
@@ -776,19 +816,48 @@ __global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* _
 
     for (int it = 0; it < iters; ++it) {
         bool changed_elsewhere = false;
+        int all_under[TH];
+        double all_below[TH];
+#pragma unroll
+        for (int k = 0; k < TH; ++k) {
+            all_under[k] = under[k];
+            all_below[k] = below[k];
+        }
 
         if (MW > 1) {  // totals over the waves, in wave order; every wave leaves the loop with the others
             const int turn = it & 1;
+            const bool from = RANKED && from_below;
             if (lane == 0) {
+                if (from) {
 #pragma unroll
-                for (int i = 0; i < SUMS; ++i) sh.part[turn][wave][i] = sum[i];
+                    for (int k = 0; k < TH; ++k) {
+                        sh.part[turn][wave][k] = below[k];
+                        sh.under[turn][wave][k] = (uint32_t)under[k];
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < SUMS; ++i) sh.part[turn][wave][i] = sum[i];
+                }
             }
             __syncthreads();
 #pragma unroll
             for (int i = 0; i < SUMS; ++i) sum[i] = 0.0;
-            for (int u = 0; u < waves; ++u) {
 #pragma unroll
-                for (int i = 0; i < SUMS; ++i) sum[i] += sh.part[turn][u][i];
+            for (int k = 0; k < TH; ++k) {
+                all_under[k] = 0;
+                all_below[k] = 0.0;
+            }
+            for (int u = 0; u < waves; ++u) {
+                if (from) {
+#pragma unroll
+                    for (int k = 0; k < TH; ++k) {
+                        all_below[k] += sh.part[turn][u][k];
+                        all_under[k] += (int)sh.under[turn][u][k];
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < SUMS; ++i) sum[i] += sh.part[turn][u][i];
+                }
                 if (it > 0) changed_elsewhere = changed_elsewhere || sh.changed[turn ^ 1][u] != 0u;
             }
             if (it > 0 && !changed_elsewhere) break;
@@ -798,7 +867,7 @@ __global__ __launch_bounds__(64 * MW) void alternating_reg_kernel(const float* _
         if (RANKED && from_below) {
             double v = part[0] * (pair ? (double)n : absolute);
 #pragma unroll
-            for (int k = 0; k + 1 < HALF; ++k) v = __builtin_fma(part[k + 1], pair ? (double)under[k] : below[k], v);
+            for (int k = 0; k + 1 < HALF; ++k) v = __builtin_fma(part[k + 1], pair ? (double)all_under[k] : all_below[k], v);
 #pragma unroll
             for (int i = 0; i < Q; ++i) rhs[i] = of_lane(v, i);
 #pragma unroll
@@ -1052,12 +1121,12 @@ static hipError_t launch_q(const float* W, int64_t V, int n, int iters, float* a
 template <int Q, int QL, int MW, bool RANKED>
 static hipError_t launch_reg_form(const float* W, int64_t V, int n, int iters, float* alpha, uint32_t* packed, int8_t* planes,
                                   int* status_word, hipStream_t st) {
-    const size_t sorted = RANKED ? 65 * 4 * QL * 8 + 64 * (4 * QL + 1) * 4 : 0;
+    const int waves = (n / 4 + 64 * QL - 1) / (64 * QL);
+    const size_t sorted = RANKED ? (size_t)waves * (65 * 4 * QL * 8 + 64 * (4 * QL + 1) * 4) : 0;
     const size_t lds = (sizeof(AltRegShared<Q, MW>) + 15) / 16 * 16 + (size_t)(n + 15) / 16 * 16 + sorted;
     static LdsLimit limit;
     hipError_t e = limit.ensure((const void*)alternating_reg_kernel<Q, QL, MW, RANKED>, lds);
     if (e != hipSuccess) return e;
-    const int waves = (n / 4 + 64 * QL - 1) / (64 * QL);
     BCQ_LAUNCH((alternating_reg_kernel<Q, QL, MW, RANKED>), dim3((unsigned)V), dim3(64 * waves), lds, st, W, V, n, iters, alpha, packed,
                        planes, status_word);
     return hipGetLastError();
@@ -1066,8 +1135,8 @@ static hipError_t launch_reg_form(const float* W, int64_t V, int n, int iters, f
 template <int Q, int QL, int MW>
 static hipError_t launch_reg(const float* W, int64_t V, int n, int iters, float* alpha, uint32_t* packed, int8_t* planes,
                              int* status_word, hipStream_t st) {
-    if constexpr (Q > 1 && MW == 1) {
-        if (iters >= ALT_SORT_ROUNDS) return launch_reg_form<Q, QL, MW, true>(W, V, n, iters, alpha, packed, planes, status_word, st);
+    if constexpr ((Q > 1 && MW == 1) || (Q == 3 && QL == 4)) {
+        if (iters >= (MW == 1 ? ALT_SORT_ROUNDS : ALT_SORT_ROUNDS_WAVES)) return launch_reg_form<Q, QL, MW, true>(W, V, n, iters, alpha, packed, planes, status_word, st);
     }
     return launch_reg_form<Q, QL, MW, false>(W, V, n, iters, alpha, packed, planes, status_word, st);
 }

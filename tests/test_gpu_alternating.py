@@ -179,9 +179,10 @@ def test_nonfinite_vectors_of_several_waves(bcq, oracle, K):
 
 
 @pytest.mark.parametrize("kind", ["normal", "heavy", "grid", "two"])
-@pytest.mark.parametrize("N,K", [(9, 32), (9, 96), (6, 256), (6, 288), (5, 480), (5, 544), (5, 992), (5, 1024)])
+@pytest.mark.parametrize("N,K", [(9, 32), (9, 96), (6, 256), (6, 288), (5, 480), (5, 544), (5, 992), (5, 1024), (4, 1056), (4, 2560),
+                                 (3, 4096)])
 def test_rounds_from_the_sorted_elements(bcq, oracle, N, K, kind):
-    """Vectors of one wave, with idle lanes and none, one round below and at the line from which their elements are sorted: normal
+    """One to four waves, with idle lanes and none, one round below and at the lines from which their elements are sorted: normal
     and heavy-tailed weights (levels that change their order, counts that stay), weights on a coarse grid (ties with the greedy levels
     and equal elements on both sides of a threshold) and two magnitudes (the later planes have next to nothing left).  Same bar."""
     rng = np.random.default_rng(K + N)
@@ -193,5 +194,5 @@ def test_rounds_from_the_sorted_elements(bcq, oracle, N, K, kind):
             W = np.round(W * 8 + 0.25) / 8 + np.float32(1e-3) * rng.standard_normal((N, 1)).astype(np.float32)
         if kind == "two":
             W = np.where(np.abs(W) > 0.6, 0.7, 0.3) * np.sign(W) + np.float32(1e-6) * W
-        for iters in (7, 8, 15):
+        for iters in (7, 8, 15) if K <= 1024 else (11, 12, 15):
             _check(bcq, oracle, W.astype(np.float32), q, iters=iters)
