@@ -815,6 +815,9 @@ __global__ __launch_bounds__(64 * MW, RANKED && MW > 1 ? 3 : 1) void alternating
     }
 
     for (int it = 0; it < iters; ++it) {
+        // The exchanges take turns from plane 0 of the greedy start on, round `it` after plane Q - 1: between the reads of one and the next
+        // writes of the same buffer lies the other one's barrier, so that no wave overwrites what a slower one still reads.
+        const int turn = (Q + it) & 1;
         bool changed_elsewhere = false;
         int all_under[TH];
         double all_below[TH];
@@ -825,7 +828,6 @@ __global__ __launch_bounds__(64 * MW, RANKED && MW > 1 ? 3 : 1) void alternating
         }
 
         if (MW > 1) {  // totals over the waves, in wave order; every wave leaves the loop with the others
-            const int turn = it & 1;
             const bool from = RANKED && from_below;
             if (lane == 0) {
                 if (from) {
@@ -1070,7 +1072,7 @@ __global__ __launch_bounds__(64 * MW, RANKED && MW > 1 ? 3 : 1) void alternating
         }
         const bool changed = __any(diff != 0u);
         if (MW == 1 && !changed) break;
-        if (MW > 1 && lane == 0) sh.changed[it & 1][wave] = changed ? 1u : 0u;
+        if (MW > 1 && lane == 0) sh.changed[turn][wave] = changed ? 1u : 0u;
         from_below = known;
         if (!from_below) form_sums();
     }

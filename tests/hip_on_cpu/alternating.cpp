@@ -1,0 +1,15 @@
+// The alternating quantizer's kernels on the CPU.
+#include "../../paper_2210_03858_amd/csrc/bcq_alternating.hip"
+
+thread_local bool bcq::tl_dry_run = false;
+namespace bcq {
+alignas(16) unsigned char alt_smem[160 * 1024];  // the workgroup's shared memory
+}
+unsigned char* const emu::shared = bcq::alt_smem;
+const size_t emu::shared_bytes = sizeof bcq::alt_smem;
+
+extern "C" int quantize_alternating(const float* W, int64_t V, int64_t n, int q, int iters, float* alpha, uint32_t* packed, int* status,
+                                    int backwards) {
+    emu::backwards = backwards != 0;
+    return bcq::launch_quantize_alternating(W, V, n, q, iters, alpha, packed, nullptr, status, nullptr);
+}

@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 from _util import packed_to_host, to_dev
+from test_cpu_alternating import degenerate_rows
 from paper_2210_03858_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -196,3 +197,13 @@ def test_rounds_from_the_sorted_elements(bcq, oracle, N, K, kind):
             W = np.where(np.abs(W) > 0.6, 0.7, 0.3) * np.sign(W) + np.float32(1e-6) * W
         for iters in (7, 8, 15) if K <= 1024 else (11, 12, 15):
             _check(bcq, oracle, W.astype(np.float32), q, iters=iters)
+
+
+@pytest.mark.parametrize("K", [1056, 2560, 4096, 4128])
+def test_singular_first_round_of_several_waves(bcq, oracle, K):
+    """Zero, constant and two-magnitude vectors return the scales of the greedy start: refused by the start from the sorted elements, and in
+    the forms that do not sort."""
+    for q in (2, 3, 4):
+        W = np.concatenate([degenerate_rows(K), synth.weights(1, "out", 3, K, extra=K + q)])
+        for iters in (0, 1, 11, 12, 15):
+            _check(bcq, oracle, W, q, iters=iters)
