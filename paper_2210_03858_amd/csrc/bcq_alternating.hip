@@ -521,6 +521,22 @@ __global__ __launch_bounds__(64 * MW, RANKED && MW > 1 ? 3 : 1) void alternating
         }
     low = wave_max(low);
     high = wave_max(high);
+    if (MW > 1) {
+        if (lane == 0) {
+            sh.extreme[wave][0] = low;
+            sh.extreme[wave][1] = high;
+        }
+        __syncthreads();
+        for (int u = 0; u < waves; ++u) {
+            low = sh.extreme[u][0] > low ? sh.extreme[u][0] : low;
+            high = sh.extreme[u][1] > high ? sh.extreme[u][1] : high;
+        }
+    }
+    const float smallest = low ? __uint_as_float(0u - low) : 3.402823466e38f, largest = __uint_as_float(high);
+    // Not with an element so small against the levels (the largest of which is rarely below an eighth of the largest element) that every
+    // round will take the fp64 distances: such a vector would pay for its sorting and not use it (q = 4, cubes of normal weights, 15 rounds,
+    // us, sorted / not: 65536 vectors of 128 882 / 740).
+    const bool ranked = RANKED && __all(high < 0x7F800000u && smallest >= 1.2e-10f * largest);
     // Sorted |w| of the wave (beyond the vector above every threshold), at lane * (NE + 1) + i, and the sums of the first of them, that of
     // the first NE l + i at 65 i + l: all that a round needs of the elements is how many lie below each threshold, and their sum.
     double* const prefixes = reinterpret_cast<double*>(alt_smem + (sizeof(Shared) + 15) / 16 * 16 + (n + 15) / 16 * 16);
@@ -528,7 +544,7 @@ __global__ __launch_bounds__(64 * MW, RANKED && MW > 1 ? 3 : 1) void alternating
     uint32_t* const sorted = reinterpret_cast<uint32_t*>(prefixes + waves * (65 * NE)) + wave * (64 * (NE + 1));
     uint32_t lane_first = 0u;  // the smallest of the lane's NE
     double absolute = 0.0;
-    if constexpr (RANKED) {
+    if (ranked) {
         uint32_t m[NE];
 #pragma unroll
         for (int u = 0; u < QL; ++u)
@@ -549,22 +565,13 @@ __global__ __launch_bounds__(64 * MW, RANKED && MW > 1 ? 3 : 1) void alternating
         if (lane == 63) prefix[64] = before + upto[NE];
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         absolute = of_lane(before + upto[NE], 63);
-    }
-    if (MW > 1) {
-        if (lane == 0) {
-            sh.extreme[wave][0] = low;
-            sh.extreme[wave][1] = high;
-            sh.absolute[wave] = absolute;
-        }
-        __syncthreads();
-        absolute = 0.0;
-        for (int u = 0; u < waves; ++u) {
-            absolute += sh.absolute[u];
-            low = sh.extreme[u][0] > low ? sh.extreme[u][0] : low;
-            high = sh.extreme[u][1] > high ? sh.extreme[u][1] : high;
+        if (MW > 1) {
+            if (lane == 0) sh.absolute[wave] = absolute;
+            __syncthreads();
+            absolute = 0.0;
+            for (int u = 0; u < waves; ++u) absolute += sh.absolute[u];
         }
     }
-    const float smallest = low ? __uint_as_float(0u - low) : 3.402823466e38f, largest = __uint_as_float(high);
 
     // B^T w and, three counts of at most 16384 to a double, the disagreeing signs of pairs of planes
     double sum[NV];
@@ -702,7 +709,7 @@ __global__ __launch_bounds__(64 * MW, RANKED && MW > 1 ? 3 : 1) void alternating
     double a[Q];
     bool started = false;
     if constexpr (RANKED) {
-        if (high < 0x7F800000u) {
+        if (ranked) {
             a[0] = (double)(float)(absolute / (double)n);
             double level[HALF];  // of the cells so far, uppermost first
             level[0] = a[0];
@@ -997,9 +1004,9 @@ __global__ __launch_bounds__(64 * MW, RANKED && MW > 1 ? 3 : 1) void alternating
             if (__builtin_expect(!same, 0)) {
                 diff = assign(thr, patterns);
                 lut = patterns;
-                if (RANKED) describe();
+                if (ranked) describe();
             }
-            if constexpr (RANKED) {
+            if (ranked) {
 #pragma unroll
                 for (int k = 0; k < TH; ++k) look(k);
 #pragma unroll
@@ -1010,7 +1017,7 @@ __global__ __launch_bounds__(64 * MW, RANKED && MW > 1 ? 3 : 1) void alternating
                 }
             }
             owed = same;
-            known = RANKED;
+            known = ranked;
         } else {
             if (RANKED && owed) assign(thr, lut);
             known = owed = false;

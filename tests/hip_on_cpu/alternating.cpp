@@ -9,7 +9,10 @@ unsigned char* const emu::shared = bcq::alt_smem;
 const size_t emu::shared_bytes = sizeof bcq::alt_smem;
 
 extern "C" int quantize_alternating(const float* W, int64_t V, int64_t n, int q, int iters, float* alpha, uint32_t* packed, int* status,
-                                    int backwards) {
+                                    int backwards, int64_t* operations) {
     emu::backwards = backwards != 0;
-    return bcq::launch_quantize_alternating(W, V, n, q, iters, alpha, packed, nullptr, status, nullptr);
+    emu::operations = 0;
+    const hipError_t e = bcq::launch_quantize_alternating(W, V, n, q, iters, alpha, packed, nullptr, status, nullptr);
+    *operations = emu::operations;
+    return e;
 }

@@ -52,6 +52,7 @@ inline std::vector<Lane>* lanes;
 inline std::vector<Wave>* waves;
 inline ucontext_t scheduler;
 inline bool backwards;     // the order of the waves
+inline int64_t operations;  // over lanes, of all waves so far
 inline int votes;          // of all lanes at the last barrier
 inline std::function<void()> body;
 extern unsigned char* const shared;
@@ -67,6 +68,7 @@ inline const uint64_t* exchange(uint64_t v) {
     if (++w.arrived[turn] == 64) {
         w.arrived[turn] = 0;
         ++w.finished;
+        ++operations;
     }
     while (w.finished <= op) yield();
     return w.posted[turn];

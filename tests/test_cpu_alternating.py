@@ -26,15 +26,17 @@ def kernels(tmp_path_factory):
                         os.path.join(HERE, "hip_on_cpu", "alternating.cpp"), "-o", out], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     lib = ctypes.CDLL(out)
-    lib.quantize_alternating.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int] + [ctypes.c_void_p] * 3 + [ctypes.c_int]
+    lib.quantize_alternating.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int] + [ctypes.c_void_p] * 3 + [ctypes.c_int, ctypes.c_void_p]
     return lib
 
 
-def _run(lib, W, q, iters, backwards):
+def _run(lib, W, q, iters, backwards=0):
+    """(scales, words, non-finite vectors, operations over lanes)"""
     V, n = W.shape
-    alpha, packed, status = np.empty((q, V), np.float32), np.empty((q, V, n // 32), np.uint32), np.empty(1, np.int32)
-    assert lib.quantize_alternating(W.ctypes.data, V, n, q, iters, alpha.ctypes.data, packed.ctypes.data, status.ctypes.data, backwards) == 0
-    return alpha, packed, int(status[0])
+    alpha, packed, status, operations = np.empty((q, V), np.float32), np.empty((q, V, n // 32), np.uint32), np.empty(1, np.int32), np.empty(1, np.int64)
+    assert lib.quantize_alternating(W.ctypes.data, V, n, q, iters, alpha.ctypes.data, packed.ctypes.data, status.ctypes.data, backwards,
+                                    operations.ctypes.data) == 0
+    return alpha, packed, int(status[0]), int(operations[0])
 
 
 @pytest.mark.parametrize("backwards", [0, 1])
@@ -44,7 +46,7 @@ def _run(lib, W, q, iters, backwards):
 def test_no_wave_depends_on_the_others_pace(kernels, oracle, q, n, iters, backwards):
     rng = np.random.default_rng(n + q)
     W = np.concatenate([degenerate_rows(n), rng.standard_normal((2, n)).astype(np.float32)])
-    alpha, packed, status = _run(kernels, W, q, iters, backwards)
+    alpha, packed, status, _ = _run(kernels, W, q, iters, backwards)
     a_ref, b_ref, margin, _ = oracle.quantize_alternating(W, q, iters=iters, with_margin=True)
     robust = (margin[:, 0] >= 1e-9) & (margin[:, 1] >= 2.0 ** -40)
     assert status == 0 and robust.sum() >= 6
@@ -59,5 +61,20 @@ def test_non_finite_vectors_in_either_order(kernels, n):
     assert all(np.array_equal(a, b) for a, b in zip(*clean))
     W[0, 3], W[2, n - 1] = np.inf, np.nan
     for backwards in (0, 1):
-        alpha, packed, status = _run(kernels, W, 3, 13, backwards)
+        alpha, packed, status, _ = _run(kernels, W, 3, 13, backwards)
         assert status == 2 and np.array_equal(alpha[:, 1], clean[0][0][:, 1]) and np.array_equal(packed[:, 1], clean[0][1][:, 1])
+
+
+@pytest.mark.parametrize("q,n,line", [(2, 96, 8), (3, 256, 8), (4, 1024, 8), (3, 1056, 12)])
+def test_no_sorting_for_an_element_far_below_the_levels(kernels, q, n, line):
+    """With such an element every round takes the fp64 distances.  The vector reaches its fixed point in two rounds, so that it costs one round
+    below and at the line of the sorted form the same but for the question itself; without the element the sorting shows."""
+    rng = np.random.default_rng(n)
+    levels = np.array([sum((1 if c >> i & 1 else -1) * 2.0 ** -i for i in range(q)) for c in range(2 ** q)])
+    W = (levels[rng.integers(0, 2 ** q, (1, n))] + 0.01 * rng.standard_normal((1, n))).astype(np.float32)
+    sorting = _run(kernels, W, q, line)[3] - _run(kernels, W, q, line - 1)[3]
+    assert sorting > 40
+    W[0, n // 2] = 1e-12
+    below, at = _run(kernels, W, q, line - 1), _run(kernels, W, q, line)
+    assert np.array_equal(below[0], at[0]) and np.array_equal(below[1], at[1])
+    assert abs(at[3] - below[3]) <= 8 * (1 if n <= 1024 else 2)
