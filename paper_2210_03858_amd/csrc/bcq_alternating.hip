@@ -29,17 +29,21 @@
 // 15 rounds of 1024 x 1024: q = 3 72 -> 27 us, q = 4 119 -> 38 (against four waves, the vector in LDS and 2^q fp64
 // distances per element).
 //
-// Vectors of one wave and at least 8 rounds, with three planes of up to four waves and at least 12 (RANKED): all that a round needs of the elements is how many lie below each threshold and their
+// Where enough rounds are allowed (sort_rounds below), for vectors of one wave and with three planes of up to four (RANKED): all that a
+// round needs of the elements is how many lie below each threshold and their
 // sum, as every sum is a combination of those of the cells between the thresholds.  So the wave sorts the |w| once (6000
 // cycles, about 1400 operations) and keeps the sums of the first of them; a threshold is then found by one comparison of the lanes'
 // smallest elements and one of 16 elements, and the greedy start is found the same way.  A round of q = 3 takes 1800 cycles for 3450: solve
 // 530, levels and thresholds 400 (1020 with sorting them anew: the last order is only confirmed), the search 600 where the
-// elements took 1880; far code out of the loop's way is worth 500 of it, a lone wave waits for every jump.  15 rounds, us, 1024
-// vectors of 1024, q = 2, 3, 4: 17.8, 26.6, 38 -> 15.3, 19.4, 29.6; 4096 of them 40, 71, 108 -> 33, 49, 77; 8192 of 256 30, 74,
-// 116 -> 27, 56, 102.  Below 8 rounds the sorting costs more than it saves (4096 of 1024, q = 2, 4 rounds 18 / 23, 8 28.5 / 27.8; q = 4
-// 39 / 44, 64 / 57).  Several waves sort apart and add their sums and counts at the round's barrier: q = 3, 15 rounds, 1024 vectors of
-// 1280, 2560, 4096 48.6, 73, 84 -> 36, 63, 75, 8 rounds of 4096 50.6 / 51.6.  With two planes a round has too little to save (1024 of 2560 44
-// / 47), with four the registers for three waves to a vector unit do not hold it (129 / 200).
+// elements took 1880; far code out of the loop's way is worth 500 of it, a lone wave waits for every jump.  15 rounds, us, normal weights,
+// element by element -> sorted, 1024 vectors of 1024, q = 2, 3, 4: 18.1, 27.1, 38.8 -> 14.7, 18.6, 28.3; 8192 of them 64, 135, 205 -> 58, 91,
+// 141; 8192 of 256 32, 74, 116 -> 25, 53, 99.  Rounds that change the levels' order, and vectors with single far elements, gain less: where waves
+// are alone on their vector units the slowest vector decides, 1024 of 256, q = 4, with 0.5 % of eightfold weights 32 -> 37; weights peaked at zero
+// (cubes of normal ones) 1.00 to 1.25 times the time, of several waves 1.1 to 1.5: their registers leave room for fewer waves, and their
+// rounds are element by element.  Several waves sort apart and add their sums and counts at the round's barrier: q = 3, 15 rounds, 1024 vectors of
+// 1280, 2560, 4096 49, 74, 86 -> 35, 64, 76.  They are compiled for three waves to a vector unit, for which 17 registers spill (64 bytes
+// a lane): without spills two fit, 1638 vectors of 2560 0.78 / 0.95 of the time element by element, 1024 of 4096 0.88 / 0.87.  With two
+// planes a round of several waves has too little to save (1024 of 2560 44 / 47), with four that register limit spills far more (129 / 200).
 #include <type_traits>
 
 #include "bcq_internal.h"
@@ -47,7 +51,6 @@
 namespace bcq {
 
 constexpr int ALT_MAX_WAVES = 4;
-constexpr int ALT_SORT_ROUNDS = 8, ALT_SORT_ROUNDS_WAVES = 12;  // (figures above)
 
 template <int Q>
 struct AltShared {
@@ -1141,11 +1144,24 @@ static hipError_t launch_reg_form(const float* W, int64_t V, int n, int iters, f
     return hipGetLastError();
 }
 
+// From how many allowed rounds on the elements are sorted.  What counts are the rounds that vectors take before their fixed point: of normal
+// weights and 32, 64, 128, 256 elements 2, 3, 4, 6 with two planes, 4, 6, 10, 12 with three, 6, 9, 12, 14 with four, so that short vectors with
+// two planes never repay their sorting, and with four planes, whose round needs seven searches, only where they may take more than 8 rounds.
+// 15 rounds, us, element by element / sorted: q = 2, 32768 vectors of 32 49.6 / 52.2, 16384 of 64 35.4 / 32.4, q = 3 104 / 94 and 84 / 68,
+// q = 4 195 / 205 and 156 / 140, 8 rounds 122 / 119, 1024 of 256 15.6 / 16.2.  Four waves: 12 rounds of 640 vectors of 4096 are equal or,
+// with heavy tails, slower by up to 1.12, 15 rounds 0.82 to 0.98 of the time with normal weights (worst, 512 vectors of 3328 with heavy tails, 1.06).
+static int sort_rounds(int q, int n) {
+    constexpr int never = 1 << 30;
+    if (n > 1024) return n > 3072 ? 15 : 12;
+    if (q != 3 && n < 64) return never;
+    return q == 4 && n <= 256 ? 12 : 8;
+}
+
 template <int Q, int QL, int MW>
 static hipError_t launch_reg(const float* W, int64_t V, int n, int iters, float* alpha, uint32_t* packed, int8_t* planes,
                              int* status_word, hipStream_t st) {
     if constexpr ((Q > 1 && MW == 1) || (Q == 3 && QL == 4)) {
-        if (iters >= (MW == 1 ? ALT_SORT_ROUNDS : ALT_SORT_ROUNDS_WAVES)) return launch_reg_form<Q, QL, MW, true>(W, V, n, iters, alpha, packed, planes, status_word, st);
+        if (iters >= sort_rounds(Q, n)) return launch_reg_form<Q, QL, MW, true>(W, V, n, iters, alpha, packed, planes, status_word, st);
     }
     return launch_reg_form<Q, QL, MW, false>(W, V, n, iters, alpha, packed, planes, status_word, st);
 }

@@ -53,6 +53,7 @@ inline std::vector<Wave>* waves;
 inline ucontext_t scheduler;
 inline bool backwards;     // the order of the waves
 inline int64_t operations;  // over lanes, of all waves so far
+inline const void* kernel;  // launched last
 inline int votes;          // of all lanes at the last barrier
 inline std::function<void()> body;
 extern unsigned char* const shared;
@@ -88,6 +89,7 @@ inline void run_lane() {
 template <typename K, typename... A>
 void launch(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t, A... args) {
     if (lds > shared_bytes) abort();
+    emu::kernel = (const void*)kernel;
     blockDim = block;
     body = [=] { kernel(args...); };
     for (unsigned b = 0; b < grid.x; ++b) {

@@ -27,6 +27,7 @@ def kernels(tmp_path_factory):
     assert r.returncode == 0, r.stderr[-2000:]
     lib = ctypes.CDLL(out)
     lib.quantize_alternating.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int] + [ctypes.c_void_p] * 3 + [ctypes.c_int, ctypes.c_void_p]
+    lib.last_kernel.restype = ctypes.c_char_p
     return lib
 
 
@@ -78,3 +79,16 @@ def test_no_sorting_for_an_element_far_below_the_levels(kernels, q, n, line):
     below, at = _run(kernels, W, q, line - 1), _run(kernels, W, q, line)
     assert np.array_equal(below[0], at[0]) and np.array_equal(below[1], at[1])
     assert abs(at[3] - below[3]) <= 8 * (1 if n <= 1024 else 2)
+
+
+@pytest.mark.parametrize("q,n,rounds", [(2, 32, None), (2, 64, 8), (2, 1024, 8), (2, 1056, None), (3, 32, 8), (3, 1024, 8), (3, 1056, 12), (3, 3072, 12),
+                                        (3, 3104, 15), (3, 4096, 15), (3, 4128, None), (4, 32, None), (4, 64, 12), (4, 256, 12), (4, 288, 8),
+                                        (4, 1024, 8), (4, 1056, None)])
+def test_short_vectors_are_sorted_only_where_they_repay_it(kernels, q, n, rounds):
+    """The number of rounds from which the form with sorted elements is launched; None: not even for 1000."""
+    W = np.tile(np.float32([0.5, -0.25, 0.25, -0.5]), n // 4)[None]
+    for iters, sorts in ((1000, rounds is not None), (rounds, True), (rounds and rounds - 1, False)):
+        if iters is not None:
+            _run(kernels, W, q, iters)
+            name = kernels.last_kernel().decode()
+            assert "alternating_reg_kernelILi%dE" % q in name and ("ELb1E" in name) == sorts, (iters, name)
