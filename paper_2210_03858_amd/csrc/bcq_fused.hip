@@ -109,7 +109,11 @@ __global__ __launch_bounds__(1024) void group_fwd_kernel(const uint32_t* __restr
                 for (int i = 0; i < TT; ++i)
                     acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(frag[f]), as_bf16x8(xf[i][f]), acc[i], 0, 0, 0);
         }
-        if (s + W < end) fetch(s + W);  // (every read of the stage has been used)
+        if (s + W < end) {  // every read of the stage has returned before its refill is asked for
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(s + W);
+        }
     }
 
     f32x4* const own = reinterpret_cast<f32x4*>(mine) + lane;  // the wave's stage is free
