@@ -233,6 +233,9 @@ def bcq_pack_transposed(packed, packed_t=None):
     K = Kw * 32
     if packed_t is None:
         packed_t = torch.empty((q, K, max(N // 32, 1)), dtype=torch.int32, device=packed.device)
+    elif N % 32 == 0 and not (packed_t.is_cuda and packed_t.is_contiguous()
+                              and packed_t.numel() * packed_t.element_size() >= q * K * (N // 32) * 4):
+        raise ValueError("packed_t must be a contiguous cuda tensor with room for %s words" % ((q, K, N // 32),))
     _check(load().bcq_pack_transposed(_ptr(packed), N, K, q, _ptr(packed_t), _stream()), "bcq_pack_transposed")
     return packed_t
 

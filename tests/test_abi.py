@@ -250,3 +250,34 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode != 0
     assert "ONE GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_transposing_into_too_small_an_output_is_refused_on_the_host(monkeypatch):
+    """The binding's own check of packed_t, without a device: tensors that say they are on one and a library that must not be called."""
+    import torch
+    from paper_2210_03858_amd import binding
+
+    class OnDevice(torch.Tensor):
+        is_cuda = True
+
+    class Library:
+        calls = 0
+
+        def bcq_pack_transposed(self, *args):
+            self.calls += 1
+            return 0
+    library = Library()
+    monkeypatch.setattr(binding, "load", lambda: library)
+    monkeypatch.setattr(binding, "_stream", lambda: None)
+    monkeypatch.setattr(binding, "_try_native", lambda *args: None)
+
+    def tensor(*shape, dtype=torch.int32):
+        return torch.zeros(shape, dtype=dtype).as_subclass(OnDevice)
+    packed = tensor(3, 64, 5)  # -> [3][160][2]
+    for wrong in (tensor(3, 160, 1), tensor(959), tensor(3, 160, 2, dtype=torch.int16), tensor(3, 2, 160).transpose(1, 2), torch.zeros((3, 160, 2), dtype=torch.int32)):
+        with pytest.raises(ValueError, match="packed_t"):
+            binding.bcq_pack_transposed(packed, wrong)
+    assert library.calls == 0
+    for right in (tensor(3, 160, 2), tensor(960), tensor(1024)):  # (any layout of the memory that the words are written to)
+        assert binding.bcq_pack_transposed(packed, right) is right
+    assert library.calls == 3

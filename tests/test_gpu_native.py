@@ -222,12 +222,25 @@ def test_quantizer_and_layouts_equal_the_python_path(monkeypatch, N, K, g, q):
     def run():
         alpha, packed, planes = bcq.bcq_quantize_grouped(W, q, g)
         assert planes is None
-        given = bcq.bcq_quantize_grouped(W, q, g, alpha=torch.zeros_like(alpha), packed=torch.zeros_like(packed),
-                                         workspace=torch.zeros(4, dtype=torch.int32, device="cuda"))
-        assert torch.equal(given[0], alpha) and torch.equal(given[1], packed)
-        out = [alpha, packed, bcq.bcq_pack_decode(packed), bcq.bcq_pack_decode(packed, torch.zeros_like(bcq.bcq_pack_decode(packed)))]
+        def given(made, call):
+            """The same result in the tensors that the call is given."""
+            own = [torch.zeros_like(t) for t in made]
+            out = call(*own)
+            for t, o, m in zip(out if isinstance(out, tuple) else (out,), own, made):
+                assert t.data_ptr() == o.data_ptr() and torch.equal(o, m)
+        given((alpha, packed), lambda a, p: bcq.bcq_quantize_grouped(W, q, g, alpha=a, packed=p,
+                                                                     workspace=torch.zeros(4, dtype=torch.int32, device="cuda")))
+        tiled = bcq.bcq_pack_decode(packed)
+        given((tiled,), lambda t: bcq.bcq_pack_decode(packed, t))
+        out = [alpha, packed, tiled]
         if N % 32 == 0:
-            out += [bcq.bcq_pack_transposed(packed), bcq.bcq_pack_transposed(packed, torch.zeros_like(bcq.bcq_pack_transposed(packed)))]
+            twin = bcq.bcq_pack_transposed(packed)
+            given((twin,), lambda t: bcq.bcq_pack_transposed(packed, t))
+            assert torch.equal(bcq.bcq_pack_transposed(packed, torch.zeros(twin.numel(), dtype=torch.int32, device="cuda")), twin.reshape(-1))
+            for wrong in (torch.zeros(twin.numel() - 1, dtype=torch.int32, device="cuda"), torch.zeros_like(twin).transpose(1, 2), torch.zeros_like(twin).cpu()):
+                with pytest.raises(ValueError):
+                    bcq.bcq_pack_transposed(packed, wrong)
+            out.append(twin)
         else:
             with pytest.raises(bcq.BcqError):
                 bcq.bcq_pack_transposed(packed)
