@@ -587,7 +587,9 @@ static hipError_t launch_group(const uint32_t* packed, const float* alpha, const
     const int stage = group_stage(T, WPL), segs = (int)((K + 128 * WPL - 1) / (128 * WPL));
     const uint32_t gw = (uint32_t)(g / 32), inverse = gw == 1 ? 0u : 0xFFFFFFFFu / gw + 1u;  // word / gw = high half of word * inverse
     const size_t lds = (size_t)p.W * stage;
-    const auto kernel = T <= 16 ? group_fwd_kernel<Q, WPL, 1> : group_fwd_kernel<Q, WPL, 2>;
+    constexpr bool one_tile = WPL == 4;  // (of tokens, as group_plan has it)
+    if (one_tile && T > 16) return hipErrorInvalidConfiguration;
+    const auto kernel = one_tile || T <= 16 ? group_fwd_kernel<Q, WPL, 1> : group_fwd_kernel<Q, WPL, one_tile ? 1 : 2>;
     static LdsLimit limit[2];
     hipError_t e = limit[T > 16].ensure((const void*)kernel, lds);
     if (e != hipSuccess) return e;
@@ -623,9 +625,11 @@ static bool one_full_round(int64_t T, int64_t N, int64_t K, int q) {
     return T <= 256 && tiles <= 512 && tiles > (q == 4 ? 384 : 320);
 }
 
-// Where one kernel is faster than expanding What and multiplying.  Up to 32 tokens always (one / two kernels, us: 32 tokens, q = 4,
-// groups of 32, of 10240 x 2592 16 / 25, of 40960 x 960 21 / 40, of 10240 x 96 3.3 / 7.2), with row-wise scales up to 128 unless the estimates below are clearly against it.
-// Row-wise scales, 129 to 384 tokens: except above 40 million weights, and with four planes above 256 tokens above 8
+// Where one kernel is faster than expanding What and multiplying.  Calls with row-wise scales, or groups of whole 512-column segments, come
+// here with more than 80 tokens (the streaming kernels take them before), those with other groups with any number.
+// Up to 32 tokens always (one / two kernels, us: 32 tokens, q = 4, groups of 32, of 10240 x 2592 16 / 25, of 40960 x 960 21 / 40, of 10240 x 96
+// 3.3 / 7.2), with row-wise scales up to 128 unless the estimates below are clearly against
+// it.  Row-wise scales, 129 to 384 tokens: except above 40 million weights, and with four planes above 256 tokens above 8
 // million, unless one_full_round, and up to 100 million, from where What no longer fits the 256 MB cache in front of HBM.  These
 // lines were set (65000 timings) against a one-kernel form of the rows and tokens that one_full_round counts; of 70 random calls in
 // their range the present form is on the side that is more than 4 % slower in 8.  With one and two planes they are early (one / two kernels,
@@ -640,11 +644,12 @@ static bool one_full_round(int64_t T, int64_t N, int64_t K, int q) {
 // Against the forms before tile_fwd_kernel, 1159 random calls of 33 to 768 tokens: 0.87 of the time, 40 more than 4 % slower, 12 of them
 // more than 8 %, worst 1.15 (140 tokens of 2720 x 2528, q = 2, 13.1 -> 15.1); no choice of route or plan would leave less than 17.
 bool fused_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
-    // layers of fewer rows than tokens have few row tiles, and no room for the sums of parts
-    if (q > 4 || T > 768 || (T > 32 && (T + 31) / 32 * 32 * K * 2 > (int64_t)mfma_fwd_workspace(N, K))) return false;
+    if (q > 4) return false;
     if (T <= 32) return true;
+    // layers of fewer rows than tokens have few row tiles, and no room for the sums of parts
+    if (T > 768 || (T + 31) / 32 * 32 * K * 2 > (int64_t)mfma_fwd_workspace(N, K)) return false;
     const int64_t work = N * K * T;
-    if (T > 32 && K > 512 && N * K > 1000000) {
+    if (K > 512 && N * K > 1000000) {
         const double one = tile_plan(T, N, K, g, q).estimate, two = two_kernel_estimate(T, N, K, q);
         if (0.9 * one > two && N * K <= 100000000) return false;
         if ((T > 384 || g != K) && 1.1 * one < two) return true;
@@ -656,7 +661,7 @@ bool fused_fwd_ok(int64_t T, int64_t N, int64_t K, int64_t g, int q) {
     }
     const bool odd = (g / 32) % 2 != 0;
     const int level = q + (odd ? 1 : 0);
-    if (odd && q > 1 && T > 32 && N * K < 1200000) return false;  // 1024 x 1024, q = 4, 64 tokens: 14 / 11
+    if (odd && q > 1 && N * K < 1200000) return false;  // 1024 x 1024, q = 4, 64 tokens: 14 / 11
     switch (level) {
         case 1: return true;
         case 2: return T <= 256 || (!odd && work <= 8000000000);

@@ -68,7 +68,7 @@ def test_every_refill_waits_for_the_reads_of_its_stage(tmp_path):
     r = subprocess.run([build._hipcc()] + flags + ["-S", "--cuda-device-only", src, "-o", out], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     bodies = re.findall(r"^(_ZN3bcq16group_fwd_kernelILi\dELi\dELi\dEE\w*):[^\n]*\n(.*?)\.Lfunc_end", open(out).read(), re.S | re.M)
-    assert len(bodies) == 24  # one to four planes, one, two and four words to a lane, one and two tiles of tokens
+    assert len(bodies) == 20  # one to four planes, one and two words to a lane with one and two tiles of tokens, four words with one
     for name, body in bodies:
         reads, refills, bad = _unguarded(body)
         assert reads >= 4 and refills >= 2 and not bad, (name, reads, refills, bad[:3])
