@@ -71,21 +71,29 @@ struct BatchPiece {  // the work of one workgroup of the main kernel
 static_assert(sizeof(BatchPiece) == 16, "table piece layout");
 
 // ---- kernels --------------------------------------------------------------------------------------------------------
-// Sets of the input gradient that a thread re-codes from one read of dy (55 blocks of 1280, q = 4, eight tokens, us: one set 21.7, two 21.0;
-// the 44 MB that it writes are 17 at half the rate of a large copy).
-constexpr int PRE_SETS = 2;
+// Sets of the input gradient that a thread re-codes from one read of dy.  As long as about all waves of one set to a thread are resident at once,
+// dy comes from the caches again and a second set only lengthens the chain; beyond, two sets save reads (55 blocks of 1280, q = 4, eight
+// tokens, us: one set 21.7, two 21.0; the 44 MB that it writes are 17 at half the rate of a large copy).  Whole calls over blocks of four layers, us, one / two
+// sets: one block of 768 to 2560 17.6 / 18.3 (q = 2, one token) to 85.5 / 86.7 (q = 4, four), 32 of 768, q = 2, one token (1920 waves) 25.7 / 27.0, 16 of
+// 1280, q = 4, eight tokens (3072) 58.9 / 60.1, q = 2, 16 tokens (3072) 43.7 / 44.5; at twice that the two are equal within the runs' own 3 %.  Three sets, of which
+// the second half of the workgroups has one, repay it earlier, eight tokens: 16 of 1280 (2304) 46.2 / 47.3, 32 of 768 (2880) 36.2 / 36.3, 16 of 2048 (3456) 83.9 / 83.1.
+static int sets_of_a_thread(uint64_t blocks, int sets, int halves) {
+    const uint64_t waves = blocks * (uint64_t)sets * (halves == 1 ? 2 : 4);
+    return sets > 1 && waves > (sets == 3 ? 3300u : 6144u) ? 2 : 1;
+}
 
 // blockIdx.x -> (layer, segment) through `map`; the loads of the map and of the layer record are uniform (scalar).
 template <int MODE>
 __global__ __launch_bounds__(256) void quant_act_batched_kernel(const BatchLayerDev* __restrict__ layers,
                                                                 const uint2* __restrict__ map,
-                                                                unsigned char* __restrict__ ws, int64_t T, int halves, int sets) {
+                                                                unsigned char* __restrict__ ws, int64_t T, int halves, int sets,
+                                                                int per) {
     const uint2 m = map[blockIdx.x];
     const BatchLayerDev& L = layers[m.x];
     // contraction length = 32 cw of the plane matrix (K for the canonical planes, N for the twin)
     quant_act_body<MODE>((const BCQ_GLOBAL bf16_t*)L.act, (const BCQ_GLOBAL float*)L.alpha, T, L.cw * 32, L.segs_act, halves, 0, m.y,
-                         ws + L.xq_off, ws + L.sq_off, (size_t)L.xq_plane, (size_t)L.sq_plane, 1, L.seg_mul, blockIdx.y * PRE_SETS,
-                         min(sets, (int)(blockIdx.y + 1) * PRE_SETS));
+                         ws + L.xq_off, ws + L.sq_off, (size_t)L.xq_plane, (size_t)L.sq_plane, 1, L.seg_mul, blockIdx.y * per,
+                         min(sets, (int)(blockIdx.y + 1) * per));
 }
 
 // ---------------------------------------------------------------------------------------------------------------------
@@ -666,9 +674,10 @@ static bcq_status batch_check(int op, const bcq_batch_layer* layers, int64_t cou
 
 template <int MODE>
 static hipError_t launch_pre(const BatchHeader& h, const unsigned char* dev, unsigned char* ws, hipStream_t st) {
-    BCQ_LAUNCH((quant_act_batched_kernel<MODE>), dim3(h.pre_blocks, (h.pre_sets + PRE_SETS - 1) / PRE_SETS), dim3(h.halves == 1 ? 128 : 256), 0, st,
+    const int sets = (int)h.pre_sets, per = sets_of_a_thread(h.pre_blocks, sets, h.halves);
+    BCQ_LAUNCH((quant_act_batched_kernel<MODE>), dim3(h.pre_blocks, (unsigned)((sets + per - 1) / per)), dim3(h.halves == 1 ? 128 : 256), 0, st,
                        reinterpret_cast<const BatchLayerDev*>(dev + h.layers_off),
-                       reinterpret_cast<const uint2*>(dev + h.pre_map_off), ws, (int64_t)h.T, h.halves, (int)h.pre_sets);
+                       reinterpret_cast<const uint2*>(dev + h.pre_map_off), ws, (int64_t)h.T, h.halves, sets, per);
     return hipGetLastError();
 }
 

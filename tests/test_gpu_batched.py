@@ -187,3 +187,24 @@ def test_batched_errors(bcq):
     with pytest.raises(bcq.BcqError) as e:
         bcq.bcq_linear_batched(plan)
     assert e.value.status == 5
+
+
+@pytest.mark.parametrize("q,T,blocks", [(2, 8, 1536), (2, 3, 1537), (3, 8, 550), (3, 1, 551), (3, 16, 276), (4, 8, 768), (4, 5, 769), (4, 16, 385)])
+def test_input_gradient_does_not_depend_on_the_sets_of_a_thread(bcq, q, T, blocks):
+    """At and beyond the line (`blocks` segments of dy over all layers) from which a thread re-codes two sets: a layer's result is bit for bit that
+    of a batch of its own, in which a thread re-codes one."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(blocks)
+    rows = [512 * (blocks // 8)] * 7 + [512 * (blocks - blocks // 8 * 7) - 32 * 3]
+    layers = []
+    for N in rows:
+        packed = torch.randint(-2 ** 31, 2 ** 31 - 1, (q, N, 1), dtype=torch.int32, device="cuda", generator=gen)
+        layers.append(dict(N=N, K=32, tiled_t=bcq.bcq_pack_decode(bcq.bcq_pack_transposed(packed)), alpha=torch.rand((q, N), device="cuda", generator=gen),
+                           dy=torch.randn((T, N), device="cuda", generator=gen).bfloat16(), dx=torch.full((T, 32), float("nan"), dtype=torch.bfloat16, device="cuda")))
+    bcq.bcq_linear_batched(bcq.batch_plan(OP_DX, layers, T, q))
+    together = [L["dx"].clone() for L in layers]
+    for L, dx in zip(layers, together):
+        L["dx"].fill_(float("nan"))
+        bcq.bcq_linear_batched(bcq.batch_plan(OP_DX, [dict(L)], T, q))
+        assert not dx.isnan().any() and torch.equal(L["dx"], dx), (q, T, L["N"])
