@@ -192,7 +192,9 @@ constexpr int tile_lds_bytes() { return KG * tile_stages<TM, KG>() * TM * 16 * 2
 // lanes hands every lane the one word of each unit whose 32 columns it contracts over: slice f of a unit is columns
 // 32 h + 8 f .. + 7 of lane row h on both sides.
 //
-// What bounds it: vector operations.  Expanding costs 22 (q = 1) to 110 (q = 4) of them per 32 weights, 4 cycles each, repeated for
+// What bounds it: reading the activations from LDS.  With 16 rows to a wave every matrix instruction takes a fragment of its own, 1 KiB at the 145 B/ns
+// that a compute unit's LDS sustains: 256 tokens, q = 4, 22.6 of 36 us for 10240 x 2560, 17.4 of 24 for 7680 x 2560.  Then start and end, and vector
+// operations, 0.3 to 0.5 of the cycles (matrix instructions 0.2).  Expanding costs 22 (q = 1) to 110 (q = 4) of them per 32 weights, 4 cycles each, repeated for
 // every 16 TM tokens, and beside a 16-cycle matrix instruction only two are free (7.2 ns alone and with two, 10.5 with four, 17 with
 // eight).  Against activations re-ordered in memory and read from L2 by every 32 rows (us, with that kernel's re-ordering): 256 tokens,
 // q = 4, of 7680 x 2560 27 -> 22, 2560 x 10240 44 -> 34, 10240 x 2560 35 -> 33; 149 tokens of 2560 x 10240, q = 1, 38 -> 21; groups
