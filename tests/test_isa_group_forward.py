@@ -50,7 +50,7 @@ def _unguarded(body):
     return reads, len(refills), [line for n, at, line in refills if not state_at(n, at, safe[n])]
 
 
-def test_the_checker_sees_a_path_without_the_wait():
+def test_a_path_without_the_wait_is_seen():
     wait = [";;#ASMSTART", "s_waitcnt lgkmcnt(0)", ";;#ASMEND"]
     first, loop = ["buffer_load_dwordx4 v1, s[0:3], s4 offen lds"], [".LBB0_1:", "ds_read_b128 v[2:5], v6"]
     refill = ["buffer_load_dwordx4 v7, s[0:3], s4 offen lds", "s_cbranch_scc1 .LBB0_1", "s_endpgm"]
